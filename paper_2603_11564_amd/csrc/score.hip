@@ -216,16 +216,20 @@ __global__ void score_chunk_prefix_kernel(const int32_t* cu_seqlens, int32_t* cu
 }
 
 // Merge the per-chunk (reference, sum) pairs of a row: lse2 = log2 sum_c z_c 2^(ref_c).
-__global__ void score_combine_kernel(ScoreParams p) {
-  const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t total = (int64_t)p.n_layers * p.batch * p.n_q_heads * p.n_pseudo;
-  if (gid >= total) return;
-  const int i = (int)(gid % p.n_pseudo);
-  const int hq = (int)((gid / p.n_pseudo) % p.n_q_heads);
-  const int b = (int)((gid / ((int64_t)p.n_pseudo * p.n_q_heads)) % p.batch);
-  const int layer = (int)(gid / ((int64_t)p.n_pseudo * p.n_q_heads * p.batch));
-  const int kv = hq / p.group;
-  const int row = (hq - kv * p.group) * p.n_pseudo + i;
+//
+// A workgroup takes 64 rows of one (layer, sequence, KV head), a lane per row, and its waves share out the chunks in
+// runs of kCombineRun, whose loads are all in flight together.  What bounds it is latency: one thread walking a row's
+// chunks alone, twice, was a chain of 2 x chunks loads (one layer, 8 heads, 128 rows, 8191 keys = 64 chunks: 37 us next
+// to two score passes of 13 us; the whole dapq_score call 60 us then, 26 us now).
+// The sum does not depend on how many waves share the work: run r belongs to class r % kCombineClasses, a class is
+// summed in run order, chunk by chunk, and the classes are added in class order (up to kCombineRun chunks: plain chunk
+// order, which is what score_fused_kernel does).
+constexpr int kCombineRun = 8, kCombineClasses = 16;
+__global__ __launch_bounds__(64 * kCombineClasses) void score_combine_kernel(ScoreParams p, int row_tiles) {
+  __shared__ float lds_max[kCombineClasses][64], lds_sum[kCombineClasses][64];
+  const int lane = threadIdx.x & 63, wave = uniform_i32((int)(threadIdx.x >> 6)), waves = (int)(blockDim.x >> 6);
+  const int b = (int)(blockIdx.x / row_tiles), row = (int)(blockIdx.x - b * row_tiles) * 64 + lane;
+  const int layer = (int)(blockIdx.y / p.n_kv_heads), kv = (int)(blockIdx.y - layer * p.n_kv_heads);
   int c0, c1;
   if (p.cu_seqlens == nullptr) {
     const int L = (int)(p.total_tokens / p.batch);
@@ -236,18 +240,52 @@ __global__ void score_combine_kernel(ScoreParams p) {
     c0 = p.cu_chunks[b];
     c1 = p.cu_chunks[b + 1];
   }
-  const float2* src = p.parts + ((int64_t)(layer * p.n_kv_heads + kv) * p.max_chunks) * p.rows_pad + row;
-  float m = -INFINITY;
-  for (int64_t e = c0; e < c1; ++e) {
-    const float2 v = src[e * p.rows_pad];
-    if (v.y > 0.0f) m = fmaxf(m, v.x + log2f(v.y));
+  const int n = c1 - c0, runs = (n + kCombineRun - 1) / kCombineRun;
+  const float2* src = p.parts + ((int64_t)blockIdx.y * p.max_chunks + c0) * p.rows_pad + (row < p.rows ? row : p.rows - 1);
+  // t[i] = log2 of the sum of chunk run * kCombineRun + i, -inf for chunks without one
+  auto load_run = [&](int run, float (&t)[kCombineRun]) {
+    float2 v[kCombineRun];
+#pragma unroll
+    for (int i = 0; i < kCombineRun; ++i) {
+      const int c = run * kCombineRun + i;
+      v[i] = src[(int64_t)(c < n ? c : n - 1) * p.rows_pad];
+    }
+#pragma unroll
+    for (int i = 0; i < kCombineRun; ++i)
+      t[i] = run * kCombineRun + i < n && v[i].y > 0.0f ? v[i].x + log2f(v[i].y) : -INFINITY;
+  };
+  float t[kCombineRun], m = -INFINITY;
+  for (int run = wave; run < runs; run += waves) {
+    load_run(run, t);
+#pragma unroll
+    for (int i = 0; i < kCombineRun; ++i) m = fmaxf(m, t[i]);
   }
+  if (waves > 1) {
+    lds_max[wave][lane] = m;
+    __syncthreads();
+    for (int w = 0; w < waves; ++w) m = fmaxf(m, lds_max[w][lane]);
+  }
+  const bool one_run = wave + waves >= runs;  // its run is still in t
   float s = 0.0f;
-  for (int64_t e = c0; e < c1; ++e) {
-    const float2 v = src[e * p.rows_pad];
-    if (v.y > 0.0f) s += exp2f(v.x + log2f(v.y) - m);
+  for (int k = wave; k < kCombineClasses && k < runs; k += waves) {
+    float sum = 0.0f;
+    for (int run = k; run < runs; run += kCombineClasses) {
+      if (!one_run) load_run(run, t);
+#pragma unroll
+      for (int i = 0; i < kCombineRun; ++i) sum += exp2f(t[i] - m);
+    }
+    if (waves > 1) lds_sum[k][lane] = sum;
+    else s += sum;
   }
-  p.lse2[gid] = (s > 0.0f) ? m + log2f(s) : 0.0f;
+  if (waves > 1) {
+    __syncthreads();
+    if (wave != 0) return;
+    for (int k = 0; k < kCombineClasses && k < runs; ++k) s += lds_sum[k][lane];
+  }
+  if (row >= p.rows) return;
+  // (m is -inf, and s not a number, only where no chunk has a sum)
+  const int64_t first = (((int64_t)layer * p.batch + b) * p.n_q_heads + (int64_t)kv * p.group) * p.n_pseudo;
+  p.lse2[first + row] = (s > 0.0f) ? m + log2f(s) : 0.0f;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1078,8 +1116,12 @@ int launch_stats(const dapq_shape* s, const ScorePlan& plan, ScoreParams p, hipS
   else DAPQ_LAUNCH_W1(8);
 #undef DAPQ_LAUNCH_W1
   DAPQ_HIP_LAUNCH_CHECK("score_wave_pass1_kernel");
-  const int64_t rows_total = (int64_t)s->n_layers * s->batch * s->n_q_heads * s->n_pseudo;
-  hipLaunchKernelGGL(score_combine_kernel, dim3((unsigned)((rows_total + 255) / 256)), dim3(256), 0, stream, p);
+  // as many waves per 64 rows as the (mean) sequence has runs of chunks
+  const int64_t chunks_per_seq = (plan.max_chunks + s->batch - 1) / s->batch, row_tiles = (plan.rows + 63) / 64;
+  int64_t combine_waves = (chunks_per_seq + kCombineRun - 1) / kCombineRun;
+  combine_waves = combine_waves < 1 ? 1 : (combine_waves > kCombineClasses ? kCombineClasses : combine_waves);
+  hipLaunchKernelGGL(score_combine_kernel, dim3((unsigned)(row_tiles * s->batch), (unsigned)(s->n_layers * s->n_kv_heads)),
+                     dim3((unsigned)(64 * combine_waves)), 0, stream, p, (int)row_tiles);
   DAPQ_HIP_LAUNCH_CHECK("score_combine_kernel");
   return DAPQ_OK;
 }
