@@ -2,30 +2,46 @@
 // uses only the compressed cache): out = softmax(q K_c^T / sqrt(d_k)) V_c per query head, over the first
 // count rows of the KV head's compact cache as dapq_gather wrote it.
 //
-// One workgroup of 1024 threads per (layer, sequence, KV head); it serves the query heads of the group
-// four at a time, so the cache rows are read once per four query heads.  The cache of a head is at
-// most a few thousand rows: the step is a matrix-vector product bound by reading K_c and V_c, and with
-// one workgroup per head what matters is how many rows a compute unit has in flight: sixteen waves, one
-// row per thread in phase 1, eight rows per thread and trip in phase 3.
-//   phase 1  a thread takes cache rows in turn: logits = q_h . k for the four heads (bf16 products, fp32
-//            accumulation), kept in LDS
-//   phase 2  weights 2^(c*logit - max) in LDS, their sums
-//   phase 3  a thread owns two channels and a sixteenth of the rows: acc_h += weight_h * v, rows of V read
-//            as contiguous 256-byte lines by each wave; the sixteen partial sums meet in LDS
+// One workgroup per (layer, sequence, KV head); its waves take tiles of 32 cache rows in turn and meet once, at the end.
+// What bounds a call is how fast the compute units in use can take in bytes and how little stands before and after: a
+// call of one layer has only a few heads, each 0.5 MB, and one compute unit takes about 20 bytes a clock from beyond its
+// L2 and 54 from L2.  So there is one sweep over K_c and V_c together, the loads of a tile are issued as soon as the
+// registers or the LDS slot of an earlier one are spent (the first ones before the row count is known), every load
+// instruction covers whole rows (K_c goes through LDS for that: loading the operand layout straight from memory,
+// consecutive lanes in consecutive rows, runs at 15 bytes a clock), both products run on v_mfma_f32_16x16x32_bf16,
+// and where the heads alone would leave most of the chip idle the value channels of a head are dealt to 2 or 4
+// workgroups ("slices"): each reads all of K_c (they start a slice of the tiles apart) but only its share of V_c.
+//   logits   D[key][column] = K_c tile (A operand, 16 keys x 32 channels per instruction) x q (B operand).  The columns
+//            are 4 query heads x 4 parts: column 4 * part + head.
+//   weights  2^(c * logit - ref) in fp32.  ref is the largest logit of the wave's first tile; it only moves (and the
+//            sums are rescaled) if a later logit lies more than 2^kDecodeHeadroom above it.
+//   output   D[column][channel] += weights (A) x V_c (B).  A weight enters as three bf16 numbers whose sum it is, bit
+//            for bit (8 + 8 + 8 bits of its significand): part 0 carries the first, part 1 the second, part 2 the third,
+//            so one instruction multiplies all three with V_c and nothing is lost against fp32 weights (part 3 is not
+//            used).  A lane's four logits of a tile are four keys of one column, which is how the A operand wants
+//            them once the keys of an instruction are counted tile by tile; V_c follows: a lane loads the same
+//            piece (CPL channels) of 8 rows and transposes the 8 x CPL block in its own registers, and instruction
+//            j of a tile gives the channels CPL * n + j.
+// Measured (32 query / 8 KV heads, one layer): 983 rows, 1 sequence 24.9 -> 7.3 us (of which the launch path of the host is
+// the larger part); 64..256 rows, 50 sequences 38.9 -> 10.8 us (3.1 TB/s); 983 rows, 64 sequences 74.9 -> 45.6 us
+// (5.6 TB/s); 8 query heads per KV head, 4096 rows, 1 sequence 140.7 -> 19.9 us.  (Before: vector products, sixteen
+// waves per head, logits and weights through LDS, the cache read twice for more than 4 query heads.)
 #include <math.h>
-
-#include <type_traits>
 
 #include "dapq_internal.h"
 
 namespace dapq {
 namespace {
 
-constexpr int kDecodeThreads = 1024;
-constexpr int kDecodeWaves = kDecodeThreads / 64;
-constexpr int kDecodeMaxRows = 8192;  // logits of four query heads in LDS (128 KB)
-constexpr int kDecodeHeads = 4;       // query heads served per sweep over the cache
-constexpr int kDecodeTrip = 8;        // value rows a wave has in flight in phase 3 (4: 7 % slower, 16: 2 %, 32: 15 %)
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+
+constexpr int kDecodeMaxRows = 8192;
+constexpr int kDecodeTile = 32;           // cache rows a wave takes at a time
+constexpr int kDecodeParts = 3;           // bf16 numbers that make up a weight
+constexpr float kDecodeHeadroom = 60.0f;  // binades a logit may lie above the reference
 
 struct DecodeParams {
   const uint16_t* q;        // [layer][seq][Hq][d]
@@ -37,153 +53,292 @@ struct DecodeParams {
   float c;                  // scale * log2(e)
 };
 
-__device__ __forceinline__ float bf16_lo(uint32_t u) { return __uint_as_float(u << 16); }
-__device__ __forceinline__ float bf16_hi(uint32_t u) { return __uint_as_float(u & 0xFFFF0000u); }
+constexpr int kDecodeSlotBytes = kDecodeTile * kHeadDim * 2;  // one tile of K_c
+constexpr int kDecodeSlots = 2;                               // per wave
+constexpr int decode_wave_bytes(int ht) { return kDecodeSlots * kDecodeSlotBytes + ht * 4 * kHeadDim * 2; }  // and its queries
 
-// Maximum or sum over the workgroup of one value per head; red: [kDecodeWaves][kDecodeHeads].
-template <bool IS_MAX>
-__device__ __forceinline__ void block_reduce(float (&v)[kDecodeHeads], float* red) {
+// K_c and V_c of a head through buffer descriptors whose range check returns zeros for rows past the budget.
+struct DecodeSource {
+  __amdgpu_buffer_rsrc_t k, v;
+  unsigned k_off[4], v_off;
+};
+// One wave moves a tile of K_c into an LDS slot, 1 KB (4 rows) per transfer, rows 256 B apart, the 16-byte chunks of a row
+// XOR-swizzled by the row so that the operand reads are free of bank conflicts.
+__device__ __forceinline__ void load_k(char* slot, const DecodeSource& src, int row0) {
 #pragma unroll
-  for (int h = 0; h < kDecodeHeads; ++h) {
+  for (int i = 0; i < 8; ++i) {
+    const unsigned off = src.k_off[i & 3] + (unsigned)(row0 + 16 * (i >> 2)) * kHeadDim * 2;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(src.k, (__attribute__((address_space(3))) void*)(slot + i * 1024), 16, (int)off, 0,
+                                             0, 0);
+  }
+}
+// A tile of a slice of V_c as it sits in the registers of lane 16 * kg + n: v[e] = channels CPL * n .. + CPL of the slice of
+// row 16 * (e / 4) + 4 * kg + e % 4.
+template <int CPL>
+__device__ __forceinline__ void load_v(unsigned (&v)[8][CPL / 2], const DecodeSource& src, int row0) {
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-      const float o = __shfl_xor(v[h], d, 64);
-      v[h] = IS_MAX ? fmaxf(v[h], o) : v[h] + o;
+  for (int e = 0; e < 8; ++e) {
+    const unsigned off = src.v_off + (unsigned)(row0 + 16 * (e >> 2)) * kHeadDim * 2 + (e & 3) * kHeadDim * 2;
+    if constexpr (CPL == 8) {
+      const u32x4 u = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(src.v, (int)off, 0, 0));
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[e][i] = u[i];
+    } else if constexpr (CPL == 4) {
+      const u32x2 u = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(src.v, (int)off, 0, 0));
+      v[e][0] = u[0];
+      v[e][1] = u[1];
+    } else {
+      v[e][0] = __builtin_bit_cast(unsigned, __builtin_amdgcn_raw_buffer_load_b32(src.v, (int)off, 0, 0));
     }
-  }
-  const int wave = threadIdx.x >> 6;
-  __syncthreads();  // red may still be read from the previous reduction
-  if ((threadIdx.x & 63) == 0) {
-#pragma unroll
-    for (int h = 0; h < kDecodeHeads; ++h) red[wave * kDecodeHeads + h] = v[h];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int h = 0; h < kDecodeHeads; ++h) {
-    float r = red[h];
-#pragma unroll
-    for (int w = 1; w < kDecodeWaves; ++w) r = IS_MAX ? fmaxf(r, red[w * kDecodeHeads + h]) : r + red[w * kDecodeHeads + h];
-    v[h] = r;
   }
 }
 
-__global__ __launch_bounds__(kDecodeThreads) void decode_attention_kernel(DecodeParams p) {
-  extern __shared__ float lds[];
-  float* qs = lds;                                  // [4][128] the queries in fp32
-  float* red = qs + kDecodeHeads * kHeadDim;                   // [waves][4]
-  float* w = red + kDecodeWaves * kDecodeHeads;                // [4][budget] logits, then weights
-  float* part = w;                                             // [waves][4][128] partial outputs, once the weights are spent
-  const int tid = threadIdx.x;
-  const int kv = blockIdx.x, seq = blockIdx.y, layer = blockIdx.z;
-  const int g = p.n_q_heads / p.n_kv_heads;
-  const int64_t head = ((int64_t)layer * gridDim.y + seq) * p.n_kv_heads + kv;
-  int n = p.count[head];
-  n = n < 0 ? 0 : (n > p.budget ? p.budget : n);
-  const uint16_t* kc = p.k_cache + head * p.budget * kHeadDim;
-  const uint16_t* vc = p.v_cache + head * p.budget * kHeadDim;
+// Keeps the loads before it before the loads after it: the waits count loads in the order they were issued.
+__device__ __forceinline__ void keep_order() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
 
-  for (int h0 = 0; h0 < g; h0 += kDecodeHeads) {
-    const int nh = g - h0 < kDecodeHeads ? g - h0 : kDecodeHeads;  // query heads of this sweep
-    const int64_t qrow0 = ((int64_t)layer * gridDim.y + seq) * p.n_q_heads + (int64_t)kv * g + h0;
-    if (n == 0) {  // an empty cache attends to nothing
-      for (int e = tid; e < nh * kHeadDim; e += kDecodeThreads) p.out[qrow0 * kHeadDim + e] = 0.0f;
+// HT tiles of 4 query heads per sweep over the cache, CPL channels per lane (16 * CPL of the 128 per workgroup).
+template <int HT, int CPL, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, 2) void decode_attention_kernel(DecodeParams p) {
+  extern __shared__ char lds[];  // [waves]: kDecodeSlots tiles of K_c, the queries; at the end weighted sums, references, sums of weights
+  constexpr int kHeads = 4 * HT, kChannels = 16 * CPL, kSlices = kHeadDim / kChannels, kThreads = 64 * WAVES;
+  static_assert((kDecodeParts * kHeads * kChannels + 2 * kHeads) * 4 <= kDecodeSlots * kDecodeSlotBytes,
+                "what a wave leaves at the end fits where its tiles were");
+  const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, kg = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  constexpr int kWaveBytes = decode_wave_bytes(HT);
+  char* ring = lds + wave * kWaveBytes;
+  const int slice = blockIdx.y;
+  const int g = p.n_q_heads / p.n_kv_heads;
+  const int64_t head = blockIdx.x;  // (layer * batch + seq) * Hkv + kv
+  DecodeSource src;
+  src.k = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p.k_cache + head * p.budget * kHeadDim), 0,
+                                            p.budget * kHeadDim * 2, 0x00020000);
+  src.v = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p.v_cache + head * p.budget * kHeadDim), 0,
+                                            p.budget * kHeadDim * 2, 0x00020000);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) src.k_off[j] = (unsigned)((4 * j + kg) * kHeadDim * 2 + ((n ^ kg) ^ (4 * j)) * 16);
+  src.v_off = (unsigned)(4 * kg * kHeadDim * 2 + (slice * kChannels + n * CPL) * 2);
+  // the part of a weight that this lane's column stands for: what is left once the leading 8 bits were taken off n / 4 times
+  const unsigned mask1 = n >= 4 ? 0xFFFF0000u : 0u, mask2 = n >= 8 ? 0xFFFF0000u : 0u;
+  // tile number i of this workgroup: the slices of a head start a slice apart
+  int tiles = (p.budget + kDecodeTile - 1) / kDecodeTile;
+  auto row_of = [&](int i) {
+    int t = i + slice * tiles / kSlices;
+    t = t < tiles ? t : t - tiles;
+    return t * kDecodeTile;
+  };
+  int rows = p.count[head];
+
+  for (int h0 = 0; h0 < g; h0 += kHeads) {
+    const int nh = g - h0 < kHeads ? g - h0 : kHeads;  // query heads of this sweep
+    const int64_t qrow0 = head * g + h0;
+    // the queries come in whole rows too: lane l has piece l % 16 of query head l / 16 of a head tile
+    u32x4 qrow[HT];
+#pragma unroll
+    for (int t = 0; t < HT; ++t) {
+      const int h = 4 * t + kg;
+      __builtin_memcpy(&qrow[t], p.q + (qrow0 + (h < nh ? h : nh - 1)) * kHeadDim + 8 * n, 16);  // (q_decode may be unaligned)
+    }
+    keep_order();
+    // the first tiles are on their way before the row count is known (rows past the count are inside the cache all the same)
+    unsigned vt[8][CPL / 2];
+    auto first_loads = [&]() {
+      load_k(ring, src, row_of(wave));
+      load_k(ring + kDecodeSlotBytes, src, row_of(wave + WAVES));
+      keep_order();
+      load_v<CPL>(vt, src, row_of(wave));
+      keep_order();
+    };
+    first_loads();
+    u32x4* qs = reinterpret_cast<u32x4*>(ring + kDecodeSlots * kDecodeSlotBytes);
+#pragma unroll
+    for (int t = 0; t < HT; ++t) qs[t * 64 + kg * 16 + (n ^ kg)] = qrow[t];  // (swizzled like the tiles, by the head)
+    bf16x8 qf[HT][4];
+#pragma unroll
+    for (int t = 0; t < HT; ++t)
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+        qf[t][s] = __builtin_bit_cast(bf16x8, qs[t * 64 + (n & 3) * 16 + ((4 * s + kg) ^ (n & 3))]);
+    if (h0 == 0) {
+      rows = __builtin_amdgcn_readfirstlane(rows);
+      rows = rows < 0 ? 0 : (rows > p.budget ? p.budget : rows);
+      const int filled = (rows + kDecodeTile - 1) / kDecodeTile;
+      if (filled != tiles) {
+        tiles = filled;
+        if (kSlices > 1) {  // the slices start elsewhere
+          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+          first_loads();
+        }
+      }
+    }
+    if (rows == 0) {  // an empty cache attends to nothing
+      for (int e = tid; e < nh * kChannels; e += kThreads)
+        p.out[(qrow0 + e / kChannels) * kHeadDim + slice * kChannels + e % kChannels] = 0.0f;
       continue;
     }
-    __syncthreads();  // the previous sweep is done with qs, w and part
-    for (int e = tid; e < kDecodeHeads * kHeadDim; e += kDecodeThreads)
-      qs[e] = e < nh * kHeadDim ? __uint_as_float((uint32_t)p.q[qrow0 * kHeadDim + e] << 16) : 0.0f;
-    __syncthreads();
+    f32x4 acc[HT][CPL];
+    float ref[HT], sum[HT];
+#pragma unroll
+    for (int t = 0; t < HT; ++t) {
+#pragma unroll
+      for (int j = 0; j < CPL; ++j) acc[t][j] = {0.0f, 0.0f, 0.0f, 0.0f};
+      ref[t] = -INFINITY;
+      sum[t] = 0.0f;
+    }
 
-    // phase 1: logits
-    float mx[kDecodeHeads];
+    int slot = 0;
+    for (int i = wave; i < tiles; i += WAVES) {
+      const int row0 = row_of(i);
+      const bool partial = row0 + kDecodeTile > rows;
+      // in flight, oldest first: K_c of this tile, K_c of the next one, V_c of this tile (8 loads each)
+      asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+      const u32x4* kt = reinterpret_cast<const u32x4*>(ring + slot * kDecodeSlotBytes);
+      bf16x8 kf[2][4];
 #pragma unroll
-    for (int h = 0; h < kDecodeHeads; ++h) mx[h] = -INFINITY;
-    for (int j = tid; j < n; j += kDecodeThreads) {
-      const uint4* row = reinterpret_cast<const uint4*>(kc + (int64_t)j * kHeadDim);
-      float acc[kDecodeHeads] = {0.0f, 0.0f, 0.0f, 0.0f};
+      for (int hf = 0; hf < 2; ++hf)
 #pragma unroll
-      for (int ch = 0; ch < 16; ++ch) {
-        const uint4 u = row[ch];
-        const float kx[8] = {bf16_lo(u.x), bf16_hi(u.x), bf16_lo(u.y), bf16_hi(u.y),
-                             bf16_lo(u.z), bf16_hi(u.z), bf16_lo(u.w), bf16_hi(u.w)};
+        for (int s = 0; s < 4; ++s) kf[hf][s] = __builtin_bit_cast(bf16x8, kt[(16 * hf + n) * 16 + ((4 * s + kg) ^ n)]);
+      float xs[HT][8];
 #pragma unroll
-        for (int h = 0; h < kDecodeHeads; ++h) {
-          const float* qq = qs + h * kHeadDim + ch * 8;
+      for (int t = 0; t < HT; ++t) {
 #pragma unroll
-          for (int e = 0; e < 8; ++e) acc[h] = fmaf(kx[e], qq[e], acc[h]);
+        for (int hf = 0; hf < 2; ++hf) {
+          f32x4 d = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+          for (int s = 0; s < 4; ++s) d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[hf][s], qf[t][s], d, 0, 0, 0);
+#pragma unroll
+          for (int v = 0; v < 4; ++v) xs[t][4 * hf + v] = d[v];
         }
       }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the tile is out of its slot before that is refilled
+      load_k(ring + slot * kDecodeSlotBytes, src, i + 2 * WAVES < tiles ? row_of(i + 2 * WAVES) : kDecodeMaxRows);
+      slot ^= 1;
+      keep_order();
+      u32x4 pa[HT];  // the weights as A operand
 #pragma unroll
-      for (int h = 0; h < kDecodeHeads; ++h) {
-        const float l = acc[h] * p.c;
-        w[h * p.budget + j] = l;
-        mx[h] = fmaxf(mx[h], l);
-      }
-    }
-    block_reduce<true>(mx, red);
-
-    // phase 2: weights and their sums
-    float sum[kDecodeHeads] = {0.0f, 0.0f, 0.0f, 0.0f};
-    for (int j = tid; j < n; j += kDecodeThreads) {
+      for (int t = 0; t < HT; ++t) {
+        float(&x)[8] = xs[t];
+        if (partial) {
 #pragma unroll
-      for (int h = 0; h < kDecodeHeads; ++h) {
-        const float e = exp2f(w[h * p.budget + j] - mx[h]);
-        w[h * p.budget + j] = e;
-        sum[h] += e;
-      }
-    }
-    block_reduce<false>(sum, red);  // its barriers also publish the weights
-
-    // phase 3: weighted sums of the value rows; a wave takes every kDecodeWaves-th row, kDecodeTrip rows per trip
-    const int c2 = tid & 63, part_id = tid >> 6;
-    float a0[kDecodeHeads] = {0.0f, 0.0f, 0.0f, 0.0f}, a1[kDecodeHeads] = {0.0f, 0.0f, 0.0f, 0.0f};
-    const uint32_t* vcol = reinterpret_cast<const uint32_t*>(vc) + c2;
-    int j = part_id;
-    auto rows_per_trip = [&](auto trip) {  // `trip` value rows of this wave in flight at a time
-      constexpr int kTrip = decltype(trip)::value;
-      for (; j + (kTrip - 1) * kDecodeWaves < n; j += kTrip * kDecodeWaves) {
-        uint32_t u[kTrip];
+          for (int e = 0; e < 8; ++e)
+            if (row0 + 16 * (e >> 2) + 4 * kg + (e & 3) >= rows) x[e] = -INFINITY;
+        }
+        float m = x[0];
 #pragma unroll
-        for (int r = 0; r < kTrip; ++r) u[r] = vcol[(int64_t)(j + r * kDecodeWaves) * (kHeadDim / 2)];
+        for (int e = 1; e < 8; ++e) m = fmaxf(m, x[e]);
+        m *= p.c;
+        if (__any(m > ref[t] + kDecodeHeadroom)) {  // (always for the first tile, whose reference is -inf)
+          m = fmaxf(m, __shfl_xor(m, 16, 64));
+          m = fmaxf(m, __shfl_xor(m, 32, 64));
+          const float moved = fmaxf(ref[t], m);
+          const float f = __builtin_amdgcn_exp2f(ref[t] - moved);
+          ref[t] = moved;
+          sum[t] *= f;
 #pragma unroll
-        for (int r = 0; r < kTrip; ++r) {
-          const float v0 = bf16_lo(u[r]), v1 = bf16_hi(u[r]);
+          for (int h = 0; h < 4; ++h) {
+            const float fh = __shfl(f, h, 64);  // column h belongs to head h; row h of every part does too
 #pragma unroll
-          for (int h = 0; h < kDecodeHeads; ++h) {
-            const float e = w[h * p.budget + j + r * kDecodeWaves];
-            a0[h] = fmaf(e, v0, a0[h]);
-            a1[h] = fmaf(e, v1, a1[h]);
+            for (int j = 0; j < CPL; ++j) acc[t][j][h] *= fh;
           }
         }
-      }
-    };
-    rows_per_trip(std::integral_constant<int, kDecodeTrip>{});
-    rows_per_trip(std::integral_constant<int, 4>{});
-    for (; j < n; j += kDecodeWaves) {
-      const uint32_t u = vcol[(int64_t)j * (kHeadDim / 2)];
-      const float v0 = bf16_lo(u), v1 = bf16_hi(u);
+        unsigned w[8];
 #pragma unroll
-      for (int h = 0; h < kDecodeHeads; ++h) {
-        const float e = w[h * p.budget + j];
-        a0[h] = fmaf(e, v0, a0[h]);
-        a1[h] = fmaf(e, v1, a1[h]);
+        for (int e = 0; e < 8; ++e) {
+          const float y = __builtin_amdgcn_exp2f(fmaf(x[e], p.c, -ref[t]));
+          sum[t] += y;
+          const float y1 = y - __uint_as_float(__float_as_uint(y) & mask1);
+          const float y2 = y1 - __uint_as_float(__float_as_uint(y1) & mask2);
+          w[e] = __float_as_uint(y2);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) pa[t][e] = __builtin_amdgcn_perm(w[2 * e + 1], w[2 * e], 0x07060302u);
       }
+      if (partial) {  // what lies past the count may be anything: 0 times it must be 0
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (row0 + 16 * (e >> 2) + 4 * kg + (e & 3) >= rows) {
+#pragma unroll
+            for (int j = 0; j < CPL / 2; ++j) vt[e][j] = 0u;
+          }
+      }
+#pragma unroll
+      for (int j = 0; j < CPL; ++j) {  // channels CPL * n + j of the slice
+        u32x4 vb;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          vb[e] = __builtin_amdgcn_perm(vt[2 * e + 1][j >> 1], vt[2 * e][j >> 1], (j & 1) ? 0x07060302u : 0x05040100u);
+#pragma unroll
+        for (int t = 0; t < HT; ++t)
+          acc[t][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, pa[t]), __builtin_bit_cast(bf16x8, vb),
+                                                             acc[t][j], 0, 0, 0);
+      }
+      load_v<CPL>(vt, src, i + WAVES < tiles ? row_of(i + WAVES) : kDecodeMaxRows);  // (past the end: fetches nothing)
+      keep_order();
     }
-    __syncthreads();  // every wave is done with the weights: their memory takes the partial sums
+
+    // What the wave leaves goes where its tiles were (none is in flight any more).  (A wave without a tile is not read below.)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    float* mine = reinterpret_cast<float*>(ring);
+    constexpr int kSums = kDecodeParts * kHeads * kChannels;  // floats in front of the references and the sums of weights
 #pragma unroll
-    for (int h = 0; h < kDecodeHeads; ++h) {
-      part[(part_id * kDecodeHeads + h) * kHeadDim + 2 * c2] = a0[h];
-      part[(part_id * kDecodeHeads + h) * kHeadDim + 2 * c2 + 1] = a1[h];
+    for (int t = 0; t < HT; ++t) {
+      float s = sum[t];
+      s += __shfl_xor(s, 16, 64);
+      s += __shfl_xor(s, 32, 64);
+      if (lane < 4) {
+        mine[kSums + 4 * t + lane] = ref[t];
+        mine[kSums + kHeads + 4 * t + lane] = s;
+      }
+      if (kg < kDecodeParts) {
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+          float* dst = mine + (kg * kHeads + 4 * t + h) * kChannels + CPL * n;
+#pragma unroll
+          for (int j = 0; j < CPL; ++j) dst[j] = acc[t][j][h];
+        }
+      }
     }
     __syncthreads();
-    for (int e = tid; e < nh * kHeadDim; e += kDecodeThreads) {
-      const int h = e / kHeadDim;
-      float o = 0.0f;
-#pragma unroll
-      for (int q = 0; q < kDecodeWaves; ++q) o += part[q * kDecodeHeads * kHeadDim + e];  // fixed order
-      p.out[qrow0 * kHeadDim + e] = o / sum[h];
+    const int waves = tiles < WAVES ? tiles : WAVES;
+    for (int e = tid; e < nh * kChannels; e += kThreads) {
+      const int h = e / kChannels;
+      auto left = [&](int w, int at) { return reinterpret_cast<const float*>(lds + w * kWaveBytes)[at]; };
+      float m = left(0, kSums + h);
+      for (int w = 1; w < waves; ++w) m = fmaxf(m, left(w, kSums + h));
+      float o = 0.0f, s = 0.0f;
+      for (int w = 0; w < waves; ++w) {  // fixed order
+        const float f = __builtin_amdgcn_exp2f(left(w, kSums + h) - m);
+        o = fmaf(f, left(w, e) + (left(w, kHeads * kChannels + e) + left(w, 2 * kHeads * kChannels + e)), o);
+        s = fmaf(f, left(w, kSums + kHeads + h), s);
+      }
+      p.out[(qrow0 + h) * kHeadDim + slice * kChannels + e % kChannels] = o / s;
     }
+    if (h0 + kHeads < g) __syncthreads();  // everything has been read before the next sweep's tiles arrive
   }
+}
+
+template <int HT, int CPL, int WAVES>
+int launch_decode(int64_t heads, const DecodeParams& p, hipStream_t stream) {
+  constexpr int kBytes = WAVES * decode_wave_bytes(HT);
+  const int rc = set_max_dynamic_lds(reinterpret_cast<const void*>(decode_attention_kernel<HT, CPL, WAVES>), kBytes);
+  if (rc != DAPQ_OK) return rc;
+  hipLaunchKernelGGL((decode_attention_kernel<HT, CPL, WAVES>), dim3((unsigned)heads, kHeadDim / (16 * CPL)),
+                     dim3(64 * WAVES), kBytes, stream, p);
+  DAPQ_HIP_LAUNCH_CHECK("decode_attention_kernel");
+  return DAPQ_OK;
+}
+
+// Slices per head: every slice reads all of K_c, so they pay only while most compute units would have no workgroup.  8
+// heads x 983 rows: 13.8 us with one slice, 11.0 us with four (before the loads were whole rows); 64 heads x 4096 rows:
+// 55.4 us with four, 37.5 us with two.
+template <int HT>
+int launch_decode_slices(int64_t heads, const DecodeParams& p, hipStream_t stream) {
+  if (heads <= 32) return launch_decode<HT, 2, 8>(heads, p, stream);
+  if (heads <= 128) return launch_decode<HT, 4, 8>(heads, p, stream);
+  return launch_decode<HT, 8, 4>(heads, p, stream);
 }
 
 }  // namespace
@@ -215,18 +370,9 @@ extern "C" DAPQ_API int dapq_decode_attention(const dapq_shape* shape, const voi
   p.n_kv_heads = shape->n_kv_heads;
   p.budget = budget;
   p.c = shape->scale * 1.4426950408889634f;
-  auto lds_for = [](int b) {
-    const int shared_floats = kDecodeHeads * b > kDecodeWaves * kDecodeHeads * kHeadDim
-                                  ? kDecodeHeads * b
-                                  : kDecodeWaves * kDecodeHeads * kHeadDim;  // weights, later the partial sums
-    return (kDecodeHeads * kHeadDim + kDecodeWaves * kDecodeHeads + shared_floats) * (int)sizeof(float);
-  };
-  const int lds_bytes = lds_for(budget);
-  // the limit is raised once, to what the largest supported budget needs
-  const int rc_lds = set_max_dynamic_lds(reinterpret_cast<const void*>(decode_attention_kernel), lds_for(kDecodeMaxRows));
-  if (rc_lds != DAPQ_OK) return rc_lds;
-  hipLaunchKernelGGL(decode_attention_kernel, dim3((unsigned)shape->n_kv_heads, (unsigned)shape->batch, (unsigned)shape->n_layers),
-                     dim3(kDecodeThreads), lds_bytes, static_cast<hipStream_t>(stream), p);
-  DAPQ_HIP_LAUNCH_CHECK("decode_attention_kernel");
-  return DAPQ_OK;
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  const int64_t heads = (int64_t)shape->n_layers * shape->batch * shape->n_kv_heads;
+  DAPQ_REQUIRE(heads < ((int64_t)1 << 31), DAPQ_ERR_UNSUPPORTED, "n_layers * batch * n_kv_heads (%lld) is too large",
+               (long long)heads);
+  return p.n_q_heads / p.n_kv_heads <= 4 ? launch_decode_slices<1>(heads, p, st) : launch_decode_slices<2>(heads, p, st);
 }

@@ -54,3 +54,40 @@ def test_normalisers_merged_over_many_chunks(H, lens):
     lse = prob.stats()
     assert torch.equal(lse, prob.stats())
     assert np.abs(lse.cpu().numpy() - oracle_lse2(q, k, 1, cu)).max() < 2e-4
+
+
+# rows around the tiles of 32 and the eight waves' first and second tiles; groups that fill one head tile of 4, several
+@pytest.mark.parametrize("g", [1, 3, 4, 5, 8, 12])
+@pytest.mark.parametrize("rows", [1, 15, 17, 32, 33, 256, 257, 300, 513, 530, 800])
+def test_decode_tiles_and_head_groups(H, rows, g):
+    """|error| <= 1e-5 max|v| + 1e-4 |o|, the bar of the other decode tests.  Heads of one call hold different numbers
+    of rows (an empty one among them); the queries are not 16-byte aligned; in the last head a key of the second round of
+    tiles lies hundreds of binades above everything before it, so the running reference has to move."""
+    announce(f"decode rows={rows} g={g}")
+    rng = np.random.default_rng(rows * 16 + g)
+    budget, hkv, batch = rows + 3, 2, 2
+    counts = np.array([[rows, max(1, rows // 2)], [0, rows]], dtype=np.int32)
+    f = lambda *s: rng.standard_normal(s, dtype=np.float32)  # noqa: E731
+    q, k, v = f(batch, hkv * g, 128), f(batch, hkv, budget, 128), f(batch, hkv, budget, 128)
+    k[1, 1, min(rows - 1, 270)] = 60.0 * q[1, g]
+    k[1, 1, rows // 3] = -60.0 * q[1, g]
+    qb, kb, vb = (W.to_bf16_bits(x) for x in (q, k, v))
+    store = torch.zeros(q.size + 1, dtype=torch.bfloat16, device="cuda")
+    store[1:] = H.dev_bf16(qb).reshape(-1)
+    out = torch.full((1, batch, hkv * g, 128), float("nan"), dtype=torch.float32, device="cuda")
+    shape = H.D.make_shape(n_layers=1, batch=batch, n_q_heads=hkv * g, n_kv_heads=hkv, n_pseudo=1, total_tokens=batch,
+                           scale=128 ** -0.5)
+    H.D.dapq_decode_attention(shape, store[1:], H.dev_bf16(kb), H.dev_bf16(vb), torch.from_numpy(counts).cuda(), budget, out)
+    got = out.cpu().numpy()[0].astype(np.float64)
+    q64, k64, v64 = (O.bf16_bits_to_f64(x) for x in (qb, kb, vb))
+    for b in range(batch):
+        for h in range(hkv * g):
+            n = counts[b, h // g]
+            if n == 0:
+                assert (got[b, h] == 0).all()
+                continue
+            x = k64[b, h // g, :n] @ q64[b, h] / np.sqrt(128)
+            w = np.exp(x - x.max())
+            want = (w / w.sum()) @ v64[b, h // g, :n]
+            bound = 1e-5 * np.abs(v64[b, h // g, :n]).max() + 1e-4 * np.abs(want)
+            assert (np.abs(got[b, h] - want) <= bound).all(), (b, h)
