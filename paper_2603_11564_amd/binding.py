@@ -110,11 +110,27 @@ def _ptr(t) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
+def _resolve_current_stream():
+    """A function for the current stream's handle.  torch.cuda.current_stream() builds a Stream object each time, 2.9 us
+    next to the 3.1 us that checking and launching a kernel take; the raw handle takes 0.2 us."""
+    import torch
+    raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+    if raw is None or device is None:
+        return lambda: torch.cuda.current_stream().cuda_stream
+    torch.cuda.current_stream()  # initialises the device the way torch wants it, once
+    return lambda: raw(device())
+
+
+_current_stream = None
+
+
 def _stream(stream) -> Optional[int]:
+    global _current_stream
     if stream is not None:
         return stream if isinstance(stream, int) else stream.cuda_stream
-    import torch
-    return torch.cuda.current_stream().cuda_stream
+    if _current_stream is None:
+        _current_stream = _resolve_current_stream()
+    return _current_stream()
 
 
 def make_shape(*, n_layers, batch, n_q_heads, n_kv_heads, n_pseudo, total_tokens, head_dim=128, cu_seqlens=None,
