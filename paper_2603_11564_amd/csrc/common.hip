@@ -82,6 +82,34 @@ int check_shape(const dapq_shape* s, bool need_q, bool need_k, bool need_v) {
   return DAPQ_OK;
 }
 
+// The plan's chunks along the key axis and its workspace, once the rows are split and the chunk is chosen.
+static int finish_score_plan(const dapq_shape* s, int64_t heads, int chunk, ScorePlan* p) {
+  p->chunk_keys = chunk;
+  if (s->cu_seqlens == nullptr) {
+    const int64_t L = s->total_tokens / s->batch;
+    p->max_chunks = (int64_t)s->batch * ((L + chunk - 1) / chunk);
+  } else {
+    p->max_chunks = (s->total_tokens + chunk - 1) / chunk + s->batch;
+  }
+  if (p->max_chunks < 1) p->max_chunks = 1;
+  DAPQ_REQUIRE(p->max_chunks < ((int64_t)1 << 31), DAPQ_ERR_UNSUPPORTED, "too many key chunks");
+  DAPQ_REQUIRE(p->n_groups <= 65535, DAPQ_ERR_UNSUPPORTED, "too many query rows per KV head");
+
+  size_t off = 0;
+  p->off_cu_chunks = off;
+  off = align_up(off + sizeof(int32_t) * ((size_t)s->batch + 1), 256);
+  p->off_work = off;  // ticket counter of a ragged batch's work list
+  off += 256;
+  p->off_parts = off;
+  off = align_up(off + sizeof(float) * 2 * (size_t)heads * (size_t)p->max_chunks * p->rows_pad, 256);
+  p->off_lse2 = off;
+  off = align_up(off + sizeof(float) * (size_t)s->n_layers * s->batch * s->n_q_heads * s->n_pseudo, 256);
+  p->off_partial = off;
+  if (p->n_groups > 1) off = align_up(off + sizeof(float) * (size_t)(p->n_groups - 1) * (size_t)heads * (size_t)s->total_tokens, 256);
+  p->total_bytes = off;
+  return DAPQ_OK;
+}
+
 int make_score_plan(const dapq_shape* s, ScorePlan* p) {
   const int g = s->n_q_heads / s->n_kv_heads;
   const int64_t rows64 = (int64_t)g * s->n_pseudo;
@@ -90,9 +118,11 @@ int make_score_plan(const dapq_shape* s, ScorePlan* p) {
   p->rows = (int)rows64;
   const int64_t heads = (int64_t)s->n_layers * s->n_kv_heads;
   // one wave per (chunk, row group): a group is up to 256 rows, all in the wave's registers
-  p->n_groups = (p->rows + 255) / 256;
-  p->row_blocks = p->rows <= 64 ? 2 : (p->rows <= 128 ? 4 : 8);
+  const RowSplit split = wave_row_split(p->rows);
+  p->n_groups = split.n_groups;
+  p->row_blocks = split.row_blocks;
   p->rows_pad = p->n_groups * p->row_blocks * 32;
+  p->tile = false;
 
   // Keys per wave.  The machine runs kWaveSlots waves at a time, each for as long as its chunk; a
   // wave pays a fixed start-up (Q fragments, ring fill) worth about kStartKeys keys.  Dense batches
@@ -120,29 +150,31 @@ int make_score_plan(const dapq_shape* s, ScorePlan* p) {
       chunk = c;
     }
   }
-  p->chunk_keys = chunk;
-  if (s->cu_seqlens == nullptr) {
-    const int64_t L = s->total_tokens / s->batch;
-    p->max_chunks = (int64_t)s->batch * ((L + chunk - 1) / chunk);
-  } else {
-    p->max_chunks = (s->total_tokens + chunk - 1) / chunk + s->batch;
-  }
-  if (p->max_chunks < 1) p->max_chunks = 1;
-  DAPQ_REQUIRE(p->max_chunks < ((int64_t)1 << 31), DAPQ_ERR_UNSUPPORTED, "too many key chunks");
-  DAPQ_REQUIRE(p->n_groups <= 65535, DAPQ_ERR_UNSUPPORTED, "too many query rows per KV head");
+  int rc = finish_score_plan(s, heads, chunk, p);
+  if (rc != DAPQ_OK) return rc;
 
-  size_t off = 0;
-  p->off_cu_chunks = off;
-  off = align_up(off + sizeof(int32_t) * ((size_t)s->batch + 1), 256);
-  p->off_work = off;  // ticket counter of a ragged batch's work list
-  off += 256;
-  p->off_parts = off;
-  off = align_up(off + sizeof(float) * 2 * (size_t)heads * (size_t)p->max_chunks * p->rows_pad, 256);
-  p->off_lse2 = off;
-  off = align_up(off + sizeof(float) * (size_t)s->n_layers * s->batch * s->n_q_heads * s->n_pseudo, 256);
-  p->off_partial = off;
-  if (p->n_groups > 1) off = align_up(off + sizeof(float) * (size_t)(p->n_groups - 1) * (size_t)heads * (size_t)s->total_tokens, 256);
-  p->total_bytes = off;
+  // The tile form: a workgroup per 128 keys, its waves a row block each.  It is the faster one where the wave form leaves
+  // the chip idle or pays its start-up per chunk (the queries of up to 256 rows into one wave, a ring of its own, tickets).
+  // Both passes of dapq_score, wave form -> tile form, 8 KV heads: one layer, 1024 keys, 256 rows 38.6 -> 15.8 us; 8191
+  // keys, 128 rows 26.9 -> 19.3; 16384 keys, 256 rows 44 -> 41, 512 rows 57 -> 61; 32768 keys, 128 rows 39 -> 45; ragged,
+  // 8 prompts of 1000 keys, one layer, 128 rows 176 -> 24, 4 layers, 512 rows 188 -> 169 (40 000 units); 32 layers, 16
+  // prompts of 700, 32 rows (30 000 units) 517 -> 440, 128 rows (120 000) 589 -> 597.  Where dapq_score runs both passes in
+  // one kernel it stays with that one.
+  const bool ragged = s->cu_seqlens != nullptr;
+  const bool one_kernel = !ragged && p->n_groups == 1 && p->max_chunks <= 4 * (int64_t)s->batch;
+  const int64_t row_blocks = (p->rows + 31) / 32;
+  const int64_t tiles = heads * (ragged ? s->total_tokens / kTileKeys + s->batch
+                                        : s->batch * ((s->total_tokens / s->batch + kTileKeys - 1) / kTileKeys));
+  if (one_kernel || tiles * row_blocks > (ragged ? 65536 : 8192) || (!ragged && tiles > 1024)) return DAPQ_OK;
+  ScorePlan t = *p;
+  t.tile = true;
+  t.row_blocks = (int)row_blocks;
+  t.n_groups = 1;
+  t.rows_pad = t.row_blocks * 32;
+  rc = finish_score_plan(s, heads, kTileKeys, &t);
+  if (rc != DAPQ_OK) return rc;
+  // (its partials are more: a shape that dapq_score_static serves is still served)
+  if (t.total_bytes <= DAPQ_STATIC_SCRATCH_BYTES || p->total_bytes > DAPQ_STATIC_SCRATCH_BYTES) *p = t;
   return DAPQ_OK;
 }
 

@@ -29,13 +29,15 @@ int fail(int code, const char* fmt, ...);
 constexpr int kHeadDim = 128;
 constexpr int kMinChunkKeys = 128;      // fewest keys one wave of a score pass walks over
 constexpr int kMaxChunkKeys = 1 << 16;  // most
+constexpr int kTileKeys = kMinChunkKeys;  // keys of a workgroup of the tile form of the score passes
 
 // How the score passes split the work; a pure function of the shape so that
 // dapq_workspace_bytes() and the launchers agree.
 struct ScorePlan {
+  bool tile;       // the tile kernels (a workgroup per chunk, its waves share out the rows) instead of the wave kernels
   int rows;        // R = (H_q/H_kv) * N query rows scored against every key of a KV head
-  int n_groups;    // row groups of row_blocks * 32 rows, one wave each per chunk
-  int row_blocks;  // 32-row blocks per wave (2, 4 or 8)
+  int n_groups;    // row groups of row_blocks * 32 rows, one wave each per chunk (tile: 1)
+  int row_blocks;  // 32-row blocks per wave (2, 4 or 8; tile: all of them)
   int rows_pad;    // n_groups * row_blocks * 32
   int chunk_keys;  // keys per wave (a power of two)
   int64_t max_chunks;  // grid size along the key axis: upper bound on sum_b ceil(L_b / chunk_keys)
@@ -47,6 +49,12 @@ struct ScorePlan {
 // groups must be usable.  Returns DAPQ_OK or sets the error and returns its code.
 int check_shape(const dapq_shape* s, bool need_q, bool need_k, bool need_v);
 int make_score_plan(const dapq_shape* s, ScorePlan* plan);
+
+// How the wave kernels split the rows: one wave holds a group of up to 256 in its registers.
+struct RowSplit {
+  int n_groups, row_blocks;
+};
+inline RowSplit wave_row_split(int rows) { return {(rows + 255) / 256, rows <= 64 ? 2 : (rows <= 128 ? 4 : 8)}; }
 
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 

@@ -40,6 +40,7 @@
 #include <mutex>
 
 #include "dapq_internal.h"
+#include "wave_scan.h"
 
 namespace dapq {
 namespace {
@@ -80,8 +81,7 @@ struct Work {
   int seq_len;
 };
 
-// The same for a wave-uniform chunk index, with the result pinned to scalar registers: everything
-// derived from it (key base pointer, buffer descriptors, trip counts) then stays scalar too.
+// Wave-uniform values pinned to scalar registers.
 __device__ __forceinline__ int uniform_i32(int v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ unsigned uniform_u32(unsigned v) { return (unsigned)__builtin_amdgcn_readfirstlane((int)v); }
 template <typename T>
@@ -91,6 +91,30 @@ __device__ __forceinline__ const T* uniform_ptr(const T* ptr) {
   const unsigned hi = (unsigned)uniform_i32((int)(unsigned)(v >> 32));
   return reinterpret_cast<const T*>((uintptr_t)(((unsigned long long)hi << 32) | lo));
 }
+// Chunks of a sequence of L keys (chunk_keys is a power of two).
+__device__ __forceinline__ int chunks_of_length(const ScoreParams& p, int L) {
+  return L > 0 ? (L + p.chunk_keys - 1) >> __builtin_ctz((unsigned)p.chunk_keys) : 0;
+}
+
+// A ragged batch of at most 64 sequences, one to a lane: the sequence's start, length and the chunks up to its end.
+// Every wave forms this itself out of two loads and a scan: looking a chunk up in the prefix in device memory is a
+// chain of log2(batch) + 3 dependent loads, and the kernel that writes the prefix a launch of its own.
+struct LaneSequence {
+  int start, len, chunks, chunks_end;
+};
+__device__ __forceinline__ LaneSequence lane_sequence(const ScoreParams& p) {
+  int lane = threadIdx.x & 63;
+  asm volatile("" : "+v"(lane));  // formed where it is asked for: not kept in registers through a wave's items
+  LaneSequence q;
+  q.start = p.cu_seqlens[lane < p.batch ? lane : p.batch];
+  q.len = p.cu_seqlens[lane < p.batch ? lane + 1 : p.batch] - q.start;
+  q.chunks = chunks_of_length(p, q.len);
+  q.chunks_end = (int)wave_scan<OpAdd>((uint32_t)q.chunks);
+  return q;
+}
+
+// The same for a wave-uniform chunk index, with the result pinned to scalar registers: everything
+// derived from it (key base pointer, buffer descriptors, trip counts) then stays scalar too.  Called by whole waves.
 __device__ __forceinline__ Work locate(const ScoreParams& p, int gchunk);
 __device__ __forceinline__ Work locate_uniform(const ScoreParams& p, int gchunk) {
   Work w = locate(p, gchunk);
@@ -116,6 +140,13 @@ __device__ __forceinline__ Work locate(const ScoreParams& p, int gchunk) {
     w.key0 = (gchunk - w.seq * cps) * p.chunk_keys;
     w.tok0 = (int64_t)w.seq * L + w.key0;
     w.seq_len = L;
+  } else if (p.batch <= 64) {
+    const LaneSequence q = lane_sequence(p);
+    w.seq = __popcll(__ballot(q.chunks_end <= gchunk));  // (lanes past the batch repeat the last end)
+    if (w.seq >= p.batch) return w;
+    w.key0 = (gchunk - __builtin_amdgcn_readlane(q.chunks_end - q.chunks, w.seq)) * p.chunk_keys;
+    w.tok0 = (int64_t)__builtin_amdgcn_readlane(q.start, w.seq) + w.key0;
+    w.seq_len = __builtin_amdgcn_readlane(q.len, w.seq);
   } else {
     if (gchunk >= p.cu_chunks[p.batch]) return w;
     int lo = 0, hi = p.batch;  // largest b with cu_chunks[b] <= gchunk
@@ -228,7 +259,7 @@ constexpr int kCombineRun = 8, kCombineClasses = 16;
 __global__ __launch_bounds__(64 * kCombineClasses) void score_combine_kernel(ScoreParams p, int row_tiles) {
   __shared__ float lds_max[kCombineClasses][64], lds_sum[kCombineClasses][64];
   const int lane = threadIdx.x & 63, wave = uniform_i32((int)(threadIdx.x >> 6)), waves = (int)(blockDim.x >> 6);
-  const int b = (int)(blockIdx.x / row_tiles), row = (int)(blockIdx.x - b * row_tiles) * 64 + lane;
+  const int b = uniform_i32((int)(blockIdx.x / row_tiles)), row = (int)(blockIdx.x - b * row_tiles) * 64 + lane;
   const int layer = (int)(blockIdx.y / p.n_kv_heads), kv = (int)(blockIdx.y - layer * p.n_kv_heads);
   int c0, c1;
   if (p.cu_seqlens == nullptr) {
@@ -236,6 +267,10 @@ __global__ __launch_bounds__(64 * kCombineClasses) void score_combine_kernel(Sco
     const int cps = (L + p.chunk_keys - 1) / p.chunk_keys;
     c0 = b * cps;
     c1 = c0 + cps;
+  } else if (p.batch <= 64) {
+    const LaneSequence q = lane_sequence(p);
+    c1 = __builtin_amdgcn_readlane(q.chunks_end, b);
+    c0 = c1 - __builtin_amdgcn_readlane(q.chunks, b);
   } else {
     c0 = p.cu_chunks[b];
     c1 = p.cu_chunks[b + 1];
@@ -562,7 +597,8 @@ __device__ __forceinline__ unsigned take_item(unsigned* work, int lane) {
 // empty it goes on to the others', so every list is drained whatever runs where.  (The host launches this form only
 // if the item count fits 31 bits whatever the lengths are.)
 struct Item {
-  int head, block, chunk, seq, nkeys;
+  int head, block, chunk;
+  Work work;
 };
 struct ItemLists {
   unsigned chunks, blocks, heads;
@@ -577,9 +613,7 @@ struct ItemLists {
     it.head = (int)(reversed ? heads - 1 - head : head);
     it.block = (int)block;
     it.chunk = (int)((reversed ? cx - 1 - c : c) * kLists + (unsigned)x);
-    const Work w = locate_uniform(p, it.chunk);
-    it.seq = w.seq;
-    it.nkeys = w.nkeys;
+    it.work = locate_uniform(p, it.chunk);
     return it;
   }
 };
@@ -632,10 +666,9 @@ __device__ __forceinline__ int home_list() {
 // FUSED (score_fused_kernel): the chunk's (reference, sum) pairs go to the start of the wave's own ring, which is
 // drained by then, instead of to global memory.
 template <int NRB, int NST, bool FUSED = false>
-__device__ __forceinline__ unsigned pass1_item(const ScoreParams& p, u32x4* ring, int chunk_id, int group, int head,
+__device__ __forceinline__ unsigned pass1_item(const ScoreParams& p, u32x4* ring, const Work& w, int chunk_id, int group, int head,
                                                bf16x8 (&qf)[NRB][8], const unsigned (&voff)[4], int lane,
                                                unsigned* work) {
-  const Work w = locate_uniform(p, chunk_id);
   // (the division runs on the vector ALU: bring the quotient back to a scalar register)
   const int layer = uniform_i32(head / p.n_kv_heads), kv = head - layer * p.n_kv_heads;
   const int n = lane & 31, h = lane >> 5;
@@ -752,8 +785,9 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_wave_pass1_kerne
   bf16x8 qf[NRB][8];
   if (!DYN) {
     const WaveSlot slot = wave_slot(p, wave_id);
-    if (locate_uniform(p, slot.chunk).nkeys == 0) return;
-    pass1_item<NRB, NST>(p, ring, slot.chunk, slot.group, (int)blockIdx.z, qf, voff, lane, nullptr);
+    const Work w = locate_uniform(p, slot.chunk);
+    if (w.nkeys == 0) return;
+    pass1_item<NRB, NST>(p, ring, w, slot.chunk, slot.group, (int)blockIdx.z, qf, voff, lane, nullptr);
     return;
   }
   const ItemLists lists = item_lists(p);
@@ -768,11 +802,11 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_wave_pass1_kerne
       const unsigned ticket = tickets.next();
       if (ticket >= n_items) break;
       const Item a = lists.at(p, x, ticket, false);
-      if (a.nkeys == 0) {  // (no chunk of a list is empty; if one were, it would only cost its ticket)
+      if (a.work.nkeys == 0) {  // (no chunk of a list is empty; if one were, it would only cost its ticket)
         tickets.post(work != nullptr ? take_item(work, lane) : 0u, lane);
         continue;
       }
-      tickets.post(pass1_item<NRB, NST>(p, ring, a.chunk, a.block * p.wg_groups + wave_id, a.head, qf, voff, lane, work),
+      tickets.post(pass1_item<NRB, NST>(p, ring, a.work, a.chunk, a.block * p.wg_groups + wave_id, a.head, qf, voff, lane, work),
                    lane);
     }
   }
@@ -781,10 +815,9 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_wave_pass1_kerne
 // Pass 2 of one chunk (arguments as pass1_item).  FUSED (score_fused_kernel): the query fragments are still in
 // registers from pass 1 and the caller has filled off2.
 template <int NRB, int NST, bool FUSED = false>
-__device__ __forceinline__ unsigned pass2_item(const ScoreParams& p, u32x4* ring, int chunk_id, int group, int head,
+__device__ __forceinline__ unsigned pass2_item(const ScoreParams& p, u32x4* ring, const Work& w, int group, int head,
                                                bf16x8 (&qf)[NRB][8], float (&off2)[NRB][16],
                                                const unsigned (&voff)[4], int lane, unsigned* work) {
-  const Work w = locate_uniform(p, chunk_id);
   // (the division runs on the vector ALU: bring the quotient back to a scalar register)
   const int layer = uniform_i32(head / p.n_kv_heads), kv = head - layer * p.n_kv_heads;
   const int n = lane & 31, h = lane >> 5;
@@ -858,8 +891,9 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_wave_pass2_kerne
   float off2[NRB][16];
   if (!DYN) {
     const WaveSlot slot = wave_slot(p, wave_id);
-    if (locate_uniform(p, slot.chunk).nkeys == 0) return;
-    pass2_item<NRB, NST>(p, ring, slot.chunk, slot.group, (int)(gridDim.z - 1 - blockIdx.z), qf, off2, voff, lane, nullptr);
+    const Work w = locate_uniform(p, slot.chunk);
+    if (w.nkeys == 0) return;
+    pass2_item<NRB, NST>(p, ring, w, slot.group, (int)(gridDim.z - 1 - blockIdx.z), qf, off2, voff, lane, nullptr);
     return;
   }
   const ItemLists lists = item_lists(p);
@@ -874,11 +908,11 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_wave_pass2_kerne
       const unsigned ticket = tickets.next();
       if (ticket >= n_items) break;
       const Item a = lists.at(p, x, ticket, true);
-      if (a.nkeys == 0) {  // (no chunk of a list is empty; if one were, it would only cost its ticket)
+      if (a.work.nkeys == 0) {  // (no chunk of a list is empty; if one were, it would only cost its ticket)
         tickets.post(work != nullptr ? take_item(work, lane) : 0u, lane);
         continue;
       }
-      tickets.post(pass2_item<NRB, NST>(p, ring, a.chunk, a.block * p.wg_groups + wave_id, a.head, qf, off2, voff, lane, work),
+      tickets.post(pass2_item<NRB, NST>(p, ring, a.work, a.block * p.wg_groups + wave_id, a.head, qf, off2, voff, lane, work),
                    lane);
     }
   }
@@ -903,7 +937,8 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_fused_kernel(Sco
   bf16x8 qf[NRB][8];
   const int chunk = uniform_i32((int)blockIdx.x * waves + wave_id);  // blockIdx.x is the sequence
   const int head = (int)blockIdx.z;
-  pass1_item<NRB, NST, true>(p, ring, chunk, 0, head, qf, voff, lane, nullptr);
+  const Work work = locate_uniform(p, chunk);
+  pass1_item<NRB, NST, true>(p, ring, work, chunk, 0, head, qf, voff, lane, nullptr);
   __syncthreads();
   // lse2 of rows lane, lane + 64, ...: every wave merges all chunks itself
   constexpr int kRowsPerLane = NRB * 32 / 64;
@@ -942,7 +977,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_fused_kernel(Sco
       off2[rb][4 * b + 3] = v.w;
     }
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // off2 is out of the ring before pass 2 refills it
-  pass2_item<NRB, NST, true>(p, ring, chunk, 0, head, qf, off2, voff, lane, nullptr);
+  pass2_item<NRB, NST, true>(p, ring, work, 0, head, qf, off2, voff, lane, nullptr);
 }
 
 // The causal block of the pseudo tokens' own keys (Sec. 4.1: they are prefilled in-sequence): one wave
@@ -998,6 +1033,252 @@ __global__ __launch_bounds__(64, 1) void score_wave_pseudo_kernel(ScoreParams p,
       const float m = fmaxf(old, block);
       lse[row] = m + log2f(__builtin_amdgcn_exp2f(old - m) + __builtin_amdgcn_exp2f(block - m));
     }
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// The tile form of the passes: one workgroup = kTileKeys keys of one (layer, sequence, KV head) x all its query rows.
+// For calls that are bound by latency (make_score_plan says which): the keys are brought into LDS once, by all waves
+// together, and a wave works on 32 query rows at a time, so it loads 8 KB of queries instead of 64 and the 4 x 8 MFMAs of a
+// row block are its whole chain; at about 90 registers four waves share a SIMD and cover for each other.  One layer,
+// 8 heads, 1024 keys, 256 rows: 18.5 us per pass in the wave form (8 compute units busy), 7.4 / 8.0 us here; what is left
+// is the launch, one trip to memory for keys and queries and 1 us of arithmetic.
+// ---------------------------------------------------------------------------------------------
+constexpr int kTileSubs = kTileKeys / 32;
+constexpr int kTileWaves = 8;                                   // most waves of a workgroup
+constexpr int kTileLds = kTileSubs * kSubBytes;
+
+// Which tile a workgroup works on: the KV heads of a chunk are neighbours in the grid (in the packed layout they share
+// the rows of K), then the chunks, then the layers; pass 2 (`reversed`) walks layers and chunks from the far end.
+struct Tile {
+  int layer, kv, chunk;
+};
+__device__ __forceinline__ Tile tile_of_workgroup(const ScoreParams& p, bool reversed) {
+  Tile t;
+  const unsigned c = blockIdx.x / (unsigned)p.n_kv_heads;
+  t.kv = uniform_i32((int)(blockIdx.x - c * (unsigned)p.n_kv_heads));
+  t.chunk = uniform_i32(reversed ? p.max_chunks - 1 - (int)c : (int)c);
+  t.layer = (int)(reversed ? gridDim.z - 1 - blockIdx.z : blockIdx.z);
+  return t;
+}
+
+// The waves of a workgroup share out the transfers of the tile's keys: 1 KB (four key rows) each, rows past the end of the
+// chunk arrive as zeros (see sub_dma).
+__device__ __forceinline__ void tile_dma(u32x4* keys, const uint16_t* kbase, int64_t stride_token, int nkeys, int wave,
+                                         int waves, int lane) {
+  const int64_t stride_b = stride_token * 2;
+  const unsigned row0 = (unsigned)lane >> 4, pos = (unsigned)lane & 15u;
+  for (int x = wave; x < kTileSubs * 8; x += waves) {
+    const int row = 4 * x;
+    const bool live = row < nkeys;
+    const char* base = reinterpret_cast<const char*>(kbase) + (live ? (int64_t)row * stride_b : (int64_t)0);
+    const int64_t span = (int64_t)(nkeys - row - 1) * stride_b + kHeadDim * 2;
+    const unsigned records = !live ? 0u : (span > (int64_t)0xFFFFFFFFll ? 0xFFFFFFFFu : (unsigned)span);
+    const __amdgpu_buffer_rsrc_t rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, (int)records, 0x00020000);
+    const unsigned voff = row0 * (unsigned)stride_b + ((pos ^ row0) ^ (4u * ((unsigned)x & 3u))) * 16u;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)(keys + x * 64), 16,
+                                             (int)voff, 0, 0, 0);
+  }
+}
+
+__device__ __forceinline__ const uint16_t* tile_q_base(const ScoreParams& p, const Tile& t, int seq) {
+  return p.q + (int64_t)t.layer * p.q_stride_layer + (int64_t)seq * p.q_stride_seq +
+         (int64_t)t.kv * p.group * p.q_stride_head;
+}
+__device__ __forceinline__ const uint16_t* tile_k_base(const ScoreParams& p, const Tile& t, const Work& w) {
+  return uniform_ptr(p.k + (int64_t)t.layer * p.k_stride_layer + (int64_t)w.seq * p.k_stride_seq +
+                     (int64_t)t.kv * p.k_stride_head + w.tok0 * p.k_stride_token);
+}
+
+// Pass 1, 64 keys at a time with a running maximum.
+__global__ __launch_bounds__(64 * kTileWaves) __attribute__((amdgpu_waves_per_eu(4))) void score_tile_pass1_kernel(ScoreParams p) {
+  __shared__ u32x4 keys[kTileLds / 16];
+  const Tile t = tile_of_workgroup(p, false);
+  const Work w = locate_uniform(p, t.chunk);
+  if (w.nkeys == 0) return;  // (the same for the whole workgroup)
+  const int wave = uniform_i32((int)(threadIdx.x >> 6)), waves = (int)(blockDim.x >> 6);
+  const int lane = threadIdx.x & 63, n = lane & 31, h = lane >> 5;
+  tile_dma(keys, tile_k_base(p, t, w), p.k_stride_token, w.nkeys, wave, waves, lane);
+  const uint16_t* qbase = tile_q_base(p, t, w.seq);
+  const int row_blocks = p.rows_pad / 32;
+  float2* outp = p.parts + (((int64_t)t.layer * p.n_kv_heads + t.kv) * p.max_chunks + t.chunk) * p.rows_pad;
+  bf16x8 qf[8];
+  frag_from_q(qf, p, qbase, wave * 32 + n, h);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  for (int rb = wave; rb < row_blocks; rb += waves) {
+    float ref = -INFINITY, z[2] = {0.0f, 0.0f};
+#pragma unroll 1
+    for (int half = 0; half < kTileSubs / 2; ++half) {
+      f32x16 a[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        bf16x8 kf[8];
+        if (u == 1) __builtin_amdgcn_sched_barrier(0);
+        wave_load_frags<1>(kf, keys + (2 * half + u) * kSubVec, n, h);
+        a[u] = f32x16{0};
+#pragma unroll
+        for (int s = 0; s < 8; ++s) a[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], qf[s], a[u], 0, 0, 0);
+      }
+      const int first = half * 64;
+      if (w.nkeys < first + 64) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+          for (int v = 0; v < 16; ++v)
+            if (u * 32 + acc_row(v, 0) >= w.nkeys - first - 4 * h) a[u][v] = -INFINITY;
+      }
+      float m = a[0][0];
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) m = fmaxf(m, a[u][v]);
+      const float mnew = fmaxf(ref, fmaxf(m, xhalf(m)) * p.c);  // (finite: the first half has a key)
+      const float scale = __builtin_amdgcn_exp2f(ref - mnew);
+      z[0] *= scale;
+      z[1] *= scale;
+      ref = mnew;
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) z[v & 1] += __builtin_amdgcn_exp2f(fmaf(a[u][v], p.c, -mnew));
+    }
+    if (rb + waves < row_blocks) frag_from_q(qf, p, qbase, (rb + waves) * 32 + n, h);
+    const float zz = z[0] + z[1];
+    const float both = zz + xhalf(zz);
+    if (h == 0) outp[rb * 32 + n] = make_float2(ref, both);
+  }
+}
+
+// Pass 2: a lane's column sums over the rows of its wave, then over the waves in wave order through LDS.
+// MERGE: lse2 is not read but formed from the partials of pass 1, by every workgroup for itself, with the arithmetic of
+// score_combine_kernel in its order (same bits).  That takes the workgroup 1 us while its keys are on the way; the combine
+// kernel and the boundary in front of it are 3 to 4 us of a call of 20.
+constexpr int kMergeRuns = 4;                                    // runs of kCombineRun chunks a thread holds
+constexpr int kMergeMaxRows = 64 * kTileWaves;
+// How many chunks per sequence the threads of a workgroup can merge (0: more rows than threads).
+__host__ __device__ constexpr int tile_merge_chunks(int rows_pad, int threads) {
+  return rows_pad > threads ? 0 : threads / rows_pad * kMergeRuns * kCombineRun < kCombineClasses * kCombineRun
+                                      ? threads / rows_pad * kMergeRuns * kCombineRun
+                                      : kCombineClasses * kCombineRun;
+}
+template <bool MERGE>
+__global__ __launch_bounds__(64 * kTileWaves) __attribute__((amdgpu_waves_per_eu(4))) void score_tile_pass2_kernel(ScoreParams p) {
+  __shared__ u32x4 keys[kTileLds / 16];
+  __shared__ float cols[kTileWaves][kTileKeys];
+  __shared__ __align__(16) float neg_lse[MERGE ? kMergeMaxRows : 4];
+  __shared__ float merge_max[MERGE ? kMergeMaxRows : 1], merge_sum[MERGE ? kMergeMaxRows * kMergeRuns : 1];
+  const Tile t = tile_of_workgroup(p, true);
+  const Work w = locate_uniform(p, t.chunk);
+  if (w.nkeys == 0) return;  // (the same for the whole workgroup)
+  const int wave = uniform_i32((int)(threadIdx.x >> 6)), waves = (int)(blockDim.x >> 6);
+  const int lane = threadIdx.x & 63, n = lane & 31, h = lane >> 5;
+  tile_dma(keys, tile_k_base(p, t, w), p.k_stride_token, w.nkeys, wave, waves, lane);
+  const uint16_t* qbase = tile_q_base(p, t, w.seq);
+  const float* lse =
+      p.lse2 + (((int64_t)t.layer * p.batch + w.seq) * p.n_q_heads + (int64_t)t.kv * p.group) * p.n_pseudo;
+  const int row_blocks = p.rows_pad / 32;
+  bf16x8 qf[8];
+  float off[16];
+  frag_from_q(qf, p, qbase, wave * 32 + n, h);
+  if (MERGE) {
+    // thread = (row, share): runs share, share + shares, ... of the sequence's chunks
+    const int row = (int)threadIdx.x % p.rows_pad, share = (int)threadIdx.x / p.rows_pad;
+    const int shares = (int)blockDim.x / p.rows_pad;
+    const int chunks = (w.seq_len + p.chunk_keys - 1) / p.chunk_keys, runs = (chunks + kCombineRun - 1) / kCombineRun;
+    const int first = t.chunk - w.key0 / p.chunk_keys;  // the sequence's first chunk
+    const float2* src = p.parts + (((int64_t)t.layer * p.n_kv_heads + t.kv) * p.max_chunks + first) * p.rows_pad + row;
+    float part[kMergeRuns][kCombineRun], m = -INFINITY;
+#pragma unroll
+    for (int k = 0; k < kMergeRuns; ++k) {
+      const int run = share + k * shares;
+      float2 v[kCombineRun];
+#pragma unroll
+      for (int i = 0; i < kCombineRun; ++i) {
+        const int c = run * kCombineRun + i;
+        v[i] = make_float2(0.0f, 0.0f);
+        if (share < shares && c < chunks) v[i] = src[(int64_t)c * p.rows_pad];
+      }
+#pragma unroll
+      for (int i = 0; i < kCombineRun; ++i) {
+        part[k][i] = v[i].y > 0.0f ? v[i].x + log2f(v[i].y) : -INFINITY;
+        m = fmaxf(m, part[k][i]);
+      }
+    }
+    merge_max[threadIdx.x] = m;
+    __syncthreads();
+    if (share < shares) {
+      for (int i = 0; i < shares; ++i) m = fmaxf(m, merge_max[i * p.rows_pad + row]);
+#pragma unroll
+      for (int k = 0; k < kMergeRuns; ++k) {
+        const int run = share + k * shares;
+        float sum = 0.0f;
+#pragma unroll
+        for (int i = 0; i < kCombineRun; ++i) sum += exp2f(part[k][i] - m);
+        if (run < runs) merge_sum[run * p.rows_pad + row] = sum;
+      }
+    }
+    __syncthreads();
+    if (share == 0) {
+      float sum = 0.0f;
+      for (int k = 0; k < runs; ++k) sum += merge_sum[k * p.rows_pad + row];
+      neg_lse[row] = row < p.rows ? (sum > 0.0f ? -(m + log2f(sum)) : -0.0f) : -INFINITY;
+    }
+    // (visible to all after the barrier below)
+  }
+  const bool quads = (reinterpret_cast<uintptr_t>(lse) & 15) == 0 && (p.rows & 3) == 0;
+  // -lse2 of the rows this lane's accumulator registers hold; -inf for padding rows, which then add 0
+  auto load_off = [&](int rb) {
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const int row = rb * 32 + acc_row(4 * b, h);
+      if (MERGE) {
+        const float4 v = *reinterpret_cast<const float4*>(&neg_lse[row]);
+        off[4 * b] = v.x;
+        off[4 * b + 1] = v.y;
+        off[4 * b + 2] = v.z;
+        off[4 * b + 3] = v.w;
+      } else if (quads) {  // the four rows of an accumulator quad are consecutive: one 16-byte load
+        const float4 v = row < p.rows ? *reinterpret_cast<const float4*>(lse + row)
+                                      : make_float4(INFINITY, INFINITY, INFINITY, INFINITY);
+        off[4 * b] = -v.x;
+        off[4 * b + 1] = -v.y;
+        off[4 * b + 2] = -v.z;
+        off[4 * b + 3] = -v.w;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) off[4 * b + e] = row + e < p.rows ? -lse[row + e] : -INFINITY;
+      }
+    }
+  };
+  if (!MERGE) load_off(wave);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  for (int rb = wave; rb < row_blocks; rb += waves) {
+    if (rb != wave) frag_from_q(qf, p, qbase, rb * 32 + n, h);
+    if (MERGE || rb != wave) load_off(rb);
+#pragma unroll 1
+    for (int sub = 0; sub < kTileSubs; ++sub) {
+      bf16x8 kf[8];
+      wave_load_frags<1>(kf, keys + sub * kSubVec, n, h);
+      f32x16 a = {0};
+#pragma unroll
+      for (int s = 0; s < 8; ++s) a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[s], kf[s], a, 0, 0, 0);
+      float z[2] = {0.0f, 0.0f};
+#pragma unroll
+      for (int v = 0; v < 16; ++v) z[v & 1] += __builtin_amdgcn_exp2f(fmaf(a[v], p.c, off[v]));
+      float* col = &cols[wave][sub * 32 + n];
+      const float both = sum_halves(z[0] + z[1]);
+      if (h == 0) *col = rb == wave ? both : *col + both;
+    }
+  }
+  __syncthreads();
+  float* out = p.scores + ((int64_t)t.layer * p.n_kv_heads + t.kv) * p.total_tokens + w.tok0;
+  for (int key = threadIdx.x; key < w.nkeys; key += (int)blockDim.x) {
+    float s = cols[0][key];
+    for (int i = 1; i < waves && i < row_blocks; ++i) s += cols[i][key];
+    out[key] = s;
   }
 }
 
@@ -1073,12 +1354,22 @@ int aligned16(const void* ptr, const char* name) {
   return DAPQ_OK;
 }
 
-int launch_stats(const dapq_shape* s, const ScorePlan& plan, ScoreParams p, hipStream_t stream) {
-  if (s->cu_seqlens != nullptr) {
-    hipLaunchKernelGGL(score_chunk_prefix_kernel, dim3(1), dim3(64), 0, stream, s->cu_seqlens, p.cu_chunks, p.work,
-                       s->batch, plan.chunk_keys);
-    DAPQ_HIP_LAUNCH_CHECK("score_chunk_prefix_kernel");
-  }
+// Whether the passes of a shape need the chunk prefix in device memory (and the work lists, which are cleared with it).
+bool needs_chunk_prefix(const dapq_shape* s, const ScorePlan& plan) {
+  return s->cu_seqlens != nullptr && !(plan.tile && s->batch <= 64);
+}
+
+// The grid of the tile kernels, and the waves of their workgroups: one per row block, at most eight, at least four (with
+// fewer than four row blocks the others only bring in keys: a lone wave issues the 32 transfers of a tile one by one).
+dim3 tile_grid(const dapq_shape* s, const ScorePlan& plan) {
+  return dim3((unsigned)(plan.max_chunks * s->n_kv_heads), 1u, (unsigned)s->n_layers);
+}
+dim3 tile_threads(const ScorePlan& plan) {
+  const int row_blocks = plan.rows_pad / 32;
+  return dim3(64u * (unsigned)(row_blocks < 4 ? 4 : (row_blocks < kTileWaves ? row_blocks : kTileWaves)));
+}
+
+int launch_wave_pass1(const dapq_shape* s, const ScorePlan& plan, ScoreParams p, hipStream_t stream) {
   int rc = DAPQ_OK;
   const int64_t waves = plan.max_chunks * plan.n_groups * s->n_layers * s->n_kv_heads;
   const GroupShape gs = group_shape(s, plan);
@@ -1116,6 +1407,23 @@ int launch_stats(const dapq_shape* s, const ScorePlan& plan, ScoreParams p, hipS
   else DAPQ_LAUNCH_W1(8);
 #undef DAPQ_LAUNCH_W1
   DAPQ_HIP_LAUNCH_CHECK("score_wave_pass1_kernel");
+  return DAPQ_OK;
+}
+
+int launch_stats(const dapq_shape* s, const ScorePlan& plan, ScoreParams p, hipStream_t stream) {
+  if (needs_chunk_prefix(s, plan)) {
+    hipLaunchKernelGGL(score_chunk_prefix_kernel, dim3(1), dim3(64), 0, stream, s->cu_seqlens, p.cu_chunks, p.work,
+                       s->batch, plan.chunk_keys);
+    DAPQ_HIP_LAUNCH_CHECK("score_chunk_prefix_kernel");
+  }
+  if (plan.tile) {
+    hipLaunchKernelGGL(score_tile_pass1_kernel, tile_grid(s, plan), tile_threads(plan), 0, stream, p);
+    DAPQ_HIP_LAUNCH_CHECK("score_tile_pass1_kernel");
+    if (p.lse2 == nullptr) return DAPQ_OK;  // pass 2 merges the partials itself
+  } else {
+    const int rc = launch_wave_pass1(s, plan, p, stream);
+    if (rc != DAPQ_OK) return rc;
+  }
   // as many waves per 64 rows as the (mean) sequence has runs of chunks
   const int64_t chunks_per_seq = (plan.max_chunks + s->batch - 1) / s->batch, row_tiles = (plan.rows + 63) / 64;
   int64_t combine_waves = (chunks_per_seq + kCombineRun - 1) / kCombineRun;
@@ -1132,6 +1440,12 @@ int launch_accumulate(const dapq_shape* s, const ScorePlan& plan, ScoreParams p,
     hipLaunchKernelGGL(score_chunk_prefix_kernel, dim3(1), dim3(64), 0, stream, s->cu_seqlens, p.cu_chunks, p.work,
                        s->batch, plan.chunk_keys);
     DAPQ_HIP_LAUNCH_CHECK("score_chunk_prefix_kernel");
+  }
+  if (plan.tile) {
+    if (p.lse2 == nullptr) hipLaunchKernelGGL(score_tile_pass2_kernel<true>, tile_grid(s, plan), tile_threads(plan), 0, stream, p);
+    else hipLaunchKernelGGL(score_tile_pass2_kernel<false>, tile_grid(s, plan), tile_threads(plan), 0, stream, p);
+    DAPQ_HIP_LAUNCH_CHECK("score_tile_pass2_kernel");
+    return DAPQ_OK;
   }
   int rc = DAPQ_OK;
   const int64_t waves = plan.max_chunks * plan.n_groups * s->n_layers * s->n_kv_heads;
@@ -1185,7 +1499,7 @@ int launch_accumulate(const dapq_shape* s, const ScorePlan& plan, ScoreParams p,
 // sequence exactly the waves of a workgroup.
 // Returns the waves of such a workgroup (1 to 4), or 0 if the passes have to be separate launches.
 int fused_waves(const dapq_shape* s, const ScorePlan& plan) {
-  if (s->cu_seqlens != nullptr || plan.n_groups != 1 || s->total_tokens == 0) return 0;
+  if (plan.tile || s->cu_seqlens != nullptr || plan.n_groups != 1 || s->total_tokens == 0) return 0;
   const int64_t chunks_per_seq = plan.max_chunks / s->batch;  // dense: max_chunks = batch * chunks per sequence
   if (chunks_per_seq * s->batch != plan.max_chunks) return 0;
   return chunks_per_seq >= 1 && chunks_per_seq <= kWavesPerGroup ? (int)chunks_per_seq : 0;
@@ -1210,6 +1524,15 @@ int launch_fused(const dapq_shape* s, const ScorePlan& plan, ScoreParams p, hipS
 #undef DAPQ_LAUNCH_F
   DAPQ_HIP_LAUNCH_CHECK("score_fused_kernel");
   return DAPQ_OK;
+}
+
+// Whether pass 2 of the tile form merges the partials itself: the threads of a workgroup can hold every sequence's, and
+// there is a compute unit for every workgroup (4096 keys of one layer: 18.7 -> 17.6 us; 8191, two workgroups to a compute
+// unit: 25.5 -> 27.2).
+bool tile_merges(const dapq_shape* s, const ScorePlan& plan) {
+  if (!plan.tile || plan.max_chunks * s->n_kv_heads * s->n_layers > simd_count() / 4) return false;
+  const int64_t longest = s->cu_seqlens == nullptr ? s->total_tokens / s->batch : s->total_tokens;
+  return (longest + plan.chunk_keys - 1) / plan.chunk_keys <= tile_merge_chunks(plan.rows_pad, (int)tile_threads(plan).x);
 }
 
 int check_workspace(void* workspace, size_t workspace_bytes, const ScorePlan& plan) {
@@ -1306,6 +1629,24 @@ extern "C" DAPQ_API int dapq_score(const dapq_shape* shape, const void* q, const
     p.scores = scores;
     return launch_fused(shape, plan, p, static_cast<hipStream_t>(stream));
   }
+  if (tile_merges(shape, plan)) {
+    if ((rc = aligned16(q, "q")) != DAPQ_OK) return rc;
+    if ((rc = aligned16(k, "k")) != DAPQ_OK) return rc;
+    ScoreParams p;
+    fill_params(shape, plan, &p);
+    char* ws = static_cast<char*>(workspace);
+    p.q = static_cast<const uint16_t*>(q);
+    p.k = static_cast<const uint16_t*>(k);
+    p.cu_chunks = reinterpret_cast<int32_t*>(ws + plan.off_cu_chunks);
+    p.work = reinterpret_cast<unsigned*>(ws + plan.off_work);
+    p.parts = reinterpret_cast<float2*>(ws + plan.off_parts);
+    p.partial = nullptr;
+    p.lse2 = nullptr;
+    p.scores = scores;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if ((rc = launch_stats(shape, plan, p, st)) != DAPQ_OK) return rc;
+    return launch_accumulate(shape, plan, p, st);
+  }
   float* lse2 = reinterpret_cast<float*>(static_cast<char*>(workspace) + plan.off_lse2);
   if ((rc = dapq_score_stats(shape, q, k, lse2, workspace, workspace_bytes, stream)) != DAPQ_OK) return rc;
   return dapq_score_accumulate(shape, q, k, lse2, scores, workspace, workspace_bytes, stream);
@@ -1343,10 +1684,11 @@ extern "C" DAPQ_API int dapq_score_stats_extend(const dapq_shape* shape, const v
   pp.kp = static_cast<const uint16_t*>(k_pseudo);
   pp.stride_layer = kp_stride_layer; pp.stride_seq = kp_stride_seq;
   pp.stride_head = kp_stride_head; pp.stride_row = kp_stride_row;
-  const dim3 grid((unsigned)shape->batch, (unsigned)plan.n_groups, (unsigned)(shape->n_layers * shape->n_kv_heads));
+  const RowSplit split = wave_row_split(plan.rows);
+  const dim3 grid((unsigned)shape->batch, (unsigned)split.n_groups, (unsigned)(shape->n_layers * shape->n_kv_heads));
   hipStream_t st = static_cast<hipStream_t>(stream);
-  if (plan.row_blocks == 2) hipLaunchKernelGGL(score_wave_pseudo_kernel<2>, grid, dim3(64), kSubBytes, st, p, pp);
-  else if (plan.row_blocks == 4) hipLaunchKernelGGL(score_wave_pseudo_kernel<4>, grid, dim3(64), kSubBytes, st, p, pp);
+  if (split.row_blocks == 2) hipLaunchKernelGGL(score_wave_pseudo_kernel<2>, grid, dim3(64), kSubBytes, st, p, pp);
+  else if (split.row_blocks == 4) hipLaunchKernelGGL(score_wave_pseudo_kernel<4>, grid, dim3(64), kSubBytes, st, p, pp);
   else hipLaunchKernelGGL(score_wave_pseudo_kernel<8>, grid, dim3(64), kSubBytes, st, p, pp);
   DAPQ_HIP_LAUNCH_CHECK("score_wave_pseudo_kernel");
   return DAPQ_OK;
