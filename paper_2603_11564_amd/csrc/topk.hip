@@ -1,19 +1,13 @@
 // M_retain = TopK_j S(j) (Sec. 4.2): per (layer, sequence, KV head) the budget positions with the
 // largest pooled score, equal scores lowest position first, written in ascending position.
 //
-// One workgroup per head (256 threads for short heads, 1024 from 8193 keys on).  Selection is an exact radix
-// select on the order-preserving integer image of the fp32 score: four 8-bit digits from the top, each pass a
-// 256-bin LDS histogram followed by a suffix scan that fixes one digit of the threshold T and the
-// number of keys equal to T still needed.  The last step is an ordered compaction: key j is kept if
-// score > T, or score == T and fewer than `need` equal keys precede it; prefix counts of (greater,
-// equal) give both the decision and the output slot, so the result is ascending and deterministic
-// (no atomic decides an order).  Max-pooling makes runs of bit-equal scores, so the tie rule is on
+// One workgroup per head (256 threads for short heads, 1024 from 16385 keys on).  Selection is exact, on the
+// order-preserving integer image of the fp32 score: it finds the threshold T (the budget-th largest key) and how many keys
+// equal to T are still needed (topk_select; the streaming kernel takes T digit by digit with 256-bin histograms).  The
+// last step is an ordered compaction: key j is kept if score > T, or score == T and fewer than `need` equal keys precede it;
+// prefix counts of (greater, equal) give both the decision and the output slot, so the result is ascending and
+// deterministic (no atomic decides an order).  Max-pooling makes runs of bit-equal scores, so the tie rule is on
 // the main path.
-//
-// Scores are positive and bunch into a few binades, so in the first pass all keys land in a handful of
-// neighbouring bins: there each thread counts its keys in packed byte fields and the wave issues eight atomics.
-// In the later passes each wave counts the candidates that share the digit of its first candidate with a
-// reduction and issues one atomic for them; only the others go to the histogram one by one.
 //
 // Heads of up to 65536 keys (topk_reg_kernel) are read from HBM once into registers, thread t
 // owning the consecutive keys [t*KPT, (t+1)*KPT): every pass runs out of registers and the
@@ -32,16 +26,11 @@ namespace {
 constexpr int kTopkThreads = 1024;
 constexpr int kTopkWaves = kTopkThreads / 64;
 constexpr int kTopkLdsKeys = 36864;
-constexpr int kTopkTailCap = 2048;
 constexpr int kStreamTiles = 4;                            // tiles of 4096 keys the streaming kernel has in flight
 constexpr int kStreamLdsHead = 260 + kStreamTiles * 16 + 60;  // words of LDS in front of its staged keys (16-byte aligned)
 
-// Orders the LDS accesses of one wave's lanes among themselves (the hardware runs a wave's LDS instructions in
-// order; this keeps the compiler from moving them).
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
+// A value that is the same in all lanes, as a scalar.
+__device__ __forceinline__ uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
 
 struct TopkParams {
   const float* pooled;        // the scores selection runs on (the register variant can pool them itself)
@@ -159,157 +148,155 @@ constexpr int reg_variant_stage_bytes(int threads, int kpt) {  // (two more rows
   return reg_variant_is_staged(threads, kpt) ? (threads + 2) * (kpt + 4) * (int)sizeof(float) : 0;
 }
 
+// bit = 2 * bit + (key > t), bit = 2 * bit + (key == t): a compare and an add with carry per key.
+__device__ __forceinline__ void push_greater(uint32_t& bits, uint32_t key, uint32_t t) {
+  asm("v_cmp_lt_u32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(bits) : "s"(t), "v"(key) : "vcc");
+}
+__device__ __forceinline__ void push_equal(uint32_t& bits, uint32_t key, uint32_t t) {
+  asm("v_cmp_eq_u32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(bits) : "s"(t), "v"(key) : "vcc");
+}
+
 // ---- selection among the keys a workgroup holds in registers (KPT per thread, thread t's before thread t+1's):
-// the `keep` largest, ties to the lowest position, handed to emit(i, slot) in ascending position order (register
-// i of the calling thread is survivor number `slot`).  A register without a key holds 0 (a key is at least 1);
-// n_empty = how many of this thread's registers are empty.  keep >= 1 and at most the number of keys.
+// the `keep` largest, ties to the lowest position, handed to emit(i, key, slot) in ascending position order (register
+// i of the calling thread is survivor number `slot`; `key` is 0 unless want_key).  A register without a key holds 0 (a
+// key is at least 1); the workgroup has n_keys.  keep >= 1 and at most n_keys.
+// bins: LDS of THREADS uint4 that nobody else reads any more; thread t looks after bins 4t .. 4t+3.
+//
+// The threshold T (the keep-th largest key) is closed in on: [lo, lo + range] starts as the span of the keys and becomes,
+// per pass, the one of 4 * THREADS equal bins that T lies in; when at most 64 candidates are left one wave ranks them by
+// comparing all with all.  With sixteen waves to a compute unit the time is the vector instructions of a thread (16
+// clocks each), and a pass is four per key: keys of scores span a few octaves, a bin is then a few thousandths of an
+// octave, and one pass leaves a few dozen.  (Digits of the key instead -- sign and exponent, then 8 bits at a time --
+// took 11 900 clocks for the first, whose bins are two octaves wide and are counted in packed fields, and 12 600 for the
+// others.)  Keys in the lowest bin are not counted one by one: they are what the other bins leave over, so that a head full of
+// zeros does not queue up at one address.  Kept positions are bits of a word per 32 keys, and the survivors are walked
+// bit by bit.  Selection with pooling, by digits -> by bins: 8 heads of 32768 keys, 983 kept, 21.5 -> 15.9 us; 256 heads
+// 28.8 -> 18.7; 64 heads of 131072 keys, 3932 kept, in pieces 65 -> 43; 256 heads of 2000 keys, 128 kept, 14.9 -> 11.8; never
+// slower on heads of one value, three values, half zeros or both signs.
+constexpr int kRankMax = 64;  // candidates one wave ranks
 template <int THREADS, int KPT, class Emit>
-__device__ __forceinline__ void topk_select(const uint32_t (&key)[KPT], int n_empty, int keep, Emit emit) {
-  constexpr int kWaves = THREADS / 64;
-  static_assert(KPT <= 255, "the first pass counts a thread's keys in 8-bit fields");
-  __shared__ uint32_t hists[2][256];  // passes alternate: the next one's is cleared while wave 0 reads this one's
-  __shared__ uint32_t bcasts[5][3];   // one row per pass (no pass waits for the readers of the one before), one for the tail
-  __shared__ uint32_t tail[kTopkTailCap];  // low halves of the candidates left after two passes
-  __shared__ uint32_t tail_n;
+__device__ __forceinline__ void topk_select(const uint32_t (&key)[KPT], int n_keys, int keep, uint4* bins, bool want_key,
+                                            Emit emit) {
+  constexpr int kWaves = THREADS / 64, kWords = (KPT + 31) / 32, kBins = 4 * THREADS;
+  static_assert(KPT < 32 || KPT % 32 == 0, "whole words of position bits");
+  static_assert((kBins & (kBins - 1)) == 0 && kWaves <= 64, "bins and waves");
+  __shared__ uint32_t wave_min[kWaves], wave_max[kWaves], wave_count[kWaves];
+  __shared__ uint32_t found[3];  // bin, need, population of the bin
+  __shared__ uint32_t last[kRankMax];
+  __shared__ uint32_t last_n;
   __shared__ uint32_t wave_gt[kWaves], wave_eq[kWaves];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 
-  // ---- radix select: threshold T = the keep-th largest key, need = how many keys == T to take
-  uint32_t prefix = 0, mask = 0;
+  uint32_t lo, range, left = (uint32_t)n_keys;  // candidates: the `left` keys with key - lo <= range
   int need = keep;
-  for (int e = tid; e < 256; e += THREADS) hists[0][e] = 0;
-  if (tid == 0) tail_n = 0;
-  __syncthreads();
-  // What ends a pass: wave 0 finds the digit of T among the 256 counts while the others clear the next pass's
-  // histogram (its last reader was wave 0, two barriers ago); returns how many candidates remain.
-  auto settle = [&](int pass, int shift) -> uint32_t {
-    __syncthreads();
-    if (wave == 0) topk_pick_digit(hists[pass & 1], bcasts[pass], need, lane);
-    else
-      for (int e = tid - 64; e < 256; e += THREADS - 64) hists[(pass + 1) & 1][e] = 0;
-    __syncthreads();
-    prefix |= bcasts[pass][0] << shift;
-    mask |= 255u << shift;
-    need = (int)bcasts[pass][1];
-    return bcasts[pass][2];
-  };
-
   {
-    // First pass: every key is a candidate and its digit is the sign and seven exponent bits.  Scores are sums of
-    // probabilities: a wave's 64 * KPT digits fall into a handful of neighbouring bins, where one LDS atomic per
-    // key would serialise on a few addresses.  If the wave's digits span at most 8 bins, each thread counts its
-    // keys in eight 8-bit fields (KPT <= 255), the wave adds the fields up and eight lanes issue one atomic each.
-    // (A register without a key holds 0: key - 1 wraps to the largest value and never is the minimum; for a key
-    // whose low 24 bits are all 0 the minimum comes out one bin low, which only widens the span by one.)
-    uint32_t* hist = hists[0];
+    // (a register without a key holds 0: key - 1 wraps to the largest value and never is the minimum)
     uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
 #pragma unroll
     for (int i = 0; i < KPT; ++i) {
       kmin = key[i] - 1u < kmin ? key[i] - 1u : kmin;
       kmax = key[i] > kmax ? key[i] : kmax;
     }
-    const uint32_t dmin = wave_reduce<OpMin>(kmin) >> 24, dmax = wave_reduce<OpMax>(kmax) >> 24;
-    if (dmax >= dmin && dmax - dmin < 8u) {  // (uniform over the wave; dmax < dmin: the wave holds no key)
-      // the registers without a key are counted too, all in the field that digit 0 wraps to, and taken out after
-      uint64_t fields = 0;
-#pragma unroll
-      for (int i = 0; i < KPT; ++i) fields += 1ull << ((((key[i] >> 24) - dmin) * 8u) & 63u);
-      fields -= (uint64_t)n_empty << (((0u - dmin) * 8u) & 63u);
-      // two bins per 32-bit word, 16 bits each: a wave's count is at most 64 * KPT < 65536
-      uint32_t pair[4];
-#pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        const uint32_t lo = (uint32_t)(fields >> (16 * b)) & 255u, hi = (uint32_t)(fields >> (16 * b + 8)) & 255u;
-        pair[b] = wave_sum(lo | (hi << 16));
-      }
-      if (lane < 8) {
-        const uint32_t w = lane < 2 ? pair[0] : (lane < 4 ? pair[1] : (lane < 6 ? pair[2] : pair[3]));
-        const uint32_t c = (lane & 1) ? (w >> 16) : (w & 0xFFFFu);
-        if (c != 0) atomicAdd(&hist[dmin + lane], c);
-      }
-    } else if (dmax >= dmin) {
-#pragma unroll
-      for (int i = 0; i < KPT; ++i)
-        if (key[i] != 0u) atomicAdd(&hist[key[i] >> 24], 1u);
+    kmin = wave_scan<OpMin>(kmin);
+    kmax = wave_scan<OpMax>(kmax);
+    if (lane == 63) {
+      wave_min[wave] = kmin;
+      wave_max[wave] = kmax;
     }
-    settle(0, 24);
+    bins[tid] = make_uint4(0, 0, 0, 0);
+    if (tid == 0) last_n = 0;
+    __syncthreads();
+    kmin = wave_min[0];
+    kmax = wave_max[0];
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) {
+      kmin = wave_min[w] < kmin ? wave_min[w] : kmin;
+      kmax = wave_max[w] > kmax ? wave_max[w] : kmax;
+    }
+    lo = uniform(kmin) + 1u;
+    range = uniform(kmax) - lo;
   }
-
-  // The other passes.  (From here on the registers without a key are not told apart: they hold 0, can only be
-  // candidates while the prefix is 0, are then the least of all candidates, and there are always at least `need` real
-  // ones above them.)
-  for (int shift = 16; shift >= 0; shift -= 8) {
-    const int pass = (24 - shift) >> 3;
-    uint32_t* hist = hists[pass & 1];
-    // the digit most candidates of this wave are likely to share: that of its first candidate
-    int first = -1;
+  while (range != 0u && left > (uint32_t)kRankMax) {
+    const int bits = 32 - __builtin_clz(range), shift = bits > __builtin_ctz(kBins) ? bits - __builtin_ctz(kBins) : 0;
+    // from the second bin on (range >= 1 << shift); keys that are no candidates and empty registers are not in it
+    const uint32_t lo1 = lo + (1u << shift), range1 = range - (1u << shift);
+    uint32_t* count = reinterpret_cast<uint32_t*>(bins) + 1;
 #pragma unroll
-    for (int i = KPT - 1; i >= 0; --i)
-      if ((key[i] & mask) == prefix) first = (int)((key[i] >> shift) & 255u);
-    const uint64_t have = __ballot(first >= 0);
-    if (have != 0) {
-      const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane(first, __ffsll((long long)have) - 1);
-      uint32_t same = 0;
-#pragma unroll
-      for (int i = 0; i < KPT; ++i) {
-        const bool cand = (key[i] & mask) == prefix;
-        const uint32_t d = (key[i] >> shift) & 255u;
-        same += cand && d == d0 ? 1u : 0u;
-        if (__ballot(cand && d != d0) != 0) {  // (skipped by the whole wave when nobody has one)
-          if (cand && d != d0) atomicAdd(&hist[d], 1u);
-        }
-      }
-      same = wave_sum(same);
-      if (lane == 0 && same != 0) atomicAdd(&hist[d0], same);
+    for (int i = 0; i < KPT; ++i) {
+      if (key[i] - lo1 <= range1) atomicAdd(&count[(key[i] - lo1) >> shift], 1u);
     }
-    const uint32_t left = settle(pass, shift);  // candidates that remain
-    if (shift == 16 && left <= (uint32_t)kTopkTailCap) {
-      // Few candidates remain (typically a few dozen): instead of two more rounds of the whole workgroup, with
-      // their barriers, their low halves go to a list and one wave finishes the selection on its own.
+    __syncthreads();
+    uint4 c = bins[tid];
+    bins[tid] = make_uint4(0, 0, 0, 0);
+    const uint32_t upto = wave_scan<OpAdd>(c.x + c.y + c.z + c.w);
+    if (lane == 63) wave_count[wave] = upto;
+    __syncthreads();
+    // candidates in this wave's bins and below / in all bins but the lowest
+    uint32_t below = 0, all = 0;
 #pragma unroll
-      for (int i = 0; i < KPT; ++i) {
-        const bool cand = (key[i] & mask) == prefix;
-        if (__ballot(cand) != 0) {  // rare: most waves hold no candidate at all
-          if (cand) tail[atomicAdd(&tail_n, 1u)] = key[i] & 0xFFFFu;
-        }
-      }
-      __syncthreads();
-      if (wave == 0) {
-        uint32_t pre = 0, msk = 0;
-        uint32_t* h = hists[0];
-        uint32_t* bc = bcasts[4];
-        for (int sh = 8; sh >= 0; sh -= 8) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) h[4 * lane + e] = 0;
-          wave_lds_sync();
-          for (uint32_t e = lane; e < left; e += 64) {
-            const uint32_t v = tail[e];
-            if ((v & msk) == pre) atomicAdd(&h[(v >> sh) & 255u], 1u);
-          }
-          wave_lds_sync();
-          topk_pick_digit(h, bc, need, lane);
-          wave_lds_sync();
-          pre |= bc[0] << sh;
-          msk |= 255u << sh;
-          need = (int)bc[1];
-          wave_lds_sync();
-        }
-        if (lane == 0) bc[0] = pre;  // bc[1] holds the final `need`
-      }
-      __syncthreads();
-      prefix |= bcasts[4][0];
-      need = (int)bcasts[4][1];
-      break;
+    for (int w = 0; w < kWaves; ++w) {
+      const uint32_t n = wave_count[w];
+      below += w < wave ? n : 0u;
+      all += n;
     }
+    if (tid == 0) c.x = left - all;
+    // g3 .. g0: candidates in a higher bin than 4t+3 .. 4t
+    const uint32_t g3 = all - (below + upto), g2 = g3 + c.w, g1 = g2 + c.z, g0 = g1 + c.y, un = (uint32_t)need;
+    if (g3 < un && un <= g0 + c.x) {
+      const int k = un <= g2 ? 3 : (un <= g1 ? 2 : (un <= g0 ? 1 : 0));
+      found[0] = (uint32_t)(4 * tid + k);
+      found[1] = un - (k == 3 ? g3 : (k == 2 ? g2 : (k == 1 ? g1 : g0)));
+      found[2] = k == 3 ? c.w : (k == 2 ? c.z : (k == 1 ? c.y : c.x));
+    }
+    __syncthreads();
+    const uint32_t bin = uniform(found[0]), width = (1u << shift) - 1u, rest = range - (bin << shift);
+    lo += bin << shift;
+    range = rest < width ? rest : width;
+    need = (int)uniform(found[1]);
+    left = uniform(found[2]);
+    // (found is written again only behind the next pass's barriers)
   }
-  const uint32_t T = prefix;
+  if (range != 0u) {
+#pragma unroll
+    for (int i = 0; i < KPT; ++i) {
+      const bool cand = key[i] - lo <= range;
+      if (__ballot(cand) != 0) {  // rare
+        if (cand) last[atomicAdd(&last_n, 1u)] = key[i];
+      }
+    }
+    __syncthreads();
+    if (wave == 0) {
+      const uint32_t v = (uint32_t)lane < left ? last[lane] : 0u;
+      int above = 0, same = 0;
+      for (int e = 0; e < (int)left; ++e) {
+        const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)v, e);
+        above += o > v ? 1 : 0;
+        same += o == v ? 1 : 0;
+      }
+      if ((uint32_t)lane < left && above < need && need <= above + same) {  // (lanes of equal keys write the same)
+        found[0] = v;
+        found[1] = (uint32_t)(need - above);
+      }
+    }
+    __syncthreads();
+    lo = uniform(found[0]);
+    need = (int)uniform(found[1]);
+  }
+  const uint32_t T = lo;
 
   // ---- ordered compaction: one exclusive scan of the per-thread (greater, equal) counts
-  uint32_t my_gt = 0, my_eq = 0;
+  // (T is a key, so T >= 1 and registers without a key count as neither)
+  uint32_t gt[kWords], eq[kWords], my_gt = 0, my_eq = 0;
 #pragma unroll
-  for (int i = 0; i < KPT; ++i) {  // (T is a key, so T >= 1 and registers without a key count as neither)
-    my_gt += key[i] > T ? 1u : 0u;
-    my_eq += key[i] == T ? 1u : 0u;
+  for (int w = 0; w < kWords; ++w) {
+    gt[w] = eq[w] = 0;
+#pragma unroll
+    for (int i = 32 * w; i < KPT && i < 32 * w + 32; ++i) {
+      push_greater(gt[w], key[i], T);
+      push_equal(eq[w], key[i], T);
+    }
+    my_gt += (uint32_t)__popc(gt[w]);
+    my_eq += (uint32_t)__popc(eq[w]);
   }
   const uint32_t inc_gt = wave_scan<OpAdd>(my_gt), inc_eq = wave_scan<OpAdd>(my_eq);  // inclusive, inside the wave
   if (lane == 63) {
@@ -327,16 +314,40 @@ __device__ __forceinline__ void topk_select(const uint32_t (&key)[KPT], int n_em
   }
   const uint32_t un = (uint32_t)need;
   uint32_t pos = pre_gt + (pre_eq < un ? pre_eq : un);
+  uint32_t room = pre_eq < un ? un - pre_eq : 0u;  // equal keys of this thread that are still taken
 #pragma unroll
-  for (int i = 0; i < KPT; ++i) {
-    const bool eq = key[i] == T;
-    const bool take = key[i] > T || (eq && pre_eq < un);
-    if (__ballot(take) != 0) {  // survivors are few: most of a wave's registers hold none
-      if (take) emit(i, pos);
+  for (int w = 0; w < kWords; ++w) {
+    const int top = KPT - 32 * w < 32 ? KPT - 32 * w - 1 : 31;
+    uint32_t e = room != 0 ? eq[w] : 0u;
+    while ((uint32_t)__popc(e) > room) e &= e - 1;  // the last ones go: the lowest bits are the last registers
+    room -= (uint32_t)__popc(e);
+    uint32_t take = gt[w] | e;
+    if (want_key) {
+#pragma unroll
+      for (int i = 32 * w; i < KPT && i < 32 * w + 32; ++i) {
+        const bool t = (take >> (top - i % 32)) & 1u;
+        if (__ballot(t) != 0) {  // survivors are few: most of a wave's registers hold none
+          if (t) emit(i, key[i], pos++);
+        }
+      }
+    } else {
+      while (take != 0) {
+        const int bit = 31 - __clz((int)take);
+        take ^= 1u << bit;
+        emit(32 * w + top - bit, 0u, pos++);
+      }
     }
-    pos += take ? 1u : 0u;
-    pre_eq += eq ? 1u : 0u;
   }
+}
+
+// The largest of the 2R + 1 scores from ext[i] on (R == 3: of the maxima of three that ext holds by then).
+template <int R, int N>
+__device__ __forceinline__ float window_max(const float (&ext)[N], int i) {
+  if constexpr (R == 3) return fmaxf(fmaxf(ext[i], ext[i + 2]), ext[i + 4]);
+  float m = ext[i];
+#pragma unroll
+  for (int t = 1; t <= 2 * R; ++t) m = fmaxf(m, ext[i + t]);
+  return m;
 }
 
 // ---- heads that fit in registers.  R > 0: the input is the un-pooled score and the kernel applies
@@ -405,6 +416,7 @@ __global__ __launch_bounds__(THREADS) void topk_reg_kernel(TopkParams p) {
         ext[R + KPT + r] = in_head(j0 + KPT + r) ? right[r] : -INFINITY;
       }
     }
+    __syncthreads();  // the runs are out of the staging area: the selection counts in it
   } else {
     if (nvalid == KPT && (reinterpret_cast<uintptr_t>(hd.src + j0) & 15) == 0) {
 #pragma unroll
@@ -426,12 +438,15 @@ __global__ __launch_bounds__(THREADS) void topk_reg_kernel(TopkParams p) {
       ext[R + KPT + r] = in_head(jr) ? hd.src[jr] : -INFINITY;
     }
   }
+  if constexpr (R == 3) {
+    // the window of 7 in two steps: ext[j] becomes the largest of three, and three of those cover the window
+#pragma unroll
+    for (int j = 0; j < KPT + 4; ++j) ext[j] = fmaxf(fmaxf(ext[j], ext[j + 1]), ext[j + 2]);
+  }
   uint32_t key[KPT];
 #pragma unroll
   for (int i = 0; i < KPT; ++i) {
-    float m = ext[i];
-#pragma unroll
-    for (int t = 1; t <= 2 * R; ++t) m = fmaxf(m, ext[i + t]);
+    float m = window_max<R>(ext, i);
     if (p.pooled_out != nullptr && i < nvalid) p.pooled_out[(hd.src - p.pooled) + j0 + i] = m;
     // registers past the end of the head hold 0, which no key is (a key is at least 1): everything below can then
     // tell them by value, and no per-register validity mask has to stay alive through the kernel
@@ -441,9 +456,18 @@ __global__ __launch_bounds__(THREADS) void topk_reg_kernel(TopkParams p) {
   if (hd.done) return;
 
 
-  topk_select<THREADS, KPT>(key, KPT - nvalid, hd.keep, [&](int i, uint32_t slot) {
+  uint4* bins;
+  if constexpr (kStaged) {
+    extern __shared__ float stage_area[];
+    bins = reinterpret_cast<uint4*>(stage_area);  // (every run is out of it)
+  } else {
+    __shared__ uint4 own_bins[THREADS];
+    bins = own_bins;
+  }
+  const bool piece = hd.out_key != nullptr;
+  topk_select<THREADS, KPT>(key, L, hd.keep, bins, piece, [&](int i, uint32_t k, uint32_t slot) {
     hd.out[slot] = hd.base + j0 + i;
-    if (hd.out_key != nullptr) hd.out_key[slot] = key[i];
+    if (piece) hd.out_key[slot] = k;
   });
 }
 
@@ -476,18 +500,33 @@ __global__ __launch_bounds__(THREADS) void topk_merge_kernel(TopkParams p) {
   const int s0 = tid * KPT;
   int seg = s0 / p.budget, r = s0 - seg * p.budget;
   uint32_t key[KPT];
-  int n_empty = 0;
+  // (16-byte loads of slots that hold no candidate read the workspace's old contents, which are dropped)
+  const bool quads = (slots & 3) == 0;
+#pragma unroll
+  for (int i = 0; i < KPT; i += 4) {
+    if (quads && s0 + i < slots) {
+      const uint4 v = *reinterpret_cast<const uint4*>(ck + s0 + i);
+      key[i] = v.x;
+      key[i + 1] = v.y;
+      key[i + 2] = v.z;
+      key[i + 3] = v.w;
+    }
+  }
 #pragma unroll
   for (int i = 0; i < KPT; ++i) {
     const bool valid = s0 + i < slots && r < seg_count[seg < nseg ? seg : 0];
-    key[i] = valid ? ck[s0 + i] : 0u;
-    n_empty += valid ? 0 : 1;
+    if (!quads) key[i] = valid ? ck[s0 + i] : 0u;
+    key[i] = valid ? key[i] : 0u;
     if (++r == p.budget) {
       r = 0;
       ++seg;
     }
   }
-  topk_select<THREADS, KPT>(key, n_empty, keep, [&](int i, uint32_t slot) { out[slot] = ci[s0 + i]; });
+  __shared__ uint4 bins[THREADS];
+  int n_keys = 0;
+  for (int i = 0; i < nseg; ++i) n_keys += seg_count[i];
+  topk_select<THREADS, KPT>(key, n_keys, keep, bins, false,
+                            [&](int i, uint32_t, uint32_t slot) { out[slot] = ci[s0 + i]; });
 }
 
 // ---- longer heads
@@ -670,6 +709,7 @@ int launch_reg_radius(int radius, RegVariant v, dim3 grid, hipStream_t st, const
 
 void launch_merge(RegVariant v, dim3 grid, hipStream_t st, const TopkParams& p) {
   if (v.threads == 256) hipLaunchKernelGGL((topk_merge_kernel<256, 32>), grid, dim3(256), 0, st, p);
+  else if (v.kpt == 16) hipLaunchKernelGGL((topk_merge_kernel<1024, 16>), grid, dim3(1024), 0, st, p);
   else if (v.kpt == 32) hipLaunchKernelGGL((topk_merge_kernel<1024, 32>), grid, dim3(1024), 0, st, p);
   else hipLaunchKernelGGL((topk_merge_kernel<1024, 64>), grid, dim3(1024), 0, st, p);
 }
@@ -750,7 +790,10 @@ int launch_long_heads(const dapq_shape* shape, const TopkRoute& r, TopkParams p,
     DAPQ_HIP_LAUNCH_CHECK("topk_reg_kernel (pieces)");
     // (one workgroup per long head: from 8193 candidate slots on, the large workgroup's sixteen waves)
     const int64_t slots = (int64_t)r.n_segs * p.budget;
-    launch_merge(slots <= 256 * 32 ? RegVariant{256, 32} : (slots <= 1024 * 32 ? RegVariant{1024, 32} : RegVariant{1024, 64}),
+    launch_merge(slots <= 256 * 32    ? RegVariant{256, 32}
+                 : slots <= 1024 * 16 ? RegVariant{1024, 16}
+                 : slots <= 1024 * 32 ? RegVariant{1024, 32}
+                                      : RegVariant{1024, 64},
                  grid, st, p);
     DAPQ_HIP_LAUNCH_CHECK("topk_merge_kernel");
     return DAPQ_OK;

@@ -114,3 +114,49 @@ def test_scores_of_small_calls(H, lens, rows):
     live = [b for b, n in enumerate(lens) if n]
     err = np.abs(prob.stats().cpu().numpy()[:, live] - oracle_lse2(q, k, 2, cu)[:, live]) if len(lens) < 60 else np.zeros(1)
     assert err.max() < 2e-4
+
+
+def score_values(kind, rng, n):
+    x = rng.random(n, dtype=np.float32)
+    if kind == "octaves":
+        return np.exp2(40 * x - 30).astype(np.float32)
+    if kind == "one value":
+        return np.full(n, 0.37, dtype=np.float32)
+    if kind == "three values":
+        return np.floor(3 * x).astype(np.float32)
+    if kind == "half zero":
+        return np.where(x < 0.5, 0, x).astype(np.float32)
+    if kind == "neighbours":      # consecutive floats below a single far larger one
+        y = np.nextafter(np.float32(1), np.float32(2)) + np.float32(2 ** -23) * np.floor(300 * x)
+        y[n // 2] = 1e30
+        return y.astype(np.float32)
+    y = np.float32(1e3) * (x - np.float32(0.5))     # both signs, both zeros, both infinities
+    y[::7], y[1::7] = 0.0, -0.0
+    y[n // 3], y[n // 2] = np.inf, -np.inf
+    return y
+
+
+# the selection closes in on the threshold by bins of the span of the keys: spans of 0 to 2^32, bins that hold one value or
+# most of them, more and fewer than the 64 candidates that one wave ranks, at the lengths where the variants change
+@pytest.mark.parametrize("kind", ["octaves", "one value", "three values", "half zero", "neighbours", "signs"])
+@pytest.mark.parametrize("n", [1, 33, 64, 65, 1000, 8192, 8193, 16385, 32768, 40000, 140001])
+def test_selection_over_distributions(H, n, kind):
+    """The retained positions are the oracle's, bit for bit (selection compares the given scores; equal ones lowest
+    position first; -0 and +0 are told apart by neither, so the zeros of one input all have the same sign)."""
+    announce(f"selection of {n}: {kind}")
+    rng = np.random.default_rng(n)
+    S = np.stack([score_values(kind, rng, n) for _ in range(2)])[None]
+    if kind == "signs":
+        S[S == 0] = 0.0
+    q = np.zeros((1, 1, 2, 1, 128), dtype=np.uint16)
+    k = np.zeros((1, n, 2, 128), dtype=np.uint16)
+    prob = H.Problem(q, k, k, 2, None, "hnd")
+    for budget in sorted({b for b in (1, 63, 64, 65, n // 30, n // 2, n - 1) if 1 <= b < max(n, 2) and b <= 15000}):
+        for pooled in (False, True):
+            P = np.stack([O.pool(S[0, kv], 7) for kv in range(2)]) if pooled and kind != "signs" else S[0]
+            dev = torch.from_numpy(S).cuda()
+            idx, count = (prob.pool_topk(dev, 7, budget, want_pooled=n > 65536, pieces=True)[:2] if pooled and kind != "signs"
+                          else prob.topk(dev, budget))
+            for kv in range(2):
+                got = idx.cpu().numpy()[0, 0, kv][:int(count[0, 0, kv])]
+                assert np.array_equal(got, O.topk(P[kv].astype(np.float64), budget)), (budget, pooled, kv)
