@@ -30,6 +30,7 @@
 #include <type_traits>
 
 #include "dapq_internal.h"
+#include "rope_math.h"
 
 namespace dapq {
 namespace {
@@ -294,6 +295,45 @@ __global__ void qproj_reduce_kernel(QprojParams p, int rows_pad, int feat_pad) {
                              (int64_t)row * p.q_stride_row + c) = o;
 }
 
+// The same with the rotation (what rope_kernel would do next, to the same bits): a thread per (layer, head, row, channel
+// pair).  All its loads are in flight before the angle is evaluated, which takes as long as they do.  One layer 4096 wide,
+// 64 rows: sums 4.3 us + rotation 3.7 us -> 3.9 us (two heads to a thread, sharing the angle: 7.3 us); the call 16.7 ->
+// 12.4 us.
+template <int SPLITS>
+__global__ __launch_bounds__(256) void qproj_reduce_rope_kernel(QprojParams p, int rows_pad, int feat_pad, const int32_t* positions,
+                                                                double neg_log2_theta_2_over_d, int pairing) {
+  const int half = p.head_dim / 2, heads = p.n_features / p.head_dim;
+  const int gid = blockIdx.x * 256 + threadIdx.x;
+  if (gid >= p.rows * half) return;
+  const int row = gid / half, c = gid - row * half;
+  const int layer = (int)blockIdx.y / heads, head = (int)blockIdx.y - layer * heads;
+  const int ia = pairing == 0 ? c : 2 * c, ib = pairing == 0 ? c + half : 2 * c + 1;
+  const int64_t plane = (int64_t)p.n_layers * rows_pad * feat_pad;
+  const float* src = p.partial + ((int64_t)layer * rows_pad + row) * feat_pad + (int64_t)head * p.head_dim;
+  float a[SPLITS], b[SPLITS];
+#pragma unroll
+  for (int k = 0; k < SPLITS; ++k) {
+    a[k] = src[k * plane + ia];
+    b[k] = src[k * plane + ib];
+  }
+  const bool has_source = p.token_idx[row] >= 0;
+  const int pos = positions[row];
+  __builtin_amdgcn_sched_barrier(0);
+  double sn, cs;
+  rope_angle(pos, c, neg_log2_theta_2_over_d, &sn, &cs);
+  float sa = a[0], sb = b[0];
+#pragma unroll
+  for (int k = 1; k < SPLITS; ++k) {
+    sa += a[k];
+    sb += b[k];
+  }
+  const double xa = bf16_to_f64(__builtin_bit_cast(uint16_t, (__bf16)(has_source ? sa : 0.0f)));
+  const double xb = bf16_to_f64(__builtin_bit_cast(uint16_t, (__bf16)(has_source ? sb : 0.0f)));
+  uint16_t* dst = p.q + (int64_t)layer * p.q_stride_layer + (int64_t)head * p.q_stride_head + (int64_t)row * p.q_stride_row;
+  dst[ia] = f64_to_bf16(xa * cs - xb * sn);
+  dst[ib] = f64_to_bf16(xb * cs + xa * sn);
+}
+
 template <int FT, int MB>
 void launch_qproj(const QprojParams& p, hipStream_t stream) {
   const int64_t grid = (int64_t)p.tiles_f * p.sweeps * p.k_splits * p.n_layers;
@@ -421,6 +461,18 @@ extern "C" DAPQ_API int dapq_pseudo_queries(const dapq_qproj* desc, const void* 
   else if (pl.mb == 2) launch_qproj<2, 2>(p, st);
   else launch_qproj<2, 1>(p, st);
   DAPQ_HIP_LAUNCH_CHECK("qproj_wave_kernel");
+  const int64_t pairs = (int64_t)s.rows * (s.head_dim / 2), head_layers = (int64_t)s.n_q_heads * s.n_layers;
+  if (pl.k_splits > 1 && positions != nullptr && pairs < ((int64_t)1 << 30) && head_layers <= 65535) {
+    const dim3 grid((unsigned)((pairs + 255) / 256), (unsigned)head_layers);
+    const int rows_pad = pl.sweeps * 32 * pl.mb, feat_pad = pl.tiles_f * 32 * pl.ft;
+    const double e = rope_exponent(theta, s.head_dim);
+    if (pl.k_splits == 2) hipLaunchKernelGGL(qproj_reduce_rope_kernel<2>, grid, dim3(256), 0, st, p, rows_pad, feat_pad, positions, e, pairing);
+    else if (pl.k_splits == 4) hipLaunchKernelGGL(qproj_reduce_rope_kernel<4>, grid, dim3(256), 0, st, p, rows_pad, feat_pad, positions, e, pairing);
+    else if (pl.k_splits == 8) hipLaunchKernelGGL(qproj_reduce_rope_kernel<8>, grid, dim3(256), 0, st, p, rows_pad, feat_pad, positions, e, pairing);
+    else hipLaunchKernelGGL(qproj_reduce_rope_kernel<16>, grid, dim3(256), 0, st, p, rows_pad, feat_pad, positions, e, pairing);
+    DAPQ_HIP_LAUNCH_CHECK("qproj_reduce_rope_kernel");
+    return DAPQ_OK;
+  }
   if (pl.k_splits > 1) {
     const int64_t work = (int64_t)s.n_layers * s.rows * (p.n_features / 4);
     hipLaunchKernelGGL(qproj_reduce_kernel, dim3((unsigned)((work + 255) / 256)), dim3(256), 0, st, p,

@@ -12,26 +12,10 @@
 #include <math.h>
 
 #include "dapq_internal.h"
+#include "rope_math.h"
 
 namespace dapq {
 namespace {
-
-__device__ __forceinline__ double bf16_to_f64(uint16_t b) { return (double)__uint_as_float((uint32_t)b << 16); }
-
-// fp64 -> bf16, round to nearest even, as if in one step: the value is first brought to fp32 with rounding to odd
-// (truncate toward zero, then set the last bit if anything was cut off: the cut-off part can then neither make nor
-// break a tie 16 bits further up), and the 16 low bits are rounded by the hardware conversion.  The truncation is
-// the ordinary (nearest) conversion stepped back by one unit when it went away from zero.
-__device__ __forceinline__ uint16_t f64_to_bf16(double x) {
-  const float f = (float)x;
-  const double back = (double)f;
-  uint32_t u = __float_as_uint(f);
-  if (back != x) {  // inexact (also true for NaN, which stays NaN)
-    if (fabs(back) > fabs(x)) u -= 1u;
-    u |= 1u;
-  }
-  return __builtin_bit_cast(uint16_t, (__bf16)__uint_as_float(u));
-}
 
 __global__ void rope_kernel(const uint16_t* x_in, uint16_t* x_out, const int32_t* __restrict__ pos,
                             int64_t rows, int heads, int head_dim, int64_t stride_row, int64_t stride_head,
@@ -41,9 +25,8 @@ __global__ void rope_kernel(const uint16_t* x_in, uint16_t* x_out, const int32_t
   if (gid >= rows * half) return;
   const int64_t row = gid / half;
   const int c = (int)(gid - row * half);
-  const double omega = exp2((double)c * neg_log2_theta_2_over_d);  // theta^(-2c/d)
   double sn, cs;
-  sincos((double)pos[row] * omega, &sn, &cs);
+  rope_angle(pos[row], c, neg_log2_theta_2_over_d, &sn, &cs);
   const int ia = pairing == 0 ? c : 2 * c;
   const int ib = pairing == 0 ? c + half : 2 * c + 1;
   const uint16_t* src = x_in + row * stride_row;
@@ -141,7 +124,7 @@ extern "C" DAPQ_API int dapq_rope_apply(const void* x_in, void* x_out, const int
   while (hpt < 64 && hpt * 2 <= heads && (work / 64) * ((heads + 2 * hpt - 1) / (2 * hpt)) >= 4096) hpt *= 2;
   const int64_t head_runs = ((int64_t)heads + hpt - 1) / hpt;
   DAPQ_REQUIRE(head_runs <= 65535, DAPQ_ERR_UNSUPPORTED, "heads (%d) exceeds %d", heads, 65535 * hpt);
-  const double e = -2.0 * log2(theta) / (double)head_dim;
+  const double e = rope_exponent(theta, head_dim);
   hipLaunchKernelGGL(rope_kernel, dim3((unsigned)((work + 255) / 256), (unsigned)head_runs), dim3(256), 0,
                      static_cast<hipStream_t>(stream),
                      static_cast<const uint16_t*>(x_in), static_cast<uint16_t*>(x_out), pos, rows, heads, head_dim,
