@@ -4,7 +4,8 @@
 // One thread owns one (row, channel pair) and a run of heads: it evaluates the angle
 // pos * theta^(-2c/d) and its sine / cosine once in fp64 and then walks its heads, so the
 // transcendental work (more than ten times the work of one rotation) is shared by the heads of a
-// run; runs are 8 heads long, longer (up to 64) while the launch still has thousands of waves.
+// run; runs are 8 heads long, longer (up to 64) while the launch still has thousands of waves, shorter while it has fewer
+// than a thousand.
 // fp64 keeps the angle exact enough at positions beyond 10^5 (an fp32 product pos * omega would be
 // off by ~1e-2 rad there); the rotation is done in fp64 as well and rounded to bf16 once, which is
 // what makes the result equal to a float64 evaluation bit for bit, and what the kernel's time goes
@@ -122,6 +123,8 @@ extern "C" DAPQ_API int dapq_rope_apply(const void* x_in, void* x_out, const int
   if (work == 0) return DAPQ_OK;
   int hpt = 8;
   while (hpt < 64 && hpt * 2 <= heads && (work / 64) * ((heads + 2 * hpt - 1) / (2 * hpt)) >= 4096) hpt *= 2;
+  // small calls: shorter runs until there is a wave per SIMD (64 rows x 32 heads as part of a score call: 0.5 to 1 us of 3.5)
+  while (hpt > 1 && hpt <= 8 && (work / 64) * ((heads + hpt - 1) / hpt) < 1024) hpt /= 2;
   const int64_t head_runs = ((int64_t)heads + hpt - 1) / hpt;
   DAPQ_REQUIRE(head_runs <= 65535, DAPQ_ERR_UNSUPPORTED, "heads (%d) exceeds %d", heads, 65535 * hpt);
   const double e = rope_exponent(theta, head_dim);
