@@ -128,8 +128,12 @@ int make_score_plan(const dapq_shape* s, ScorePlan* p) {
   // wave pays a fixed start-up (Q fragments, ring fill) worth about kStartKeys keys.  Dense batches
   // run in whole rounds of equal chunks: pick the chunk with the shortest rounds x (chunk +
   // start-up).  Ragged batches (lengths unknown on the host) are handed out chunk by chunk to
-  // persistent waves, so the cost is the work per slot plus half a chunk of tail imbalance on average.
-  constexpr int64_t kWaveSlots = 1024, kStartKeys = 160;
+  // persistent waves, so the cost is the work per slot plus half a chunk of tail imbalance on average -- a
+  // sequence shorter than the chunk is a shorter one, so beyond the mean length only half as much again.  Their items
+  // start later too (ticket, look-up, then queries and ring): kStartRagged.  Both passes, chunks of 1024 -> 2048, 32
+  // layers: 16 prompts of 200..2500 keys, 128 rows 754 -> 720 us, 16 of 175..1400, 256 rows 798 -> 703, 8 of 750..6000,
+  // 128 rows 784 -> 736; at 8 of 4096..16384, 512 rows it stays with the 4096 that are best there (2048: 2.5 % more).
+  constexpr int64_t kWaveSlots = 1024, kStartKeys = 160, kStartRagged = 256;
   const int64_t units_per_chunk_row = heads * p->n_groups;
   int chunk = kMinChunkKeys;
   int64_t best = INT64_MAX;
@@ -143,7 +147,9 @@ int make_score_plan(const dapq_shape* s, ScorePlan* p) {
     } else {
       const int64_t chunks = (s->total_tokens + c - 1) / c + s->batch / 2;
       const int64_t units = units_per_chunk_row * chunks;
-      cost = (units_per_chunk_row * s->total_tokens + units * kStartKeys) / kWaveSlots + c / 2;
+      const int64_t mean = s->total_tokens / s->batch;
+      cost = (units_per_chunk_row * s->total_tokens + units * kStartRagged) / kWaveSlots +
+             (c <= mean ? c / 2 : mean / 2 + (c - mean) / 4);
     }
     if (cost < best) {
       best = cost;
@@ -157,9 +163,9 @@ int make_score_plan(const dapq_shape* s, ScorePlan* p) {
   // the chip idle or pays its start-up per chunk (the queries of up to 256 rows into one wave, a ring of its own, tickets).
   // Both passes of dapq_score, wave form -> tile form, 8 KV heads: one layer, 1024 keys, 256 rows 38.6 -> 15.8 us; 8191
   // keys, 128 rows 26.9 -> 19.3; 16384 keys, 256 rows 44 -> 41, 512 rows 57 -> 61; 32768 keys, 128 rows 39 -> 45; ragged,
-  // 8 prompts of 1000 keys, one layer, 128 rows 176 -> 24, 4 layers, 512 rows 188 -> 169 (40 000 units); 32 layers, 16
-  // prompts of 700, 32 rows (30 000 units) 517 -> 440, 128 rows (120 000) 589 -> 597.  Where dapq_score runs both passes in
-  // one kernel it stays with that one.
+  // 8 prompts of 1000 keys, one layer, 128 rows 76 -> 24, 4 layers, 128 rows (10 000 units) 146 -> 59, 512 rows (40 000
+  // units) 188 -> 169; 32 layers, 16 prompts of 700, 128 rows (120 000) 530 -> 597.  Where dapq_score runs both passes in one
+  // kernel it stays with that one.
   const bool ragged = s->cu_seqlens != nullptr;
   const bool one_kernel = !ragged && p->n_groups == 1 && p->max_chunks <= 4 * (int64_t)s->batch;
   const int64_t row_blocks = (p->rows + 31) / 32;
