@@ -101,7 +101,7 @@ static int finish_score_plan(const dapq_shape* s, int64_t heads, int chunk, Scor
   p->off_work = off;  // ticket counter of a ragged batch's work list
   off += 256;
   p->off_parts = off;
-  off = align_up(off + sizeof(float) * 2 * (size_t)heads * (size_t)p->max_chunks * p->rows_pad, 256);
+  off = align_up(off + sizeof(float) * (p->tile ? 1 : 2) * (size_t)heads * (size_t)p->max_chunks * p->rows_pad, 256);
   p->off_lse2 = off;
   off = align_up(off + sizeof(float) * (size_t)s->n_layers * s->batch * s->n_q_heads * s->n_pseudo, 256);
   p->off_partial = off;
@@ -161,10 +161,10 @@ int make_score_plan(const dapq_shape* s, ScorePlan* p) {
 
   // The tile form: a workgroup per 128 keys, its waves a row block each.  It is the faster one where the wave form leaves
   // the chip idle or pays its start-up per chunk (the queries of up to 256 rows into one wave, a ring of its own, tickets).
-  // Both passes of dapq_score, wave form -> tile form, 8 KV heads: one layer, 1024 keys, 256 rows 38.6 -> 15.8 us; 8191
-  // keys, 128 rows 26.9 -> 19.3; 16384 keys, 256 rows 44 -> 41, 512 rows 57 -> 61; 32768 keys, 128 rows 39 -> 45; ragged,
+  // Both passes of dapq_score, wave form -> tile form, 8 KV heads: one layer, 1024 keys, 256 rows 38.6 -> 14.9 us; 8191
+  // keys, 128 rows 26.9 -> 18.6; 16384 keys, 256 rows 44 -> 41, 512 rows 57 -> 61; 32768 keys, 128 rows 39 -> 45; ragged,
   // 8 prompts of 1000 keys, one layer, 128 rows 76 -> 24, 4 layers, 128 rows (10 000 units) 146 -> 59, 512 rows (40 000
-  // units) 188 -> 169; 32 layers, 16 prompts of 700, 128 rows (120 000) 530 -> 597.  Where dapq_score runs both passes in one
+  // units) 188 -> 174; 32 layers, 16 prompts of 700, 128 rows (120 000) 530 -> 597.  Where dapq_score runs both passes in one
   // kernel it stays with that one.
   const bool ragged = s->cu_seqlens != nullptr;
   const bool one_kernel = !ragged && p->n_groups == 1 && p->max_chunks <= 4 * (int64_t)s->batch;

@@ -58,6 +58,7 @@ struct ScoreParams {
   int32_t* cu_chunks;         // [batch+1] prefix of per-sequence chunk counts (ragged only)
   unsigned* work;             // ragged only: [kLists] next ticket of every work list; zeroed with cu_chunks
   float2* parts;              // [layer*Hkv][max_chunks][rows_pad] (reference, sum) in the log2 domain
+  float* tile_parts;          // tile form: their log2 in one value, reference + log2(sum), -inf for no sum (parts is NULL)
   float* lse2;                // [layer][batch][Hq][N]
   float* scores;              // [layer][Hkv][total_tokens]
   float* partial;             // [n_groups-1][layer][Hkv][total_tokens] column sums of row groups 1.. (n_groups > 1)
@@ -276,14 +277,23 @@ __global__ __launch_bounds__(64 * kCombineClasses) void score_combine_kernel(Sco
     c1 = p.cu_chunks[b + 1];
   }
   const int n = c1 - c0, runs = (n + kCombineRun - 1) / kCombineRun;
-  const float2* src = p.parts + ((int64_t)blockIdx.y * p.max_chunks + c0) * p.rows_pad + (row < p.rows ? row : p.rows - 1);
+  const int64_t src = ((int64_t)blockIdx.y * p.max_chunks + c0) * p.rows_pad + (row < p.rows ? row : p.rows - 1);
   // t[i] = log2 of the sum of chunk run * kCombineRun + i, -inf for chunks without one
   auto load_run = [&](int run, float (&t)[kCombineRun]) {
+    if (p.tile_parts != nullptr) {
+#pragma unroll
+      for (int i = 0; i < kCombineRun; ++i) {
+        const int c = run * kCombineRun + i;
+        const float v = p.tile_parts[src + (int64_t)(c < n ? c : n - 1) * p.rows_pad];
+        t[i] = c < n ? v : -INFINITY;
+      }
+      return;
+    }
     float2 v[kCombineRun];
 #pragma unroll
     for (int i = 0; i < kCombineRun; ++i) {
       const int c = run * kCombineRun + i;
-      v[i] = src[(int64_t)(c < n ? c : n - 1) * p.rows_pad];
+      v[i] = p.parts[src + (int64_t)(c < n ? c : n - 1) * p.rows_pad];
     }
 #pragma unroll
     for (int i = 0; i < kCombineRun; ++i)
@@ -1117,7 +1127,7 @@ __global__ __launch_bounds__(64 * kTileWaves) __attribute__((amdgpu_waves_per_eu
   tile_dma(keys, tile_k_base(p, t, w), p.k_stride_token, w.nkeys, wave, waves, lane);
   const uint16_t* qbase = tile_q_base(p, t, w.seq);
   const int row_blocks = p.rows_pad / 32;
-  float2* outp = p.parts + (((int64_t)t.layer * p.n_kv_heads + t.kv) * p.max_chunks + t.chunk) * p.rows_pad;
+  float* outp = p.tile_parts + (((int64_t)t.layer * p.n_kv_heads + t.kv) * p.max_chunks + t.chunk) * p.rows_pad;
   bf16x8 qf[8];
   frag_from_q(qf, p, qbase, wave * 32 + n, h);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -1162,7 +1172,7 @@ __global__ __launch_bounds__(64 * kTileWaves) __attribute__((amdgpu_waves_per_eu
     if (rb + waves < row_blocks) frag_from_q(qf, p, qbase, (rb + waves) * 32 + n, h);
     const float zz = z[0] + z[1];
     const float both = zz + xhalf(zz);
-    if (h == 0) outp[rb * 32 + n] = make_float2(ref, both);
+    if (h == 0) outp[rb * 32 + n] = both > 0.0f ? ref + log2f(both) : -INFINITY;
   }
 }
 
@@ -1203,23 +1213,19 @@ __global__ __launch_bounds__(64 * kTileWaves) __attribute__((amdgpu_waves_per_eu
     const int shares = (int)blockDim.x / p.rows_pad;
     const int chunks = (w.seq_len + p.chunk_keys - 1) / p.chunk_keys, runs = (chunks + kCombineRun - 1) / kCombineRun;
     const int first = t.chunk - w.key0 / p.chunk_keys;  // the sequence's first chunk
-    const float2* src = p.parts + (((int64_t)t.layer * p.n_kv_heads + t.kv) * p.max_chunks + first) * p.rows_pad + row;
+    const float* src = p.tile_parts + (((int64_t)t.layer * p.n_kv_heads + t.kv) * p.max_chunks + first) * p.rows_pad + row;
     float part[kMergeRuns][kCombineRun], m = -INFINITY;
 #pragma unroll
     for (int k = 0; k < kMergeRuns; ++k) {
       const int run = share + k * shares;
-      float2 v[kCombineRun];
 #pragma unroll
       for (int i = 0; i < kCombineRun; ++i) {
         const int c = run * kCombineRun + i;
-        v[i] = make_float2(0.0f, 0.0f);
-        if (share < shares && c < chunks) v[i] = src[(int64_t)c * p.rows_pad];
+        part[k][i] = -INFINITY;
+        if (share < shares && c < chunks) part[k][i] = src[(int64_t)c * p.rows_pad];
       }
 #pragma unroll
-      for (int i = 0; i < kCombineRun; ++i) {
-        part[k][i] = v[i].y > 0.0f ? v[i].x + log2f(v[i].y) : -INFINITY;
-        m = fmaxf(m, part[k][i]);
-      }
+      for (int i = 0; i < kCombineRun; ++i) m = fmaxf(m, part[k][i]);
     }
     merge_max[threadIdx.x] = m;
     __syncthreads();
@@ -1359,8 +1365,14 @@ int fill_params(const dapq_shape* s, const ScorePlan& plan, ScoreParams* p) {
   p->rows = plan.rows; p->rows_pad = plan.rows_pad; p->n_groups = plan.n_groups;
   p->chunk_keys = plan.chunk_keys; p->max_chunks = (int32_t)plan.max_chunks;
   p->wg_groups = 1;
+  p->tile_parts = nullptr;
   p->c = s->scale * 1.4426950408889634f;
   return DAPQ_OK;
+}
+
+void set_parts(const ScorePlan& plan, char* workspace, ScoreParams* p) {
+  p->parts = plan.tile ? nullptr : reinterpret_cast<float2*>(workspace + plan.off_parts);
+  p->tile_parts = plan.tile ? reinterpret_cast<float*>(workspace + plan.off_parts) : nullptr;
 }
 
 int aligned16(const void* ptr, const char* name) {
@@ -1581,7 +1593,7 @@ extern "C" DAPQ_API int dapq_score_stats(const dapq_shape* shape, const void* q,
   p.k = static_cast<const uint16_t*>(k);
   p.cu_chunks = reinterpret_cast<int32_t*>(ws + plan.off_cu_chunks);
   p.work = reinterpret_cast<unsigned*>(ws + plan.off_work);
-  p.parts = reinterpret_cast<float2*>(ws + plan.off_parts);
+  set_parts(plan, ws, &p);
   p.lse2 = lse2;
   p.scores = nullptr;
   p.partial = nullptr;
@@ -1654,7 +1666,7 @@ extern "C" DAPQ_API int dapq_score(const dapq_shape* shape, const void* q, const
     p.k = static_cast<const uint16_t*>(k);
     p.cu_chunks = reinterpret_cast<int32_t*>(ws + plan.off_cu_chunks);
     p.work = reinterpret_cast<unsigned*>(ws + plan.off_work);
-    p.parts = reinterpret_cast<float2*>(ws + plan.off_parts);
+    set_parts(plan, ws, &p);
     p.partial = nullptr;
     p.lse2 = nullptr;
     p.scores = scores;
