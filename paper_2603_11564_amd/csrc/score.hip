@@ -7,6 +7,8 @@
 // share one KV head.  Nothing of size N x L_p is ever stored.  Where a (layer, sequence, KV head) fits one
 // workgroup -- one row group, at most 4 chunks per sequence of a dense batch -- dapq_score runs both passes in
 // one launch (score_fused_kernel: the same two walks, the merge in between through LDS).
+// Calls too small to fill the chip that way go through score_tile_pass1_kernel and score_tile_pass2_kernel instead: a
+// workgroup per 128 keys whose waves share out the query rows (make_score_plan draws the line).
 //
 // Work split.  The unit of work is ONE wave (four independent ones are launched as a workgroup).  It keeps a group of up to 256 Q rows of one KV head in
 // registers as MFMA operand fragments (eight 32-row blocks = 256 registers, pinned to the
