@@ -179,7 +179,9 @@ int make_score_plan(const dapq_shape* s, ScorePlan* p) {
   t.rows_pad = t.row_blocks * 32;
   rc = finish_score_plan(s, heads, kTileKeys, &t);
   if (rc != DAPQ_OK) return rc;
-  // (its partials are more: a shape that dapq_score_static serves is still served)
+  // The workspace is no smaller than the wave form's: its size does not depend on which side of the line a shape falls.
+  if (t.total_bytes < p->total_bytes) t.total_bytes = p->total_bytes;
+  // (where it would be larger, a shape that dapq_score_static serves is still served)
   if (t.total_bytes <= DAPQ_STATIC_SCRATCH_BYTES || p->total_bytes > DAPQ_STATIC_SCRATCH_BYTES) *p = t;
   return DAPQ_OK;
 }
