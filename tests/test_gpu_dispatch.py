@@ -160,3 +160,26 @@ def test_selection_over_distributions(H, n, kind):
             for kv in range(2):
                 got = idx.cpu().numpy()[0, 0, kv][:int(count[0, 0, kv])]
                 assert np.array_equal(got, O.topk(P[kv].astype(np.float64), budget)), (budget, pooled, kv)
+
+
+# ragged batches too large for the tile form (more than 65536 units): one, two and four row blocks' kernels, teams of two,
+# up to and beyond the 64 sequences that a wave looks up by itself
+@pytest.mark.parametrize("batch", [40, 64, 65, 100])
+@pytest.mark.parametrize("rows", [33, 128, 200, 512])
+def test_ragged_batches_in_the_wave_form(H, rows, batch):
+    """Every layer is the same problem (layer strides of 0): all layers have the same bits, and the first has the oracle's
+    scores within 1e-3 (the bar of the other score tests)."""
+    announce(f"ragged wave form: rows={rows} batch={batch}")
+    lens = [(37 * b) % 211 for b in range(batch - 1)] + [1500]
+    q, k, v, cu = problem_bits(batch, 1, lens, 2, 2, rows)
+    prob = H.Problem(q, k, v, 2, cu, "thd")
+    tokens = int(cu[-1])
+    layers = 66000 // (2 * (tokens // 128 + batch) * ((rows + 31) // 32)) + 1
+    shape = H.D.make_shape(n_layers=layers, batch=batch, n_q_heads=2, n_kv_heads=2, n_pseudo=rows, total_tokens=tokens,
+                           cu_seqlens=prob.cu, k_strides=(0, 0, 128, 256), q_strides=(0, 2 * rows * 128, rows * 128, 128),
+                           scale=128 ** -0.5)
+    ws = torch.empty(H.D.workspace_bytes(shape), dtype=torch.uint8, device="cuda")
+    S = torch.full((layers, 2, tokens), float("nan"), dtype=torch.float32, device="cuda")
+    H.D.dapq_score(shape, prob.q, prob.k, S, ws)
+    assert torch.equal(S, S[:1].expand_as(S))
+    H.assert_scores_close(S[:1].cpu().numpy(), O.score(q, k, 2, cu), f"rows={rows} batch={batch}")
