@@ -1,0 +1,88 @@
+"""Checks of the gfx950 code that hipcc generates from the kernel sources: what the kernels rely on and the compiler does
+not check in hand-written instructions."""
+import os
+import re
+import subprocess
+from concurrent.futures import ThreadPoolExecutor
+
+import pytest
+
+from paper_2603_11564_amd import build
+
+
+def compile_device(src, out):
+    """Compiles one translation unit for the device; returns its assembly (one list of lines per kernel or function)."""
+    r = subprocess.run([build._hipcc(), *build.FLAGS, "--cuda-device-only", "-S", os.path.join(build.CSRC, src), "-o", out],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-4000:]
+    functions, current = {}, None
+    for line in open(out):
+        line = line.split(";")[0].split("//")[0].rstrip()
+        label = re.match(r"(_Z\w+):", line)
+        if label:
+            current = functions.setdefault(label.group(1), [])
+        elif current is not None and line.strip():
+            current.append(line.strip())
+    return functions
+
+
+@pytest.fixture(scope="module")
+def units(tmp_path_factory):
+    folder = tmp_path_factory.mktemp("device_code")
+    with ThreadPoolExecutor(max_workers=6) as pool:
+        jobs = {src: pool.submit(compile_device, src, str(folder / (src + ".s"))) for src in build.SOURCES}
+        return {src: job.result() for src, job in jobs.items()}
+
+
+def scalar_registers(operand):
+    """The scalar registers that an operand names: "s5", "s[4:5]", "vcc"."""
+    operand = operand.strip().strip("-|")
+    m = re.fullmatch(r"s\[(\d+):(\d+)\]", operand)
+    if m:
+        return set(range(int(m.group(1)), int(m.group(2)) + 1))
+    m = re.fullmatch(r"s(\d+)", operand)
+    return {int(m.group(1))} if m else {operand[:3]} if operand in ("vcc", "vcc_lo", "vcc_hi") else set()
+
+
+def early_reads_of_vector_written_scalars(lines):
+    """Vector instructions that read a scalar register (as a carry, a mask or a value) fewer than two wait states after a vector
+    instruction wrote it: gfx950 needs two there, and does not check."""
+    written, clock, found = {}, 0, []
+    for line in lines:
+        if line.endswith(":") or line.startswith("."):
+            continue
+        op, _, rest = line.partition(" ")
+        operands = re.findall(r"s\[\d+:\d+\]|v\[\d+:\d+\]|a\[\d+:\d+\]|[^,\s]+", rest)
+        clock += 1 if op != "s_nop" else int(operands[0], 0) + 1
+        if not op.startswith("v_"):
+            if op.startswith("s_") and operands:    # (a scalar write takes the register over)
+                for r in scalar_registers(operands[0]):
+                    written.pop(r, None)
+            continue
+        two_results = re.match(r"v_(add|sub|subrev|addc|subb|subbrev)_co_|v_div_scale|v_mad_[ui]64", op) is not None
+        n = 2 if two_results else 1
+        for operand in operands[n:]:
+            if any(clock - written.get(r, -9) <= 2 for r in scalar_registers(operand)):
+                found.append(line)
+        for operand in operands[:n]:
+            for r in scalar_registers(operand):
+                written[r] = clock
+    return found
+
+
+def test_the_scan_itself():
+    cmp, use = "v_cmp_lt_u32_e32 vcc, s2, v2", "v_addc_co_u32_e32 v0, vcc, v0, v0, vcc"
+    assert early_reads_of_vector_written_scalars([cmp, use]) == [use]
+    assert early_reads_of_vector_written_scalars([cmp, "s_nop 0", use]) == [use]
+    assert early_reads_of_vector_written_scalars([cmp, "s_nop 1", use]) == []
+    assert early_reads_of_vector_written_scalars([cmp, "v_mov_b32_e32 v1, v2", "v_mov_b32_e32 v1, v3", use]) == []
+    assert early_reads_of_vector_written_scalars(["v_cmp_lt_u32_e64 s[4:5], v1, v2", "v_cndmask_b32_e64 v0, 0, 1, s[4:5]"]) != []
+    assert early_reads_of_vector_written_scalars(["v_readfirstlane_b32 s4, v1", "v_add_u32_e32 v0, s4, v0"]) != []
+    assert early_reads_of_vector_written_scalars(["v_readfirstlane_b32 s4, v1", "s_mov_b32 s4, 0", "v_add_u32_e32 v0, s4, v0"]) == []
+
+
+def test_vector_written_scalars_are_read_two_wait_states_later(units):
+    """The compiler inserts these waits for its own instructions, not inside inline assembly or around it."""
+    early = {f"{src}: {name}": lines[:4] for src, fs in units.items() for name, body in fs.items()
+             if (lines := early_reads_of_vector_written_scalars(body))}
+    assert not early, early
