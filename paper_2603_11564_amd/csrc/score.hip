@@ -692,8 +692,10 @@ __device__ __forceinline__ unsigned next_list(const ScoreParams& p, const ItemLi
 // drained by then, instead of to global memory.
 template <int NRB, int NST, bool FUSED = false>
 __device__ __forceinline__ unsigned pass1_item(const ScoreParams& p, u32x4* ring, const Work& w, int chunk_id, int group, int head,
-                                               bf16x8 (&qf)[NRB][8], const unsigned (&voff)[4], int lane,
-                                               unsigned* work) {
+                                               bf16x8 (&qf)[NRB][8], int lane, unsigned* work) {
+  if (NRB == 8) asm volatile("" : "+v"(lane));  // what follows from the lane is formed per item (see score_wave_pass1_kernel)
+  unsigned voff[4];
+  sub_dma_lane_offsets(voff, p.k_stride_token, lane);
   // (the division runs on the vector ALU: bring the quotient back to a scalar register)
   const int layer = uniform_i32(head / p.n_kv_heads), kv = head - layer * p.n_kv_heads;
   const int n = lane & 31, h = lane >> 5;
@@ -799,20 +801,23 @@ __device__ __forceinline__ WaveSlot wave_slot(const ScoreParams& p, int wave_id)
 // DYN = true (ragged batches, whose lengths the host does not know): one persistent wave per SIMD takes items from
 // work lists in device memory until they are empty (see ItemLists).  A short chunk costs a ticket and a ring refill
 // instead of a workgroup launch; the hand-out also evens out the ragged tail.
+// At 8 row blocks, what follows from the lane number alone (transfer offsets, fragment addresses, row masks: some 40 registers) is
+// formed anew for every item: kept across the items it does not fit beside the queries, and a register that is spilled is
+// reloaded between the ring fill and the walk, behind a wait for every transfer in flight.  (A spill is also one more of the
+// vector memory operations that the ring's waits count.)  32 layers, 256 rows, both passes: 16 prompts of 175..1400 keys 587 ->
+// 562 us, 64 of 300 keys 1202 -> 1148; 8 of 4096..16384, 512 rows unchanged.
 template <int NRB, bool DYN, int NST>
 __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_wave_pass1_kernel(ScoreParams p) {
   extern __shared__ u32x4 rings[];
   const int wave_id = uniform_i32((int)(threadIdx.x >> 6));
   u32x4* ring = rings + wave_id * (wave_lds(NST) / 16);
   const int lane = threadIdx.x & 63;
-  unsigned voff[4];
-  sub_dma_lane_offsets(voff, p.k_stride_token, lane);
   bf16x8 qf[NRB][8];
   if (!DYN) {
     const WaveSlot slot = wave_slot(p, wave_id);
     const Work w = locate_uniform(p, slot.chunk);
     if (w.nkeys == 0) return;
-    pass1_item<NRB, NST>(p, ring, w, slot.chunk, slot.group, (int)blockIdx.z, qf, voff, lane, nullptr);
+    pass1_item<NRB, NST>(p, ring, w, slot.chunk, slot.group, (int)blockIdx.z, qf, lane, nullptr);
     return;
   }
   const ItemLists lists = item_lists(p);
@@ -830,7 +835,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_wave_pass1_kerne
         tickets.post(work != nullptr ? take_item(work, lane) : 0u, lane);
         continue;
       }
-      tickets.post(pass1_item<NRB, NST>(p, ring, a.work, a.chunk, a.block * p.wg_groups + wave_id, a.head, qf, voff, lane, work),
+      tickets.post(pass1_item<NRB, NST>(p, ring, a.work, a.chunk, a.block * p.wg_groups + wave_id, a.head, qf, lane, work),
                    lane);
     }
     tickets.post(tickets.leader ? next_list(p, lists, home, lane) : 0u, lane);
@@ -842,8 +847,10 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_wave_pass1_kerne
 // registers from pass 1 and the caller has filled off2.
 template <int NRB, int NST, bool FUSED = false>
 __device__ __forceinline__ unsigned pass2_item(const ScoreParams& p, u32x4* ring, const Work& w, int group, int head,
-                                               bf16x8 (&qf)[NRB][8], float (&off2)[NRB][16],
-                                               const unsigned (&voff)[4], int lane, unsigned* work) {
+                                               bf16x8 (&qf)[NRB][8], float (&off2)[NRB][16], int lane, unsigned* work) {
+  if (NRB == 8) asm volatile("" : "+v"(lane));  // what follows from the lane is formed per item (see score_wave_pass1_kernel)
+  unsigned voff[4];
+  sub_dma_lane_offsets(voff, p.k_stride_token, lane);
   // (the division runs on the vector ALU: bring the quotient back to a scalar register)
   const int layer = uniform_i32(head / p.n_kv_heads), kv = head - layer * p.n_kv_heads;
   const int n = lane & 31, h = lane >> 5;
@@ -911,15 +918,13 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_wave_pass2_kerne
   const int wave_id = uniform_i32((int)(threadIdx.x >> 6));
   u32x4* ring = rings + wave_id * (wave_lds(NST) / 16);
   const int lane = threadIdx.x & 63;
-  unsigned voff[4];
-  sub_dma_lane_offsets(voff, p.k_stride_token, lane);
   bf16x8 qf[NRB][8];
   float off2[NRB][16];
   if (!DYN) {
     const WaveSlot slot = wave_slot(p, wave_id);
     const Work w = locate_uniform(p, slot.chunk);
     if (w.nkeys == 0) return;
-    pass2_item<NRB, NST>(p, ring, w, slot.group, (int)(gridDim.z - 1 - blockIdx.z), qf, off2, voff, lane, nullptr);
+    pass2_item<NRB, NST>(p, ring, w, slot.group, (int)(gridDim.z - 1 - blockIdx.z), qf, off2, lane, nullptr);
     return;
   }
   const ItemLists lists = item_lists(p);
@@ -937,7 +942,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_wave_pass2_kerne
         tickets.post(work != nullptr ? take_item(work, lane) : 0u, lane);
         continue;
       }
-      tickets.post(pass2_item<NRB, NST>(p, ring, a.work, a.block * p.wg_groups + wave_id, a.head, qf, off2, voff, lane, work),
+      tickets.post(pass2_item<NRB, NST>(p, ring, a.work, a.block * p.wg_groups + wave_id, a.head, qf, off2, lane, work),
                    lane);
     }
     tickets.post(tickets.leader ? next_list(p, lists, home, lane) : 0u, lane);
@@ -959,13 +964,11 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_fused_kernel(Sco
   const int wave_id = uniform_i32((int)(threadIdx.x >> 6)), waves = (int)(blockDim.x >> 6);
   u32x4* ring = rings + wave_id * (wave_lds(NST) / 16);
   const int lane = threadIdx.x & 63, h = lane >> 5;
-  unsigned voff[4];
-  sub_dma_lane_offsets(voff, p.k_stride_token, lane);
   bf16x8 qf[NRB][8];
   const int chunk = uniform_i32((int)blockIdx.x * waves + wave_id);  // blockIdx.x is the sequence
   const int head = (int)blockIdx.z;
   const Work work = locate_uniform(p, chunk);
-  pass1_item<NRB, NST, true>(p, ring, work, chunk, 0, head, qf, voff, lane, nullptr);
+  pass1_item<NRB, NST, true>(p, ring, work, chunk, 0, head, qf, lane, nullptr);
   __syncthreads();
   // lse2 of rows lane, lane + 64, ...: every wave merges all chunks itself
   constexpr int kRowsPerLane = NRB * 32 / 64;
@@ -1004,7 +1007,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_fused_kernel(Sco
       off2[rb][4 * b + 3] = v.w;
     }
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // off2 is out of the ring before pass 2 refills it
-  pass2_item<NRB, NST, true>(p, ring, work, 0, head, qf, off2, voff, lane, nullptr);
+  pass2_item<NRB, NST, true>(p, ring, work, 0, head, qf, off2, lane, nullptr);
 }
 
 // The causal block of the pseudo tokens' own keys (Sec. 4.1: they are prefilled in-sequence): one wave

@@ -11,19 +11,25 @@ from paper_2603_11564_amd import build
 
 
 def compile_device(src, out):
-    """Compiles one translation unit for the device; returns its assembly (one list of lines per kernel or function)."""
+    """Compiles one translation unit for the device; returns its assembly (one list of lines per kernel or function) and how
+    many vector registers each kernel spills."""
     r = subprocess.run([build._hipcc(), *build.FLAGS, "--cuda-device-only", "-S", os.path.join(build.CSRC, src), "-o", out],
                        capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-4000:]
-    functions, current = {}, None
+    functions, current, spills, kernel = {}, None, {}, None
     for line in open(out):
+        entry = re.match(r"\s+\.(symbol|vgpr_spill_count):\s+(\S+)", line)    # of the kernel descriptors at the end
+        if entry and entry.group(1) == "symbol":
+            kernel = entry.group(2)
+        elif entry:
+            spills[kernel] = int(entry.group(2))
         line = line.split(";")[0].split("//")[0].rstrip()
         label = re.match(r"(_Z\w+):", line)
         if label:
             current = functions.setdefault(label.group(1), [])
         elif current is not None and line.strip():
             current.append(line.strip())
-    return functions
+    return functions, spills
 
 
 @pytest.fixture(scope="module")
@@ -83,6 +89,14 @@ def test_the_scan_itself():
 
 def test_vector_written_scalars_are_read_two_wait_states_later(units):
     """The compiler inserts these waits for its own instructions, not inside inline assembly or around it."""
-    early = {f"{src}: {name}": lines[:4] for src, fs in units.items() for name, body in fs.items()
+    early = {f"{src}: {name}": lines[:4] for src, (fs, _) in units.items() for name, body in fs.items()
              if (lines := early_reads_of_vector_written_scalars(body))}
     assert not early, early
+
+
+def test_no_kernel_spills_vector_registers(units):
+    """The waits of the key rings count vector memory operations in the order they were issued: a spilled register's store or
+    reload is one more of them, and a reload waits for all that are in flight."""
+    spills = {f"{src}: {name}": n for src, (_, kernels) in units.items() for name, n in kernels.items()}
+    assert len(spills) > 40 and any("score_wave_pass1_kernel" in name for name in spills)
+    assert not {name: n for name, n in spills.items() if n}
