@@ -124,7 +124,8 @@ extern "C" DAPQ_API int dapq_rope_apply(const void* x_in, void* x_out, const int
   int hpt = 8;
   while (hpt < 64 && hpt * 2 <= heads && (work / 64) * ((heads + 2 * hpt - 1) / (2 * hpt)) >= 4096) hpt *= 2;
   // small calls: shorter runs until there is a wave per SIMD (64 rows x 32 heads as part of a score call: 0.5 to 1 us of 3.5)
-  while (hpt > 1 && hpt <= 8 && (work / 64) * ((heads + hpt - 1) / hpt) < 1024) hpt /= 2;
+  // (the waves of a run of heads are rounded up: fewer than 64 channel pairs are one wave, and many heads of them keep their runs)
+  while (hpt > 1 && hpt <= 8 && (work + 63) / 64 * (((int64_t)heads + hpt - 1) / hpt) < 1024) hpt /= 2;
   const int64_t head_runs = ((int64_t)heads + hpt - 1) / hpt;
   DAPQ_REQUIRE(head_runs <= 65535, DAPQ_ERR_UNSUPPORTED, "heads (%d) exceeds %d", heads, 65535 * hpt);
   const double e = rope_exponent(theta, head_dim);

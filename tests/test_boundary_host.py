@@ -10,7 +10,7 @@ import paper_2603_11564_amd as D
 from paper_2603_11564_amd import binding
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-ERR_INVALID, ERR_UNSUPPORTED, ERR_WORKSPACE = -1, -2, -3
+ERR_INVALID, ERR_UNSUPPORTED, ERR_WORKSPACE, ERR_HIP = -1, -2, -3, -4
 
 
 @pytest.fixture(scope="module")
@@ -242,6 +242,15 @@ def test_score_plan_covers_every_shape(lib):
     # very many rows are still planned (row groups on the grid), absurdly many are refused
     assert ws(n_pseudo=4096, q_strides=(32 * 4096 * 128, 32 * 4096 * 128, 4096 * 128, 128)) > 0
     assert ws(n_pseudo=1 << 19) == 0 and b"rows per KV head" in lib.dapq_last_error()
+
+
+def test_many_heads_of_few_rows_are_not_refused(lib):
+    """dapq_rope_apply takes up to 65535 runs of 8 heads, however few rows there are: the call gets as far as its launch, which
+    reports that there is no GPU here."""
+    if os.path.exists("/dev/kfd"):
+        pytest.skip("would be launched, with pointers that are none")
+    for rows, heads, d in ((1, 65536, 64), (1, 100000, 64), (1, 65535 * 8, 8), (3, 65535 * 8, 128)):
+        assert lib.dapq_rope_apply(FAKE, FAKE, FAKE, rows, heads, d, heads * d, d, 5e5, 0, None) == ERR_HIP, lib.dapq_last_error()
 
 
 def test_binding_raises_with_the_library_message():

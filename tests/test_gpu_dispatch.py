@@ -183,3 +183,14 @@ def test_ragged_batches_in_the_wave_form(H, rows, batch):
     H.D.dapq_score(shape, prob.q, prob.k, S, ws)
     assert torch.equal(S, S[:1].expand_as(S))
     H.assert_scores_close(S[:1].cpu().numpy(), O.score(q, k, 2, cu), f"rows={rows} batch={batch}")
+
+
+# fewer channel pairs than a wave has lanes, one wave, a few; heads up to the most a launch takes
+@pytest.mark.parametrize("rows,heads,d", [(1, 65536, 64), (1, 100000, 64), (1, 65535 * 8, 8), (2, 9000, 64), (1, 3, 128), (3, 1025, 24)])
+def test_rotation_of_many_heads(H, rows, heads, d):
+    """The oracle's bits, as in the other tests of the rotation."""
+    announce(f"rotation: {rows} rows, {heads} heads of {d}")
+    rng = np.random.default_rng(heads)
+    x = W.to_bf16_bits(rng.standard_normal((rows, heads, d), dtype=np.float32))
+    pos = rng.integers(0, 140000, rows)
+    assert np.array_equal(H.rope_gpu(x, pos, 500000.0), O.rope_apply(x, pos, 500000.0))
