@@ -13,8 +13,8 @@
 // workgroups ("slices"): each reads all of K_c (they start a slice of the tiles apart) but only its share of V_c.
 //   logits   D[key][column] = K_c tile (A operand, 16 keys x 32 channels per instruction) x q (B operand).  The columns
 //            are 4 query heads x 4 parts: column 4 * part + head.
-//   weights  2^(c * logit - ref) in fp32.  ref is the largest logit of the wave's first tile; it only moves (and the
-//            sums are rescaled) if a later logit lies more than 2^kDecodeHeadroom above it.
+//   weights  2^(c * logit - ref) in fp32.  ref is the largest logit of the wave's first tile with a finite one; it only
+//            moves (and the sums are rescaled) if a later logit lies more than 2^kDecodeHeadroom above it.
 //   output   D[column][channel] += weights (A) x V_c (B).  A weight enters as three bf16 numbers whose sum it is, bit
 //            for bit (8 + 8 + 8 bits of its significand): part 0 carries the first, part 1 the second, part 2 the third,
 //            so one instruction multiplies all three with V_c and nothing is lost against fp32 weights (part 3 is not
@@ -42,6 +42,7 @@ constexpr int kDecodeMaxRows = 8192;
 constexpr int kDecodeTile = 32;           // cache rows a wave takes at a time
 constexpr int kDecodeParts = 3;           // bf16 numbers that make up a weight
 constexpr float kDecodeHeadroom = 60.0f;  // binades a logit may lie above the reference
+constexpr float kDecodeLowest = -3.4028234663852886e38f;  // where the reference starts: finite, a logit of -inf then weighs 0
 
 struct DecodeParams {
   const uint16_t* q;        // [layer][seq][Hq][d]
@@ -185,7 +186,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void decode_attention_kernel(DecodeP
     for (int t = 0; t < HT; ++t) {
 #pragma unroll
       for (int j = 0; j < CPL; ++j) acc[t][j] = {0.0f, 0.0f, 0.0f, 0.0f};
-      ref[t] = -INFINITY;
+      ref[t] = kDecodeLowest;
       sum[t] = 0.0f;
     }
 
@@ -230,7 +231,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void decode_attention_kernel(DecodeP
 #pragma unroll
         for (int e = 1; e < 8; ++e) m = fmaxf(m, x[e]);
         m *= p.c;
-        if (__any(m > ref[t] + kDecodeHeadroom)) {  // (always for the first tile, whose reference is -inf)
+        if (__any(m > ref[t] + kDecodeHeadroom)) {  // (always for the first tile that has a logit)
           m = fmaxf(m, __shfl_xor(m, 16, 64));
           m = fmaxf(m, __shfl_xor(m, 32, 64));
           const float moved = fmaxf(ref[t], m);

@@ -93,6 +93,51 @@ def test_decode_tiles_and_head_groups(H, rows, g):
             assert (np.abs(got[b, h] - want) <= bound).all(), (b, h)
 
 
+def decode_call(H, q, k, v, counts, layers=1):
+    """One decode step; q [batch, Hq, 128], k and v [batch, Hkv, budget, 128] (bf16 bits), counts [batch, Hkv]: [batch, Hq, 128]."""
+    batch, hq, hkv, budget = q.shape[0], q.shape[1], k.shape[1], k.shape[2]
+    out = torch.full((batch, hq, 128), float("nan"), dtype=torch.float32, device="cuda")
+    shape = H.D.make_shape(n_layers=layers, batch=batch // layers, n_q_heads=hq, n_kv_heads=hkv, n_pseudo=1,
+                           total_tokens=batch // layers, scale=128 ** -0.5)
+    H.D.dapq_decode_attention(shape, H.dev_bf16(q), H.dev_bf16(k), H.dev_bf16(v),
+                              torch.from_numpy(np.ascontiguousarray(counts, dtype=np.int32)).cuda(), budget, out)
+    return out.cpu().numpy().astype(np.float64)
+
+
+def decode_want(q, k, v, counts):
+    """The same in float64."""
+    q, k, v = (O.bf16_bits_to_f64(x) for x in (q, k, v))
+    g = q.shape[1] // k.shape[1]
+    want = np.zeros(q.shape)
+    for b, h in np.ndindex(q.shape[:2]):
+        n = counts[b, h // g]
+        if n:
+            x = k[b, h // g, :n] @ q[b, h] / np.sqrt(128)
+            w = np.exp(x - x.max())
+            want[b, h] = (w / w.sum()) @ v[b, h // g, :n]
+    return want
+
+
+# the three slice counts (up to 32 heads, up to 128, more), both head tiles
+@pytest.mark.parametrize("batch", [2, 9, 33])
+@pytest.mark.parametrize("g", [4, 5])
+def test_decode_rows_that_weigh_nothing(H, g, batch):
+    """Rows whose logits are -inf (a key of that channel at the largest value, against a query as large) weigh 0 wherever they
+    lie: in all of a wave's first tile, in its last, everywhere but in one row.  |error| as in the other decode tests."""
+    announce(f"decode: -inf logits, g={g} batch={batch}")
+    rng = np.random.default_rng(g)
+    rows, hkv = 600, 4
+    f = lambda *s: rng.standard_normal(s, dtype=np.float32)  # noqa: E731
+    q, k, v = f(batch, hkv * g, 128), f(batch, hkv, rows, 128), f(batch, hkv, rows, 128)
+    q[..., 5], k[..., 5] = 3e38, 0.0
+    for kv, gone in enumerate((slice(0, 400), slice(256, 288), slice(500, 600), slice(1, 600))):
+        k[:, kv, gone, 5] = -3e38
+    q, k, v = (W.to_bf16_bits(x) for x in (q, k, v))
+    counts = np.full((batch, hkv), rows)
+    got, want = decode_call(H, q, k, v, counts), decode_want(q, k, v, counts)     # (-1e77 in float64: weight 0 as well)
+    assert (np.abs(got - want) <= 1e-5 * np.abs(O.bf16_bits_to_f64(v)).max() + 1e-4 * np.abs(want)).all()
+
+
 # few workgroups: keys around the sub-blocks and tiles of 128, rows around the row blocks of 32, the eight waves (256) and the
 # 512 rows whose partials pass 2 merges itself; more than 64 sequences (their chunk prefix lies in device memory), empty ones
 @pytest.mark.parametrize("rows", [1, 31, 33, 74, 257, 512, 520])
