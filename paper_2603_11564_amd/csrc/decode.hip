@@ -309,13 +309,16 @@ __global__ __launch_bounds__(64 * WAVES, 2) void decode_attention_kernel(DecodeP
       auto left = [&](int w, int at) { return reinterpret_cast<const float*>(lds + w * kWaveBytes)[at]; };
       float m = left(0, kSums + h);
       for (int w = 1; w < waves; ++w) m = fmaxf(m, left(w, kSums + h));
-      float o = 0.0f, s = 0.0f;
+      float o = 0.0f, first = 0.0f, s = 0.0f;  // first: the sums over the weights' first parts alone
       for (int w = 0; w < waves; ++w) {  // fixed order
         const float f = __builtin_amdgcn_exp2f(left(w, kSums + h) - m);
         o = fmaf(f, left(w, e) + (left(w, kHeads * kChannels + e) + left(w, 2 * kHeads * kChannels + e)), o);
+        first = fmaf(f, left(w, e), first);
         s = fmaf(f, left(w, kSums + kHeads + h), s);
       }
-      p.out[(qrow0 + h) * kHeadDim + slice * kChannels + e % kChannels] = o / s;
+      // (an infinite value times the second or third part of a weight, which may be 0, is no number: the first part, which is not 0
+      // where the weight is not, then has the say)
+      p.out[(qrow0 + h) * kHeadDim + slice * kChannels + e % kChannels] = (o == o ? o : first) / s;
     }
     if (h0 + kHeads < g) __syncthreads();  // everything has been read before the next sweep's tiles arrive
   }

@@ -138,6 +138,32 @@ def test_decode_rows_that_weigh_nothing(H, g, batch):
     assert (np.abs(got - want) <= 1e-5 * np.abs(O.bf16_bits_to_f64(v)).max() + 1e-4 * np.abs(want)).all()
 
 
+@pytest.mark.parametrize("batch", [2, 9, 33])
+@pytest.mark.parametrize("g", [4, 5])
+def test_decode_infinite_values(H, g, batch):
+    """An infinite value makes its channel infinite in every query head that gives its row a weight, whichever bits of the weight's
+    significand are set; the other channels are not touched (|error| as in the other decode tests)."""
+    announce(f"decode: infinite values, g={g} batch={batch}")
+    rng = np.random.default_rng(g)
+    rows, hkv = 70, 4
+    f = lambda *s: rng.standard_normal(s, dtype=np.float32)  # noqa: E731
+    q, k, v = f(batch, hkv * g, 128), f(batch, hkv, rows, 128), f(batch, hkv, rows, 128)
+    k[:, 1] = 0.0                         # all weights 1: their second and third part are 0
+    q, k, v = (W.to_bf16_bits(x) for x in (q, k, v))
+    counts = np.full((batch, hkv), rows)
+    want = decode_want(q, k, v, counts)
+    bound = 1e-5 * np.abs(O.bf16_bits_to_f64(v)).max() + 1e-4 * np.abs(want)
+    for channel in (3, 64, 127):
+        v[:, :, channel % rows, channel] = 0x7F80
+        want[..., channel] = np.inf
+    v[:, :, 40, 90] = 0xFF80
+    want[..., 90] = -np.inf
+    got = decode_call(H, q, k, v, counts)
+    infinite = np.isinf(want)
+    assert np.array_equal(got[infinite], want[infinite])
+    assert (np.abs(got[~infinite] - want[~infinite]) <= bound[~infinite]).all()
+
+
 # few workgroups: keys around the sub-blocks and tiles of 128, rows around the row blocks of 32, the eight waves (256) and the
 # 512 rows whose partials pass 2 merges itself; more than 64 sequences (their chunk prefix lies in device memory), empty ones
 @pytest.mark.parametrize("rows", [1, 31, 33, 74, 257, 512, 520])
