@@ -164,6 +164,27 @@ def test_decode_infinite_values(H, g, batch):
     assert (np.abs(got[~infinite] - want[~infinite]) <= bound[~infinite]).all()
 
 
+@pytest.mark.parametrize("batch", [2, 9, 33])
+@pytest.mark.parametrize("rise", [5, 14, 40, 59, 61, 300])
+@pytest.mark.parametrize("size", [1e33, 1.0, 1e-30])
+def test_decode_logits_that_rise_late(H, size, rise, batch):
+    """Rows late in the cache whose logits lie `rise` binades above the others', and values of up to `size`: the sums must not leave the
+    range of fp32 on the way.  |error| as in the other decode tests, and 2^-22 max|v| per binade of the logits: an fp32
+    logit of `rise` binades is known to about two units of its last place, 2^-23 rise, and with it the ratio of two weights."""
+    announce(f"decode: a logit {rise} binades higher late, values of {size}, batch={batch}")
+    rng = np.random.default_rng(rise)
+    rows, hkv, g = 700, 4, 4
+    f = lambda *s: rng.standard_normal(s, dtype=np.float32)  # noqa: E731
+    q, k = f(batch, hkv * g, 128), 0.1 * f(batch, hkv, rows, 128)
+    v = np.float32(size) * (2 * rng.random((batch, hkv, rows, 128), dtype=np.float32) - 1)
+    q[..., 7], k[..., 7] = 8.0, 0.0
+    k[:, :, (600, 300, 37, 699), 7] = rise * np.log(2) * np.sqrt(128) / 8
+    q, k, v = (W.to_bf16_bits(x) for x in (q, k, v))
+    counts = np.full((batch, hkv), rows)
+    got, want = decode_call(H, q, k, v, counts), decode_want(q, k, v, counts)
+    assert (np.abs(got - want) <= (1e-5 + rise * 2.0 ** -22) * np.abs(O.bf16_bits_to_f64(v)).max() + 1e-4 * np.abs(want)).all()
+
+
 # few workgroups: keys around the sub-blocks and tiles of 128, rows around the row blocks of 32, the eight waves (256) and the
 # 512 rows whose partials pass 2 merges itself; more than 64 sequences (their chunk prefix lies in device memory), empty ones
 @pytest.mark.parametrize("rows", [1, 31, 33, 74, 257, 512, 520])
