@@ -332,9 +332,21 @@ int launch_decode(int64_t heads, const DecodeParams& p, hipStream_t stream) {
   constexpr int kBytes = WAVES * decode_wave_bytes(HT);
   const int rc = set_max_dynamic_lds(reinterpret_cast<const void*>(decode_attention_kernel<HT, CPL, WAVES>), kBytes);
   if (rc != DAPQ_OK) return rc;
-  hipLaunchKernelGGL((decode_attention_kernel<HT, CPL, WAVES>), dim3((unsigned)heads, kHeadDim / (16 * CPL)),
-                     dim3(64 * WAVES), kBytes, stream, p);
-  DAPQ_HIP_LAUNCH_CHECK("decode_attention_kernel");
+  // a launch holds fewer than 2^32 threads along an axis: 2^24 heads and more go in several
+  constexpr int64_t kMostHeads = (int64_t)1 << 22;
+  const int64_t q_step = (int64_t)(p.n_q_heads / p.n_kv_heads) * kHeadDim, cache_step = (int64_t)p.budget * kHeadDim;
+  for (int64_t first = 0; first < heads; first += kMostHeads) {
+    DecodeParams part = p;
+    part.q += first * q_step;
+    part.k_cache += first * cache_step;
+    part.v_cache += first * cache_step;
+    part.count += first;
+    part.out += first * q_step;
+    hipLaunchKernelGGL((decode_attention_kernel<HT, CPL, WAVES>),
+                       dim3((unsigned)(heads - first < kMostHeads ? heads - first : kMostHeads), kHeadDim / (16 * CPL)),
+                       dim3(64 * WAVES), kBytes, stream, part);
+    DAPQ_HIP_LAUNCH_CHECK("decode_attention_kernel");
+  }
   return DAPQ_OK;
 }
 
@@ -379,7 +391,5 @@ extern "C" DAPQ_API int dapq_decode_attention(const dapq_shape* shape, const voi
   p.c = shape->scale * 1.4426950408889634f;
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int64_t heads = (int64_t)shape->n_layers * shape->batch * shape->n_kv_heads;
-  DAPQ_REQUIRE(heads < ((int64_t)1 << 31), DAPQ_ERR_UNSUPPORTED, "n_layers * batch * n_kv_heads (%lld) is too large",
-               (long long)heads);
   return p.n_q_heads / p.n_kv_heads <= 4 ? launch_decode_slices<1>(heads, p, st) : launch_decode_slices<2>(heads, p, st);
 }

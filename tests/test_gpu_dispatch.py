@@ -185,6 +185,23 @@ def test_decode_logits_that_rise_late(H, size, rise, batch):
     assert (np.abs(got - want) <= (1e-5 + rise * 2.0 ** -22) * np.abs(O.bf16_bits_to_f64(v)).max() + 1e-4 * np.abs(want)).all()
 
 
+def test_decode_step_of_very_many_heads(H):
+    """2^24 + 2^19 heads of one row each: the output is the row's value, within 2^-21 of itself (weight times value over weight: three
+    sums and a quotient in fp32, 2^-24 each).  One tensor of 4.4 GB is queries, keys and values at once; the output takes 8.9 GB."""
+    announce("decode: 17.3 million heads")
+    layers, batch, hkv = 33, 1024, 512
+    x = torch.randn((layers * batch * hkv, 128), dtype=torch.bfloat16, device="cuda")
+    count = torch.ones(layers * batch * hkv, dtype=torch.int32, device="cuda")
+    count[-1] = 0
+    out = torch.empty(x.shape, dtype=torch.float32, device="cuda")
+    shape = H.D.make_shape(n_layers=layers, batch=batch, n_q_heads=hkv, n_kv_heads=hkv, n_pseudo=1, total_tokens=batch,
+                           scale=128 ** -0.5)
+    H.D.dapq_decode_attention(shape, x, x, x, count, 1, out)
+    assert (out[-1] == 0).all()
+    for a, b in zip(out[:-1].split(1 << 20), x[:-1].float().split(1 << 20)):
+        assert ((a - b).abs() <= 2.0 ** -21 * b.abs()).all()
+
+
 # few workgroups: keys around the sub-blocks and tiles of 128, rows around the row blocks of 32, the eight waves (256) and the
 # 512 rows whose partials pass 2 merges itself; more than 64 sequences (their chunk prefix lies in device memory), empty ones
 @pytest.mark.parametrize("rows", [1, 31, 33, 74, 257, 512, 520])
