@@ -1467,7 +1467,7 @@ int launch_stats(const dapq_shape* s, const ScorePlan& plan, ScoreParams p, hipS
 }
 
 int launch_accumulate(const dapq_shape* s, const ScorePlan& plan, ScoreParams p, hipStream_t stream) {
-  if (s->cu_seqlens != nullptr) {
+  if (needs_chunk_prefix(s, plan)) {
     // pass 2 can be called on its own: rebuild the chunk prefix it walks
     hipLaunchKernelGGL(score_chunk_prefix_kernel, dim3(1), dim3(64), 0, stream, s->cu_seqlens, p.cu_chunks, p.work,
                        s->batch, plan.chunk_keys);

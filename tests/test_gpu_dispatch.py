@@ -225,6 +225,23 @@ def test_scores_of_small_calls(H, lens, rows):
     assert err.max() < 2e-4
 
 
+@pytest.mark.parametrize("batch", [2, 64, 65])
+def test_small_ragged_calls_write_no_chunk_prefix(H, batch):
+    """Up to 64 sequences every wave of the tile form finds its chunk by itself: neither pass writes the prefix of the chunk
+    counts (the first batch + 1 words of the workspace) or the tickets behind it; more sequences need it in both passes."""
+    announce(f"chunk prefix of {batch} sequences")
+    lens = [(7 * i) % 150 + 1 for i in range(batch)]
+    q, k, v, cu = problem_bits(batch, 1, lens, 2, 2, 16)
+    prob = H.Problem(q, k, v, 2, cu, "thd")
+    lse = prob.stats()
+    for call in (prob.score, prob.stats, lambda: H.D.dapq_score_accumulate(prob.shape, prob.q, prob.k, lse, torch.empty(
+            (1, 2, prob.tokens), dtype=torch.float32, device="cuda"), prob.ws)):
+        prob.ws.fill_(0xA5)
+        call()
+        kept = bool((prob.ws[:512] == 0xA5).all())
+        assert kept == (batch <= 64)
+
+
 def score_values(kind, rng, n):
     x = rng.random(n, dtype=np.float32)
     if kind == "octaves":
