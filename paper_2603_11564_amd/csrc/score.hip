@@ -259,10 +259,11 @@ __global__ void score_chunk_prefix_kernel(const int32_t* cu_seqlens, int32_t* cu
 // summed in run order, chunk by chunk, and the classes are added in class order (up to kCombineRun chunks: plain chunk
 // order, which is what score_fused_kernel does).
 constexpr int kCombineRun = 8, kCombineClasses = 16;
-__global__ __launch_bounds__(64 * kCombineClasses) void score_combine_kernel(ScoreParams p, int row_tiles) {
+__global__ __launch_bounds__(64 * kCombineClasses) void score_combine_kernel(ScoreParams p, int row_tiles, int first_seq) {
   __shared__ float lds_max[kCombineClasses][64], lds_sum[kCombineClasses][64];
   const int lane = threadIdx.x & 63, wave = uniform_i32((int)(threadIdx.x >> 6)), waves = (int)(blockDim.x >> 6);
-  const int b = uniform_i32((int)(blockIdx.x / row_tiles)), row = (int)(blockIdx.x - b * row_tiles) * 64 + lane;
+  const int seq = uniform_i32((int)(blockIdx.x / row_tiles)), row = (int)(blockIdx.x - seq * row_tiles) * 64 + lane;
+  const int b = first_seq + seq;
   const int layer = (int)(blockIdx.y / p.n_kv_heads), kv = (int)(blockIdx.y - layer * p.n_kv_heads);
   int c0, c1;
   if (p.cu_seqlens == nullptr) {
@@ -1460,9 +1461,14 @@ int launch_stats(const dapq_shape* s, const ScorePlan& plan, ScoreParams p, hipS
   const int64_t chunks_per_seq = (plan.max_chunks + s->batch - 1) / s->batch, row_tiles = (plan.rows + 63) / 64;
   int64_t combine_waves = (chunks_per_seq + kCombineRun - 1) / kCombineRun;
   combine_waves = combine_waves < 1 ? 1 : (combine_waves > kCombineClasses ? kCombineClasses : combine_waves);
-  hipLaunchKernelGGL(score_combine_kernel, dim3((unsigned)(row_tiles * s->batch), (unsigned)(s->n_layers * s->n_kv_heads)),
-                     dim3((unsigned)(64 * combine_waves)), 0, stream, p, (int)row_tiles);
-  DAPQ_HIP_LAUNCH_CHECK("score_combine_kernel");
+  // (a launch holds fewer than 2^32 threads along an axis)
+  const int64_t seqs_per_launch = ((int64_t)1 << 21) / row_tiles;
+  for (int64_t first = 0; first < s->batch; first += seqs_per_launch) {
+    const int64_t seqs = s->batch - first < seqs_per_launch ? s->batch - first : seqs_per_launch;
+    hipLaunchKernelGGL(score_combine_kernel, dim3((unsigned)(row_tiles * seqs), (unsigned)(s->n_layers * s->n_kv_heads)),
+                       dim3((unsigned)(64 * combine_waves)), 0, stream, p, (int)row_tiles, (int)first);
+    DAPQ_HIP_LAUNCH_CHECK("score_combine_kernel");
+  }
   return DAPQ_OK;
 }
 

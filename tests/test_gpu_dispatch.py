@@ -242,6 +242,22 @@ def test_small_ragged_calls_write_no_chunk_prefix(H, batch):
         assert kept == (batch <= 64)
 
 
+def test_scores_of_very_many_sequences(H):
+    """2^26 + 100 sequences of one key each: every score is the number of query rows.  Keys of 17 GB, a workspace of 35 GB."""
+    announce("scores of 67 million sequences")
+    batch = (1 << 26) + 100
+    cu = torch.arange(batch + 1, dtype=torch.int32, device="cuda")
+    k = torch.zeros((batch, 128), dtype=torch.bfloat16, device="cuda")
+    q = torch.ones((2, 128), dtype=torch.bfloat16, device="cuda")
+    shape = H.D.make_shape(n_layers=1, batch=batch, n_q_heads=2, n_kv_heads=1, n_pseudo=1, total_tokens=batch, cu_seqlens=cu,
+                           k_strides=(0, 0, 0, 128), q_strides=(0, 0, 128, 128), scale=128 ** -0.5)
+    ws = torch.empty(H.D.workspace_bytes(shape), dtype=torch.uint8, device="cuda")
+    ws.fill_(0xFF)
+    S = torch.empty((1, 1, batch), dtype=torch.float32, device="cuda")
+    H.D.dapq_score(shape, q, k, S, ws)
+    assert (S == 2.0).all()
+
+
 def score_values(kind, rng, n):
     x = rng.random(n, dtype=np.float32)
     if kind == "octaves":
