@@ -110,7 +110,7 @@ static int finish_score_plan(const dapq_shape* s, int64_t heads, int chunk, Scor
   return DAPQ_OK;
 }
 
-int make_score_plan(const dapq_shape* s, ScorePlan* p) {
+int make_score_plan(const dapq_shape* s, size_t workspace_bytes, ScorePlan* p) {
   const int g = s->n_q_heads / s->n_kv_heads;
   const int64_t rows64 = (int64_t)g * s->n_pseudo;
   DAPQ_REQUIRE(rows64 <= (1 << 20), DAPQ_ERR_UNSUPPORTED, "group * n_pseudo = %lld rows per KV head is too large",
@@ -158,6 +158,14 @@ int make_score_plan(const dapq_shape* s, ScorePlan* p) {
   }
   int rc = finish_score_plan(s, heads, chunk, p);
   if (rc != DAPQ_OK) return rc;
+  // Ragged batches choose their chunk by the total and the mean length, so a shorter one may have more chunks than a longer one (4 layers
+  // of 8 KV heads, 8 prompts, 128 rows: 2.3 MB at 29 696 tokens, 1.4 MB at 32 768).  A workspace that was sized for the longer one
+  // holds the sums of the shorter one in chunks as long.
+  if (s->cu_seqlens != nullptr && p->total_bytes > workspace_bytes) {
+    for (int c = 2 * chunk; c <= kMaxChunkKeys && p->total_bytes > workspace_bytes; c *= 2)
+      if ((rc = finish_score_plan(s, heads, c, p)) != DAPQ_OK) return rc;
+    if (p->total_bytes > workspace_bytes && (rc = finish_score_plan(s, heads, chunk, p)) != DAPQ_OK) return rc;
+  }
 
   // The tile form: a workgroup per 128 keys, its waves a row block each.  It is the faster one where the wave form leaves
   // the chip idle or pays its start-up per chunk (the queries of up to 256 rows into one wave, a ring of its own, tickets).
@@ -179,10 +187,13 @@ int make_score_plan(const dapq_shape* s, ScorePlan* p) {
   t.rows_pad = t.row_blocks * 32;
   rc = finish_score_plan(s, heads, kTileKeys, &t);
   if (rc != DAPQ_OK) return rc;
-  // The workspace is no smaller than the wave form's: its size does not depend on which side of the line a shape falls.
+  // The figure is no smaller than the wave form's, which a caller may have sized its workspace for by another shape.
   if (t.total_bytes < p->total_bytes) t.total_bytes = p->total_bytes;
-  // (where it would be larger, a shape that dapq_score_static serves is still served)
-  if (t.total_bytes <= DAPQ_STATIC_SCRATCH_BYTES || p->total_bytes > DAPQ_STATIC_SCRATCH_BYTES) *p = t;
+  // The partials of the tile form can take more room than the wave form does (the shapes above: 4.0 MB at 29 696 tokens).  A workspace
+  // that holds only the wave form gets the wave form.  And a shape that dapq_score_static serves is still served, by the same kernels
+  // as dapq_score's: tiles of more than its scratch array are not taken.
+  if (t.total_bytes > DAPQ_STATIC_SCRATCH_BYTES && p->total_bytes <= DAPQ_STATIC_SCRATCH_BYTES) return DAPQ_OK;
+  if (t.total_bytes <= workspace_bytes) *p = t;
   return DAPQ_OK;
 }
 
@@ -191,7 +202,7 @@ int make_score_plan(const dapq_shape* s, ScorePlan* p) {
 extern "C" DAPQ_API size_t dapq_workspace_bytes(const dapq_shape* shape) {
   if (dapq::check_shape(shape, false, false, false) != DAPQ_OK) return 0;
   dapq::ScorePlan plan;
-  if (dapq::make_score_plan(shape, &plan) != DAPQ_OK) return 0;
+  if (dapq::make_score_plan(shape, SIZE_MAX, &plan) != DAPQ_OK) return 0;
   return plan.total_bytes;
 }
 

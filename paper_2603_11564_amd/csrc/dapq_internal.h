@@ -31,7 +31,7 @@ constexpr int kMinChunkKeys = 128;      // fewest keys one wave of a score pass 
 constexpr int kMaxChunkKeys = 1 << 16;  // most
 constexpr int kTileKeys = kMinChunkKeys;  // keys of a workgroup of the tile form of the score passes
 
-// How the score passes split the work; a pure function of the shape so that
+// How the score passes split the work; a pure function of the shape and of the size of the workspace, so that
 // dapq_workspace_bytes() and the launchers agree.
 struct ScorePlan {
   bool tile;       // the tile kernels (a workgroup per chunk, its waves share out the rows) instead of the wave kernels
@@ -48,7 +48,8 @@ struct ScorePlan {
 // Validates the fields every entry point relies on.  need_q / need_k / need_v say which stride
 // groups must be usable.  Returns DAPQ_OK or sets the error and returns its code.
 int check_shape(const dapq_shape* s, bool need_q, bool need_k, bool need_v);
-int make_score_plan(const dapq_shape* s, ScorePlan* plan);
+// workspace_bytes: what the caller's workspace holds (SIZE_MAX to ask for what the shape would like).
+int make_score_plan(const dapq_shape* s, size_t workspace_bytes, ScorePlan* plan);
 
 // How the wave kernels split the rows: one wave holds a group of up to 256 in its registers.
 struct RowSplit {

@@ -1592,7 +1592,7 @@ extern "C" DAPQ_API int dapq_score_stats(const dapq_shape* shape, const void* q,
   int rc = check_shape(shape, true, true, false);
   if (rc != DAPQ_OK) return rc;
   ScorePlan plan;
-  if ((rc = make_score_plan(shape, &plan)) != DAPQ_OK) return rc;
+  if ((rc = make_score_plan(shape, workspace_bytes, &plan)) != DAPQ_OK) return rc;
   if ((rc = aligned16(q, "q")) != DAPQ_OK) return rc;
   if ((rc = aligned16(k, "k")) != DAPQ_OK) return rc;
   DAPQ_REQUIRE(lse2 != nullptr, DAPQ_ERR_INVALID_ARG, "lse2 is NULL");
@@ -1617,7 +1617,7 @@ extern "C" DAPQ_API int dapq_score_accumulate(const dapq_shape* shape, const voi
   int rc = check_shape(shape, true, true, false);
   if (rc != DAPQ_OK) return rc;
   ScorePlan plan;
-  if ((rc = make_score_plan(shape, &plan)) != DAPQ_OK) return rc;
+  if ((rc = make_score_plan(shape, workspace_bytes, &plan)) != DAPQ_OK) return rc;
   if ((rc = aligned16(q, "q")) != DAPQ_OK) return rc;
   if ((rc = aligned16(k, "k")) != DAPQ_OK) return rc;
   DAPQ_REQUIRE(lse2 != nullptr, DAPQ_ERR_INVALID_ARG, "lse2 is NULL");
@@ -1640,7 +1640,7 @@ extern "C" DAPQ_API int dapq_score_single_launch(const dapq_shape* shape) {
   int rc = check_shape(shape, true, true, false);
   if (rc != DAPQ_OK) return rc;
   ScorePlan plan;
-  if ((rc = make_score_plan(shape, &plan)) != DAPQ_OK) return rc;
+  if ((rc = make_score_plan(shape, SIZE_MAX, &plan)) != DAPQ_OK) return rc;
   return fused_applies(shape, plan) ? 1 : 0;
 }
 
@@ -1649,7 +1649,7 @@ extern "C" DAPQ_API int dapq_score(const dapq_shape* shape, const void* q, const
   int rc = check_shape(shape, true, true, false);
   if (rc != DAPQ_OK) return rc;
   ScorePlan plan;
-  if ((rc = make_score_plan(shape, &plan)) != DAPQ_OK) return rc;
+  if ((rc = make_score_plan(shape, workspace_bytes, &plan)) != DAPQ_OK) return rc;
   DAPQ_REQUIRE(scores != nullptr, DAPQ_ERR_INVALID_ARG, "scores is NULL");
   if ((rc = check_workspace(workspace, workspace_bytes, plan)) != DAPQ_OK) return rc;
   if (fused_applies(shape, plan)) {
@@ -1697,7 +1697,7 @@ extern "C" DAPQ_API int dapq_score_stats_extend(const dapq_shape* shape, const v
   int rc = check_shape(shape, true, false, false);
   if (rc != DAPQ_OK) return rc;
   ScorePlan plan;
-  if ((rc = make_score_plan(shape, &plan)) != DAPQ_OK) return rc;
+  if ((rc = make_score_plan(shape, SIZE_MAX, &plan)) != DAPQ_OK) return rc;
   if ((rc = aligned16(q, "q")) != DAPQ_OK) return rc;
   if ((rc = aligned16(k_pseudo, "k_pseudo")) != DAPQ_OK) return rc;
   DAPQ_REQUIRE(lse2 != nullptr, DAPQ_ERR_INVALID_ARG, "lse2 is NULL");
@@ -1774,7 +1774,7 @@ extern "C" DAPQ_API int dapq_score_static(const dapq_shape* shape, const void* q
   int rc = check_shape(shape, true, true, false);
   if (rc != DAPQ_OK) return rc;
   ScorePlan plan;
-  if ((rc = make_score_plan(shape, &plan)) != DAPQ_OK) return rc;
+  if ((rc = make_score_plan(shape, SIZE_MAX, &plan)) != DAPQ_OK) return rc;
   DAPQ_REQUIRE(plan.total_bytes <= kStaticScratchBytes, DAPQ_ERR_WORKSPACE,
                "this shape needs %zu bytes of workspace, the built-in scratch array holds %zu: use dapq_score with a "
                "caller workspace", plan.total_bytes, kStaticScratchBytes);

@@ -253,6 +253,27 @@ def test_many_heads_of_few_rows_are_not_refused(lib):
         assert lib.dapq_rope_apply(FAKE, FAKE, FAKE, rows, heads, d, heads * d, d, 5e5, 0, None) == ERR_HIP, lib.dapq_last_error()
 
 
+def test_a_workspace_sized_for_a_longer_batch_serves_shorter_ones(lib):
+    """Small ragged batches like more workspace than larger ones, and run without it: the call gets as far as its launch, which
+    reports that there is no GPU here."""
+    if os.path.exists("/dev/kfd"):
+        pytest.skip("would be launched, with pointers that are none")
+
+    def ragged(tokens):
+        s = good_shape(n_layers=4, batch=8, n_pseudo=32, total_tokens=tokens, k_strides=(tokens * 8 * 128, 0, 128, 8 * 128),
+                       q_strides=(8 * 32 * 32 * 128, 32 * 32 * 128, 32 * 128, 128))
+        s.cu_seqlens = FAKE                                                                  # never dereferenced here
+        return s
+    # (the first three: what these batches asked for when every shape ran in the kernels for larger ones)
+    for tokens, enough in ((16384, 1442304), (20000, 1704448), (25000, 1999360), (29696, D.workspace_bytes(ragged(32768)))):
+        sp = C.byref(ragged(tokens))
+        assert enough < D.workspace_bytes(ragged(tokens))
+        assert lib.dapq_score(sp, FAKE, FAKE, FAKE, FAKE, enough, None) == ERR_HIP, lib.dapq_last_error()
+        assert lib.dapq_score_stats(sp, FAKE, FAKE, FAKE, FAKE, enough, None) == ERR_HIP, lib.dapq_last_error()
+        assert lib.dapq_score_accumulate(sp, FAKE, FAKE, FAKE, FAKE, FAKE, enough, None) == ERR_HIP, lib.dapq_last_error()
+        assert lib.dapq_score(sp, FAKE, FAKE, FAKE, FAKE, 1 << 18, None) == ERR_WORKSPACE
+
+
 def test_binding_raises_with_the_library_message():
     with pytest.raises(D.DapqError) as e:
         D.dapq_pool(good_shape(), None, None, 7, stream=0)

@@ -258,6 +258,31 @@ def test_scores_of_very_many_sequences(H):
     assert (S == 2.0).all()
 
 
+@pytest.mark.parametrize("rows", [128, 200])
+def test_small_ragged_scores_in_a_workspace_sized_for_longer_ones(H, rows):
+    """A workspace that holds the wave form's sums only: the oracle's scores within 1e-3 (the bar of the other score tests), the same
+    bits from the two separate entry points, and nothing written past the end of it."""
+    announce(f"small workspace: rows={rows}")
+    lens = [3000, 1, 4000, 0, 2500, 700, 3300, 2047]
+    q, k, v, cu = problem_bits(rows, 2, lens, 2, 2, rows)
+    prob = H.Problem(q, k, v, 2, cu, "thd")
+    prob.shape.n_layers, prob.shape.k_stride_layer, prob.shape.q_stride_layer = 16, 0, 0        # 16 times the first layer
+    want = H.D.workspace_bytes(prob.shape)
+    prob.shape.total_tokens = 40000
+    ws_bytes = H.D.workspace_bytes(prob.shape)
+    prob.shape.total_tokens = prob.tokens
+    assert ws_bytes < want
+    whole = torch.full((want,), 0xA5, dtype=torch.uint8, device="cuda")
+    S, T = (torch.full((16, 2, prob.tokens), float("nan"), dtype=torch.float32, device="cuda") for _ in range(2))
+    H.D.dapq_score(prob.shape, prob.q, prob.k, S, whole[:ws_bytes])
+    lse = torch.empty((16, len(lens), 2, rows), dtype=torch.float32, device="cuda")
+    H.D.dapq_score_stats(prob.shape, prob.q, prob.k, lse, whole[:ws_bytes])
+    H.D.dapq_score_accumulate(prob.shape, prob.q, prob.k, lse, T, whole[:ws_bytes])
+    assert torch.equal(S, T) and torch.equal(S, S[:1].expand_as(S))
+    assert (whole[ws_bytes:] == 0xA5).all()
+    H.assert_scores_close(S[:1].cpu().numpy(), O.score(q[:1], k[:1], 2, cu), f"rows={rows}")
+
+
 def score_values(kind, rng, n):
     x = rng.random(n, dtype=np.float32)
     if kind == "octaves":
