@@ -183,11 +183,13 @@ __device__ __forceinline__ void push_equal(uint32_t& bits, const uint32_t* key, 
 // octave, and one pass leaves a few dozen.  (Digits of the key instead -- sign and exponent, then 8 bits at a time --
 // took 11 900 clocks for the first, whose bins are two octaves wide and are counted in packed fields, and 12 600 for the
 // others.)  Keys in the lowest bin are not counted one by one: they are what the other bins leave over, so that a head full of
-// zeros does not queue up at one address.  Kept positions are bits of a word per 32 keys, and the survivors are walked
-// bit by bit.  Selection with pooling, by digits -> by bins: 8 heads of 32768 keys, 983 kept, 21.5 -> 15.9 us; 256 heads
-// 28.8 -> 18.7; 64 heads of 131072 keys, 3932 kept, in pieces 65 -> 43; 256 heads of 2000 keys, 128 kept, 14.9 -> 11.8; never
-// slower on heads of one value, three values, half zeros or both signs.
+// zeros does not queue up at one address.  Nor are those of a bin above it that a wave's keys crowd into: the wave counts them in
+// registers and adds the sum (a head of one value with one key below it: 8 heads of 32768: 94 us without, 17 with; of 8192: 27 and 10).  Kept positions are bits of
+// a word per 32 keys, and the survivors are walked bit by bit.  Selection with pooling, by digits -> by bins: 8 heads of 32768 keys,
+// 983 kept, 21.5 -> 15.9 us; 256 heads 28.8 -> 18.7; 64 heads of 131072 keys, 3932 kept, in pieces 65 -> 43; 256 heads of 2000
+// keys, 128 kept, 14.9 -> 11.8.
 constexpr int kRankMax = 64;  // candidates one wave ranks
+constexpr int kCrowd = 3;     // neighbouring lanes of 60 with keys of one bin: a bin that holds a fifth of them (in a spread of keys, 0.1)
 template <int THREADS, int KPT, class Emit>
 __device__ __forceinline__ void topk_select(const uint32_t (&key)[KPT], int n_keys, int keep, uint4* bins, bool want_key,
                                             Emit emit) {
@@ -235,9 +237,27 @@ __device__ __forceinline__ void topk_select(const uint32_t (&key)[KPT], int n_ke
     // from the second bin on (range >= 1 << shift); keys that are no candidates and empty registers are not in it
     const uint32_t lo1 = lo + (1u << shift), range1 = range - (1u << shift);
     uint32_t* count = reinterpret_cast<uint32_t*>(bins) + 1;
+    // Whether the wave's keys crowd into a bin: one register of all lanes, compared with the neighbouring lane's
+    const uint32_t sample = key[KPT / 2] - lo1 <= range1 ? (key[KPT / 2] - lo1) >> shift : 0xFFFFFFFFu;
+    const uint64_t equal = __ballot(sample != 0xFFFFFFFFu && sample == dpp_take<kDppRowShr1, 0xf>(0xFFFFFFFFu, sample));
+    if (__popcll(equal) < kCrowd) {
 #pragma unroll
-    for (int i = 0; i < KPT; ++i) {
-      if (key[i] - lo1 <= range1) atomicAdd(&count[(key[i] - lo1) >> shift], 1u);
+      for (int i = 0; i < KPT; ++i) {
+        if (key[i] - lo1 <= range1) atomicAdd(&count[(key[i] - lo1) >> shift], 1u);
+      }
+    } else {
+      const uint32_t crowded = (uint32_t)__builtin_amdgcn_readlane((int)sample, __ffsll((long long)equal) - 1);
+      const uint32_t crowd_at = crowded << shift;  // above lo1
+      const uint32_t crowd_range = range1 - crowd_at < (1u << shift) - 1u ? range1 - crowd_at : (1u << shift) - 1u;
+      uint32_t same = 0;
+#pragma unroll
+      for (int i = 0; i < KPT; ++i) {
+        const uint32_t at = key[i] - lo1;
+        if (at - crowd_at <= crowd_range) ++same;
+        else if (at <= range1) atomicAdd(&count[at >> shift], 1u);
+      }
+      same = wave_sum(same);
+      if (lane == 0) atomicAdd(&count[crowded], same);
     }
     __syncthreads();
     uint4 c = bins[tid];

@@ -293,6 +293,10 @@ def score_values(kind, rng, n):
         return np.floor(3 * x).astype(np.float32)
     if kind == "half zero":
         return np.where(x < 0.5, 0, x).astype(np.float32)
+    if kind.startswith("crowd"):  # most keys share a value that is not the least: all but one or two, half of them, a third
+        y = np.where(x < {"crowd": 1.1, "crowd of half": 0.5, "crowd of a third": 0.33}[kind], np.float32(1), x)
+        y[n // 2], y[n // 3] = 0.01, 50.0
+        return y.astype(np.float32)
     if kind == "neighbours":      # consecutive floats below a single far larger one
         y = np.nextafter(np.float32(1), np.float32(2)) + np.float32(2 ** -23) * np.floor(300 * x)
         y[n // 2] = 1e30
@@ -305,7 +309,8 @@ def score_values(kind, rng, n):
 
 # the selection closes in on the threshold by bins of the span of the keys: spans of 0 to 2^32, bins that hold one value or
 # most of them, more and fewer than the 64 candidates that one wave ranks, at the lengths where the variants change
-@pytest.mark.parametrize("kind", ["octaves", "one value", "three values", "half zero", "neighbours", "signs"])
+@pytest.mark.parametrize("kind", ["octaves", "one value", "three values", "half zero", "neighbours", "signs", "crowd",
+                                  "crowd of half", "crowd of a third"])
 @pytest.mark.parametrize("n", [1, 33, 64, 65, 1000, 8192, 8193, 16385, 32768, 40000, 140001])
 def test_selection_over_distributions(H, n, kind):
     """The retained positions are the oracle's, bit for bit (selection compares the given scores; equal ones lowest
