@@ -184,10 +184,10 @@ __device__ __forceinline__ void push_equal(uint32_t& bits, const uint32_t* key, 
 // took 11 900 clocks for the first, whose bins are two octaves wide and are counted in packed fields, and 12 600 for the
 // others.)  Keys in the lowest bin are not counted one by one: they are what the other bins leave over, so that a head full of
 // zeros does not queue up at one address.  Nor are those of a bin above it that a wave's keys crowd into: the wave counts them in
-// registers and adds the sum (a head of one value with one key below it: 8 heads of 32768: 94 us without, 17 with; of 8192: 27 and 10).  Kept positions are bits of
-// a word per 32 keys, and the survivors are walked bit by bit.  Selection with pooling, by digits -> by bins: 8 heads of 32768 keys,
-// 983 kept, 21.5 -> 15.9 us; 256 heads 28.8 -> 18.7; 64 heads of 131072 keys, 3932 kept, in pieces 65 -> 43; 256 heads of 2000
-// keys, 128 kept, 14.9 -> 11.8.
+// registers and adds the sum (heads of one value with one key below it: 8 of 32768 keys 94 us without, 17 with; 256 of 8192
+// 27 and 10).  Kept positions are bits of a word per 32 keys, and the survivors are walked bit by bit.  Selection with pooling, by
+// digits -> by bins: 8 heads of 32768 keys, 983 kept, 21.5 -> 15.9 us; 256 heads 28.8 -> 18.7; 64 heads of 131072 keys, 3932
+// kept, in pieces 65 -> 43; 256 heads of 2000 keys, 128 kept, 14.9 -> 11.8.
 constexpr int kRankMax = 64;  // candidates one wave ranks
 constexpr int kCrowd = 3;     // neighbouring lanes of 60 with keys of one bin: a bin that holds a fifth of them (in a spread of keys, 0.1)
 template <int THREADS, int KPT, class Emit>
@@ -535,7 +535,7 @@ __global__ __launch_bounds__(THREADS) void topk_merge_kernel(TopkParams p) {
   int seg = s0 / p.budget, r = s0 - seg * p.budget;
   uint32_t key[KPT];
   // (16-byte loads of slots that hold no candidate read the workspace's old contents, which are dropped)
-  const bool quads = (slots & 3) == 0;
+  const bool quads = (slots & 3) == 0 && (reinterpret_cast<uintptr_t>(ck) & 15) == 0;
 #pragma unroll
   for (int i = 0; i < KPT; i += 4) {
     if (quads && s0 + i < slots) {

@@ -366,3 +366,20 @@ def test_rotation_of_many_heads(H, rows, heads, d):
     x = W.to_bf16_bits(rng.standard_normal((rows, heads, d), dtype=np.float32))
     pos = rng.integers(0, 140000, rows)
     assert np.array_equal(H.rope_gpu(x, pos, 500000.0), O.rope_apply(x, pos, 500000.0))
+
+
+@pytest.mark.parametrize("offset", [0, 4, 8])
+def test_candidates_of_long_heads_off_16_bytes(H, offset):
+    """A workspace that starts `offset` bytes past a 16-byte boundary gives the oracle's positions too."""
+    announce(f"selection in pieces, workspace {offset} bytes off")
+    n, budget = 100000, 1000
+    S = np.random.default_rng(offset).random((1, 2, n), dtype=np.float32)
+    zero = np.zeros((1, n, 2, 128), dtype=np.uint16)
+    prob = H.Problem(np.zeros((1, 1, 2, 1, 128), dtype=np.uint16), zero, zero, 2, None, "hnd")
+    need = H.D.topk_workspace_bytes(prob.shape, budget)
+    ws = torch.full((need + 16,), 0xA5, dtype=torch.uint8, device="cuda")[offset:offset + need]
+    idx = torch.empty((1, 1, 2, budget), dtype=torch.int32, device="cuda")
+    count = torch.empty((1, 1, 2), dtype=torch.int32, device="cuda")
+    H.D.dapq_topk(prob.shape, torch.from_numpy(S).cuda(), budget, None, idx, count, ws)
+    for kv in range(2):
+        assert np.array_equal(idx.cpu().numpy()[0, 0, kv], O.topk(S[0, kv].astype(np.float64), budget))
