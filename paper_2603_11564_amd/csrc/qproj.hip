@@ -461,9 +461,9 @@ extern "C" DAPQ_API int dapq_pseudo_queries(const dapq_qproj* desc, const void* 
   else if (pl.mb == 2) launch_qproj<2, 2>(p, st);
   else launch_qproj<2, 1>(p, st);
   DAPQ_HIP_LAUNCH_CHECK("qproj_wave_kernel");
-  const int64_t pairs = (int64_t)s.rows * (s.head_dim / 2), head_layers = (int64_t)s.n_q_heads * s.n_layers;
-  if (pl.k_splits > 1 && positions != nullptr && pairs < ((int64_t)1 << 30) && head_layers <= 65535) {
-    const dim3 grid((unsigned)((pairs + 255) / 256), (unsigned)head_layers);
+  if (pl.k_splits > 1 && positions != nullptr) {
+    // (a split call has fewer than 768 tiles of 64 features and 64 rows: fewer than 2^13 heads of all layers, and 2^21 channel pairs)
+    const dim3 grid((unsigned)(((int64_t)s.rows * (s.head_dim / 2) + 255) / 256), (unsigned)(s.n_q_heads * s.n_layers));
     const int rows_pad = pl.sweeps * 32 * pl.mb, feat_pad = pl.tiles_f * 32 * pl.ft;
     const double e = rope_exponent(theta, s.head_dim);
     if (pl.k_splits == 2) hipLaunchKernelGGL(qproj_reduce_rope_kernel<2>, grid, dim3(256), 0, st, p, rows_pad, feat_pad, positions, e, pairing);

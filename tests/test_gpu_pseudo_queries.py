@@ -209,6 +209,33 @@ def test_rotated_queries_match_oracle_and_the_two_calls(H, pairing):
         assert (got[l] == want_bits).mean() > 0.98
 
 
+# 2, 4, 8 and 16 hidden splits, whose sums are rotated as they are added up; channel pairs that do not fill a workgroup, head sizes
+# that do not fill a feature tile, one and several sweeps and layers
+@pytest.mark.parametrize("pairing", [0, 1])
+@pytest.mark.parametrize("hidden,splits", [(1024, 2), (2048, 4), (4096, 8), (8192, 16)])
+@pytest.mark.parametrize("layers,Hq,d,rows", [(1, 3, 72, 37), (2, 2, 128, 65), (1, 1, 8, 1)])
+def test_rotated_queries_of_split_calls(H, layers, Hq, d, rows, hidden, splits, pairing):
+    """One call = the projection (without positions), then dapq_rope_apply on its output: bit for bit, with missing sources, padded
+    strides and rows past the end left alone; and the projection is the oracle's (check_projection)."""
+    announce(f"pseudo queries: rotation of {splits} splits, {layers} layers, {Hq} heads of {d}, {rows} rows, pairing {pairing}")
+    r = np.random.default_rng(hidden + rows)
+    tokens = 20
+    tok = r.integers(-1, tokens, rows).tolist()
+    pos = r.integers(0, 140000, rows).tolist()
+    desc = H.D.Qproj(n_layers=layers, rows=rows, hidden=hidden, n_q_heads=Hq, head_dim=d, total_tokens=tokens, x_stride_layer=0,
+                     x_stride_token=hidden, w_stride_layer=0, w_stride_row=hidden, q_stride_layer=0, q_stride_head=rows * d,
+                     q_stride_row=d)
+    block = 64 if rows > 32 else 32
+    assert H.D.pseudo_queries_workspace_bytes(desc) == splits * layers * (-(-rows // block) * block) * (-(-Hq * d // 64) * 64) * 4
+    args = dict(x_pad=8, w_pad=8, q_pad_rows=2)
+    got, x_bits, w_bits = run_case(H, 80, layers, tokens, hidden, Hq, d, tok, positions=pos, pairing=pairing, **args)
+    pre, _, _ = run_case(H, 80, layers, tokens, hidden, Hq, d, tok, **args)
+    check_projection(pre, x_bits, w_bits, tok, Hq, hidden)
+    for l in range(layers):
+        turned = H.rope_gpu(np.ascontiguousarray(pre[l].transpose(1, 0, 2)), pos, 500000.0, pairing)
+        assert np.array_equal(turned.transpose(1, 0, 2), got[l])
+
+
 def test_queries_feed_the_score_path(H):
     """token indices -> queries -> scores: the chain of Sec. 4.1 and 4.2 on the device against the same chain in the
     oracle.  The device's queries may differ from the oracle's by one bf16 step where the projection sat on a
