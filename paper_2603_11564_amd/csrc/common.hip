@@ -191,7 +191,8 @@ int make_score_plan(const dapq_shape* s, size_t workspace_bytes, ScorePlan* p) {
   if (t.total_bytes < p->total_bytes) t.total_bytes = p->total_bytes;
   // The partials of the tile form can take more room than the wave form does (the shapes above: 4.0 MB at 29 696 tokens).  A workspace
   // that holds only the wave form gets the wave form.  And a shape that dapq_score_static serves is still served, by the same kernels
-  // as dapq_score's: tiles of more than its scratch array are not taken.
+  // as dapq_score's: tiles of more than its scratch array (128 bytes per unit: about 32 000 units) are not taken where the wave form
+  // fits it.  That line is one of room, not of time.
   if (t.total_bytes > DAPQ_STATIC_SCRATCH_BYTES && p->total_bytes <= DAPQ_STATIC_SCRATCH_BYTES) return DAPQ_OK;
   if (t.total_bytes <= workspace_bytes) *p = t;
   return DAPQ_OK;

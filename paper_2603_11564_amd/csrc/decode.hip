@@ -350,9 +350,13 @@ int launch_decode(int64_t heads, const DecodeParams& p, hipStream_t stream) {
   return DAPQ_OK;
 }
 
-// Slices per head: every slice reads all of K_c, so they pay only while most compute units would have no workgroup.  8
-// heads x 983 rows: 13.8 us with one slice, 11.0 us with four (before the loads were whole rows); 64 heads x 4096 rows:
-// 55.4 us with four, 37.5 us with two.
+// Slices per head: every slice reads all of K_c, so they pay only while most compute units would have no workgroup.  One layer,
+// us with four / two / one slice:
+//   4 query heads per KV head, 983 rows    32 heads 7.1 / 7.8 / 8.7   40: 7.2 / 7.9 / 8.8   64: 7.8 / 8.3 / 9.0   96: 15.3 / 10.2 / 10.2
+//                                          128: 19.2 / 13.3 / 12.1    144: 25.9 / 19.7 / 13.0
+//   4, 256 rows                            40: 4.9 / 5.5 / 5.6        96: 8.5 / 5.4 / 5.5   144: 12.5 / 9.7 / 5.7
+//   8, 4096 rows                           8: 19.4 / 21.5 / 30.1      32: 27.8 / 23.3 / 30.1   64: 56.9 / 30.6 / 30.2   128: 112 / 60 / 42
+// The lines are between where short and where long caches would have them: of these, 128 heads of 4096 rows lose most (1.43 times).
 template <int HT>
 int launch_decode_slices(int64_t heads, const DecodeParams& p, hipStream_t stream) {
   if (heads <= 32) return launch_decode<HT, 2, 8>(heads, p, stream);
