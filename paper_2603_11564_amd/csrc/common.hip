@@ -85,7 +85,9 @@ int check_shape(const dapq_shape* s, bool need_q, bool need_k, bool need_v) {
 // The plan's chunks along the key axis and its workspace, once the rows are split and the chunk is chosen.
 static int finish_score_plan(const dapq_shape* s, int64_t heads, int chunk, ScorePlan* p) {
   p->chunk_keys = chunk;
-  if (s->cu_seqlens == nullptr) {
+  if (p->segments > 0) {
+    p->max_chunks = (int64_t)s->batch + p->segments;
+  } else if (s->cu_seqlens == nullptr) {
     const int64_t L = s->total_tokens / s->batch;
     p->max_chunks = (int64_t)s->batch * ((L + chunk - 1) / chunk);
   } else {
@@ -98,8 +100,7 @@ static int finish_score_plan(const dapq_shape* s, int64_t heads, int chunk, Scor
   size_t off = 0;
   p->off_cu_chunks = off;
   off = align_up(off + sizeof(int32_t) * ((size_t)s->batch + 1), 256);
-  p->off_work = off;  // ticket counter of a ragged batch's work list
-  off += 256;
+  off += 256;  // (nothing lies here: workspaces have always had it)
   p->off_parts = off;
   off = align_up(off + sizeof(float) * (p->tile ? 1 : 2) * (size_t)heads * (size_t)p->max_chunks * p->rows_pad, 256);
   p->off_lse2 = off;
@@ -108,6 +109,26 @@ static int finish_score_plan(const dapq_shape* s, int64_t heads, int chunk, Scor
   if (p->n_groups > 1) off = align_up(off + sizeof(float) * (size_t)(p->n_groups - 1) * (size_t)heads * (size_t)s->total_tokens, 256);
   p->total_bytes = off;
   return DAPQ_OK;
+}
+
+// Segments per head of a ragged batch, `streams` heads x row groups: the waves run in whole rounds of wave_slots, each as long as
+// its share of the key axis, whatever the lengths of the sequences.  Of the numbers that fill 1, 2, ... 16 rounds the one with the
+// least to do: a round's start-up (ring, queries) costs about what a two-hundredth of a head's keys do.  (At most 2^26 keys to a
+// segment, for the offsets in it.)  It does not fall with the tokens, so that fewer of them never need a larger workspace.
+static int ragged_segments(int64_t streams, int64_t wave_slots, int64_t total_tokens) {
+  int64_t best = 1;
+  double least = INFINITY;
+  for (int64_t rounds = 1; rounds <= 16; ++rounds) {
+    const int64_t n = rounds * wave_slots / streams;
+    if (n < 1) continue;
+    const double cost = (double)rounds * (1.0 / (double)n + 0.005);
+    if (cost < least) {
+      least = cost;
+      best = n;
+    }
+  }
+  const int64_t fewest = (total_tokens >> 26) + 1;
+  return (int)(best > fewest ? best : fewest);
 }
 
 int make_score_plan(const dapq_shape* s, size_t workspace_bytes, ScorePlan* p) {
@@ -123,52 +144,37 @@ int make_score_plan(const dapq_shape* s, size_t workspace_bytes, ScorePlan* p) {
   p->row_blocks = split.row_blocks;
   p->rows_pad = p->n_groups * p->row_blocks * 32;
   p->tile = false;
+  p->segments = 0;
 
-  // Keys per wave.  The machine runs kWaveSlots waves at a time, each for as long as its chunk; a
-  // wave pays a fixed start-up (Q fragments, ring fill) worth about kStartKeys keys.  Dense batches
-  // run in whole rounds of equal chunks: pick the chunk with the shortest rounds x (chunk +
-  // start-up).  Ragged batches (lengths unknown on the host) are handed out chunk by chunk to
-  // persistent waves, so the cost is the work per slot plus half a chunk of tail imbalance on average -- a
-  // sequence shorter than the chunk is a shorter one, so beyond the mean length only half as much again.  Their items
-  // start later too (ticket, look-up, then queries and ring): kStartRagged.  Both passes, chunks of 1024 -> 2048, 32
-  // layers: 16 prompts of 200..2500 keys, 128 rows 754 -> 720 us, 16 of 175..1400, 256 rows 798 -> 703, 8 of 750..6000,
-  // 128 rows 784 -> 736; at 8 of 4096..16384, 512 rows it stays with the 4096 that are best there (2048: 2.5 % more).
-  constexpr int64_t kWaveSlots = 1024, kStartKeys = 160, kStartRagged = 256;
-  const int64_t units_per_chunk_row = heads * p->n_groups;
-  int chunk = kMinChunkKeys;
-  int64_t best = INT64_MAX;
-  for (int c = kMaxChunkKeys; c >= kMinChunkKeys; c /= 2) {
-    int64_t cost;
-    if (s->cu_seqlens == nullptr) {
-      const int64_t L = s->total_tokens / s->batch;
-      const int64_t units = units_per_chunk_row * s->batch * ((L + c - 1) / c);
+  constexpr int64_t kWaveSlots = 1024;
+  int rc;
+  if (s->cu_seqlens == nullptr) {
+    // Keys per wave.  The machine runs kWaveSlots waves at a time, each for as long as its chunk; a
+    // wave pays a fixed start-up (Q fragments, ring fill) worth about kStartKeys keys.  Dense batches
+    // run in whole rounds of equal chunks: pick the chunk with the shortest rounds x (chunk +
+    // start-up).
+    constexpr int64_t kStartKeys = 160;
+    const int64_t L = s->total_tokens / s->batch;
+    int chunk = kMinChunkKeys;
+    int64_t best = INT64_MAX;
+    for (int c = kMaxChunkKeys; c >= kMinChunkKeys; c /= 2) {
+      const int64_t units = heads * p->n_groups * s->batch * ((L + c - 1) / c);
       const int64_t rounds = (units + kWaveSlots - 1) / kWaveSlots;
-      cost = rounds * ((L < c ? L : c) + kStartKeys);
-    } else {
-      const int64_t chunks = (s->total_tokens + c - 1) / c + s->batch / 2;
-      const int64_t units = units_per_chunk_row * chunks;
-      const int64_t mean = s->total_tokens / s->batch;
-      cost = (units_per_chunk_row * s->total_tokens + units * kStartRagged) / kWaveSlots +
-             (c <= mean ? c / 2 : mean / 2 + (c - mean) / 4);
+      const int64_t cost = rounds * ((L < c ? L : c) + kStartKeys);
+      if (cost < best) {
+        best = cost;
+        chunk = c;
+      }
     }
-    if (cost < best) {
-      best = cost;
-      chunk = c;
-    }
+    rc = finish_score_plan(s, heads, chunk, p);
+  } else {
+    p->segments = ragged_segments(heads * p->n_groups, kWaveSlots, s->total_tokens);
+    rc = finish_score_plan(s, heads, 32, p);
   }
-  int rc = finish_score_plan(s, heads, chunk, p);
   if (rc != DAPQ_OK) return rc;
-  // Ragged batches choose their chunk by the total and the mean length, so a shorter one may have more chunks than a longer one (4 layers
-  // of 8 KV heads, 8 prompts, 128 rows: 2.3 MB at 29 696 tokens, 1.4 MB at 32 768).  A workspace that was sized for the longer one
-  // holds the sums of the shorter one in chunks as long.
-  if (s->cu_seqlens != nullptr && p->total_bytes > workspace_bytes) {
-    for (int c = 2 * chunk; c <= kMaxChunkKeys && p->total_bytes > workspace_bytes; c *= 2)
-      if ((rc = finish_score_plan(s, heads, c, p)) != DAPQ_OK) return rc;
-    if (p->total_bytes > workspace_bytes && (rc = finish_score_plan(s, heads, chunk, p)) != DAPQ_OK) return rc;
-  }
 
   // The tile form: a workgroup per 128 keys, its waves a row block each.  It is the faster one where the wave form leaves
-  // the chip idle or pays its start-up per chunk (the queries of up to 256 rows into one wave, a ring of its own, tickets).
+  // the chip idle or pays its start-up per chunk (the queries of up to 256 rows into one wave, a ring of its own).
   // Both passes of dapq_score, wave form -> tile form, 8 KV heads: one layer, 1024 keys, 256 rows 38.6 -> 14.9 us; 8191
   // keys, 128 rows 26.9 -> 18.6; 16384 keys, 256 rows 44 -> 41, 512 rows 57 -> 61; 32768 keys, 128 rows 39 -> 45; ragged,
   // 8 prompts of 1000 keys, one layer, 128 rows 76 -> 24, 4 layers, 128 rows (10 000 units) 146 -> 59, 512 rows (40 000
@@ -182,6 +188,7 @@ int make_score_plan(const dapq_shape* s, size_t workspace_bytes, ScorePlan* p) {
   if (one_kernel || tiles * row_blocks > (ragged ? 65536 : 8192) || (!ragged && tiles > 1024)) return DAPQ_OK;
   ScorePlan t = *p;
   t.tile = true;
+  t.segments = 0;
   t.row_blocks = (int)row_blocks;
   t.n_groups = 1;
   t.rows_pad = t.row_blocks * 32;

@@ -39,10 +39,11 @@ struct ScorePlan {
   int n_groups;    // row groups of row_blocks * 32 rows, one wave each per chunk (tile: 1)
   int row_blocks;  // 32-row blocks per wave (2, 4 or 8; tile: all of them)
   int rows_pad;    // n_groups * row_blocks * 32
-  int chunk_keys;  // keys per wave (a power of two)
-  int64_t max_chunks;  // grid size along the key axis: upper bound on sum_b ceil(L_b / chunk_keys)
+  int chunk_keys;  // keys per wave (a power of two; a ragged batch in segments: those of a sub-block)
+  int segments;    // ragged batches in the wave form: the waves that share a head's packed key axis (else 0)
+  int64_t max_chunks;  // partial sums of a row: upper bound on sum_b ceil(L_b / chunk_keys), or batch + segments
   // workspace carving (byte offsets)
-  size_t off_cu_chunks, off_work, off_parts, off_lse2, off_partial, total_bytes;
+  size_t off_cu_chunks, off_parts, off_lse2, off_partial, total_bytes;
 };
 
 // Validates the fields every entry point relies on.  need_q / need_k / need_v say which stride

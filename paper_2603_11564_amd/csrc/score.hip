@@ -51,15 +51,13 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));  // 16 bytes; native vector, stays in registers
 
-constexpr int kLists = 8;  // work lists of a ragged batch, one per XCD (see ItemLists)
-
 struct ScoreParams {
   const uint16_t* q;
   const uint16_t* k;
   const int32_t* cu_seqlens;  // NULL = dense
-  int32_t* cu_chunks;         // [batch+1] prefix of per-sequence chunk counts (ragged only)
-  unsigned* work;             // ragged only: [kLists] next ticket of every work list; zeroed with cu_chunks
-  float2* parts;              // [layer*Hkv][max_chunks][rows_pad] (reference, sum) in the log2 domain
+  int32_t* cu_chunks;         // [batch+1] prefix of per-sequence chunk counts (ragged batches of more than 64 sequences)
+  float2* parts;              // [layer*Hkv][max_chunks][rows_pad] (reference, sum) in the log2 domain; a ragged batch: of
+                              // sequence b in segment i at index b + i
   float* tile_parts;          // tile form: their log2 in one value, reference + log2(sum), -inf for no sum (parts is NULL)
   float* lse2;                // [layer][batch][Hq][N]
   float* scores;              // [layer][Hkv][total_tokens]
@@ -69,6 +67,7 @@ struct ScoreParams {
   int64_t total_tokens;
   int32_t n_layers, batch, n_q_heads, n_kv_heads, group, n_pseudo;
   int32_t rows, rows_pad, n_groups, chunk_keys, max_chunks;
+  int32_t segments;           // ragged batches in the wave form: segments a head is cut into (chunk_keys is a sub-block then)
   int32_t wg_groups;          // row groups that sit side by side in a workgroup (dense launches; 1, 2 or 4)
   float c;  // scale * log2(e)
 };
@@ -94,9 +93,15 @@ __device__ __forceinline__ const T* uniform_ptr(const T* ptr) {
   const unsigned hi = (unsigned)uniform_i32((int)(unsigned)(v >> 32));
   return reinterpret_cast<const T*>((uintptr_t)(((unsigned long long)hi << 32) | lo));
 }
-// Chunks of a sequence of L keys (chunk_keys is a power of two).
+// Chunks of a sequence of L keys (of a ragged batch: chunk_keys is a power of two).
 __device__ __forceinline__ int chunks_of_length(const ScoreParams& p, int L) {
   return L > 0 ? (L + p.chunk_keys - 1) >> __builtin_ctz((unsigned)p.chunk_keys) : 0;
+}
+// The lane number, formed where it is asked for: neither it nor what follows from it is kept in registers from before.
+__device__ __forceinline__ int fresh_lane() {
+  int lane;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
+  return lane;
 }
 
 // A ragged batch of at most 64 sequences, one to a lane: the sequence's start, length and the chunks up to its end.
@@ -106,8 +111,7 @@ struct LaneSequence {
   int start, len, chunks, chunks_end;
 };
 __device__ __forceinline__ LaneSequence lane_sequence(const ScoreParams& p) {
-  int lane = threadIdx.x & 63;
-  asm volatile("" : "+v"(lane));  // formed where it is asked for: not kept in registers through a wave's items
+  const int lane = fresh_lane();
   LaneSequence q;
   q.start = p.cu_seqlens[lane < p.batch ? lane : p.batch];
   q.len = p.cu_seqlens[lane < p.batch ? lane + 1 : p.batch] - q.start;
@@ -169,6 +173,62 @@ __device__ __forceinline__ Work locate(const ScoreParams& p, int gchunk) {
   return w;
 }
 
+// A ragged batch in the wave form: the packed key axis of a head -- the 32-key sub-blocks of its sequences one after the other,
+// `total` of them -- is cut into segments of equal length, the same for all heads, and a wave (per row group) takes one.
+// Segment i holds sub-blocks total * i / n up to total * (i + 1) / n of n segments; none is empty.  (Handed out chunk by chunk from
+// work lists, each chunk with a ring fill of its own, the waves kept too few keys in flight -- with at most 128 rows the passes are
+// bound by the key stream -- and the last items of a launch ran alone.  32 layers, both passes and what belongs to them: 16 prompts
+// of 200..2500 keys, 128 rows, extended 860 -> 766 us; 2 of 11520, 128 rows 651 -> 586; 64 of 100..500, 256 rows 1514 -> 1400; 8 of
+// 4096..16384, 512 rows 5500 -> 5373.  Two waves to a SIMD with a ring of two slots each, on the lists: 987 in the first case.)
+struct Segments {
+  int total, n;
+  __device__ __forceinline__ int start(int i) const { return (int)((int64_t)total * i / n); }
+  // the segment of sub-block g: the last one that starts at or before it
+  __device__ __forceinline__ int of(int g) const { return (int)((((int64_t)g + 1) * n - 1) / total); }
+};
+__device__ __forceinline__ Segments segments_of(const ScoreParams& p, int total) {
+  return {total, p.segments < total ? p.segments : total};
+}
+// The sub-blocks of a segment: `left` of them, from number `sub` of sequence `seq` on (`last`: down from there, the segment's last).
+struct Segment {
+  int seq, sub, left;
+};
+__device__ __forceinline__ Segment segment_of_wave(const ScoreParams& p, int i, bool last) {
+  Segment r = {0, 0, 0};
+  LaneSequence q;
+  const bool by_lanes = p.batch <= 64;
+  if (by_lanes) q = lane_sequence(p);
+  const Segments segs = segments_of(p, by_lanes ? __builtin_amdgcn_readlane(q.chunks_end, 63) : p.cu_chunks[p.batch]);
+  if (i >= segs.n) return r;
+  const int first = segs.start(i), end = segs.start(i + 1), g = last ? end - 1 : first;
+  if (by_lanes) {
+    r.seq = __popcll(__ballot(q.chunks_end <= g));
+    r.sub = g - __builtin_amdgcn_readlane(q.chunks_end - q.chunks, r.seq);
+  } else {
+    int lo = 0, hi = p.batch;  // largest b with cu_chunks[b] <= g (no empty sequence: those end where they start)
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (p.cu_chunks[mid] <= g) lo = mid; else hi = mid;
+    }
+    r.seq = lo;
+    r.sub = g - p.cu_chunks[lo];
+  }
+  r.seq = uniform_i32(r.seq);
+  r.sub = uniform_i32(r.sub);
+  r.left = uniform_i32(end - first);
+  return r;
+}
+// Start and length of a sequence, through the scalar cache: a vector load's answer would be waited for behind the key ring.
+struct SeqRange {
+  int start, len;
+};
+__device__ __forceinline__ SeqRange seq_range(const ScoreParams& p, int seq) {
+  const __attribute__((address_space(4))) int32_t* cu =
+      (const __attribute__((address_space(4))) int32_t*)(uintptr_t)p.cu_seqlens + seq;
+  const int start = cu[0], end = cu[1];
+  return {start, end - start};
+}
+
 // LDS position of 16-byte chunk `ch` of sub-block row `key`: rows are 256 B apart, chunks XOR-swizzled by
 // the row so that 16 consecutive rows reading the same logical chunk hit 16 different bank groups.
 __device__ __forceinline__ int lds_chunk_index(int key, int ch) { return key * 16 + (ch ^ (key & 15)); }
@@ -225,11 +285,9 @@ __device__ __forceinline__ bf16x8 lds_read16(unsigned lane_addr, int const_off) 
 
 // Per-sequence prefix of chunk counts for ragged batches: one wave, 64 sequences per trip (a scan by shuffles
 // inside the wave, the running total carried from trip to trip).
-__global__ void score_chunk_prefix_kernel(const int32_t* cu_seqlens, int32_t* cu_chunks, unsigned* work,
-                                         int batch, int chunk_keys) {
+__global__ void score_chunk_prefix_kernel(const int32_t* cu_seqlens, int32_t* cu_chunks, int batch, int chunk_keys) {
   const int lane = threadIdx.x;  // launched with exactly 64 threads
   if (lane == 0) cu_chunks[0] = 0;
-  if (lane < kLists) work[lane] = 0u;  // the pass that follows hands its items out from here (one counter per work list)
   int carry = 0;
   for (int b0 = 0; b0 < batch; b0 += 64) {
     const int b = b0 + lane;
@@ -265,7 +323,7 @@ __global__ __launch_bounds__(64 * kCombineClasses) void score_combine_kernel(Sco
   const int seq = uniform_i32((int)(blockIdx.x / row_tiles)), row = (int)(blockIdx.x - seq * row_tiles) * 64 + lane;
   const int b = first_seq + seq;
   const int layer = (int)(blockIdx.y / p.n_kv_heads), kv = (int)(blockIdx.y - layer * p.n_kv_heads);
-  int c0, c1;
+  int c0, c1, total = 0;
   if (p.cu_seqlens == nullptr) {
     const int L = (int)(p.total_tokens / p.batch);
     const int cps = (L + p.chunk_keys - 1) / p.chunk_keys;
@@ -275,9 +333,16 @@ __global__ __launch_bounds__(64 * kCombineClasses) void score_combine_kernel(Sco
     const LaneSequence q = lane_sequence(p);
     c1 = __builtin_amdgcn_readlane(q.chunks_end, b);
     c0 = c1 - __builtin_amdgcn_readlane(q.chunks, b);
+    total = __builtin_amdgcn_readlane(q.chunks_end, 63);
   } else {
     c0 = p.cu_chunks[b];
     c1 = p.cu_chunks[b + 1];
+    total = p.cu_chunks[p.batch];
+  }
+  if (p.segments > 0 && c1 > c0) {  // the wave form of a ragged batch: one sum per segment that holds some of the sequence
+    const Segments segs = segments_of(p, total);
+    c0 = b + segs.of(c0);
+    c1 = b + segs.of(c1 - 1) + 1;
   }
   const int n = c1 - c0, runs = (n + kCombineRun - 1) / kCombineRun;
   const int64_t src = ((int64_t)blockIdx.y * p.max_chunks + c0) * p.rows_pad + (row < p.rows ? row : p.rows - 1);
@@ -340,10 +405,6 @@ __global__ __launch_bounds__(64 * kCombineClasses) void score_combine_kernel(Sco
 // The score kernels: one wave = a group of query rows x its own key stream.
 // ---------------------------------------------------------------------------------------------
 constexpr int kWaveStages = 5;            // ring slots (40 KB per wave, 160 KB per compute unit)
-// Persistent workgroups of several waves (ragged batches with more than 256 query rows per KV head) need a few bytes
-// of LDS to pass tickets around, which five slots per wave leave no room for; the ring depth makes no measurable
-// difference between 3 and 5.
-constexpr int kTeamStages = 4;
 constexpr int kSubVec = kSubBytes / 16;   // 512 16-byte chunks per sub-block
 // Dense launches start their waves up to four to a workgroup, one per SIMD of a compute unit, each with its own ring:
 // they never meet at a barrier.  The waves of a workgroup are the row groups of a chunk side by side (a KV head with
@@ -352,7 +413,7 @@ constexpr int kSubVec = kSubBytes / 16;   // 512 16-byte chunks per sub-block
 // (the dispatcher places fewer workgroups and the waves of a compute unit read one head's queries once: 2-3 % for the
 // stream-bound shapes).  Every workgroup must be full -- waves of a half-empty one would idle their SIMDs for the whole
 // launch -- so the number of consecutive chunks is the largest of 4, 2, 1 (divided by the row groups) that divides
-// the chunk count.  (Ragged batches: see the DYN form of the kernels.)
+// the chunk count.  (Ragged batches: the same, with segments of the packed key axis for chunks.)
 constexpr int kWavesPerGroup = 4;
 constexpr int wave_lds(int nst) { return nst * kSubBytes; }
 
@@ -369,14 +430,13 @@ __device__ __forceinline__ void sub_dma_lane_offsets(unsigned (&voff)[4], int64_
 // (buffer_load_dwordx4 ... lds).  The buffer descriptor spans from the first row of the sub-block to
 // the end of the last key row of the chunk, so rows past the end of the chunk read as zeros; the
 // uniform part of every address lives in scalar registers (descriptor base, scalar offset per
-// transfer) and the lane part is one of the four precomputed offsets.  A sub-block that starts before
-// the chunk or at or past its end gets an empty descriptor: the eight transfers still count as vector
+// transfer) and the lane part is one of the four precomputed offsets.  A sub-block that is not `live` (it starts before
+// the chunk or at or past its end) gets an empty descriptor: the eight transfers still count as vector
 // memory operations (the waits rely on a fixed number per sub-block) but fetch nothing and fill the
 // slot with zeros.
-__device__ __forceinline__ void sub_dma(u32x4* slot, const uint16_t* kbase, int64_t stride_token, int key0, int nkeys,
+__device__ __forceinline__ void sub_dma(u32x4* slot, const uint16_t* kbase, int64_t stride_token, int key0, int nkeys, bool live,
                                         const unsigned (&voff)[4]) {
   const int64_t stride_b = stride_token * 2;
-  const bool live = key0 >= 0 && key0 < nkeys;
   const char* base = reinterpret_cast<const char*>(kbase) + (live ? (int64_t)key0 * stride_b : (int64_t)0);
   const int64_t span = (int64_t)(nkeys - key0 - 1) * stride_b + kHeadDim * 2;
   const unsigned records = !live ? 0u : (span > (int64_t)0xFFFFFFFFll ? 0xFFFFFFFFu : (unsigned)span);
@@ -422,47 +482,53 @@ __device__ __forceinline__ void wait_ring_full() {
 // t1), the exponents formed in the previous step are exponentiated into the registers just freed,
 // and the exponents of a new pair are formed (x = a*c + o).  Every result is first read a full step
 // after the instruction that produces it, whatever order the compiler picks inside a step.
-#define DAPQ_VALU_STEP(a0, a1, o0, o1, t0, t1, p0, p1) \
+// (first: t0 starts with this pair)
+#define DAPQ_VALU_STEP(first, a0, a1, o0, o1, t0, t1, p0, p1) \
   do {                                                 \
-    t0 += p0;                                          \
-    t1 += p1;                                          \
+    if (first) {                                       \
+      t0 = p0 + p1;                                    \
+    } else {                                           \
+      t0 += p0;                                        \
+      t1 += p1;                                        \
+    }                                                  \
     p0 = __builtin_amdgcn_exp2f(x0);                   \
     p1 = __builtin_amdgcn_exp2f(x1);                   \
     x0 = fmaf((a0), c, (o0));                          \
     x1 = fmaf((a1), c, (o1));                          \
   } while (0)
 // step k of a unit: even steps use the first set of pending exponentials, odd steps the second
-#define DAPQ_VALU_STEP_K(k, a0, a1, o0, o1, t0, t1)                     \
-  do {                                                                  \
-    if ((k) % 2 == 0) DAPQ_VALU_STEP(a0, a1, o0, o1, t0, t1, ea0, ea1); \
-    else DAPQ_VALU_STEP(a0, a1, o0, o1, t0, t1, eb0, eb1);              \
+#define DAPQ_VALU_STEP_K(k, first, a0, a1, o0, o1, t0, t1)                     \
+  do {                                                                         \
+    if ((k) % 2 == 0) DAPQ_VALU_STEP(first, a0, a1, o0, o1, t0, t1, ea0, ea1); \
+    else DAPQ_VALU_STEP(first, a0, a1, o0, o1, t0, t1, eb0, eb1);              \
   } while (0)
 
-// Pipelined walk of one wave over sub-blocks [sb0, sb1) of its chunk.
-//   on entry  kf = fragments of sub-block sb0; the transfers of sub-blocks sb0+1 .. sb0+NST-1 are
-//             under way (sub-block i lives in ring slot i % NST)
-//   on exit   kf = fragments of sub-block sb1 (zeros if it does not exist)
-// Every iteration issues the transfer of sub-block sub+NST into the slot of the current sub-block
-// once its fragments are in registers, and waits for sub-block sub+1 before its last unit; as every
+// Pipelined walk of one wave over `count` sub-blocks of its stream of keys, all of one sequence: numbers first_sub,
+// first_sub + 1, ... of it (a reversed stream: first_sub, first_sub - 1, ...).
+//   on entry  kf = fragments of the first one, which lies in ring slot `slot`; the transfers of the NST - 1 sub-blocks
+//             after it are under way (they lie in the slots after that one, in turn)
+//   on exit   kf = fragments of the sub-block after the last one, in slot `slot` (zeros if it does not exist)
+// Every iteration issues the transfer of the sub-block NST ahead into the slot of the current sub-block
+// once its fragments are in registers, and waits for the next sub-block before its last unit; as every
 // sub-block is 8 operations, existing or not, that wait is a fixed count.
 // A unit is one sub-block against one 32-row block of Q: 8 MFMAs, one per slice.  While the MFMAs
 // of a unit issue, the 16 logits per lane of the unit before it enter the vector pipeline, one pair
 // per slice (the MFMA leads its slice, so the last MFMA of a unit is a full slice old when its
 // first result is read).  The sum a step adds to belongs to the pair three steps back: steps 0..2
 // of a unit still feed the unit two back.
-// PASS 1: off1[rb] = -(reference logit * c) of row block rb; acc[rb] receives the row sums.
+// PASS 1: off1[rb] = -(reference logit * c) of row block rb; acc[rb] receives the row sums.  In a segment,
+// whose sequences may be long, a unit's 16 terms of a lane are added up first (su): the same number of additions, and small
+// terms meet a large sum once a unit instead of one by one (8 prompts of 4096..16384 keys, 512 rows: 6e-7 off float64).
 // PASS 2: off2[rb][v] = -lse2 of the row that accumulator register v of this lane holds in row
 //         block rb (-inf for padding rows, which then add 0).  S of every key goes to out.
 // NST = slots of the sub-block ring.
-template <int NRB, int PASS, int NST, bool REV = false>
-__device__ __forceinline__ void wave_walk(u32x4* ring, const uint16_t* kbase, int64_t stride_token, int nkeys,
-                                          int sb0, int sb1, bf16x8 (&kf)[8], const bf16x8 (&qf)[NRB][8], float c,
+template <int NRB, int PASS, int NST, class Stream>
+__device__ __forceinline__ void wave_walk(u32x4* ring, int& slot, Stream& keys, int first_sub, int count, int nkeys,
+                                          bf16x8 (&kf)[8], const bf16x8 (&qf)[NRB][8], float c,
                                           const float (&off1)[NRB], const float (&off2)[PASS == 2 ? NRB : 1][16],
-                                          float (&acc)[NRB], float* out, const unsigned (&voff)[4], int n, int h,
-                                          int last_sub = 0) {
-  // REV: step `sub` of the walk works on sub-block last_sub - sub of the chunk (the chunk is walked from
-  // its end to its start); otherwise on sub-block sub
-  auto first_key = [&](int sub) { return (REV ? last_sub - sub : sub) * 32; };
+                                          float (&acc)[NRB], float* out, const unsigned (&voff)[4], int n, int h) {
+  constexpr bool kUnitSums = PASS == 1 && Stream::kSegment;
+  auto first_key = [&](int sub) { return (Stream::kReversed ? first_sub - sub : first_sub + sub) * 32; };
   const unsigned ring_base = (unsigned)(uintptr_t)(lds_vec_ptr)ring;
   unsigned fa[8];
 #pragma unroll
@@ -471,13 +537,12 @@ __device__ __forceinline__ void wave_walk(u32x4* ring, const uint16_t* kbase, in
   f32x16 prev;
 #pragma unroll
   for (int v = 0; v < 16; ++v) prev[v] = -INFINITY;  // 2^(-inf) = 0: the first steps add nothing
-  float x0 = -INFINITY, x1 = -INFINITY, ea0 = 0.0f, ea1 = 0.0f, eb0 = 0.0f, eb1 = 0.0f, sa = 0.0f, sb = 0.0f;
+  float x0 = -INFINITY, x1 = -INFINITY, ea0 = 0.0f, ea1 = 0.0f, eb0 = 0.0f, eb1 = 0.0f, sa = 0.0f, sb = 0.0f, su = 0.0f;
 #pragma unroll
   for (int rb = 0; rb < NRB; ++rb) acc[rb] = 0.0f;
 
-  int issue_slot = sb0 % NST;          // ring slot of the current sub-block: the next transfer goes there
-  int read_slot = (sb0 + 1) % NST;     // ring slot of the sub-block after the current one
-  for (int sub = sb0; sub < sb1; ++sub) {
+  int read_slot = slot + 1 == NST ? 0 : slot + 1;  // ring slot of the sub-block after the current one
+  for (int sub = 0; sub < count; ++sub) {
     const unsigned next_slot = (unsigned)read_slot * (unsigned)kSubBytes;
     read_slot = read_slot + 1 == NST ? 0 : read_slot + 1;
 #pragma unroll
@@ -487,8 +552,8 @@ __device__ __forceinline__ void wave_walk(u32x4* ring, const uint16_t* kbase, in
       const int rb2 = (rb + NRB - 2) % NRB;  // row block of the unit before it
       if (rb == 1) {
         // the slot of this sub-block is free (its fragments are in registers and have been used)
-        sub_dma(ring + issue_slot * kSubVec, kbase, stride_token, first_key(sub + NST), nkeys, voff);
-        issue_slot = issue_slot + 1 == NST ? 0 : issue_slot + 1;
+        keys.fetch(ring + slot * kSubVec, voff, first_key(sub + NST));
+        slot = slot + 1 == NST ? 0 : slot + 1;
       }
       if (rb == kLast) wait_ring_full<NST>();  // sub-block sub+1 has landed: NST-1 newer ones are in flight
       f32x16 cur = {0};
@@ -499,18 +564,24 @@ __device__ __forceinline__ void wave_walk(u32x4* ring, const uint16_t* kbase, in
         DAPQ_WAVE_SLICE_MID(kf[s], x0, x1);
         if (rb == kLast) kf[s] = lds_read16(fa[s] + next_slot, 0);  // last use: fetch the next sub-block's
         if (PASS == 2) {
-          DAPQ_VALU_STEP_K(s, prev[2 * s], prev[2 * s + 1], off2[PASS == 2 ? rb1 : 0][2 * s],
+          DAPQ_VALU_STEP_K(s, false, prev[2 * s], prev[2 * s + 1], off2[PASS == 2 ? rb1 : 0][2 * s],
                            off2[PASS == 2 ? rb1 : 0][2 * s + 1], sa, sb);
           if (s == 2 && rb == 1) {
             // the adds above took in the last logits of the previous sub-block: its column sums are complete
-            if (sub > sb0) store_columns(cols, first_key(sub - 1), sum_halves(sa + sb));
+            if (sub > 0) store_columns(cols, first_key(sub - 1), sum_halves(sa + sb));
             sa = sb = 0.0f;
           }
           DAPQ_WAVE_SLICE_END(prev, x0, x1, sa, sb, fa[(s + 1) & 7]);
         } else {
-          if (s < 3) DAPQ_VALU_STEP_K(s, prev[2 * s], prev[2 * s + 1], off1[rb1], off1[rb1], acc[rb2], acc[rb2]);
-          else DAPQ_VALU_STEP_K(s, prev[2 * s], prev[2 * s + 1], off1[rb1], off1[rb1], acc[rb1], acc[rb1]);
-          DAPQ_WAVE_SLICE_END(prev, x0, x1, acc[rb1], acc[rb2], fa[(s + 1) & 7]);
+          if constexpr (kUnitSums) {
+            DAPQ_VALU_STEP_K(s, s == 3, prev[2 * s], prev[2 * s + 1], off1[rb1], off1[rb1], su, su);
+            if (s == 2) acc[rb2] += su;  // the unit two back is complete
+            DAPQ_WAVE_SLICE_END(prev, x0, x1, su, acc[rb2], fa[(s + 1) & 7]);
+          } else {
+            if (s < 3) DAPQ_VALU_STEP_K(s, false, prev[2 * s], prev[2 * s + 1], off1[rb1], off1[rb1], acc[rb2], acc[rb2]);
+            else DAPQ_VALU_STEP_K(s, false, prev[2 * s], prev[2 * s + 1], off1[rb1], off1[rb1], acc[rb1], acc[rb1]);
+            DAPQ_WAVE_SLICE_END(prev, x0, x1, acc[rb1], acc[rb2], fa[(s + 1) & 7]);
+          }
         }
       }
       prev = cur;
@@ -524,14 +595,20 @@ __device__ __forceinline__ void wave_walk(u32x4* ring, const uint16_t* kbase, in
     for (int k = 0; k < 11; ++k) {
       const float a0 = k < 8 ? prev[(2 * k) & 15] : -INFINITY, a1 = k < 8 ? prev[(2 * k + 1) & 15] : -INFINITY;
       if (PASS == 1) {
-        if (k < 3) DAPQ_VALU_STEP_K(k, a0, a1, off1[rbl], off1[rbl], acc[rbl1], acc[rbl1]);
-        else DAPQ_VALU_STEP_K(k, a0, a1, off1[rbl], off1[rbl], acc[rbl], acc[rbl]);
+        if constexpr (kUnitSums) {
+          DAPQ_VALU_STEP_K(k, k == 3, a0, a1, off1[rbl], off1[rbl], su, su);
+          if (k == 2) acc[rbl1] += su;
+          if (k == 10) acc[rbl] += su;
+        } else {
+          if (k < 3) DAPQ_VALU_STEP_K(k, false, a0, a1, off1[rbl], off1[rbl], acc[rbl1], acc[rbl1]);
+          else DAPQ_VALU_STEP_K(k, false, a0, a1, off1[rbl], off1[rbl], acc[rbl], acc[rbl]);
+        }
       } else {
-        DAPQ_VALU_STEP_K(k, a0, a1, off2[PASS == 2 ? rbl : 0][(2 * k) & 15], off2[PASS == 2 ? rbl : 0][(2 * k + 1) & 15], sa,
+        DAPQ_VALU_STEP_K(k, false, a0, a1, off2[PASS == 2 ? rbl : 0][(2 * k) & 15], off2[PASS == 2 ? rbl : 0][(2 * k + 1) & 15], sa,
                          sb);
       }
     }
-    if (PASS == 2 && sb1 > sb0) store_columns(cols, first_key(sb1 - 1), sum_halves(sa + sb));
+    if (PASS == 2 && count > 0) store_columns(cols, first_key(count - 1), sum_halves(sa + sb));
   }
 }
 
@@ -594,159 +671,97 @@ __device__ __forceinline__ void wave_load_frags(bf16x8 (&kf)[8], const u32x4* sl
   for (int s = 0; s < 8; ++s) kf[s] = __builtin_bit_cast(bf16x8, slot[lds_chunk_index(n, 2 * s + h)]);
 }
 
-// The next item of a ragged batch's work list (see the kernels below): lane 0 takes a ticket, everybody gets it.
-__device__ __forceinline__ unsigned take_item(unsigned* work, int lane) {
-  unsigned v = 0;
-  if (lane == 0) v = atomicAdd(work, 1u);
-  return (unsigned)uniform_i32((int)v);
-}
-
-// The work lists of a ragged batch: one per XCD (kLists of them: each XCD has its own L2).  List x holds the chunks c of
-// the packed key axis with c mod kLists == x, for every head and every block of row groups; ticket t of list x is item
-// ((head * chunks_x + c') * blocks + block) with c = c' * kLists + x.  A block is the row groups that the waves of one
-// workgroup (a team) take side by side: they read the same keys at the same time, so the second reader finds them in
-// the compute unit's L2 and the keys go through the fabric once.  A team takes tickets from the list of the XCD it
-// runs on (consecutive tickets are blocks of the same chunk: the same keys again, behind the same L2); when that list is
-// empty it goes on to the others', so every list is drained whatever runs where.  (The host launches this form only
-// if the item count fits 31 bits whatever the lengths are.)
-struct Item {
-  int head, block, chunk;
-  Work work;
-};
-struct ItemLists {
-  unsigned chunks, blocks, heads;
-  __device__ __forceinline__ unsigned chunks_of(int x) const { return (chunks + (unsigned)(kLists - 1 - x)) / kLists; }
-  __device__ __forceinline__ unsigned count(int x) const { return heads * chunks_of(x) * blocks; }
-  // `reversed`: heads and chunks from the far end (pass 2)
-  __device__ __forceinline__ Item at(const ScoreParams& p, int x, unsigned ticket, bool reversed) const {
-    const unsigned cx = chunks_of(x);
-    const unsigned u = uniform_u32(ticket / blocks), block = ticket - u * blocks;
-    const unsigned head = uniform_u32(u / cx), c = u - head * cx;
-    Item it;
-    it.head = (int)(reversed ? heads - 1 - head : head);
-    it.block = (int)block;
-    it.chunk = (int)((reversed ? cx - 1 - c : c) * kLists + (unsigned)x);
-    it.work = locate_uniform(p, it.chunk);
-    return it;
+// The keys a wave goes through, in the order in which they enter its ring: the sub-blocks of one chunk of a dense batch, or
+// (SEG) of a segment of a ragged one, sequence after sequence.  REV: from the last sub-block down.  The ring is filled ahead
+// across the sequences of a segment: while the wave changes to the queries of the next one, that one's first NST - 1
+// sub-blocks are on their way.
+template <bool REV, bool SEG>
+struct KeyStream {
+  static constexpr bool kReversed = REV, kSegment = SEG;
+  const ScoreParams& p;
+  const uint16_t* head;  // SEG: the KV head's keys
+  const uint16_t* base;  // first key of the sequence (dense: of the chunk) that is being fetched
+  int nkeys;             // its keys
+  int sub, seq, left;    // SEG: the sub-block that is fetched next, of which sequence, and how many of the segment are to come
+  __device__ __forceinline__ void enter(SeqRange r) {
+    nkeys = uniform_i32(r.len);
+    base = uniform_ptr(head + (int64_t)seq * p.k_stride_seq + (int64_t)r.start * p.k_stride_token);
+  }
+  // key0: the first key of the sub-block in its chunk (a segment counts them itself)
+  __device__ __forceinline__ void fetch(u32x4* slot, const unsigned (&voff)[4], int key0) {
+    sub_dma(slot, base, p.k_stride_token, SEG ? sub * 32 : key0, nkeys, SEG ? left > 0 : (REV ? key0 >= 0 : key0 < nkeys), voff);
+    if constexpr (SEG) {
+      sub += REV ? -1 : 1;
+      left -= 1;
+      if (left > 0 && (REV ? sub < 0 : sub > (nkeys - 1) / 32)) {
+        SeqRange r;
+        do {  // (a segment that goes on has another sequence with keys)
+          seq += REV ? -1 : 1;
+          r = seq_range(p, seq);
+        } while (r.len <= 0);
+        enter(r);
+        sub = REV ? (nkeys - 1) / 32 : 0;
+      }
+    }
   }
 };
-__device__ __forceinline__ ItemLists item_lists(const ScoreParams& p) {
-  ItemLists l;
-  l.chunks = (unsigned)uniform_i32(p.cu_chunks[p.batch]);
-  l.blocks = (unsigned)(p.n_groups / p.wg_groups);
-  l.heads = (unsigned)(p.n_layers * p.n_kv_heads);
-  return l;
-}
-
-// The tickets of a team.  A team of one wave keeps its ticket in a register; in a larger team wave 0 takes the ticket and
-// leaves it in one of two LDS words (behind the rings), which the others read after the barrier that starts the item:
-// the slots alternate, so a slot is rewritten only after two more barriers.
-struct TeamTickets {
-  unsigned* slots;  // LDS, two words (teams of more than one wave)
-  unsigned mine;    // team of one: the ticket
-  int parity;
-  bool team, leader;
-  __device__ __forceinline__ void post(unsigned ticket, int lane) {
-    if (!team) mine = ticket;
-    else if (leader && lane == 0) slots[parity] = ticket;
-  }
-  __device__ __forceinline__ unsigned next() {
-    if (!team) return mine;
-    __syncthreads();
-    const unsigned t = uniform_u32(slots[parity]);
-    parity ^= 1;
-    return t;
-  }
-};
-__device__ __forceinline__ TeamTickets team_tickets(u32x4* rings, int nst, int wave_id) {
-  TeamTickets t;
-  const int waves = (int)(blockDim.x >> 6);
-  t.slots = reinterpret_cast<unsigned*>(rings + waves * (wave_lds(nst) / 16));
-  t.mine = 0;
-  t.parity = 0;
-  t.team = waves > 1;
-  t.leader = wave_id == 0;
-  return t;
-}
-// The XCD this wave runs on (hardware register XCC_ID, bits 3:0).
-__device__ __forceinline__ int home_list() {
-  return (int)(__builtin_amdgcn_s_getreg(20 | (0 << 6) | ((4 - 1) << 11)) & (unsigned)(kLists - 1));
-}
-
-// The next list, in turn from the home list, that still has tickets (they may be gone when the caller comes for one: then it
-// asks again); kLists if none has.  One load looks at all the counters: taking a ticket of every other list to find it
-// empty was seven round trips at the end of every wave's life, all of them on the same few words (one layer, 8 prompts
-// of 1000 keys, 128 rows: both passes 176 us with them, 82 us without).
-__device__ __forceinline__ unsigned next_list(const ScoreParams& p, const ItemLists& lists, int home, int lane) {
-  const int x = (home + lane) & (kLists - 1);
-  bool has = false;
-  if (lane < kLists)
-    has = __hip_atomic_load(p.work + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < lists.count(x);
-  const unsigned turn = (unsigned)__ballot(has);
-  return turn == 0 ? (unsigned)kLists : (unsigned)((home + __builtin_ctz(turn)) & (kLists - 1));
-}
-
-// Pass 1 of one chunk: `head` = layer * n_kv_heads + KV head, `group` = row group, `chunk_id` = chunk along the packed
-// key axis.  If `work` is not NULL the ticket for the wave's next item is taken from it while the chunk drains (so
-// its round trip costs nothing) and returned.  The chunk must have keys.
-// FUSED (score_fused_kernel): the chunk's (reference, sum) pairs go to the start of the wave's own ring, which is
-// drained by then, instead of to global memory.
-template <int NRB, int NST, bool FUSED = false>
-__device__ __forceinline__ unsigned pass1_item(const ScoreParams& p, u32x4* ring, const Work& w, int chunk_id, int group, int head,
-                                               bf16x8 (&qf)[NRB][8], int lane, unsigned* work) {
-  if (NRB == 8) asm volatile("" : "+v"(lane));  // what follows from the lane is formed per item (see score_wave_pass1_kernel)
-  unsigned voff[4];
-  sub_dma_lane_offsets(voff, p.k_stride_token, lane);
-  // (the division runs on the vector ALU: bring the quotient back to a scalar register)
-  const int layer = uniform_i32(head / p.n_kv_heads), kv = head - layer * p.n_kv_heads;
-  const int n = lane & 31, h = lane >> 5;
-  const uint16_t* qbase = p.q + (int64_t)layer * p.q_stride_layer + (int64_t)w.seq * p.q_stride_seq +
-                          (int64_t)kv * p.group * p.q_stride_head;
-  const uint16_t* kbase = uniform_ptr(p.k + (int64_t)layer * p.k_stride_layer + (int64_t)w.seq * p.k_stride_seq +
-                                      (int64_t)kv * p.k_stride_head + w.tok0 * p.k_stride_token);
-  const int gbase = group * (NRB * 32);  // first row of this wave's row group
-  const int nsubs = (w.nkeys + 31) / 32, nfull = w.nkeys / 32;
-  // the ring is filled whether the sub-blocks exist or not (sub_dma): the waits count operations
+// The ring is filled whether the sub-blocks exist or not (sub_dma): the waits count operations.
+template <int NST, class Stream>
+__device__ __forceinline__ void fill_ring(u32x4* ring, Stream& keys, const unsigned (&voff)[4], int first_sub) {
 #pragma unroll
-  for (int i = 0; i < NST; ++i) sub_dma(ring + i * kSubVec, kbase, p.k_stride_token, i * 32, w.nkeys, voff);
+  for (int i = 0; i < NST; ++i) keys.fetch(ring + i * kSubVec, voff, (Stream::kReversed ? first_sub - i : first_sub + i) * 32);
+}
+
+// Pass 1 of `count` sub-blocks of one sequence (or chunk), from number first_sub on, against row group `group` of `head` =
+// layer * n_kv_heads + KV head.  kbase: its first key, nkeys: its keys; `start`: the first of this wave.  kf, slot and keys: as
+// in wave_walk.  The (reference, sum) pairs go to outp.
+template <int NRB, int NST, class Stream>
+__device__ __forceinline__ void pass1_piece(const ScoreParams& p, u32x4* ring, int& slot, Stream& keys, bf16x8 (&kf)[8],
+                                            bf16x8 (&qf)[NRB][8], const uint16_t* qbase, const uint16_t* kbase, int first_sub,
+                                            int count, int nkeys, int gbase, const unsigned (&voff)[4], bool start,
+                                            float2* outp) {
+  const int lane = fresh_lane(), n = lane & 31, h = lane >> 5;
 #pragma unroll
   for (int rb = 0; rb < NRB; ++rb) frag_from_q(qf[rb], p, qbase, gbase + rb * 32 + n, h);
   if (NRB == 8) pin_q_in_agprs<NRB>(qf);
-
+  if (start) {
+    wait_ring_full<NST>();
+    wave_load_frags<NRB>(kf, ring + slot * kSubVec, n, h);
+  }
+  // the fragments in kf have been used: their slot takes the sub-block NST ahead, and the next one's fragments follow
+  auto advance = [&](int sub) {
+    keys.fetch(ring + slot * kSubVec, voff, (sub + NST) * 32);
+    slot = slot + 1 == NST ? 0 : slot + 1;
+    wait_ring_full<NST>();
+    wave_load_frags<NRB>(kf, ring + slot * kSubVec, n, h);
+  };
   float ref[NRB], z[NRB];
 #pragma unroll
   for (int rb = 0; rb < NRB; ++rb) {
     ref[rb] = -INFINITY;
     z[rb] = 0.0f;
   }
-  bf16x8 kf[8];
-  wait_subblocks(NST - 1);
-  wave_load_frags<NRB>(kf, ring, n, h);
-  // sub-block 0 the plain way: it fixes the reference logits
-  wave_sub_simple<NRB, false, true>(kf, qf, p.c, ref, z, 0, w.nkeys, h);
-  if (nsubs > 1) {
-    wait_subblocks(NST - 2);
-    wave_load_frags<NRB>(kf, ring + kSubVec, n, h);
-    sub_dma(ring, kbase, p.k_stride_token, NST * 32, w.nkeys, voff);  // slot 0 is free
-    if (nfull > 1) {
-      float off[NRB], zs[NRB];
+  // the first sub-block the plain way: it fixes the reference logits
+  wave_sub_simple<NRB, false, true>(kf, qf, p.c, ref, z, first_sub * 32, nkeys, h);
+  advance(first_sub);
+  const int last_sub = first_sub + count - 1, full = nkeys / 32 - first_sub - 1;  // sub-blocks of 32 keys after the first one
+  const int walk = full < count - 1 ? full : count - 1;
+  if (walk > 0) {
+    float off[NRB], zs[NRB];
 #pragma unroll
-      for (int rb = 0; rb < NRB; ++rb) off[rb] = -ref[rb];
-      const float no_off2[1][16] = {};
-      wave_walk<NRB, 1, NST>(ring, kbase, p.k_stride_token, w.nkeys, 1, nfull, kf, qf, p.c, off, no_off2, zs,
-                                      nullptr, voff, n, h);
+    for (int rb = 0; rb < NRB; ++rb) off[rb] = -ref[rb];
+    const float no_off2[1][16] = {};
+    wave_walk<NRB, 1, NST>(ring, slot, keys, first_sub + 1, walk, nkeys, kf, qf, p.c, off, no_off2, zs, nullptr, voff, n, h);
 #pragma unroll
-      for (int rb = 0; rb < NRB; ++rb) z[rb] += zs[rb];
-    }
+    for (int rb = 0; rb < NRB; ++rb) z[rb] += zs[rb];
   }
-  // (no counted wait follows: the ticket's round trip overlaps what is left of the chunk)
-  const unsigned next = work != nullptr ? take_item(work, lane) : 0u;
-  if (nsubs > 1 && nfull < nsubs && nfull >= 1)  // the partial last sub-block; its fragments are in kf
-    wave_sub_simple<NRB, false, false>(kf, qf, p.c, ref, z, nfull * 32, w.nkeys, h);
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  if (count > 1 && walk < count - 1) {  // the partial last sub-block
+    wave_sub_simple<NRB, false, false>(kf, qf, p.c, ref, z, last_sub * 32, nkeys, h);
+    advance(last_sub);
+  }
 
   // a sum that is not finite means a logit sat more than ~127 binades above the reference: redo
-  // the chunk with a running maximum, one sub-block at a time
+  // the piece with a running maximum, one sub-block at a time, straight from memory
   bool bad = false;
 #pragma unroll
   for (int rb = 0; rb < NRB; ++rb) bad = bad || !(z[rb] < INFINITY);
@@ -756,32 +771,82 @@ __device__ __forceinline__ unsigned pass1_item(const ScoreParams& p, u32x4* ring
       ref[rb] = -INFINITY;
       z[rb] = 0.0f;
     }
-    for (int sub = 0; sub < nsubs; ++sub) {
-      sub_dma(ring, kbase, p.k_stride_token, sub * 32, w.nkeys, voff);
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      wave_load_frags<NRB>(kf, ring, n, h);
-      wave_sub_simple<NRB, true, false>(kf, qf, p.c, ref, z, sub * 32, w.nkeys, h);
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the fragments are out of the slot before it is refilled
+    for (int sub = first_sub; sub <= last_sub; ++sub) {
+      const int key = sub * 32 + n < nkeys ? sub * 32 + n : nkeys - 1;  // (repeated keys are masked)
+      const uint16_t* src = kbase + (int64_t)key * p.k_stride_token + 8 * h;
+#pragma unroll
+      for (int s = 0; s < 8; ++s) kf[s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(src + 16 * s));
+      wave_sub_simple<NRB, true, false>(kf, qf, p.c, ref, z, sub * 32, nkeys, h);
     }
+    wave_load_frags<NRB>(kf, ring + slot * kSubVec, n, h);  // (what was in kf before)
   }
 
+  if (!Stream::kSegment) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (outp may be in the ring)
   // the two lane halves hold different keys of the same query
-  if constexpr (FUSED) {
-    float2* outp = reinterpret_cast<float2*>(ring);
 #pragma unroll
-    for (int rb = 0; rb < NRB; ++rb) {
-      const float zz = z[rb] + xhalf(z[rb]);
-      if (h == 0) outp[rb * 32 + n] = make_float2(ref[rb], zz);
-    }
-  } else {
-    float2* outp = p.parts + ((int64_t)head * p.max_chunks + chunk_id) * p.rows_pad + gbase;
-#pragma unroll
-    for (int rb = 0; rb < NRB; ++rb) {
-      const float zz = z[rb] + xhalf(z[rb]);
-      if (h == 0) outp[rb * 32 + n] = make_float2(ref[rb], zz);
-    }
+  for (int rb = 0; rb < NRB; ++rb) {
+    const float zz = z[rb] + xhalf(z[rb]);
+    if (h == 0) outp[rb * 32 + n] = make_float2(ref[rb], zz);
   }
-  return next;
+}
+
+__device__ __forceinline__ const uint16_t* wave_q_base(const ScoreParams& p, int layer, int kv, int seq) {
+  return p.q + (int64_t)layer * p.q_stride_layer + (int64_t)seq * p.q_stride_seq + (int64_t)kv * p.group * p.q_stride_head;
+}
+
+// Pass 1 of one chunk of a dense batch: `group` = row group, `chunk_id` = chunk along the packed key axis.  The chunk must have
+// keys.  FUSED (score_fused_kernel): the chunk's (reference, sum) pairs go to the start of the wave's own ring, which is
+// drained by then, instead of to global memory.
+template <int NRB, int NST, bool FUSED = false>
+__device__ __forceinline__ void pass1_chunk(const ScoreParams& p, u32x4* ring, const Work& w, int chunk_id, int group, int head,
+                                            bf16x8 (&qf)[NRB][8], int lane) {
+  unsigned voff[4];
+  sub_dma_lane_offsets(voff, p.k_stride_token, lane);
+  // (the division runs on the vector ALU: bring the quotient back to a scalar register)
+  const int layer = uniform_i32(head / p.n_kv_heads), kv = head - layer * p.n_kv_heads;
+  const uint16_t* kbase = uniform_ptr(p.k + (int64_t)layer * p.k_stride_layer + (int64_t)w.seq * p.k_stride_seq +
+                                      (int64_t)kv * p.k_stride_head + w.tok0 * p.k_stride_token);
+  const int gbase = group * (NRB * 32);  // first row of this wave's row group
+  KeyStream<false, false> keys = {p, nullptr, kbase, w.nkeys, 0, 0, 0};
+  fill_ring<NST>(ring, keys, voff, 0);
+  bf16x8 kf[8];
+  int slot = 0;
+  float2* outp = FUSED ? reinterpret_cast<float2*>(ring) : p.parts + ((int64_t)head * p.max_chunks + chunk_id) * p.rows_pad + gbase;
+  pass1_piece<NRB, NST>(p, ring, slot, keys, kf, qf, wave_q_base(p, layer, kv, w.seq), kbase, 0, (w.nkeys + 31) / 32, w.nkeys,
+                        gbase, voff, true, outp);
+}
+
+// Pass 1 of one segment of a ragged batch.
+template <int NRB, int NST>
+__device__ __forceinline__ void pass1_segment(const ScoreParams& p, u32x4* ring, int segment, int group, int head,
+                                              bf16x8 (&qf)[NRB][8], int lane) {
+  Segment at = segment_of_wave(p, segment, false);
+  if (at.left == 0) return;
+  unsigned voff[4];
+  sub_dma_lane_offsets(voff, p.k_stride_token, lane);
+  const int layer = uniform_i32(head / p.n_kv_heads), kv = head - layer * p.n_kv_heads;
+  const int gbase = group * (NRB * 32);
+  KeyStream<false, true> keys = {p, uniform_ptr(p.k + (int64_t)layer * p.k_stride_layer + (int64_t)kv * p.k_stride_head),
+                                 nullptr, 0, at.sub, at.seq, at.left};
+  keys.enter(seq_range(p, at.seq));
+  fill_ring<NST>(ring, keys, voff, 0);
+  bf16x8 kf[8];
+  int slot = 0;
+  for (bool start = true;; start = false) {
+    const SeqRange r = seq_range(p, at.seq);
+    if (r.len > 0) {
+      const int nkeys = uniform_i32(r.len), rest = (nkeys - 1) / 32 + 1 - at.sub, count = at.left < rest ? at.left : rest;
+      const uint16_t* kbase = uniform_ptr(keys.head + (int64_t)at.seq * p.k_stride_seq + (int64_t)r.start * p.k_stride_token);
+      pass1_piece<NRB, NST>(p, ring, slot, keys, kf, qf, wave_q_base(p, layer, kv, at.seq), kbase, at.sub, count, nkeys, gbase,
+                            voff, start,
+                            p.parts + ((int64_t)head * p.max_chunks + at.seq + segment) * p.rows_pad + gbase);
+      at.left -= count;
+      if (at.left == 0) break;
+    }
+    at.seq += 1;
+    at.sub = 0;
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
 // Which (chunk, row group) a wave of a dense launch works on.  The waves of a workgroup take p.wg_groups row groups of
@@ -798,78 +863,35 @@ __device__ __forceinline__ WaveSlot wave_slot(const ScoreParams& p, int wave_id)
   return s;
 }
 
-// DYN = false (dense batches): the grid names the items, one per wave: (chunk, row group, layer x KV head).
-// DYN = true (ragged batches, whose lengths the host does not know): one persistent wave per SIMD takes items from
-// work lists in device memory until they are empty (see ItemLists).  A short chunk costs a ticket and a ring refill
-// instead of a workgroup launch; the hand-out also evens out the ragged tail.
-// At 8 row blocks, what follows from the lane number alone (transfer offsets, fragment addresses, row masks: some 40 registers) is
-// formed anew for every item: kept across the items it does not fit beside the queries, and a register that is spilled is
-// reloaded between the ring fill and the walk, behind a wait for every transfer in flight.  (A spill is also one more of the
-// vector memory operations that the ring's waits count.)  32 layers, 256 rows, both passes: 16 prompts of 175..1400 keys 587 ->
-// 562 us, 64 of 300 keys 1202 -> 1148; 8 of 4096..16384, 512 rows unchanged.
-template <int NRB, bool DYN, int NST>
+// The grid names the items, one per wave: (chunk, row group, layer x KV head).  SEG (ragged batches, whose lengths
+// the host does not know): a segment of the packed key axis in the place of the chunk.
+template <int NRB, bool SEG, int NST>
 __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_wave_pass1_kernel(ScoreParams p) {
   extern __shared__ u32x4 rings[];
   const int wave_id = uniform_i32((int)(threadIdx.x >> 6));
   u32x4* ring = rings + wave_id * (wave_lds(NST) / 16);
   const int lane = threadIdx.x & 63;
   bf16x8 qf[NRB][8];
-  if (!DYN) {
-    const WaveSlot slot = wave_slot(p, wave_id);
+  const WaveSlot slot = wave_slot(p, wave_id);
+  if constexpr (SEG) {
+    pass1_segment<NRB, NST>(p, ring, slot.chunk, slot.group, (int)blockIdx.z, qf, lane);
+  } else {
     const Work w = locate_uniform(p, slot.chunk);
     if (w.nkeys == 0) return;
-    pass1_item<NRB, NST>(p, ring, w, slot.chunk, slot.group, (int)blockIdx.z, qf, lane, nullptr);
-    return;
-  }
-  const ItemLists lists = item_lists(p);
-  const int home = home_list();
-  TeamTickets tickets = team_tickets(rings, NST, wave_id);
-  for (unsigned x = (unsigned)home; x < (unsigned)kLists;) {  // this XCD's list first, then those not yet drained
-    unsigned* work = tickets.leader ? p.work + x : nullptr;  // (only the leader of a team takes tickets)
-    const unsigned n_items = lists.count((int)x);
-    tickets.post(work != nullptr ? take_item(work, lane) : 0u, lane);
-    for (;;) {  // every team leaves: the tickets only grow
-      const unsigned ticket = tickets.next();
-      if (ticket >= n_items) break;
-      const Item a = lists.at(p, (int)x, ticket, false);
-      if (a.work.nkeys == 0) {  // (no chunk of a list is empty; if one were, it would only cost its ticket)
-        tickets.post(work != nullptr ? take_item(work, lane) : 0u, lane);
-        continue;
-      }
-      tickets.post(pass1_item<NRB, NST>(p, ring, a.work, a.chunk, a.block * p.wg_groups + wave_id, a.head, qf, lane, work),
-                   lane);
-    }
-    tickets.post(tickets.leader ? next_list(p, lists, home, lane) : 0u, lane);
-    x = tickets.next();
+    pass1_chunk<NRB, NST>(p, ring, w, slot.chunk, slot.group, (int)blockIdx.z, qf, lane);
   }
 }
 
-// Pass 2 of one chunk (arguments as pass1_item).  FUSED (score_fused_kernel): the query fragments are still in
-// registers from pass 1 and the caller has filled off2.
-template <int NRB, int NST, bool FUSED = false>
-__device__ __forceinline__ unsigned pass2_item(const ScoreParams& p, u32x4* ring, const Work& w, int group, int head,
-                                               bf16x8 (&qf)[NRB][8], float (&off2)[NRB][16], int lane, unsigned* work) {
-  if (NRB == 8) asm volatile("" : "+v"(lane));  // what follows from the lane is formed per item (see score_wave_pass1_kernel)
-  unsigned voff[4];
-  sub_dma_lane_offsets(voff, p.k_stride_token, lane);
-  // (the division runs on the vector ALU: bring the quotient back to a scalar register)
-  const int layer = uniform_i32(head / p.n_kv_heads), kv = head - layer * p.n_kv_heads;
-  const int n = lane & 31, h = lane >> 5;
-  const uint16_t* qbase = p.q + (int64_t)layer * p.q_stride_layer + (int64_t)w.seq * p.q_stride_seq +
-                          (int64_t)kv * p.group * p.q_stride_head;
-  const uint16_t* kbase = uniform_ptr(p.k + (int64_t)layer * p.k_stride_layer + (int64_t)w.seq * p.k_stride_seq +
-                                      (int64_t)kv * p.k_stride_head + w.tok0 * p.k_stride_token);
-  const float* lse = p.lse2 + (((int64_t)layer * p.batch + w.seq) * p.n_q_heads + (int64_t)kv * p.group) * p.n_pseudo;
-  const int gbase = group * (NRB * 32);  // first row of this wave's row group
-  // with several row groups each writes its own plane of column sums (group 0 straight into the
-  // result); a small kernel adds the others onto it
-  float* plane = group == 0 ? p.scores : p.partial + (int64_t)(group - 1) * p.n_layers * p.n_kv_heads * p.total_tokens;
-  float* out = const_cast<float*>(uniform_ptr(plane + ((int64_t)layer * p.n_kv_heads + kv) * p.total_tokens + w.tok0));
-  const int nsubs = (w.nkeys + 31) / 32;
-#pragma unroll
-  for (int i = 0; i < NST; ++i)
-    sub_dma(ring + i * kSubVec, kbase, p.k_stride_token, (nsubs - 1 - i) * 32, w.nkeys, voff);
-  if constexpr (!FUSED) {
+// Pass 2 of `count` sub-blocks of one sequence (or chunk), from number first_sub down (arguments as pass1_piece).  lse: of the
+// sequence's first row, out: where the sums of its first key go.  LOADED: the query fragments are in registers and off2 is
+// filled.
+template <int NRB, int NST, bool LOADED, class Stream>
+__device__ __forceinline__ void pass2_piece(const ScoreParams& p, u32x4* ring, int& slot, Stream& keys, bf16x8 (&kf)[8],
+                                            bf16x8 (&qf)[NRB][8], float (&off2)[NRB][16], const uint16_t* qbase,
+                                            const float* lse, int first_sub, int count, int nkeys, int gbase,
+                                            const unsigned (&voff)[4], bool start, float* out) {
+  const int lane = fresh_lane(), n = lane & 31, h = lane >> 5;
+  if constexpr (!LOADED) {
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) frag_from_q(qf[rb], p, qbase, gbase + rb * 32 + n, h);
     if (NRB == 8) pin_q_in_agprs<NRB>(qf);
@@ -897,23 +919,85 @@ __device__ __forceinline__ unsigned pass2_item(const ScoreParams& p, u32x4* ring
         }
     }
   }
-  bf16x8 kf[8];
-  wait_subblocks(NST - 1);
-  wave_load_frags<NRB>(kf, ring, n, h);
+  if (start) {
+    wait_ring_full<NST>();
+    wave_load_frags<NRB>(kf, ring + slot * kSubVec, n, h);
+  }
   float unused_off[NRB], unused_acc[NRB];
 #pragma unroll
   for (int rb = 0; rb < NRB; ++rb) unused_off[rb] = 0.0f;
-  wave_walk<NRB, 2, NST, true>(ring, kbase, p.k_stride_token, w.nkeys, 0, nsubs, kf, qf, p.c, unused_off, off2,
-                                        unused_acc, out, voff, n, h, nsubs - 1);
-  const unsigned next = work != nullptr ? take_item(work, lane) : 0u;
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  return next;
+  wave_walk<NRB, 2, NST>(ring, slot, keys, first_sub, count, nkeys, kf, qf, p.c, unused_off, off2, unused_acc, out, voff, n, h);
+}
+__device__ __forceinline__ const float* wave_lse(const ScoreParams& p, int layer, int kv, int seq) {
+  return p.lse2 + (((int64_t)layer * p.batch + seq) * p.n_q_heads + (int64_t)kv * p.group) * p.n_pseudo;
+}
+// The column sums of a row group of a head.  With several row groups each writes its own plane (group 0 straight into the
+// result); a small kernel adds the others onto it.
+__device__ __forceinline__ float* wave_plane(const ScoreParams& p, int head, int group) {
+  float* plane = group == 0 ? p.scores : p.partial + (int64_t)(group - 1) * p.n_layers * p.n_kv_heads * p.total_tokens;
+  return plane + (int64_t)head * p.total_tokens;
 }
 
-// (DYN as in pass 1.)  Heads and, inside a chunk, the keys are walked in the opposite order to pass 1: what pass 1
+// Pass 2 of one chunk of a dense batch (arguments as pass1_chunk).  FUSED (score_fused_kernel): the query fragments are still in
+// registers from pass 1 and the caller has filled off2.
+template <int NRB, int NST, bool FUSED = false>
+__device__ __forceinline__ void pass2_chunk(const ScoreParams& p, u32x4* ring, const Work& w, int group, int head,
+                                            bf16x8 (&qf)[NRB][8], float (&off2)[NRB][16], int lane) {
+  unsigned voff[4];
+  sub_dma_lane_offsets(voff, p.k_stride_token, lane);
+  // (the division runs on the vector ALU: bring the quotient back to a scalar register)
+  const int layer = uniform_i32(head / p.n_kv_heads), kv = head - layer * p.n_kv_heads;
+  const uint16_t* kbase = uniform_ptr(p.k + (int64_t)layer * p.k_stride_layer + (int64_t)w.seq * p.k_stride_seq +
+                                      (int64_t)kv * p.k_stride_head + w.tok0 * p.k_stride_token);
+  float* out = const_cast<float*>(uniform_ptr(wave_plane(p, head, group) + w.tok0));
+  const int nsubs = (w.nkeys + 31) / 32;
+  KeyStream<true, false> keys = {p, nullptr, kbase, w.nkeys, 0, 0, 0};
+  fill_ring<NST>(ring, keys, voff, nsubs - 1);
+  bf16x8 kf[8];
+  int slot = 0;
+  pass2_piece<NRB, NST, FUSED>(p, ring, slot, keys, kf, qf, off2, wave_q_base(p, layer, kv, w.seq), wave_lse(p, layer, kv, w.seq),
+                               nsubs - 1, nsubs, w.nkeys, group * (NRB * 32), voff, true, out);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
+// Pass 2 of one segment of a ragged batch, from its last sub-block to its first.
+template <int NRB, int NST>
+__device__ __forceinline__ void pass2_segment(const ScoreParams& p, u32x4* ring, int segment, int group, int head,
+                                              bf16x8 (&qf)[NRB][8], float (&off2)[NRB][16], int lane) {
+  Segment at = segment_of_wave(p, segment, true);
+  if (at.left == 0) return;
+  unsigned voff[4];
+  sub_dma_lane_offsets(voff, p.k_stride_token, lane);
+  const int layer = uniform_i32(head / p.n_kv_heads), kv = head - layer * p.n_kv_heads;
+  KeyStream<true, true> keys = {p, uniform_ptr(p.k + (int64_t)layer * p.k_stride_layer + (int64_t)kv * p.k_stride_head),
+                                nullptr, 0, at.sub, at.seq, at.left};
+  keys.enter(seq_range(p, at.seq));
+  fill_ring<NST>(ring, keys, voff, 0);
+  bf16x8 kf[8];
+  int slot = 0;
+  for (bool start = true;; start = false) {
+    const SeqRange r = seq_range(p, at.seq);
+    if (r.len > 0) {
+      const int nkeys = uniform_i32(r.len);
+      if (!start) at.sub = (nkeys - 1) / 32;
+      const int count = at.left < at.sub + 1 ? at.left : at.sub + 1;
+      // (the sums of a piece go out relative to its first key: their offsets are 32 bits wide)
+      const int key0 = (at.sub + 1 - count) * 32, keys_here = nkeys - key0 < count * 32 ? nkeys - key0 : count * 32;
+      float* out = const_cast<float*>(uniform_ptr(wave_plane(p, head, group) + r.start + key0));
+      pass2_piece<NRB, NST, false>(p, ring, slot, keys, kf, qf, off2, wave_q_base(p, layer, kv, at.seq),
+                                   wave_lse(p, layer, kv, at.seq), count - 1, count, keys_here, group * (NRB * 32), voff, start, out);
+      at.left -= count;
+      if (at.left == 0) break;
+    }
+    at.seq -= 1;
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
+// (SEG as in pass 1.)  Heads and, inside a chunk or segment, the keys are walked in the opposite order to pass 1: what pass 1
 // read last (the ends of the chunks in flight, the heads of the last round) is still in the 256 MB memory-side cache
 // when pass 2 starts.
-template <int NRB, bool DYN, int NST>
+template <int NRB, bool SEG, int NST>
 __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_wave_pass2_kernel(ScoreParams p) {
   extern __shared__ u32x4 rings[];
   const int wave_id = uniform_i32((int)(threadIdx.x >> 6));
@@ -921,33 +1005,14 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_wave_pass2_kerne
   const int lane = threadIdx.x & 63;
   bf16x8 qf[NRB][8];
   float off2[NRB][16];
-  if (!DYN) {
-    const WaveSlot slot = wave_slot(p, wave_id);
+  const WaveSlot slot = wave_slot(p, wave_id);
+  const int head = (int)(gridDim.z - 1 - blockIdx.z);
+  if constexpr (SEG) {
+    pass2_segment<NRB, NST>(p, ring, slot.chunk, slot.group, head, qf, off2, lane);
+  } else {
     const Work w = locate_uniform(p, slot.chunk);
     if (w.nkeys == 0) return;
-    pass2_item<NRB, NST>(p, ring, w, slot.group, (int)(gridDim.z - 1 - blockIdx.z), qf, off2, lane, nullptr);
-    return;
-  }
-  const ItemLists lists = item_lists(p);
-  const int home = home_list();
-  TeamTickets tickets = team_tickets(rings, NST, wave_id);
-  for (unsigned x = (unsigned)home; x < (unsigned)kLists;) {  // this XCD's list first, then those not yet drained
-    unsigned* work = tickets.leader ? p.work + x : nullptr;  // (only the leader of a team takes tickets)
-    const unsigned n_items = lists.count((int)x);
-    tickets.post(work != nullptr ? take_item(work, lane) : 0u, lane);
-    for (;;) {  // every team leaves: the tickets only grow
-      const unsigned ticket = tickets.next();
-      if (ticket >= n_items) break;
-      const Item a = lists.at(p, (int)x, ticket, true);
-      if (a.work.nkeys == 0) {  // (no chunk of a list is empty; if one were, it would only cost its ticket)
-        tickets.post(work != nullptr ? take_item(work, lane) : 0u, lane);
-        continue;
-      }
-      tickets.post(pass2_item<NRB, NST>(p, ring, a.work, a.block * p.wg_groups + wave_id, a.head, qf, off2, lane, work),
-                   lane);
-    }
-    tickets.post(tickets.leader ? next_list(p, lists, home, lane) : 0u, lane);
-    x = tickets.next();
+    pass2_chunk<NRB, NST>(p, ring, w, slot.group, head, qf, off2, lane);
   }
 }
 
@@ -969,7 +1034,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_fused_kernel(Sco
   const int chunk = uniform_i32((int)blockIdx.x * waves + wave_id);  // blockIdx.x is the sequence
   const int head = (int)blockIdx.z;
   const Work work = locate_uniform(p, chunk);
-  pass1_item<NRB, NST, true>(p, ring, work, chunk, 0, head, qf, lane, nullptr);
+  pass1_chunk<NRB, NST, true>(p, ring, work, chunk, 0, head, qf, lane);
   __syncthreads();
   // lse2 of rows lane, lane + 64, ...: every wave merges all chunks itself
   constexpr int kRowsPerLane = NRB * 32 / 64;
@@ -1008,7 +1073,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_fused_kernel(Sco
       off2[rb][4 * b + 3] = v.w;
     }
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // off2 is out of the ring before pass 2 refills it
-  pass2_item<NRB, NST, true>(p, ring, work, 0, head, qf, off2, lane, nullptr);
+  pass2_chunk<NRB, NST, true>(p, ring, work, 0, head, qf, off2, lane);
 }
 
 // The causal block of the pseudo tokens' own keys (Sec. 4.1: they are prefilled in-sequence): one wave
@@ -1048,7 +1113,7 @@ __global__ __launch_bounds__(64, 1) void score_wave_pseudo_kernel(ScoreParams p,
   bf16x8 kf[8];
   const int nsubs = (p.n_pseudo + 31) / 32;
   for (int sub = 0; sub < nsubs; ++sub) {
-    sub_dma(ring, kbase, pp.stride_row, sub * 32, p.n_pseudo, voff);
+    sub_dma(ring, kbase, pp.stride_row, sub * 32, p.n_pseudo, true, voff);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     wave_load_frags<NRB>(kf, ring, n, h);
     wave_sub_simple<NRB, true, false, true>(kf, qf, p.c, ref, z, sub * 32, p.n_pseudo, h, last_key);
@@ -1338,26 +1403,25 @@ int simd_count() {
   return simds[dev];
 }
 
-// How a dense launch packs its waves into workgroups: `waves` to a workgroup (kWavesPerGroup or 1), of which `groups`
+// The waves of a launch per head and row group: chunks of a dense batch, segments of a ragged one.
+int64_t wave_chunks(const ScorePlan& plan) { return plan.segments > 0 ? plan.segments : plan.max_chunks; }
+
+// How a launch packs its waves into workgroups: `waves` to a workgroup (kWavesPerGroup or 1), of which `groups`
 // are the row groups of one chunk side by side (see wave_slot) and waves / groups consecutive chunks.
 struct GroupShape {
   int waves, groups;
   dim3 grid(const ScorePlan& plan, const dapq_shape* s) const {
     const int cpw = waves / groups;
-    return dim3((unsigned)((plan.max_chunks + cpw - 1) / cpw), (unsigned)(plan.n_groups / groups),
+    return dim3((unsigned)((wave_chunks(plan) + cpw - 1) / cpw), (unsigned)(plan.n_groups / groups),
                 (unsigned)(s->n_layers * s->n_kv_heads));
   }
 };
 GroupShape group_shape(const dapq_shape* s, const ScorePlan& plan) {
-  if (s->cu_seqlens != nullptr) return {1, 1};
   const int groups = plan.n_groups % 4 == 0 ? 4 : (plan.n_groups % 2 == 0 ? 2 : 1);
   int chunks = kWavesPerGroup / groups;  // consecutive chunks in a workgroup: every workgroup must be full
-  while (chunks > 1 && plan.max_chunks % chunks != 0) chunks /= 2;
+  while (chunks > 1 && wave_chunks(plan) % chunks != 0) chunks /= 2;
   return {groups * chunks, groups};
 }
-
-// Waves of a persistent team of a ragged launch: the row groups of a chunk side by side (see ItemLists).
-int team_size(const ScorePlan& plan) { return plan.n_groups % 4 == 0 ? 4 : (plan.n_groups % 2 == 0 ? 2 : 1); }
 
 int fill_params(const dapq_shape* s, const ScorePlan& plan, ScoreParams* p) {
   p->cu_seqlens = s->cu_seqlens;
@@ -1370,6 +1434,7 @@ int fill_params(const dapq_shape* s, const ScorePlan& plan, ScoreParams* p) {
   p->group = s->n_q_heads / s->n_kv_heads; p->n_pseudo = s->n_pseudo;
   p->rows = plan.rows; p->rows_pad = plan.rows_pad; p->n_groups = plan.n_groups;
   p->chunk_keys = plan.chunk_keys; p->max_chunks = (int32_t)plan.max_chunks;
+  p->segments = plan.segments;
   p->wg_groups = 1;
   p->tile_parts = nullptr;
   p->c = s->scale * 1.4426950408889634f;
@@ -1387,9 +1452,13 @@ int aligned16(const void* ptr, const char* name) {
   return DAPQ_OK;
 }
 
-// Whether the passes of a shape need the chunk prefix in device memory (and the work lists, which are cleared with it).
-bool needs_chunk_prefix(const dapq_shape* s, const ScorePlan& plan) {
-  return s->cu_seqlens != nullptr && !(plan.tile && s->batch <= 64);
+// The prefix of the chunk counts in device memory, for the passes of a shape that need it.
+int launch_chunk_prefix(const dapq_shape* s, const ScorePlan& plan, const ScoreParams& p, hipStream_t stream) {
+  if (s->cu_seqlens == nullptr || s->batch <= 64) return DAPQ_OK;
+  hipLaunchKernelGGL(score_chunk_prefix_kernel, dim3(1), dim3(64), 0, stream, s->cu_seqlens, p.cu_chunks, s->batch,
+                     plan.chunk_keys);
+  DAPQ_HIP_LAUNCH_CHECK("score_chunk_prefix_kernel");
+  return DAPQ_OK;
 }
 
 // The grid of the tile kernels, and the waves of their workgroups: one per row block, at most eight, at least four (with
@@ -1404,58 +1473,39 @@ dim3 tile_threads(const ScorePlan& plan) {
 
 int launch_wave_pass1(const dapq_shape* s, const ScorePlan& plan, ScoreParams p, hipStream_t stream) {
   int rc = DAPQ_OK;
-  const int64_t waves = plan.max_chunks * plan.n_groups * s->n_layers * s->n_kv_heads;
   const GroupShape gs = group_shape(s, plan);
-  const int wpg = gs.waves;
-  // ragged: persistent teams (one wave per SIMD; a team = the row groups of a chunk side by side) take their chunks
-  // from work lists (32-bit tickets)
-  const bool dyn = s->cu_seqlens != nullptr && waves < ((int64_t)1 << 31);
-  const int team = dyn ? team_size(plan) : 1;
-  p.wg_groups = dyn ? team : gs.groups;
-  const int64_t teams = waves / team, team_slots = simd_count() / team;
-  const dim3 dyn_grid((unsigned)(teams < team_slots ? teams : team_slots));
-  const dim3 grid = gs.grid(plan, s);
-#define DAPQ_LAUNCH_W1(NRBV)                                                                                        \
-  do {                                                                                                              \
-    if (dyn && team > 1) { /* (more than 256 rows: eight row blocks per wave) */                                    \
-      const int lds = team * wave_lds(kTeamStages) + 16;                                                            \
-      if ((rc = set_lds(score_wave_pass1_kernel<8, true, kTeamStages>, kWavesPerGroup * wave_lds(kTeamStages) + 16)) != \
-          DAPQ_OK)                                                                                                  \
-        return rc;                                                                                                  \
-      hipLaunchKernelGGL((score_wave_pass1_kernel<8, true, kTeamStages>), dyn_grid, dim3(64 * team), lds, stream, p);   \
-    } else if (dyn) {                                                                                               \
-      if ((rc = set_lds(score_wave_pass1_kernel<NRBV, true, kWaveStages>, wave_lds(kWaveStages))) != DAPQ_OK) return rc; \
-      hipLaunchKernelGGL((score_wave_pass1_kernel<NRBV, true, kWaveStages>), dyn_grid, dim3(64), wave_lds(kWaveStages), \
-                         stream, p);                                                                                \
-    } else {                                                                                                        \
-      if ((rc = set_lds(score_wave_pass1_kernel<NRBV, false, kWaveStages>, kWavesPerGroup * wave_lds(kWaveStages))) !=  \
-          DAPQ_OK)                                                                                                  \
-        return rc;                                                                                                  \
-      hipLaunchKernelGGL((score_wave_pass1_kernel<NRBV, false, kWaveStages>), grid, dim3(64 * wpg),                     \
-                         wpg * wave_lds(kWaveStages), stream, p);                                                   \
-    }                                                                                                               \
+  p.wg_groups = gs.groups;
+#define DAPQ_LAUNCH_W1(NRBV, SEGV)                                                                                      \
+  do {                                                                                                                  \
+    if ((rc = set_lds(score_wave_pass1_kernel<NRBV, SEGV, kWaveStages>, kWavesPerGroup * wave_lds(kWaveStages))) !=     \
+        DAPQ_OK)                                                                                                        \
+      return rc;                                                                                                        \
+    hipLaunchKernelGGL((score_wave_pass1_kernel<NRBV, SEGV, kWaveStages>), gs.grid(plan, s), dim3(64 * gs.waves),       \
+                       gs.waves * wave_lds(kWaveStages), stream, p);                                                    \
   } while (0)
-  if (plan.row_blocks == 2) DAPQ_LAUNCH_W1(2);
-  else if (plan.row_blocks == 4) DAPQ_LAUNCH_W1(4);
-  else DAPQ_LAUNCH_W1(8);
+  if (plan.segments > 0) {
+    if (plan.row_blocks == 2) DAPQ_LAUNCH_W1(2, true);
+    else if (plan.row_blocks == 4) DAPQ_LAUNCH_W1(4, true);
+    else DAPQ_LAUNCH_W1(8, true);
+  } else {
+    if (plan.row_blocks == 2) DAPQ_LAUNCH_W1(2, false);
+    else if (plan.row_blocks == 4) DAPQ_LAUNCH_W1(4, false);
+    else DAPQ_LAUNCH_W1(8, false);
+  }
 #undef DAPQ_LAUNCH_W1
   DAPQ_HIP_LAUNCH_CHECK("score_wave_pass1_kernel");
   return DAPQ_OK;
 }
 
 int launch_stats(const dapq_shape* s, const ScorePlan& plan, ScoreParams p, hipStream_t stream) {
-  if (needs_chunk_prefix(s, plan)) {
-    hipLaunchKernelGGL(score_chunk_prefix_kernel, dim3(1), dim3(64), 0, stream, s->cu_seqlens, p.cu_chunks, p.work,
-                       s->batch, plan.chunk_keys);
-    DAPQ_HIP_LAUNCH_CHECK("score_chunk_prefix_kernel");
-  }
+  int rc = launch_chunk_prefix(s, plan, p, stream);
+  if (rc != DAPQ_OK) return rc;
   if (plan.tile) {
     hipLaunchKernelGGL(score_tile_pass1_kernel, tile_grid(s, plan), tile_threads(plan), 0, stream, p);
     DAPQ_HIP_LAUNCH_CHECK("score_tile_pass1_kernel");
     if (p.lse2 == nullptr) return DAPQ_OK;  // pass 2 merges the partials itself
   } else {
-    const int rc = launch_wave_pass1(s, plan, p, stream);
-    if (rc != DAPQ_OK) return rc;
+    if ((rc = launch_wave_pass1(s, plan, p, stream)) != DAPQ_OK) return rc;
   }
   // as many waves per 64 rows as the (mean) sequence has runs of chunks
   const int64_t chunks_per_seq = (plan.max_chunks + s->batch - 1) / s->batch, row_tiles = (plan.rows + 63) / 64;
@@ -1473,53 +1523,33 @@ int launch_stats(const dapq_shape* s, const ScorePlan& plan, ScoreParams p, hipS
 }
 
 int launch_accumulate(const dapq_shape* s, const ScorePlan& plan, ScoreParams p, hipStream_t stream) {
-  if (needs_chunk_prefix(s, plan)) {
-    // pass 2 can be called on its own: rebuild the chunk prefix it walks
-    hipLaunchKernelGGL(score_chunk_prefix_kernel, dim3(1), dim3(64), 0, stream, s->cu_seqlens, p.cu_chunks, p.work,
-                       s->batch, plan.chunk_keys);
-    DAPQ_HIP_LAUNCH_CHECK("score_chunk_prefix_kernel");
-  }
+  int rc = launch_chunk_prefix(s, plan, p, stream);  // (pass 2 can be called on its own: it rebuilds the prefix it walks)
+  if (rc != DAPQ_OK) return rc;
   if (plan.tile) {
     if (p.lse2 == nullptr) hipLaunchKernelGGL(score_tile_pass2_kernel<true>, tile_grid(s, plan), tile_threads(plan), 0, stream, p);
     else hipLaunchKernelGGL(score_tile_pass2_kernel<false>, tile_grid(s, plan), tile_threads(plan), 0, stream, p);
     DAPQ_HIP_LAUNCH_CHECK("score_tile_pass2_kernel");
     return DAPQ_OK;
   }
-  int rc = DAPQ_OK;
-  const int64_t waves = plan.max_chunks * plan.n_groups * s->n_layers * s->n_kv_heads;
   const GroupShape gs = group_shape(s, plan);
-  const int wpg = gs.waves;
-  // ragged: persistent teams (one wave per SIMD; a team = the row groups of a chunk side by side) take their chunks
-  // from work lists (32-bit tickets)
-  const bool dyn = s->cu_seqlens != nullptr && waves < ((int64_t)1 << 31);
-  const int team = dyn ? team_size(plan) : 1;
-  p.wg_groups = dyn ? team : gs.groups;
-  const int64_t teams = waves / team, team_slots = simd_count() / team;
-  const dim3 dyn_grid((unsigned)(teams < team_slots ? teams : team_slots));
-  const dim3 grid = gs.grid(plan, s);
-#define DAPQ_LAUNCH_W2(NRBV)                                                                                        \
-  do {                                                                                                              \
-    if (dyn && team > 1) { /* (more than 256 rows: eight row blocks per wave) */                                    \
-      const int lds = team * wave_lds(kTeamStages) + 16;                                                            \
-      if ((rc = set_lds(score_wave_pass2_kernel<8, true, kTeamStages>, kWavesPerGroup * wave_lds(kTeamStages) + 16)) != \
-          DAPQ_OK)                                                                                                  \
-        return rc;                                                                                                  \
-      hipLaunchKernelGGL((score_wave_pass2_kernel<8, true, kTeamStages>), dyn_grid, dim3(64 * team), lds, stream, p);   \
-    } else if (dyn) {                                                                                               \
-      if ((rc = set_lds(score_wave_pass2_kernel<NRBV, true, kWaveStages>, wave_lds(kWaveStages))) != DAPQ_OK) return rc; \
-      hipLaunchKernelGGL((score_wave_pass2_kernel<NRBV, true, kWaveStages>), dyn_grid, dim3(64), wave_lds(kWaveStages), \
-                         stream, p);                                                                                \
-    } else {                                                                                                        \
-      if ((rc = set_lds(score_wave_pass2_kernel<NRBV, false, kWaveStages>, kWavesPerGroup * wave_lds(kWaveStages))) !=  \
-          DAPQ_OK)                                                                                                  \
-        return rc;                                                                                                  \
-      hipLaunchKernelGGL((score_wave_pass2_kernel<NRBV, false, kWaveStages>), grid, dim3(64 * wpg),                     \
-                         wpg * wave_lds(kWaveStages), stream, p);                                                   \
-    }                                                                                                               \
+  p.wg_groups = gs.groups;
+#define DAPQ_LAUNCH_W2(NRBV, SEGV)                                                                                      \
+  do {                                                                                                                  \
+    if ((rc = set_lds(score_wave_pass2_kernel<NRBV, SEGV, kWaveStages>, kWavesPerGroup * wave_lds(kWaveStages))) !=     \
+        DAPQ_OK)                                                                                                        \
+      return rc;                                                                                                        \
+    hipLaunchKernelGGL((score_wave_pass2_kernel<NRBV, SEGV, kWaveStages>), gs.grid(plan, s), dim3(64 * gs.waves),       \
+                       gs.waves * wave_lds(kWaveStages), stream, p);                                                    \
   } while (0)
-  if (plan.row_blocks == 2) DAPQ_LAUNCH_W2(2);
-  else if (plan.row_blocks == 4) DAPQ_LAUNCH_W2(4);
-  else DAPQ_LAUNCH_W2(8);
+  if (plan.segments > 0) {
+    if (plan.row_blocks == 2) DAPQ_LAUNCH_W2(2, true);
+    else if (plan.row_blocks == 4) DAPQ_LAUNCH_W2(4, true);
+    else DAPQ_LAUNCH_W2(8, true);
+  } else {
+    if (plan.row_blocks == 2) DAPQ_LAUNCH_W2(2, false);
+    else if (plan.row_blocks == 4) DAPQ_LAUNCH_W2(4, false);
+    else DAPQ_LAUNCH_W2(8, false);
+  }
 #undef DAPQ_LAUNCH_W2
   DAPQ_HIP_LAUNCH_CHECK("score_wave_pass2_kernel");
   if (plan.n_groups > 1) {
@@ -1603,7 +1633,6 @@ extern "C" DAPQ_API int dapq_score_stats(const dapq_shape* shape, const void* q,
   p.q = static_cast<const uint16_t*>(q);
   p.k = static_cast<const uint16_t*>(k);
   p.cu_chunks = reinterpret_cast<int32_t*>(ws + plan.off_cu_chunks);
-  p.work = reinterpret_cast<unsigned*>(ws + plan.off_work);
   set_parts(plan, ws, &p);
   p.lse2 = lse2;
   p.scores = nullptr;
@@ -1628,7 +1657,6 @@ extern "C" DAPQ_API int dapq_score_accumulate(const dapq_shape* shape, const voi
   p.q = static_cast<const uint16_t*>(q);
   p.k = static_cast<const uint16_t*>(k);
   p.cu_chunks = reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + plan.off_cu_chunks);
-  p.work = reinterpret_cast<unsigned*>(static_cast<char*>(workspace) + plan.off_work);
   p.parts = nullptr;
   p.partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + plan.off_partial);
   p.lse2 = const_cast<float*>(lse2);
@@ -1660,7 +1688,6 @@ extern "C" DAPQ_API int dapq_score(const dapq_shape* shape, const void* q, const
     p.q = static_cast<const uint16_t*>(q);
     p.k = static_cast<const uint16_t*>(k);
     p.cu_chunks = nullptr;
-    p.work = nullptr;
     p.parts = nullptr;
     p.partial = nullptr;
     p.lse2 = nullptr;
@@ -1676,7 +1703,6 @@ extern "C" DAPQ_API int dapq_score(const dapq_shape* shape, const void* q, const
     p.q = static_cast<const uint16_t*>(q);
     p.k = static_cast<const uint16_t*>(k);
     p.cu_chunks = reinterpret_cast<int32_t*>(ws + plan.off_cu_chunks);
-    p.work = reinterpret_cast<unsigned*>(ws + plan.off_work);
     set_parts(plan, ws, &p);
     p.partial = nullptr;
     p.lse2 = nullptr;
@@ -1713,7 +1739,6 @@ extern "C" DAPQ_API int dapq_score_stats_extend(const dapq_shape* shape, const v
   p.q = static_cast<const uint16_t*>(q);
   p.k = nullptr;
   p.cu_chunks = nullptr;
-  p.work = nullptr;
   p.parts = nullptr;
   p.partial = nullptr;
   p.scores = nullptr;

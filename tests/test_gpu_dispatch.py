@@ -377,6 +377,40 @@ def test_ragged_batches_in_the_wave_form(H, rows, batch):
     H.assert_scores_close(S[:1].cpu().numpy(), O.score(q, k, 2, cu), f"rows={rows} batch={batch}")
 
 
+# segments that begin and end inside sequences, take in several, empty ones among them, or hold one sub-block; a head of one key
+@pytest.mark.parametrize("rows", [33, 128, 250, 300])
+@pytest.mark.parametrize("lens", [[1, 0, 31, 32, 33, 0, 0, 64, 900, 5, 0, 1300, 0], [0, 2500, 0, 65], [1], [0, 3, 0]],
+                         ids=lambda lens: f"{len(lens)}x{max(lens)}")
+def test_segments_of_ragged_batches(H, rows, lens):
+    """Enough layers of the same problem for the wave form, with a key hundreds of binades above the others (its piece is summed
+    again): the oracle's scores and normalisers (the bars of the other score tests), the same bits in every layer and from the two
+    separate entry points."""
+    announce(f"segments: {lens} rows={rows}")
+    q, k, v, cu = problem_bits(rows, 1, lens, 2, 2, rows)
+    tokens = int(cu[-1])
+    layers = 66000 // (2 * (tokens // 128 + len(lens)) * ((rows + 31) // 32)) + 1
+    b = int(np.argmax(lens))
+    if tokens > 1:
+        k[0, int(cu[b]) + 3 * lens[b] // 5, 1] = W.to_bf16_bits(30.0 * O.bf16_bits_to_f64(q[0, b, 1, 0]))
+    prob = H.Problem(q, k, v, 2, cu, "thd")
+    shape = H.D.make_shape(n_layers=layers, batch=len(lens), n_q_heads=2, n_kv_heads=2, n_pseudo=rows, total_tokens=tokens,
+                           cu_seqlens=prob.cu, k_strides=(0, 0, 128, 256), q_strides=(0, 2 * rows * 128, rows * 128, 128),
+                           scale=128 ** -0.5)
+    ws_bytes = H.D.workspace_bytes(shape)
+    ws = torch.full((ws_bytes,), 0xA5, dtype=torch.uint8, device="cuda")
+    S, T = (torch.full((layers, 2, tokens), float("nan"), dtype=torch.float32, device="cuda") for _ in range(2))
+    lse = torch.full((layers, len(lens), 2, rows), float("nan"), dtype=torch.float32, device="cuda")
+    H.D.dapq_score(shape, prob.q, prob.k, S, ws)
+    H.D.dapq_score_stats(shape, prob.q, prob.k, lse, ws)
+    H.D.dapq_score_accumulate(shape, prob.q, prob.k, lse, T, ws)
+    assert torch.equal(S, T) and torch.equal(S, S[:1].expand_as(S)) and torch.equal(lse, lse[:1].expand_as(lse))
+    if tokens:
+        H.assert_scores_close(S[:1].cpu().numpy(), O.score(q, k, 2, cu), f"{lens} rows={rows}")
+    live = [i for i, n in enumerate(lens) if n]
+    err = np.abs(lse[:1].cpu().numpy()[:, live] - oracle_lse2(q, k, 2, cu)[:, live])
+    assert not live or err.max() < 2e-4
+
+
 # fewer channel pairs than a wave has lanes, one wave, a few; heads up to the most a launch takes
 @pytest.mark.parametrize("rows,heads,d", [(1, 65536, 64), (1, 100000, 64), (1, 65535 * 8, 8), (2, 9000, 64), (1, 3, 128), (3, 1025, 24)])
 def test_rotation_of_many_heads(H, rows, heads, d):
