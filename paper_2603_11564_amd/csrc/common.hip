@@ -144,6 +144,7 @@ int make_score_plan(const dapq_shape* s, size_t workspace_bytes, ScorePlan* p) {
   p->row_blocks = split.row_blocks;
   p->rows_pad = p->n_groups * p->row_blocks * 32;
   p->tile = false;
+  p->stage_q = false;
   p->segments = 0;
 
   constexpr int64_t kWaveSlots = 1024;
@@ -173,13 +174,17 @@ int make_score_plan(const dapq_shape* s, size_t workspace_bytes, ScorePlan* p) {
   }
   if (rc != DAPQ_OK) return rc;
 
-  // The tile form: a workgroup per 128 keys, its waves a row block each.  It is the faster one where the wave form leaves
-  // the chip idle or pays its start-up per chunk (the queries of up to 256 rows into one wave, a ring of its own).
-  // Both passes of dapq_score, wave form -> tile form, 8 KV heads: one layer, 1024 keys, 256 rows 38.6 -> 14.9 us; 8191
-  // keys, 128 rows 26.9 -> 18.6; 16384 keys, 256 rows 44 -> 41, 512 rows 57 -> 61; 32768 keys, 128 rows 39 -> 45; ragged,
-  // 8 prompts of 1000 keys, one layer, 128 rows 76 -> 24, 4 layers, 128 rows (10 000 units) 146 -> 59, 512 rows (40 000
-  // units) 188 -> 174; 32 layers, 16 prompts of 700, 128 rows (120 000) 530 -> 597.  Where dapq_score runs both passes in one
+  // The tile form.  It is the faster one where the wave form leaves the chip idle or pays its start-up per chunk (the queries of up
+  // to 256 rows into one wave, a ring of its own).  Both passes of dapq_score, wave form -> tiles of 128 keys with the queries
+  // straight from memory, 8 KV heads: one layer, 1024 keys, 256 rows 38.6 -> 14.9 us; 8191 keys, 128 rows 26.9 -> 18.6; 16384 keys,
+  // 256 rows 44 -> 41, 512 rows 57 -> 61; 32768 keys, 128 rows 39 -> 45; ragged, 8 prompts of 1000 keys, one layer, 128 rows 76 ->
+  // 24, 4 layers, 128 rows (10 000 units) 146 -> 59, 512 rows (40 000 units) 188 -> 174.  Where dapq_score runs both passes in one
   // kernel it stays with that one.
+  // Calls of at most 256 workgroups, a compute unit each, take tiles as small as that allows (ragged ones up to 128 keys: larger
+  // tiles would need less workspace than a longer batch), with the queries through LDS in whole rows; larger calls live from several
+  // workgroups to a compute unit, which the queries' LDS would keep out (128 rows, 16384 keys: 32 us with it, 27 without).
+  // With the rotation, tiles of 128 keys -> these: 1024 keys, 256 rows 17.7 -> 13.4 us; 4096 keys 19.1 -> 17.1; 8191 keys, 128 rows
+  // 21.9 -> 17.7 (no separate merge of the normalisers at 32 tiles); 5000 keys, 16 rows 17.9 -> 12.8.
   const bool ragged = s->cu_seqlens != nullptr;
   const bool one_kernel = !ragged && p->n_groups == 1 && p->max_chunks <= 4 * (int64_t)s->batch;
   const int64_t row_blocks = (p->rows + 31) / 32;
@@ -192,7 +197,17 @@ int make_score_plan(const dapq_shape* s, size_t workspace_bytes, ScorePlan* p) {
   t.row_blocks = (int)row_blocks;
   t.n_groups = 1;
   t.rows_pad = t.row_blocks * 32;
-  rc = finish_score_plan(s, heads, kTileKeys, &t);
+  int keys = kTileKeys;
+  t.stage_q = false;
+  for (int c = kTileMinKeys; c <= (ragged ? kTileKeys : kTileMaxKeys); c *= 2) {
+    const int64_t L = s->total_tokens / s->batch;
+    if (heads * (ragged ? s->total_tokens / c + s->batch : s->batch * ((L + c - 1) / c)) <= 256) {
+      keys = c;
+      t.stage_q = true;
+      break;
+    }
+  }
+  rc = finish_score_plan(s, heads, keys, &t);
   if (rc != DAPQ_OK) return rc;
   // The figure is no smaller than the wave form's, which a caller may have sized its workspace for by another shape.
   if (t.total_bytes < p->total_bytes) t.total_bytes = p->total_bytes;

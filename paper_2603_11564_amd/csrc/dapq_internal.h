@@ -29,11 +29,13 @@ int fail(int code, const char* fmt, ...);
 constexpr int kHeadDim = 128;
 constexpr int kMinChunkKeys = 128;      // fewest keys one wave of a score pass walks over
 constexpr int kMaxChunkKeys = 1 << 16;  // most
-constexpr int kTileKeys = kMinChunkKeys;  // keys of a workgroup of the tile form of the score passes
+// Keys of a workgroup of the tile form of the score passes; the size of a call is counted in tiles of kTileKeys.
+constexpr int kTileKeys = 128, kTileMinKeys = 32, kTileMaxKeys = 256;
 
 // How the score passes split the work; a pure function of the shape and of the size of the workspace, so that
 // dapq_workspace_bytes() and the launchers agree.
 struct ScorePlan {
+  bool stage_q;    // tile form: the queries go through LDS
   bool tile;       // the tile kernels (a workgroup per chunk, its waves share out the rows) instead of the wave kernels
   int rows;        // R = (H_q/H_kv) * N query rows scored against every key of a KV head
   int n_groups;    // row groups of row_blocks * 32 rows, one wave each per chunk (tile: 1)

@@ -42,6 +42,7 @@
 #include <mutex>
 
 #include "dapq_internal.h"
+#include "kernel_args.h"
 #include "wave_scan.h"
 
 namespace dapq {
@@ -70,7 +71,16 @@ struct ScoreParams {
   int32_t segments;           // ragged batches in the wave form: segments a head is cut into (chunk_keys is a sub-block then)
   int32_t wg_groups;          // row groups that sit side by side in a workgroup (dense launches; 1, 2 or 4)
   float c;  // scale * log2(e)
+  // What every workgroup would divide for before it can ask for its first key (a division is twenty instructions in a row, one
+  // of 64 bits a hundred; a pass of a small call lasts 10 000 clocks):
+  int32_t seq_len, chunks_per_seq;  // dense batches
+  int32_t chunk_shift;              // log2(chunk_keys)
+  int32_t stage_q;                  // tile form: the queries go through LDS too
+  float inv_n_pseudo, inv_kv_heads, inv_rows_pad;  // tile form
 };
+
+// a / b for inv = 1 / b, a < 2^21: (a + 1/2) * inv is off by less than 2^-2 / b, and at least half of 1 / b away from a whole number.
+__device__ __forceinline__ int quotient(int a, float inv) { return (int)(((float)a + 0.5f) * inv); }
 
 constexpr int kSubBytes = 32 * kHeadDim * 2;          // one 32-key sub-block
 
@@ -95,7 +105,7 @@ __device__ __forceinline__ const T* uniform_ptr(const T* ptr) {
 }
 // Chunks of a sequence of L keys (of a ragged batch: chunk_keys is a power of two).
 __device__ __forceinline__ int chunks_of_length(const ScoreParams& p, int L) {
-  return L > 0 ? (L + p.chunk_keys - 1) >> __builtin_ctz((unsigned)p.chunk_keys) : 0;
+  return L > 0 ? (L + p.chunk_keys - 1) >> p.chunk_shift : 0;
 }
 // The lane number, formed where it is asked for: neither it nor what follows from it is kept in registers from before.
 __device__ __forceinline__ int fresh_lane() {
@@ -139,14 +149,13 @@ __device__ __forceinline__ Work locate(const ScoreParams& p, int gchunk) {
   Work w;
   w.nkeys = 0;
   if (p.cu_seqlens == nullptr) {
-    const int L = (int)(p.total_tokens / p.batch);
-    const int cps = (L + p.chunk_keys - 1) / p.chunk_keys;
-    if (cps == 0) return w;
-    w.seq = gchunk / cps;
+    if (p.chunks_per_seq == 0) return w;
+    w.seq = 0;
+    if (p.batch > 1) w.seq = gchunk / p.chunks_per_seq;
     if (w.seq >= p.batch) return w;
-    w.key0 = (gchunk - w.seq * cps) * p.chunk_keys;
-    w.tok0 = (int64_t)w.seq * L + w.key0;
-    w.seq_len = L;
+    w.key0 = (gchunk - w.seq * p.chunks_per_seq) * p.chunk_keys;
+    w.tok0 = (int64_t)w.seq * p.seq_len + w.key0;
+    w.seq_len = p.seq_len;
   } else if (p.batch <= 64) {
     const LaneSequence q = lane_sequence(p);
     w.seq = __popcll(__ballot(q.chunks_end <= gchunk));  // (lanes past the batch repeat the last end)
@@ -255,6 +264,11 @@ __device__ __forceinline__ float sum_halves(float v) {
   asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
   return a + b;  // a = (v.lo, v.lo), b = (v.hi, v.hi)
 }
+__device__ __forceinline__ float max_halves(float v) {
+  float a = v, b = v;
+  asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
+  return fmaxf(a, b);
+}
 
 // Column sums of one sub-block go out through a buffer store whose range check drops what must not be written:
 // lanes of the upper half carry an offset far past the end, and keys at or past nkeys fall outside num_records.
@@ -325,10 +339,8 @@ __global__ __launch_bounds__(64 * kCombineClasses) void score_combine_kernel(Sco
   const int layer = (int)(blockIdx.y / p.n_kv_heads), kv = (int)(blockIdx.y - layer * p.n_kv_heads);
   int c0, c1, total = 0;
   if (p.cu_seqlens == nullptr) {
-    const int L = (int)(p.total_tokens / p.batch);
-    const int cps = (L + p.chunk_keys - 1) / p.chunk_keys;
-    c0 = b * cps;
-    c1 = c0 + cps;
+    c0 = b * p.chunks_per_seq;
+    c1 = c0 + p.chunks_per_seq;
   } else if (p.batch <= 64) {
     const LaneSequence q = lane_sequence(p);
     c1 = __builtin_amdgcn_readlane(q.chunks_end, b);
@@ -448,15 +460,8 @@ __device__ __forceinline__ void sub_dma(u32x4* slot, const uint16_t* kbase, int6
                                              (int)voff[i & 3], (int)((unsigned)(4 * i) * (unsigned)stride_b), 0, 0);
 }
 
-// Waits until at most `newer` sub-block transfers (8 operations each) of this wave are in flight.
-__device__ __forceinline__ void wait_subblocks(int newer) {
-  if (newer <= 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  else if (newer == 1) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-  else if (newer == 2) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
-  else if (newer == 3) asm volatile("s_waitcnt vmcnt(24)" ::: "memory");
-  else asm volatile("s_waitcnt vmcnt(32)" ::: "memory");
-}
-
+// Waits until the sub-block after the current one has landed: at most the transfers (8 operations each) of the NST - 1 newer
+// ones are in flight.
 template <int NST>
 __device__ __forceinline__ void wait_ring_full() {
   static_assert(NST >= 2 && NST <= 5, "ring sizes the kernels use");
@@ -1133,16 +1138,18 @@ __global__ __launch_bounds__(64, 1) void score_wave_pseudo_kernel(ScoreParams p,
 }
 
 // ---------------------------------------------------------------------------------------------
-// The tile form of the passes: one workgroup = kTileKeys keys of one (layer, sequence, KV head) x all its query rows.
-// For calls that are bound by latency (make_score_plan says which): the keys are brought into LDS once, by all waves
-// together, and a wave works on 32 query rows at a time, so it loads 8 KB of queries instead of 64 and the 4 x 8 MFMAs of a
-// row block are its whole chain; at about 90 registers four waves share a SIMD and cover for each other.  One layer,
-// 8 heads, 1024 keys, 256 rows: 18.5 us per pass in the wave form (8 compute units busy), 7.4 / 8.0 us here; what is left
-// is the launch, one trip to memory for keys and queries and 1 us of arithmetic.
+// The tile form of the passes: one workgroup = a tile of p.chunk_keys (32 to 256) keys of one (layer, sequence, KV head) x all its
+// query rows.  For calls that are bound by latency (make_score_plan says which, and how many keys a tile has): keys and queries are
+// brought into LDS once, in whole rows, by all waves together, and a wave works on one row block and its share of the
+// sub-blocks, so that a call of a few thousand keys still has a workgroup for every compute unit and each wave a chain of one to four
+// (sub-block, row block) units.  Operands loaded straight from memory into the layout of the matrix instructions (32 bytes of
+// each of 32 rows per load) cost the queries more than everything else in the kernel.
 // ---------------------------------------------------------------------------------------------
-constexpr int kTileSubs = kTileKeys / 32;
-constexpr int kTileWaves = 8;                                   // most waves of a workgroup
-constexpr int kTileLds = kTileSubs * kSubBytes;
+constexpr int kTileWaves = 8;
+constexpr int kTileThreads = 64 * kTileWaves;
+constexpr int tile_lds(int chunk_keys, int row_blocks, bool stage_q) {
+  return chunk_keys * kHeadDim * 2 + (!stage_q ? 0 : (row_blocks < kTileWaves ? row_blocks : kTileWaves) * kSubBytes);
+}
 
 // Which tile a workgroup works on: the KV heads of a chunk are neighbours in the grid (in the packed layout they share
 // the rows of K), then the chunks, then the layers; pass 2 (`reversed`) walks layers and chunks from the far end.
@@ -1151,20 +1158,51 @@ struct Tile {
 };
 __device__ __forceinline__ Tile tile_of_workgroup(const ScoreParams& p, bool reversed) {
   Tile t;
-  const unsigned c = blockIdx.x / (unsigned)p.n_kv_heads;
-  t.kv = uniform_i32((int)(blockIdx.x - c * (unsigned)p.n_kv_heads));
-  t.chunk = uniform_i32(reversed ? p.max_chunks - 1 - (int)c : (int)c);
+  const int c = uniform_i32(quotient((int)blockIdx.x, p.inv_kv_heads));
+  t.kv = (int)blockIdx.x - c * p.n_kv_heads;
+  t.chunk = reversed ? p.max_chunks - 1 - c : c;
   t.layer = (int)(reversed ? gridDim.z - 1 - blockIdx.z : blockIdx.z);
   return t;
 }
 
-// The waves of a workgroup share out the transfers of the tile's keys: 1 KB (four key rows) each, rows past the end of the
-// chunk arrive as zeros (see sub_dma).
-__device__ __forceinline__ void tile_dma(u32x4* keys, const uint16_t* kbase, int64_t stride_token, int nkeys, int wave,
-                                         int waves, int lane) {
-  const int64_t stride_b = stride_token * 2;
-  const unsigned row0 = (unsigned)lane >> 4, pos = (unsigned)lane & 15u;
-  for (int x = wave; x < kTileSubs * 8; x += waves) {
+// How the waves of a workgroup share out the row blocks and sub-blocks: wave = part * rbs + row block, a part being every
+// parts-th sub-block.  (Waves past the last part only bring in keys and queries.)  Where the queries do not go through LDS a wave
+// takes all sub-blocks: it would load its row block for fewer of them.
+struct TileShare {
+  int subs, rbs, parts, rb, part;
+};
+__device__ __forceinline__ TileShare tile_share(const ScoreParams& p, int wave, int waves) {
+  TileShare s;
+  const int row_blocks = p.rows_pad >> 5;
+  s.subs = p.chunk_keys >> 5;
+  s.rbs = row_blocks < waves ? row_blocks : waves;
+  s.parts = !p.stage_q || s.rbs > 4 ? 1 : (s.rbs > 2 ? 2 : (s.rbs == 2 ? 4 : 8));
+  s.parts = s.parts < s.subs ? s.parts : s.subs;
+  s.part = 0;
+  s.rb = wave;
+  while (s.rb >= s.rbs) {
+    s.rb -= s.rbs;
+    s.part += 1;
+  }
+  return s;
+}
+
+// The waves share out the transfers, 1 KB (four rows) each: first the row blocks of the queries (rows past the last one repeat
+// it; their results are dropped), then the tile's keys (rows past the end of the chunk arrive as zeros, see sub_dma); with eight
+// waves one transfer per wave and row block or sub-block.
+__device__ __forceinline__ void tile_dma(u32x4* keys, u32x4* queries, const ScoreParams& p, const uint16_t* kbase,
+                                         const uint16_t* qbase, int nkeys, const TileShare& s, int wave, int waves, int lane) {
+  const int r = lane >> 4;
+  const unsigned piece = (unsigned)(lane & 15) ^ (unsigned)r;
+  for (int i = 0; p.stage_q && i < s.rbs; ++i) {
+    const int row = i * 32 + 4 * wave + r, rc = row < p.rows ? row : p.rows - 1;
+    const int head = quotient(rc, p.inv_n_pseudo), at = rc - head * p.n_pseudo;
+    const uint16_t* src = qbase + (int64_t)head * p.q_stride_head + (int64_t)at * p.q_stride_row + (piece ^ (4u * (unsigned)(wave & 3))) * 8u;
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                     (__attribute__((address_space(3))) void*)(queries + i * kSubVec + wave * 64), 16, 0, 0);
+  }
+  const int64_t stride_b = p.k_stride_token * 2;
+  for (int x = wave; x < s.subs * 8; x += waves) {
     const int row = 4 * x;
     const bool live = row < nkeys;
     const char* base = reinterpret_cast<const char*>(kbase) + (live ? (int64_t)row * stride_b : (int64_t)0);
@@ -1172,10 +1210,24 @@ __device__ __forceinline__ void tile_dma(u32x4* keys, const uint16_t* kbase, int
     const unsigned records = !live ? 0u : (span > (int64_t)0xFFFFFFFFll ? 0xFFFFFFFFu : (unsigned)span);
     const __amdgpu_buffer_rsrc_t rsrc =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, (int)records, 0x00020000);
-    const unsigned voff = row0 * (unsigned)stride_b + ((pos ^ row0) ^ (4u * ((unsigned)x & 3u))) * 16u;
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)(keys + x * 64), 16,
-                                             (int)voff, 0, 0, 0);
+    const unsigned voff = (unsigned)r * (unsigned)stride_b + (piece ^ (4u * ((unsigned)x & 3u))) * 16u;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)(keys + x * 64), 16, (int)voff, 0, 0, 0);
   }
+}
+// Until all but the last `newer` sub-blocks of the tile have landed, for the whole workgroup.
+__device__ __forceinline__ void tile_wait(int newer) {
+  switch (newer) {
+    case 0: asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); break;
+    case 1: asm volatile("s_waitcnt vmcnt(1)" ::: "memory"); break;
+    case 2: asm volatile("s_waitcnt vmcnt(2)" ::: "memory"); break;
+    case 3: asm volatile("s_waitcnt vmcnt(3)" ::: "memory"); break;
+    case 4: asm volatile("s_waitcnt vmcnt(4)" ::: "memory"); break;
+    case 5: asm volatile("s_waitcnt vmcnt(5)" ::: "memory"); break;
+    case 6: asm volatile("s_waitcnt vmcnt(6)" ::: "memory"); break;
+    default: asm volatile("s_waitcnt vmcnt(7)" ::: "memory"); break;
+  }
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
 }
 
 __device__ __forceinline__ const uint16_t* tile_q_base(const ScoreParams& p, const Tile& t, int seq) {
@@ -1187,116 +1239,185 @@ __device__ __forceinline__ const uint16_t* tile_k_base(const ScoreParams& p, con
                      (int64_t)t.kv * p.k_stride_head + w.tok0 * p.k_stride_token);
 }
 
-// Pass 1, 64 keys at a time with a running maximum.
-__global__ __launch_bounds__(64 * kTileWaves) __attribute__((amdgpu_waves_per_eu(4))) void score_tile_pass1_kernel(ScoreParams p) {
-  __shared__ u32x4 keys[kTileLds / 16];
+// Pass 1 with a running maximum.  STAGED: a sub-block at a time, as the sub-blocks arrive; else 64 keys at a time, a wave's next
+// row block loaded while it finishes the one before.
+template <bool STAGED>
+__global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(STAGED ? 4 : 5))) void score_tile_pass1_kernel(ScoreParams p) {
+  extern __shared__ u32x4 tile_area[];
+  __shared__ float2 sums[STAGED ? kTileWaves : 1][32];
+  touch_args<sizeof(ScoreParams)>();
   const Tile t = tile_of_workgroup(p, false);
   const Work w = locate_uniform(p, t.chunk);
   if (w.nkeys == 0) return;  // (the same for the whole workgroup)
   const int wave = uniform_i32((int)(threadIdx.x >> 6)), waves = (int)(blockDim.x >> 6);
   const int lane = threadIdx.x & 63, n = lane & 31, h = lane >> 5;
-  tile_dma(keys, tile_k_base(p, t, w), p.k_stride_token, w.nkeys, wave, waves, lane);
+  const TileShare s = tile_share(p, wave, waves);
+  u32x4 *keys = tile_area, *queries = tile_area + s.subs * kSubVec;
   const uint16_t* qbase = tile_q_base(p, t, w.seq);
+  tile_dma(keys, queries, p, tile_k_base(p, t, w), qbase, w.nkeys, s, wave, waves, lane);
   const int row_blocks = p.rows_pad / 32;
   float* outp = p.tile_parts + (((int64_t)t.layer * p.n_kv_heads + t.kv) * p.max_chunks + t.chunk) * p.rows_pad;
   bf16x8 qf[8];
-  frag_from_q(qf, p, qbase, wave * 32 + n, h);
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-  for (int rb = wave; rb < row_blocks; rb += waves) {
-    float ref = -INFINITY, z[2] = {0.0f, 0.0f};
+  if constexpr (!STAGED) {
+    frag_from_q(qf, p, qbase, wave * 32 + n, h);
+    tile_wait(0);
+    for (int rb = wave; rb < row_blocks; rb += waves) {
+      float ref = -INFINITY, z[2] = {0.0f, 0.0f};
 #pragma unroll 1
-    for (int half = 0; half < kTileSubs / 2; ++half) {
-      f32x16 a[2];
+      for (int half = 0; half < kTileKeys / 64; ++half) {
+        f32x16 a[2];
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        bf16x8 kf[8];
-        if (u == 1) __builtin_amdgcn_sched_barrier(0);
-        wave_load_frags<1>(kf, keys + (2 * half + u) * kSubVec, n, h);
-        a[u] = f32x16{0};
+        for (int u = 0; u < 2; ++u) {
+          bf16x8 kf[8];
+          if (u == 1) __builtin_amdgcn_sched_barrier(0);
+          wave_load_frags<1>(kf, keys + (2 * half + u) * kSubVec, n, h);
+          a[u] = f32x16{0};
 #pragma unroll
-        for (int s = 0; s < 8; ++s) a[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], qf[s], a[u], 0, 0, 0);
-      }
-      const int first = half * 64;
-      if (w.nkeys < first + 64) {
+          for (int e = 0; e < 8; ++e) a[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[e], qf[e], a[u], 0, 0, 0);
+        }
+        const int first = half * 64;
+        if (w.nkeys < first + 64) {
+#pragma unroll
+          for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+              if (u * 32 + acc_row(v, 0) >= w.nkeys - first - 4 * h) a[u][v] = -INFINITY;
+        }
+        float m = a[0][0];
 #pragma unroll
         for (int u = 0; u < 2; ++u)
 #pragma unroll
-          for (int v = 0; v < 16; ++v)
-            if (u * 32 + acc_row(v, 0) >= w.nkeys - first - 4 * h) a[u][v] = -INFINITY;
+          for (int v = 0; v < 16; ++v) m = fmaxf(m, a[u][v]);
+        const float mnew = fmaxf(ref, max_halves(m) * p.c);  // (finite: the first half has a key)
+        const float scale = __builtin_amdgcn_exp2f(ref - mnew);
+        z[0] *= scale;
+        z[1] *= scale;
+        ref = mnew;
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) z[v & 1] += __builtin_amdgcn_exp2f(fmaf(a[u][v], p.c, -mnew));
       }
-      float m = a[0][0];
+      if (rb + waves < row_blocks) frag_from_q(qf, p, qbase, (rb + waves) * 32 + n, h);
+      const float both = sum_halves(z[0] + z[1]);
+      if (h == 0) outp[rb * 32 + n] = both > 0.0f ? ref + log2f(both) : -INFINITY;
+    }
+    return;
+  }
+  for (int rb0 = 0; rb0 < row_blocks; rb0 += s.rbs) {  // (one trip up to eight row blocks)
+    const int rb = rb0 + s.rb;
+    const bool mine = s.part < s.parts && rb < row_blocks;
+    if (rb0 != 0 && mine) frag_from_q(qf, p, qbase, rb * 32 + n, h);
+    float ref = -INFINITY, z[2] = {0.0f, 0.0f};
+#pragma unroll 1
+    for (int sub0 = 0; sub0 < s.subs; sub0 += s.parts) {
+      if (rb0 == 0) tile_wait(s.subs - sub0 - s.parts);
+      if (rb0 == 0 && sub0 == 0 && mine) wave_load_frags<1>(qf, queries + s.rb * kSubVec, n, h);
+      const int first = (sub0 + s.part) * 32;
+      if (!mine || first >= w.nkeys) continue;
+      bf16x8 kf[8];
+      wave_load_frags<1>(kf, keys + (sub0 + s.part) * kSubVec, n, h);
+      f32x16 a = {0};
 #pragma unroll
-      for (int u = 0; u < 2; ++u)
+      for (int e = 0; e < 8; ++e) a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[e], qf[e], a, 0, 0, 0);
+      if (w.nkeys < first + 32) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) m = fmaxf(m, a[u][v]);
-      const float mnew = fmaxf(ref, fmaxf(m, xhalf(m)) * p.c);  // (finite: the first half has a key)
+        for (int v = 0; v < 16; ++v)
+          if (acc_row(v, 0) >= w.nkeys - first - 4 * h) a[v] = -INFINITY;
+      }
+      float m = a[0];
+#pragma unroll
+      for (int v = 1; v < 16; ++v) m = fmaxf(m, a[v]);
+      const float mnew = fmaxf(ref, max_halves(m) * p.c);  // (finite: the sub-block has a key)
       const float scale = __builtin_amdgcn_exp2f(ref - mnew);
       z[0] *= scale;
       z[1] *= scale;
       ref = mnew;
 #pragma unroll
-      for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) z[v & 1] += __builtin_amdgcn_exp2f(fmaf(a[u][v], p.c, -mnew));
+      for (int v = 0; v < 16; ++v) z[v & 1] += __builtin_amdgcn_exp2f(fmaf(a[v], p.c, -mnew));
     }
-    if (rb + waves < row_blocks) frag_from_q(qf, p, qbase, (rb + waves) * 32 + n, h);
-    const float zz = z[0] + z[1];
-    const float both = zz + xhalf(zz);
-    if (h == 0) outp[rb * 32 + n] = both > 0.0f ? ref + log2f(both) : -INFINITY;
+    const float both = sum_halves(z[0] + z[1]);
+    if (s.parts == 1) {
+      if (h == 0 && mine) outp[rb * 32 + n] = both > 0.0f ? ref + log2f(both) : -INFINITY;
+      continue;
+    }
+    // the parts of a row block in order (a part without keys has no sum); at most four row blocks: one trip
+    if (h == 0 && mine) sums[wave][n] = make_float2(ref, both);
+    __syncthreads();
+    if (threadIdx.x < s.rbs * 32) {
+      const int block = (int)threadIdx.x >> 5;
+      float m = -INFINITY, sum = 0.0f;
+      for (int i = 0; i < s.parts; ++i) m = fmaxf(m, sums[i * s.rbs + block][n].x);
+      for (int i = 0; i < s.parts; ++i) {
+        const float2 v = sums[i * s.rbs + block][n];
+        sum = fmaf(v.y, __builtin_amdgcn_exp2f(v.x - m), sum);
+      }
+      outp[threadIdx.x] = sum > 0.0f ? m + log2f(sum) : -INFINITY;
+    }
   }
 }
 
-// Pass 2: a lane's column sums over the rows of its wave, then over the waves in wave order through LDS.
+// Pass 2: a lane's column sums over the rows of its wave, then over the row blocks in order through LDS.
 // MERGE: lse2 is not read but formed from the partials of pass 1, by every workgroup for itself, with the arithmetic of
-// score_combine_kernel in its order (same bits).  That takes the workgroup 1 us while its keys are on the way; the combine
-// kernel and the boundary in front of it are 3 to 4 us of a call of 20.
+// score_combine_kernel in its order (same bits), instead of a launch of 3 to 4 us.
 constexpr int kMergeRuns = 4;                                    // runs of kCombineRun chunks a thread holds
-constexpr int kMergeMaxRows = 64 * kTileWaves;
+constexpr int kMergeMaxRows = kTileThreads;
 // How many chunks per sequence the threads of a workgroup can merge (0: more rows than threads).
-__host__ __device__ constexpr int tile_merge_chunks(int rows_pad, int threads) {
-  return rows_pad > threads ? 0 : threads / rows_pad * kMergeRuns * kCombineRun < kCombineClasses * kCombineRun
-                                      ? threads / rows_pad * kMergeRuns * kCombineRun
-                                      : kCombineClasses * kCombineRun;
+__host__ __device__ constexpr int tile_merge_chunks(int rows_pad) {
+  return rows_pad > kTileThreads ? 0 : kTileThreads / rows_pad * kMergeRuns * kCombineRun < kCombineClasses * kCombineRun
+                                           ? kTileThreads / rows_pad * kMergeRuns * kCombineRun
+                                           : kCombineClasses * kCombineRun;
 }
 template <bool MERGE>
-__global__ __launch_bounds__(64 * kTileWaves) __attribute__((amdgpu_waves_per_eu(4))) void score_tile_pass2_kernel(ScoreParams p) {
-  __shared__ u32x4 keys[kTileLds / 16];
-  __shared__ float cols[kTileWaves][kTileKeys];
+__global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(4))) void score_tile_pass2_kernel(ScoreParams p) {
+  extern __shared__ u32x4 tile_area[];
+  __shared__ float cols[kTileWaves][kTileMaxKeys];
   __shared__ __align__(16) float neg_lse[MERGE ? kMergeMaxRows : 4];
   __shared__ float merge_max[MERGE ? kMergeMaxRows : 1], merge_sum[MERGE ? kMergeMaxRows * kMergeRuns : 1];
+  touch_args<sizeof(ScoreParams)>();
   const Tile t = tile_of_workgroup(p, true);
   const Work w = locate_uniform(p, t.chunk);
   if (w.nkeys == 0) return;  // (the same for the whole workgroup)
-  const int wave = uniform_i32((int)(threadIdx.x >> 6)), waves = (int)(blockDim.x >> 6);
+  const int wave = uniform_i32((int)(threadIdx.x >> 6));
   const int lane = threadIdx.x & 63, n = lane & 31, h = lane >> 5;
-  tile_dma(keys, tile_k_base(p, t, w), p.k_stride_token, w.nkeys, wave, waves, lane);
+  const int waves = (int)(blockDim.x >> 6);
+  const TileShare s = tile_share(p, wave, waves);
+  u32x4 *keys = tile_area, *queries = tile_area + s.subs * kSubVec;
   const uint16_t* qbase = tile_q_base(p, t, w.seq);
   const float* lse =
       p.lse2 + (((int64_t)t.layer * p.batch + w.seq) * p.n_q_heads + (int64_t)t.kv * p.group) * p.n_pseudo;
   const int row_blocks = p.rows_pad / 32;
-  bf16x8 qf[8];
-  float off[16];
-  frag_from_q(qf, p, qbase, wave * 32 + n, h);
+  // thread = (row, share): runs share, share + shares, ... of the sequence's chunks
+  const int share = MERGE ? quotient((int)threadIdx.x, p.inv_rows_pad) : 0, row = MERGE ? (int)threadIdx.x - share * p.rows_pad : 0;
+  const int shares = quotient(kTileThreads, p.inv_rows_pad);
+  const int chunks = chunks_of_length(p, w.seq_len), runs = (chunks + kCombineRun - 1) / kCombineRun;
+  float part[kMergeRuns][kCombineRun];
   if (MERGE) {
-    // thread = (row, share): runs share, share + shares, ... of the sequence's chunks
-    const int row = (int)threadIdx.x % p.rows_pad, share = (int)threadIdx.x / p.rows_pad;
-    const int shares = (int)blockDim.x / p.rows_pad;
-    const int chunks = (w.seq_len + p.chunk_keys - 1) / p.chunk_keys, runs = (chunks + kCombineRun - 1) / kCombineRun;
-    const int first = t.chunk - w.key0 / p.chunk_keys;  // the sequence's first chunk
-    const float* src = p.tile_parts + (((int64_t)t.layer * p.n_kv_heads + t.kv) * p.max_chunks + first) * p.rows_pad + row;
-    float part[kMergeRuns][kCombineRun], m = -INFINITY;
+    const int first = t.chunk - (w.key0 >> p.chunk_shift);  // the sequence's first chunk
+    const float* src = uniform_ptr(p.tile_parts + (((int64_t)t.layer * p.n_kv_heads + t.kv) * p.max_chunks + first) * p.rows_pad);
 #pragma unroll
     for (int k = 0; k < kMergeRuns; ++k) {
-      const int run = share + k * shares;
+      if (k * shares < runs) {
 #pragma unroll
-      for (int i = 0; i < kCombineRun; ++i) {
-        const int c = run * kCombineRun + i;
-        part[k][i] = -INFINITY;
-        if (share < shares && c < chunks) part[k][i] = src[(int64_t)c * p.rows_pad];
+        for (int i = 0; i < kCombineRun; ++i) {
+          const int c = (share + k * shares) * kCombineRun + i;
+          part[k][i] = src[(unsigned)((c < chunks ? c : chunks - 1) * p.rows_pad + row)];
+        }
       }
+    }
+  }
+  tile_dma(keys, queries, p, tile_k_base(p, t, w), qbase, w.nkeys, s, wave, waves, lane);
+  if (MERGE) {
+    float m = -INFINITY;
 #pragma unroll
-      for (int i = 0; i < kCombineRun; ++i) m = fmaxf(m, part[k][i]);
+    for (int k = 0; k < kMergeRuns; ++k) {
+      if (k * shares < runs) {
+#pragma unroll
+        for (int i = 0; i < kCombineRun; ++i) {
+          part[k][i] = (share + k * shares) * kCombineRun + i < chunks ? part[k][i] : -INFINITY;
+          m = fmaxf(m, part[k][i]);
+        }
+      }
     }
     merge_max[threadIdx.x] = m;
     __syncthreads();
@@ -1305,10 +1426,12 @@ __global__ __launch_bounds__(64 * kTileWaves) __attribute__((amdgpu_waves_per_eu
 #pragma unroll
       for (int k = 0; k < kMergeRuns; ++k) {
         const int run = share + k * shares;
-        float sum = 0.0f;
+        if (run < runs) {
+          float sum = 0.0f;
 #pragma unroll
-        for (int i = 0; i < kCombineRun; ++i) sum += exp2f(part[k][i] - m);
-        if (run < runs) merge_sum[run * p.rows_pad + row] = sum;
+          for (int i = 0; i < kCombineRun; ++i) sum += exp2f(part[k][i] - m);
+          merge_sum[run * p.rows_pad + row] = sum;
+        }
       }
     }
     __syncthreads();
@@ -1320,8 +1443,16 @@ __global__ __launch_bounds__(64 * kTileWaves) __attribute__((amdgpu_waves_per_eu
     // (visible to all after the barrier below)
   }
   const bool quads = (reinterpret_cast<uintptr_t>(lse) & 15) == 0 && (p.rows & 3) == 0;
-  // -lse2 of the rows this lane's accumulator registers hold; -inf for padding rows, which then add 0
-  auto load_off = [&](int rb) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  for (int rb0 = 0; rb0 < row_blocks; rb0 += s.rbs) {  // (one trip up to eight row blocks)
+    const int rb = rb0 + s.rb;
+    if (s.part >= s.parts || rb >= row_blocks) continue;
+    bf16x8 qf[8];
+    if (rb0 != 0 || !p.stage_q) frag_from_q(qf, p, qbase, rb * 32 + n, h);
+    else wave_load_frags<1>(qf, queries + s.rb * kSubVec, n, h);
+    // -lse2 of the rows this lane's accumulator registers hold; -inf for padding rows, which then add 0
+    float off[16];
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
       const int row = rb * 32 + acc_row(4 * b, h);
@@ -1343,34 +1474,27 @@ __global__ __launch_bounds__(64 * kTileWaves) __attribute__((amdgpu_waves_per_eu
         for (int e = 0; e < 4; ++e) off[4 * b + e] = row + e < p.rows ? -lse[row + e] : -INFINITY;
       }
     }
-  };
-  if (!MERGE) load_off(wave);
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-  for (int rb = wave; rb < row_blocks; rb += waves) {
-    if (rb != wave) frag_from_q(qf, p, qbase, rb * 32 + n, h);
-    if (MERGE || rb != wave) load_off(rb);
 #pragma unroll 1
-    for (int sub = 0; sub < kTileSubs; ++sub) {
+    for (int sub = s.part; sub < s.subs; sub += s.parts) {
       bf16x8 kf[8];
       wave_load_frags<1>(kf, keys + sub * kSubVec, n, h);
       f32x16 a = {0};
 #pragma unroll
-      for (int s = 0; s < 8; ++s) a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[s], kf[s], a, 0, 0, 0);
+      for (int e = 0; e < 8; ++e) a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[e], kf[e], a, 0, 0, 0);
       float z[2] = {0.0f, 0.0f};
 #pragma unroll
       for (int v = 0; v < 16; ++v) z[v & 1] += __builtin_amdgcn_exp2f(fmaf(a[v], p.c, off[v]));
-      float* col = &cols[wave][sub * 32 + n];
+      float* col = &cols[s.rb][sub * 32 + n];
       const float both = sum_halves(z[0] + z[1]);
-      if (h == 0) *col = rb == wave ? both : *col + both;
+      if (h == 0) *col = rb0 == 0 ? both : *col + both;
     }
   }
   __syncthreads();
   float* out = p.scores + ((int64_t)t.layer * p.n_kv_heads + t.kv) * p.total_tokens + w.tok0;
   for (int key = threadIdx.x; key < w.nkeys; key += (int)blockDim.x) {
-    float s = cols[0][key];
-    for (int i = 1; i < waves && i < row_blocks; ++i) s += cols[i][key];
-    out[key] = s;
+    float sum = cols[0][key];
+    for (int i = 1; i < s.rbs; ++i) sum += cols[i][key];
+    out[key] = sum;
   }
 }
 
@@ -1438,6 +1562,13 @@ int fill_params(const dapq_shape* s, const ScorePlan& plan, ScoreParams* p) {
   p->wg_groups = 1;
   p->tile_parts = nullptr;
   p->c = s->scale * 1.4426950408889634f;
+  p->seq_len = (int32_t)(s->total_tokens / s->batch);
+  p->chunks_per_seq = (p->seq_len + plan.chunk_keys - 1) / plan.chunk_keys;
+  p->chunk_shift = __builtin_ctz((unsigned)plan.chunk_keys);
+  p->stage_q = plan.tile && plan.stage_q;
+  p->inv_n_pseudo = 1.0f / (float)s->n_pseudo;
+  p->inv_kv_heads = 1.0f / (float)s->n_kv_heads;
+  p->inv_rows_pad = 1.0f / (float)plan.rows_pad;
   return DAPQ_OK;
 }
 
@@ -1461,15 +1592,22 @@ int launch_chunk_prefix(const dapq_shape* s, const ScorePlan& plan, const ScoreP
   return DAPQ_OK;
 }
 
-// The grid of the tile kernels, and the waves of their workgroups: one per row block, at most eight, at least four (with
-// fewer than four row blocks the others only bring in keys: a lone wave issues the 32 transfers of a tile one by one).
 dim3 tile_grid(const dapq_shape* s, const ScorePlan& plan) {
   return dim3((unsigned)(plan.max_chunks * s->n_kv_heads), 1u, (unsigned)s->n_layers);
 }
+// Eight waves where the queries are staged; else one per row block, at most eight, at least four (with fewer than four row
+// blocks the others only bring in keys: a lone wave issues the 32 transfers of a tile one by one).
 dim3 tile_threads(const ScorePlan& plan) {
-  const int row_blocks = plan.rows_pad / 32;
-  return dim3(64u * (unsigned)(row_blocks < 4 ? 4 : (row_blocks < kTileWaves ? row_blocks : kTileWaves)));
+  const int waves = plan.stage_q || plan.row_blocks > kTileWaves ? kTileWaves : (plan.row_blocks < 4 ? 4 : plan.row_blocks);
+  return dim3(64u * (unsigned)waves);
 }
+// (the whole dynamic limit once: see set_max_dynamic_lds)
+#define DAPQ_LAUNCH_TILE(kernel)                                                                                 \
+  do {                                                                                                           \
+    if ((rc = set_lds(kernel, tile_lds(kTileMaxKeys, kTileWaves, true))) != DAPQ_OK) return rc;                        \
+    hipLaunchKernelGGL(kernel, tile_grid(s, plan), tile_threads(plan), tile_lds(plan.chunk_keys, plan.row_blocks, plan.stage_q), stream, p); \
+    DAPQ_HIP_LAUNCH_CHECK(#kernel);                                                                              \
+  } while (0)
 
 int launch_wave_pass1(const dapq_shape* s, const ScorePlan& plan, ScoreParams p, hipStream_t stream) {
   int rc = DAPQ_OK;
@@ -1501,8 +1639,8 @@ int launch_stats(const dapq_shape* s, const ScorePlan& plan, ScoreParams p, hipS
   int rc = launch_chunk_prefix(s, plan, p, stream);
   if (rc != DAPQ_OK) return rc;
   if (plan.tile) {
-    hipLaunchKernelGGL(score_tile_pass1_kernel, tile_grid(s, plan), tile_threads(plan), 0, stream, p);
-    DAPQ_HIP_LAUNCH_CHECK("score_tile_pass1_kernel");
+    if (plan.stage_q) DAPQ_LAUNCH_TILE(score_tile_pass1_kernel<true>);
+    else DAPQ_LAUNCH_TILE(score_tile_pass1_kernel<false>);
     if (p.lse2 == nullptr) return DAPQ_OK;  // pass 2 merges the partials itself
   } else {
     if ((rc = launch_wave_pass1(s, plan, p, stream)) != DAPQ_OK) return rc;
@@ -1526,9 +1664,8 @@ int launch_accumulate(const dapq_shape* s, const ScorePlan& plan, ScoreParams p,
   int rc = launch_chunk_prefix(s, plan, p, stream);  // (pass 2 can be called on its own: it rebuilds the prefix it walks)
   if (rc != DAPQ_OK) return rc;
   if (plan.tile) {
-    if (p.lse2 == nullptr) hipLaunchKernelGGL(score_tile_pass2_kernel<true>, tile_grid(s, plan), tile_threads(plan), 0, stream, p);
-    else hipLaunchKernelGGL(score_tile_pass2_kernel<false>, tile_grid(s, plan), tile_threads(plan), 0, stream, p);
-    DAPQ_HIP_LAUNCH_CHECK("score_tile_pass2_kernel");
+    if (p.lse2 == nullptr) DAPQ_LAUNCH_TILE(score_tile_pass2_kernel<true>);
+    else DAPQ_LAUNCH_TILE(score_tile_pass2_kernel<false>);
     return DAPQ_OK;
   }
   const GroupShape gs = group_shape(s, plan);
@@ -1598,9 +1735,9 @@ int launch_fused(const dapq_shape* s, const ScorePlan& plan, ScoreParams p, hipS
 // there is a compute unit for every workgroup (4096 keys of one layer: 18.7 -> 17.6 us; 8191, two workgroups to a compute
 // unit: 25.5 -> 27.2).
 bool tile_merges(const dapq_shape* s, const ScorePlan& plan) {
-  if (!plan.tile || plan.max_chunks * s->n_kv_heads * s->n_layers > simd_count() / 4) return false;
+  if (!plan.tile || !plan.stage_q || plan.max_chunks * s->n_kv_heads * s->n_layers > simd_count() / 4) return false;
   const int64_t longest = s->cu_seqlens == nullptr ? s->total_tokens / s->batch : s->total_tokens;
-  return (longest + plan.chunk_keys - 1) / plan.chunk_keys <= tile_merge_chunks(plan.rows_pad, (int)tile_threads(plan).x);
+  return (longest + plan.chunk_keys - 1) / plan.chunk_keys <= tile_merge_chunks(plan.rows_pad);
 }
 
 int check_workspace(void* workspace, size_t workspace_bytes, const ScorePlan& plan) {

@@ -245,6 +245,25 @@ def test_scores_of_small_calls(H, lens, rows):
     assert err.max() < 2e-4
 
 
+# tiles of 128 and 256 keys, the last ones short, and of 128 keys whose queries do not go through LDS (40000); one to five row
+# blocks, shared out to eight waves in one to eight parts, and nine, in two trips
+@pytest.mark.parametrize("rows", [32, 64, 96, 128, 160, 257])
+@pytest.mark.parametrize("lens", [[9000], [20001], [40000], [3000, 0, 77, 2100]], ids=lambda lens: f"{len(lens)}x{max(lens)}")
+def test_tiles_of_small_calls(H, lens, rows):
+    """The oracle's scores within 1e-3 and its normalisers within 2e-4 in the log2 domain, and the bits of dapq_score from the two
+    separate entry points, with a key hundreds of binades above the others."""
+    announce(f"tiles: {lens} rows={rows}")
+    q, k, v, cu = problem_bits(rows, 1, lens, 2, 2, rows)
+    b = int(np.argmax(lens))
+    k[0, int(cu[b]) + lens[b] // 2, 1] = W.to_bf16_bits(30.0 * O.bf16_bits_to_f64(q[0, b, 1, 0]))
+    prob = H.Problem(q, k, v, 2, cu if len(lens) > 1 else None, "thd")
+    S = prob.score()
+    assert torch.equal(S, prob.score_split())
+    H.assert_scores_close(S.cpu().numpy(), O.score(q, k, 2, cu), f"{lens} rows={rows}")
+    live = [i for i, n in enumerate(lens) if n]
+    assert np.abs(prob.stats().cpu().numpy()[:, live] - oracle_lse2(q, k, 2, cu)[:, live]).max() < 2e-4
+
+
 @pytest.mark.parametrize("batch", [2, 64, 65])
 def test_small_ragged_calls_write_no_chunk_prefix(H, batch):
     """Up to 64 sequences every wave of the tile form finds its chunk by itself: neither pass writes the prefix of the chunk
