@@ -53,7 +53,7 @@ struct DecodeParams {
   const uint16_t* v_cache;
   const int32_t* count;     // [layer][seq][Hkv]
   float* out;               // [layer][seq][Hq][d]
-  int32_t n_q_heads, n_kv_heads, budget;
+  int32_t group, budget;    // group: query heads per KV head
   float c;                  // scale * log2(e)
 };
 
@@ -115,7 +115,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void decode_attention_kernel(DecodeP
   constexpr int kWaveBytes = decode_wave_bytes(HT);
   char* ring = lds + wave * kWaveBytes;
   const int slice = blockIdx.y;
-  const int g = p.n_q_heads / p.n_kv_heads;
+  const int g = p.group;
   const int64_t head = blockIdx.x;  // (layer * batch + seq) * Hkv + kv
   DecodeSource src;
   src.k = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p.k_cache + head * p.budget * kHeadDim), 0,
@@ -334,7 +334,7 @@ int launch_decode(int64_t heads, const DecodeParams& p, hipStream_t stream) {
   if (rc != DAPQ_OK) return rc;
   // a launch holds fewer than 2^32 threads along an axis: 2^24 heads and more go in several
   constexpr int64_t kMostHeads = (int64_t)1 << 22;
-  const int64_t q_step = (int64_t)(p.n_q_heads / p.n_kv_heads) * kHeadDim, cache_step = (int64_t)p.budget * kHeadDim;
+  const int64_t q_step = (int64_t)p.group * kHeadDim, cache_step = (int64_t)p.budget * kHeadDim;
   for (int64_t first = 0; first < heads; first += kMostHeads) {
     DecodeParams part = p;
     part.q += first * q_step;
@@ -389,11 +389,10 @@ extern "C" DAPQ_API int dapq_decode_attention(const dapq_shape* shape, const voi
   p.v_cache = static_cast<const uint16_t*>(v_cache);
   p.count = count;
   p.out = out;
-  p.n_q_heads = shape->n_q_heads;
-  p.n_kv_heads = shape->n_kv_heads;
+  p.group = shape->n_q_heads / shape->n_kv_heads;
   p.budget = budget;
   p.c = shape->scale * 1.4426950408889634f;
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int64_t heads = (int64_t)shape->n_layers * shape->batch * shape->n_kv_heads;
-  return p.n_q_heads / p.n_kv_heads <= 4 ? launch_decode_slices<1>(heads, p, st) : launch_decode_slices<2>(heads, p, st);
+  return p.group <= 4 ? launch_decode_slices<1>(heads, p, st) : launch_decode_slices<2>(heads, p, st);
 }

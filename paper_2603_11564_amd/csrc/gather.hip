@@ -6,6 +6,7 @@
 // read and written in full cache lines; a workgroup of 256 threads moves 64 rows of K or of V, four
 // per 16-lane group, with the four loads in flight together.
 #include "dapq_internal.h"
+#include "kernel_args.h"
 
 namespace dapq {
 namespace {
@@ -20,42 +21,44 @@ struct GatherParams {
   uint16_t* v_out;
   int64_t k_stride_layer, k_stride_seq, k_stride_head, k_stride_token;
   int64_t v_stride_layer, v_stride_seq, v_stride_head, v_stride_token;
-  int64_t total_tokens;
-  int32_t batch, n_kv_heads, budget;
+  int32_t batch, n_kv_heads, budget, seq_len;  // seq_len: dense batches
+  float inv_kv_heads, inv_batch;
 };
 
 constexpr int kGatherRowsPerGroup = 4;  // rows in flight per 16-lane group
 constexpr int kGatherRowsPerBlock = 16 * kGatherRowsPerGroup;
 
 __global__ __launch_bounds__(256) void gather_kernel(GatherParams p) {
+  touch_args<sizeof(GatherParams)>();
   const int ch = threadIdx.x & 15;
   const int slot0 = blockIdx.x * kGatherRowsPerBlock + (threadIdx.x >> 4);  // this group's slots: slot0 + 16*r
-  const int64_t head = blockIdx.y;  // (layer * batch + seq) * Hkv + kv
+  const int head = (int)blockIdx.y;  // (layer * batch + seq) * Hkv + kv
   const bool is_v = blockIdx.z == 1;
   const int n = p.count[head];
-  if (slot0 >= n) return;
-  const int kv = (int)(head % p.n_kv_heads);
-  const int seq = (int)((head / p.n_kv_heads) % p.batch);
-  const int layer = (int)(head / ((int64_t)p.n_kv_heads * p.batch));
+  // (a launch has at most 65535 heads)
+  const int rest = __builtin_amdgcn_readfirstlane(quotient(head, p.inv_kv_heads)), kv = head - rest * p.n_kv_heads;
+  const int layer = __builtin_amdgcn_readfirstlane(quotient(rest, p.inv_batch)), seq = rest - layer * p.batch;
   int64_t start;
   int L;
   if (p.cu_seqlens == nullptr) {
-    L = (int)(p.total_tokens / p.batch);
+    L = p.seq_len;
     start = (int64_t)seq * L;
   } else {
     start = p.cu_seqlens[seq];
     L = p.cu_seqlens[seq + 1] - (int)start;
   }
+  if (slot0 >= n) return;
   const uint16_t* base = is_v ? p.v + layer * p.v_stride_layer + seq * p.v_stride_seq + kv * p.v_stride_head
                               : p.k + layer * p.k_stride_layer + seq * p.k_stride_seq + kv * p.k_stride_head;
   const int64_t stride_token = is_v ? p.v_stride_token : p.k_stride_token;
-  uint16_t* dst = (is_v ? p.v_out : p.k_out) + head * p.budget * kHeadDim;
+  uint16_t* dst = (is_v ? p.v_out : p.k_out) + (int64_t)head * p.budget * kHeadDim;
+  const int32_t* idx = p.idx + (int64_t)head * p.budget;
   // all index loads first, then all row loads, then the stores: four rows in flight per group
   int j[kGatherRowsPerGroup];
 #pragma unroll
   for (int r = 0; r < kGatherRowsPerGroup; ++r) {
     const int slot = slot0 + 16 * r;
-    j[r] = slot < n ? p.idx[head * p.budget + slot] : -1;
+    j[r] = slot < n ? idx[slot] : -1;
   }
   uint4 row[kGatherRowsPerGroup];
 #pragma unroll
@@ -101,7 +104,9 @@ extern "C" DAPQ_API int dapq_gather(const dapq_shape* shape, const void* k, cons
   p.k_stride_head = shape->k_stride_head; p.k_stride_token = shape->k_stride_token;
   p.v_stride_layer = shape->v_stride_layer; p.v_stride_seq = shape->v_stride_seq;
   p.v_stride_head = shape->v_stride_head; p.v_stride_token = shape->v_stride_token;
-  p.total_tokens = shape->total_tokens;
+  p.seq_len = (int32_t)(shape->total_tokens / shape->batch);
+  p.inv_kv_heads = 1.0f / (float)shape->n_kv_heads;
+  p.inv_batch = 1.0f / (float)shape->batch;
   p.batch = shape->batch;
   p.n_kv_heads = shape->n_kv_heads;
   p.budget = budget;

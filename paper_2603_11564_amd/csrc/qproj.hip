@@ -30,6 +30,7 @@
 #include <type_traits>
 
 #include "dapq_internal.h"
+#include "kernel_args.h"
 #include "rope_math.h"
 
 namespace dapq {
@@ -52,6 +53,9 @@ struct QprojParams {
   int32_t n_layers, rows, hidden, n_features, head_dim;
   int32_t tiles_f, sweeps;
   int32_t k_splits, kb_per_split;  // hidden blocks are dealt to k_splits waves per tile; > 1 writes fp32 partial sums
+  float inv_sweeps, inv_tiles_f, inv_splits;
+  float inv_half, inv_heads;       // of head_dim / 2 and n_features / head_dim
+  int32_t heads;
   float* partial;                  // [k_splits][n_layers][sweeps * 32 MB rows][tiles_f * 32 FT features]
 };
 
@@ -95,6 +99,7 @@ __global__ __launch_bounds__(64) void qproj_wave_kernel(QprojParams p) {
   u32x4* const wring = lds;
   u32x4* const xbuf = lds + kRing * kTileVec;
 
+  touch_args<sizeof(QprojParams)>();
   const int lane = threadIdx.x, n = lane & 31, h = lane >> 5;
   // consecutive work items (all tiles of a layer, layer after layer) go to the same XCD when the grid
   // allows it: the waves that share a layer's x rows then share an L2
@@ -104,9 +109,9 @@ __global__ __launch_bounds__(64) void qproj_wave_kernel(QprojParams p) {
   id = qp_uniform(id);
   // the row sweeps of one feature tile are neighbours: they run at the same time and read the tile's weights
   // from HBM once
-  const int sweep = qp_uniform(id % p.sweeps), rest = id / p.sweeps;
-  const int tile = qp_uniform(rest % p.tiles_f), rest2 = rest / p.tiles_f;
-  const int split = qp_uniform(rest2 % p.k_splits), layer = qp_uniform(rest2 / p.k_splits);
+  const int rest = uniform_quotient(id, p.sweeps, p.inv_sweeps), sweep = id - rest * p.sweeps;
+  const int rest2 = uniform_quotient(rest, p.tiles_f, p.inv_tiles_f), tile = rest - rest2 * p.tiles_f;
+  const int layer = uniform_quotient(rest2, p.k_splits, p.inv_splits), split = rest2 - layer * p.k_splits;
   const int f0 = tile * (32 * FT), m0 = sweep * (32 * MB);
   // this wave's hidden blocks [kb0, n_kb)
   const int kb0 = split * p.kb_per_split;
@@ -302,11 +307,12 @@ __global__ void qproj_reduce_kernel(QprojParams p, int rows_pad, int feat_pad) {
 template <int SPLITS>
 __global__ __launch_bounds__(256) void qproj_reduce_rope_kernel(QprojParams p, int rows_pad, int feat_pad, const int32_t* positions,
                                                                 double neg_log2_theta_2_over_d, int pairing) {
-  const int half = p.head_dim / 2, heads = p.n_features / p.head_dim;
+  touch_args<sizeof(QprojParams) + 32>();
+  const int half = p.head_dim >> 1;
   const int gid = blockIdx.x * 256 + threadIdx.x;
   if (gid >= p.rows * half) return;
-  const int row = gid / half, c = gid - row * half;
-  const int layer = (int)blockIdx.y / heads, head = (int)blockIdx.y - layer * heads;
+  const int row = quotient(gid, p.inv_half), c = gid - row * half;  // (a split call has fewer than 2^21 channel pairs and 2^13 heads)
+  const int layer = qp_uniform(quotient((int)blockIdx.y, p.inv_heads)), head = (int)blockIdx.y - layer * p.heads;
   const int ia = pairing == 0 ? c : 2 * c, ib = pairing == 0 ? c + half : 2 * c + 1;
   const int64_t plane = (int64_t)p.n_layers * rows_pad * feat_pad;
   const float* src = p.partial + ((int64_t)layer * rows_pad + row) * feat_pad + (int64_t)head * p.head_dim;
@@ -452,6 +458,12 @@ extern "C" DAPQ_API int dapq_pseudo_queries(const dapq_qproj* desc, const void* 
   p.sweeps = pl.sweeps;
   p.k_splits = pl.k_splits;
   p.kb_per_split = pl.kb_per_split;
+  p.inv_sweeps = 1.0f / (float)pl.sweeps;
+  p.inv_tiles_f = 1.0f / (float)pl.tiles_f;
+  p.inv_splits = 1.0f / (float)pl.k_splits;
+  p.heads = s.n_q_heads;
+  p.inv_half = s.head_dim >= 2 ? 1.0f / (float)(s.head_dim / 2) : 1.0f;
+  p.inv_heads = 1.0f / (float)s.n_q_heads;
   p.partial = pl.k_splits > 1 ? static_cast<float*>(workspace) : nullptr;
   DAPQ_REQUIRE((int64_t)p.tiles_f * p.sweeps * p.k_splits * s.n_layers < ((int64_t)1 << 31), DAPQ_ERR_UNSUPPORTED,
                "too many tiles");

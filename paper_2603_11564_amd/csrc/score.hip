@@ -71,16 +71,13 @@ struct ScoreParams {
   int32_t segments;           // ragged batches in the wave form: segments a head is cut into (chunk_keys is a sub-block then)
   int32_t wg_groups;          // row groups that sit side by side in a workgroup (dense launches; 1, 2 or 4)
   float c;  // scale * log2(e)
-  // What every workgroup would divide for before it can ask for its first key (a division is twenty instructions in a row, one
-  // of 64 bits a hundred; a pass of a small call lasts 10 000 clocks):
+  // What every workgroup would divide for before it can ask for its first key:
   int32_t seq_len, chunks_per_seq;  // dense batches
   int32_t chunk_shift;              // log2(chunk_keys)
   int32_t stage_q;                  // tile form: the queries go through LDS too
-  float inv_n_pseudo, inv_kv_heads, inv_rows_pad;  // tile form
+  float inv_n_pseudo, inv_kv_heads, inv_rows_pad;
 };
 
-// a / b for inv = 1 / b, a < 2^21: (a + 1/2) * inv is off by less than 2^-2 / b, and at least half of 1 / b away from a whole number.
-__device__ __forceinline__ int quotient(int a, float inv) { return (int)(((float)a + 0.5f) * inv); }
 
 constexpr int kSubBytes = 32 * kHeadDim * 2;          // one 32-key sub-block
 
@@ -247,7 +244,7 @@ __device__ __forceinline__ int lds_chunk_index(int key, int ch) { return key * 1
 __device__ __forceinline__ void frag_from_q(bf16x8 (&f)[8], const ScoreParams& p, const uint16_t* qbase, int row,
                                             int h) {
   const int rc = row < p.rows ? row : p.rows - 1;  // padding rows repeat the last row; their results are dropped
-  const int head = rc / p.n_pseudo, i = rc - head * p.n_pseudo;
+  const int head = quotient(rc, p.inv_n_pseudo), i = rc - head * p.n_pseudo;
   const uint16_t* src = qbase + (int64_t)head * p.q_stride_head + (int64_t)i * p.q_stride_row;
 #pragma unroll
   for (int s = 0; s < 8; ++s) f[s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(src + (2 * s + h) * 8));
@@ -331,12 +328,13 @@ __global__ void score_chunk_prefix_kernel(const int32_t* cu_seqlens, int32_t* cu
 // summed in run order, chunk by chunk, and the classes are added in class order (up to kCombineRun chunks: plain chunk
 // order, which is what score_fused_kernel does).
 constexpr int kCombineRun = 8, kCombineClasses = 16;
-__global__ __launch_bounds__(64 * kCombineClasses) void score_combine_kernel(ScoreParams p, int row_tiles, int first_seq) {
+__global__ __launch_bounds__(64 * kCombineClasses) void score_combine_kernel(ScoreParams p, int row_tiles, float inv_row_tiles, int first_seq) {
   __shared__ float lds_max[kCombineClasses][64], lds_sum[kCombineClasses][64];
   const int lane = threadIdx.x & 63, wave = uniform_i32((int)(threadIdx.x >> 6)), waves = (int)(blockDim.x >> 6);
-  const int seq = uniform_i32((int)(blockIdx.x / row_tiles)), row = (int)(blockIdx.x - seq * row_tiles) * 64 + lane;
+  touch_args<sizeof(ScoreParams) + 12>();
+  const int seq = uniform_i32(quotient((int)blockIdx.x, inv_row_tiles)), row = (int)(blockIdx.x - seq * row_tiles) * 64 + lane;
   const int b = first_seq + seq;
-  const int layer = (int)(blockIdx.y / p.n_kv_heads), kv = (int)(blockIdx.y - layer * p.n_kv_heads);
+  const int layer = uniform_i32(quotient((int)blockIdx.y, p.inv_kv_heads)), kv = (int)blockIdx.y - layer * p.n_kv_heads;
   int c0, c1, total = 0;
   if (p.cu_seqlens == nullptr) {
     c0 = b * p.chunks_per_seq;
@@ -807,8 +805,7 @@ __device__ __forceinline__ void pass1_chunk(const ScoreParams& p, u32x4* ring, c
                                             bf16x8 (&qf)[NRB][8], int lane) {
   unsigned voff[4];
   sub_dma_lane_offsets(voff, p.k_stride_token, lane);
-  // (the division runs on the vector ALU: bring the quotient back to a scalar register)
-  const int layer = uniform_i32(head / p.n_kv_heads), kv = head - layer * p.n_kv_heads;
+  const int layer = uniform_i32(quotient(head, p.inv_kv_heads)), kv = head - layer * p.n_kv_heads;
   const uint16_t* kbase = uniform_ptr(p.k + (int64_t)layer * p.k_stride_layer + (int64_t)w.seq * p.k_stride_seq +
                                       (int64_t)kv * p.k_stride_head + w.tok0 * p.k_stride_token);
   const int gbase = group * (NRB * 32);  // first row of this wave's row group
@@ -829,7 +826,7 @@ __device__ __forceinline__ void pass1_segment(const ScoreParams& p, u32x4* ring,
   if (at.left == 0) return;
   unsigned voff[4];
   sub_dma_lane_offsets(voff, p.k_stride_token, lane);
-  const int layer = uniform_i32(head / p.n_kv_heads), kv = head - layer * p.n_kv_heads;
+  const int layer = uniform_i32(quotient(head, p.inv_kv_heads)), kv = head - layer * p.n_kv_heads;
   const int gbase = group * (NRB * 32);
   KeyStream<false, true> keys = {p, uniform_ptr(p.k + (int64_t)layer * p.k_stride_layer + (int64_t)kv * p.k_stride_head),
                                  nullptr, 0, at.sub, at.seq, at.left};
@@ -950,8 +947,7 @@ __device__ __forceinline__ void pass2_chunk(const ScoreParams& p, u32x4* ring, c
                                             bf16x8 (&qf)[NRB][8], float (&off2)[NRB][16], int lane) {
   unsigned voff[4];
   sub_dma_lane_offsets(voff, p.k_stride_token, lane);
-  // (the division runs on the vector ALU: bring the quotient back to a scalar register)
-  const int layer = uniform_i32(head / p.n_kv_heads), kv = head - layer * p.n_kv_heads;
+  const int layer = uniform_i32(quotient(head, p.inv_kv_heads)), kv = head - layer * p.n_kv_heads;
   const uint16_t* kbase = uniform_ptr(p.k + (int64_t)layer * p.k_stride_layer + (int64_t)w.seq * p.k_stride_seq +
                                       (int64_t)kv * p.k_stride_head + w.tok0 * p.k_stride_token);
   float* out = const_cast<float*>(uniform_ptr(wave_plane(p, head, group) + w.tok0));
@@ -973,7 +969,7 @@ __device__ __forceinline__ void pass2_segment(const ScoreParams& p, u32x4* ring,
   if (at.left == 0) return;
   unsigned voff[4];
   sub_dma_lane_offsets(voff, p.k_stride_token, lane);
-  const int layer = uniform_i32(head / p.n_kv_heads), kv = head - layer * p.n_kv_heads;
+  const int layer = uniform_i32(quotient(head, p.inv_kv_heads)), kv = head - layer * p.n_kv_heads;
   KeyStream<true, true> keys = {p, uniform_ptr(p.k + (int64_t)layer * p.k_stride_layer + (int64_t)kv * p.k_stride_head),
                                 nullptr, 0, at.sub, at.seq, at.left};
   keys.enter(seq_range(p, at.seq));
@@ -1094,7 +1090,7 @@ template <int NRB>
 __global__ __launch_bounds__(64, 1) void score_wave_pseudo_kernel(ScoreParams p, PseudoParams pp) {
   extern __shared__ u32x4 ring[];
   const int seq = blockIdx.x;
-  const int layer = uniform_i32(blockIdx.z / p.n_kv_heads), kv = blockIdx.z - layer * p.n_kv_heads;
+  const int layer = uniform_i32(quotient((int)blockIdx.z, p.inv_kv_heads)), kv = (int)blockIdx.z - layer * p.n_kv_heads;
   const int lane = threadIdx.x, n = lane & 31, h = lane >> 5;
   const uint16_t* qbase = p.q + (int64_t)layer * p.q_stride_layer + (int64_t)seq * p.q_stride_seq +
                           (int64_t)kv * p.group * p.q_stride_head;
@@ -1111,7 +1107,8 @@ __global__ __launch_bounds__(64, 1) void score_wave_pseudo_kernel(ScoreParams p,
   for (int rb = 0; rb < NRB; ++rb) {
     frag_from_q(qf[rb], p, qbase, gbase + rb * 32 + n, h);
     const int row = gbase + rb * 32 + n;
-    last_key[rb] = (row < p.rows ? row : p.rows - 1) % p.n_pseudo;
+    const int rc = row < p.rows ? row : p.rows - 1;
+    last_key[rb] = rc - quotient(rc, p.inv_n_pseudo) * p.n_pseudo;
     ref[rb] = -INFINITY;
     z[rb] = 0.0f;
   }
@@ -1650,11 +1647,12 @@ int launch_stats(const dapq_shape* s, const ScorePlan& plan, ScoreParams p, hipS
   int64_t combine_waves = (chunks_per_seq + kCombineRun - 1) / kCombineRun;
   combine_waves = combine_waves < 1 ? 1 : (combine_waves > kCombineClasses ? kCombineClasses : combine_waves);
   // (a launch holds fewer than 2^32 threads along an axis)
-  const int64_t seqs_per_launch = ((int64_t)1 << 21) / row_tiles;
+  const int64_t seqs_per_launch = (kQuotientMax - 1) / row_tiles;
   for (int64_t first = 0; first < s->batch; first += seqs_per_launch) {
     const int64_t seqs = s->batch - first < seqs_per_launch ? s->batch - first : seqs_per_launch;
     hipLaunchKernelGGL(score_combine_kernel, dim3((unsigned)(row_tiles * seqs), (unsigned)(s->n_layers * s->n_kv_heads)),
-                       dim3((unsigned)(64 * combine_waves)), 0, stream, p, (int)row_tiles, (int)first);
+                       dim3((unsigned)(64 * combine_waves)), 0, stream, p, (int)row_tiles, 1.0f / (float)row_tiles,
+                       (int)first);
     DAPQ_HIP_LAUNCH_CHECK("score_combine_kernel");
   }
   return DAPQ_OK;

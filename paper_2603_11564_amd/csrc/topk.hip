@@ -18,6 +18,7 @@
 // (caller's workspace), and topk_merge_kernel selects among the candidates of a head; without the workspace
 // topk_stream_kernel stages what fits in LDS (36864 keys) or re-reads the scores on every pass.
 #include "dapq_internal.h"
+#include "kernel_args.h"
 #include "wave_scan.h"
 
 namespace dapq {
@@ -41,6 +42,8 @@ struct TopkParams {
   int32_t* count;
   int64_t total_tokens;
   int32_t batch, n_kv_heads, budget;
+  int32_t seq_len;            // dense batches: total_tokens / batch
+  float inv_segs, inv_budget;
   int32_t min_len, max_len;  // this launch handles the heads with min_len <= L <= max_len
   // Long heads in pieces (cand_idx != NULL): workgroup (kv * n_segs + seg) selects among keys [seg * seg_len,
   // (seg + 1) * seg_len) of its head and leaves its survivors (order keys and positions in the head, ascending) and
@@ -74,10 +77,11 @@ __device__ __forceinline__ TopkHead topk_head(const TopkParams& p) {
   const int tid = threadIdx.x;
   const bool pieces = p.cand_idx != nullptr;
   const int nseg = pieces ? p.n_segs : 1;
-  const int kv = (int)blockIdx.x / nseg, seg = (int)blockIdx.x - kv * nseg, b = blockIdx.y, layer = blockIdx.z;
+  const int kv = uniform_quotient((int)blockIdx.x, nseg, pieces ? p.inv_segs : 1.0f), seg = (int)blockIdx.x - kv * nseg;
+  const int b = blockIdx.y, layer = blockIdx.z;
   int64_t start;
   if (p.cu_seqlens == nullptr) {
-    hd.head_len = (int)(p.total_tokens / p.batch);
+    hd.head_len = p.seq_len;
     start = (int64_t)b * hd.head_len;
   } else {
     start = p.cu_seqlens[b];
@@ -389,6 +393,7 @@ __device__ __forceinline__ float window_max(const float (&ext)[N], int i) {
 template <int THREADS, int KPT, int R>
 __global__ __launch_bounds__(THREADS) void topk_reg_kernel(TopkParams p) {
   constexpr bool kStaged = reg_variant_is_staged(THREADS, KPT);
+  touch_args<sizeof(TopkParams)>();
   const int tid = threadIdx.x;
   const TopkHead hd = topk_head(p);
   if (hd.foreign || (hd.done && p.pooled_out == nullptr)) return;  // a finished head may still owe its pooled scores
@@ -513,10 +518,11 @@ constexpr int kTopkMaxSegs = 64;
 template <int THREADS, int KPT>
 __global__ __launch_bounds__(THREADS) void topk_merge_kernel(TopkParams p) {
   __shared__ int32_t seg_count[kTopkMaxSegs];
+  touch_args<sizeof(TopkParams)>();
   const int tid = threadIdx.x;
   const int kv = blockIdx.x, b = blockIdx.y, layer = blockIdx.z;
   int L;
-  if (p.cu_seqlens == nullptr) L = (int)(p.total_tokens / p.batch);
+  if (p.cu_seqlens == nullptr) L = p.seq_len;
   else L = p.cu_seqlens[b + 1] - p.cu_seqlens[b];
   if (L < p.min_len || L > p.max_len) return;
   int want = p.budget_per_seq ? p.budget_per_seq[b] : p.budget;
@@ -532,7 +538,7 @@ __global__ __launch_bounds__(THREADS) void topk_merge_kernel(TopkParams p) {
   const int32_t* ci = p.cand_idx + head * slots;
   int32_t* out = p.idx + head * p.budget;
   const int s0 = tid * KPT;
-  int seg = s0 / p.budget, r = s0 - seg * p.budget;
+  int seg = quotient(s0, p.inv_budget), r = s0 - seg * p.budget;  // (at most 65536 slots)
   uint32_t key[KPT];
   // (16-byte loads of slots that hold no candidate read the workspace's old contents, which are dropped)
   const bool quads = (slots & 3) == 0 && (reinterpret_cast<uintptr_t>(ck) & 15) == 0;
@@ -814,6 +820,7 @@ int launch_long_heads(const dapq_shape* shape, const TopkRoute& r, TopkParams p,
   if (r.pieces_possible && workspace != nullptr && workspace_bytes >= r.pieces_bytes) {
     char* ws = static_cast<char*>(workspace);
     p.n_segs = r.n_segs;
+    p.inv_segs = 1.0f / (float)r.n_segs;
     p.seg_len = kTopkPieceLen;
     p.cand_key = reinterpret_cast<uint32_t*>(ws + r.off_key);
     p.cand_idx = reinterpret_cast<int32_t*>(ws + r.off_idx);
@@ -858,6 +865,9 @@ TopkParams topk_params(const dapq_shape* shape, const float* in, float* pooled_o
   p.batch = shape->batch;
   p.n_kv_heads = shape->n_kv_heads;
   p.budget = budget;
+  p.seq_len = (int32_t)(shape->total_tokens / shape->batch);
+  p.inv_segs = 1.0f;
+  p.inv_budget = 1.0f / (float)budget;
   p.min_len = 0;
   p.max_len = INT32_MAX;
   p.n_segs = 1;
