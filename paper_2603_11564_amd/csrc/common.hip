@@ -111,6 +111,52 @@ static int finish_score_plan(const dapq_shape* s, int64_t heads, int chunk, Scor
   return DAPQ_OK;
 }
 
+// Keys per wave of a dense batch.  The machine runs wave_slots waves at a time, each for as long as its chunk; a wave pays a fixed
+// start-up (Q fragments, ring fill) worth about kStartKeys keys.  A sequence is cut into equal chunks of whole sub-blocks, as many
+// as fill 1, 2, ... 16 rounds; of these the number with the shortest rounds x (chunk + start-up).  Where all of a sequence's chunks
+// are the waves of one workgroup (dapq_score in one kernel: one row group, at most four chunks) three of them leave the fourth
+// SIMD of a compute unit idle.
+// Powers of two -> equal chunks, with the rotation, us: 32 layers, 20000 keys, 256 rows 789 -> 690, 128 rows 518 -> 468; 8 layers,
+// 256 rows, 10000 keys 140 -> 111, 50000 keys 484 -> 441; 2 layers, 512 rows, 20000 keys 133 -> 103; 16 layers, 4 KV heads, 512 rows,
+// 2 prompts of 9999 keys 418 -> 329; prompts of 700 to 3000 keys in batches of 5 to 16 within 1 %.
+static int dense_chunk(const dapq_shape* s, int64_t heads, const ScorePlan& p, int64_t wave_slots) {
+  constexpr int64_t kStartKeys = 160;
+  const int64_t L = s->total_tokens / s->batch, streams = heads * p.n_groups * s->batch;
+  int64_t best = INT64_MAX;
+  int chunk = kMinChunkKeys;
+  for (int64_t r = 0; r <= 16; ++r) {
+    // (r = 0: as few chunks as a chunk may be long)
+    int64_t n = r == 0 ? 1 : r * wave_slots / streams;
+    if (n < 1) continue;
+    int64_t c = ((L + n - 1) / n + 31) / 32 * 32;
+    c = c < kMinChunkKeys ? kMinChunkKeys : (c > kMaxChunkKeys ? kMaxChunkKeys : c);
+    n = (L + c - 1) / c;
+    const int64_t slots = p.n_groups == 1 && n == 3 ? wave_slots / 4 * 3 : wave_slots;
+    const int64_t cost = (streams * n + slots - 1) / slots * ((L < c ? L : c) + kStartKeys);
+    if (cost < best) {
+      best = cost;
+      chunk = (int)c;
+    }
+    if (c == kMinChunkKeys) break;
+  }
+  return chunk;
+}
+// The best power of two, which bounds what a chunk may do to accuracy and workspace (see make_score_plan).
+static int dense_chunk_of_two(const dapq_shape* s, int64_t heads, const ScorePlan& p, int64_t wave_slots) {
+  const int64_t L = s->total_tokens / s->batch;
+  int64_t best = INT64_MAX;
+  int chunk = kMinChunkKeys;
+  for (int c = kMaxChunkKeys; c >= kMinChunkKeys; c /= 2) {
+    const int64_t units = heads * p.n_groups * s->batch * ((L + c - 1) / c);
+    const int64_t cost = (units + wave_slots - 1) / wave_slots * ((L < c ? L : c) + 160);
+    if (cost < best) {
+      best = cost;
+      chunk = c;
+    }
+  }
+  return chunk;
+}
+
 // Segments per head of a ragged batch, `streams` heads x row groups: the waves run in whole rounds of wave_slots, each as long as
 // its share of the key axis, whatever the lengths of the sequences.  Of the numbers that fill 1, 2, ... 16 rounds the one with the
 // least to do: a round's start-up (ring, queries) costs about what a two-hundredth of a head's keys do.  (At most 2^26 keys to a
@@ -145,29 +191,28 @@ int make_score_plan(const dapq_shape* s, size_t workspace_bytes, ScorePlan* p) {
   p->rows_pad = p->n_groups * p->row_blocks * 32;
   p->tile = false;
   p->stage_q = false;
+  p->unit_sums = false;
   p->segments = 0;
 
   constexpr int64_t kWaveSlots = 1024;
   int rc;
   if (s->cu_seqlens == nullptr) {
-    // Keys per wave.  The machine runs kWaveSlots waves at a time, each for as long as its chunk; a
-    // wave pays a fixed start-up (Q fragments, ring fill) worth about kStartKeys keys.  Dense batches
-    // run in whole rounds of equal chunks: pick the chunk with the shortest rounds x (chunk +
-    // start-up).
-    constexpr int64_t kStartKeys = 160;
-    const int64_t L = s->total_tokens / s->batch;
-    int chunk = kMinChunkKeys;
-    int64_t best = INT64_MAX;
-    for (int c = kMaxChunkKeys; c >= kMinChunkKeys; c /= 2) {
-      const int64_t units = heads * p->n_groups * s->batch * ((L + c - 1) / c);
-      const int64_t rounds = (units + kWaveSlots - 1) / kWaveSlots;
-      const int64_t cost = rounds * ((L < c ? L : c) + kStartKeys);
-      if (cost < best) {
-        best = cost;
-        chunk = c;
-      }
-    }
+    const int two = dense_chunk_of_two(s, heads, *p, kWaveSlots);
+    int chunk = dense_chunk(s, heads, *p, kWaveSlots);
+    // A lane of pass 1 adds up its half of a chunk one by one, and what that costs in accuracy grows with the chunk (2^14 keys:
+    // 1.7e-5 of a score): chunks longer than the power of two form their sums in two steps, which is as fast and more accurate.
+    // (Not so the others, whose results stay what they were; and powers of two above 2^13 are not exceeded, since two results
+    // that are both right would be that far apart.)
+    if (chunk > two && two > 8192) chunk = two;
+    p->unit_sums = chunk > two;
     rc = finish_score_plan(s, heads, chunk, p);
+    if (rc == DAPQ_OK && chunk != two && p->total_bytes > DAPQ_STATIC_SCRATCH_BYTES) {
+      // a shape that dapq_score_static served with the power of two is still served, by the same kernels as dapq_score's: a line of
+      // room, not of time
+      ScorePlan t = *p;
+      t.unit_sums = false;
+      if (finish_score_plan(s, heads, two, &t) == DAPQ_OK && t.total_bytes <= DAPQ_STATIC_SCRATCH_BYTES) *p = t;
+    }
   } else {
     p->segments = ragged_segments(heads * p->n_groups, kWaveSlots, s->total_tokens);
     rc = finish_score_plan(s, heads, 32, p);

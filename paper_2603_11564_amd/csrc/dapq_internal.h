@@ -36,12 +36,13 @@ constexpr int kTileKeys = 128, kTileMinKeys = 32, kTileMaxKeys = 256;
 // dapq_workspace_bytes() and the launchers agree.
 struct ScorePlan {
   bool stage_q;    // tile form: the queries go through LDS
+  bool unit_sums;  // wave form, dense: pass 1 adds up a unit's terms first
   bool tile;       // the tile kernels (a workgroup per chunk, its waves share out the rows) instead of the wave kernels
   int rows;        // R = (H_q/H_kv) * N query rows scored against every key of a KV head
   int n_groups;    // row groups of row_blocks * 32 rows, one wave each per chunk (tile: 1)
   int row_blocks;  // 32-row blocks per wave (2, 4 or 8; tile: all of them)
   int rows_pad;    // n_groups * row_blocks * 32
-  int chunk_keys;  // keys per wave (a power of two; a ragged batch in segments: those of a sub-block)
+  int chunk_keys;  // keys per wave, a multiple of 32 (tile form: keys of a tile, a power of two; in segments: those of a sub-block)
   int segments;    // ragged batches in the wave form: the waves that share a head's packed key axis (else 0)
   int64_t max_chunks;  // partial sums of a row: upper bound on sum_b ceil(L_b / chunk_keys), or batch + segments
   // workspace carving (byte offsets)

@@ -73,7 +73,7 @@ struct ScoreParams {
   float c;  // scale * log2(e)
   // What every workgroup would divide for before it can ask for its first key:
   int32_t seq_len, chunks_per_seq;  // dense batches
-  int32_t chunk_shift;              // log2(chunk_keys)
+  int32_t chunk_shift;              // ragged batches and the tile form: log2(chunk_keys)
   int32_t stage_q;                  // tile form: the queries go through LDS too
   float inv_n_pseudo, inv_kv_heads, inv_rows_pad;
 };
@@ -519,8 +519,8 @@ __device__ __forceinline__ void wait_ring_full() {
 // per slice (the MFMA leads its slice, so the last MFMA of a unit is a full slice old when its
 // first result is read).  The sum a step adds to belongs to the pair three steps back: steps 0..2
 // of a unit still feed the unit two back.
-// PASS 1: off1[rb] = -(reference logit * c) of row block rb; acc[rb] receives the row sums.  In a segment,
-// whose sequences may be long, a unit's 16 terms of a lane are added up first (su): the same number of additions, and small
+// PASS 1: off1[rb] = -(reference logit * c) of row block rb; acc[rb] receives the row sums.  In segments
+// and long chunks a unit's 16 terms of a lane are added up first (su): the same number of additions, and small
 // terms meet a large sum once a unit instead of one by one (8 prompts of 4096..16384 keys, 512 rows: 6e-7 off float64).
 // PASS 2: off2[rb][v] = -lse2 of the row that accumulator register v of this lane holds in row
 //         block rb (-inf for padding rows, which then add 0).  S of every key goes to out.
@@ -530,7 +530,7 @@ __device__ __forceinline__ void wave_walk(u32x4* ring, int& slot, Stream& keys, 
                                           bf16x8 (&kf)[8], const bf16x8 (&qf)[NRB][8], float c,
                                           const float (&off1)[NRB], const float (&off2)[PASS == 2 ? NRB : 1][16],
                                           float (&acc)[NRB], float* out, const unsigned (&voff)[4], int n, int h) {
-  constexpr bool kUnitSums = PASS == 1 && Stream::kSegment;
+  constexpr bool kUnitSums = PASS == 1 && Stream::kUnitSums;
   auto first_key = [&](int sub) { return (Stream::kReversed ? first_sub - sub : first_sub + sub) * 32; };
   const unsigned ring_base = (unsigned)(uintptr_t)(lds_vec_ptr)ring;
   unsigned fa[8];
@@ -678,9 +678,9 @@ __device__ __forceinline__ void wave_load_frags(bf16x8 (&kf)[8], const u32x4* sl
 // (SEG) of a segment of a ragged one, sequence after sequence.  REV: from the last sub-block down.  The ring is filled ahead
 // across the sequences of a segment: while the wave changes to the queries of the next one, that one's first NST - 1
 // sub-blocks are on their way.
-template <bool REV, bool SEG>
+template <bool REV, bool SEG, bool UNIT = SEG>
 struct KeyStream {
-  static constexpr bool kReversed = REV, kSegment = SEG;
+  static constexpr bool kReversed = REV, kSegment = SEG, kUnitSums = UNIT;
   const ScoreParams& p;
   const uint16_t* head;  // SEG: the KV head's keys
   const uint16_t* base;  // first key of the sequence (dense: of the chunk) that is being fetched
@@ -800,7 +800,7 @@ __device__ __forceinline__ const uint16_t* wave_q_base(const ScoreParams& p, int
 // Pass 1 of one chunk of a dense batch: `group` = row group, `chunk_id` = chunk along the packed key axis.  The chunk must have
 // keys.  FUSED (score_fused_kernel): the chunk's (reference, sum) pairs go to the start of the wave's own ring, which is
 // drained by then, instead of to global memory.
-template <int NRB, int NST, bool FUSED = false>
+template <int NRB, int NST, bool UNIT, bool FUSED = false>
 __device__ __forceinline__ void pass1_chunk(const ScoreParams& p, u32x4* ring, const Work& w, int chunk_id, int group, int head,
                                             bf16x8 (&qf)[NRB][8], int lane) {
   unsigned voff[4];
@@ -809,7 +809,7 @@ __device__ __forceinline__ void pass1_chunk(const ScoreParams& p, u32x4* ring, c
   const uint16_t* kbase = uniform_ptr(p.k + (int64_t)layer * p.k_stride_layer + (int64_t)w.seq * p.k_stride_seq +
                                       (int64_t)kv * p.k_stride_head + w.tok0 * p.k_stride_token);
   const int gbase = group * (NRB * 32);  // first row of this wave's row group
-  KeyStream<false, false> keys = {p, nullptr, kbase, w.nkeys, 0, 0, 0};
+  KeyStream<false, false, UNIT> keys = {p, nullptr, kbase, w.nkeys, 0, 0, 0};
   fill_ring<NST>(ring, keys, voff, 0);
   bf16x8 kf[8];
   int slot = 0;
@@ -867,7 +867,7 @@ __device__ __forceinline__ WaveSlot wave_slot(const ScoreParams& p, int wave_id)
 
 // The grid names the items, one per wave: (chunk, row group, layer x KV head).  SEG (ragged batches, whose lengths
 // the host does not know): a segment of the packed key axis in the place of the chunk.
-template <int NRB, bool SEG, int NST>
+template <int NRB, bool SEG, bool UNIT, int NST>
 __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_wave_pass1_kernel(ScoreParams p) {
   extern __shared__ u32x4 rings[];
   const int wave_id = uniform_i32((int)(threadIdx.x >> 6));
@@ -880,7 +880,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_wave_pass1_kerne
   } else {
     const Work w = locate_uniform(p, slot.chunk);
     if (w.nkeys == 0) return;
-    pass1_chunk<NRB, NST>(p, ring, w, slot.chunk, slot.group, (int)blockIdx.z, qf, lane);
+    pass1_chunk<NRB, NST, UNIT>(p, ring, w, slot.chunk, slot.group, (int)blockIdx.z, qf, lane);
   }
 }
 
@@ -1025,7 +1025,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_wave_pass2_kerne
 // the query fragments still in registers.  What this saves is everything between the passes: a kernel boundary at
 // which every wave of the chip waits for the slowest, the combine kernel, the second placement of the workgroups and
 // the second read of the queries.  lse2 is not written anywhere.
-template <int NRB, int NST>
+template <int NRB, bool UNIT, int NST>
 __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_fused_kernel(ScoreParams p) {
   extern __shared__ u32x4 rings[];
   const int wave_id = uniform_i32((int)(threadIdx.x >> 6)), waves = (int)(blockDim.x >> 6);
@@ -1035,7 +1035,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_fused_kernel(Sco
   const int chunk = uniform_i32((int)blockIdx.x * waves + wave_id);  // blockIdx.x is the sequence
   const int head = (int)blockIdx.z;
   const Work work = locate_uniform(p, chunk);
-  pass1_chunk<NRB, NST, true>(p, ring, work, chunk, 0, head, qf, lane);
+  pass1_chunk<NRB, NST, UNIT, true>(p, ring, work, chunk, 0, head, qf, lane);
   __syncthreads();
   // lse2 of rows lane, lane + 64, ...: every wave merges all chunks itself
   constexpr int kRowsPerLane = NRB * 32 / 64;
@@ -1610,23 +1610,24 @@ int launch_wave_pass1(const dapq_shape* s, const ScorePlan& plan, ScoreParams p,
   int rc = DAPQ_OK;
   const GroupShape gs = group_shape(s, plan);
   p.wg_groups = gs.groups;
-#define DAPQ_LAUNCH_W1(NRBV, SEGV)                                                                                      \
+#define DAPQ_LAUNCH_W1(NRBV, SEGV, UNITV)                                                                                  \
   do {                                                                                                                  \
-    if ((rc = set_lds(score_wave_pass1_kernel<NRBV, SEGV, kWaveStages>, kWavesPerGroup * wave_lds(kWaveStages))) !=     \
+    if ((rc = set_lds(score_wave_pass1_kernel<NRBV, SEGV, UNITV, kWaveStages>, kWavesPerGroup * wave_lds(kWaveStages))) != \
         DAPQ_OK)                                                                                                        \
       return rc;                                                                                                        \
-    hipLaunchKernelGGL((score_wave_pass1_kernel<NRBV, SEGV, kWaveStages>), gs.grid(plan, s), dim3(64 * gs.waves),       \
+    hipLaunchKernelGGL((score_wave_pass1_kernel<NRBV, SEGV, UNITV, kWaveStages>), gs.grid(plan, s), dim3(64 * gs.waves),  \
                        gs.waves * wave_lds(kWaveStages), stream, p);                                                    \
   } while (0)
-  if (plan.segments > 0) {
-    if (plan.row_blocks == 2) DAPQ_LAUNCH_W1(2, true);
-    else if (plan.row_blocks == 4) DAPQ_LAUNCH_W1(4, true);
-    else DAPQ_LAUNCH_W1(8, true);
-  } else {
-    if (plan.row_blocks == 2) DAPQ_LAUNCH_W1(2, false);
-    else if (plan.row_blocks == 4) DAPQ_LAUNCH_W1(4, false);
-    else DAPQ_LAUNCH_W1(8, false);
-  }
+#define DAPQ_LAUNCH_W1_KEYS(NRBV)                             \
+  do {                                                        \
+    if (plan.segments > 0) DAPQ_LAUNCH_W1(NRBV, true, true);  \
+    else if (plan.unit_sums) DAPQ_LAUNCH_W1(NRBV, false, true); \
+    else DAPQ_LAUNCH_W1(NRBV, false, false);                  \
+  } while (0)
+  if (plan.row_blocks == 2) DAPQ_LAUNCH_W1_KEYS(2);
+  else if (plan.row_blocks == 4) DAPQ_LAUNCH_W1_KEYS(4);
+  else DAPQ_LAUNCH_W1_KEYS(8);
+#undef DAPQ_LAUNCH_W1_KEYS
 #undef DAPQ_LAUNCH_W1
   DAPQ_HIP_LAUNCH_CHECK("score_wave_pass1_kernel");
   return DAPQ_OK;
@@ -1714,16 +1715,22 @@ int launch_fused(const dapq_shape* s, const ScorePlan& plan, ScoreParams p, hipS
   p.wg_groups = 1;
   const dim3 grid((unsigned)s->batch, 1u, (unsigned)(s->n_layers * s->n_kv_heads));
   int rc = DAPQ_OK;
-#define DAPQ_LAUNCH_F(NRBV)                                                                                            \
+#define DAPQ_LAUNCH_F(NRBV, UNITV)                                                                                     \
   do {                                                                                                                 \
-    if ((rc = set_lds(score_fused_kernel<NRBV, kWaveStages>, kWavesPerGroup * wave_lds(kWaveStages))) != DAPQ_OK)     \
+    if ((rc = set_lds(score_fused_kernel<NRBV, UNITV, kWaveStages>, kWavesPerGroup * wave_lds(kWaveStages))) != DAPQ_OK) \
       return rc;                                                                                                       \
-    hipLaunchKernelGGL((score_fused_kernel<NRBV, kWaveStages>), grid, dim3(64 * gs.waves),                             \
+    hipLaunchKernelGGL((score_fused_kernel<NRBV, UNITV, kWaveStages>), grid, dim3(64 * gs.waves),                      \
                        gs.waves * wave_lds(kWaveStages), stream, p);                                                   \
   } while (0)
-  if (plan.row_blocks == 2) DAPQ_LAUNCH_F(2);
-  else if (plan.row_blocks == 4) DAPQ_LAUNCH_F(4);
-  else DAPQ_LAUNCH_F(8);
+  if (plan.unit_sums) {
+    if (plan.row_blocks == 2) DAPQ_LAUNCH_F(2, true);
+    else if (plan.row_blocks == 4) DAPQ_LAUNCH_F(4, true);
+    else DAPQ_LAUNCH_F(8, true);
+  } else {
+    if (plan.row_blocks == 2) DAPQ_LAUNCH_F(2, false);
+    else if (plan.row_blocks == 4) DAPQ_LAUNCH_F(4, false);
+    else DAPQ_LAUNCH_F(8, false);
+  }
 #undef DAPQ_LAUNCH_F
   DAPQ_HIP_LAUNCH_CHECK("score_fused_kernel");
   return DAPQ_OK;

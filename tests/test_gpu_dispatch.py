@@ -396,6 +396,32 @@ def test_ragged_batches_in_the_wave_form(H, rows, batch):
     H.assert_scores_close(S[:1].cpu().numpy(), O.score(q, k, 2, cu), f"rows={rows} batch={batch}")
 
 
+# dense batches whose chunks are no powers of two: eight per sequence, shorter than the power of two; four, longer (sums in two
+# steps; up to 256 rows both passes in one kernel); three and one; several sequences; the last chunk with a partial sub-block or short
+@pytest.mark.parametrize("rows", [33, 128, 250, 300])
+@pytest.mark.parametrize("layers,batch,length", [(64, 1, 3001), (128, 1, 5000), (170, 1, 2900), (70, 7, 1111), (25, 3, 2017)])
+def test_equal_chunks_of_dense_batches(H, layers, batch, length, rows):
+    """Every layer is the same problem (layer strides of 0), with a key hundreds of binades above the others: the oracle's scores within
+    1e-3 and normalisers within 2e-4 in the log2 domain, the same bits in every layer and from the two separate entry points."""
+    announce(f"equal chunks: {layers} layers, {batch} x {length} keys, rows={rows}")
+    lens = [length] * batch
+    q, k, v, cu = problem_bits(rows, 1, lens, 2, 2, rows)
+    k[0, 2 * length // 3, 1] = W.to_bf16_bits(30.0 * O.bf16_bits_to_f64(q[0, 0, 1, 0]))
+    prob = H.Problem(q, k, v, 2, None, "thd")
+    tokens = batch * length
+    shape = H.D.make_shape(n_layers=layers, batch=batch, n_q_heads=2, n_kv_heads=2, n_pseudo=rows, total_tokens=tokens,
+                           k_strides=(0, 0, 128, 256), q_strides=(0, 2 * rows * 128, rows * 128, 128), scale=128 ** -0.5)
+    ws = torch.full((H.D.workspace_bytes(shape),), 0xA5, dtype=torch.uint8, device="cuda")
+    S, T = (torch.full((layers, 2, tokens), float("nan"), dtype=torch.float32, device="cuda") for _ in range(2))
+    lse = torch.full((layers, batch, 2, rows), float("nan"), dtype=torch.float32, device="cuda")
+    H.D.dapq_score(shape, prob.q, prob.k, S, ws)
+    H.D.dapq_score_stats(shape, prob.q, prob.k, lse, ws)
+    H.D.dapq_score_accumulate(shape, prob.q, prob.k, lse, T, ws)
+    assert torch.equal(S, T) and torch.equal(S, S[:1].expand_as(S)) and torch.equal(lse, lse[:1].expand_as(lse))
+    H.assert_scores_close(S[:1].cpu().numpy(), O.score(q, k, 2, cu), f"{layers} {lens} rows={rows}")
+    assert np.abs(lse[:1].cpu().numpy() - oracle_lse2(q, k, 2, cu)).max() < 2e-4
+
+
 # segments that begin and end inside sequences, take in several, empty ones among them, or hold one sub-block; a head of one key
 @pytest.mark.parametrize("rows", [33, 128, 250, 300])
 @pytest.mark.parametrize("lens", [[1, 0, 31, 32, 33, 0, 0, 64, 900, 5, 0, 1300, 0], [0, 2500, 0, 65], [1], [0, 3, 0]],
