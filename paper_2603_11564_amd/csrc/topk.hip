@@ -57,7 +57,7 @@ struct TopkParams {
 // fp32 -> uint32 with the same order for all non-NaN values.
 __device__ __forceinline__ uint32_t order_key(float f) {
   const uint32_t u = __float_as_uint(f);
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+  return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
 }
 
 // What every variant needs to know about its head; heads of another launch (length outside
@@ -152,7 +152,7 @@ constexpr int reg_variant_stage_bytes(int threads, int kpt) {  // (two more rows
   return reg_variant_is_staged(threads, kpt) ? (threads + 2) * (kpt + 4) * (int)sizeof(float) : 0;
 }
 
-// bits = 16 * bits + the flags key > t (key == t) of four keys, the first one on top: a compare and an add with carry per key.
+// bits = 16 * bits + the flags key > t of four keys, the first one on top: a compare and an add with carry per key.
 // A carry may be read two wait states after the compare that made it, and neither the hardware nor the compiler sees to that
 // inside inline assembly: the flags of four keys lie in four register pairs, three instructions stand between each compare and
 // its add.  (t in a vector register: that one is free to read whenever it was written.)  As fast as compare and add in turn
@@ -165,23 +165,15 @@ __device__ __forceinline__ void push_greater(uint32_t& bits, const uint32_t* key
       : "+&v"(bits), "=&s"(c0), "=&s"(c1), "=&s"(c2), "=&s"(c3)
       : "v"(t), "v"(key[0]), "v"(key[1]), "v"(key[2]), "v"(key[3]));
 }
-__device__ __forceinline__ void push_equal(uint32_t& bits, const uint32_t* key, uint32_t t) {
-  uint64_t c0, c1, c2, c3;
-  asm("v_cmp_eq_u32 %1, %5, %6\n\tv_cmp_eq_u32 %2, %5, %7\n\tv_cmp_eq_u32 %3, %5, %8\n\tv_cmp_eq_u32 %4, %5, %9\n\t"
-      "v_addc_co_u32 %0, %1, %0, %0, %1\n\tv_addc_co_u32 %0, %2, %0, %0, %2\n\t"
-      "v_addc_co_u32 %0, %3, %0, %0, %3\n\tv_addc_co_u32 %0, %4, %0, %0, %4"
-      : "+&v"(bits), "=&s"(c0), "=&s"(c1), "=&s"(c2), "=&s"(c3)
-      : "v"(t), "v"(key[0]), "v"(key[1]), "v"(key[2]), "v"(key[3]));
-}
 
 // ---- selection among the keys a workgroup holds in registers (KPT per thread, thread t's before thread t+1's):
 // the `keep` largest, ties to the lowest position, handed to emit(i, key, slot) in ascending position order (register
 // i of the calling thread is survivor number `slot`; `key` is 0 unless want_key).  A register without a key holds 0 (a
-// key is at least 1); the workgroup has n_keys.  keep >= 1 and at most n_keys.
+// key is at least 1); the workgroup has n_keys; `whole`: all registers of this wave hold keys.  keep >= 1 and at most n_keys.
 // bins: LDS of THREADS uint4 that nobody else reads any more; thread t looks after bins 4t .. 4t+3.
 //
 // The threshold T (the keep-th largest key) is closed in on: [lo, lo + range] starts as the span of the keys and becomes,
-// per pass, the one of 4 * THREADS equal bins that T lies in; when at most 64 candidates are left one wave ranks them by
+// per pass, the one of 4 * THREADS equal bins that T lies in; when at most 64 candidates are left they are ranked by
 // comparing all with all.  With sixteen waves to a compute unit the time is the vector instructions of a thread (16
 // clocks each), and a pass is four per key: keys of scores span a few octaves, a bin is then a few thousandths of an
 // octave, and one pass leaves a few dozen.  (Digits of the key instead -- sign and exponent, then 8 bits at a time --
@@ -192,17 +184,22 @@ __device__ __forceinline__ void push_equal(uint32_t& bits, const uint32_t* key, 
 // 27 and 10).  Kept positions are bits of a word per 32 keys, and the survivors are walked bit by bit.  Selection with pooling, by
 // digits -> by bins: 8 heads of 32768 keys, 983 kept, 21.5 -> 15.9 us; 256 heads 28.8 -> 18.7; 64 heads of 131072 keys, 3932
 // kept, in pieces 65 -> 43; 256 heads of 2000 keys, 128 kept, 14.9 -> 11.8.
-constexpr int kRankMax = 64;  // candidates one wave ranks
+// Of 27 000 clocks of one workgroup over 32768 keys (33 000 with a test per register for whether it holds a key, candidates looked
+// for register by register and ranked by one wave) 24 000 are left: arguments 800, loading 4100 (11 400 with 256 heads), dealing out
+// and pooling 2000, keys and their span 3000, bins 6800 (a wave's LDS addition takes 12 clocks however many of its lanes add,
+// and whether or not the loop masks them), bits and ranks 3800, compaction 3000.  With the gather: 8 heads 19.1 -> 15.9 us, 64 heads
+// of 131072 keys in pieces 88.2 -> 82.9.
+constexpr int kRankMax = 64;  // candidates that are ranked
 constexpr int kCrowd = 3;     // neighbouring lanes of 60 with keys of one bin: a bin that holds a fifth of them (in a spread of keys, 0.1)
 template <int THREADS, int KPT, class Emit>
-__device__ __forceinline__ void topk_select(const uint32_t (&key)[KPT], int n_keys, int keep, uint4* bins, bool want_key,
+__device__ __forceinline__ void topk_select(const uint32_t (&key)[KPT], int n_keys, int keep, uint4* bins, bool whole, bool want_key,
                                             Emit emit) {
   constexpr int kWaves = THREADS / 64, kWords = (KPT + 31) / 32, kBins = 4 * THREADS;
   static_assert(KPT % 4 == 0 && (KPT < 32 || KPT % 32 == 0), "whole quads and whole words of position bits");
   static_assert((kBins & (kBins - 1)) == 0 && kWaves <= 64, "bins and waves");
   __shared__ uint32_t wave_min[kWaves], wave_max[kWaves], wave_count[kWaves];
   __shared__ uint32_t found[3];  // bin, need, population of the bin
-  __shared__ uint32_t last[kRankMax];
+  __shared__ uint32_t last[kRankMax], ranks[kRankMax];
   __shared__ uint32_t last_n;
   __shared__ uint32_t wave_gt[kWaves], wave_eq[kWaves];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -210,12 +207,20 @@ __device__ __forceinline__ void topk_select(const uint32_t (&key)[KPT], int n_ke
   uint32_t lo, range, left = (uint32_t)n_keys;  // candidates: the `left` keys with key - lo <= range
   int need = keep;
   {
-    // (a register without a key holds 0: key - 1 wraps to the largest value and never is the minimum)
     uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
+    if (whole) {
 #pragma unroll
-    for (int i = 0; i < KPT; ++i) {
-      kmin = key[i] - 1u < kmin ? key[i] - 1u : kmin;
-      kmax = key[i] > kmax ? key[i] : kmax;
+      for (int i = 0; i < KPT; ++i) {
+        kmin = key[i] < kmin ? key[i] : kmin;
+        kmax = key[i] > kmax ? key[i] : kmax;
+      }
+      kmin -= 1u;
+    } else {  // (a register without a key holds 0: key - 1 wraps to the largest value and never is the minimum)
+#pragma unroll
+      for (int i = 0; i < KPT; ++i) {
+        kmin = key[i] - 1u < kmin ? key[i] - 1u : kmin;
+        kmax = key[i] > kmax ? key[i] : kmax;
+      }
     }
     kmin = wave_scan<OpMin>(kmin);
     kmax = wave_scan<OpMax>(kmax);
@@ -225,14 +230,12 @@ __device__ __forceinline__ void topk_select(const uint32_t (&key)[KPT], int n_ke
     }
     bins[tid] = make_uint4(0, 0, 0, 0);
     if (tid == 0) last_n = 0;
+    if (tid < kRankMax) ranks[tid] = 0;
     __syncthreads();
-    kmin = wave_min[0];
-    kmax = wave_max[0];
-#pragma unroll
-    for (int w = 1; w < kWaves; ++w) {
-      kmin = wave_min[w] < kmin ? wave_min[w] : kmin;
-      kmax = wave_max[w] > kmax ? wave_max[w] : kmax;
-    }
+    kmin = wave_scan<OpMin>(lane < kWaves ? wave_min[lane] : 0xFFFFFFFFu);  // (lane 63 has all of them)
+    kmax = wave_scan<OpMax>(lane < kWaves ? wave_max[lane] : 0u);
+    kmin = (uint32_t)__builtin_amdgcn_readlane((int)kmin, 63);
+    kmax = (uint32_t)__builtin_amdgcn_readlane((int)kmax, 63);
     lo = uniform(kmin) + 1u;
     range = uniform(kmax) - lo;
   }
@@ -294,45 +297,71 @@ __device__ __forceinline__ void topk_select(const uint32_t (&key)[KPT], int n_ke
     left = uniform(found[2]);
     // (found is written again only behind the next pass's barriers)
   }
-  if (range != 0u) {
-#pragma unroll
-    for (int i = 0; i < KPT; ++i) {
-      const bool cand = key[i] - lo <= range;
-      if (__ballot(cand) != 0) {  // rare
-        if (cand) last[atomicAdd(&last_n, 1u)] = key[i];
-      }
-    }
-    __syncthreads();
-    if (wave == 0) {
-      const uint32_t v = (uint32_t)lane < left ? last[lane] : 0u;
-      int above = 0, same = 0;
-      for (int e = 0; e < (int)left; ++e) {
-        const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)v, e);
-        above += o > v ? 1 : 0;
-        same += o == v ? 1 : 0;
-      }
-      if ((uint32_t)lane < left && above < need && need <= above + same) {  // (lanes of equal keys write the same)
-        found[0] = v;
-        found[1] = (uint32_t)(need - above);
-      }
-    }
-    __syncthreads();
-    lo = uniform(found[0]);
-    need = (int)uniform(found[1]);
-  }
-  const uint32_t T = lo;
-
-  // ---- ordered compaction: one exclusive scan of the per-thread (greater, equal) counts
-  // (T is a key, so T >= 1 and registers without a key count as neither)
+  // ---- which keys are above the span and which are in it, a bit each (lo >= 1: registers without a key are neither)
   uint32_t gt[kWords], eq[kWords], my_gt = 0, my_eq = 0;
 #pragma unroll
   for (int w = 0; w < kWords; ++w) {
     gt[w] = eq[w] = 0;
 #pragma unroll
     for (int i = 32 * w; i < KPT && i < 32 * w + 32; i += 4) {
-      push_greater(gt[w], &key[i], T);
-      push_equal(eq[w], &key[i], T);
+      push_greater(gt[w], &key[i], lo + range);
+      push_greater(eq[w], &key[i], lo - 1u);
     }
+    eq[w] &= ~gt[w];
+  }
+  if (range != 0u) {
+    // the candidates of a thread go to the list one after the other; registers that no thread of the wave has one in are
+    // passed over four at a time
+    uint32_t mine = 0;
+#pragma unroll
+    for (int w = 0; w < kWords; ++w) mine += (uint32_t)__popc(eq[w]);
+    uint32_t at = 0;
+    if (mine != 0) at = atomicAdd(&last_n, mine);
+    const uint32_t first_at = at;
+#pragma unroll
+    for (int i = 0; i < KPT; i += 4) {
+      const int top = KPT - i / 32 * 32 < 32 ? KPT - i / 32 * 32 - 1 : 31;
+      const uint32_t four = (eq[i / 32] >> (top - i % 32 - 3)) & 15u;
+      if (__any((int)four)) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (four & (8u >> u)) last[at++] = key[i + u];
+      }
+    }
+    __syncthreads();
+    // all with all: lane = candidate, every wave compares it with its share of them (one wave alone: up to 3000 clocks while the
+    // others wait)
+    const uint32_t v = (uint32_t)lane < left ? last[lane] : 0u;
+    uint32_t rank = 0;  // candidates above this one, and (<< 16) the same as this one
+    for (int e = wave; e < (int)left; e += kWaves) {
+      const uint32_t o = last[e];
+      rank += o > v ? 1u : (o == v ? 0x10000u : 0u);
+    }
+    if (wave < (int)left) atomicAdd(&ranks[lane], rank);
+    __syncthreads();
+    rank = ranks[lane];
+    const int above = (int)(rank & 0xFFFFu), same = (int)(rank >> 16);
+    const uint64_t hit = __ballot((uint32_t)lane < left && above < need && need <= above + same);  // (equal keys hit together)
+    const int first = __ffsll((long long)hit) - 1;
+    const uint32_t T = (uint32_t)__builtin_amdgcn_readlane((int)v, first);
+    need -= __builtin_amdgcn_readlane(above, first);
+    at = first_at;
+#pragma unroll
+    for (int w = 0; w < kWords; ++w) {
+      uint32_t rest = eq[w];
+      while (rest != 0) {  // (first register on top)
+        const uint32_t bit = 0x80000000u >> __clz((int)rest);
+        const uint32_t k = last[at++];
+        rest ^= bit;
+        if (k > T) gt[w] |= bit;
+        if (k != T) eq[w] ^= bit;
+      }
+    }
+  }
+
+  // ---- ordered compaction: one exclusive scan of the per-thread (greater, equal) counts
+#pragma unroll
+  for (int w = 0; w < kWords; ++w) {
     my_gt += (uint32_t)__popc(gt[w]);
     my_eq += (uint32_t)__popc(eq[w]);
   }
@@ -405,6 +434,8 @@ __global__ __launch_bounds__(THREADS) void topk_reg_kernel(TopkParams p) {
   // contiguous rows per wave makes the compaction twice as long.)
   const int j0 = tid * KPT;
   const int nvalid = L - j0 < 0 ? 0 : (L - j0 > KPT ? KPT : L - j0);
+  // (a wave whose threads all have KPT keys is spared the tests)
+  const bool whole = __all(nvalid == KPT);
   float ext[KPT + 2 * R];  // scores j0-R .. j0+KPT+R-1; -inf outside the sequence
   if (kStaged) {
     // The head comes in with coalesced 16-byte loads (a thread reading its own run straight from memory makes
@@ -440,10 +471,14 @@ __global__ __launch_bounds__(THREADS) void topk_reg_kernel(TopkParams p) {
 #pragma unroll
     for (int i = 0; i < KPT; i += 4) {
       const float4 v = *reinterpret_cast<const float4*>(&stage[tid * kRow + i]);
-      ext[R + i] = i < nvalid ? v.x : -INFINITY;
-      ext[R + i + 1] = i + 1 < nvalid ? v.y : -INFINITY;
-      ext[R + i + 2] = i + 2 < nvalid ? v.z : -INFINITY;
-      ext[R + i + 3] = i + 3 < nvalid ? v.w : -INFINITY;
+      ext[R + i] = v.x;
+      ext[R + i + 1] = v.y;
+      ext[R + i + 2] = v.z;
+      ext[R + i + 3] = v.w;
+    }
+    if (!whole) {
+#pragma unroll
+      for (int i = 0; i < KPT; ++i) ext[R + i] = i < nvalid ? ext[R + i] : -INFINITY;
     }
     if (R > 0) {
       const float4 lv = *reinterpret_cast<const float4*>(&stage[(tid - 1) * kRow + KPT - 4]);
@@ -483,17 +518,34 @@ __global__ __launch_bounds__(THREADS) void topk_reg_kernel(TopkParams p) {
     for (int j = 0; j < KPT + 4; ++j) ext[j] = fmaxf(fmaxf(ext[j], ext[j + 1]), ext[j + 2]);
   }
   uint32_t key[KPT];
+  uint32_t signs = 0;
 #pragma unroll
   for (int i = 0; i < KPT; ++i) {
-    float m = window_max<R>(ext, i);
-    if (p.pooled_out != nullptr && i < nvalid) p.pooled_out[(hd.src - p.pooled) + j0 + i] = m;
-    // registers past the end of the head hold 0, which no key is (a key is at least 1): everything below can then
-    // tell them by value, and no per-register validity mask has to stay alive through the kernel
-    const uint32_t k = order_key(m);
-    key[i] = i < nvalid ? (k > 1u ? k : 1u) : 0u;
+    key[i] = __float_as_uint(window_max<R>(ext, i));
+    signs |= key[i];
+  }
+  if (KPT > 32 || __any((int)signs < 0)) {
+#pragma unroll
+    for (int i = 0; i < KPT; ++i) {
+      const uint32_t k = order_key(__uint_as_float(key[i]));
+      key[i] = k > 1u ? k : 1u;
+    }
+  } else {  // no negative score in this wave, as in sums of weights: one operation per key instead of four
+#pragma unroll
+    for (int i = 0; i < KPT; ++i) key[i] |= 0x80000000u;
+  }
+  if (p.pooled_out != nullptr) {
+#pragma unroll
+    for (int i = 0; i < KPT; ++i)
+      if (i < nvalid) p.pooled_out[(hd.src - p.pooled) + j0 + i] = window_max<R>(ext, i);
+  }
+  // registers past the end of the head hold 0, which no key is (a key is at least 1): everything below can then
+  // tell them by value, and no per-register validity mask has to stay alive through the kernel
+  if (!whole) {
+#pragma unroll
+    for (int i = 0; i < KPT; ++i) key[i] = i < nvalid ? key[i] : 0u;
   }
   if (hd.done) return;
-
 
   uint4* bins;
   if constexpr (kStaged) {
@@ -504,7 +556,7 @@ __global__ __launch_bounds__(THREADS) void topk_reg_kernel(TopkParams p) {
     bins = own_bins;
   }
   const bool piece = hd.out_key != nullptr;
-  topk_select<THREADS, KPT>(key, L, hd.keep, bins, piece, [&](int i, uint32_t k, uint32_t slot) {
+  topk_select<THREADS, KPT>(key, L, hd.keep, bins, whole, piece, [&](int i, uint32_t k, uint32_t slot) {
     hd.out[slot] = hd.base + j0 + i;
     if (piece) hd.out_key[slot] = k;
   });
@@ -565,7 +617,7 @@ __global__ __launch_bounds__(THREADS) void topk_merge_kernel(TopkParams p) {
   __shared__ uint4 bins[THREADS];
   int n_keys = 0;
   for (int i = 0; i < nseg; ++i) n_keys += seg_count[i];
-  topk_select<THREADS, KPT>(key, n_keys, keep, bins, false,
+  topk_select<THREADS, KPT>(key, n_keys, keep, bins, false, false,
                             [&](int i, uint32_t, uint32_t slot) { out[slot] = ci[s0 + i]; });
 }
 

@@ -373,6 +373,32 @@ def test_selection_over_distributions(H, n, kind):
                 assert np.array_equal(got, O.topk(P[kv].astype(np.float64), budget)), (budget, pooled, kv)
 
 
+# waves with and without negative scores in one head (their keys are formed differently), waves that are full, partly filled and
+# empty; as many equal keys at the threshold as one list of candidates holds, one fewer and one more, spread and side by side
+@pytest.mark.parametrize("equal", [63, 64, 65])
+@pytest.mark.parametrize("n", [70, 2047, 2048, 2050, 8191, 16384, 32767, 40000])
+def test_selection_of_mixed_waves(H, n, equal):
+    """The retained positions are the oracle's, bit for bit, with budgets that take none, some and all of the equal keys."""
+    announce(f"selection of {n}, {equal} equal")
+    rng = np.random.default_rng(n + equal)
+    S = rng.random((1, 2, n), dtype=np.float32)
+    S[0, 0, n // 3: n // 3 + n // 7] -= np.float32(2.0)
+    above = n // 40
+    order = np.argsort(-S[0], axis=1, kind="stable")
+    S[0, 0, order[0, above: above + equal]] = np.float32(0.97)                     # spread
+    S[0, 0, order[0, :above]] = np.float32(1.5) + S[0, 0, order[0, :above]]
+    S[0, 1, n // 2: n // 2 + min(equal, n - n // 2)] = np.float32(7.0)             # side by side
+    q = np.zeros((1, 1, 2, 1, 128), dtype=np.uint16)
+    k = np.zeros((1, n, 2, 128), dtype=np.uint16)
+    prob = H.Problem(q, k, k, 2, None, "hnd")
+    dev = torch.from_numpy(S).cuda()
+    for budget in sorted({b for b in (1, above, above + 1, above + equal - 1, above + equal, above + equal + 1, 30) if 1 <= b < n}):
+        idx, count = prob.topk(dev, budget)
+        for kv in range(2):
+            got = idx.cpu().numpy()[0, 0, kv][:int(count[0, 0, kv])]
+            assert np.array_equal(got, O.topk(S[0, kv].astype(np.float64), budget)), (budget, kv)
+
+
 # ragged batches too large for the tile form (more than 65536 units): one, two and four row blocks' kernels, teams of two,
 # up to and beyond the 64 sequences that a wave looks up by itself
 @pytest.mark.parametrize("batch", [40, 64, 65, 100])
