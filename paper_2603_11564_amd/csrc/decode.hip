@@ -350,17 +350,20 @@ int launch_decode(int64_t heads, const DecodeParams& p, hipStream_t stream) {
   return DAPQ_OK;
 }
 
-// Slices per head: every slice reads all of K_c, so they pay only while most compute units would have no workgroup.  One layer,
-// us with four / two / one slice:
-//   4 query heads per KV head, 983 rows    32 heads 7.1 / 7.8 / 8.7   40: 7.2 / 7.9 / 8.8   64: 7.8 / 8.3 / 9.0   96: 15.3 / 10.2 / 10.2
-//                                          128: 19.2 / 13.3 / 12.1    144: 25.9 / 19.7 / 13.0
-//   4, 256 rows                            40: 4.9 / 5.5 / 5.6        96: 8.5 / 5.4 / 5.5   144: 12.5 / 9.7 / 5.7
-//   8, 4096 rows                           8: 19.4 / 21.5 / 30.1      32: 27.8 / 23.3 / 30.1   64: 56.9 / 30.6 / 30.2   128: 112 / 60 / 42
-// The lines are between where short and where long caches would have them: of these, 128 heads of 4096 rows lose most (1.43 times).
+// Slices per head: every slice reads all of K_c, so they pay only while their workgroups have a compute unit each (four slices up to
+// 64 heads, two up to 128) and the caches of all heads together are not so large that the second and further readers of K_c
+// find it gone.  One layer, us with four / two / one slice:
+//   4 query heads per KV head, 256 rows    32 heads 5.0 / 5.6 / 5.9   64: 5.3 / 5.8 / 5.7     80: 8.7 / 6.0 / 5.9    160: 12.9 / 10.1 / 6.2
+//                              983         32: 7.4 / 7.9 / 8.9        64: 8.2 / 8.7 / 9.2     96: 15.5 / 10.6 / 10.5 128: 19.3 / 13.6 / 12.5
+//                              2048        40: 12.5 / 12.8 / 14.5     48: 15.1 / 13.1 / 14.9  56: 18.4 / 14.1 / 14.8 64: 22.0 / 15.4 / 15.0
+//                              4096        24: 20.5 / 21.0 / 23.7     32: 25.6 / 21.5 / 24.1  48: 39.5 / 24.2 / 25.0 56: 47.2 / 26.6 / 25.1
+//   8, 983                                 64: 9.5 / 10.1 / 12.5      96: 17.1 / 11.5 / 12.9  128: 21.3 / 15.2 / 14.2
+//   8, 4096                                24: 22.5 / 22.9 / 30.8     32: 27.9 / 23.6 / 30.9  64: 58.2 / 30.6 / 31.0 80: 74.8 / 37.1 / 31.2
 template <int HT>
 int launch_decode_slices(int64_t heads, const DecodeParams& p, hipStream_t stream) {
-  if (heads <= 32) return launch_decode<HT, 2, 8>(heads, p, stream);
-  if (heads <= 128) return launch_decode<HT, 4, 8>(heads, p, stream);
+  const int64_t rows = heads * p.budget;
+  if (heads <= 64 && (rows <= 88 * 1024 || heads <= 24)) return launch_decode<HT, 2, 8>(heads, p, stream);
+  if (heads <= 128 && (rows <= (HT == 1 ? 112 : 136) * 1024 || heads <= (HT == 1 ? 48 : 64))) return launch_decode<HT, 4, 8>(heads, p, stream);
   return launch_decode<HT, 8, 4>(heads, p, stream);
 }
 

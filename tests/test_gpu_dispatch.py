@@ -138,6 +138,23 @@ def test_decode_slices(H, rows, g, layers, batch, hkv):
     assert (got[want == 0] == 0).all()
 
 
+# the lines between four, two and one slice: by the number of heads (64, 128; long caches: 24, 48 and, from 5 query heads per KV head
+# on, 64) and by heads x rows
+@pytest.mark.parametrize("heads,rows,g", [(64, 1408, 4), (64, 1409, 4), (65, 40, 4), (24, 4096, 2), (25, 4096, 2), (128, 896, 4),
+                                          (128, 897, 4), (129, 100, 1), (48, 4096, 1), (49, 4096, 1), (128, 1088, 8), (128, 1089, 5),
+                                          (64, 2500, 8), (65, 2500, 8)])
+def test_decode_lines_between_slices(H, heads, rows, g):
+    """|error| as in the other decode tests, for full and half full heads."""
+    announce(f"decode: {heads} heads, rows={rows} g={g}")
+    rng = np.random.default_rng(heads + rows)
+    f = lambda *s: rng.standard_normal(s, dtype=np.float32)  # noqa: E731
+    q, k, v = (W.to_bf16_bits(x) for x in (2 * f(heads, g, 128), f(heads, 1, rows, 128), f(heads, 1, rows, 128)))
+    counts = np.array([rows, rows // 2])[np.arange(heads) % 2].reshape(heads, 1)
+    want = decode_want(q, k, v, counts)
+    got = decode_call(H, q, k, v, counts, 1)
+    assert (np.abs(got - want) <= 1e-5 * np.abs(O.bf16_bits_to_f64(v)).max() + 1e-4 * np.abs(want)).all()
+
+
 # the three slice counts (up to 32 heads, up to 128, more), both head tiles
 @pytest.mark.parametrize("batch", [2, 9, 33])
 @pytest.mark.parametrize("g", [4, 5])
