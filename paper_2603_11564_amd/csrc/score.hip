@@ -8,7 +8,8 @@
 // workgroup -- one row group, at most 4 chunks per sequence of a dense batch -- dapq_score runs both passes in
 // one launch (score_fused_kernel: the same two walks, the merge in between through LDS).
 // Calls too small to fill the chip that way go through score_tile_pass1_kernel and score_tile_pass2_kernel instead: a
-// workgroup per 128 keys whose waves share out the query rows (make_score_plan draws the line).
+// workgroup per 32 to 256 keys whose waves share out the query rows (make_score_plan draws the line).  Ragged batches go through the
+// wave kernels in segments of the packed key axis (Segments).
 //
 // Work split.  The unit of work is ONE wave (four independent ones are launched as a workgroup).  It keeps a group of up to 256 Q rows of one KV head in
 // registers as MFMA operand fragments (eight 32-row blocks = 256 registers, pinned to the
@@ -1737,8 +1738,8 @@ int launch_fused(const dapq_shape* s, const ScorePlan& plan, ScoreParams p, hipS
 }
 
 // Whether pass 2 of the tile form merges the partials itself: the threads of a workgroup can hold every sequence's, and
-// there is a compute unit for every workgroup (4096 keys of one layer: 18.7 -> 17.6 us; 8191, two workgroups to a compute
-// unit: 25.5 -> 27.2).
+// there is a compute unit for every workgroup (tiles of 128 keys, one layer: 4096 keys 18.7 -> 17.6 us; 8191, two workgroups to a
+// compute unit: 25.5 -> 27.2).
 bool tile_merges(const dapq_shape* s, const ScorePlan& plan) {
   if (!plan.tile || !plan.stage_q || plan.max_chunks * s->n_kv_heads * s->n_layers > simd_count() / 4) return false;
   const int64_t longest = s->cu_seqlens == nullptr ? s->total_tokens / s->batch : s->total_tokens;
