@@ -161,12 +161,13 @@ static int dense_chunk_of_two(const dapq_shape* s, int64_t heads, const ScorePla
 // its share of the key axis, whatever the lengths of the sequences.  Of the numbers that fill 1, 2, ... 16 rounds the one with the
 // least to do: a round's start-up (ring, queries) costs about what a two-hundredth of a head's keys do.  (At most 2^26 keys to a
 // segment, for the offsets in it.)  It does not fall with the tokens, so that fewer of them never need a larger workspace.
-static int ragged_segments(int64_t streams, int64_t wave_slots, int64_t total_tokens) {
+// `most`: no more of them (1 if not even one round of waves is that few).
+static int ragged_segments(int64_t streams, int64_t wave_slots, int64_t total_tokens, int64_t most) {
   int64_t best = 1;
   double least = INFINITY;
   for (int64_t rounds = 1; rounds <= 16; ++rounds) {
     const int64_t n = rounds * wave_slots / streams;
-    if (n < 1) continue;
+    if (n < 1 || n > most) continue;
     const double cost = (double)rounds * (1.0 / (double)n + 0.005);
     if (cost < least) {
       least = cost;
@@ -175,6 +176,43 @@ static int ragged_segments(int64_t streams, int64_t wave_slots, int64_t total_to
   }
   const int64_t fewest = (total_tokens >> 26) + 1;
   return (int)(best > fewest ? best : fewest);
+}
+
+// Whether a ragged shape in chunks of a power of two keys, the one with the least work per wave slot and half a chunk of tail, fits the
+// array of dapq_score_static: those shapes it has always served.
+static bool ragged_chunks_fit_static(const dapq_shape* s, int64_t heads, const ScorePlan& p, int64_t wave_slots) {
+  const int64_t streams = heads * p.n_groups, mean = s->total_tokens / s->batch;
+  int64_t best = INT64_MAX;
+  int chunk = kMinChunkKeys;
+  for (int c = kMaxChunkKeys; c >= kMinChunkKeys; c /= 2) {
+    const int64_t units = streams * ((s->total_tokens + c - 1) / c + s->batch / 2);
+    const int64_t cost = (streams * s->total_tokens + units * 256) / wave_slots + (c <= mean ? c / 2 : mean / 2 + (c - mean) / 4);
+    if (cost < best) {
+      best = cost;
+      chunk = c;
+    }
+  }
+  ScorePlan t = p;
+  t.segments = 0;
+  return finish_score_plan(s, heads, chunk, &t) == DAPQ_OK && t.total_bytes <= DAPQ_STATIC_SCRATCH_BYTES;
+}
+
+// Takes fewer segments to a ragged plan in the wave form, so that it fits the array of dapq_score_static.  All such plans ask for the
+// whole array: fewer tokens then never need a larger workspace.
+static void fit_static_scratch(const dapq_shape* s, int64_t heads, int64_t wave_slots, ScorePlan* p) {
+  const int64_t per_segment = (int64_t)sizeof(float) * 2 * heads * p->rows_pad;
+  const int64_t over = (int64_t)(p->total_bytes - DAPQ_STATIC_SCRATCH_BYTES) + 256;
+  int64_t most = p->segments - over / per_segment;
+  for (int tries = 0; tries < 3 && most >= 1; ++tries, --most) {
+    ScorePlan t = *p;
+    t.segments = ragged_segments(heads * p->n_groups, wave_slots, s->total_tokens, most);
+    // (not even one round of waves: as many as there is room for)
+    if (wave_slots / (heads * p->n_groups) > most && t.segments < most) t.segments = (int)most;
+    if (finish_score_plan(s, heads, 32, &t) != DAPQ_OK || t.total_bytes > DAPQ_STATIC_SCRATCH_BYTES) continue;
+    t.total_bytes = DAPQ_STATIC_SCRATCH_BYTES;
+    *p = t;
+    return;
+  }
 }
 
 int make_score_plan(const dapq_shape* s, size_t workspace_bytes, ScorePlan* p) {
@@ -214,8 +252,14 @@ int make_score_plan(const dapq_shape* s, size_t workspace_bytes, ScorePlan* p) {
       if (finish_score_plan(s, heads, two, &t) == DAPQ_OK && t.total_bytes <= DAPQ_STATIC_SCRATCH_BYTES) *p = t;
     }
   } else {
-    p->segments = ragged_segments(heads * p->n_groups, kWaveSlots, s->total_tokens);
+    p->segments = ragged_segments(heads * p->n_groups, kWaveSlots, s->total_tokens, INT64_MAX);
     rc = finish_score_plan(s, heads, 32, p);
+    // A line of room, not of time: a shape that dapq_score_static has always served is still served, by the same kernels as
+    // dapq_score's; and a workspace that was sized for a longer batch of that kind is enough.
+    if (rc == DAPQ_OK && p->total_bytes > DAPQ_STATIC_SCRATCH_BYTES &&
+        (ragged_chunks_fit_static(s, heads, *p, kWaveSlots) ||
+         (workspace_bytes >= DAPQ_STATIC_SCRATCH_BYTES && p->total_bytes > workspace_bytes)))
+      fit_static_scratch(s, heads, kWaveSlots, p);
   }
   if (rc != DAPQ_OK) return rc;
 

@@ -49,7 +49,7 @@ def test_static_scratch_matches_caller_workspace_twice_in_a_row():
 
 
 def test_static_scratch_serves_a_ragged_batch():
-    """A ragged batch keeps a prefix of chunk counts and the ticket counter of its work list in the scratch array; both
+    """A ragged batch keeps its partial sums (with many sequences a prefix of chunk counts too) in the scratch array; they
     are rewritten by every call, so calls in a row (another batch in between) give the scores of dapq_score."""
     rng = np.random.default_rng(13)
     lens = [700, 0, 45, 1300]
@@ -67,6 +67,29 @@ def test_static_scratch_serves_a_ragged_batch():
     torch.cuda.synchronize()
     assert torch.equal(S1, ref_ragged) and torch.equal(S2, ref_dense) and torch.equal(S3, ref_ragged)
     assert_scores_close(S1.cpu().numpy(), O.score(ragged.q_bits, ragged.k_bits, 2, cu, 128 ** -0.5), "static ragged")
+
+
+@pytest.mark.parametrize("heads,n_pseudo,lens", [
+    (8, 256, [10] * 100 + [0, 31, 33]),                     # all segments of the wave form would ask for more than the array; tiles run
+    (2, 1024, [0, 2000, 3, 3610] + [1940] * 27),        # tiles do not fit it: the wave form with as many segments as there is room for
+])
+def test_static_scratch_serves_ragged_batches_with_fewer_segments(heads, n_pseudo, lens):
+    rng = np.random.default_rng(17)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    q = O.f64_to_bf16_bits(rng.standard_normal((1, len(lens), heads, n_pseudo, 128)))
+    k = O.f64_to_bf16_bits(rng.standard_normal((1, int(cu[-1]), heads, 128)))
+    prob = Problem(q, k, k, heads, cu, "thd", 128 ** -0.5)
+    assert D.workspace_bytes(prob.shape) == D.score_static_capacity()
+    ref, S = prob.score(), new_scores(prob)
+    D.dapq_score_static(prob.shape, prob.q, prob.k, S)
+    torch.cuda.synchronize()
+    assert torch.equal(S, ref)
+    # the first, a middle and the last sequences against the oracle
+    picks = [b for b in (0, 1, 2, len(lens) // 2, len(lens) - 2, len(lens) - 1) if lens[b]]
+    S_h = S.cpu().numpy()
+    for b in picks:
+        kb = prob.k_bits[:, cu[b]:cu[b + 1]]
+        assert_scores_close(S_h[..., cu[b]:cu[b + 1]], O.score(prob.q_bits[:, b:b + 1], kb, heads, None, 128 ** -0.5), f"sequence {b}")
 
 
 def test_static_scratch_one_kernel_shape():
