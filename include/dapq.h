@@ -74,9 +74,10 @@ typedef struct dapq_shape {
 
 /* Bytes of device workspace dapq_score / dapq_score_stats / dapq_score_accumulate need for this shape
  * (one figure covers all of them).  Returns 0 if the shape is invalid.
- * Small shapes may ask for more than larger ones: their kernels, which share out a short call over the whole chip, hold
- * more partial sums.  A workspace below the figure that holds those of the kernels for larger shapes (one sized for a longer prompt,
- * say) is taken all the same, and those kernels run: slower, and equal up to the order of fp32 sums. */
+ * Small shapes may ask for more than larger ones: their calls, shared out over the whole chip, hold more partial sums.  The
+ * figure of a shape is taken all the same for every shape that exceeds it in nothing (layers, sequences, heads, pseudo queries, keys
+ * of a sequence or, in a ragged batch, of all of them), which then runs in fewer and longer shares: slower, and equal up to
+ * the order of fp32 sums. */
 size_t dapq_workspace_bytes(const dapq_shape* shape);
 
 /* Message for the last error returned on the calling thread ("" if none). Host pointer, owned by the library. */

@@ -82,6 +82,30 @@ int check_shape(const dapq_shape* s, bool need_q, bool need_k, bool need_v) {
   return DAPQ_OK;
 }
 
+// Lays out the workspace of a plan whose rows are split and whose partial sums are counted.
+static void carve_workspace(const dapq_shape* s, int64_t heads, ScorePlan* p) {
+  size_t off = 0;
+  p->off_cu_chunks = off;
+  off = align_up(off + sizeof(int32_t) * ((size_t)s->batch + 1), 256);
+  off += 256;  // (nothing lies here: workspaces have always had it)
+  p->off_parts = off;
+  off = align_up(off + sizeof(float) * (p->tile ? 1 : 2) * (size_t)heads * (size_t)p->max_chunks * p->rows_pad, 256);
+  p->off_lse2 = off;
+  off = align_up(off + sizeof(float) * (size_t)s->n_layers * s->batch * s->n_q_heads * s->n_pseudo, 256);
+  p->off_partial = off;
+  if (p->n_groups > 1) off = align_up(off + sizeof(float) * (size_t)(p->n_groups - 1) * (size_t)heads * (size_t)s->total_tokens, 256);
+  p->total_bytes = off;
+}
+// How many partial sums of a row a workspace of `room` bytes holds in the wave form (negative: it does not even hold the rest).
+static int64_t partials_that_fit(const dapq_shape* s, int64_t heads, ScorePlan p, size_t room) {
+  p.max_chunks = 0;
+  carve_workspace(s, heads, &p);
+  if (room < p.total_bytes) return -1;
+  // (a row block's partials are whole multiples of 256 bytes)
+  const uint64_t most = (room - p.total_bytes) / (sizeof(float) * 2 * (size_t)heads * p.rows_pad);
+  return most < ((uint64_t)1 << 31) ? (int64_t)most : ((int64_t)1 << 31);
+}
+
 // The plan's chunks along the key axis and its workspace, once the rows are split and the chunk is chosen.
 static int finish_score_plan(const dapq_shape* s, int64_t heads, int chunk, ScorePlan* p) {
   p->chunk_keys = chunk;
@@ -96,20 +120,11 @@ static int finish_score_plan(const dapq_shape* s, int64_t heads, int chunk, Scor
   if (p->max_chunks < 1) p->max_chunks = 1;
   DAPQ_REQUIRE(p->max_chunks < ((int64_t)1 << 31), DAPQ_ERR_UNSUPPORTED, "too many key chunks");
   DAPQ_REQUIRE(p->n_groups <= 65535, DAPQ_ERR_UNSUPPORTED, "too many query rows per KV head");
-
-  size_t off = 0;
-  p->off_cu_chunks = off;
-  off = align_up(off + sizeof(int32_t) * ((size_t)s->batch + 1), 256);
-  off += 256;  // (nothing lies here: workspaces have always had it)
-  p->off_parts = off;
-  off = align_up(off + sizeof(float) * (p->tile ? 1 : 2) * (size_t)heads * (size_t)p->max_chunks * p->rows_pad, 256);
-  p->off_lse2 = off;
-  off = align_up(off + sizeof(float) * (size_t)s->n_layers * s->batch * s->n_q_heads * s->n_pseudo, 256);
-  p->off_partial = off;
-  if (p->n_groups > 1) off = align_up(off + sizeof(float) * (size_t)(p->n_groups - 1) * (size_t)heads * (size_t)s->total_tokens, 256);
-  p->total_bytes = off;
+  carve_workspace(s, heads, p);
   return DAPQ_OK;
 }
+
+constexpr int64_t kStartKeys = 160;  // see dense_chunk
 
 // Keys per wave of a dense batch.  The machine runs wave_slots waves at a time, each for as long as its chunk; a wave pays a fixed
 // start-up (Q fragments, ring fill) worth about kStartKeys keys.  A sequence is cut into equal chunks of whole sub-blocks, as many
@@ -119,8 +134,8 @@ static int finish_score_plan(const dapq_shape* s, int64_t heads, int chunk, Scor
 // Powers of two -> equal chunks, with the rotation, us: 32 layers, 20000 keys, 256 rows 789 -> 690, 128 rows 518 -> 468; 8 layers,
 // 256 rows, 10000 keys 140 -> 111, 50000 keys 484 -> 441; 2 layers, 512 rows, 20000 keys 133 -> 103; 16 layers, 4 KV heads, 512 rows,
 // 2 prompts of 9999 keys 418 -> 329; prompts of 700 to 3000 keys in batches of 5 to 16 within 1 %.
-static int dense_chunk(const dapq_shape* s, int64_t heads, const ScorePlan& p, int64_t wave_slots) {
-  constexpr int64_t kStartKeys = 160;
+// `most`: no more chunks per sequence (at least what the longest chunks make).
+static int dense_chunk(const dapq_shape* s, int64_t heads, const ScorePlan& p, int64_t wave_slots, int64_t most) {
   const int64_t L = s->total_tokens / s->batch, streams = heads * p.n_groups * s->batch;
   int64_t best = INT64_MAX;
   int chunk = kMinChunkKeys;
@@ -128,16 +143,18 @@ static int dense_chunk(const dapq_shape* s, int64_t heads, const ScorePlan& p, i
     // (r = 0: as few chunks as a chunk may be long)
     int64_t n = r == 0 ? 1 : r * wave_slots / streams;
     if (n < 1) continue;
+    if (n > most) n = most;
     int64_t c = ((L + n - 1) / n + 31) / 32 * 32;
     c = c < kMinChunkKeys ? kMinChunkKeys : (c > kMaxChunkKeys ? kMaxChunkKeys : c);
     n = (L + c - 1) / c;
+    if (n > most) continue;
     const int64_t slots = p.n_groups == 1 && n == 3 ? wave_slots / 4 * 3 : wave_slots;
     const int64_t cost = (streams * n + slots - 1) / slots * ((L < c ? L : c) + kStartKeys);
     if (cost < best) {
       best = cost;
       chunk = (int)c;
     }
-    if (c == kMinChunkKeys) break;
+    if (c == kMinChunkKeys || n == most) break;
   }
   return chunk;
 }
@@ -148,7 +165,7 @@ static int dense_chunk_of_two(const dapq_shape* s, int64_t heads, const ScorePla
   int chunk = kMinChunkKeys;
   for (int c = kMaxChunkKeys; c >= kMinChunkKeys; c /= 2) {
     const int64_t units = heads * p.n_groups * s->batch * ((L + c - 1) / c);
-    const int64_t cost = (units + wave_slots - 1) / wave_slots * ((L < c ? L : c) + 160);
+    const int64_t cost = (units + wave_slots - 1) / wave_slots * ((L < c ? L : c) + kStartKeys);
     if (cost < best) {
       best = cost;
       chunk = c;
@@ -197,22 +214,59 @@ static bool ragged_chunks_fit_static(const dapq_shape* s, int64_t heads, const S
   return finish_score_plan(s, heads, chunk, &t) == DAPQ_OK && t.total_bytes <= DAPQ_STATIC_SCRATCH_BYTES;
 }
 
-// Takes fewer segments to a ragged plan in the wave form, so that it fits the array of dapq_score_static.  All such plans ask for the
-// whole array: fewer tokens then never need a larger workspace.
-static void fit_static_scratch(const dapq_shape* s, int64_t heads, int64_t wave_slots, ScorePlan* p) {
-  const int64_t per_segment = (int64_t)sizeof(float) * 2 * heads * p->rows_pad;
-  const int64_t over = (int64_t)(p->total_bytes - DAPQ_STATIC_SCRATCH_BYTES) + 256;
-  int64_t most = p->segments - over / per_segment;
-  for (int tries = 0; tries < 3 && most >= 1; ++tries, --most) {
-    ScorePlan t = *p;
-    t.segments = ragged_segments(heads * p->n_groups, wave_slots, s->total_tokens, most);
-    // (not even one round of waves: as many as there is room for)
-    if (wave_slots / (heads * p->n_groups) > most && t.segments < most) t.segments = (int)most;
-    if (finish_score_plan(s, heads, 32, &t) != DAPQ_OK || t.total_bytes > DAPQ_STATIC_SCRATCH_BYTES) continue;
-    t.total_bytes = DAPQ_STATIC_SCRATCH_BYTES;
-    *p = t;
-    return;
+// The workspace that a shape asks for serves every shape that is no larger in layers, heads, rows, sequences and (dense) keys of a
+// sequence or (ragged) keys: plans do not fall and rise with the shape, a smaller one may want more partial sums, and it then makes do
+// with fewer chunks or segments.  For that no shape asks for less than kRoomWaves waves' partials (or what it has at all: of all its
+// chunks of the fewest keys; a wave each), and none is refused that many: half the machine's waves, which every plan of several
+// launches fills anyway.
+constexpr int64_t kRoomWaves = 512;
+
+// Fewest chunks of a sequence, of those that a shape makes do with.
+static int64_t dense_fewest(int64_t L, int64_t streams) {
+  const int64_t all = (L + kMinChunkKeys - 1) / kMinChunkKeys, longest = (L + kMaxChunkKeys - 1) / kMaxChunkKeys;
+  const int64_t some = all < kRoomWaves / streams ? all : kRoomWaves / streams;
+  return some > longest ? some : (longest > 1 ? longest : 1);
+}
+// What a dense shape asks for at least.
+static size_t dense_least_bytes(const dapq_shape* s, int64_t heads, ScorePlan p) {
+  const int64_t L = s->total_tokens / s->batch, streams = heads * p.n_groups * s->batch;
+  const int64_t all = streams * ((L + kMinChunkKeys - 1) / kMinChunkKeys);
+  const int64_t waves = all < kRoomWaves ? all : kRoomWaves;
+  p.max_chunks = 0;
+  carve_workspace(s, heads, &p);
+  return p.total_bytes + sizeof(float) * 2 * (size_t)waves * p.row_blocks * 32;
+}
+// Fewer and longer chunks, in a workspace of `room` bytes that does not hold the plan's.  (The power of two where it fits and is long:
+// see make_score_plan.)
+static void fit_dense(const dapq_shape* s, int64_t heads, int64_t wave_slots, int two, size_t room, ScorePlan* p) {
+  const int64_t L = s->total_tokens / s->batch, streams = heads * p->n_groups * s->batch;
+  const int64_t most = partials_that_fit(s, heads, *p, room) / s->batch;
+  if (most < dense_fewest(L, streams)) return;
+  int chunk = dense_chunk(s, heads, *p, wave_slots, most);
+  if (chunk > two && two > 8192 && (L + two - 1) / two <= most) chunk = two;
+  ScorePlan t = *p;
+  t.unit_sums = chunk > two;
+  if (finish_score_plan(s, heads, chunk, &t) == DAPQ_OK && t.total_bytes <= room) *p = t;
+}
+
+// Fewer segments, in a workspace of `room` bytes that does not hold the plan's.  (Where all shapes that fit the array of
+// dapq_score_static ask for it whole, their plans may be of fewer waves than kRoomWaves.)
+static bool fit_ragged(const dapq_shape* s, int64_t heads, int64_t wave_slots, size_t room, ScorePlan* p) {
+  const int64_t streams = heads * p->n_groups, chunks = (s->total_tokens + kMinChunkKeys - 1) / kMinChunkKeys;
+  const int64_t most = partials_that_fit(s, heads, *p, room) - s->batch;
+  int64_t fewest = (s->total_tokens >> 26) + 1;
+  if (room < DAPQ_STATIC_SCRATCH_BYTES) {
+    const int64_t some = chunks < kRoomWaves / streams ? chunks : kRoomWaves / streams;
+    fewest = some > fewest ? some : fewest;
   }
+  if (most < fewest) return false;
+  ScorePlan t = *p;
+  t.segments = ragged_segments(streams, wave_slots, s->total_tokens, most);
+  // (not even one round of waves: as many as there is room for)
+  if (wave_slots / streams > most && t.segments < most) t.segments = (int)most;
+  if (finish_score_plan(s, heads, 32, &t) != DAPQ_OK || t.total_bytes > room) return false;
+  *p = t;
+  return true;
 }
 
 int make_score_plan(const dapq_shape* s, size_t workspace_bytes, ScorePlan* p) {
@@ -236,7 +290,7 @@ int make_score_plan(const dapq_shape* s, size_t workspace_bytes, ScorePlan* p) {
   int rc;
   if (s->cu_seqlens == nullptr) {
     const int two = dense_chunk_of_two(s, heads, *p, kWaveSlots);
-    int chunk = dense_chunk(s, heads, *p, kWaveSlots);
+    int chunk = dense_chunk(s, heads, *p, kWaveSlots, INT64_MAX);
     // A lane of pass 1 adds up its half of a chunk one by one, and what that costs in accuracy grows with the chunk (2^14 keys:
     // 1.7e-5 of a score): chunks longer than the power of two form their sums in two steps, which is as fast and more accurate.
     // (Not so the others, whose results stay what they were; and powers of two above 2^13 are not exceeded, since two results
@@ -251,15 +305,20 @@ int make_score_plan(const dapq_shape* s, size_t workspace_bytes, ScorePlan* p) {
       t.unit_sums = false;
       if (finish_score_plan(s, heads, two, &t) == DAPQ_OK && t.total_bytes <= DAPQ_STATIC_SCRATCH_BYTES) *p = t;
     }
+    if (rc == DAPQ_OK) {
+      const size_t least = dense_least_bytes(s, heads, *p);
+      if (p->total_bytes < least) p->total_bytes = least;
+      if (p->total_bytes > workspace_bytes) fit_dense(s, heads, kWaveSlots, two, workspace_bytes, p);
+    }
   } else {
     p->segments = ragged_segments(heads * p->n_groups, kWaveSlots, s->total_tokens, INT64_MAX);
     rc = finish_score_plan(s, heads, 32, p);
     // A line of room, not of time: a shape that dapq_score_static has always served is still served, by the same kernels as
-    // dapq_score's; and a workspace that was sized for a longer batch of that kind is enough.
-    if (rc == DAPQ_OK && p->total_bytes > DAPQ_STATIC_SCRATCH_BYTES &&
-        (ragged_chunks_fit_static(s, heads, *p, kWaveSlots) ||
-         (workspace_bytes >= DAPQ_STATIC_SCRATCH_BYTES && p->total_bytes > workspace_bytes)))
-      fit_static_scratch(s, heads, kWaveSlots, p);
+    // dapq_score's.  All such plans ask for the whole array: fewer tokens then never need a larger workspace.
+    if (rc == DAPQ_OK && p->total_bytes > DAPQ_STATIC_SCRATCH_BYTES && ragged_chunks_fit_static(s, heads, *p, kWaveSlots) &&
+        fit_ragged(s, heads, kWaveSlots, DAPQ_STATIC_SCRATCH_BYTES, p))
+      p->total_bytes = DAPQ_STATIC_SCRATCH_BYTES;
+    if (rc == DAPQ_OK && p->total_bytes > workspace_bytes) fit_ragged(s, heads, kWaveSlots, workspace_bytes, p);
   }
   if (rc != DAPQ_OK) return rc;
 
@@ -298,7 +357,7 @@ int make_score_plan(const dapq_shape* s, size_t workspace_bytes, ScorePlan* p) {
   }
   rc = finish_score_plan(s, heads, keys, &t);
   if (rc != DAPQ_OK) return rc;
-  // The figure is no smaller than the wave form's, which a caller may have sized its workspace for by another shape.
+  // The figure is no smaller than the wave form's: smaller shapes may run in that (see kRoomWaves).
   if (t.total_bytes < p->total_bytes) t.total_bytes = p->total_bytes;
   // The partials of the tile form can take more room than the wave form does (the shapes above: 4.0 MB at 29 696 tokens).  A workspace
   // that holds only the wave form gets the wave form.  And a shape that dapq_score_static serves is still served, by the same kernels

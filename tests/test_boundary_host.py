@@ -2,6 +2,7 @@
 and rejects bad arguments on the host before anything is enqueued."""
 import ctypes as C
 import os
+import random
 import re
 
 import pytest
@@ -272,6 +273,46 @@ def test_a_workspace_sized_for_a_longer_batch_serves_shorter_ones(lib):
         assert lib.dapq_score_stats(sp, FAKE, FAKE, FAKE, FAKE, enough, None) == ERR_HIP, lib.dapq_last_error()
         assert lib.dapq_score_accumulate(sp, FAKE, FAKE, FAKE, FAKE, FAKE, enough, None) == ERR_HIP, lib.dapq_last_error()
         assert lib.dapq_score(sp, FAKE, FAKE, FAKE, FAKE, 1 << 18, None) == ERR_WORKSPACE
+
+
+def test_a_workspace_sized_for_a_larger_shape_serves_smaller_ones(lib):
+    """Fewer layers, sequences, heads, rows or keys can make a plan of more partial sums: in the workspace of the larger shape such a call
+    makes do with fewer chunks (dense) or segments (ragged).  It gets as far as its launch, which reports that there is no GPU here."""
+    if os.path.exists("/dev/kfd"):
+        pytest.skip("would be launched, with pointers that are none")
+
+    def shape(layers, batch, kv_heads, group, n, keys, ragged):  # keys: of a sequence, of a ragged batch all
+        tokens = keys if ragged else keys * batch
+        s = D.make_shape(n_layers=layers, batch=batch, n_q_heads=kv_heads * group, n_kv_heads=kv_heads, n_pseudo=n, total_tokens=tokens,
+                         k_strides=(tokens * kv_heads * 128, 0, 128, kv_heads * 128),
+                         q_strides=(batch * kv_heads * group * n * 128, kv_heads * group * n * 128, n * 128, 128), scale=128 ** -0.5)
+        s.cu_seqlens = FAKE if ragged else None                                             # never dereferenced here
+        return s
+
+    def serves(large, small, ragged):
+        room, sp = D.workspace_bytes(shape(*large, ragged)), C.byref(shape(*small, ragged))
+        for rc in (lib.dapq_score(sp, FAKE, FAKE, FAKE, FAKE, room, None),
+                   lib.dapq_score_stats(sp, FAKE, FAKE, FAKE, FAKE, room, None),
+                   lib.dapq_score_accumulate(sp, FAKE, FAKE, FAKE, FAKE, FAKE, room, None)):
+            assert rc == ERR_HIP, (large, small, ragged, lib.dapq_last_error())
+
+    serves((1, 1, 8, 4, 32, 20800), (1, 1, 8, 4, 32, 19400), False)
+    serves((2, 1, 8, 4, 64, 40314), (2, 1, 8, 4, 64, 36685), False)
+    serves((32, 16, 8, 4, 32, 93604), (32, 13, 8, 4, 32, 93604), False)
+    serves((16, 5, 8, 4, 32, 865), (15, 5, 8, 4, 32, 865), True)
+    serves((257, 1, 1, 4, 64, 384), (256, 1, 1, 4, 64, 384), False)                         # one chunk a wave, then three
+    rng = random.Random(3)
+    for _ in range(1500):
+        ragged = rng.random() < 0.5
+        large = [rng.choice((1, 2, 8, 15, 16, 32, 80)), int(2 ** rng.uniform(0, 8)), rng.choice((1, 2, 3, 4, 8)),
+                 rng.choice((1, 2, 4, 5, 8)), rng.choice((7, 16, 32, 37, 64, 128, 256)), int(2 ** rng.uniform(0, 17))]
+        small = list(large)
+        for i in rng.sample(range(6), rng.choice((1, 1, 2, 6))):
+            small[i] = max(1, int(large[i] * rng.uniform(0.3, 1.0)))
+        serves(large, small, ragged)
+    # a call is not made to do with anything: a workspace that fills less than half the chip with waves is one for another call
+    long = shape(1, 1, 8, 4, 64, 1 << 17, False)
+    assert lib.dapq_score(C.byref(long), FAKE, FAKE, FAKE, FAKE, D.workspace_bytes(long) // 3, None) == ERR_WORKSPACE
 
 
 def test_binding_raises_with_the_library_message():

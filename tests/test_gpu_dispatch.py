@@ -465,6 +465,42 @@ def test_equal_chunks_of_dense_batches(H, layers, batch, length, rows):
     assert np.abs(lse[:1].cpu().numpy() - oracle_lse2(q, k, 2, cu)).max() < 2e-4
 
 
+# calls whose own workspace would be larger than that of a larger shape, which they are given: longer chunks (sums in one step and, where
+# they are longer than the power of two, in two; one chunk per sequence; two row groups), fewer segments
+@pytest.mark.parametrize("rows,lens,layers,larger,ragged", [
+    (250, [4402], 28, 48, False), (250, [1491] * 3, 42, 64, False), (33, [1592] * 3, 41, 64, False), (33, [980] * 3, 72, 128, False),
+    (300, [1617] * 7, 20, 24, False), (300, [1293] * 7, 6, 8, False), (128, [4418], 18, 24, False),
+    (300, [2000, 0, 7, 3000, 401, 31, 70], 116, 128, True), (250, [3000, 3, 504], 66, 100, True), (128, [4660], 117, 128, True)])
+def test_calls_in_the_workspace_of_a_larger_shape(H, rows, lens, layers, larger, ragged):
+    """The oracle's scores and normalisers (the bars of the other score tests), the same bits in every layer and from the two separate
+    entry points; every layer is the same problem (layer strides of 0)."""
+    announce(f"workspace of {larger} layers: {layers} of {len(lens)}x{max(lens)}, rows={rows}")
+    q, k, v, cu = problem_bits(rows + layers, 1, lens, 2, 2, rows)
+    b = int(np.argmax(lens))
+    k[0, int(cu[b]) + 2 * lens[b] // 3, 1] = W.to_bf16_bits(30.0 * O.bf16_bits_to_f64(q[0, b, 1, 0]))
+    prob = H.Problem(q, k, v, 2, cu if ragged else None, "thd")
+    tokens = int(cu[-1])
+
+    def shape(n_layers):
+        return H.D.make_shape(n_layers=n_layers, batch=len(lens), n_q_heads=2, n_kv_heads=2, n_pseudo=rows, total_tokens=tokens,
+                              cu_seqlens=prob.cu, k_strides=(0, 0, 128, 256), q_strides=(0, 2 * rows * 128, rows * 128, 128),
+                              scale=128 ** -0.5)
+    room = H.D.workspace_bytes(shape(larger))
+    assert room < H.D.workspace_bytes(shape(layers))
+    guard = torch.full((room + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+    ws = guard[:room]
+    S, T = (torch.full((layers, 2, tokens), float("nan"), dtype=torch.float32, device="cuda") for _ in range(2))
+    lse = torch.full((layers, len(lens), 2, rows), float("nan"), dtype=torch.float32, device="cuda")
+    H.D.dapq_score(shape(layers), prob.q, prob.k, S, ws)
+    H.D.dapq_score_stats(shape(layers), prob.q, prob.k, lse, ws)
+    H.D.dapq_score_accumulate(shape(layers), prob.q, prob.k, lse, T, ws)
+    assert (guard[room:] == 0xA5).all()
+    assert torch.equal(S, T) and torch.equal(S, S[:1].expand_as(S)) and torch.equal(lse, lse[:1].expand_as(lse))
+    H.assert_scores_close(S[:1].cpu().numpy(), O.score(q, k, 2, cu), f"{lens} rows={rows}")
+    live = [i for i, n in enumerate(lens) if n]
+    assert np.abs(lse[:1].cpu().numpy()[:, live] - oracle_lse2(q, k, 2, cu)[:, live]).max() < 2e-4
+
+
 # segments that begin and end inside sequences, take in several, empty ones among them, or hold one sub-block; a head of one key
 @pytest.mark.parametrize("rows", [33, 128, 250, 300])
 @pytest.mark.parametrize("lens", [[1, 0, 31, 32, 33, 0, 0, 64, 900, 5, 0, 1300, 0], [0, 2500, 0, 65], [1], [0, 3, 0]],
