@@ -124,54 +124,81 @@ static int finish_score_plan(const dapq_shape* s, int64_t heads, int chunk, Scor
   return DAPQ_OK;
 }
 
-constexpr int64_t kStartKeys = 160;  // see dense_chunk
-
-// Keys per wave of a dense batch.  The machine runs wave_slots waves at a time, each for as long as its chunk; a wave pays a fixed
-// start-up (Q fragments, ring fill) worth about kStartKeys keys.  A sequence is cut into equal chunks of whole sub-blocks, as many
-// as fill 1, 2, ... 16 rounds; of these the number with the shortest rounds x (chunk + start-up).  Where all of a sequence's chunks
-// are the waves of one workgroup (dapq_score in one kernel: one row group, at most four chunks) three of them leave the fourth
-// SIMD of a compute unit idle.
-// Powers of two -> equal chunks, with the rotation, us: 32 layers, 20000 keys, 256 rows 789 -> 690, 128 rows 518 -> 468; 8 layers,
-// 256 rows, 10000 keys 140 -> 111, 50000 keys 484 -> 441; 2 layers, 512 rows, 20000 keys 133 -> 103; 16 layers, 4 KV heads, 512 rows,
-// 2 prompts of 9999 keys 418 -> 329; prompts of 700 to 3000 keys in batches of 5 to 16 within 1 %.
-// `most`: no more chunks per sequence (at least what the longest chunks make).
-static int dense_chunk(const dapq_shape* s, int64_t heads, const ScorePlan& p, int64_t wave_slots, int64_t most) {
-  const int64_t L = s->total_tokens / s->batch, streams = heads * p.n_groups * s->batch;
-  int64_t best = INT64_MAX;
-  int chunk = kMinChunkKeys;
-  for (int64_t r = 0; r <= 16; ++r) {
-    // (r = 0: as few chunks as a chunk may be long)
-    int64_t n = r == 0 ? 1 : r * wave_slots / streams;
-    if (n < 1) continue;
-    if (n > most) n = most;
-    int64_t c = ((L + n - 1) / n + 31) / 32 * 32;
-    c = c < kMinChunkKeys ? kMinChunkKeys : (c > kMaxChunkKeys ? kMaxChunkKeys : c);
-    n = (L + c - 1) / c;
-    if (n > most) continue;
-    const int64_t slots = p.n_groups == 1 && n == 3 ? wave_slots / 4 * 3 : wave_slots;
-    const int64_t cost = (streams * n + slots - 1) / slots * ((L < c ? L : c) + kStartKeys);
-    if (cost < best) {
-      best = cost;
-      chunk = (int)c;
-    }
-    if (c == kMinChunkKeys || n == most) break;
-  }
-  return chunk;
-}
-// The best power of two, which bounds what a chunk may do to accuracy and workspace (see make_score_plan).
+// The power of two with the shortest rounds x (chunk + a start-up of 160 keys), which bounds what a chunk may do to accuracy and
+// workspace (see make_score_plan).
 static int dense_chunk_of_two(const dapq_shape* s, int64_t heads, const ScorePlan& p, int64_t wave_slots) {
   const int64_t L = s->total_tokens / s->batch;
   int64_t best = INT64_MAX;
   int chunk = kMinChunkKeys;
   for (int c = kMaxChunkKeys; c >= kMinChunkKeys; c /= 2) {
     const int64_t units = heads * p.n_groups * s->batch * ((L + c - 1) / c);
-    const int64_t cost = (units + wave_slots - 1) / wave_slots * ((L < c ? L : c) + kStartKeys);
+    const int64_t cost = (units + wave_slots - 1) / wave_slots * ((L < c ? L : c) + 160);
     if (cost < best) {
       best = cost;
       chunk = c;
     }
   }
   return chunk;
+}
+
+// Time of both passes of a dense batch in chunks of c keys, in nanoseconds, as far as c decides it.  The machine runs wave_slots waves
+// at a time, each for as long as its chunk, and a round of waves pays a start-up (queries, ring fill).  Up to four chunks of a
+// sequence with one row group are the waves of one workgroup, which does both passes (dapq_score in one kernel): one start-up for both and
+// no merge between them, but a compute unit holds four such waves only if their number divides four.  Otherwise there are three
+// launches, the merge reads a row of partials per chunk, and with few rows workgroups of two waves, which an even number of chunks makes
+// that four does not divide, are placed badly (64 rows, 32 chunk streams: 20 chunks 48 us, 22 chunks 57, 23 chunks 48).
+// The constants lose least over 732 dense shapes (1 to 32 layers, 1 to 16 prompts of 130 to 131072 keys, 16 to 1024 rows), each timed in
+// some 20 chunk lengths: against the best power of two 0.906 of the time in the geometric mean, none above 1.09 (with a start-up of
+// 160 keys for both forms, and one to four chunks only where they fill the rounds: 0.940 and 1.85; the best of the lengths: 0.896).
+static int64_t dense_cost(const ScorePlan& p, int64_t streams, int64_t batch, int64_t L, int64_t c, int64_t wave_slots) {
+  const int64_t n = (L + c - 1) / c, walk = (L < c ? L : c) * (p.row_blocks == 8 ? 75 : (p.row_blocks == 4 ? 52 : 45));
+  if (p.n_groups == 1 && n <= 4) {
+    const int64_t workgroups = wave_slots / 4 * (n <= 1 ? 4 : 4 / n);
+    return (streams + workgroups - 1) / workgroups * (walk + 10000);
+  }
+  const bool pairs = p.row_blocks <= 4 && batch * n % 4 == 2;
+  return (streams * n + wave_slots - 1) / wave_slots * (walk + 15000) + 7500 + 120 * n + (pairs ? 6000 : 0);
+}
+
+struct DenseChunk {
+  int keys;      // 0: none
+  int64_t cost;  // see dense_cost
+};
+// Keys per wave of a dense batch, with at most `most` chunks per sequence (at least what the longest chunks make): the best power of
+// two (`two`), unless another number of equal chunks of whole sub-blocks is better by a hundredth: as many as fill 1, 2, ... 16
+// rounds of waves, or one to four.
+// A lane of pass 1 adds up its half of a chunk one by one, and what that costs in accuracy grows with the chunk (2^14 keys: 1.7e-5 of a
+// score): chunks longer than the power of two form their sums in two steps, which is as fast and more accurate.  (Not so the others,
+// whose results stay what they were; and powers of two above 2^13 are not exceeded, since two results that are both right would be that
+// far apart.)
+// Best power of two -> this, us: 32 layers, 256 rows, 19748 keys 784 -> 613; 16 layers, 512 rows, 2 prompts of 2556 keys 238 -> 182; 8
+// layers, 128 rows, 5 prompts of 2316 keys 122 -> 73.
+static DenseChunk dense_chunk(const dapq_shape* s, int64_t heads, const ScorePlan& p, int64_t wave_slots, int two, int64_t most) {
+  const int64_t L = s->total_tokens / s->batch, streams = heads * p.n_groups * s->batch;
+  DenseChunk best = {0, INT64_MAX};
+  if (most < 1) return best;
+  int64_t bar = INT64_MAX;  // what a chunk that is not the power of two has to stay below
+  const bool two_fits = (L + two - 1) / two <= most;
+  if (two_fits) {
+    best = {two, dense_cost(p, streams, s->batch, L, two, wave_slots)};
+    bar = best.cost - best.cost / 100;
+  }
+  auto consider = [&](int64_t n) {
+    n = n < most ? n : most;
+    int64_t c = ((L + n - 1) / n + 31) / 32 * 32;
+    c = c < kMinChunkKeys ? kMinChunkKeys : (c > kMaxChunkKeys ? kMaxChunkKeys : c);
+    if ((L + c - 1) / c > most || (c > two && two > 8192 && two_fits)) return false;
+    const int64_t cost = dense_cost(p, streams, s->batch, L, c, wave_slots);
+    if (cost < bar) {
+      best = {(int)c, cost};
+      bar = cost;
+    }
+    return c == kMinChunkKeys || n == most;  // more would not be more
+  };
+  for (int64_t n = 1; n <= (p.n_groups == 1 ? 4 : 1); ++n) consider(n);
+  for (int64_t r = 1; r <= 16; ++r)
+    if (r * wave_slots >= streams && consider(r * wave_slots / streams)) break;
+  return best;
 }
 
 // Segments per head of a ragged batch, `streams` heads x row groups: the waves run in whole rounds of wave_slots, each as long as
@@ -236,14 +263,12 @@ static size_t dense_least_bytes(const dapq_shape* s, int64_t heads, ScorePlan p)
   carve_workspace(s, heads, &p);
   return p.total_bytes + sizeof(float) * 2 * (size_t)waves * p.row_blocks * 32;
 }
-// Fewer and longer chunks, in a workspace of `room` bytes that does not hold the plan's.  (The power of two where it fits and is long:
-// see make_score_plan.)
+// Fewer and longer chunks, in a workspace of `room` bytes that does not hold the plan's.
 static void fit_dense(const dapq_shape* s, int64_t heads, int64_t wave_slots, int two, size_t room, ScorePlan* p) {
   const int64_t L = s->total_tokens / s->batch, streams = heads * p->n_groups * s->batch;
   const int64_t most = partials_that_fit(s, heads, *p, room) / s->batch;
   if (most < dense_fewest(L, streams)) return;
-  int chunk = dense_chunk(s, heads, *p, wave_slots, most);
-  if (chunk > two && two > 8192 && (L + two - 1) / two <= most) chunk = two;
+  const int chunk = dense_chunk(s, heads, *p, wave_slots, two, most).keys;
   ScorePlan t = *p;
   t.unit_sums = chunk > two;
   if (finish_score_plan(s, heads, chunk, &t) == DAPQ_OK && t.total_bytes <= room) *p = t;
@@ -290,20 +315,20 @@ int make_score_plan(const dapq_shape* s, size_t workspace_bytes, ScorePlan* p) {
   int rc;
   if (s->cu_seqlens == nullptr) {
     const int two = dense_chunk_of_two(s, heads, *p, kWaveSlots);
-    int chunk = dense_chunk(s, heads, *p, kWaveSlots, INT64_MAX);
-    // A lane of pass 1 adds up its half of a chunk one by one, and what that costs in accuracy grows with the chunk (2^14 keys:
-    // 1.7e-5 of a score): chunks longer than the power of two form their sums in two steps, which is as fast and more accurate.
-    // (Not so the others, whose results stay what they were; and powers of two above 2^13 are not exceeded, since two results
-    // that are both right would be that far apart.)
-    if (chunk > two && two > 8192) chunk = two;
-    p->unit_sums = chunk > two;
-    rc = finish_score_plan(s, heads, chunk, p);
-    if (rc == DAPQ_OK && chunk != two && p->total_bytes > DAPQ_STATIC_SCRATCH_BYTES) {
-      // a shape that dapq_score_static served with the power of two is still served, by the same kernels as dapq_score's: a line of
-      // room, not of time
-      ScorePlan t = *p;
-      t.unit_sums = false;
-      if (finish_score_plan(s, heads, two, &t) == DAPQ_OK && t.total_bytes <= DAPQ_STATIC_SCRATCH_BYTES) *p = t;
+    const DenseChunk best = dense_chunk(s, heads, *p, kWaveSlots, two, INT64_MAX);
+    p->unit_sums = best.keys > two;
+    rc = finish_score_plan(s, heads, best.keys, p);
+    if (rc == DAPQ_OK && p->total_bytes > DAPQ_STATIC_SCRATCH_BYTES) {
+      // a shape that dapq_score_static serves with the power of two, with hardly more time than the best takes, or in one kernel (which
+      // leaves the workspace alone) with a sixteenth more, is served, by the same kernels as dapq_score's: a line of room, not of time
+      const int64_t most = partials_that_fit(s, heads, *p, DAPQ_STATIC_SCRATCH_BYTES) / s->batch, L = s->total_tokens / s->batch;
+      const DenseChunk fits = dense_chunk(s, heads, *p, kWaveSlots, two, most);
+      const bool one_kernel = p->n_groups == 1 && fits.keys != 0 && (L + fits.keys - 1) / fits.keys <= 4;
+      if (fits.keys != 0 &&
+          ((L + two - 1) / two <= most || fits.cost <= best.cost + best.cost / (one_kernel ? 16 : 100))) {
+        p->unit_sums = fits.keys > two;
+        rc = finish_score_plan(s, heads, fits.keys, p);
+      }
     }
     if (rc == DAPQ_OK) {
       const size_t least = dense_least_bytes(s, heads, *p);
@@ -326,15 +351,15 @@ int make_score_plan(const dapq_shape* s, size_t workspace_bytes, ScorePlan* p) {
   // to 256 rows into one wave, a ring of its own).  Both passes of dapq_score, wave form -> tiles of 128 keys with the queries
   // straight from memory, 8 KV heads: one layer, 1024 keys, 256 rows 38.6 -> 14.9 us; 8191 keys, 128 rows 26.9 -> 18.6; 16384 keys,
   // 256 rows 44 -> 41, 512 rows 57 -> 61; 32768 keys, 128 rows 39 -> 45; ragged, 8 prompts of 1000 keys, one layer, 128 rows 76 ->
-  // 24, 4 layers, 128 rows (10 000 units) 146 -> 59, 512 rows (40 000 units) 188 -> 174.  Where dapq_score runs both passes in one
-  // kernel it stays with that one.
+  // 24, 4 layers, 128 rows (10 000 units) 146 -> 59, 512 rows (40 000 units) 188 -> 174.  Where a sequence is at most four chunks of the
+  // fewest keys, dapq_score runs both passes in one kernel and stays with that one.
   // Calls of at most 256 workgroups, a compute unit each, take tiles as small as that allows (ragged ones up to 128 keys: larger
   // tiles would need less workspace than a longer batch), with the queries through LDS in whole rows; larger calls live from several
   // workgroups to a compute unit, which the queries' LDS would keep out (128 rows, 16384 keys: 32 us with it, 27 without).
   // With the rotation, tiles of 128 keys -> these: 1024 keys, 256 rows 17.7 -> 13.4 us; 4096 keys 19.1 -> 17.1; 8191 keys, 128 rows
   // 21.9 -> 17.7 (no separate merge of the normalisers at 32 tiles); 5000 keys, 16 rows 17.9 -> 12.8.
   const bool ragged = s->cu_seqlens != nullptr;
-  const bool one_kernel = !ragged && p->n_groups == 1 && p->max_chunks <= 4 * (int64_t)s->batch;
+  const bool one_kernel = !ragged && p->n_groups == 1 && s->total_tokens / s->batch <= 4 * kMinChunkKeys;
   const int64_t row_blocks = (p->rows + 31) / 32;
   const int64_t tiles = heads * (ragged ? s->total_tokens / kTileKeys + s->batch
                                         : s->batch * ((s->total_tokens / s->batch + kTileKeys - 1) / kTileKeys));

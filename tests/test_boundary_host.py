@@ -106,6 +106,21 @@ def test_score_single_launch_follows_the_launch_plan(lib):
         D.score_single_launch(good_shape(n_q_heads=30))
 
 
+def test_few_chunks_of_a_sequence_stay_in_one_kernel(lib):
+    """Where one to four chunks of a sequence leave some of the chip idle in the only round, or a last round nearly empty, one kernel with
+    one start-up is still faster than three launches with fuller rounds: five prompts of 2265 keys, 16 layers, 256 rows 245 us in four
+    chunks each, 277 in five and 281 in six; five of 2316, 8 layers, 128 rows 72 us in two and 94 in six."""
+    def five(layers, keys, group, n):
+        return good_shape(n_layers=layers, batch=5, n_q_heads=8 * group, n_pseudo=n, total_tokens=5 * keys,
+                          k_strides=(5 * keys * 8 * 128, 0, 128, 8 * 128),
+                          q_strides=(5 * 8 * group * n * 128, 8 * group * n * 128, n * 128, 128))
+    for layers, keys, group, n in ((16, 2265, 8, 32), (16, 2811, 4, 64), (8, 2316, 4, 32), (8, 696, 4, 32), (8, 1906, 1, 16)):
+        assert D.score_single_launch(five(layers, keys, group, n)), (layers, keys, group, n)
+    # long prompts fill their rounds (465 us in six chunks, 556 in two); the tiles of small calls stay tiles
+    assert not D.score_single_launch(five(8, 10983, 4, 37))
+    assert not D.score_single_launch(good_shape(n_layers=1, total_tokens=640))
+
+
 FAKE = 0x1000  # never dereferenced: every call below must fail validation first
 
 

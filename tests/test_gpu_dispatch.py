@@ -439,8 +439,8 @@ def test_ragged_batches_in_the_wave_form(H, rows, batch):
     H.assert_scores_close(S[:1].cpu().numpy(), O.score(q, k, 2, cu), f"rows={rows} batch={batch}")
 
 
-# dense batches whose chunks are no powers of two: eight per sequence, shorter than the power of two; four, longer (sums in two
-# steps; up to 256 rows both passes in one kernel); three and one; several sequences; the last chunk with a partial sub-block or short
+# dense batches whose chunks are no powers of two: eight per sequence, shorter than the power of two; four and two, longer (sums in
+# two steps; up to 256 rows both passes in one kernel); three and one; several sequences; the last chunk with a partial sub-block or short
 @pytest.mark.parametrize("rows", [33, 128, 250, 300])
 @pytest.mark.parametrize("layers,batch,length", [(64, 1, 3001), (128, 1, 5000), (170, 1, 2900), (70, 7, 1111), (25, 3, 2017)])
 def test_equal_chunks_of_dense_batches(H, layers, batch, length, rows):
@@ -463,6 +463,13 @@ def test_equal_chunks_of_dense_batches(H, layers, batch, length, rows):
     assert torch.equal(S, T) and torch.equal(S, S[:1].expand_as(S)) and torch.equal(lse, lse[:1].expand_as(lse))
     H.assert_scores_close(S[:1].cpu().numpy(), O.score(q, k, 2, cu), f"{layers} {lens} rows={rows}")
     assert np.abs(lse[:1].cpu().numpy() - oracle_lse2(q, k, 2, cu)).max() < 2e-4
+
+
+@pytest.mark.parametrize("rows", [33, 128, 250])
+@pytest.mark.parametrize("layers,batch,length", [(160, 2, 700), (100, 3, 1500), (40, 5, 3000)])
+def test_one_or_two_chunks_in_one_kernel(H, layers, batch, length, rows):
+    """One chunk of a sequence, or two, longer than the power of two (sums in two steps): as above."""
+    test_equal_chunks_of_dense_batches(H, layers, batch, length, rows)
 
 
 # calls whose own workspace would be larger than that of a larger shape, which they are given: longer chunks (sums in one step and, where
