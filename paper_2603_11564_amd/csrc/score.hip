@@ -1145,8 +1145,10 @@ __global__ __launch_bounds__(64, 1) void score_wave_pseudo_kernel(ScoreParams p,
 // ---------------------------------------------------------------------------------------------
 constexpr int kTileWaves = 8;
 constexpr int kTileThreads = 64 * kTileWaves;
-constexpr int tile_lds(int chunk_keys, int row_blocks, bool stage_q) {
-  return chunk_keys * kHeadDim * 2 + (!stage_q ? 0 : (row_blocks < kTileWaves ? row_blocks : kTileWaves) * kSubBytes);
+// `sums`: and the column sums of its row blocks, in pass 2
+constexpr int tile_lds(int chunk_keys, int row_blocks, bool stage_q, bool sums) {
+  return chunk_keys * kHeadDim * 2 +
+         (row_blocks < kTileWaves ? row_blocks : kTileWaves) * ((stage_q ? kSubBytes : 0) + (sums ? chunk_keys * (int)sizeof(float) : 0));
 }
 
 // Which tile a workgroup works on: the KV heads of a chunk are neighbours in the grid (in the packed layout they share
@@ -1164,20 +1166,26 @@ __device__ __forceinline__ Tile tile_of_workgroup(const ScoreParams& p, bool rev
 }
 
 // How the waves of a workgroup share out the row blocks and sub-blocks: wave = part * rbs + row block, a part being every
-// parts-th sub-block.  (Waves past the last part only bring in keys and queries.)  Where the queries do not go through LDS a wave
-// takes all sub-blocks: it would load its row block for fewer of them.
+// parts-th sub-block.  (Waves past the last part only bring in keys and queries.)  Where the queries do not go through LDS (STAGED
+// is false; tiles of kTileKeys) a wave takes all sub-blocks: it would load its row block for fewer of them.
 struct TileShare {
   int subs, rbs, parts, rb, part;
 };
+template <bool STAGED>
 __device__ __forceinline__ TileShare tile_share(const ScoreParams& p, int wave, int waves) {
   TileShare s;
   const int row_blocks = p.rows_pad >> 5;
-  s.subs = p.chunk_keys >> 5;
+  s.subs = STAGED ? p.chunk_keys >> 5 : kTileKeys / 32;
   s.rbs = row_blocks < waves ? row_blocks : waves;
-  s.parts = !p.stage_q || s.rbs > 4 ? 1 : (s.rbs > 2 ? 2 : (s.rbs == 2 ? 4 : 8));
-  s.parts = s.parts < s.subs ? s.parts : s.subs;
-  s.part = 0;
   s.rb = wave;
+  s.part = 0;
+  s.parts = 1;
+  if (!STAGED) {
+    if (wave >= s.rbs) s.part = 1;
+    return s;
+  }
+  s.parts = s.rbs > 4 ? 1 : (s.rbs > 2 ? 2 : (s.rbs == 2 ? 4 : 8));
+  s.parts = s.parts < s.subs ? s.parts : s.subs;
   while (s.rb >= s.rbs) {
     s.rb -= s.rbs;
     s.part += 1;
@@ -1188,11 +1196,12 @@ __device__ __forceinline__ TileShare tile_share(const ScoreParams& p, int wave, 
 // The waves share out the transfers, 1 KB (four rows) each: first the row blocks of the queries (rows past the last one repeat
 // it; their results are dropped), then the tile's keys (rows past the end of the chunk arrive as zeros, see sub_dma); with eight
 // waves one transfer per wave and row block or sub-block.
+template <bool STAGED>
 __device__ __forceinline__ void tile_dma(u32x4* keys, u32x4* queries, const ScoreParams& p, const uint16_t* kbase,
                                          const uint16_t* qbase, int nkeys, const TileShare& s, int wave, int waves, int lane) {
   const int r = lane >> 4;
   const unsigned piece = (unsigned)(lane & 15) ^ (unsigned)r;
-  for (int i = 0; p.stage_q && i < s.rbs; ++i) {
+  for (int i = 0; STAGED && i < s.rbs; ++i) {
     const int row = i * 32 + 4 * wave + r, rc = row < p.rows ? row : p.rows - 1;
     const int head = quotient(rc, p.inv_n_pseudo), at = rc - head * p.n_pseudo;
     const uint16_t* src = qbase + (int64_t)head * p.q_stride_head + (int64_t)at * p.q_stride_row + (piece ^ (4u * (unsigned)(wave & 3))) * 8u;
@@ -1249,10 +1258,10 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(ST
   if (w.nkeys == 0) return;  // (the same for the whole workgroup)
   const int wave = uniform_i32((int)(threadIdx.x >> 6)), waves = (int)(blockDim.x >> 6);
   const int lane = threadIdx.x & 63, n = lane & 31, h = lane >> 5;
-  const TileShare s = tile_share(p, wave, waves);
+  const TileShare s = tile_share<STAGED>(p, wave, waves);
   u32x4 *keys = tile_area, *queries = tile_area + s.subs * kSubVec;
   const uint16_t* qbase = tile_q_base(p, t, w.seq);
-  tile_dma(keys, queries, p, tile_k_base(p, t, w), qbase, w.nkeys, s, wave, waves, lane);
+  tile_dma<STAGED>(keys, queries, p, tile_k_base(p, t, w), qbase, w.nkeys, s, wave, waves, lane);
   const int row_blocks = p.rows_pad / 32;
   float* outp = p.tile_parts + (((int64_t)t.layer * p.n_kv_heads + t.kv) * p.max_chunks + t.chunk) * p.rows_pad;
   bf16x8 qf[8];
@@ -1358,6 +1367,9 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(ST
 // Pass 2: a lane's column sums over the rows of its wave, then over the row blocks in order through LDS.
 // MERGE: lse2 is not read but formed from the partials of pass 1, by every workgroup for itself, with the arithmetic of
 // score_combine_kernel in its order (same bits), instead of a launch of 3 to 4 us.
+// Not STAGED: calls of several workgroups to a compute unit; four fit (the column sums lie behind the keys, as large as the launch needs
+// them; 96 registers for workgroups of five waves), and queries and lse2 are asked for with the keys.  Pass 2, ragged, us: 16 layers, 64
+// rows, 12355 keys 105.2 -> 101.6; 2 layers, 32 rows, 74770 keys 70.5 -> 68.8.
 constexpr int kMergeRuns = 4;                                    // runs of kCombineRun chunks a thread holds
 constexpr int kMergeMaxRows = kTileThreads;
 // How many chunks per sequence the threads of a workgroup can merge (0: more rows than threads).
@@ -1366,10 +1378,9 @@ __host__ __device__ constexpr int tile_merge_chunks(int rows_pad) {
                                            ? kTileThreads / rows_pad * kMergeRuns * kCombineRun
                                            : kCombineClasses * kCombineRun;
 }
-template <bool MERGE>
-__global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(4))) void score_tile_pass2_kernel(ScoreParams p) {
+template <bool MERGE, bool STAGED>
+__global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(STAGED ? 4 : 5))) void score_tile_pass2_kernel(ScoreParams p) {
   extern __shared__ u32x4 tile_area[];
-  __shared__ float cols[kTileWaves][kTileMaxKeys];
   __shared__ __align__(16) float neg_lse[MERGE ? kMergeMaxRows : 4];
   __shared__ float merge_max[MERGE ? kMergeMaxRows : 1], merge_sum[MERGE ? kMergeMaxRows * kMergeRuns : 1];
   touch_args<sizeof(ScoreParams)>();
@@ -1379,8 +1390,10 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(4)
   const int wave = uniform_i32((int)(threadIdx.x >> 6));
   const int lane = threadIdx.x & 63, n = lane & 31, h = lane >> 5;
   const int waves = (int)(blockDim.x >> 6);
-  const TileShare s = tile_share(p, wave, waves);
+  const TileShare s = tile_share<STAGED>(p, wave, waves);
   u32x4 *keys = tile_area, *queries = tile_area + s.subs * kSubVec;
+  const int tile_keys = s.subs * 32;
+  float* cols = reinterpret_cast<float*>(queries + (STAGED ? s.rbs * kSubVec : 0));  // [row block][key]
   const uint16_t* qbase = tile_q_base(p, t, w.seq);
   const float* lse =
       p.lse2 + (((int64_t)t.layer * p.batch + w.seq) * p.n_q_heads + (int64_t)t.kv * p.group) * p.n_pseudo;
@@ -1404,7 +1417,7 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(4)
       }
     }
   }
-  tile_dma(keys, queries, p, tile_k_base(p, t, w), qbase, w.nkeys, s, wave, waves, lane);
+  tile_dma<STAGED>(keys, queries, p, tile_k_base(p, t, w), qbase, w.nkeys, s, wave, waves, lane);
   if (MERGE) {
     float m = -INFINITY;
 #pragma unroll
@@ -1441,16 +1454,10 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(4)
     // (visible to all after the barrier below)
   }
   const bool quads = (reinterpret_cast<uintptr_t>(lse) & 15) == 0 && (p.rows & 3) == 0;
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-  for (int rb0 = 0; rb0 < row_blocks; rb0 += s.rbs) {  // (one trip up to eight row blocks)
-    const int rb = rb0 + s.rb;
-    if (s.part >= s.parts || rb >= row_blocks) continue;
-    bf16x8 qf[8];
-    if (rb0 != 0 || !p.stage_q) frag_from_q(qf, p, qbase, rb * 32 + n, h);
-    else wave_load_frags<1>(qf, queries + s.rb * kSubVec, n, h);
-    // -lse2 of the rows this lane's accumulator registers hold; -inf for padding rows, which then add 0
-    float off[16];
+  bf16x8 qf[8];
+  float off[16];
+  // -lse2 of the rows this lane's accumulator registers hold; -inf for padding rows, which then add 0
+  auto load_off = [&](int rb) {
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
       const int row = rb * 32 + acc_row(4 * b, h);
@@ -1472,8 +1479,21 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(4)
         for (int e = 0; e < 4; ++e) off[4 * b + e] = row + e < p.rows ? -lse[row + e] : -INFINITY;
       }
     }
+  };
+  if (!STAGED && s.part == 0) {  // (what comes straight from memory is asked for with the tile)
+    frag_from_q(qf, p, qbase, s.rb * 32 + n, h);
+    load_off(s.rb);
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  for (int rb0 = 0; rb0 < row_blocks; rb0 += s.rbs) {  // (one trip up to eight row blocks)
+    const int rb = rb0 + s.rb;
+    if (s.part >= s.parts || rb >= row_blocks) continue;
+    if (rb0 != 0) frag_from_q(qf, p, qbase, rb * 32 + n, h);
+    else if (STAGED) wave_load_frags<1>(qf, queries + s.rb * kSubVec, n, h);
+    if (STAGED || rb0 != 0) load_off(rb);
 #pragma unroll 1
-    for (int sub = s.part; sub < s.subs; sub += s.parts) {
+    for (int sub = STAGED ? s.part : 0; sub < s.subs; sub += s.parts) {
       bf16x8 kf[8];
       wave_load_frags<1>(kf, keys + sub * kSubVec, n, h);
       f32x16 a = {0};
@@ -1482,7 +1502,7 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(4)
       float z[2] = {0.0f, 0.0f};
 #pragma unroll
       for (int v = 0; v < 16; ++v) z[v & 1] += __builtin_amdgcn_exp2f(fmaf(a[v], p.c, off[v]));
-      float* col = &cols[s.rb][sub * 32 + n];
+      float* col = cols + s.rb * tile_keys + sub * 32 + n;
       const float both = sum_halves(z[0] + z[1]);
       if (h == 0) *col = rb0 == 0 ? both : *col + both;
     }
@@ -1490,8 +1510,8 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(4)
   __syncthreads();
   float* out = p.scores + ((int64_t)t.layer * p.n_kv_heads + t.kv) * p.total_tokens + w.tok0;
   for (int key = threadIdx.x; key < w.nkeys; key += (int)blockDim.x) {
-    float sum = cols[0][key];
-    for (int i = 1; i < s.rbs; ++i) sum += cols[i][key];
+    float sum = cols[key];
+    for (int i = 1; i < s.rbs; ++i) sum += cols[i * tile_keys + key];
     out[key] = sum;
   }
 }
@@ -1600,10 +1620,11 @@ dim3 tile_threads(const ScorePlan& plan) {
   return dim3(64u * (unsigned)waves);
 }
 // (the whole dynamic limit once: see set_max_dynamic_lds)
-#define DAPQ_LAUNCH_TILE(kernel)                                                                                 \
+#define DAPQ_LAUNCH_TILE(kernel, sums)                                                                           \
   do {                                                                                                           \
-    if ((rc = set_lds(kernel, tile_lds(kTileMaxKeys, kTileWaves, true))) != DAPQ_OK) return rc;                        \
-    hipLaunchKernelGGL(kernel, tile_grid(s, plan), tile_threads(plan), tile_lds(plan.chunk_keys, plan.row_blocks, plan.stage_q), stream, p); \
+    if ((rc = set_lds(kernel, tile_lds(kTileMaxKeys, kTileWaves, true, sums))) != DAPQ_OK) return rc;            \
+    hipLaunchKernelGGL(kernel, tile_grid(s, plan), tile_threads(plan),                                           \
+                       tile_lds(plan.chunk_keys, plan.row_blocks, plan.stage_q, sums), stream, p);               \
     DAPQ_HIP_LAUNCH_CHECK(#kernel);                                                                              \
   } while (0)
 
@@ -1638,8 +1659,8 @@ int launch_stats(const dapq_shape* s, const ScorePlan& plan, ScoreParams p, hipS
   int rc = launch_chunk_prefix(s, plan, p, stream);
   if (rc != DAPQ_OK) return rc;
   if (plan.tile) {
-    if (plan.stage_q) DAPQ_LAUNCH_TILE(score_tile_pass1_kernel<true>);
-    else DAPQ_LAUNCH_TILE(score_tile_pass1_kernel<false>);
+    if (plan.stage_q) DAPQ_LAUNCH_TILE(score_tile_pass1_kernel<true>, false);
+    else DAPQ_LAUNCH_TILE(score_tile_pass1_kernel<false>, false);
     if (p.lse2 == nullptr) return DAPQ_OK;  // pass 2 merges the partials itself
   } else {
     if ((rc = launch_wave_pass1(s, plan, p, stream)) != DAPQ_OK) return rc;
@@ -1664,8 +1685,9 @@ int launch_accumulate(const dapq_shape* s, const ScorePlan& plan, ScoreParams p,
   int rc = launch_chunk_prefix(s, plan, p, stream);  // (pass 2 can be called on its own: it rebuilds the prefix it walks)
   if (rc != DAPQ_OK) return rc;
   if (plan.tile) {
-    if (p.lse2 == nullptr) DAPQ_LAUNCH_TILE(score_tile_pass2_kernel<true>);
-    else DAPQ_LAUNCH_TILE(score_tile_pass2_kernel<false>);
+    if (p.lse2 == nullptr) DAPQ_LAUNCH_TILE((score_tile_pass2_kernel<true, true>), true);
+    else if (plan.stage_q) DAPQ_LAUNCH_TILE((score_tile_pass2_kernel<false, true>), true);
+    else DAPQ_LAUNCH_TILE((score_tile_pass2_kernel<false, false>), true);
     return DAPQ_OK;
   }
   const GroupShape gs = group_shape(s, plan);

@@ -10,6 +10,9 @@ import pytest
 from paper_2603_11564_amd import build
 
 
+LDS_BYTES = {}  # of a kernel, without what its launch adds
+
+
 def compile_device(src, out):
     """Compiles one translation unit for the device; returns its assembly (one list of lines per kernel or function) and how
     many vector registers each kernel spills."""
@@ -21,8 +24,12 @@ def compile_device(src, out):
         entry = re.match(r"\s+\.(symbol|vgpr_spill_count):\s+(\S+)", line)    # of the kernel descriptors at the end
         if entry and entry.group(1) == "symbol":
             kernel = entry.group(2)
+            LDS_BYTES[kernel] = lds
         elif entry:
             spills[kernel] = int(entry.group(2))
+        size = re.match(r"\s+\.group_segment_fixed_size:\s+(\d+)", line)     # (stands before the symbol)
+        if size:
+            lds = int(size.group(1))
         line = line.split(";")[0].split("//")[0].rstrip()
         label = re.match(r"(_Z\w+):", line)
         if label:
@@ -100,3 +107,13 @@ def test_no_kernel_spills_vector_registers(units):
     spills = {f"{src}: {name}": n for src, (_, kernels) in units.items() for name, n in kernels.items()}
     assert len(spills) > 40 and any("score_wave_pass1_kernel" in name for name in spills)
     assert not {name: n for name, n in spills.items() if n}
+
+
+def test_four_workgroups_of_a_large_tile_call_fit_a_compute_unit(units):
+    """Calls of more tiles than compute units live from several workgroups to each (make_score_plan): four of 128 keys, with the column
+    sums of eight row blocks in pass 2.  (With those of the largest tiles in its static part three fitted: pass 2 of a ragged batch, two
+    layers, 32 rows, 80751 keys 68.2 -> 72.6 us, and half of that back with four.)"""
+    tile = 128 * 256
+    for kernel, launch in (("score_tile_pass1_kernelILb0E", tile), ("score_tile_pass2_kernelILb0ELb0E", tile + 8 * 128 * 4)):
+        static, = (n for name, n in LDS_BYTES.items() if kernel in name)
+        assert 4 * (static + launch) <= 160 * 1024, (kernel, static)
