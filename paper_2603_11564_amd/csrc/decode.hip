@@ -359,11 +359,14 @@ int launch_decode(int64_t heads, const DecodeParams& p, hipStream_t stream) {
 //                              4096        24: 20.5 / 21.0 / 23.7     32: 25.6 / 21.5 / 24.1  48: 39.5 / 24.2 / 25.0 56: 47.2 / 26.6 / 25.1
 //   8, 983                                 64: 9.5 / 10.1 / 12.5      96: 17.1 / 11.5 / 12.9  128: 21.3 / 15.2 / 14.2
 //   8, 4096                                24: 22.5 / 22.9 / 30.8     32: 27.9 / 23.6 / 30.9  64: 58.2 / 30.6 / 31.0 80: 74.8 / 37.1 / 31.2
+// From 5 query heads per KV head on, two slices against one are even at 128 heads of 800 rows, 112 of 950, 96 of 1200 and 80 of 1750 or
+// so: a line by heads x heads x rows (two / one, 8 heads: 128 of 1088 16.2 / 15.0, 112 of 1243 16.2 / 15.3, 96 of 1100 12.9 / 13.5, 80 of
+// 1600 15.6 / 15.9, 66 of 2110 18.4 / 19.0).
 template <int HT>
 int launch_decode_slices(int64_t heads, const DecodeParams& p, hipStream_t stream) {
   const int64_t rows = heads * p.budget;
   if (heads <= 64 && (rows <= 88 * 1024 || heads <= 24)) return launch_decode<HT, 2, 8>(heads, p, stream);
-  if (heads <= 128 && (rows <= (HT == 1 ? 112 : 136) * 1024 || heads <= (HT == 1 ? 48 : 64))) return launch_decode<HT, 4, 8>(heads, p, stream);
+  if (heads <= 128 && (HT == 1 ? rows <= 112 * 1024 || heads <= 48 : heads * rows <= 11 << 20 || heads <= 64)) return launch_decode<HT, 4, 8>(heads, p, stream);
   return launch_decode<HT, 8, 4>(heads, p, stream);
 }
 

@@ -139,7 +139,7 @@ def test_decode_slices(H, rows, g, layers, batch, hkv):
 
 
 # the lines between four, two and one slice: by the number of heads (64, 128; long caches: 24, 48 and, from 5 query heads per KV head
-# on, 64) and by heads x rows
+# on, 64) and by heads x rows (from 5 on, by heads x heads x rows)
 @pytest.mark.parametrize("heads,rows,g", [(64, 1408, 4), (64, 1409, 4), (65, 40, 4), (24, 4096, 2), (25, 4096, 2), (128, 896, 4),
                                           (128, 897, 4), (129, 100, 1), (48, 4096, 1), (49, 4096, 1), (128, 1088, 8), (128, 1089, 5),
                                           (64, 2500, 8), (65, 2500, 8)])
@@ -153,6 +153,11 @@ def test_decode_lines_between_slices(H, heads, rows, g):
     want = decode_want(q, k, v, counts)
     got = decode_call(H, q, k, v, counts, 1)
     assert (np.abs(got - want) <= 1e-5 * np.abs(O.bf16_bits_to_f64(v)).max() + 1e-4 * np.abs(want)).all()
+
+
+@pytest.mark.parametrize("heads,rows,g", [(128, 704, 8), (128, 705, 5), (100, 1153, 8), (100, 1154, 8)])
+def test_decode_lines_of_many_query_heads(H, heads, rows, g):
+    test_decode_lines_between_slices(H, heads, rows, g)
 
 
 # the three slice counts (up to 32 heads, up to 128, more), both head tiles
