@@ -184,9 +184,9 @@ __device__ __forceinline__ Work locate(const ScoreParams& p, int gchunk) {
 // `total` of them -- is cut into segments of equal length, the same for all heads, and a wave (per row group) takes one.
 // Segment i holds sub-blocks total * i / n up to total * (i + 1) / n of n segments; none is empty.  (Handed out chunk by chunk from
 // work lists, each chunk with a ring fill of its own, the waves kept too few keys in flight -- with at most 128 rows the passes are
-// bound by the key stream -- and the last items of a launch ran alone.  32 layers, both passes and what belongs to them: 16 prompts
-// of 200..2500 keys, 128 rows, extended 860 -> 766 us; 2 of 11520, 128 rows 651 -> 586; 64 of 100..500, 256 rows 1514 -> 1400; 8 of
-// 4096..16384, 512 rows 5500 -> 5373.  Two waves to a SIMD with a ring of two slots each, on the lists: 987 in the first case.)
+// bound by the key stream -- and the last items of a launch ran alone.  dapq_score, 32 layers: 16 prompts of 200..2500 keys, 128 rows
+// 742 -> 611 us; 2 of 11520, 128 rows 640 -> 557; 64 of 100..500, 256 rows 1167 -> 1020; 8 of 4096..16384, 512 rows 5326 -> 5259.  Two
+// waves to a SIMD with a ring of two slots each, on the lists, were slower than either.)
 struct Segments {
   int total, n;
   __device__ __forceinline__ int start(int i) const { return (int)((int64_t)total * i / n); }

@@ -249,7 +249,7 @@ def test_score_plan_covers_every_shape(lib):
         return D.workspace_bytes(good_shape(**kw))
     lse = 2 * 1 * 32 * 64 * 4
     # 2 layers x 8 KV heads x 4096 keys, 256 rows: 128-key chunks -> 32 chunks per head, (ref, sum) per row and chunk;
-    # in front of them the chunk prefix of the sequences and the ticket counter of a ragged batch, 256 bytes each
+    # in front of them the chunk prefix of the sequences, 256 bytes, and 256 that nothing uses
     assert ws() == 256 + 256 + 2 * 8 * 32 * 256 * 8 + lse
     # 512 rows per KV head: two row groups; one extra plane of column sums
     big = dict(n_pseudo=128, q_strides=(32 * 128 * 128, 32 * 128 * 128, 128 * 128, 128))

@@ -289,7 +289,7 @@ def test_tiles_of_small_calls(H, lens, rows):
 @pytest.mark.parametrize("batch", [2, 64, 65])
 def test_small_ragged_calls_write_no_chunk_prefix(H, batch):
     """Up to 64 sequences every wave of the tile form finds its chunk by itself: neither pass writes the prefix of the chunk
-    counts (the first batch + 1 words of the workspace) or the tickets behind it; more sequences need it in both passes."""
+    counts, the first batch + 1 words of the workspace; more sequences need it in both passes."""
     announce(f"chunk prefix of {batch} sequences")
     lens = [(7 * i) % 150 + 1 for i in range(batch)]
     q, k, v, cu = problem_bits(batch, 1, lens, 2, 2, 16)
@@ -299,7 +299,7 @@ def test_small_ragged_calls_write_no_chunk_prefix(H, batch):
             (1, 2, prob.tokens), dtype=torch.float32, device="cuda"), prob.ws)):
         prob.ws.fill_(0xA5)
         call()
-        kept = bool((prob.ws[:512] == 0xA5).all())
+        kept = bool((prob.ws[:4 * (batch + 1)] == 0xA5).all())
         assert kept == (batch <= 64)
 
 
@@ -421,7 +421,7 @@ def test_selection_of_mixed_waves(H, n, equal):
             assert np.array_equal(got, O.topk(S[0, kv].astype(np.float64), budget)), (budget, kv)
 
 
-# ragged batches too large for the tile form (more than 65536 units): one, two and four row blocks' kernels, teams of two,
+# ragged batches too large for the tile form (more than 65536 units): the kernels of two, four and eight row blocks, two row groups,
 # up to and beyond the 64 sequences that a wave looks up by itself
 @pytest.mark.parametrize("batch", [40, 64, 65, 100])
 @pytest.mark.parametrize("rows", [33, 128, 200, 512])

@@ -1,7 +1,7 @@
 """The whole step recorded into a HIP graph and replayed.
 
-The library allocates nothing, clears its counters with kernels of its own and keeps no state between calls
-besides the workspaces the caller owns, so a step (rotation of the pseudo queries, both score passes, max-pool +
+The library allocates nothing, writes what it reads from a workspace with kernels of the same call and keeps no state between
+calls besides the workspaces the caller owns, so a step (rotation of the pseudo queries, both score passes, max-pool +
 TopK, gather) can be captured once and replayed by a serving loop.  Each case replays the graph several times, with
 eager work of the program and synchronisations between the replays, and compares every replay bit for bit with the
 eager step on the same inputs.  One eager step runs before the capture: the first call on a device does the
@@ -26,7 +26,7 @@ pytestmark = pytest.mark.gpu
 
 def _cases():
     dense = W.workload("C1")                                                    # one wave per chunk, four to a workgroup
-    ragged = replace(W.workload("C3"), n_layers=2, batch=5, ragged=(300, 2500), budget=96)   # teams, work lists, tickets
+    ragged = replace(W.workload("C3"), n_layers=2, batch=5, ragged=(300, 2500), budget=96)   # tiles over a ragged batch
     empty_mix = replace(W.workload("C3"), n_layers=1, batch=4, ragged=(0, 700), n_pseudo=32, budget=40)
     long_head = replace(W.workload("C5"), n_layers=1, seq_len=70000, budget=1500, needles=8)  # selection in pieces
     one_kernel = replace(W.workload("C1"), seq_len=500, n_layers=3)             # both passes in one kernel
@@ -115,3 +115,40 @@ def test_static_scores_replay_from_a_graph():
         torch.cuda.synchronize()
         assert torch.equal(S_dense, want_dense), f"replay {replay}: eager call between replays"
         assert torch.equal(S_ragged, want_ragged), f"replay {replay}: captured call"
+
+
+@pytest.mark.parametrize("lens,rows", [([(37 * i) % 211 for i in range(69)] + [1500], 128), ([900, 0, 37, 2100], 300)],
+                         ids=["70x1500", "4x2100"])
+def test_segments_replay_from_a_graph(lens, rows):
+    """Ragged batches in segments of the packed key axis, with the prefix of the chunk counts that more than 64 sequences need and
+    without, and two row groups' planes: enough layers of the same problem (layer strides of 0) for that form."""
+    import paper_2603_11564_amd as D
+    from dapq_harness import Problem
+    print(f"graph replay: segments of {len(lens)} sequences", flush=True)
+    rng = np.random.default_rng(rows)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    tokens = int(cu[-1])
+    layers = 66000 // (2 * (tokens // 128 + len(lens)) * ((rows + 31) // 32)) + 1
+    q = W.to_bf16_bits(rng.standard_normal((1, len(lens), 2, rows, 128)))
+    k = W.to_bf16_bits(rng.standard_normal((1, tokens, 2, 128)))
+    prob = Problem(q, k, k, 2, cu, "thd", 128 ** -0.5)
+    shape = D.make_shape(n_layers=layers, batch=len(lens), n_q_heads=2, n_kv_heads=2, n_pseudo=rows, total_tokens=tokens,
+                         cu_seqlens=prob.cu, k_strides=(0, 0, 128, 256), q_strides=(0, 2 * rows * 128, rows * 128, 128),
+                         scale=128 ** -0.5)
+    ws = torch.empty(D.workspace_bytes(shape), dtype=torch.uint8, device="cuda")
+    S = torch.empty((layers, 2, tokens), dtype=torch.float32, device="cuda")
+    D.dapq_score(shape, prob.q, prob.k, S, ws)                           # first call on the device: set-up
+    want, small = S.clone(), prob.score()
+    side = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        D.dapq_score(shape, prob.q, prob.k, S, ws, torch.cuda.current_stream())
+    for replay in range(4):
+        S.fill_(float("nan"))
+        ws.fill_(0xA5)
+        assert torch.equal(prob.score(), small)                          # the program's own eager work
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(S, want), f"replay {replay}"
