@@ -22,10 +22,23 @@ def test_profiled_traffic_belongs_to_the_current_score_kernels():
     assert os.path.exists(os.path.join(ROOT, bench.TRAFFIC_SOURCE["file"]))
     if _git("rev-parse", "--git-dir").returncode != 0 or _git("cat-file", "-e", commit + "^{commit}").returncode != 0:
         pytest.skip("no git history here to compare against")
-    changed = _git("diff", "--quiet", commit, "--", "paper_2603_11564_amd/csrc/score.hip")
-    assert changed.returncode == 0, (f"csrc/score.hip differs from commit {commit}, where {bench.TRAFFIC_SOURCE['file']} "
+    sources = [f"paper_2603_11564_amd/csrc/{f}" for f in ("score.hip", "kernel_args.h", "wave_scan.h")]
+    changed = _git("diff", "--quiet", commit, "--", *sources)
+    assert changed.returncode == 0, (f"{sources} differ from commit {commit}, where {bench.TRAFFIC_SOURCE['file']} "
                                      "was measured: profile the kernels again and update both")
     assert commit in open(os.path.join(ROOT, bench.TRAFFIC_SOURCE["file"])).read()
+
+
+@pytest.mark.parametrize("n_pseudo,rows_pad", [(64, 256), (32, 128)])
+def test_profiled_traffic_belongs_to_the_current_plan(n_pseudo, rows_pad):
+    """The figures are of the 8B shape in four chunks of 8192 keys per head, both passes in one kernel: its workspace, which holds a pair
+    of numbers per row and chunk and the normalisers, names that plan."""
+    import paper_2603_11564_amd as D
+    L, layers = 32768, 32
+    s = D.make_shape(n_layers=layers, batch=1, n_q_heads=32, n_kv_heads=8, n_pseudo=n_pseudo, total_tokens=L,
+                     k_strides=(8 * L * 128, 0, L * 128, 128), q_strides=(32 * n_pseudo * 128, 0, n_pseudo * 128, 128), scale=128 ** -0.5)
+    assert D.score_single_launch(s)
+    assert D.workspace_bytes(s) == 512 + layers * 8 * 4 * rows_pad * 8 + layers * 32 * n_pseudo * 4
 
 
 def test_probe_library_exports_what_its_binding_names():
