@@ -89,7 +89,7 @@ static void carve_workspace(const dapq_shape* s, int64_t heads, ScorePlan* p) {
   off = align_up(off + sizeof(int32_t) * ((size_t)s->batch + 1), 256);
   off += 256;  // (nothing lies here: workspaces have always had it)
   p->off_parts = off;
-  off = align_up(off + sizeof(float) * (p->tile ? 1 : 2) * (size_t)heads * (size_t)p->max_chunks * p->rows_pad, 256);
+  off = align_up(off + sizeof(float) * (p->tile ? 1 : 2) * (size_t)heads * (size_t)p->max_chunks * p->room_rows, 256);
   p->off_lse2 = off;
   off = align_up(off + sizeof(float) * (size_t)s->n_layers * s->batch * s->n_q_heads * s->n_pseudo, 256);
   p->off_partial = off;
@@ -102,7 +102,7 @@ static int64_t partials_that_fit(const dapq_shape* s, int64_t heads, ScorePlan p
   carve_workspace(s, heads, &p);
   if (room < p.total_bytes) return -1;
   // (a row block's partials are whole multiples of 256 bytes)
-  const uint64_t most = (room - p.total_bytes) / (sizeof(float) * 2 * (size_t)heads * p.rows_pad);
+  const uint64_t most = (room - p.total_bytes) / (sizeof(float) * 2 * (size_t)heads * p.room_rows);
   return most < ((uint64_t)1 << 31) ? (int64_t)most : ((int64_t)1 << 31);
 }
 
@@ -141,6 +141,11 @@ static int dense_chunk_of_two(const dapq_shape* s, int64_t heads, const ScorePla
   return chunk;
 }
 
+// What a key costs both walks of a wave, in nanoseconds (fitted for two, four and eight row blocks, see dense_cost; five to seven lie
+// on the line between four and eight, three move the same keys as four).
+static int64_t walk_cost(int row_blocks) {
+  return row_blocks > 4 ? 29 + 6 * row_blocks - (row_blocks == 8 ? 2 : 0) : (row_blocks > 2 ? 52 : 45);
+}
 // Time of both passes of a dense batch in chunks of c keys, in nanoseconds, as far as c decides it.  The machine runs wave_slots waves
 // at a time, each for as long as its chunk, and a round of waves pays a start-up (queries, ring fill).  Up to four chunks of a
 // sequence with one row group are the waves of one workgroup, which does both passes (dapq_score in one kernel): one start-up for both and
@@ -151,7 +156,7 @@ static int dense_chunk_of_two(const dapq_shape* s, int64_t heads, const ScorePla
 // some 20 chunk lengths: against the best power of two 0.906 of the time in the geometric mean, none above 1.09 (with a start-up of
 // 160 keys for both forms, and one to four chunks only where they fill the rounds: 0.940 and 1.85; the best of the lengths: 0.896).
 static int64_t dense_cost(const ScorePlan& p, int64_t streams, int64_t batch, int64_t L, int64_t c, int64_t wave_slots) {
-  const int64_t n = (L + c - 1) / c, walk = (L < c ? L : c) * (p.row_blocks == 8 ? 75 : (p.row_blocks == 4 ? 52 : 45));
+  const int64_t n = (L + c - 1) / c, walk = (L < c ? L : c) * walk_cost(p.row_blocks);
   if (p.n_groups == 1 && n <= 4) {
     const int64_t workgroups = wave_slots / 4 * (n <= 1 ? 4 : 4 / n);
     return (streams + workgroups - 1) / workgroups * (walk + 10000);
@@ -261,7 +266,7 @@ static size_t dense_least_bytes(const dapq_shape* s, int64_t heads, ScorePlan p)
   const int64_t waves = all < kRoomWaves ? all : kRoomWaves;
   p.max_chunks = 0;
   carve_workspace(s, heads, &p);
-  return p.total_bytes + sizeof(float) * 2 * (size_t)waves * p.row_blocks * 32;
+  return p.total_bytes + sizeof(float) * 2 * (size_t)waves * (p.room_rows / p.n_groups);
 }
 // Fewer and longer chunks, in a workspace of `room` bytes that does not hold the plan's.
 static void fit_dense(const dapq_shape* s, int64_t heads, int64_t wave_slots, int two, size_t room, ScorePlan* p) {
@@ -306,6 +311,7 @@ int make_score_plan(const dapq_shape* s, size_t workspace_bytes, ScorePlan* p) {
   p->n_groups = split.n_groups;
   p->row_blocks = split.row_blocks;
   p->rows_pad = p->n_groups * p->row_blocks * 32;
+  p->room_rows = p->n_groups * split.room_blocks * 32;
   p->tile = false;
   p->stage_q = false;
   p->unit_sums = false;
@@ -369,7 +375,7 @@ int make_score_plan(const dapq_shape* s, size_t workspace_bytes, ScorePlan* p) {
   t.segments = 0;
   t.row_blocks = (int)row_blocks;
   t.n_groups = 1;
-  t.rows_pad = t.row_blocks * 32;
+  t.rows_pad = t.room_rows = t.row_blocks * 32;
   int keys = kTileKeys;
   t.stage_q = false;
   for (int c = kTileMinKeys; c <= (ragged ? kTileKeys : kTileMaxKeys); c *= 2) {

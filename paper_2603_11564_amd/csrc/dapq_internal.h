@@ -40,8 +40,9 @@ struct ScorePlan {
   bool tile;       // the tile kernels (a workgroup per chunk, its waves share out the rows) instead of the wave kernels
   int rows;        // R = (H_q/H_kv) * N query rows scored against every key of a KV head
   int n_groups;    // row groups of row_blocks * 32 rows, one wave each per chunk (tile: 1)
-  int row_blocks;  // 32-row blocks per wave (2, 4 or 8; tile: all of them)
+  int row_blocks;  // 32-row blocks per wave (2 to 8; tile: all of them)
   int rows_pad;    // n_groups * row_blocks * 32
+  int room_rows;   // rows that the workspace has partial sums for: at least rows_pad
   int chunk_keys;  // keys per wave, a multiple of 32 (tile form: keys of a tile, a power of two; in segments: those of a sub-block)
   int segments;    // ragged batches in the wave form: the waves that share a head's packed key axis (else 0)
   int64_t max_chunks;  // partial sums of a row: upper bound on sum_b ceil(L_b / chunk_keys), or batch + segments
@@ -55,11 +56,16 @@ int check_shape(const dapq_shape* s, bool need_q, bool need_k, bool need_v);
 // workspace_bytes: what the caller's workspace holds (SIZE_MAX to ask for what the shape would like).
 int make_score_plan(const dapq_shape* s, size_t workspace_bytes, ScorePlan* plan);
 
-// How the wave kernels split the rows: one wave holds a group of up to 256 in its registers.
+// How the wave kernels split the rows: one wave holds a group of up to 256 in its registers, the groups of a head as many each.
+// The workspace is sized as if a wave held 2, 4 or 8 row blocks, so that its figure does not fall where a row more makes a
+// head two groups of fewer blocks.
 struct RowSplit {
-  int n_groups, row_blocks;
+  int n_groups, row_blocks, room_blocks;
 };
-inline RowSplit wave_row_split(int rows) { return {(rows + 255) / 256, rows <= 64 ? 2 : (rows <= 128 ? 4 : 8)}; }
+inline RowSplit wave_row_split(int rows) {
+  const int blocks = (rows + 31) / 32, n_groups = (blocks + 7) / 8, each = (blocks + n_groups - 1) / n_groups;
+  return {n_groups, each < 2 ? 2 : each, each <= 2 ? 2 : (each <= 4 ? 4 : 8)};
+}
 
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 

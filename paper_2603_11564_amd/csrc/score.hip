@@ -12,9 +12,13 @@
 // wave kernels in segments of the packed key axis (Segments).
 //
 // Work split.  The unit of work is ONE wave (four independent ones are launched as a workgroup).  It keeps a group of up to 256 Q rows of one KV head in
-// registers as MFMA operand fragments (eight 32-row blocks = 256 registers, pinned to the
+// registers as MFMA operand fragments (up to eight 32-row blocks = 256 registers, from five on pinned to the
 // accumulation half of the register file; one wave per SIMD owns the whole 512-register file) and
-// walks its own chunk of keys of one (layer, sequence, KV head).  Nothing is shared between waves:
+// walks its own chunk of keys of one (layer, sequence, KV head).  There are kernels for two to eight row blocks, and the row groups
+// of a head hold as many each: a padded row block is a sixth to an eighth of the arithmetic, which bounds the passes from five on (both
+// passes, 32 layers, 8 KV heads, us, with two, four and eight only -> these: 148 rows, 32768 keys 1106 -> 829; 192, 20000 keys 690 ->
+// 576; 224, 32768 keys 1143 -> 1055; 296 (twice five), 8 layers, 40000 keys 606 -> 450; 96, 32768 keys 776 -> 750; 74, 4 KV heads, 5
+// prompts of 3926 keys 254 -> 231).  Nothing is shared between waves:
 // no barrier anywhere in the separate-pass kernels (the one-launch form has two, between its passes),
 // no cross-wave reduction.  Heads with more than 256 rows are split into row
 // groups (grid.y): pass 1 needs nothing more (its sums are per row), pass 2 writes one plane of
@@ -727,7 +731,7 @@ __device__ __forceinline__ void pass1_piece(const ScoreParams& p, u32x4* ring, i
   const int lane = fresh_lane(), n = lane & 31, h = lane >> 5;
 #pragma unroll
   for (int rb = 0; rb < NRB; ++rb) frag_from_q(qf[rb], p, qbase, gbase + rb * 32 + n, h);
-  if (NRB == 8) pin_q_in_agprs<NRB>(qf);
+  if (NRB > 4) pin_q_in_agprs<NRB>(qf);
   if (start) {
     wait_ring_full<NST>();
     wave_load_frags<NRB>(kf, ring + slot * kSubVec, n, h);
@@ -897,7 +901,7 @@ __device__ __forceinline__ void pass2_piece(const ScoreParams& p, u32x4* ring, i
   if constexpr (!LOADED) {
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) frag_from_q(qf[rb], p, qbase, gbase + rb * 32 + n, h);
-    if (NRB == 8) pin_q_in_agprs<NRB>(qf);
+    if (NRB > 4) pin_q_in_agprs<NRB>(qf);
     // -lse2 of the rows this lane's accumulator registers hold; -inf for padding rows, which then add 0
     if ((reinterpret_cast<uintptr_t>(lse) & 15) == 0 && (p.rows & 3) == 0) {
       // the four rows of an accumulator quad are consecutive: one 16-byte load each
@@ -1039,7 +1043,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_fused_kernel(Sco
   pass1_chunk<NRB, NST, UNIT, true>(p, ring, work, chunk, 0, head, qf, lane);
   __syncthreads();
   // lse2 of rows lane, lane + 64, ...: every wave merges all chunks itself
-  constexpr int kRowsPerLane = NRB * 32 / 64;
+  constexpr int kRowsPerLane = (NRB * 32 + 63) / 64;  // (an odd number of row blocks: the last rows are no one's)
   float lse[kRowsPerLane];
 #pragma unroll
   for (int r = 0; r < kRowsPerLane; ++r) {
@@ -1628,6 +1632,20 @@ dim3 tile_threads(const ScorePlan& plan) {
     DAPQ_HIP_LAUNCH_CHECK(#kernel);                                                                              \
   } while (0)
 
+// launch(row blocks of a wave) for the numbers that wave_row_split gives.
+#define DAPQ_BY_ROW_BLOCKS(row_blocks, launch) \
+  do {                                         \
+    switch (row_blocks) {                      \
+      case 2: launch(2); break;                \
+      case 3: launch(3); break;                \
+      case 4: launch(4); break;                \
+      case 5: launch(5); break;                \
+      case 6: launch(6); break;                \
+      case 7: launch(7); break;                \
+      default: launch(8);                      \
+    }                                          \
+  } while (0)
+
 int launch_wave_pass1(const dapq_shape* s, const ScorePlan& plan, ScoreParams p, hipStream_t stream) {
   int rc = DAPQ_OK;
   const GroupShape gs = group_shape(s, plan);
@@ -1646,9 +1664,7 @@ int launch_wave_pass1(const dapq_shape* s, const ScorePlan& plan, ScoreParams p,
     else if (plan.unit_sums) DAPQ_LAUNCH_W1(NRBV, false, true); \
     else DAPQ_LAUNCH_W1(NRBV, false, false);                  \
   } while (0)
-  if (plan.row_blocks == 2) DAPQ_LAUNCH_W1_KEYS(2);
-  else if (plan.row_blocks == 4) DAPQ_LAUNCH_W1_KEYS(4);
-  else DAPQ_LAUNCH_W1_KEYS(8);
+  DAPQ_BY_ROW_BLOCKS(plan.row_blocks, DAPQ_LAUNCH_W1_KEYS);
 #undef DAPQ_LAUNCH_W1_KEYS
 #undef DAPQ_LAUNCH_W1
   DAPQ_HIP_LAUNCH_CHECK("score_wave_pass1_kernel");
@@ -1700,15 +1716,13 @@ int launch_accumulate(const dapq_shape* s, const ScorePlan& plan, ScoreParams p,
     hipLaunchKernelGGL((score_wave_pass2_kernel<NRBV, SEGV, kWaveStages>), gs.grid(plan, s), dim3(64 * gs.waves),       \
                        gs.waves * wave_lds(kWaveStages), stream, p);                                                    \
   } while (0)
-  if (plan.segments > 0) {
-    if (plan.row_blocks == 2) DAPQ_LAUNCH_W2(2, true);
-    else if (plan.row_blocks == 4) DAPQ_LAUNCH_W2(4, true);
-    else DAPQ_LAUNCH_W2(8, true);
-  } else {
-    if (plan.row_blocks == 2) DAPQ_LAUNCH_W2(2, false);
-    else if (plan.row_blocks == 4) DAPQ_LAUNCH_W2(4, false);
-    else DAPQ_LAUNCH_W2(8, false);
-  }
+#define DAPQ_LAUNCH_W2_KEYS(NRBV)                     \
+  do {                                                \
+    if (plan.segments > 0) DAPQ_LAUNCH_W2(NRBV, true); \
+    else DAPQ_LAUNCH_W2(NRBV, false);                 \
+  } while (0)
+  DAPQ_BY_ROW_BLOCKS(plan.row_blocks, DAPQ_LAUNCH_W2_KEYS);
+#undef DAPQ_LAUNCH_W2_KEYS
 #undef DAPQ_LAUNCH_W2
   DAPQ_HIP_LAUNCH_CHECK("score_wave_pass2_kernel");
   if (plan.n_groups > 1) {
@@ -1745,15 +1759,13 @@ int launch_fused(const dapq_shape* s, const ScorePlan& plan, ScoreParams p, hipS
     hipLaunchKernelGGL((score_fused_kernel<NRBV, UNITV, kWaveStages>), grid, dim3(64 * gs.waves),                      \
                        gs.waves * wave_lds(kWaveStages), stream, p);                                                   \
   } while (0)
-  if (plan.unit_sums) {
-    if (plan.row_blocks == 2) DAPQ_LAUNCH_F(2, true);
-    else if (plan.row_blocks == 4) DAPQ_LAUNCH_F(4, true);
-    else DAPQ_LAUNCH_F(8, true);
-  } else {
-    if (plan.row_blocks == 2) DAPQ_LAUNCH_F(2, false);
-    else if (plan.row_blocks == 4) DAPQ_LAUNCH_F(4, false);
-    else DAPQ_LAUNCH_F(8, false);
-  }
+#define DAPQ_LAUNCH_F_SUMS(NRBV)                 \
+  do {                                           \
+    if (plan.unit_sums) DAPQ_LAUNCH_F(NRBV, true); \
+    else DAPQ_LAUNCH_F(NRBV, false);             \
+  } while (0)
+  DAPQ_BY_ROW_BLOCKS(plan.row_blocks, DAPQ_LAUNCH_F_SUMS);
+#undef DAPQ_LAUNCH_F_SUMS
 #undef DAPQ_LAUNCH_F
   DAPQ_HIP_LAUNCH_CHECK("score_fused_kernel");
   return DAPQ_OK;
@@ -1915,9 +1927,9 @@ extern "C" DAPQ_API int dapq_score_stats_extend(const dapq_shape* shape, const v
   const RowSplit split = wave_row_split(plan.rows);
   const dim3 grid((unsigned)shape->batch, (unsigned)split.n_groups, (unsigned)(shape->n_layers * shape->n_kv_heads));
   hipStream_t st = static_cast<hipStream_t>(stream);
-  if (split.row_blocks == 2) hipLaunchKernelGGL(score_wave_pseudo_kernel<2>, grid, dim3(64), kSubBytes, st, p, pp);
-  else if (split.row_blocks == 4) hipLaunchKernelGGL(score_wave_pseudo_kernel<4>, grid, dim3(64), kSubBytes, st, p, pp);
-  else hipLaunchKernelGGL(score_wave_pseudo_kernel<8>, grid, dim3(64), kSubBytes, st, p, pp);
+#define DAPQ_LAUNCH_PSEUDO(NRBV) hipLaunchKernelGGL(score_wave_pseudo_kernel<NRBV>, grid, dim3(64), kSubBytes, st, p, pp)
+  DAPQ_BY_ROW_BLOCKS(split.row_blocks, DAPQ_LAUNCH_PSEUDO);
+#undef DAPQ_LAUNCH_PSEUDO
   DAPQ_HIP_LAUNCH_CHECK("score_wave_pseudo_kernel");
   return DAPQ_OK;
 }

@@ -573,3 +573,33 @@ def test_candidates_of_long_heads_off_16_bytes(H, offset):
     H.D.dapq_topk(prob.shape, torch.from_numpy(S).cuda(), budget, None, idx, count, ws)
     for kv in range(2):
         assert np.array_equal(idx.cpu().numpy()[0, 0, kv], O.topk(S[0, kv].astype(np.float64), budget))
+
+
+# a wave holds two to eight row blocks, the row groups of a head as many each: the last rows of one number and the first of the next,
+# one to three groups; both passes in one kernel, in separate launches, and in segments of a ragged batch
+@pytest.mark.parametrize("lens,layers,ragged", [([700, 700], 130, False), ([5100], 24, False), ([1500, 0, 33, 800, 64], 200, True)],
+                         ids=["one kernel", "launches", "segments"])
+@pytest.mark.parametrize("rows", [64, 65, 96, 97, 129, 160, 161, 192, 193, 224, 225, 257, 321, 449, 513])
+def test_row_blocks_of_a_wave(H, rows, lens, layers, ragged):
+    """Every layer is the same problem (layer strides of 0): the oracle's scores within 1e-3, with and without the pseudo tokens' own keys
+    in the normaliser, the same bits in every layer and from the two separate entry points."""
+    announce(f"row blocks: rows={rows} {lens}")
+    q, k, v, cu = problem_bits(rows, 1, lens, 1, 1, rows)
+    prob = H.Problem(q, k, v, 1, cu if ragged else None, "thd")
+    tokens = int(cu[-1])
+    layers = layers * 513 // rows if ragged else layers                                     # beyond the tile form
+    shape = H.D.make_shape(n_layers=layers, batch=len(lens), n_q_heads=1, n_kv_heads=1, n_pseudo=rows, total_tokens=tokens,
+                           cu_seqlens=prob.cu, k_strides=(0, 0, 128, 128), q_strides=(0, rows * 128, rows * 128, 128), scale=128 ** -0.5)
+    ws = torch.full((H.D.workspace_bytes(shape),), 0xA5, dtype=torch.uint8, device="cuda")
+    S, T, X = (torch.full((layers, 1, tokens), float("nan"), dtype=torch.float32, device="cuda") for _ in range(3))
+    lse = torch.full((layers, len(lens), 1, rows), float("nan"), dtype=torch.float32, device="cuda")
+    H.D.dapq_score(shape, prob.q, prob.k, S, ws)
+    H.D.dapq_score_stats(shape, prob.q, prob.k, lse, ws)
+    H.D.dapq_score_accumulate(shape, prob.q, prob.k, lse, T, ws)
+    assert torch.equal(S, T) and torch.equal(S, S[:1].expand_as(S))
+    H.assert_scores_close(S[:1].cpu().numpy(), O.score(q, k, 1, cu), f"rows={rows}")
+    kp = W.to_bf16_bits(np.random.default_rng(rows).standard_normal((1, len(lens), 1, rows, 128), dtype=np.float32))
+    H.D.dapq_score_stats_extend(shape, prob.q, H.dev_bf16(kp), (0, rows * 128, rows * 128, 128), lse)
+    H.D.dapq_score_accumulate(shape, prob.q, prob.k, lse, X, ws)
+    assert torch.equal(X, X[:1].expand_as(X))
+    H.assert_scores_close(X[:1].cpu().numpy(), O.score(q, k, 1, cu, None, kp), f"extended, rows={rows}")
