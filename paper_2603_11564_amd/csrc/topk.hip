@@ -1,7 +1,7 @@
 // M_retain = TopK_j S(j) (Sec. 4.2): per (layer, sequence, KV head) the budget positions with the
 // largest pooled score, equal scores lowest position first, written in ascending position.
 //
-// One workgroup per head (256 threads for short heads, 1024 from 16385 keys on).  Selection is exact, on the
+// One workgroup per head (256 to 1024 threads of 8 to 64 keys, reg_kernel_for).  Selection is exact, on the
 // order-preserving integer image of the fp32 score: it finds the threshold T (the budget-th largest key) and how many keys
 // equal to T are still needed (topk_select; the streaming kernel takes T digit by digit with 256-bin histograms).  The
 // last step is an ordered compaction: key j is kept if score > T, or score == T and fewer than `need` equal keys precede it;
@@ -72,12 +72,13 @@ struct TopkHead {
   bool foreign;       // the head belongs to another launch
 };
 
+// PIECES: the workgroup takes a piece of a long head.
+template <bool PIECES>
 __device__ __forceinline__ TopkHead topk_head(const TopkParams& p) {
   TopkHead hd;
   const int tid = threadIdx.x;
-  const bool pieces = p.cand_idx != nullptr;
-  const int nseg = pieces ? p.n_segs : 1;
-  const int kv = uniform_quotient((int)blockIdx.x, nseg, pieces ? p.inv_segs : 1.0f), seg = (int)blockIdx.x - kv * nseg;
+  const int nseg = PIECES ? p.n_segs : 1;
+  const int kv = PIECES ? uniform_quotient((int)blockIdx.x, nseg, p.inv_segs) : (int)blockIdx.x, seg = (int)blockIdx.x - kv * nseg;
   const int b = blockIdx.y, layer = blockIdx.z;
   int64_t start;
   if (p.cu_seqlens == nullptr) {
@@ -102,7 +103,7 @@ __device__ __forceinline__ TopkHead topk_head(const TopkParams& p) {
   want = want < 0 ? 0 : (want > p.budget ? p.budget : want);
   const int64_t head = ((int64_t)layer * p.batch + b) * p.n_kv_heads + kv;
   const float* head_src = p.pooled + ((int64_t)layer * p.n_kv_heads + kv) * p.total_tokens + start;
-  if (pieces) {
+  if (PIECES) {
     hd.base = seg * p.seg_len;
     const int left = hd.head_len - hd.base;
     hd.L = left < 0 ? 0 : (left > p.seg_len ? p.seg_len : left);
@@ -144,12 +145,22 @@ __device__ __forceinline__ void topk_pick_digit(const uint32_t* hist, uint32_t* 
   if (g0 < un && un <= g0 + h0) { bcast[0] = 4 * lane + 0; bcast[1] = un - g0; bcast[2] = h0; }
 }
 
-// Whether a register variant brings its head in through an LDS staging area of THREADS * (KPT + 4) words (launched
-// as dynamic LDS): the variant for 8K..32K keys, which has a compute unit to itself anyway.  The short-head variants
-// share a compute unit and would lose occupancy to the area; 64 keys per thread times 1024 threads do not fit.
-constexpr bool reg_variant_is_staged(int threads, int kpt) { return threads == 1024 && kpt == 32; }
-constexpr int reg_variant_stage_bytes(int threads, int kpt) {  // (two more rows: the halos of the first and last thread)
-  return reg_variant_is_staged(threads, kpt) ? (threads + 2) * (kpt + 4) * (int)sizeof(float) : 0;
+// The register variants of up to 32 keys per thread bring their head in through LDS: the staging area of a wave is its threads' runs, KPT
+// words each, and eight more words for the scores before and after them.  (64 keys per thread times 1024 threads do not fit.)
+constexpr bool reg_variant_is_staged(int kpt) { return kpt <= 32; }
+constexpr int reg_variant_wave_words(int kpt) { return 64 * kpt + 8; }
+constexpr int reg_variant_rows_bytes(int threads, int kpt) { return threads / 64 * reg_variant_wave_words(kpt) * (int)sizeof(float); }
+// (then the bins, which have a place of their own: a wave need not wait for the others until it counts)
+constexpr int reg_variant_stage_bytes(int threads, int kpt) {
+  return reg_variant_is_staged(kpt) ? reg_variant_rows_bytes(threads, kpt) + threads * (int)sizeof(uint4) : 0;
+}
+// Where the 16-byte piece `piece` of row `row` lies (in words), rows of KPT words: pieces XOR-swizzled so that sixteen threads next to
+// each other find the same piece of their rows in sixteen different groups of banks.
+template <int KPT>
+__device__ __forceinline__ int stage_piece(int row, int piece) {
+  constexpr int kPieces = KPT / 4, kShift = __builtin_ctz(16 / kPieces);
+  static_assert(kPieces >= 1 && kPieces <= 16 && (kPieces & (kPieces - 1)) == 0, "whole rows of 16 pieces");
+  return (row * kPieces + (piece ^ ((row >> kShift) & (kPieces - 1)))) * 4;
 }
 
 // bits = 16 * bits + the flags key > t of four keys, the first one on top: a compare and an add with carry per key.
@@ -167,9 +178,10 @@ __device__ __forceinline__ void push_greater(uint32_t& bits, const uint32_t* key
 }
 
 // ---- selection among the keys a workgroup holds in registers (KPT per thread, thread t's before thread t+1's):
-// the `keep` largest, ties to the lowest position, handed to emit(i, key, slot) in ascending position order (register
-// i of the calling thread is survivor number `slot`; `key` is 0 unless want_key).  A register without a key holds 0 (a
-// key is at least 1); the workgroup has n_keys; `whole`: all registers of this wave hold keys.  keep >= 1 and at most n_keys.
+// the `keep` largest, ties to the lowest position, handed to place(i, slot) in ascending position order (register
+// i of the calling thread is survivor number `slot`; BY_REGISTER: i is known to the compiler, so that place can look into registers, and
+// many survivors cost no more than few).  All threads have passed a barrier between their last use of `bins` and the first
+// place().  A register without a key holds 0 (a key is at least 1); the workgroup has n_keys; `whole`: all registers of this wave hold keys.  keep >= 1 and at most n_keys.
 // bins: LDS of THREADS uint4 that nobody else reads any more; thread t looks after bins 4t .. 4t+3.
 //
 // The threshold T (the keep-th largest key) is closed in on: [lo, lo + range] starts as the span of the keys and becomes,
@@ -188,12 +200,12 @@ __device__ __forceinline__ void push_greater(uint32_t& bits, const uint32_t* key
 // for register by register and ranked by one wave) 24 000 are left: arguments 800, loading 4100 (11 400 with 256 heads), dealing out
 // and pooling 2000, keys and their span 3000, bins 6800 (a wave's LDS addition takes 12 clocks however many of its lanes add,
 // and whether or not the loop masks them), bits and ranks 3800, compaction 3000.  With the gather: 8 heads 19.1 -> 15.9 us, 64 heads
-// of 131072 keys in pieces 88.2 -> 82.9.
+// of 131072 keys in pieces 88.2 -> 82.9.  (Two and four times the bins, which leave fewer candidates: 17.1 -> 17.2 and 18.3 us.)
 constexpr int kRankMax = 64;  // candidates that are ranked
 constexpr int kCrowd = 3;     // neighbouring lanes of 60 with keys of one bin: a bin that holds a fifth of them (in a spread of keys, 0.1)
-template <int THREADS, int KPT, class Emit>
-__device__ __forceinline__ void topk_select(const uint32_t (&key)[KPT], int n_keys, int keep, uint4* bins, bool whole, bool want_key,
-                                            Emit emit) {
+template <int THREADS, int KPT, bool BY_REGISTER, class Place>
+__device__ __forceinline__ void topk_select(const uint32_t (&key)[KPT], int n_keys, int keep, uint4* bins, bool whole,
+                                            Place place) {
   constexpr int kWaves = THREADS / 64, kWords = (KPT + 31) / 32, kBins = 4 * THREADS;
   static_assert(KPT % 4 == 0 && (KPT < 32 || KPT % 32 == 0), "whole quads and whole words of position bits");
   static_assert((kBins & (kBins - 1)) == 0 && kWaves <= 64, "bins and waves");
@@ -389,19 +401,16 @@ __device__ __forceinline__ void topk_select(const uint32_t (&key)[KPT], int n_ke
     while ((uint32_t)__popc(e) > room) e &= e - 1;  // the last ones go: the lowest bits are the last registers
     room -= (uint32_t)__popc(e);
     uint32_t take = gt[w] | e;
-    if (want_key) {
+    if constexpr (BY_REGISTER) {
 #pragma unroll
       for (int i = 32 * w; i < KPT && i < 32 * w + 32; ++i) {
-        const bool t = (take >> (top - i % 32)) & 1u;
-        if (__ballot(t) != 0) {  // survivors are few: most of a wave's registers hold none
-          if (t) emit(i, key[i], pos++);
-        }
+        if ((take >> (top - i % 32)) & 1u) place(i, pos++);
       }
     } else {
       while (take != 0) {
         const int bit = 31 - __clz((int)take);
         take ^= 1u << bit;
-        emit(32 * w + top - bit, 0u, pos++);
+        place(32 * w + top - bit, pos++);
       }
     }
   }
@@ -419,12 +428,13 @@ __device__ __forceinline__ float window_max(const float (&ext)[N], int i) {
 
 // ---- heads that fit in registers.  R > 0: the input is the un-pooled score and the kernel applies
 // the max-pool of radius R itself (window clipped at the ends of the sequence) before selecting.
-template <int THREADS, int KPT, int R>
+template <int THREADS, int KPT, int R, bool PIECES>
 __global__ __launch_bounds__(THREADS) void topk_reg_kernel(TopkParams p) {
-  constexpr bool kStaged = reg_variant_is_staged(THREADS, KPT);
+  static_assert(!PIECES || reg_variant_is_staged(KPT), "the keys of a piece's survivors go through the staging area");
+  constexpr bool kStaged = reg_variant_is_staged(KPT);
   touch_args<sizeof(TopkParams)>();
   const int tid = threadIdx.x;
-  const TopkHead hd = topk_head(p);
+  const TopkHead hd = topk_head<PIECES>(p);
   if (hd.foreign || (hd.done && p.pooled_out == nullptr)) return;  // a finished head may still owe its pooled scores
   const int L = hd.L;
   // position j of this piece is a position of its head (the pooling window does not stop at the end of a piece)
@@ -437,40 +447,60 @@ __global__ __launch_bounds__(THREADS) void topk_reg_kernel(TopkParams p) {
   // (a wave whose threads all have KPT keys is spared the tests)
   const bool whole = __all(nvalid == KPT);
   float ext[KPT + 2 * R];  // scores j0-R .. j0+KPT+R-1; -inf outside the sequence
-  if (kStaged) {
-    // The head comes in with coalesced 16-byte loads (a thread reading its own run straight from memory makes
-    // every load instruction touch 64 cache lines, and the halo loads as many again) and is dealt out to its
-    // owners through LDS.  Row t + 1 of the staging area is thread t's run; rows are KPT + 4 words apart, which keeps
-    // them 16-byte aligned and spreads consecutive rows over the banks.  Row 0 ends with the four scores before the
-    // piece and row THREADS + 1 starts with the four after it (neighbouring pieces of a long head), if the head has them.
+  if constexpr (kStaged) {
+    // A wave brings in its own keys with coalesced loads (a thread reading its run straight from memory makes every load instruction
+    // touch 64 cache lines) and deals them out to its threads through its part of the staging area; the scores before and
+    // after them, of which the windows at its ends take some, come along.  Nothing is shared with the other waves: those whose keys
+    // arrive first pool them while the others wait.  Pooling, selection and gather of 8 heads of 32768 keys 15.7 -> 14.9 us, 256 heads
+    // 72.9 -> 71.5; 32 of 8757 keys, straight from memory before, 20.2 -> 16.7.
     extern __shared__ float stage_area[];
-    constexpr int kRow = KPT + 4;
-    float* stage = stage_area + kRow;  // row 0 of `stage` is thread 0's
     static_assert(R <= 4, "the halo of a run is read as one 16-byte piece of each neighbouring row");
-    if ((reinterpret_cast<uintptr_t>(hd.src) & 15) == 0) {
+    const int lane = tid & 63, first = (tid - lane) * KPT;
+    float* rows = stage_area + (tid >> 6) * reg_variant_wave_words(KPT);
+    if (first < L) {
+      float halo = -INFINITY;
+      if (R > 0 && lane < 8) {
+        const int j = lane < 4 ? first - 4 + lane : first + 64 * KPT + (lane - 4);
+        if (in_head(j)) halo = hd.src[j];
+      }
+      if ((reinterpret_cast<uintptr_t>(hd.src) & 15) == 0) {
+        float4 v[KPT / 4];
 #pragma unroll
-      for (int it = 0; it < KPT / 4; ++it) {
-        const int g = (it * THREADS + tid) * 4;
-        if (g + 4 <= L) {
-          *reinterpret_cast<float4*>(&stage[(g / KPT) * kRow + (g % KPT)]) = *reinterpret_cast<const float4*>(hd.src + g);
-        } else {
-          for (int k = 0; k < 4 && g + k < L; ++k) stage[(g / KPT) * kRow + (g % KPT) + k] = hd.src[g + k];
+        for (int it = 0; it < KPT / 4; ++it) {
+          const int g = first + (it * 64 + lane) * 4;
+          if (g + 4 <= L) {
+            v[it] = *reinterpret_cast<const float4*>(hd.src + g);
+          } else {
+            v[it] = make_float4(g < L ? hd.src[g] : 0.0f, g + 1 < L ? hd.src[g + 1] : 0.0f, g + 2 < L ? hd.src[g + 2] : 0.0f, 0.0f);
+          }
+        }
+#pragma unroll
+        for (int it = 0; it < KPT / 4; ++it) {
+          const int at = it * 64 + lane;
+          *reinterpret_cast<float4*>(rows + stage_piece<KPT>(at / (KPT / 4), at % (KPT / 4))) = v[it];
+        }
+      } else {
+        // Heads of an odd length follow each other: words instead of quads, all of them in flight (one by one: with the gather 128 heads
+        // of 53063 keys 75.3 us, now 64.8; 32 of 60001 39.1, now 29.2).
+        float v[KPT];
+#pragma unroll
+        for (int it = 0; it < KPT; ++it) {
+          const int j = first + it * 64 + lane;
+          v[it] = hd.src[j < L ? j : L - 1];
+        }
+#pragma unroll
+        for (int it = 0; it < KPT; ++it) {
+          const int at = it * 64 + lane;
+          rows[stage_piece<KPT>(at / KPT, at % KPT / 4) + at % 4] = v[it];
         }
       }
-    } else {
-      for (int j = tid; j < L; j += THREADS) stage[(j / KPT) * kRow + (j % KPT)] = hd.src[j];
+      if (R > 0 && lane < 8) rows[64 * KPT + lane] = halo;
     }
-    if (R > 0 && tid < 8) {
-      const int j = tid < 4 ? tid - 4 : THREADS * KPT + (tid - 4);
-      const float v = in_head(j) ? hd.src[j] : -INFINITY;
-      if (tid < 4) stage[-kRow + KPT - 4 + tid] = v;
-      else stage[THREADS * kRow + (tid - 4)] = v;
-    }
-    __syncthreads();
-    // (words of the area that no key was written to are never selected below)
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    // (words that no key of the head was written to are never selected below)
 #pragma unroll
     for (int i = 0; i < KPT; i += 4) {
-      const float4 v = *reinterpret_cast<const float4*>(&stage[tid * kRow + i]);
+      const float4 v = *reinterpret_cast<const float4*>(rows + stage_piece<KPT>(lane, i / 4));
       ext[R + i] = v.x;
       ext[R + i + 1] = v.y;
       ext[R + i + 2] = v.z;
@@ -481,8 +511,8 @@ __global__ __launch_bounds__(THREADS) void topk_reg_kernel(TopkParams p) {
       for (int i = 0; i < KPT; ++i) ext[R + i] = i < nvalid ? ext[R + i] : -INFINITY;
     }
     if (R > 0) {
-      const float4 lv = *reinterpret_cast<const float4*>(&stage[(tid - 1) * kRow + KPT - 4]);
-      const float4 rv = *reinterpret_cast<const float4*>(&stage[(tid + 1) * kRow]);
+      const float4 lv = *reinterpret_cast<const float4*>(rows + (lane > 0 ? stage_piece<KPT>(lane - 1, KPT / 4 - 1) : 64 * KPT));
+      const float4 rv = *reinterpret_cast<const float4*>(rows + (lane < 63 ? stage_piece<KPT>(lane + 1, 0) : 64 * KPT + 4));
       const float left[4] = {lv.x, lv.y, lv.z, lv.w}, right[4] = {rv.x, rv.y, rv.z, rv.w};
 #pragma unroll
       for (int r = 0; r < R; ++r) {  // (words of the area nobody wrote lie outside the head)
@@ -490,7 +520,6 @@ __global__ __launch_bounds__(THREADS) void topk_reg_kernel(TopkParams p) {
         ext[R + KPT + r] = in_head(j0 + KPT + r) ? right[r] : -INFINITY;
       }
     }
-    __syncthreads();  // the runs are out of the staging area: the selection counts in it
   } else {
     if (nvalid == KPT && (reinterpret_cast<uintptr_t>(hd.src + j0) & 15) == 0) {
 #pragma unroll
@@ -547,19 +576,41 @@ __global__ __launch_bounds__(THREADS) void topk_reg_kernel(TopkParams p) {
   }
   if (hd.done) return;
 
-  uint4* bins;
+  // The survivors go out through LDS where there is room (the staging area, which everybody has read by then): whole cache lines
+  // instead of a few words of many.  64 heads of 131072 keys, 3932 kept: pieces 24.7 -> 19.6 us, and the merge, whose lists came in 64 bytes
+  // to a thread and whose positions were fetched one by one, 14.2 -> 12.2.
   if constexpr (kStaged) {
     extern __shared__ float stage_area[];
-    bins = reinterpret_cast<uint4*>(stage_area);  // (every run is out of it)
+    uint4* bins = reinterpret_cast<uint4*>(stage_area + reg_variant_rows_bytes(THREADS, KPT) / (int)sizeof(float));
+    if constexpr (PIECES) {
+      constexpr int kRoom = reg_variant_rows_bytes(THREADS, KPT) / (int)sizeof(uint2);
+      uint2* kept = reinterpret_cast<uint2*>(stage_area);
+      const bool room = hd.keep <= kRoom;
+      topk_select<THREADS, KPT, true>(key, L, hd.keep, bins, whole, [&](int i, uint32_t slot) {
+        if (room) {
+          kept[slot] = make_uint2(key[i], (uint32_t)(hd.base + j0 + i));
+        } else {
+          hd.out_key[slot] = key[i];
+          hd.out[slot] = hd.base + j0 + i;
+        }
+      });
+      if (!room) return;
+      __syncthreads();
+      for (int s = tid; s < hd.keep; s += THREADS) {
+        const uint2 v = kept[s];
+        hd.out_key[s] = v.x;
+        hd.out[s] = (int32_t)v.y;
+      }
+    } else {
+      int32_t* kept = reinterpret_cast<int32_t*>(stage_area);
+      topk_select<THREADS, KPT, false>(key, L, hd.keep, bins, whole, [&](int i, uint32_t slot) { kept[slot] = j0 + i; });
+      __syncthreads();
+      for (int s = tid; s < hd.keep; s += THREADS) hd.out[s] = kept[s];
+    }
   } else {
-    __shared__ uint4 own_bins[THREADS];
-    bins = own_bins;
+    __shared__ uint4 bins[THREADS];
+    topk_select<THREADS, KPT, false>(key, L, hd.keep, bins, whole, [&](int i, uint32_t slot) { hd.out[slot] = j0 + i; });
   }
-  const bool piece = hd.out_key != nullptr;
-  topk_select<THREADS, KPT>(key, L, hd.keep, bins, whole, piece, [&](int i, uint32_t k, uint32_t slot) {
-    hd.out[slot] = hd.base + j0 + i;
-    if (piece) hd.out_key[slot] = k;
-  });
 }
 
 // ---- a long head whose pieces have been through topk_reg_kernel: the `keep` largest of the candidates they left.
@@ -567,6 +618,13 @@ __global__ __launch_bounds__(THREADS) void topk_reg_kernel(TopkParams p) {
 // are empty.  Candidates are in ascending position inside a list and the lists in piece order, so ties still go to
 // the lowest position and the result is ascending.
 constexpr int kTopkMaxSegs = 64;
+// Up to 32 slots to a thread, a wave's part of the candidate lists comes in with coalesced loads and is dealt out to its threads through
+// rows of LDS, as in topk_reg_kernel (a thread reading its own run straight from memory makes every load touch 64 cache lines); the
+// area is then the bins', and in the end the survivors'.
+constexpr bool merge_variant_is_staged(int kpt) { return kpt <= 32; }
+constexpr int merge_variant_bytes(int threads, int kpt) {
+  return merge_variant_is_staged(kpt) ? threads * (kpt + 4) * (int)sizeof(int32_t) : 0;
+}
 template <int THREADS, int KPT>
 __global__ __launch_bounds__(THREADS) void topk_merge_kernel(TopkParams p) {
   __shared__ int32_t seg_count[kTopkMaxSegs];
@@ -584,41 +642,89 @@ __global__ __launch_bounds__(THREADS) void topk_merge_kernel(TopkParams p) {
   if (tid == 0) p.count[head] = keep;
   if (keep == 0) return;
   const int nseg = p.n_segs, slots = nseg * p.budget;
-  if (tid < nseg) seg_count[tid] = p.cand_count[head * nseg + tid];
-  __syncthreads();
+  int32_t of_seg = 0;
+  if (tid < nseg) of_seg = p.cand_count[head * nseg + tid];
   const uint32_t* ck = p.cand_key + head * slots;
   const int32_t* ci = p.cand_idx + head * slots;
   int32_t* out = p.idx + head * p.budget;
   const int s0 = tid * KPT;
   int seg = quotient(s0, p.inv_budget), r = s0 - seg * p.budget;  // (at most 65536 slots)
-  uint32_t key[KPT];
-  // (16-byte loads of slots that hold no candidate read the workspace's old contents, which are dropped)
+  // (slots that hold no candidate are read too: the workspace's old contents, which are dropped)
   const bool quads = (slots & 3) == 0 && (reinterpret_cast<uintptr_t>(ck) & 15) == 0;
+  constexpr bool kStaged = merge_variant_is_staged(KPT);
+  constexpr int kRow = KPT + 4;
+  extern __shared__ float stage_area[];
+  uint32_t* rows = reinterpret_cast<uint32_t*>(stage_area);
+  uint32_t key[KPT], at[KPT];
+  // val[i] = list[s0 + i], for the slots there are
+  auto load_run = [&](const uint32_t* list, uint32_t (&val)[KPT]) {
+    if constexpr (kStaged) {
+      const int lane = tid & 63, first = (tid - lane) * KPT;  // a wave's own slots: nothing is shared with the others
+      if (quads) {
 #pragma unroll
-  for (int i = 0; i < KPT; i += 4) {
-    if (quads && s0 + i < slots) {
-      const uint4 v = *reinterpret_cast<const uint4*>(ck + s0 + i);
-      key[i] = v.x;
-      key[i + 1] = v.y;
-      key[i + 2] = v.z;
-      key[i + 3] = v.w;
+        for (int i = 0; i < KPT; i += 4) {
+          const int g = first + i * 64 + lane * 4;
+          if (g < slots) *reinterpret_cast<uint4*>(&rows[g / KPT * kRow + g % KPT]) = *reinterpret_cast<const uint4*>(list + g);
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < KPT; ++i) {
+          const int g = first + i * 64 + lane;
+          if (g < slots) rows[g / KPT * kRow + g % KPT] = list[g];
+        }
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+      for (int i = 0; i < KPT; i += 4) {
+        const uint4 v = *reinterpret_cast<const uint4*>(&rows[tid * kRow + i]);
+        val[i] = v.x;
+        val[i + 1] = v.y;
+        val[i + 2] = v.z;
+        val[i + 3] = v.w;
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // (the next list goes through the same rows)
+    } else {
+#pragma unroll
+      for (int i = 0; i < KPT; i += 4) {
+        if (quads && s0 + i < slots) {
+          const uint4 v = *reinterpret_cast<const uint4*>(list + s0 + i);
+          val[i] = v.x;
+          val[i + 1] = v.y;
+          val[i + 2] = v.z;
+          val[i + 3] = v.w;
+        } else if (!quads) {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) val[i + u] = s0 + i + u < slots ? list[s0 + i + u] : 0u;
+        }
+      }
     }
-  }
+  };
+  load_run(ck, key);
+  if constexpr (kStaged) load_run(reinterpret_cast<const uint32_t*>(ci), at);
+  if (tid < nseg) seg_count[tid] = of_seg;
+  __syncthreads();
 #pragma unroll
   for (int i = 0; i < KPT; ++i) {
     const bool valid = s0 + i < slots && r < seg_count[seg < nseg ? seg : 0];
-    if (!quads) key[i] = valid ? ck[s0 + i] : 0u;
     key[i] = valid ? key[i] : 0u;
     if (++r == p.budget) {
       r = 0;
       ++seg;
     }
   }
-  __shared__ uint4 bins[THREADS];
   int n_keys = 0;
   for (int i = 0; i < nseg; ++i) n_keys += seg_count[i];
-  topk_select<THREADS, KPT>(key, n_keys, keep, bins, false, false,
-                            [&](int i, uint32_t, uint32_t slot) { out[slot] = ci[s0 + i]; });
+  if constexpr (kStaged) {
+    // (all rows have been read: there was a barrier)
+    int32_t* kept = reinterpret_cast<int32_t*>(stage_area);
+    topk_select<THREADS, KPT, true>(key, n_keys, keep, reinterpret_cast<uint4*>(stage_area), false,
+                                    [&](int i, uint32_t slot) { kept[slot] = (int32_t)at[i]; });
+    __syncthreads();
+    for (int s = tid; s < keep; s += THREADS) out[s] = kept[s];
+  } else {
+    __shared__ uint4 bins[THREADS];
+    topk_select<THREADS, KPT, false>(key, n_keys, keep, bins, false, [&](int i, uint32_t slot) { out[slot] = ci[s0 + i]; });
+  }
 }
 
 // ---- longer heads
@@ -630,7 +736,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_stream_kernel(TopkParams p)
   uint32_t* keys = smem + kStreamLdsHead;  // [kTopkLdsKeys] staged order keys (if they fit)
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const TopkHead hd = topk_head(p);
+  const TopkHead hd = topk_head<false>(p);
   if (hd.done) return;
   const int L = hd.L;
   const float* src = hd.src;
@@ -776,34 +882,69 @@ RegVariant reg_variant_for(int64_t len) {
   return {1024, 64};
 }
 
-template <int R>
-int launch_reg(RegVariant v, dim3 grid, hipStream_t st, const TopkParams& p) {
-  if (v.threads == 256 && v.kpt == 32) hipLaunchKernelGGL((topk_reg_kernel<256, 32, R>), grid, dim3(256), 0, st, p);
-  else if (v.threads == 512) hipLaunchKernelGGL((topk_reg_kernel<512, 32, R>), grid, dim3(512), 0, st, p);
-  else if (v.kpt == 32) {
-    constexpr int kBytes = reg_variant_stage_bytes(1024, 32);
-    const int rc = set_max_dynamic_lds(reinterpret_cast<const void*>(topk_reg_kernel<1024, 32, R>), kBytes);
+// The kernel for a launch of `heads` heads of at most `longest` keys that variant v holds.  Eight keys to a thread instead of 32 make
+// four times the waves, which hide each other's waits, of as many instructions; up to 4096 keys they are also the faster ones where
+// several workgroups share a compute unit, beyond that only while there is one for every head.  Pooling and selection, us, 8 / 256 /
+// 512 / 1024 heads: 1000 keys 256 x 32 8.3 / 9.0 / 9.8 / 12.5, 256 x 8 5.7 / 6.2 / 6.6 / 7.6; 4000 keys 256 x 32 8.6 / 9.1 / 10.2 / 13.1,
+// 512 x 8 6.2 / 6.7 / 8.1 / 11.0; 8000 keys 256 x 32 8.8 / 9.5 / 10.6 / 14.6, 1024 x 8 7.8 / 8.6 / 11.9 / 20.9.  (16000 keys: 512 x 32 10.0 /
+// 10.6 / 15.0, 1024 x 16 9.8 / 10.6 / 20.3.)
+RegVariant reg_kernel_for(RegVariant v, int64_t longest, int64_t heads) {
+  if (longest <= 256 * 8) return {256, 8};
+  if (longest <= 512 * 8) return {512, 8};
+  if (longest <= 1024 * 8 && heads <= 256) return {1024, 8};
+  return v;
+}
+
+template <int THREADS, int KPT, int R, bool PIECES>
+int launch_reg_kernel(dim3 grid, hipStream_t st, const TopkParams& p) {
+  constexpr int kBytes = reg_variant_stage_bytes(THREADS, KPT);
+  if (kBytes > 0) {
+    const int rc = set_max_dynamic_lds(reinterpret_cast<const void*>(topk_reg_kernel<THREADS, KPT, R, PIECES>), kBytes);
     if (rc != DAPQ_OK) return rc;
-    hipLaunchKernelGGL((topk_reg_kernel<1024, 32, R>), grid, dim3(1024), kBytes, st, p);
-  } else hipLaunchKernelGGL((topk_reg_kernel<1024, 64, R>), grid, dim3(1024), 0, st, p);
+  }
+  hipLaunchKernelGGL((topk_reg_kernel<THREADS, KPT, R, PIECES>), grid, dim3(THREADS), kBytes, st, p);
   return DAPQ_OK;
 }
 
-int launch_reg_radius(int radius, RegVariant v, dim3 grid, hipStream_t st, const TopkParams& p) {
+template <int R>
+int launch_reg(RegVariant v, bool pieces, dim3 grid, hipStream_t st, const TopkParams& p) {
+  if (pieces) return launch_reg_kernel<1024, 32, R, true>(grid, st, p);
+  if (v.kpt == 8) {
+    if (v.threads == 256) return launch_reg_kernel<256, 8, R, false>(grid, st, p);
+    if (v.threads == 512) return launch_reg_kernel<512, 8, R, false>(grid, st, p);
+    return launch_reg_kernel<1024, 8, R, false>(grid, st, p);
+  }
+  if (v.threads == 256) return launch_reg_kernel<256, 32, R, false>(grid, st, p);
+  if (v.threads == 512) return launch_reg_kernel<512, 32, R, false>(grid, st, p);
+  if (v.kpt == 32) return launch_reg_kernel<1024, 32, R, false>(grid, st, p);
+  return launch_reg_kernel<1024, 64, R, false>(grid, st, p);
+}
+
+int launch_reg_radius(int radius, RegVariant v, bool pieces, dim3 grid, hipStream_t st, const TopkParams& p) {
   switch (radius) {
-    case 0: return launch_reg<0>(v, grid, st, p);
-    case 1: return launch_reg<1>(v, grid, st, p);
-    case 2: return launch_reg<2>(v, grid, st, p);
-    case 3: return launch_reg<3>(v, grid, st, p);
-    default: return launch_reg<4>(v, grid, st, p);
+    case 0: return launch_reg<0>(v, pieces, grid, st, p);
+    case 1: return launch_reg<1>(v, pieces, grid, st, p);
+    case 2: return launch_reg<2>(v, pieces, grid, st, p);
+    case 3: return launch_reg<3>(v, pieces, grid, st, p);
+    default: return launch_reg<4>(v, pieces, grid, st, p);
   }
 }
 
-void launch_merge(RegVariant v, dim3 grid, hipStream_t st, const TopkParams& p) {
-  if (v.threads == 256) hipLaunchKernelGGL((topk_merge_kernel<256, 32>), grid, dim3(256), 0, st, p);
-  else if (v.kpt == 16) hipLaunchKernelGGL((topk_merge_kernel<1024, 16>), grid, dim3(1024), 0, st, p);
-  else if (v.kpt == 32) hipLaunchKernelGGL((topk_merge_kernel<1024, 32>), grid, dim3(1024), 0, st, p);
-  else hipLaunchKernelGGL((topk_merge_kernel<1024, 64>), grid, dim3(1024), 0, st, p);
+template <int THREADS, int KPT>
+int launch_merge_kernel(dim3 grid, hipStream_t st, const TopkParams& p) {
+  constexpr int kBytes = merge_variant_bytes(THREADS, KPT);
+  if (kBytes > 0) {
+    const int rc = set_max_dynamic_lds(reinterpret_cast<const void*>(topk_merge_kernel<THREADS, KPT>), kBytes);
+    if (rc != DAPQ_OK) return rc;
+  }
+  hipLaunchKernelGGL((topk_merge_kernel<THREADS, KPT>), grid, dim3(THREADS), kBytes, st, p);
+  return DAPQ_OK;
+}
+int launch_merge(RegVariant v, dim3 grid, hipStream_t st, const TopkParams& p) {
+  if (v.threads == 256) return launch_merge_kernel<256, 32>(grid, st, p);
+  if (v.kpt == 16) return launch_merge_kernel<1024, 16>(grid, st, p);
+  if (v.kpt == 32) return launch_merge_kernel<1024, 32>(grid, st, p);
+  return launch_merge_kernel<1024, 64>(grid, st, p);
 }
 
 int topk_common_checks(const dapq_shape* shape, const float* in, int32_t budget, const int32_t* idx, const int32_t* count) {
@@ -823,7 +964,7 @@ int topk_common_checks(const dapq_shape* shape, const float* in, int32_t budget,
 // each skipping the heads of the other.
 constexpr int kTopkPieceLen = 1024 * 32;
 struct TopkRoute {
-  RegVariant variant;
+  RegVariant variant, kernel;  // what the short heads' kernel has to hold, and the kernel
   int64_t reg_max;     // heads up to this length: the register variant
   bool any_short, any_long;
   // the long heads in pieces
@@ -844,6 +985,8 @@ TopkRoute topk_route(const dapq_shape* shape, int32_t budget, bool with_pieces) 
   if (with_pieces && sized_for > kTopkPieceLen) sized_for = kTopkPieceLen;
   r.variant = reg_variant_for(sized_for);
   r.reg_max = r.variant.max_len();
+  const int64_t heads = (int64_t)shape->n_layers * shape->batch * shape->n_kv_heads;
+  r.kernel = reg_kernel_for(r.variant, longest < r.reg_max ? longest : r.reg_max, heads);
   r.any_short = ragged || mean <= r.reg_max;  // (a dense batch of longer heads has nothing for the register variant)
   r.any_long = longest > r.reg_max;
   const int64_t n_segs = (longest + kTopkPieceLen - 1) / kTopkPieceLen;
@@ -852,12 +995,11 @@ TopkRoute topk_route(const dapq_shape* shape, int32_t budget, bool with_pieces) 
   r.n_segs = (int)n_segs;
   r.off_key = r.off_idx = r.off_count = r.pieces_bytes = 0;
   if (r.pieces_possible) {
-    const size_t heads = (size_t)shape->n_layers * shape->batch * shape->n_kv_heads;
-    const size_t list = align_up(heads * (size_t)n_segs * (size_t)budget * 4, 256);
+    const size_t list = align_up((size_t)heads * (size_t)n_segs * (size_t)budget * 4, 256);
     r.off_key = 0;
     r.off_idx = list;
     r.off_count = 2 * list;
-    r.pieces_bytes = 2 * list + align_up(heads * (size_t)n_segs * 4, 256);
+    r.pieces_bytes = 2 * list + align_up((size_t)heads * (size_t)n_segs * 4, 256);
   }
   return r;
 }
@@ -878,16 +1020,17 @@ int launch_long_heads(const dapq_shape* shape, const TopkRoute& r, TopkParams p,
     p.cand_idx = reinterpret_cast<int32_t*>(ws + r.off_idx);
     p.cand_count = reinterpret_cast<int32_t*>(ws + r.off_count);
     const dim3 piece_grid((unsigned)(shape->n_kv_heads * r.n_segs), (unsigned)shape->batch, (unsigned)shape->n_layers);
-    const int rc = launch_reg_radius(radius, RegVariant{1024, 32}, piece_grid, st, p);
+    int rc = launch_reg_radius(radius, RegVariant{1024, 32}, true, piece_grid, st, p);
     if (rc != DAPQ_OK) return rc;
     DAPQ_HIP_LAUNCH_CHECK("topk_reg_kernel (pieces)");
     // (one workgroup per long head: from 8193 candidate slots on, the large workgroup's sixteen waves)
     const int64_t slots = (int64_t)r.n_segs * p.budget;
-    launch_merge(slots <= 256 * 32    ? RegVariant{256, 32}
-                 : slots <= 1024 * 16 ? RegVariant{1024, 16}
-                 : slots <= 1024 * 32 ? RegVariant{1024, 32}
-                                      : RegVariant{1024, 64},
-                 grid, st, p);
+    rc = launch_merge(slots <= 256 * 32    ? RegVariant{256, 32}
+                      : slots <= 1024 * 16 ? RegVariant{1024, 16}
+                      : slots <= 1024 * 32 ? RegVariant{1024, 32}
+                                           : RegVariant{1024, 64},
+                      grid, st, p);
+    if (rc != DAPQ_OK) return rc;
     DAPQ_HIP_LAUNCH_CHECK("topk_merge_kernel");
     return DAPQ_OK;
   }
@@ -959,7 +1102,7 @@ extern "C" DAPQ_API int dapq_topk(const dapq_shape* shape, const float* pooled, 
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (route.any_short) {
     p.max_len = (int32_t)route.reg_max;
-    if ((rc = launch_reg<0>(route.variant, grid, st, p)) != DAPQ_OK) return rc;
+    if ((rc = launch_reg<0>(route.kernel, false, grid, st, p)) != DAPQ_OK) return rc;
     DAPQ_HIP_LAUNCH_CHECK("topk_reg_kernel");
   }
   if (route.any_long) return launch_long_heads(shape, route, p, 0, workspace, workspace_bytes, st);
@@ -977,6 +1120,7 @@ extern "C" DAPQ_API int dapq_pool_topk(const dapq_shape* shape, const float* sco
   const int64_t longest = shape->cu_seqlens == nullptr ? shape->total_tokens / shape->batch : shape->total_tokens;
   const dim3 grid((unsigned)shape->n_kv_heads, (unsigned)shape->batch, (unsigned)shape->n_layers);
   hipStream_t st = static_cast<hipStream_t>(stream);
+  const int64_t heads = (int64_t)shape->n_layers * shape->batch * shape->n_kv_heads;
   TopkParams p = topk_params(shape, scores, pooled, budget, budget_per_seq, idx, count);
   const TopkRoute route = topk_route_for(shape, budget, workspace, workspace_bytes);
   if (width <= 9 && route.any_long && route.pieces_possible && workspace != nullptr &&
@@ -985,14 +1129,15 @@ extern "C" DAPQ_API int dapq_pool_topk(const dapq_shape* shape, const float* sco
     // workgroup each
     if (route.any_short) {
       p.max_len = (int32_t)route.reg_max;
-      if ((rc = launch_reg_radius(width / 2, route.variant, grid, st, p)) != DAPQ_OK) return rc;
+      if ((rc = launch_reg_radius(width / 2, route.kernel, false, grid, st, p)) != DAPQ_OK) return rc;
       DAPQ_HIP_LAUNCH_CHECK("topk_reg_kernel");
     }
     return launch_long_heads(shape, route, p, width / 2, workspace, workspace_bytes, st);
   }
   if (width <= 9 && longest <= 64 * kTopkThreads) {
     // one kernel: every head fits a register variant, which pools on the way in
-    if ((rc = launch_reg_radius(width / 2, reg_variant_for(longest), grid, st, p)) != DAPQ_OK) return rc;
+    const RegVariant v = reg_kernel_for(reg_variant_for(longest), longest, heads);
+    if ((rc = launch_reg_radius(width / 2, v, false, grid, st, p)) != DAPQ_OK) return rc;
     DAPQ_HIP_LAUNCH_CHECK("topk_reg_kernel");
     return DAPQ_OK;
   }

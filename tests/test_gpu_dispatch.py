@@ -603,3 +603,53 @@ def test_row_blocks_of_a_wave(H, rows, lens, layers, ragged):
     H.D.dapq_score_accumulate(shape, prob.q, prob.k, lse, X, ws)
     assert torch.equal(X, X[:1].expand_as(X))
     H.assert_scores_close(X[:1].cpu().numpy(), O.score(q, k, 1, cu, None, kp), f"extended, rows={rows}")
+
+
+def selection_call(H, S, batch, width, budget, pieces):
+    """dapq_pool_topk over scores [layers][heads][batch * length]: positions, counts and pooled scores on the host."""
+    layers, heads, tokens = S.shape
+    shape = H.D.make_shape(n_layers=layers, batch=batch, n_q_heads=heads, n_kv_heads=heads, n_pseudo=1, total_tokens=tokens, scale=1.0)
+    n = H.D.topk_workspace_bytes(shape, budget) if pieces else 0
+    ws = torch.full((n,), 0xA5, dtype=torch.uint8, device="cuda") if n else None
+    dev = torch.from_numpy(S).cuda()
+    idx = torch.full((layers, batch, heads, budget), -7, dtype=torch.int32, device="cuda")
+    count = torch.full((layers, batch, heads), -7, dtype=torch.int32, device="cuda")
+    pooled = torch.full_like(dev, float("nan"))
+    H.D.dapq_pool_topk(shape, dev, width, budget, None, idx, count, pooled, workspace=ws)
+    return idx.cpu().numpy(), count.cpu().numpy(), pooled.cpu().numpy()
+
+
+def check_selection(S, batch, width, budget, got, sample):
+    idx, count, pooled = got
+    length = S.shape[2] // batch
+    for l, b, h in sample:
+        P = O.pool(S[l, h, b * length:(b + 1) * length].astype(np.float64), width)
+        want = O.topk(P, budget)
+        assert np.array_equal(pooled[l, h, b * length:(b + 1) * length].astype(np.float64), P), (l, b, h)
+        assert count[l, b, h] == len(want) and np.array_equal(idx[l, b, h, :len(want)], want), (l, b, h)
+        assert (idx[l, b, h, len(want):] == -7).all()
+
+
+# the lengths around every variant's limit, as many heads as compute units and more, scores on and off 16 bytes (sequences of an odd length
+# follow each other), waves of the last one full, partly filled and empty
+@pytest.mark.parametrize("heads", [4, 300])
+@pytest.mark.parametrize("length", [1, 3, 511, 513, 2047, 2048, 2049, 4095, 4097, 8191, 8192, 8193, 16383, 16385, 32767])
+def test_selection_variants(H, length, heads):
+    """The pooled scores and retained positions are the oracle's, bit for bit."""
+    announce(f"selection variants: {heads} x 2 of {length}")
+    rng = np.random.default_rng(length + heads)
+    S = rng.lognormal(0.0, 0.5, (heads // 4, 2, 2 * length)).astype(np.float32)
+    sample = [(0, 0, 0), (0, 1, 1), (heads // 4 - 1, 1, 0)]
+    for width, budget in ((7, max(1, length // 5)), (1, 40), (9, length + 3)):
+        check_selection(S, 2, width, budget, selection_call(H, S, 2, width, budget, False), sample)
+
+
+# pieces whose survivors fit the area they go out through and not; candidate lists of every merge kernel, of whole quads and not
+@pytest.mark.parametrize("length,budget", [(40001, 100), (40000, 4000), (65539, 4097), (65536, 16000), (65536, 16449), (70001, 20000), (70000, 20001)])
+def test_survivors_of_pieces(H, length, budget):
+    """The pooled scores and retained positions are the oracle's, bit for bit."""
+    announce(f"survivors of pieces: {budget} of {length}")
+    rng = np.random.default_rng(budget)
+    S = rng.lognormal(0.0, 0.5, (2, 2, length)).astype(np.float32)
+    for width in (1, 7):
+        check_selection(S, 1, width, budget, selection_call(H, S, 1, width, budget, True), [(0, 0, 0), (1, 0, 1)])
