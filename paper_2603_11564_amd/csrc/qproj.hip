@@ -219,7 +219,9 @@ __global__ __launch_bounds__(64) void qproj_wave_kernel(QprojParams p) {
 #pragma unroll
       for (int rb = 0; rb < MB; ++rb)
         acc[T][rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[s], xf[rb][s], acc[T][rb], 0, 0, 0);
-    // the slot just read takes the tile of the unit kRing ahead (the MFMAs above have consumed the reads)
+    // the slot just read takes the tile of the unit kRing ahead, once its fragments are in registers: a transfer past the end fetches
+    // nothing and its zeros arrive at once, ahead of reads that are still queued
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     issue(kb + kRing / FT, tile_c);
   };
 

@@ -117,3 +117,25 @@ def test_four_workgroups_of_a_large_tile_call_fit_a_compute_unit(units):
     for kernel, launch in (("score_tile_pass1_kernelILb0E", tile), ("score_tile_pass2_kernelILb0ELb0E", tile + 8 * 128 * 4)):
         static, = (n for name, n in LDS_BYTES.items() if kernel in name)
         assert 4 * (static + launch) <= 160 * 1024, (kernel, static)
+
+
+def transfers_before_reads_are_done(lines):
+    """Transfers from memory into LDS that are issued while reads of LDS may still be queued (in the order of the text)."""
+    queued, found = 0, []
+    for line in lines:
+        if line.startswith("ds_read"):
+            queued += 1
+        wait = re.search(r"lgkmcnt\((\d+)\)", line)
+        if line.startswith("s_waitcnt") and wait:
+            queued = min(queued, int(wait.group(1)))
+        if queued and re.match(r"(buffer_load|global_load)\w* .*\blds\b|global_load_lds", line):
+            found.append(line)
+    return found
+
+
+def test_ring_slots_are_refilled_after_their_reads(units):
+    """A transfer past the end of its source fetches nothing, and its zeros are in LDS before reads that were issued just before it."""
+    assert transfers_before_reads_are_done(["ds_read_b128 v[0:3], v4", "buffer_load_dwordx4 v1, s[0:3], s4 offen lds"]) != []
+    early = {name: found[:2] for src in ("qproj.hip", "score.hip") for name, body in units[src][0].items()
+             if (found := transfers_before_reads_are_done(body))}
+    assert not early, early
