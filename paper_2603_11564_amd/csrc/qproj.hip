@@ -9,7 +9,7 @@
 // The contraction is short in rows (batch * N pseudo tokens, 32 .. 128) and long in the weight
 // (features x hidden, 32 MB per layer for a 4096-wide model), so the kernel is a stream over the
 // weight: every weight element is read from HBM once and meets all rows of a sweep while it is in
-// LDS.  A workgroup is ONE wave.  It owns FT tiles of 32 output features and MB blocks of 32 rows
+// LDS.  The unit of work is ONE wave (a workgroup, or one of four).  It owns FT tiles of 32 output features and MB blocks of 32 rows
 // (FT * MB accumulator tiles, at most 128 registers) and walks the hidden axis in blocks of 64:
 //   * the weight tile of a (hidden block, feature tile) "unit" is 32 rows x 128 B = 4 KB, four
 //     buffer_load_dwordx4 ... lds transfers into a ring of four slots;
@@ -19,12 +19,13 @@
 //   * rows are 128 B apart in LDS; 16-byte chunks are XOR-swizzled by bits 1..3 of the row so that
 //     16 consecutive rows reading the same logical chunk hit 16 different bank groups.
 // The weight is the A operand (D[feature][row]): a lane ends up with runs of four consecutive
-// features of one row, stored as 8 bytes.  Nothing is shared between waves: no barrier anywhere.
+// features of one row, stored as 8 bytes.  Nothing is shared between waves before their sums are done.
 // Work items are numbered sweep -> feature tile -> hidden split -> layer and dealt to the eight XCDs in
 // contiguous ranges: the waves that read the same gathered rows share an L2, and the row sweeps of one
 // feature tile run side by side, so the tile's weights leave HBM once.
-// A call with too few tiles to fill the chip (a single layer) deals the hidden blocks of a tile to
-// several waves; their fp32 sums go to a workspace and qproj_reduce_kernel adds them in a fixed order.
+// A call with too few tiles to fill the chip (a few layers) deals the hidden blocks of a tile to
+// several workgroups, of one wave or of four whose sums meet in LDS (make_qproj_plan); their fp32 sums go to a workspace and
+// qproj_reduce_kernel adds them in a fixed order.
 #include <math.h>
 
 #include <type_traits>
@@ -52,7 +53,7 @@ struct QprojParams {
   int64_t total_tokens;
   int32_t n_layers, rows, hidden, n_features, head_dim;
   int32_t tiles_f, sweeps;
-  int32_t k_splits, kb_per_split;  // hidden blocks are dealt to k_splits waves per tile; > 1 writes fp32 partial sums
+  int32_t k_splits, kb_per_split;  // hidden blocks are dealt to k_splits workgroups per tile; partial: they write fp32 partial sums
   float inv_sweeps, inv_tiles_f, inv_splits;
   float inv_half, inv_heads;       // of head_dim / 2 and n_features / head_dim
   int32_t heads;
@@ -88,19 +89,23 @@ __device__ __forceinline__ void qp_wait_vm() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
-template <int FT, int MB>
-__global__ __launch_bounds__(64) void qproj_wave_kernel(QprojParams p) {
+// WAVES > 1: that many waves, each with a ring of its own and kb_per_split hidden blocks, add their sums up through LDS and write one
+// plane of partial sums.
+template <int FT, int MB, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void qproj_wave_kernel(QprojParams p) {
   constexpr int NXB = XBuffers<FT>::value;
   constexpr int XT = 4 * MB;       // 1 KB transfers per x block
   constexpr int XQ = XT / FT;      // of them riding with one unit
   constexpr int OPS = 4 + XQ;      // transfers per unit
   static_assert(XT % FT == 0 && (kRing % FT == 0) && (kRing - 1) * OPS <= 63, "unit bookkeeping");
-  __shared__ u32x4 lds[QprojLds<FT, MB>::bytes / 16];
+  extern __shared__ u32x4 rings[];
+  const int wave = WAVES > 1 ? qp_uniform((int)(threadIdx.x >> 6)) : 0;
+  u32x4* const lds = rings + wave * (QprojLds<FT, MB>::bytes / 16);
   u32x4* const wring = lds;
   u32x4* const xbuf = lds + kRing * kTileVec;
 
   touch_args<sizeof(QprojParams)>();
-  const int lane = threadIdx.x, n = lane & 31, h = lane >> 5;
+  const int lane = threadIdx.x & 63, n = lane & 31, h = lane >> 5;
   // consecutive work items (all tiles of a layer, layer after layer) go to the same XCD when the grid
   // allows it: the waves that share a layer's x rows then share an L2
   int id = blockIdx.x;
@@ -114,7 +119,7 @@ __global__ __launch_bounds__(64) void qproj_wave_kernel(QprojParams p) {
   const int layer = uniform_quotient(rest2, p.k_splits, p.inv_splits), split = rest2 - layer * p.k_splits;
   const int f0 = tile * (32 * FT), m0 = sweep * (32 * MB);
   // this wave's hidden blocks [kb0, n_kb)
-  const int kb0 = split * p.kb_per_split;
+  const int kb0 = (split * WAVES + wave) * p.kb_per_split;
   const int n_kb = min(p.hidden / kBlockK, kb0 + p.kb_per_split);
 
   // ---- transfer addressing: lane (r0 = lane / 8, pos = lane % 8) fills LDS chunk `pos` of row 8i + r0 of a
@@ -214,15 +219,15 @@ __global__ __launch_bounds__(64) void qproj_wave_kernel(QprojParams p) {
     bf16x8 wf[4];
 #pragma unroll
     for (int s = 0; s < 4; ++s) wf[s] = __builtin_bit_cast(bf16x8, slot[frag_idx[s]]);
+    // the slot just read takes the tile of the unit kRing ahead, once its fragments are in registers: a transfer past the end fetches
+    // nothing and its zeros arrive at once, ahead of reads that are still queued
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    issue(kb + kRing / FT, tile_c);
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
       for (int rb = 0; rb < MB; ++rb)
         acc[T][rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[s], xf[rb][s], acc[T][rb], 0, 0, 0);
-    // the slot just read takes the tile of the unit kRing ahead, once its fragments are in registers: a transfer past the end fetches
-    // nothing and its zeros arrive at once, ahead of reads that are still queued
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    issue(kb + kRing / FT, tile_c);
   };
 
   for (int kb = kb0; kb < n_kb; ++kb) {
@@ -236,19 +241,41 @@ __global__ __launch_bounds__(64) void qproj_wave_kernel(QprojParams p) {
   qp_wait_vm<0>();
 
   // ---- epilogue: accumulator register v of lane (n, h) is feature 8 (v / 4) + 4 h + v % 4 of the tile, row n
-  if (p.partial != nullptr) {
-    // one of several waves of this tile: the fp32 sums go to this split's plane, padding included
+  if constexpr (FT == 2) if (WAVES > 1 || p.partial != nullptr) {  // (calls of four-tile waves fill the chip: make_qproj_plan)
+    // one of several workgroups of this tile: the fp32 sums go to this split's plane, padding included; through LDS (the rings are
+    // drained) so that a store covers whole cache lines instead of 32 bytes of 32 rows (one layer 4096 wide, 64 rows, 8 splits: 8.4 MB
+    // of sums, kernel 10.3 -> 9.2 us)
     const int64_t rows_pad = (int64_t)p.sweeps * (32 * MB), feat_pad = (int64_t)p.tiles_f * (32 * FT);
     float* plane = p.partial + ((int64_t)split * p.n_layers + layer) * rows_pad * feat_pad;
+    constexpr int kRow = 32 * FT + 4, kQuads = 8 * FT;  // words and quads of a row of the tile
+    static_assert(32 * MB * kRow * 4 <= QprojLds<FT, MB>::bytes, "a wave's sums fit where its ring was");
+    float* sums = reinterpret_cast<float*>(lds);
 #pragma unroll
     for (int rb = 0; rb < MB; ++rb)
 #pragma unroll
       for (int t = 0; t < FT; ++t)
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          float4 o = make_float4(acc[t][rb][4 * g], acc[t][rb][4 * g + 1], acc[t][rb][4 * g + 2], acc[t][rb][4 * g + 3]);
-          *reinterpret_cast<float4*>(plane + (int64_t)(m0 + 32 * rb + n) * feat_pad + f0 + 32 * t + 8 * g + 4 * h) = o;
-        }
+        for (int g = 0; g < 4; ++g)
+          *reinterpret_cast<float4*>(sums + (32 * rb + n) * kRow + 32 * t + 8 * g + 4 * h) =
+              make_float4(acc[t][rb][4 * g], acc[t][rb][4 * g + 1], acc[t][rb][4 * g + 2], acc[t][rb][4 * g + 3]);
+    if constexpr (WAVES > 1) __syncthreads();
+    else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    constexpr int kWaveWords = QprojLds<FT, MB>::bytes / 4;
+#pragma unroll
+    for (int i = 0; i < 32 * MB * kQuads / (64 * WAVES); ++i) {
+      const int at = i * (64 * WAVES) + (int)threadIdx.x, row = at / kQuads, quad = at % kQuads;
+      const float* src = reinterpret_cast<const float*>(rings) + row * kRow + 4 * quad;
+      float4 o = *reinterpret_cast<const float4*>(src);
+#pragma unroll
+      for (int w = 1; w < WAVES; ++w) {  // in the order of the hidden blocks
+        const float4 v = *reinterpret_cast<const float4*>(src + w * kWaveWords);
+        o.x += v.x;
+        o.y += v.y;
+        o.z += v.z;
+        o.w += v.w;
+      }
+      *reinterpret_cast<float4*>(plane + (int64_t)(m0 + row) * feat_pad + f0 + 4 * quad) = o;
+    }
     return;
   }
 #pragma unroll
@@ -304,8 +331,7 @@ __global__ void qproj_reduce_kernel(QprojParams p, int rows_pad, int feat_pad) {
 
 // The same with the rotation (what rope_kernel would do next, to the same bits): a thread per (layer, head, row, channel
 // pair).  All its loads are in flight before the angle is evaluated, which takes as long as they do.  One layer 4096 wide,
-// 64 rows: sums 4.3 us + rotation 3.7 us -> 3.9 us (two heads to a thread, sharing the angle: 7.3 us); the call 16.7 ->
-// 12.4 us.
+// 64 rows: sums of eight planes 4.3 us + rotation 3.7 us -> 3.9 us (two heads to a thread, sharing the angle: 7.3 us); of four 2.8.
 template <int SPLITS>
 __global__ __launch_bounds__(256) void qproj_reduce_rope_kernel(QprojParams p, int rows_pad, int feat_pad, const int32_t* positions,
                                                                 double neg_log2_theta_2_over_d, int pairing) {
@@ -342,16 +368,25 @@ __global__ __launch_bounds__(256) void qproj_reduce_rope_kernel(QprojParams p, i
   dst[ib] = f64_to_bf16(xb * cs + xa * sn);
 }
 
-template <int FT, int MB>
-void launch_qproj(const QprojParams& p, hipStream_t stream) {
+template <int FT, int MB, int WAVES>
+int launch_qproj(const QprojParams& p, hipStream_t stream) {
+  constexpr int kBytes = WAVES * QprojLds<FT, MB>::bytes;
+  if (kBytes > 64 * 1024) {
+    const int rc = set_max_dynamic_lds(reinterpret_cast<const void*>(qproj_wave_kernel<FT, MB, WAVES>), kBytes);
+    if (rc != DAPQ_OK) return rc;
+  }
   const int64_t grid = (int64_t)p.tiles_f * p.sweeps * p.k_splits * p.n_layers;
-  hipLaunchKernelGGL((qproj_wave_kernel<FT, MB>), dim3((unsigned)grid), dim3(64), 0, stream, p);
+  hipLaunchKernelGGL((qproj_wave_kernel<FT, MB, WAVES>), dim3((unsigned)grid), dim3(64 * WAVES), kBytes, stream, p);
+  DAPQ_HIP_LAUNCH_CHECK("qproj_wave_kernel");
+  return DAPQ_OK;
 }
+
+constexpr int64_t kQprojUnits = 256;  // compute units
 
 // How a call is cut into waves; a pure function of the description so that the workspace query and the
 // launcher agree.
 struct QprojPlan {
-  int ft, mb, tiles_f, sweeps, k_splits, kb_per_split;
+  int ft, mb, waves, tiles_f, sweeps, k_splits, kb_per_split;  // waves of a workgroup, workgroups along the hidden axis, blocks to a wave
   size_t workspace_bytes;
 };
 
@@ -375,6 +410,32 @@ QprojPlan make_qproj_plan(const dapq_qproj& s) {
   pl.workspace_bytes = pl.k_splits == 1 ? 0
                                         : (size_t)pl.k_splits * s.n_layers * ((size_t)pl.sweeps * 32 * pl.mb) *
                                               ((size_t)pl.tiles_f * 32 * pl.ft) * sizeof(float);
+  pl.waves = 1;
+  if (pl.k_splits == 1) return pl;
+  // Four waves to a workgroup, which has a compute unit to itself, add up before they write: half the planes or fewer, and more of
+  // the weight in flight.  As many workgroups along the hidden axis as cost least, in blocks of four waves: a workgroup's own and a start-up of
+  // two; no more planes than the workspace holds, and not more than eight, which cost the kernel that adds them.  Single waves share a
+  // compute unit four or five at a time (their rings), write a plane each and are slower by a tenth or more for the same cost; they
+  // stay where whole rounds of workgroups do not come out.  Whole call, us, single waves -> four: one layer 4096 wide, 64 rows 14.4 -> 14.0
+  // (three launches of the host); 256 rows 24.0 -> 20.9; 2 layers 22.8 -> 18.0; 8 layers 83.0 -> 66.8, of 16 rows 73.5 -> 55.7; 5120 wide, 64
+  // rows 18.5 -> 16.5; 8 layers 5120 wide, 32 rows 87.9 -> 92.8 (stays).
+  const int per_unit = pl.mb == 2 ? 4 : 5;
+  const int64_t tiles = waves, singles = tiles * pl.k_splits, units = kQprojUnits;
+  const int64_t together = per_unit > 4 && singles > 4 * units ? 5 : 4;  // (fewer than four take a block no faster)
+  int64_t best = (singles + units * per_unit - 1) / (units * per_unit) * (pl.kb_per_split * together + 8);  // (four times blocks)
+  best += best / 10;
+  const int most = pl.k_splits < 8 ? pl.k_splits : 8;
+  for (int splits = 1; splits <= most; ++splits) {
+    const int each = (n_kb + 4 * splits - 1) / (4 * splits);
+    if ((int64_t)(splits - 1) * 4 * each >= n_kb) continue;  // (a workgroup without blocks)
+    const int64_t cost = (tiles * splits + units - 1) / units * (each + 2) * 4;
+    if (cost < best) {
+      best = cost;
+      pl.waves = 4;
+      pl.k_splits = splits;
+      pl.kb_per_split = each;
+    }
+  }
   return pl;
 }
 
@@ -466,28 +527,39 @@ extern "C" DAPQ_API int dapq_pseudo_queries(const dapq_qproj* desc, const void* 
   p.heads = s.n_q_heads;
   p.inv_half = s.head_dim >= 2 ? 1.0f / (float)(s.head_dim / 2) : 1.0f;
   p.inv_heads = 1.0f / (float)s.n_q_heads;
-  p.partial = pl.k_splits > 1 ? static_cast<float*>(workspace) : nullptr;
+  const bool split = pl.workspace_bytes > 0;
+  p.partial = split ? static_cast<float*>(workspace) : nullptr;
   DAPQ_REQUIRE((int64_t)p.tiles_f * p.sweeps * p.k_splits * s.n_layers < ((int64_t)1 << 31), DAPQ_ERR_UNSUPPORTED,
                "too many tiles");
   hipStream_t st = static_cast<hipStream_t>(stream);
-  if (pl.ft == 4 && pl.mb == 2) launch_qproj<4, 2>(p, st);
-  else if (pl.ft == 4) launch_qproj<4, 1>(p, st);
-  else if (pl.mb == 2) launch_qproj<2, 2>(p, st);
-  else launch_qproj<2, 1>(p, st);
-  DAPQ_HIP_LAUNCH_CHECK("qproj_wave_kernel");
-  if (pl.k_splits > 1 && positions != nullptr) {
+  int rc2;
+  if (pl.waves == 4) rc2 = pl.mb == 2 ? launch_qproj<2, 2, 4>(p, st) : launch_qproj<2, 1, 4>(p, st);
+  else if (pl.ft == 4) rc2 = pl.mb == 2 ? launch_qproj<4, 2, 1>(p, st) : launch_qproj<4, 1, 1>(p, st);
+  else rc2 = pl.mb == 2 ? launch_qproj<2, 2, 1>(p, st) : launch_qproj<2, 1, 1>(p, st);
+  if (rc2 != DAPQ_OK) return rc2;
+  if (split && positions != nullptr) {
     // (a split call has fewer than 768 tiles of 64 features and 64 rows: fewer than 2^13 heads of all layers, and 2^21 channel pairs)
     const dim3 grid((unsigned)(((int64_t)s.rows * (s.head_dim / 2) + 255) / 256), (unsigned)(s.n_q_heads * s.n_layers));
     const int rows_pad = pl.sweeps * 32 * pl.mb, feat_pad = pl.tiles_f * 32 * pl.ft;
     const double e = rope_exponent(theta, s.head_dim);
-    if (pl.k_splits == 2) hipLaunchKernelGGL(qproj_reduce_rope_kernel<2>, grid, dim3(256), 0, st, p, rows_pad, feat_pad, positions, e, pairing);
-    else if (pl.k_splits == 4) hipLaunchKernelGGL(qproj_reduce_rope_kernel<4>, grid, dim3(256), 0, st, p, rows_pad, feat_pad, positions, e, pairing);
-    else if (pl.k_splits == 8) hipLaunchKernelGGL(qproj_reduce_rope_kernel<8>, grid, dim3(256), 0, st, p, rows_pad, feat_pad, positions, e, pairing);
-    else hipLaunchKernelGGL(qproj_reduce_rope_kernel<16>, grid, dim3(256), 0, st, p, rows_pad, feat_pad, positions, e, pairing);
+#define DAPQ_REDUCE(planes) \
+  case planes: hipLaunchKernelGGL(qproj_reduce_rope_kernel<planes>, grid, dim3(256), 0, st, p, rows_pad, feat_pad, positions, e, pairing); break
+    switch (pl.k_splits) {
+      DAPQ_REDUCE(1);
+      DAPQ_REDUCE(2);
+      DAPQ_REDUCE(3);
+      DAPQ_REDUCE(4);
+      DAPQ_REDUCE(5);
+      DAPQ_REDUCE(6);
+      DAPQ_REDUCE(7);
+      DAPQ_REDUCE(8);
+      default: return fail(DAPQ_ERR_INVALID_ARG, "internal: %d planes", pl.k_splits);
+    }
+#undef DAPQ_REDUCE
     DAPQ_HIP_LAUNCH_CHECK("qproj_reduce_rope_kernel");
     return DAPQ_OK;
   }
-  if (pl.k_splits > 1) {
+  if (split) {
     const int64_t work = (int64_t)s.n_layers * s.rows * (p.n_features / 4);
     hipLaunchKernelGGL(qproj_reduce_kernel, dim3((unsigned)((work + 255) / 256)), dim3(256), 0, st, p,
                        pl.sweeps * 32 * pl.mb, pl.tiles_f * 32 * pl.ft);
@@ -502,7 +574,7 @@ extern "C" DAPQ_API int dapq_pseudo_queries(const dapq_qproj* desc, const void* 
     }
     for (int l = 0; l < s.n_layers; ++l) {
       uint16_t* ql = p.q + (int64_t)l * s.q_stride_layer;
-      const int rc2 = dapq_rope_apply(ql, ql, positions, s.rows, s.n_q_heads, s.head_dim, s.q_stride_row, s.q_stride_head,
+      rc2 = dapq_rope_apply(ql, ql, positions, s.rows, s.n_q_heads, s.head_dim, s.q_stride_row, s.q_stride_head,
                                       theta, pairing, stream);
       if (rc2 != DAPQ_OK) return rc2;
     }

@@ -236,6 +236,22 @@ def test_rotated_queries_of_split_calls(H, layers, Hq, d, rows, hidden, splits, 
         assert np.array_equal(turned.transpose(1, 0, 2), got[l])
 
 
+# hidden axes dealt to one and to four waves of a workgroup, in equal shares and with shares that are short or empty
+@pytest.mark.parametrize("hidden", [1024, 1088, 1344, 2240, 4096, 5120, 6208])
+@pytest.mark.parametrize("layers,Hq,d,rows", [(1, 8, 128, 64), (3, 2, 72, 30), (9, 16, 128, 33), (1, 5, 64, 130)])
+def test_shares_of_the_hidden_axis(H, layers, Hq, d, rows, hidden):
+    """The projection is the oracle's (check_projection), its rotation is dapq_rope_apply's, bit for bit."""
+    announce(f"pseudo queries: shares of {hidden}, {layers} layers, {Hq} heads of {d}, {rows} rows")
+    r = np.random.default_rng(hidden + rows)
+    tok, pos = r.integers(0, 40, rows).tolist(), r.integers(0, 140000, rows).tolist()
+    pre, x_bits, w_bits = run_case(H, 81, layers, 40, hidden, Hq, d, tok)
+    got, _, _ = run_case(H, 81, layers, 40, hidden, Hq, d, tok, positions=pos)
+    check_projection(pre, x_bits, w_bits, tok, Hq, hidden)
+    for l in range(layers):
+        turned = H.rope_gpu(np.ascontiguousarray(pre[l].transpose(1, 0, 2)), pos, 500000.0)
+        assert np.array_equal(turned.transpose(1, 0, 2), got[l])
+
+
 def test_queries_feed_the_score_path(H):
     """token indices -> queries -> scores: the chain of Sec. 4.1 and 4.2 on the device against the same chain in the
     oracle.  The device's queries may differ from the oracle's by one bf16 step where the projection sat on a
