@@ -155,14 +155,16 @@ static int64_t walk_cost(int row_blocks) {
 // The constants lose least over 732 dense shapes (1 to 32 layers, 1 to 16 prompts of 130 to 131072 keys, 16 to 1024 rows), each timed in
 // some 20 chunk lengths: against the best power of two 0.906 of the time in the geometric mean, none above 1.09 (with a start-up of
 // 160 keys for both forms, and one to four chunks only where they fill the rounds: 0.940 and 1.85; the best of the lengths: 0.896).
+// The start-ups were 10000 and 15000 then; since the queries come through the ring 7000 and 11000 are the better ones (70 dense shapes of 1
+// to 32 layers, 0.997 of the time in the geometric mean, 0.94 to 1.03).
 static int64_t dense_cost(const ScorePlan& p, int64_t streams, int64_t batch, int64_t L, int64_t c, int64_t wave_slots) {
   const int64_t n = (L + c - 1) / c, walk = (L < c ? L : c) * walk_cost(p.row_blocks);
   if (p.n_groups == 1 && n <= 4) {
     const int64_t workgroups = wave_slots / 4 * (n <= 1 ? 4 : 4 / n);
-    return (streams + workgroups - 1) / workgroups * (walk + 10000);
+    return (streams + workgroups - 1) / workgroups * (walk + 7000);
   }
   const bool pairs = p.row_blocks <= 4 && batch * n % 4 == 2;
-  return (streams * n + wave_slots - 1) / wave_slots * (walk + 15000) + 7500 + 120 * n + (pairs ? 6000 : 0);
+  return (streams * n + wave_slots - 1) / wave_slots * (walk + 11000) + 7500 + 120 * n + (pairs ? 6000 : 0);
 }
 
 struct DenseChunk {

@@ -677,7 +677,7 @@ __device__ __forceinline__ void pin_q_in_agprs(bf16x8 (&qf)[NRB][8]) {
 template <int NRB>
 __device__ __forceinline__ void wave_load_frags(bf16x8 (&kf)[8], const u32x4* slot, int n, int h) {
 #pragma unroll
-  for (int s = 0; s < 8; ++s) kf[s] = __builtin_bit_cast(bf16x8, slot[lds_chunk_index(n, 2 * s + h)]);
+  for (int s = 0; s < 8; ++s) kf[s] = lds_read16((unsigned)(uintptr_t)(lds_vec_ptr)slot + (unsigned)lds_chunk_index(n, 2 * s + h) * 16u, 0);
 }
 
 // The keys a wave goes through, in the order in which they enter its ring: the sub-blocks of one chunk of a dense batch, or
@@ -721,6 +721,61 @@ __device__ __forceinline__ void fill_ring(u32x4* ring, Stream& keys, const unsig
   for (int i = 0; i < NST; ++i) keys.fetch(ring + i * kSubVec, voff, (Stream::kReversed ? first_sub - i : first_sub + i) * 32);
 }
 
+// One row block of the queries into a ring slot, laid out like a sub-block of keys: row `row0` of the head and the 31 after it (rows past
+// the last one repeat it; their results are dropped).
+__device__ __forceinline__ void queries_dma(u32x4* slot, const ScoreParams& p, const uint16_t* qbase, int row0) {
+  const int lane = fresh_lane();
+  if ((p.n_pseudo & 31) == 0 && row0 + 32 <= p.rows && p.q_stride_row < ((int64_t)1 << 26)) {  // all of one query head
+    const int head = uniform_i32(quotient(row0, p.inv_n_pseudo)), at = row0 - head * p.n_pseudo;
+    unsigned voff[4];
+    sub_dma_lane_offsets(voff, p.q_stride_row, lane);
+    sub_dma(slot, uniform_ptr(qbase + (int64_t)head * p.q_stride_head + (int64_t)at * p.q_stride_row), p.q_stride_row, 0, 32, true, voff);
+    return;
+  }
+  const int r = lane >> 4;
+  const unsigned piece = (unsigned)(lane & 15) ^ (unsigned)r;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int row = row0 + 4 * i + r, rc = row < p.rows ? row : p.rows - 1;
+    const int head = quotient(rc, p.inv_n_pseudo), at = rc - head * p.n_pseudo;
+    const uint16_t* src = qbase + (int64_t)head * p.q_stride_head + (int64_t)at * p.q_stride_row + (piece ^ (4u * (i & 3))) * 8u;
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                     (__attribute__((address_space(3))) void*)(slot + i * 64), 16, 0, 0);
+  }
+}
+// The start of a wave of a dense launch: its queries come through the ring in front of its keys.  On exit the first sub-block lies, or
+// will, in ring slot `slot`, and the NST - 1 after it are under way.  Loaded as fragments, 32 bytes of each of 32 rows at a time, the queries
+// of the four waves of a compute unit kept its address unit busy for some 7 us at the start of every chunk.  Both passes with the
+// rotation, us: 8 layers, 256 rows, 4096 keys 68.2 -> 58.8; 32 layers of 4 KV heads, 256 rows, 1104 keys 50.0 -> 44.4; one layer, 256
+// rows, 2 prompts of 24498 keys, extended 87.4 -> 81.4; 64 prompts of 512 keys 1602 -> 1579; C2's one chunk to a wave 1.000.  (The sequences of a
+// segment, whose ring is running: no faster so, 757 -> 764 for 16 prompts of 200..2500 keys, 128 rows.)
+template <int NRB, int NST, class Stream>
+__device__ __forceinline__ void start_with_queries(const ScoreParams& p, u32x4* ring, int& slot, Stream& keys, bf16x8 (&qf)[NRB][8],
+                                                   const uint16_t* qbase, int gbase, const unsigned (&voff)[4], int first_sub, int n,
+                                                   int h) {
+  if constexpr (NRB == 2) {  // (few queries: 16 rows, 8 prompts of 9783 keys 55.1 us, through the ring 56.8; 64 rows, 8 of 5000 as fast)
+    fill_ring<NST>(ring, keys, voff, first_sub);
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb) frag_from_q(qf[rb], p, qbase, gbase + rb * 32 + n, h);
+    return;
+  }
+  auto item = [&](int i) {  // number i of what goes through the ring
+    if (i < NRB) queries_dma(ring + i % NST * kSubVec, p, qbase, gbase + i * 32);
+    else keys.fetch(ring + i % NST * kSubVec, voff, (Stream::kReversed ? first_sub - (i - NRB) : first_sub + (i - NRB)) * 32);
+  };
+#pragma unroll
+  for (int i = 0; i < NST; ++i) item(i);
+#pragma unroll
+  for (int rb = 0; rb < NRB; ++rb) {
+    wait_ring_full<NST>();
+    wave_load_frags<NRB>(qf[rb], ring + rb % NST * kSubVec, n, h);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // they are out of their slot
+    item(rb + NST);
+  }
+  if (NRB > 4) pin_q_in_agprs<NRB>(qf);
+  slot = NRB % NST;
+}
+
 // Pass 1 of `count` sub-blocks of one sequence (or chunk), from number first_sub on, against row group `group` of `head` =
 // layer * n_kv_heads + KV head.  kbase: its first key, nkeys: its keys; `start`: the first of this wave.  kf, slot and keys: as
 // in wave_walk.  The (reference, sum) pairs go to outp.
@@ -730,15 +785,20 @@ __device__ __forceinline__ void pass1_piece(const ScoreParams& p, u32x4* ring, i
                                             int count, int nkeys, int gbase, const unsigned (&voff)[4], bool start,
                                             float2* outp) {
   const int lane = fresh_lane(), n = lane & 31, h = lane >> 5;
+  if constexpr (Stream::kSegment) {
 #pragma unroll
-  for (int rb = 0; rb < NRB; ++rb) frag_from_q(qf[rb], p, qbase, gbase + rb * 32 + n, h);
-  if (NRB > 4) pin_q_in_agprs<NRB>(qf);
+    for (int rb = 0; rb < NRB; ++rb) frag_from_q(qf[rb], p, qbase, gbase + rb * 32 + n, h);
+    if (NRB > 4) pin_q_in_agprs<NRB>(qf);
+  } else {
+    start_with_queries<NRB, NST>(p, ring, slot, keys, qf, qbase, gbase, voff, first_sub, n, h);
+  }
   if (start) {
     wait_ring_full<NST>();
     wave_load_frags<NRB>(kf, ring + slot * kSubVec, n, h);
   }
   // the fragments in kf have been used: their slot takes the sub-block NST ahead, and the next one's fragments follow
   auto advance = [&](int sub) {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (they are out of their slot)
     keys.fetch(ring + slot * kSubVec, voff, (sub + NST) * 32);
     slot = slot + 1 == NST ? 0 : slot + 1;
     wait_ring_full<NST>();
@@ -816,7 +876,6 @@ __device__ __forceinline__ void pass1_chunk(const ScoreParams& p, u32x4* ring, c
                                       (int64_t)kv * p.k_stride_head + w.tok0 * p.k_stride_token);
   const int gbase = group * (NRB * 32);  // first row of this wave's row group
   KeyStream<false, false, UNIT> keys = {p, nullptr, kbase, w.nkeys, 0, 0, 0};
-  fill_ring<NST>(ring, keys, voff, 0);
   bf16x8 kf[8];
   int slot = 0;
   float2* outp = FUSED ? reinterpret_cast<float2*>(ring) : p.parts + ((int64_t)head * p.max_chunks + chunk_id) * p.rows_pad + gbase;
@@ -900,9 +959,13 @@ __device__ __forceinline__ void pass2_piece(const ScoreParams& p, u32x4* ring, i
                                             const unsigned (&voff)[4], bool start, float* out) {
   const int lane = fresh_lane(), n = lane & 31, h = lane >> 5;
   if constexpr (!LOADED) {
+    if constexpr (Stream::kSegment) {
 #pragma unroll
-    for (int rb = 0; rb < NRB; ++rb) frag_from_q(qf[rb], p, qbase, gbase + rb * 32 + n, h);
-    if (NRB > 4) pin_q_in_agprs<NRB>(qf);
+      for (int rb = 0; rb < NRB; ++rb) frag_from_q(qf[rb], p, qbase, gbase + rb * 32 + n, h);
+      if (NRB > 4) pin_q_in_agprs<NRB>(qf);
+    } else {
+      start_with_queries<NRB, NST>(p, ring, slot, keys, qf, qbase, gbase, voff, first_sub, n, h);
+    }
     // -lse2 of the rows this lane's accumulator registers hold; -inf for padding rows, which then add 0
     if ((reinterpret_cast<uintptr_t>(lse) & 15) == 0 && (p.rows & 3) == 0) {
       // the four rows of an accumulator quad are consecutive: one 16-byte load each
@@ -959,7 +1022,7 @@ __device__ __forceinline__ void pass2_chunk(const ScoreParams& p, u32x4* ring, c
   float* out = const_cast<float*>(uniform_ptr(wave_plane(p, head, group) + w.tok0));
   const int nsubs = (w.nkeys + 31) / 32;
   KeyStream<true, false> keys = {p, nullptr, kbase, w.nkeys, 0, 0, 0};
-  fill_ring<NST>(ring, keys, voff, nsubs - 1);
+  if (FUSED) fill_ring<NST>(ring, keys, voff, nsubs - 1);
   bf16x8 kf[8];
   int slot = 0;
   pass2_piece<NRB, NST, FUSED>(p, ring, slot, keys, kf, qf, off2, wave_q_base(p, layer, kv, w.seq), wave_lse(p, layer, kv, w.seq),

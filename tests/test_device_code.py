@@ -120,9 +120,13 @@ def test_four_workgroups_of_a_large_tile_call_fit_a_compute_unit(units):
 
 
 def transfers_before_reads_are_done(lines):
-    """Transfers from memory into LDS that are issued while reads of LDS may still be queued (in the order of the text)."""
-    queued, found = 0, []
+    """Transfers from memory into LDS that are issued while reads of LDS may still be queued, in the order of the text; a block that
+    the text before it does not run into is taken to begin with none."""
+    queued, found, left = 0, [], False
     for line in lines:
+        if left and line.endswith(":"):
+            queued = 0
+        left = line.startswith(("s_branch", "s_endpgm", "s_setpc"))
         if line.startswith("ds_read"):
             queued += 1
         wait = re.search(r"lgkmcnt\((\d+)\)", line)
