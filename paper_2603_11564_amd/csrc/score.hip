@@ -1146,60 +1146,71 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_fused_kernel(Sco
   pass2_chunk<NRB, NST, true>(p, ring, work, 0, head, qf, off2, lane);
 }
 
-// The causal block of the pseudo tokens' own keys (Sec. 4.1: they are prefilled in-sequence): one wave
-// per (sequence, row group, layer x KV head) scores its Q rows against the n_pseudo pseudo keys, row
-// i = row % n_pseudo seeing keys 0..i, and folds the result into lse2 in place.  Every row sees key 0,
-// so its running maximum is finite from the first sub-block on.
+// The causal block of the pseudo tokens' own keys (Sec. 4.1: they are prefilled in-sequence): a wave scores one block of 32 query rows
+// against the n_pseudo pseudo keys, row i = row % n_pseudo seeing keys 0..i, and folds the result into lse2 in place.  Every row sees
+// key 0, so its running maximum is finite from the first sub-block on.  The four waves of a workgroup have row blocks of the same (sequence,
+// layer, KV head) and share its keys; both come into LDS in whole rows, and up to sixteen waves of a compute unit hide each
+// other's trips to memory.  (One wave for up to eight row blocks, fragments
+// straight from memory: 4096 sequences x heads of 128 rows 40 us, now 32; one layer, 2 prompts of 24498 keys, 256 rows, the three calls
+// with the rotation 81 us, now 75.)
 struct PseudoParams {
   const uint16_t* kp;
   int64_t stride_layer, stride_seq, stride_head, stride_row;
 };
 
-template <int NRB>
-__global__ __launch_bounds__(64, 1) void score_wave_pseudo_kernel(ScoreParams p, PseudoParams pp) {
-  extern __shared__ u32x4 ring[];
+constexpr int kPseudoWaves = 4, kPseudoSubs = 4;  // most row blocks of a workgroup, sub-blocks of keys that lie in LDS at a time
+__global__ __launch_bounds__(64 * kPseudoWaves, 4) void score_pseudo_kernel(ScoreParams p, PseudoParams pp) {
+  extern __shared__ u32x4 pseudo_area[];  // the queries' row blocks, then the keys
   const int seq = blockIdx.x;
   const int layer = uniform_i32(quotient((int)blockIdx.z, p.inv_kv_heads)), kv = (int)blockIdx.z - layer * p.n_kv_heads;
-  const int lane = threadIdx.x, n = lane & 31, h = lane >> 5;
+  const int wave = uniform_i32((int)(threadIdx.x >> 6)), waves = (int)(blockDim.x >> 6);
+  const int lane = threadIdx.x & 63, n = lane & 31, h = lane >> 5;
   const uint16_t* qbase = p.q + (int64_t)layer * p.q_stride_layer + (int64_t)seq * p.q_stride_seq +
                           (int64_t)kv * p.group * p.q_stride_head;
   const uint16_t* kbase = uniform_ptr(pp.kp + (int64_t)layer * pp.stride_layer + (int64_t)seq * pp.stride_seq +
                                       (int64_t)kv * pp.stride_head);
   float* lse = p.lse2 + (((int64_t)layer * p.batch + seq) * p.n_q_heads + (int64_t)kv * p.group) * p.n_pseudo;
-  const int gbase = blockIdx.y * (NRB * 32);
-  unsigned voff[4];
-  sub_dma_lane_offsets(voff, pp.stride_row, lane);
-  bf16x8 qf[NRB][8];
-  int last_key[NRB];
-  float ref[NRB], z[NRB];
-#pragma unroll
-  for (int rb = 0; rb < NRB; ++rb) {
-    frag_from_q(qf[rb], p, qbase, gbase + rb * 32 + n, h);
-    const int row = gbase + rb * 32 + n;
-    const int rc = row < p.rows ? row : p.rows - 1;
-    last_key[rb] = rc - quotient(rc, p.inv_n_pseudo) * p.n_pseudo;
-    ref[rb] = -INFINITY;
-    z[rb] = 0.0f;
-  }
-  bf16x8 kf[8];
+  const int row0 = ((int)blockIdx.y * waves + wave) * 32, row = row0 + n, rc = row < p.rows ? row : p.rows - 1;
+  const bool mine = row0 < p.rows;  // (a wave without rows brings in keys)
+  u32x4 *queries = pseudo_area + wave * kSubVec, *keys = pseudo_area + waves * kSubVec;
+  if (mine) queries_dma(queries, p, qbase, row0);
+  const int last_key[1] = {rc - quotient(rc, p.inv_n_pseudo) * p.n_pseudo};
+  const float old = lse[rc];
+  float ref[1] = {-INFINITY}, z[1] = {0.0f};
+  bf16x8 qf[1][8];
+  const unsigned r = (unsigned)lane >> 4, piece = ((unsigned)lane & 15u) ^ r;
+  const int64_t stride_b = pp.stride_row * 2;
   const int nsubs = (p.n_pseudo + 31) / 32;
-  for (int sub = 0; sub < nsubs; ++sub) {
-    sub_dma(ring, kbase, pp.stride_row, sub * 32, p.n_pseudo, true, voff);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    wave_load_frags<NRB>(kf, ring, n, h);
-    wave_sub_simple<NRB, true, false, true>(kf, qf, p.c, ref, z, sub * 32, p.n_pseudo, h, last_key);
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the fragments are out of the slot before it is refilled
-  }
-#pragma unroll
-  for (int rb = 0; rb < NRB; ++rb) {
-    const float zz = z[rb] + xhalf(z[rb]);
-    const int row = gbase + rb * 32 + n;
-    if (h == 0 && row < p.rows) {
-      const float block = ref[rb] + log2f(zz);  // log2 of the block's sum; zz >= 1
-      const float old = lse[row];
-      const float m = fmaxf(old, block);
-      lse[row] = m + log2f(__builtin_amdgcn_exp2f(old - m) + __builtin_amdgcn_exp2f(block - m));
+  for (int sub0 = 0; sub0 < nsubs; sub0 += kPseudoSubs) {
+    const int subs = nsubs - sub0 < kPseudoSubs ? nsubs - sub0 : kPseudoSubs;
+    if (sub0 != 0) __syncthreads();  // everybody is done with the keys before these
+    for (int x = wave; x < subs * 8; x += waves) {  // four rows each; those past the last one arrive as zeros
+      const int key = sub0 * 32 + 4 * x;
+      const bool live = key < p.n_pseudo;
+      const int64_t span = (int64_t)(p.n_pseudo - key - 1) * stride_b + kHeadDim * 2;
+      const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+          const_cast<char*>(reinterpret_cast<const char*>(kbase) + (live ? (int64_t)key * stride_b : (int64_t)0)), 0,
+          (int)(!live ? 0u : (span > (int64_t)0xFFFFFFFFll ? 0xFFFFFFFFu : (unsigned)span)), 0x00020000);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)(keys + x * 64), 16,
+                                               (int)(r * (unsigned)stride_b + (piece ^ (4u * ((unsigned)x & 3u))) * 16u), 0, 0, 0);
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (!mine) continue;
+    if (sub0 == 0) wave_load_frags<1>(qf[0], queries, n, h);
+    for (int sub = 0; sub < subs; ++sub) {
+      const int key0 = (sub0 + sub) * 32;
+      if (!__any(last_key[0] >= key0)) continue;
+      bf16x8 kf[8];
+      wave_load_frags<1>(kf, keys + sub * kSubVec, n, h);
+      wave_sub_simple<1, true, false, true>(kf, qf, p.c, ref, z, key0, p.n_pseudo, h, last_key);
+    }
+  }
+  const float zz = z[0] + xhalf(z[0]);
+  if (mine && h == 0 && row < p.rows) {
+    const float block = ref[0] + log2f(zz);  // log2 of the block's sum; zz >= 1
+    const float m = fmaxf(old, block);
+    lse[row] = m + log2f(__builtin_amdgcn_exp2f(old - m) + __builtin_amdgcn_exp2f(block - m));
   }
 }
 
@@ -2041,13 +2052,12 @@ extern "C" DAPQ_API int dapq_score_stats_extend(const dapq_shape* shape, const v
   pp.kp = static_cast<const uint16_t*>(k_pseudo);
   pp.stride_layer = kp_stride_layer; pp.stride_seq = kp_stride_seq;
   pp.stride_head = kp_stride_head; pp.stride_row = kp_stride_row;
-  const RowSplit split = wave_row_split(plan.rows);
-  const dim3 grid((unsigned)shape->batch, (unsigned)split.n_groups, (unsigned)(shape->n_layers * shape->n_kv_heads));
-  hipStream_t st = static_cast<hipStream_t>(stream);
-#define DAPQ_LAUNCH_PSEUDO(NRBV) hipLaunchKernelGGL(score_wave_pseudo_kernel<NRBV>, grid, dim3(64), kSubBytes, st, p, pp)
-  DAPQ_BY_ROW_BLOCKS(split.row_blocks, DAPQ_LAUNCH_PSEUDO);
-#undef DAPQ_LAUNCH_PSEUDO
-  DAPQ_HIP_LAUNCH_CHECK("score_wave_pseudo_kernel");
+  const int row_blocks = (plan.rows + 31) / 32, nsubs = (shape->n_pseudo + 31) / 32;
+  const int waves = row_blocks < kPseudoWaves ? row_blocks : kPseudoWaves;
+  const dim3 grid((unsigned)shape->batch, (unsigned)((row_blocks + waves - 1) / waves), (unsigned)(shape->n_layers * shape->n_kv_heads));
+  hipLaunchKernelGGL(score_pseudo_kernel, grid, dim3(64u * (unsigned)waves), (waves + (nsubs < kPseudoSubs ? nsubs : kPseudoSubs)) * kSubBytes,
+                     static_cast<hipStream_t>(stream), p, pp);
+  DAPQ_HIP_LAUNCH_CHECK("score_pseudo_kernel");
   return DAPQ_OK;
 }
 
