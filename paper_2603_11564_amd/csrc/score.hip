@@ -753,8 +753,8 @@ template <int NRB, int NST, class Stream>
 __device__ __forceinline__ void start_with_queries(const ScoreParams& p, u32x4* ring, int& slot, Stream& keys, bf16x8 (&qf)[NRB][8],
                                                    const uint16_t* qbase, int gbase, const unsigned (&voff)[4], int first_sub, int n,
                                                    int h) {
-  if constexpr (NRB == 2) {  // (few queries: 16 rows, 8 prompts of 9783 keys 55.1 us, through the ring 56.8; 64 rows, 8 of 5000 as fast)
-    fill_ring<NST>(ring, keys, voff, first_sub);
+  if constexpr (NRB == 2) {  // (few queries: 16 rows, 8 prompts of 9783 keys 55.1 us, through the ring 56.8; 64 rows, 8 of 5000 as fast;
+                            // the caller has filled the ring)
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) frag_from_q(qf[rb], p, qbase, gbase + rb * 32 + n, h);
     return;
@@ -876,6 +876,7 @@ __device__ __forceinline__ void pass1_chunk(const ScoreParams& p, u32x4* ring, c
                                       (int64_t)kv * p.k_stride_head + w.tok0 * p.k_stride_token);
   const int gbase = group * (NRB * 32);  // first row of this wave's row group
   KeyStream<false, false, UNIT> keys = {p, nullptr, kbase, w.nkeys, 0, 0, 0};
+  if (NRB == 2) fill_ring<NST>(ring, keys, voff, 0);  // (see start_with_queries)
   bf16x8 kf[8];
   int slot = 0;
   float2* outp = FUSED ? reinterpret_cast<float2*>(ring) : p.parts + ((int64_t)head * p.max_chunks + chunk_id) * p.rows_pad + gbase;
@@ -1022,7 +1023,7 @@ __device__ __forceinline__ void pass2_chunk(const ScoreParams& p, u32x4* ring, c
   float* out = const_cast<float*>(uniform_ptr(wave_plane(p, head, group) + w.tok0));
   const int nsubs = (w.nkeys + 31) / 32;
   KeyStream<true, false> keys = {p, nullptr, kbase, w.nkeys, 0, 0, 0};
-  if (FUSED) fill_ring<NST>(ring, keys, voff, nsubs - 1);
+  if (FUSED || NRB == 2) fill_ring<NST>(ring, keys, voff, nsubs - 1);
   bf16x8 kf[8];
   int slot = 0;
   pass2_piece<NRB, NST, FUSED>(p, ring, slot, keys, kf, qf, off2, wave_q_base(p, layer, kv, w.seq), wave_lse(p, layer, kv, w.seq),
