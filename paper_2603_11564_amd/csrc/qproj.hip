@@ -98,8 +98,15 @@ __global__ __launch_bounds__(64 * WAVES) void qproj_wave_kernel(QprojParams p) {
   constexpr int XQ = XT / FT;      // of them riding with one unit
   constexpr int OPS = 4 + XQ;      // transfers per unit
   static_assert(XT % FT == 0 && (kRing % FT == 0) && (kRing - 1) * OPS <= 63, "unit bookkeeping");
-  extern __shared__ u32x4 rings[];
   const int wave = WAVES > 1 ? qp_uniform((int)(threadIdx.x >> 6)) : 0;
+  u32x4* rings;
+  if constexpr (WAVES > 1) {
+    extern __shared__ u32x4 all_rings[];
+    rings = all_rings;
+  } else {
+    __shared__ u32x4 own_ring[QprojLds<FT, MB>::bytes / 16];
+    rings = own_ring;
+  }
   u32x4* const lds = rings + wave * (QprojLds<FT, MB>::bytes / 16);
   u32x4* const wring = lds;
   u32x4* const xbuf = lds + kRing * kTileVec;
@@ -219,15 +226,15 @@ __global__ __launch_bounds__(64 * WAVES) void qproj_wave_kernel(QprojParams p) {
     bf16x8 wf[4];
 #pragma unroll
     for (int s = 0; s < 4; ++s) wf[s] = __builtin_bit_cast(bf16x8, slot[frag_idx[s]]);
-    // the slot just read takes the tile of the unit kRing ahead, once its fragments are in registers: a transfer past the end fetches
-    // nothing and its zeros arrive at once, ahead of reads that are still queued
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    issue(kb + kRing / FT, tile_c);
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
       for (int rb = 0; rb < MB; ++rb)
         acc[T][rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[s], xf[rb][s], acc[T][rb], 0, 0, 0);
+    // the slot just read takes the tile of the unit kRing ahead, once its fragments are in registers: a transfer past the end fetches
+    // nothing and its zeros arrive at once, ahead of reads that are still queued
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    issue(kb + kRing / FT, tile_c);
   };
 
   for (int kb = kb0; kb < n_kb; ++kb) {
@@ -242,13 +249,24 @@ __global__ __launch_bounds__(64 * WAVES) void qproj_wave_kernel(QprojParams p) {
 
   // ---- epilogue: accumulator register v of lane (n, h) is feature 8 (v / 4) + 4 h + v % 4 of the tile, row n
   if constexpr (FT == 2) if (WAVES > 1 || p.partial != nullptr) {  // (calls of four-tile waves fill the chip: make_qproj_plan)
-    // one of several workgroups of this tile: the fp32 sums go to this split's plane, padding included; through LDS (the rings are
-    // drained) so that a store covers whole cache lines instead of 32 bytes of 32 rows (one layer 4096 wide, 64 rows, 8 splits: 8.4 MB
-    // of sums, kernel 10.3 -> 9.2 us)
+    // one of several workgroups of this tile: the fp32 sums go to this split's plane, padding included.  Those of four waves meet in LDS
+    // (the rings are drained) and leave it in whole cache lines; single waves store 32 bytes of 32 rows at a time, which is the
+    // faster way while others of their compute unit still read (2 layers 5120 wide, 128 rows 38.3 us, through LDS 40.9).
     const int64_t rows_pad = (int64_t)p.sweeps * (32 * MB), feat_pad = (int64_t)p.tiles_f * (32 * FT);
     float* plane = p.partial + ((int64_t)split * p.n_layers + layer) * rows_pad * feat_pad;
     constexpr int kRow = 32 * FT + 4, kQuads = 8 * FT;  // words and quads of a row of the tile
     static_assert(32 * MB * kRow * 4 <= QprojLds<FT, MB>::bytes, "a wave's sums fit where its ring was");
+    if constexpr (WAVES == 1) {
+#pragma unroll
+      for (int rb = 0; rb < MB; ++rb)
+#pragma unroll
+        for (int t = 0; t < FT; ++t)
+#pragma unroll
+          for (int g = 0; g < 4; ++g)
+            *reinterpret_cast<float4*>(plane + (int64_t)(m0 + 32 * rb + n) * feat_pad + f0 + 32 * t + 8 * g + 4 * h) =
+                make_float4(acc[t][rb][4 * g], acc[t][rb][4 * g + 1], acc[t][rb][4 * g + 2], acc[t][rb][4 * g + 3]);
+      return;
+    }
     float* sums = reinterpret_cast<float*>(lds);
 #pragma unroll
     for (int rb = 0; rb < MB; ++rb)
@@ -258,8 +276,7 @@ __global__ __launch_bounds__(64 * WAVES) void qproj_wave_kernel(QprojParams p) {
         for (int g = 0; g < 4; ++g)
           *reinterpret_cast<float4*>(sums + (32 * rb + n) * kRow + 32 * t + 8 * g + 4 * h) =
               make_float4(acc[t][rb][4 * g], acc[t][rb][4 * g + 1], acc[t][rb][4 * g + 2], acc[t][rb][4 * g + 3]);
-    if constexpr (WAVES > 1) __syncthreads();
-    else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __syncthreads();
     constexpr int kWaveWords = QprojLds<FT, MB>::bytes / 4;
 #pragma unroll
     for (int i = 0; i < 32 * MB * kQuads / (64 * WAVES); ++i) {
@@ -370,7 +387,7 @@ __global__ __launch_bounds__(256) void qproj_reduce_rope_kernel(QprojParams p, i
 
 template <int FT, int MB, int WAVES>
 int launch_qproj(const QprojParams& p, hipStream_t stream) {
-  constexpr int kBytes = WAVES * QprojLds<FT, MB>::bytes;
+  constexpr int kBytes = WAVES > 1 ? WAVES * QprojLds<FT, MB>::bytes : 0;
   if (kBytes > 64 * 1024) {
     const int rc = set_max_dynamic_lds(reinterpret_cast<const void*>(qproj_wave_kernel<FT, MB, WAVES>), kBytes);
     if (rc != DAPQ_OK) return rc;
@@ -411,7 +428,9 @@ QprojPlan make_qproj_plan(const dapq_qproj& s) {
                                         : (size_t)pl.k_splits * s.n_layers * ((size_t)pl.sweeps * 32 * pl.mb) *
                                               ((size_t)pl.tiles_f * 32 * pl.ft) * sizeof(float);
   pl.waves = 1;
-  if (pl.k_splits == 1) return pl;
+  // (Several sweeps of more than one round: bound by what the compute units take in of the rows, and a round's start-up is in the open.  2
+  // layers, single waves -> four: 5120 wide, 128 rows 37.4 -> 44.9; 4096 wide, 148 rows 28.7 -> 33.0.)
+  if (pl.k_splits == 1 || (pl.sweeps > 1 && waves > kQprojUnits)) return pl;
   // Four waves to a workgroup, which has a compute unit to itself, add up before they write: half the planes or fewer, and more of
   // the weight in flight.  As many workgroups along the hidden axis as cost least, in blocks of four waves: a workgroup's own and a start-up of
   // two; no more planes than the workspace holds, and not more than eight, which cost the kernel that adds them.  Single waves share a
