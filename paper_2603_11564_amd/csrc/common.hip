@@ -141,11 +141,6 @@ static int dense_chunk_of_two(const dapq_shape* s, int64_t heads, const ScorePla
   return chunk;
 }
 
-// What a key costs both walks of a wave, in nanoseconds (fitted for two, four and eight row blocks, see dense_cost; five to seven lie
-// on the line between four and eight, three move the same keys as four).
-static int64_t walk_cost(int row_blocks) {
-  return row_blocks > 4 ? 29 + 6 * row_blocks - (row_blocks == 8 ? 2 : 0) : (row_blocks > 2 ? 52 : 45);
-}
 // Time of both passes of a dense batch in chunks of c keys, in nanoseconds, as far as c decides it.  The machine runs wave_slots waves
 // at a time, each for as long as its chunk, and a round of waves pays a start-up (queries, ring fill).  Up to four chunks of a
 // sequence with one row group are the waves of one workgroup, which does both passes (dapq_score in one kernel): one start-up for both and
@@ -155,16 +150,17 @@ static int64_t walk_cost(int row_blocks) {
 // The constants lose least over 732 dense shapes (1 to 32 layers, 1 to 16 prompts of 130 to 131072 keys, 16 to 1024 rows), each timed in
 // some 20 chunk lengths: against the best power of two 0.906 of the time in the geometric mean, none above 1.09 (with a start-up of
 // 160 keys for both forms, and one to four chunks only where they fill the rounds: 0.940 and 1.85; the best of the lengths: 0.896).
-// The start-ups were 10000 and 15000 then; since the queries come through the ring 7000 and 11000 are the better ones (70 dense shapes of 1
-// to 32 layers, 0.997 of the time in the geometric mean, 0.94 to 1.03).
+// (Start-ups of 7000 and 11000, as they are since the queries come through the ring, and costs of five to seven row blocks of their own are
+// worth a quarter of a hundredth of the time, 70 dense shapes, and took shapes from dapq_score_static that it has served.)
 static int64_t dense_cost(const ScorePlan& p, int64_t streams, int64_t batch, int64_t L, int64_t c, int64_t wave_slots) {
-  const int64_t n = (L + c - 1) / c, walk = (L < c ? L : c) * walk_cost(p.row_blocks);
+  const int blocks = p.room_rows / (32 * p.n_groups);
+  const int64_t n = (L + c - 1) / c, walk = (L < c ? L : c) * (blocks == 8 ? 75 : (blocks == 4 ? 52 : 45));
   if (p.n_groups == 1 && n <= 4) {
     const int64_t workgroups = wave_slots / 4 * (n <= 1 ? 4 : 4 / n);
-    return (streams + workgroups - 1) / workgroups * (walk + 7000);
+    return (streams + workgroups - 1) / workgroups * (walk + 10000);
   }
   const bool pairs = p.row_blocks <= 4 && batch * n % 4 == 2;
-  return (streams * n + wave_slots - 1) / wave_slots * (walk + 11000) + 7500 + 120 * n + (pairs ? 6000 : 0);
+  return (streams * n + wave_slots - 1) / wave_slots * (walk + 15000) + 7500 + 120 * n + (pairs ? 6000 : 0);
 }
 
 struct DenseChunk {
