@@ -32,6 +32,7 @@
 
 #include "dapq_internal.h"
 #include "kernel_args.h"
+#include "qproj_plan.h"
 #include "rope_math.h"
 
 namespace dapq {
@@ -61,7 +62,6 @@ struct QprojParams {
 };
 
 constexpr int kRing = 4;          // weight slots; a unit's transfers are issued four units ahead
-constexpr int kBlockK = 64;       // hidden channels per block: 128-byte rows in LDS
 constexpr int kTileBytes = 32 * kBlockK * 2;
 constexpr int kTileVec = kTileBytes / 16;
 
@@ -398,66 +398,6 @@ int launch_qproj(const QprojParams& p, hipStream_t stream) {
   return DAPQ_OK;
 }
 
-constexpr int64_t kQprojUnits = 256;  // compute units
-
-// How a call is cut into waves; a pure function of the description so that the workspace query and the
-// launcher agree.
-struct QprojPlan {
-  int ft, mb, waves, tiles_f, sweeps, k_splits, kb_per_split;  // waves of a workgroup, workgroups along the hidden axis, blocks to a wave
-  size_t workspace_bytes;
-};
-
-QprojPlan make_qproj_plan(const dapq_qproj& s) {
-  QprojPlan pl;
-  const int64_t features = (int64_t)s.n_q_heads * s.head_dim;
-  // two row blocks per wave unless 32 rows are all there is
-  pl.mb = s.rows > 32 ? 2 : 1;
-  pl.sweeps = (int)(((int64_t)s.rows + 32 * pl.mb - 1) / (32 * pl.mb));
-  // four feature tiles per wave while that still fills the chip (1024 SIMDs), two otherwise
-  const int64_t waves4 = (features + 127) / 128 * pl.sweeps * s.n_layers;
-  pl.ft = waves4 >= 768 ? 4 : 2;
-  pl.tiles_f = (int)((features + 32 * pl.ft - 1) / (32 * pl.ft));
-  // still too few waves: several waves per tile, each with a share of the hidden blocks (at least 8 per wave,
-  // so that the ring's start-up is paid a few times at most), and one pass that adds their sums
-  const int n_kb = s.hidden / kBlockK;
-  const int64_t waves = (int64_t)pl.tiles_f * pl.sweeps * s.n_layers;
-  pl.k_splits = 1;
-  while (pl.k_splits < 16 && waves * pl.k_splits < 768 && n_kb / (pl.k_splits * 2) >= 8) pl.k_splits *= 2;
-  pl.kb_per_split = (n_kb + pl.k_splits - 1) / pl.k_splits;
-  pl.workspace_bytes = pl.k_splits == 1 ? 0
-                                        : (size_t)pl.k_splits * s.n_layers * ((size_t)pl.sweeps * 32 * pl.mb) *
-                                              ((size_t)pl.tiles_f * 32 * pl.ft) * sizeof(float);
-  pl.waves = 1;
-  // (Several sweeps of more than one round: bound by what the compute units take in of the rows, and a round's start-up is in the open.  2
-  // layers, single waves -> four: 5120 wide, 128 rows 37.4 -> 44.9; 4096 wide, 148 rows 28.7 -> 33.0.)
-  if (pl.k_splits == 1 || (pl.sweeps > 1 && waves > kQprojUnits)) return pl;
-  // Four waves to a workgroup, which has a compute unit to itself, add up before they write: half the planes or fewer, and more of
-  // the weight in flight.  As many workgroups along the hidden axis as cost least, in blocks of four waves: a workgroup's own and a start-up of
-  // two; no more planes than the workspace holds, and not more than eight, which cost the kernel that adds them.  Single waves share a
-  // compute unit four or five at a time (their rings), write a plane each and are slower by a tenth or more for the same cost; they
-  // stay where whole rounds of workgroups do not come out.  Whole call, us, single waves -> four: one layer 4096 wide, 64 rows 14.4 -> 14.0
-  // (three launches of the host); 256 rows 24.0 -> 20.9; 2 layers 22.8 -> 18.0; 8 layers 83.0 -> 66.8, of 16 rows 73.5 -> 55.7; 5120 wide, 64
-  // rows 18.5 -> 16.5; 8 layers 5120 wide, 32 rows 87.9 -> 92.8 (stays).
-  const int per_unit = pl.mb == 2 ? 4 : 5;
-  const int64_t tiles = waves, singles = tiles * pl.k_splits, units = kQprojUnits;
-  const int64_t together = per_unit > 4 && singles > 4 * units ? 5 : 4;  // (fewer than four take a block no faster)
-  int64_t best = (singles + units * per_unit - 1) / (units * per_unit) * (pl.kb_per_split * together + 8);  // (four times blocks)
-  best += best / 10;
-  const int most = pl.k_splits < 8 ? pl.k_splits : 8;
-  for (int splits = 1; splits <= most; ++splits) {
-    const int each = (n_kb + 4 * splits - 1) / (4 * splits);
-    if ((int64_t)(splits - 1) * 4 * each >= n_kb) continue;  // (a workgroup without blocks)
-    const int64_t cost = (tiles * splits + units - 1) / units * (each + 2) * 4;
-    if (cost < best) {
-      best = cost;
-      pl.waves = 4;
-      pl.k_splits = splits;
-      pl.kb_per_split = each;
-    }
-  }
-  return pl;
-}
-
 int check_qproj(const dapq_qproj* desc) {
   DAPQ_REQUIRE(desc != nullptr, DAPQ_ERR_INVALID_ARG, "desc must not be NULL");
   const dapq_qproj& s = *desc;
@@ -550,6 +490,8 @@ extern "C" DAPQ_API int dapq_pseudo_queries(const dapq_qproj* desc, const void* 
   p.partial = split ? static_cast<float*>(workspace) : nullptr;
   DAPQ_REQUIRE((int64_t)p.tiles_f * p.sweeps * p.k_splits * s.n_layers < ((int64_t)1 << 31), DAPQ_ERR_UNSUPPORTED,
                "too many tiles");
+  DAPQ_REQUIRE(!split || positions == nullptr || qproj_planes_have_a_kernel(pl.k_splits), DAPQ_ERR_UNSUPPORTED,
+               "internal: no kernel adds and rotates %d planes", pl.k_splits);
   hipStream_t st = static_cast<hipStream_t>(stream);
   int rc2;
   if (pl.waves == 4) rc2 = pl.mb == 2 ? launch_qproj<2, 2, 4>(p, st) : launch_qproj<2, 1, 4>(p, st);
@@ -561,20 +503,12 @@ extern "C" DAPQ_API int dapq_pseudo_queries(const dapq_qproj* desc, const void* 
     const dim3 grid((unsigned)(((int64_t)s.rows * (s.head_dim / 2) + 255) / 256), (unsigned)(s.n_q_heads * s.n_layers));
     const int rows_pad = pl.sweeps * 32 * pl.mb, feat_pad = pl.tiles_f * 32 * pl.ft;
     const double e = rope_exponent(theta, s.head_dim);
-#define DAPQ_REDUCE(planes) \
-  case planes: hipLaunchKernelGGL(qproj_reduce_rope_kernel<planes>, grid, dim3(256), 0, st, p, rows_pad, feat_pad, positions, e, pairing); break
     switch (pl.k_splits) {
-      DAPQ_REDUCE(1);
-      DAPQ_REDUCE(2);
-      DAPQ_REDUCE(3);
-      DAPQ_REDUCE(4);
-      DAPQ_REDUCE(5);
-      DAPQ_REDUCE(6);
-      DAPQ_REDUCE(7);
-      DAPQ_REDUCE(8);
-      default: return fail(DAPQ_ERR_INVALID_ARG, "internal: %d planes", pl.k_splits);
-    }
+#define DAPQ_REDUCE(planes) \
+  case planes: hipLaunchKernelGGL(qproj_reduce_rope_kernel<planes>, grid, dim3(256), 0, st, p, rows_pad, feat_pad, positions, e, pairing); break;
+      DAPQ_QPROJ_PLANES(DAPQ_REDUCE)
 #undef DAPQ_REDUCE
+    }
     DAPQ_HIP_LAUNCH_CHECK("qproj_reduce_rope_kernel");
     return DAPQ_OK;
   }

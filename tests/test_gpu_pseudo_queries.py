@@ -14,6 +14,7 @@ import pytest
 import torch
 
 import workloads as W
+from qproj_shapes import SPLIT_SHAPES
 from oracle import dapq_oracle as O
 
 pytestmark = pytest.mark.gpu
@@ -233,6 +234,21 @@ def test_rotated_queries_of_split_calls(H, layers, Hq, d, rows, hidden, splits, 
     check_projection(pre, x_bits, w_bits, tok, Hq, hidden)
     for l in range(layers):
         turned = H.rope_gpu(np.ascontiguousarray(pre[l].transpose(1, 0, 2)), pos, 500000.0, pairing)
+        assert np.array_equal(turned.transpose(1, 0, 2), got[l])
+
+
+@pytest.mark.parametrize("shape", SPLIT_SHAPES, ids=lambda shape: "x".join(map(str, shape)))
+def test_every_number_of_planes(H, shape):
+    """The projection is the oracle's (check_projection), its rotation is dapq_rope_apply's, bit for bit."""
+    layers, Hq, d, rows, hidden = shape
+    announce(f"pseudo queries: {SPLIT_SHAPES[shape]} waves and planes, {shape}")
+    r = np.random.default_rng(hidden + rows)
+    tok, pos = r.integers(0, 40, rows).tolist(), r.integers(0, 140000, rows).tolist()
+    pre, x_bits, w_bits = run_case(H, 82, layers, 40, hidden, Hq, d, tok)
+    got, _, _ = run_case(H, 82, layers, 40, hidden, Hq, d, tok, positions=pos)
+    check_projection(pre, x_bits, w_bits, tok, Hq, hidden)
+    for l in range(layers):
+        turned = H.rope_gpu(np.ascontiguousarray(pre[l].transpose(1, 0, 2)), pos, 500000.0)
         assert np.array_equal(turned.transpose(1, 0, 2), got[l])
 
 
