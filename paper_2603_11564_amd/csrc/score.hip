@@ -748,17 +748,12 @@ __device__ __forceinline__ void queries_dma(u32x4* slot, const ScoreParams& p, c
 // of the four waves of a compute unit kept its address unit busy for some 7 us at the start of every chunk.  Both passes with the
 // rotation, us: 8 layers, 256 rows, 4096 keys 68.2 -> 58.8; 32 layers of 4 KV heads, 256 rows, 1104 keys 50.0 -> 44.4; one layer, 256
 // rows, 2 prompts of 24498 keys, extended 87.4 -> 81.4; 64 prompts of 512 keys 1602 -> 1579; C2's one chunk to a wave 1.000.  (The sequences of a
-// segment, whose ring is running: no faster so, 757 -> 764 for 16 prompts of 200..2500 keys, 128 rows.)
+// segment, whose ring is running: no faster so, 757 -> 764 for 16 prompts of 200..2500 keys, 128 rows; nor two row blocks: 16 rows, 8
+// prompts of 9783 keys 55.1 -> 56.8, 64 rows, 8 of 5000 as fast; nor short chunks, see launch_fused.  Those load them as fragments.)
 template <int NRB, int NST, class Stream>
 __device__ __forceinline__ void start_with_queries(const ScoreParams& p, u32x4* ring, int& slot, Stream& keys, bf16x8 (&qf)[NRB][8],
                                                    const uint16_t* qbase, int gbase, const unsigned (&voff)[4], int first_sub, int n,
                                                    int h) {
-  if constexpr (NRB == 2) {  // (few queries: 16 rows, 8 prompts of 9783 keys 55.1 us, through the ring 56.8; 64 rows, 8 of 5000 as fast;
-                            // the caller has filled the ring)
-#pragma unroll
-    for (int rb = 0; rb < NRB; ++rb) frag_from_q(qf[rb], p, qbase, gbase + rb * 32 + n, h);
-    return;
-  }
   auto item = [&](int i) {  // number i of what goes through the ring
     if (i < NRB) queries_dma(ring + i % NST * kSubVec, p, qbase, gbase + i * 32);
     else keys.fetch(ring + i % NST * kSubVec, voff, (Stream::kReversed ? first_sub - (i - NRB) : first_sub + (i - NRB)) * 32);
@@ -778,14 +773,15 @@ __device__ __forceinline__ void start_with_queries(const ScoreParams& p, u32x4* 
 
 // Pass 1 of `count` sub-blocks of one sequence (or chunk), from number first_sub on, against row group `group` of `head` =
 // layer * n_kv_heads + KV head.  kbase: its first key, nkeys: its keys; `start`: the first of this wave.  kf, slot and keys: as
-// in wave_walk.  The (reference, sum) pairs go to outp.
-template <int NRB, int NST, class Stream>
+// in wave_walk.  FRAGS: the queries come as fragments, beside a ring that the caller has filled (else through it, see
+// start_with_queries).  The (reference, sum) pairs go to outp.
+template <int NRB, int NST, bool FRAGS, class Stream>
 __device__ __forceinline__ void pass1_piece(const ScoreParams& p, u32x4* ring, int& slot, Stream& keys, bf16x8 (&kf)[8],
                                             bf16x8 (&qf)[NRB][8], const uint16_t* qbase, const uint16_t* kbase, int first_sub,
                                             int count, int nkeys, int gbase, const unsigned (&voff)[4], bool start,
                                             float2* outp) {
   const int lane = fresh_lane(), n = lane & 31, h = lane >> 5;
-  if constexpr (Stream::kSegment) {
+  if constexpr (FRAGS) {
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) frag_from_q(qf[rb], p, qbase, gbase + rb * 32 + n, h);
     if (NRB > 4) pin_q_in_agprs<NRB>(qf);
@@ -865,8 +861,8 @@ __device__ __forceinline__ const uint16_t* wave_q_base(const ScoreParams& p, int
 
 // Pass 1 of one chunk of a dense batch: `group` = row group, `chunk_id` = chunk along the packed key axis.  The chunk must have
 // keys.  FUSED (score_fused_kernel): the chunk's (reference, sum) pairs go to the start of the wave's own ring, which is
-// drained by then, instead of to global memory.
-template <int NRB, int NST, bool UNIT, bool FUSED = false>
+// drained by then, instead of to global memory.  SHORT: the queries as fragments (launch_fused).
+template <int NRB, int NST, bool UNIT, bool FUSED = false, bool SHORT = false>
 __device__ __forceinline__ void pass1_chunk(const ScoreParams& p, u32x4* ring, const Work& w, int chunk_id, int group, int head,
                                             bf16x8 (&qf)[NRB][8], int lane) {
   unsigned voff[4];
@@ -876,11 +872,12 @@ __device__ __forceinline__ void pass1_chunk(const ScoreParams& p, u32x4* ring, c
                                       (int64_t)kv * p.k_stride_head + w.tok0 * p.k_stride_token);
   const int gbase = group * (NRB * 32);  // first row of this wave's row group
   KeyStream<false, false, UNIT> keys = {p, nullptr, kbase, w.nkeys, 0, 0, 0};
-  if (NRB == 2) fill_ring<NST>(ring, keys, voff, 0);  // (see start_with_queries)
+  constexpr bool kFrags = NRB == 2 || SHORT;
+  if (kFrags) fill_ring<NST>(ring, keys, voff, 0);
   bf16x8 kf[8];
   int slot = 0;
   float2* outp = FUSED ? reinterpret_cast<float2*>(ring) : p.parts + ((int64_t)head * p.max_chunks + chunk_id) * p.rows_pad + gbase;
-  pass1_piece<NRB, NST>(p, ring, slot, keys, kf, qf, wave_q_base(p, layer, kv, w.seq), kbase, 0, (w.nkeys + 31) / 32, w.nkeys,
+  pass1_piece<NRB, NST, kFrags>(p, ring, slot, keys, kf, qf, wave_q_base(p, layer, kv, w.seq), kbase, 0, (w.nkeys + 31) / 32, w.nkeys,
                         gbase, voff, true, outp);
 }
 
@@ -905,7 +902,7 @@ __device__ __forceinline__ void pass1_segment(const ScoreParams& p, u32x4* ring,
     if (r.len > 0) {
       const int nkeys = uniform_i32(r.len), rest = (nkeys - 1) / 32 + 1 - at.sub, count = at.left < rest ? at.left : rest;
       const uint16_t* kbase = uniform_ptr(keys.head + (int64_t)at.seq * p.k_stride_seq + (int64_t)r.start * p.k_stride_token);
-      pass1_piece<NRB, NST>(p, ring, slot, keys, kf, qf, wave_q_base(p, layer, kv, at.seq), kbase, at.sub, count, nkeys, gbase,
+      pass1_piece<NRB, NST, true>(p, ring, slot, keys, kf, qf, wave_q_base(p, layer, kv, at.seq), kbase, at.sub, count, nkeys, gbase,
                             voff, start,
                             p.parts + ((int64_t)head * p.max_chunks + at.seq + segment) * p.rows_pad + gbase);
       at.left -= count;
@@ -960,7 +957,7 @@ __device__ __forceinline__ void pass2_piece(const ScoreParams& p, u32x4* ring, i
                                             const unsigned (&voff)[4], bool start, float* out) {
   const int lane = fresh_lane(), n = lane & 31, h = lane >> 5;
   if constexpr (!LOADED) {
-    if constexpr (Stream::kSegment) {
+    if constexpr (Stream::kSegment || NRB == 2) {
 #pragma unroll
       for (int rb = 0; rb < NRB; ++rb) frag_from_q(qf[rb], p, qbase, gbase + rb * 32 + n, h);
       if (NRB > 4) pin_q_in_agprs<NRB>(qf);
@@ -1095,7 +1092,8 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_wave_pass2_kerne
 // the query fragments still in registers.  What this saves is everything between the passes: a kernel boundary at
 // which every wave of the chip waits for the slowest, the combine kernel, the second placement of the workgroups and
 // the second read of the queries.  lse2 is not written anywhere.
-template <int NRB, bool UNIT, int NST>
+// SHORT: see launch_fused.
+template <int NRB, bool UNIT, bool SHORT, int NST>
 __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_fused_kernel(ScoreParams p) {
   extern __shared__ u32x4 rings[];
   const int wave_id = uniform_i32((int)(threadIdx.x >> 6)), waves = (int)(blockDim.x >> 6);
@@ -1105,7 +1103,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_fused_kernel(Sco
   const int chunk = uniform_i32((int)blockIdx.x * waves + wave_id);  // blockIdx.x is the sequence
   const int head = (int)blockIdx.z;
   const Work work = locate_uniform(p, chunk);
-  pass1_chunk<NRB, NST, UNIT, true>(p, ring, work, chunk, 0, head, qf, lane);
+  pass1_chunk<NRB, NST, UNIT, true, SHORT>(p, ring, work, chunk, 0, head, qf, lane);
   __syncthreads();
   // lse2 of rows lane, lane + 64, ...: every wave merges all chunks itself
   constexpr int kRowsPerLane = (NRB * 32 + 63) / 64;  // (an odd number of row blocks: the last rows are no one's)
@@ -1880,21 +1878,30 @@ int launch_fused(const dapq_shape* s, const ScorePlan& plan, ScoreParams p, hipS
   const GroupShape gs = {fused_waves(s, plan), 1};
   p.wg_groups = 1;
   const dim3 grid((unsigned)s->batch, 1u, (unsigned)(s->n_layers * s->n_kv_heads));
+  // One chunk of a few sub-blocks: all of its keys fit the ring at once, and they and the queries, loaded as fragments, arrive in one trip to
+  // memory; behind queries that go through the ring they wait for two or three.  Up to some 8 rounds of waves that is the shorter start,
+  // inputs in the caches / out of memory, us, through the ring -> fragments: 64 prompts x heads of 64 keys, 96 rows 8.9 / 8.8 -> 7.9 / 8.0; 1024,
+  // 128 rows 16.2 / 18.7 -> 13.9 / 18.4; 4096, 256 rows 90.6 / 92.8 -> 82.3 / 84.1; 8192, 192 rows 131.5 / 131.8 -> 128.3 / 126.9 (256 and 512 of
+  // them out of memory: up to 1.05 the other way, 192 rows 15.6 -> 16.0).  In more rounds the fragments' many loads set the pace: 16384 of
+  // 32 keys, 256 rows 232.8 -> 257.7, 128 rows 147.6 -> 157.5.  And so they do from two chunks on, whose waves share a compute unit: 32 of 512
+  // keys, 256 rows 30.2 -> 36.7.
+  const bool few = gs.waves == 1 && p.seq_len <= kMinChunkKeys && (int64_t)grid.x * grid.z <= 8192;
   int rc = DAPQ_OK;
-#define DAPQ_LAUNCH_F(NRBV, UNITV)                                                                                     \
-  do {                                                                                                                 \
-    if ((rc = set_lds(score_fused_kernel<NRBV, UNITV, kWaveStages>, kWavesPerGroup * wave_lds(kWaveStages))) != DAPQ_OK) \
-      return rc;                                                                                                       \
-    hipLaunchKernelGGL((score_fused_kernel<NRBV, UNITV, kWaveStages>), grid, dim3(64 * gs.waves),                      \
-                       gs.waves * wave_lds(kWaveStages), stream, p);                                                   \
+#define DAPQ_LAUNCH_F(NRBV, UNITV, SHORTV)                                                                                     \
+  do {                                                                                                                         \
+    if ((rc = set_lds(score_fused_kernel<NRBV, UNITV, SHORTV, kWaveStages>, kWavesPerGroup * wave_lds(kWaveStages))) != DAPQ_OK) \
+      return rc;                                                                                                               \
+    hipLaunchKernelGGL((score_fused_kernel<NRBV, UNITV, SHORTV, kWaveStages>), grid, dim3(64 * gs.waves),                      \
+                       gs.waves * wave_lds(kWaveStages), stream, p);                                                           \
   } while (0)
-#define DAPQ_LAUNCH_F_SUMS(NRBV)                 \
-  do {                                           \
-    if (plan.unit_sums) DAPQ_LAUNCH_F(NRBV, true); \
-    else DAPQ_LAUNCH_F(NRBV, false);             \
+#define DAPQ_LAUNCH_F_FORM(NRBV)                                       \
+  do {                                                                 \
+    if (plan.unit_sums) DAPQ_LAUNCH_F(NRBV, true, false);              \
+    else if (few && NRBV > 2) DAPQ_LAUNCH_F(NRBV, false, (NRBV > 2));  \
+    else DAPQ_LAUNCH_F(NRBV, false, false);                            \
   } while (0)
-  DAPQ_BY_ROW_BLOCKS(plan.row_blocks, DAPQ_LAUNCH_F_SUMS);
-#undef DAPQ_LAUNCH_F_SUMS
+  DAPQ_BY_ROW_BLOCKS(plan.row_blocks, DAPQ_LAUNCH_F_FORM);
+#undef DAPQ_LAUNCH_F_FORM
 #undef DAPQ_LAUNCH_F
   DAPQ_HIP_LAUNCH_CHECK("score_fused_kernel");
   return DAPQ_OK;

@@ -470,6 +470,14 @@ def test_equal_chunks_of_dense_batches(H, layers, batch, length, rows):
     assert np.abs(lse[:1].cpu().numpy() - oracle_lse2(q, k, 2, cu)).max() < 2e-4
 
 
+# one chunk of at most 128 keys: up to 8192 of them the queries come as fragments, with more through the ring; from 129 keys on it does not hold
+@pytest.mark.parametrize("rows", [64, 65, 128, 129, 192, 193, 256])
+@pytest.mark.parametrize("layers,batch,length", [(2, 3, 1), (3, 1, 33), (1, 2, 127), (2, 2, 128), (2, 2, 129), (1365, 3, 40), (1366, 3, 40)])
+def test_chunks_of_few_keys(H, layers, batch, length, rows):
+    """As above."""
+    test_equal_chunks_of_dense_batches(H, layers, batch, length, rows)
+
+
 @pytest.mark.parametrize("rows", [33, 128, 250])
 @pytest.mark.parametrize("layers,batch,length", [(160, 2, 700), (100, 3, 1500), (40, 5, 3000)])
 def test_one_or_two_chunks_in_one_kernel(H, layers, batch, length, rows):
