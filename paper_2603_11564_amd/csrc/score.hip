@@ -45,7 +45,6 @@
 #include <math.h>
 
 #include <mutex>
-#include <type_traits>
 
 #include "dapq_internal.h"
 #include "kernel_args.h"
@@ -1249,6 +1248,8 @@ __device__ __forceinline__ Tile tile_of_workgroup(const ScoreParams& p, bool rev
 struct TileShare {
   int subs, rbs, parts, rb, part;
 };
+// The most parts that the eight waves make of rbs row blocks (staged).
+__host__ __device__ constexpr int tile_most_parts(int rbs) { return rbs > 4 ? 1 : (rbs > 2 ? 2 : (rbs == 2 ? 4 : 8)); }
 template <bool STAGED>
 __device__ __forceinline__ TileShare tile_share(const ScoreParams& p, int wave, int waves) {
   TileShare s;
@@ -1262,7 +1263,7 @@ __device__ __forceinline__ TileShare tile_share(const ScoreParams& p, int wave, 
     if (wave >= s.rbs) s.part = 1;
     return s;
   }
-  s.parts = s.rbs > 4 ? 1 : (s.rbs > 2 ? 2 : (s.rbs == 2 ? 4 : 8));
+  s.parts = tile_most_parts(s.rbs);
   s.parts = s.parts < s.subs ? s.parts : s.subs;
   while (s.rb >= s.rbs) {
     s.rb -= s.rbs;
@@ -1324,11 +1325,10 @@ __device__ __forceinline__ const uint16_t* tile_k_base(const ScoreParams& p, con
                      (int64_t)t.kv * p.k_stride_head + w.tok0 * p.k_stride_token);
 }
 
-// Pass 1 with a running maximum.  STAGED: two sub-blocks at a time, as they arrive (two waves to a SIMD do not hide each other's waits: one
-// after the other, both passes with the rotation, 4096 keys, 256 rows 17.3 us, now 16.6, 512 rows 25.7, now 24.4; 8191 keys, 128 rows
-// 17.7, now 17.4); else 64 keys at a time, a wave's next row block loaded while it finishes the one before.
-template <bool STAGED>
-__global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(STAGED ? 2 : 5))) void score_tile_pass1_kernel(ScoreParams p) {
+// Pass 1 with a running maximum.  STAGED: U sub-blocks of a wave at a time, parts apart, as they arrive (two_at_a_time); else 64 keys at a
+// time, a wave's next row block loaded while it finishes the one before.
+template <bool STAGED, int U>
+__global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(!STAGED ? 5 : (U == 1 ? 4 : 2)))) void score_tile_pass1_kernel(ScoreParams p) {
   extern __shared__ u32x4 tile_area[];
   __shared__ float2 sums[STAGED ? kTileWaves : 1][32];
   touch_args<sizeof(ScoreParams)>();
@@ -1395,11 +1395,13 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(ST
     const bool mine = s.part < s.parts && rb < row_blocks;
     if (rb0 != 0 && mine) frag_from_q(qf, p, qbase, rb * 32 + n, h);
     float ref = -INFINITY, z[2] = {0.0f, 0.0f};
-    // U sub-blocks from number sub0 on, parts apart, at a time
-    auto units = [&](int sub0, auto count) {
-      constexpr int U = decltype(count)::value;
+    const int step = U * s.parts;
+#pragma unroll 1
+    for (int sub0 = 0; sub0 < s.subs; sub0 += step) {
+      if (rb0 == 0) tile_wait(s.subs - sub0 - step);
+      if (rb0 == 0 && sub0 == 0 && mine) wave_load_frags<1>(qf, queries + s.rb * kSubVec, n, h);
       const int first = (sub0 + s.part) * 32;
-      if (!mine || first >= w.nkeys) return;
+      if (!mine || first >= w.nkeys) continue;
       bf16x8 kf[U][8];
       f32x16 a[U];
 #pragma unroll
@@ -1432,14 +1434,6 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(ST
       for (int u = 0; u < U; ++u)
 #pragma unroll
         for (int v = 0; v < 16; ++v) z[v & 1] += __builtin_amdgcn_exp2f(fmaf(a[u][v], p.c, -mnew));
-    };
-    const int step = s.subs > s.parts ? 2 * s.parts : s.parts;
-#pragma unroll 1
-    for (int sub0 = 0; sub0 < s.subs; sub0 += step) {
-      if (rb0 == 0) tile_wait(s.subs - sub0 - step);
-      if (rb0 == 0 && sub0 == 0 && mine) wave_load_frags<1>(qf, queries + s.rb * kSubVec, n, h);
-      if (step > s.parts) units(sub0, std::integral_constant<int, 2>{});
-      else units(sub0, std::integral_constant<int, 1>{});
     }
     const float both = sum_halves(z[0] + z[1]);
     if (s.parts == 1) {
@@ -1476,8 +1470,8 @@ __host__ __device__ constexpr int tile_merge_chunks(int rows_pad) {
                                            ? kTileThreads / rows_pad * kMergeRuns * kCombineRun
                                            : kCombineClasses * kCombineRun;
 }
-template <bool MERGE, bool STAGED>
-__global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(STAGED ? 2 : 5))) void score_tile_pass2_kernel(ScoreParams p) {
+template <bool MERGE, bool STAGED, int U>
+__global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(!STAGED ? 5 : (U == 1 ? 4 : 2)))) void score_tile_pass2_kernel(ScoreParams p) {
   extern __shared__ u32x4 tile_area[];
   __shared__ __align__(16) float neg_lse[MERGE ? kMergeMaxRows : 4];
   __shared__ float merge_max[MERGE ? kMergeMaxRows : 1], merge_sum[MERGE ? kMergeMaxRows * kMergeRuns : 1];
@@ -1590,26 +1584,8 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(ST
     if (rb0 != 0) frag_from_q(qf, p, qbase, rb * 32 + n, h);
     else if (STAGED) wave_load_frags<1>(qf, queries + s.rb * kSubVec, n, h);
     if (STAGED || rb0 != 0) load_off(rb);
-    if constexpr (!STAGED) {
 #pragma unroll 1
-      for (int sub = 0; sub < s.subs; sub += s.parts) {
-        bf16x8 kf[8];
-        wave_load_frags<1>(kf, keys + sub * kSubVec, n, h);
-        f32x16 a = {0};
-#pragma unroll
-        for (int e = 0; e < 8; ++e) a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[e], kf[e], a, 0, 0, 0);
-        float z[2] = {0.0f, 0.0f};
-#pragma unroll
-        for (int v = 0; v < 16; ++v) z[v & 1] += __builtin_amdgcn_exp2f(fmaf(a[v], p.c, off[v]));
-        float* col = cols + s.rb * tile_keys + sub * 32 + n;
-        const float both = sum_halves(z[0] + z[1]);
-        if (h == 0) *col = rb0 == 0 ? both : *col + both;
-      }
-      continue;
-    }
-    // U sub-blocks from number sub on, parts apart, at a time
-    auto units = [&](int sub, auto count) {
-      constexpr int U = decltype(count)::value;
+    for (int sub = s.part; sub < s.subs; sub += U * s.parts) {
       bf16x8 kf[U][8];
       f32x16 a[U];
 #pragma unroll
@@ -1630,12 +1606,6 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(ST
         const float both = sum_halves(z[0] + z[1]);
         if (h == 0) *col = rb0 == 0 ? both : *col + both;
       }
-    };
-    const int step = s.subs > s.parts ? 2 * s.parts : s.parts;
-#pragma unroll 1
-    for (int sub = s.part; sub < s.subs; sub += step) {
-      if (step > s.parts) units(sub, std::integral_constant<int, 2>{});
-      else units(sub, std::integral_constant<int, 1>{});
     }
   }
   __syncthreads();
@@ -1750,6 +1720,13 @@ dim3 tile_threads(const ScorePlan& plan) {
   const int waves = plan.stage_q || plan.row_blocks > kTileWaves ? kTileWaves : (plan.row_blocks < 4 ? 4 : plan.row_blocks);
   return dim3(64u * (unsigned)waves);
 }
+// Whether a wave of a staged call takes two of its sub-blocks at a time: where it has several (both numbers are powers of two).  Two waves to a
+// SIMD do not hide each other's waits, two interleaved sub-blocks do; dapq_score of one layer of 8 KV heads, us, one -> two: 4096 keys, 256
+// rows 14.2 -> 14.0, 296 18.9 -> 17.8, 512 22.2 -> 21.0; 8192 keys, 128 rows 14.4 -> 14.1, 256 20.4 -> 19.5, 384 29.5 -> 27.0.  A kernel
+// with both forms in it is slower by 0.3 us, a first trip through more code: 1024 keys, 256 rows 10.2 -> 10.6, 8192 keys, 16 rows 10.5 -> 10.8.
+bool two_at_a_time(const ScorePlan& plan) {
+  return plan.stage_q && plan.chunk_keys / 32 > tile_most_parts(plan.row_blocks < kTileWaves ? plan.row_blocks : kTileWaves);
+}
 // (the whole dynamic limit once: see set_max_dynamic_lds)
 #define DAPQ_LAUNCH_TILE(kernel, sums)                                                                           \
   do {                                                                                                           \
@@ -1802,8 +1779,9 @@ int launch_stats(const dapq_shape* s, const ScorePlan& plan, ScoreParams p, hipS
   int rc = launch_chunk_prefix(s, plan, p, stream);
   if (rc != DAPQ_OK) return rc;
   if (plan.tile) {
-    if (plan.stage_q) DAPQ_LAUNCH_TILE(score_tile_pass1_kernel<true>, false);
-    else DAPQ_LAUNCH_TILE(score_tile_pass1_kernel<false>, false);
+    if (two_at_a_time(plan)) DAPQ_LAUNCH_TILE((score_tile_pass1_kernel<true, 2>), false);
+    else if (plan.stage_q) DAPQ_LAUNCH_TILE((score_tile_pass1_kernel<true, 1>), false);
+    else DAPQ_LAUNCH_TILE((score_tile_pass1_kernel<false, 1>), false);
     if (p.lse2 == nullptr) return DAPQ_OK;  // pass 2 merges the partials itself
   } else {
     if ((rc = launch_wave_pass1(s, plan, p, stream)) != DAPQ_OK) return rc;
@@ -1828,9 +1806,12 @@ int launch_accumulate(const dapq_shape* s, const ScorePlan& plan, ScoreParams p,
   int rc = launch_chunk_prefix(s, plan, p, stream);  // (pass 2 can be called on its own: it rebuilds the prefix it walks)
   if (rc != DAPQ_OK) return rc;
   if (plan.tile) {
-    if (p.lse2 == nullptr) DAPQ_LAUNCH_TILE((score_tile_pass2_kernel<true, true>), true);
-    else if (plan.stage_q) DAPQ_LAUNCH_TILE((score_tile_pass2_kernel<false, true>), true);
-    else DAPQ_LAUNCH_TILE((score_tile_pass2_kernel<false, false>), true);
+    const bool two = two_at_a_time(plan);
+    if (p.lse2 == nullptr && two) DAPQ_LAUNCH_TILE((score_tile_pass2_kernel<true, true, 2>), true);
+    else if (p.lse2 == nullptr) DAPQ_LAUNCH_TILE((score_tile_pass2_kernel<true, true, 1>), true);
+    else if (two) DAPQ_LAUNCH_TILE((score_tile_pass2_kernel<false, true, 2>), true);
+    else if (plan.stage_q) DAPQ_LAUNCH_TILE((score_tile_pass2_kernel<false, true, 1>), true);
+    else DAPQ_LAUNCH_TILE((score_tile_pass2_kernel<false, false, 1>), true);
     return DAPQ_OK;
   }
   const GroupShape gs = group_shape(s, plan);
