@@ -1147,18 +1147,20 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_fused_kernel(Sco
 // The causal block of the pseudo tokens' own keys (Sec. 4.1: they are prefilled in-sequence): a wave scores one block of 32 query rows
 // against the n_pseudo pseudo keys, row i = row % n_pseudo seeing keys 0..i, and folds the result into lse2 in place.  Every row sees
 // key 0, so its running maximum is finite from the first sub-block on.  The four waves of a workgroup have row blocks of the same (sequence,
-// layer, KV head) and share its keys; both come into LDS in whole rows, and up to sixteen waves of a compute unit hide each
-// other's trips to memory.  (One wave for up to eight row blocks, fragments
-// straight from memory: 4096 sequences x heads of 128 rows 40 us, now 32; one layer, 2 prompts of 24498 keys, 256 rows, the three calls
-// with the rotation 81 us, now 75.)
+// layer, KV head) and share its keys, which come into LDS in whole rows, a sub-block to a wave; the queries too, or, FRAGS, straight
+// from memory: up to two row blocks, whose loads keep no one waiting and whose LDS would keep other workgroups out.  Up to sixteen waves of
+// a compute unit hide each other's trips to memory.  One launch, us, one wave for up to eight row blocks -> this: 4096 sequences x heads of 128
+// rows 34.9 -> 30.9, of 256 89.1 -> 59.0; 256 of 128 rows 6.4 -> 4.9; of 64 rows 5.7 -> 5.1 (queries through LDS 5.0), 4096 of them 27.0 ->
+// 25.3 (25.6); 8 of one row 3.6 -> 3.4 (3.8), 4096 of them 7.0 -> 5.4 (8.0).
 struct PseudoParams {
   const uint16_t* kp;
   int64_t stride_layer, stride_seq, stride_head, stride_row;
 };
 
 constexpr int kPseudoWaves = 4, kPseudoSubs = 4;  // most row blocks of a workgroup, sub-blocks of keys that lie in LDS at a time
+template <bool FRAGS>
 __global__ __launch_bounds__(64 * kPseudoWaves, 4) void score_pseudo_kernel(ScoreParams p, PseudoParams pp) {
-  extern __shared__ u32x4 pseudo_area[];  // the queries' row blocks, then the keys
+  extern __shared__ u32x4 pseudo_area[];  // the queries' row blocks (not FRAGS), then the keys
   const int seq = blockIdx.x;
   const int layer = uniform_i32(quotient((int)blockIdx.z, p.inv_kv_heads)), kv = (int)blockIdx.z - layer * p.n_kv_heads;
   const int wave = uniform_i32((int)(threadIdx.x >> 6)), waves = (int)(blockDim.x >> 6);
@@ -1170,32 +1172,27 @@ __global__ __launch_bounds__(64 * kPseudoWaves, 4) void score_pseudo_kernel(Scor
   float* lse = p.lse2 + (((int64_t)layer * p.batch + seq) * p.n_q_heads + (int64_t)kv * p.group) * p.n_pseudo;
   const int row0 = ((int)blockIdx.y * waves + wave) * 32, row = row0 + n, rc = row < p.rows ? row : p.rows - 1;
   const bool mine = row0 < p.rows;  // (a wave without rows brings in keys)
-  u32x4 *queries = pseudo_area + wave * kSubVec, *keys = pseudo_area + waves * kSubVec;
-  if (mine) queries_dma(queries, p, qbase, row0);
+  u32x4 *queries = pseudo_area + wave * kSubVec, *keys = pseudo_area + (FRAGS ? 0 : waves * kSubVec);
+  bf16x8 qf[1][8];
+  if (mine) {
+    if constexpr (FRAGS) frag_from_q(qf[0], p, qbase, row, h);
+    else queries_dma(queries, p, qbase, row0);
+  }
   const int last_key[1] = {rc - quotient(rc, p.inv_n_pseudo) * p.n_pseudo};
   const float old = lse[rc];
   float ref[1] = {-INFINITY}, z[1] = {0.0f};
-  bf16x8 qf[1][8];
-  const unsigned r = (unsigned)lane >> 4, piece = ((unsigned)lane & 15u) ^ r;
-  const int64_t stride_b = pp.stride_row * 2;
+  unsigned voff[4];
+  sub_dma_lane_offsets(voff, pp.stride_row, lane);
   const int nsubs = (p.n_pseudo + 31) / 32;
   for (int sub0 = 0; sub0 < nsubs; sub0 += kPseudoSubs) {
     const int subs = nsubs - sub0 < kPseudoSubs ? nsubs - sub0 : kPseudoSubs;
     if (sub0 != 0) __syncthreads();  // everybody is done with the keys before these
-    for (int x = wave; x < subs * 8; x += waves) {  // four rows each; those past the last one arrive as zeros
-      const int key = sub0 * 32 + 4 * x;
-      const bool live = key < p.n_pseudo;
-      const int64_t span = (int64_t)(p.n_pseudo - key - 1) * stride_b + kHeadDim * 2;
-      const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
-          const_cast<char*>(reinterpret_cast<const char*>(kbase) + (live ? (int64_t)key * stride_b : (int64_t)0)), 0,
-          (int)(!live ? 0u : (span > (int64_t)0xFFFFFFFFll ? 0xFFFFFFFFu : (unsigned)span)), 0x00020000);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)(keys + x * 64), 16,
-                                               (int)(r * (unsigned)stride_b + (piece ^ (4u * ((unsigned)x & 3u))) * 16u), 0, 0, 0);
-    }
+    for (int sub = wave; sub < subs; sub += waves)  // (rows past the last one arrive as zeros)
+      sub_dma(keys + sub * kSubVec, kbase, pp.stride_row, (sub0 + sub) * 32, p.n_pseudo, true, voff);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (!mine) continue;
-    if (sub0 == 0) wave_load_frags<1>(qf[0], queries, n, h);
+    if (!FRAGS && sub0 == 0) wave_load_frags<1>(qf[0], queries, n, h);
     for (int sub = 0; sub < subs; ++sub) {
       const int key0 = (sub0 + sub) * 32;
       if (!__any(last_key[0] >= key0)) continue;
@@ -2044,8 +2041,11 @@ extern "C" DAPQ_API int dapq_score_stats_extend(const dapq_shape* shape, const v
   const int row_blocks = (plan.rows + 31) / 32, nsubs = (shape->n_pseudo + 31) / 32;
   const int waves = row_blocks < kPseudoWaves ? row_blocks : kPseudoWaves;
   const dim3 grid((unsigned)shape->batch, (unsigned)((row_blocks + waves - 1) / waves), (unsigned)(shape->n_layers * shape->n_kv_heads));
-  hipLaunchKernelGGL(score_pseudo_kernel, grid, dim3(64u * (unsigned)waves), (waves + (nsubs < kPseudoSubs ? nsubs : kPseudoSubs)) * kSubBytes,
-                     static_cast<hipStream_t>(stream), p, pp);
+  const int key_subs = nsubs < kPseudoSubs ? nsubs : kPseudoSubs;
+  const dim3 threads(64u * (unsigned)waves);
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  if (row_blocks <= 2) hipLaunchKernelGGL(score_pseudo_kernel<true>, grid, threads, key_subs * kSubBytes, st, p, pp);
+  else hipLaunchKernelGGL(score_pseudo_kernel<false>, grid, threads, (waves + key_subs) * kSubBytes, st, p, pp);
   DAPQ_HIP_LAUNCH_CHECK("score_pseudo_kernel");
   return DAPQ_OK;
 }
