@@ -145,15 +145,12 @@ __device__ __forceinline__ void topk_pick_digit(const uint32_t* hist, uint32_t* 
   if (g0 < un && un <= g0 + h0) { bcast[0] = 4 * lane + 0; bcast[1] = un - g0; bcast[2] = h0; }
 }
 
-// The register variants of up to 32 keys per thread bring their head in through LDS: the staging area of a wave is its threads' runs, KPT
+// STAGED: the register variants of up to 32 keys per thread bring their head in through LDS (reg_kernel_for): the staging area of a wave is its threads' runs, KPT
 // words each, and eight more words for the scores before and after them.  (64 keys per thread times 1024 threads do not fit.)
-constexpr bool reg_variant_is_staged(int kpt) { return kpt <= 32; }
 constexpr int reg_variant_wave_words(int kpt) { return 64 * kpt + 8; }
 constexpr int reg_variant_rows_bytes(int threads, int kpt) { return threads / 64 * reg_variant_wave_words(kpt) * (int)sizeof(float); }
 // (then the bins, which have a place of their own: a wave need not wait for the others until it counts)
-constexpr int reg_variant_stage_bytes(int threads, int kpt) {
-  return reg_variant_is_staged(kpt) ? reg_variant_rows_bytes(threads, kpt) + threads * (int)sizeof(uint4) : 0;
-}
+constexpr int reg_variant_stage_bytes(int threads, int kpt) { return reg_variant_rows_bytes(threads, kpt) + threads * (int)sizeof(uint4); }
 // Where the 16-byte piece `piece` of row `row` lies (in words), rows of KPT words: pieces XOR-swizzled so that sixteen threads next to
 // each other find the same piece of their rows in sixteen different groups of banks.
 template <int KPT>
@@ -428,10 +425,9 @@ __device__ __forceinline__ float window_max(const float (&ext)[N], int i) {
 
 // ---- heads that fit in registers.  R > 0: the input is the un-pooled score and the kernel applies
 // the max-pool of radius R itself (window clipped at the ends of the sequence) before selecting.
-template <int THREADS, int KPT, int R, bool PIECES>
+template <int THREADS, int KPT, int R, bool PIECES, bool STAGED>
 __global__ __launch_bounds__(THREADS) void topk_reg_kernel(TopkParams p) {
-  static_assert(!PIECES || reg_variant_is_staged(KPT), "the keys of a piece's survivors go through the staging area");
-  constexpr bool kStaged = reg_variant_is_staged(KPT);
+  static_assert(!PIECES || STAGED, "the keys of a piece's survivors go through the staging area");
   touch_args<sizeof(TopkParams)>();
   const int tid = threadIdx.x;
   const TopkHead hd = topk_head<PIECES>(p);
@@ -447,7 +443,7 @@ __global__ __launch_bounds__(THREADS) void topk_reg_kernel(TopkParams p) {
   // (a wave whose threads all have KPT keys is spared the tests)
   const bool whole = __all(nvalid == KPT);
   float ext[KPT + 2 * R];  // scores j0-R .. j0+KPT+R-1; -inf outside the sequence
-  if constexpr (kStaged) {
+  if constexpr (STAGED) {
     // A wave brings in its own keys with coalesced loads (a thread reading its run straight from memory makes every load instruction
     // touch 64 cache lines) and deals them out to its threads through its part of the staging area; the scores before and
     // after them, of which the windows at its ends take some, come along.  Nothing is shared with the other waves: those whose keys
@@ -579,7 +575,7 @@ __global__ __launch_bounds__(THREADS) void topk_reg_kernel(TopkParams p) {
   // The survivors go out through LDS where there is room (the staging area, which everybody has read by then): whole cache lines
   // instead of a few words of many.  64 heads of 131072 keys, 3932 kept: pieces 24.7 -> 19.6 us, and the merge, whose lists came in 64 bytes
   // to a thread and whose positions were fetched one by one, 14.2 -> 12.2.
-  if constexpr (kStaged) {
+  if constexpr (STAGED) {
     extern __shared__ float stage_area[];
     uint4* bins = reinterpret_cast<uint4*>(stage_area + reg_variant_rows_bytes(THREADS, KPT) / (int)sizeof(float));
     if constexpr (PIECES) {
@@ -872,52 +868,58 @@ namespace {
 // several of them share a compute unit.
 struct RegVariant {
   int threads, kpt;
+  bool staged;  // the scores through LDS
   int64_t max_len() const { return (int64_t)threads * kpt; }
 };
 
 RegVariant reg_variant_for(int64_t len) {
-  if (len <= 256 * 32) return {256, 32};
-  if (len <= 512 * 32) return {512, 32};  // (32 keys per thread is the lean code: 64 per thread spills scalar registers)
-  if (len <= 1024 * 32) return {1024, 32};
-  return {1024, 64};
+  if (len <= 256 * 32) return {256, 32, true};
+  if (len <= 512 * 32) return {512, 32, true};  // (32 keys per thread is the lean code: 64 per thread spills scalar registers)
+  if (len <= 1024 * 32) return {1024, 32, true};
+  return {1024, 64, false};
 }
 
-// The kernel for a launch of `heads` heads of at most `longest` keys that variant v holds.  Eight keys to a thread instead of 32 make
+// The kernel for a launch of `heads` heads of at most `longest` keys, and `mean` on average, that variant v holds.  Eight keys to a thread instead of 32 make
 // four times the waves, which hide each other's waits, of as many instructions; up to 4096 keys they are also the faster ones where
 // several workgroups share a compute unit, beyond that only while there is one for every head.  Pooling and selection, us, 8 / 256 /
 // 512 / 1024 heads: 1000 keys 256 x 32 8.3 / 9.0 / 9.8 / 12.5, 256 x 8 5.7 / 6.2 / 6.6 / 7.6; 4000 keys 256 x 32 8.6 / 9.1 / 10.2 / 13.1,
 // 512 x 8 6.2 / 6.7 / 8.1 / 11.0; 8000 keys 256 x 32 8.8 / 9.5 / 10.6 / 14.6, 1024 x 8 7.8 / 8.6 / 11.9 / 20.9.  (16000 keys: 512 x 32 10.0 /
 // 10.6 / 15.0, 1024 x 16 9.8 / 10.6 / 20.3.)
-RegVariant reg_kernel_for(RegVariant v, int64_t longest, int64_t heads) {
-  if (longest <= 256 * 8) return {256, 8};
-  if (longest <= 512 * 8) return {512, 8};
-  if (longest <= 1024 * 8 && heads <= 256) return {1024, 8};
+RegVariant reg_kernel_for(RegVariant v, int64_t longest, int64_t mean, int64_t heads) {
+  if (longest <= 256 * 8) return {256, 8, true};
+  if (longest <= 512 * 8) return {512, 8, true};
+  if (longest <= 1024 * 8 && heads <= 256) return {1024, 8, true};
+  // Many heads of a ragged batch that are much shorter than the workgroup could hold: the staging area, of which they use the start, lets four
+  // workgroups of 256 threads (two of 512) share a compute unit, registers would let seven.  Us, through LDS -> straight from memory: 1280
+  // heads of 1083 keys on average 17.5 -> 14.9, 4096 of 783 47.2 -> 41.7 (without a workspace, 512 threads, 69.4 -> 56.6), 4096 of 1872
+  // 49.8 -> 45.3; 1024 of 822 10.3, 2048 of 2557 29.1 and longer ones stay as they are (straight from memory 13.4 and 31.7).
+  if (v.threads < 1024 && mean * 4 <= v.max_len() && heads * v.threads > 256 * 1024) v.staged = false;
   return v;
 }
 
-template <int THREADS, int KPT, int R, bool PIECES>
+template <int THREADS, int KPT, int R, bool PIECES, bool STAGED>
 int launch_reg_kernel(dim3 grid, hipStream_t st, const TopkParams& p) {
-  constexpr int kBytes = reg_variant_stage_bytes(THREADS, KPT);
+  constexpr int kBytes = STAGED ? reg_variant_stage_bytes(THREADS, KPT) : 0;
   if (kBytes > 0) {
-    const int rc = set_max_dynamic_lds(reinterpret_cast<const void*>(topk_reg_kernel<THREADS, KPT, R, PIECES>), kBytes);
+    const int rc = set_max_dynamic_lds(reinterpret_cast<const void*>(topk_reg_kernel<THREADS, KPT, R, PIECES, STAGED>), kBytes);
     if (rc != DAPQ_OK) return rc;
   }
-  hipLaunchKernelGGL((topk_reg_kernel<THREADS, KPT, R, PIECES>), grid, dim3(THREADS), kBytes, st, p);
+  hipLaunchKernelGGL((topk_reg_kernel<THREADS, KPT, R, PIECES, STAGED>), grid, dim3(THREADS), kBytes, st, p);
   return DAPQ_OK;
 }
 
 template <int R>
 int launch_reg(RegVariant v, bool pieces, dim3 grid, hipStream_t st, const TopkParams& p) {
-  if (pieces) return launch_reg_kernel<1024, 32, R, true>(grid, st, p);
+  if (pieces) return launch_reg_kernel<1024, 32, R, true, true>(grid, st, p);
   if (v.kpt == 8) {
-    if (v.threads == 256) return launch_reg_kernel<256, 8, R, false>(grid, st, p);
-    if (v.threads == 512) return launch_reg_kernel<512, 8, R, false>(grid, st, p);
-    return launch_reg_kernel<1024, 8, R, false>(grid, st, p);
+    if (v.threads == 256) return launch_reg_kernel<256, 8, R, false, true>(grid, st, p);
+    if (v.threads == 512) return launch_reg_kernel<512, 8, R, false, true>(grid, st, p);
+    return launch_reg_kernel<1024, 8, R, false, true>(grid, st, p);
   }
-  if (v.threads == 256) return launch_reg_kernel<256, 32, R, false>(grid, st, p);
-  if (v.threads == 512) return launch_reg_kernel<512, 32, R, false>(grid, st, p);
-  if (v.kpt == 32) return launch_reg_kernel<1024, 32, R, false>(grid, st, p);
-  return launch_reg_kernel<1024, 64, R, false>(grid, st, p);
+  if (v.threads == 256) return v.staged ? launch_reg_kernel<256, 32, R, false, true>(grid, st, p) : launch_reg_kernel<256, 32, R, false, false>(grid, st, p);
+  if (v.threads == 512) return v.staged ? launch_reg_kernel<512, 32, R, false, true>(grid, st, p) : launch_reg_kernel<512, 32, R, false, false>(grid, st, p);
+  if (v.kpt == 32) return launch_reg_kernel<1024, 32, R, false, true>(grid, st, p);
+  return launch_reg_kernel<1024, 64, R, false, false>(grid, st, p);
 }
 
 int launch_reg_radius(int radius, RegVariant v, bool pieces, dim3 grid, hipStream_t st, const TopkParams& p) {
@@ -986,7 +988,7 @@ TopkRoute topk_route(const dapq_shape* shape, int32_t budget, bool with_pieces) 
   r.variant = reg_variant_for(sized_for);
   r.reg_max = r.variant.max_len();
   const int64_t heads = (int64_t)shape->n_layers * shape->batch * shape->n_kv_heads;
-  r.kernel = reg_kernel_for(r.variant, longest < r.reg_max ? longest : r.reg_max, heads);
+  r.kernel = reg_kernel_for(r.variant, longest < r.reg_max ? longest : r.reg_max, mean, heads);
   r.any_short = ragged || mean <= r.reg_max;  // (a dense batch of longer heads has nothing for the register variant)
   r.any_long = longest > r.reg_max;
   const int64_t n_segs = (longest + kTopkPieceLen - 1) / kTopkPieceLen;
@@ -1020,15 +1022,15 @@ int launch_long_heads(const dapq_shape* shape, const TopkRoute& r, TopkParams p,
     p.cand_idx = reinterpret_cast<int32_t*>(ws + r.off_idx);
     p.cand_count = reinterpret_cast<int32_t*>(ws + r.off_count);
     const dim3 piece_grid((unsigned)(shape->n_kv_heads * r.n_segs), (unsigned)shape->batch, (unsigned)shape->n_layers);
-    int rc = launch_reg_radius(radius, RegVariant{1024, 32}, true, piece_grid, st, p);
+    int rc = launch_reg_radius(radius, RegVariant{1024, 32, true}, true, piece_grid, st, p);
     if (rc != DAPQ_OK) return rc;
     DAPQ_HIP_LAUNCH_CHECK("topk_reg_kernel (pieces)");
     // (one workgroup per long head: from 8193 candidate slots on, the large workgroup's sixteen waves)
     const int64_t slots = (int64_t)r.n_segs * p.budget;
-    rc = launch_merge(slots <= 256 * 32    ? RegVariant{256, 32}
-                      : slots <= 1024 * 16 ? RegVariant{1024, 16}
-                      : slots <= 1024 * 32 ? RegVariant{1024, 32}
-                                           : RegVariant{1024, 64},
+    rc = launch_merge(slots <= 256 * 32    ? RegVariant{256, 32, true}
+                      : slots <= 1024 * 16 ? RegVariant{1024, 16, true}
+                      : slots <= 1024 * 32 ? RegVariant{1024, 32, true}
+                                           : RegVariant{1024, 64, false},
                       grid, st, p);
     if (rc != DAPQ_OK) return rc;
     DAPQ_HIP_LAUNCH_CHECK("topk_merge_kernel");
@@ -1136,7 +1138,7 @@ extern "C" DAPQ_API int dapq_pool_topk(const dapq_shape* shape, const float* sco
   }
   if (width <= 9 && longest <= 64 * kTopkThreads) {
     // one kernel: every head fits a register variant, which pools on the way in
-    const RegVariant v = reg_kernel_for(reg_variant_for(longest), longest, heads);
+    const RegVariant v = reg_kernel_for(reg_variant_for(longest), longest, shape->total_tokens / shape->batch, heads);
     if ((rc = launch_reg_radius(width / 2, v, false, grid, st, p)) != DAPQ_OK) return rc;
     DAPQ_HIP_LAUNCH_CHECK("topk_reg_kernel");
     return DAPQ_OK;

@@ -661,3 +661,39 @@ def test_survivors_of_pieces(H, length, budget):
     S = rng.lognormal(0.0, 0.5, (2, 2, length)).astype(np.float32)
     for width in (1, 7):
         check_selection(S, 1, width, budget, selection_call(H, S, 1, width, budget, True), [(0, 0, 0), (1, 0, 1)])
+
+
+# ragged batches of many heads much shorter than their kernel could hold, whose scores come straight from memory, and as many as still go
+# through LDS; heads on and off 16 bytes, empty, of one key, longer than a wave holds and as long as the workgroup
+@pytest.mark.parametrize("lens,layers,pieces", [
+    ([0, 1, 37, 601, 2049, 1300, 8, 3000], 65, False),              # 256 threads, 1040 heads
+    ([0, 1, 37, 601, 2049, 1300, 8, 3000], 64, False),              # 1024
+    ([5, 8192, 0, 13, 640, 1, 66, 2100], 65, True),                 # and a longer total: the same kernel beside the pieces
+    ([5, 8192, 0, 13, 640, 1, 66, 2100], 33, False),                # 512 threads, 528 heads
+    ([16000, 3, 0, 129, 32, 1, 64, 31], 33, False)])
+def test_short_heads_of_ragged_batches(H, lens, layers, pieces):
+    """The pooled scores and retained positions are the oracle's, bit for bit."""
+    announce(f"short heads: {layers} x 2 of {lens}, pieces {pieces}")
+    rng = np.random.default_rng(layers + lens[0])
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    S = rng.lognormal(0.0, 0.5, (layers, 2, int(cu[-1]))).astype(np.float32)
+    dev, cu_dev = torch.from_numpy(S).cuda(), torch.from_numpy(cu).cuda()
+    for width, budget in ((7, 300), (1, 40), (9, 9000)):
+        shape = H.D.make_shape(n_layers=layers, batch=len(lens), n_q_heads=2, n_kv_heads=2, n_pseudo=1, total_tokens=int(cu[-1]),
+                               cu_seqlens=cu_dev, scale=1.0)
+        n = H.D.topk_workspace_bytes(shape, budget) if pieces else 0
+        assert bool(n) == pieces
+        ws = torch.full((n,), 0xA5, dtype=torch.uint8, device="cuda") if n else None
+        idx = torch.full((layers, len(lens), 2, budget), -7, dtype=torch.int32, device="cuda")
+        count = torch.full((layers, len(lens), 2), -7, dtype=torch.int32, device="cuda")
+        pooled = torch.full_like(dev, float("nan"))
+        H.D.dapq_pool_topk(shape, dev, width, budget, None, idx, count, pooled, workspace=ws)
+        got, counts, P = idx.cpu().numpy(), count.cpu().numpy(), pooled.cpu().numpy()
+        for l, h in ((0, 0), (layers // 2, 1), (layers - 1, 0)):
+            for b in range(len(lens)):
+                head = slice(int(cu[b]), int(cu[b + 1]))
+                want_p = O.pool(S[l, h, head].astype(np.float64), width)
+                want = O.topk(want_p, budget)
+                assert np.array_equal(P[l, h, head].astype(np.float64), want_p), (l, h, b)
+                assert counts[l, b, h] == len(want) and np.array_equal(got[l, b, h, :len(want)], want), (l, h, b)
+                assert (got[l, b, h, len(want):] == -7).all()
