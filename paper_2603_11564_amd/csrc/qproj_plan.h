@@ -12,9 +12,9 @@ namespace dapq {
 constexpr int kBlockK = 64;           // hidden channels per block: 128-byte rows in LDS
 constexpr int64_t kQprojUnits = 256;  // compute units
 
-// The numbers of planes of partial sums that a call may have: qproj_reduce_rope_kernel is built for each of them.  Four waves to a workgroup
-// write one to eight planes, single waves a power of two up to sixteen.
-#define DAPQ_QPROJ_PLANES(each) each(1) each(2) each(3) each(4) each(5) each(6) each(7) each(8) each(16)
+// The numbers of planes of partial sums that a call may have: qproj_reduce_rope_kernel is built for each of them.  (There is room for sixteen
+// single waves' planes, but where so many are possible fewer workgroups of four cost less.)
+#define DAPQ_QPROJ_PLANES(each) each(1) each(2) each(3) each(4) each(5) each(6) each(7) each(8)
 constexpr bool qproj_planes_have_a_kernel(int planes) {
 #define DAPQ_ONE_OF(n) planes == n ||
   return DAPQ_QPROJ_PLANES(DAPQ_ONE_OF) false;
@@ -53,22 +53,28 @@ inline QprojPlan make_qproj_plan(const dapq_qproj& s) {
   // layers, single waves -> four: 5120 wide, 128 rows 37.4 -> 44.9; 4096 wide, 148 rows 28.7 -> 33.0.)
   if (pl.k_splits == 1 || (pl.sweeps > 1 && waves > kQprojUnits)) return pl;
   // Four waves to a workgroup, which has a compute unit to itself, add up before they write: half the planes or fewer, and more of
-  // the weight in flight.  As many workgroups along the hidden axis as cost least, in blocks of four waves: a workgroup's own and a start-up of
-  // two; no more planes than the workspace holds, and not more than eight, which cost the kernel that adds them.  Single waves share a
-  // compute unit four or five at a time (their rings), write a plane each and are slower by a tenth or more for the same cost; they
-  // stay where whole rounds of workgroups do not come out.  Whole call, us, single waves -> four: one layer 4096 wide, 64 rows 14.4 -> 14.0
-  // (three launches of the host); 256 rows 24.0 -> 20.9; 2 layers 22.8 -> 18.0; 8 layers 83.0 -> 66.8, of 16 rows 73.5 -> 55.7; 5120 wide, 64
-  // rows 18.5 -> 16.5; 8 layers 5120 wide, 32 rows 87.9 -> 92.8 (stays).
+  // the weight in flight.  Whatever costs least, in tenths of the time that one of four waves takes for a block: workgroups of four, as many
+  // along the hidden axis as there is room for planes, but not more than eight, or single waves, of which a compute unit holds four or
+  // five (their rings) and which take a block the faster the fewer they are.  The constants lose least over 826 calls (1 to 8 layers, 16 to
+  // 256 rows, 1024 to 16384 wide, 8 to 64 heads of 128), each timed as single waves and as one to eight workgroups of four, weights out of
+  // memory: against the single waves 0.942 of the time in the geometric mean and 32 calls above 1.025, none above 1.10 (with 40 for a block of
+  // three single waves too, and a tenth on top of them for their planes: 0.949, 86 calls, up to 1.245; the best of all ways 0.923).  Calls,
+  // us, single waves -> four: one layer 4096 wide, 256 rows 24.0 -> 20.9; 2 layers of 64 rows 22.8 -> 18.0; 8 layers 83.0 -> 66.8, of 16
+  // rows 73.5 -> 55.7; 5120 wide, 64 rows 18.5 -> 16.5.  Single waves stay where three to each unit are a whole round: 3 layers of 8 heads, 5120
+  // wide, 256 rows 23.9, four 29.6; 2 layers 6144 wide, 64 rows 38.8, four 44.8.
   const int per_unit = pl.mb == 2 ? 4 : 5;
   const int64_t tiles = waves, singles = tiles * pl.k_splits, units = kQprojUnits;
-  const int64_t together = per_unit > 4 && singles > 4 * units ? 5 : 4;  // (fewer than four take a block no faster)
-  int64_t best = (singles + units * per_unit - 1) / (units * per_unit) * (pl.kb_per_split * together + 8);  // (four times blocks)
-  best += best / 10;
+  const int64_t rounds = (singles + units * per_unit - 1) / (units * per_unit), shared = rounds > 1 ? per_unit : (singles + units - 1) / units;
+  constexpr int kPlane = 6;
+  int64_t best = kPlane * pl.k_splits;
+  if (shared <= 3) best += 33 * pl.kb_per_split + 150;
+  else if (shared == 4) best += rounds * (45 * pl.kb_per_split + 60);
+  else best += rounds * (55 * pl.kb_per_split + 130);
   const int most = pl.k_splits < 8 ? pl.k_splits : 8;
   for (int splits = 1; splits <= most; ++splits) {
     const int each = (n_kb + 4 * splits - 1) / (4 * splits);
     if ((int64_t)(splits - 1) * 4 * each >= n_kb) continue;  // (a workgroup without blocks)
-    const int64_t cost = (tiles * splits + units - 1) / units * (each + 2) * 4;
+    const int64_t cost = (tiles * splits + units - 1) / units * (40 * (int64_t)each + (pl.mb == 2 ? 110 : 80)) + kPlane * splits;
     if (cost < best) {
       best = cost;
       pl.waves = 4;

@@ -210,15 +210,15 @@ def test_rotated_queries_match_oracle_and_the_two_calls(H, pairing):
         assert (got[l] == want_bits).mean() > 0.98
 
 
-# 2, 4, 8 and 16 hidden splits, whose sums are rotated as they are added up; channel pairs that do not fill a workgroup, head sizes
-# that do not fill a feature tile, one and several sweeps and layers
+# workspaces with room for 2, 4, 8 and 16 planes of sums, which are rotated as they are added up (how many a call writes: the shapes by plan
+# below); channel pairs that do not fill a workgroup, head sizes that do not fill a feature tile, one and several sweeps and layers
 @pytest.mark.parametrize("pairing", [0, 1])
 @pytest.mark.parametrize("hidden,splits", [(1024, 2), (2048, 4), (4096, 8), (8192, 16)])
 @pytest.mark.parametrize("layers,Hq,d,rows", [(1, 3, 72, 37), (2, 2, 128, 65), (1, 1, 8, 1)])
 def test_rotated_queries_of_split_calls(H, layers, Hq, d, rows, hidden, splits, pairing):
     """One call = the projection (without positions), then dapq_rope_apply on its output: bit for bit, with missing sources, padded
     strides and rows past the end left alone; and the projection is the oracle's (check_projection)."""
-    announce(f"pseudo queries: rotation of {splits} splits, {layers} layers, {Hq} heads of {d}, {rows} rows, pairing {pairing}")
+    announce(f"pseudo queries: rotation, room for {splits} planes, {layers} layers, {Hq} heads of {d}, {rows} rows, pairing {pairing}")
     r = np.random.default_rng(hidden + rows)
     tokens = 20
     tok = r.integers(-1, tokens, rows).tolist()

@@ -69,4 +69,6 @@ def test_every_plan_has_its_kernels(program):
 def test_the_shapes_of_the_gpu_tests_get_the_plans_they_stand_for(program):
     lines = "".join("%d %d %d %d %d\n" % shape for shape in SPLIT_SHAPES)
     out = subprocess.run([program, "-"], input=lines, capture_output=True, text=True, check=True, timeout=60).stdout
-    assert [tuple(map(int, line.split())) for line in out.splitlines()] == list(SPLIT_SHAPES.values())
+    got = dict(zip(SPLIT_SHAPES, (tuple(map(int, line.split())) for line in out.splitlines())))
+    assert got == SPLIT_SHAPES
+    assert {planes for waves, planes in got.values() if waves == 4} == set(range(1, 9))
