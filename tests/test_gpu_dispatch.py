@@ -421,10 +421,10 @@ def test_selection_of_mixed_waves(H, n, equal):
             assert np.array_equal(got, O.topk(S[0, kv].astype(np.float64), budget)), (budget, kv)
 
 
-# ragged batches too large for the tile form (more than 65536 units): the kernels of two, four and eight row blocks, two row groups,
-# up to and beyond the 64 sequences that a wave looks up by itself
+# ragged batches too large for the tile form (more than 65536 units): the kernels of two, four, seven and eight row blocks, two row groups
+# of eight, up to and beyond the 64 sequences that a wave looks up by itself
 @pytest.mark.parametrize("batch", [40, 64, 65, 100])
-@pytest.mark.parametrize("rows", [33, 128, 200, 512])
+@pytest.mark.parametrize("rows", [33, 128, 200, 250, 512])
 def test_ragged_batches_in_the_wave_form(H, rows, batch):
     """Every layer is the same problem (layer strides of 0): all layers have the same bits, and the first has the oracle's
     scores within 1e-3 (the bar of the other score tests)."""
@@ -445,8 +445,9 @@ def test_ragged_batches_in_the_wave_form(H, rows, batch):
 
 
 # dense batches whose chunks are no powers of two: eight per sequence, shorter than the power of two; four and two, longer (sums in
-# two steps; up to 256 rows both passes in one kernel); three and one; several sequences; the last chunk with a partial sub-block or short
-@pytest.mark.parametrize("rows", [33, 128, 250, 300])
+# two steps; up to 256 rows both passes in one kernel); three and one; several sequences; the last chunk with a partial sub-block or short;
+# a wave of two to eight row blocks, two row groups of five
+@pytest.mark.parametrize("rows", [33, 96, 128, 160, 192, 224, 250, 300])
 @pytest.mark.parametrize("layers,batch,length", [(64, 1, 3001), (128, 1, 5000), (170, 1, 2900), (70, 7, 1111), (25, 3, 2017)])
 def test_equal_chunks_of_dense_batches(H, layers, batch, length, rows):
     """Every layer is the same problem (layer strides of 0), with a key hundreds of binades above the others: the oracle's scores within
@@ -478,7 +479,7 @@ def test_chunks_of_few_keys(H, layers, batch, length, rows):
     test_equal_chunks_of_dense_batches(H, layers, batch, length, rows)
 
 
-@pytest.mark.parametrize("rows", [33, 128, 250])
+@pytest.mark.parametrize("rows", [33, 96, 128, 160, 192, 224, 250])
 @pytest.mark.parametrize("layers,batch,length", [(160, 2, 700), (100, 3, 1500), (40, 5, 3000)])
 def test_one_or_two_chunks_in_one_kernel(H, layers, batch, length, rows):
     """One chunk of a sequence, or two, longer than the power of two (sums in two steps): as above."""
@@ -585,7 +586,7 @@ def test_candidates_of_long_heads_off_16_bytes(H, offset):
 
 # a wave holds two to eight row blocks, the row groups of a head as many each: the last rows of one number and the first of the next,
 # one to three groups; both passes in one kernel, in separate launches, and in segments of a ragged batch
-@pytest.mark.parametrize("lens,layers,ragged", [([700, 700], 130, False), ([5100], 24, False), ([1500, 0, 33, 800, 64], 200, True)],
+@pytest.mark.parametrize("lens,layers,ragged", [([700, 700], 130, False), ([5100], 30, False), ([1500, 0, 33, 800, 64], 200, True)],
                          ids=["one kernel", "launches", "segments"])
 @pytest.mark.parametrize("rows", [64, 65, 96, 97, 129, 160, 161, 192, 193, 224, 225, 257, 321, 449, 513])
 def test_row_blocks_of_a_wave(H, rows, lens, layers, ragged):
@@ -598,6 +599,9 @@ def test_row_blocks_of_a_wave(H, rows, lens, layers, ragged):
     layers = layers * 513 // rows if ragged else layers                                     # beyond the tile form
     shape = H.D.make_shape(n_layers=layers, batch=len(lens), n_q_heads=1, n_kv_heads=1, n_pseudo=rows, total_tokens=tokens,
                            cu_seqlens=prob.cu, k_strides=(0, 0, 128, 128), q_strides=(0, rows * 128, rows * 128, 128), scale=128 ** -0.5)
+    if not ragged:  # (dense calls of up to 1024 tiles of 128 keys may take the tile form)
+        assert len(lens) == 2 or layers * -(-tokens // 128) > 1024
+        assert H.D.score_single_launch(shape) == (len(lens) == 2 and rows <= 256)
     ws = torch.full((H.D.workspace_bytes(shape),), 0xA5, dtype=torch.uint8, device="cuda")
     S, T, X = (torch.full((layers, 1, tokens), float("nan"), dtype=torch.float32, device="cuda") for _ in range(3))
     lse = torch.full((layers, len(lens), 1, rows), float("nan"), dtype=torch.float32, device="cuda")
