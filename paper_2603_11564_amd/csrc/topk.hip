@@ -145,8 +145,8 @@ __device__ __forceinline__ void topk_pick_digit(const uint32_t* hist, uint32_t* 
   if (g0 < un && un <= g0 + h0) { bcast[0] = 4 * lane + 0; bcast[1] = un - g0; bcast[2] = h0; }
 }
 
-// STAGED: the register variants of up to 32 keys per thread bring their head in through LDS (reg_kernel_for): the staging area of a wave is its threads' runs, KPT
-// words each, and eight more words for the scores before and after them.  (64 keys per thread times 1024 threads do not fit.)
+// STAGED: the register variants of up to 32 keys per thread bring their head in through LDS (reg_kernel_for): the staging area of a wave is its
+// threads' runs, KPT words each, and eight more words for the scores before and after them.  (64 keys per thread times 1024 threads do not fit.)
 constexpr int reg_variant_wave_words(int kpt) { return 64 * kpt + 8; }
 constexpr int reg_variant_rows_bytes(int threads, int kpt) { return threads / 64 * reg_variant_wave_words(kpt) * (int)sizeof(float); }
 // (then the bins, which have a place of their own: a wave need not wait for the others until it counts)
@@ -573,8 +573,8 @@ __global__ __launch_bounds__(THREADS) void topk_reg_kernel(TopkParams p) {
   if (hd.done) return;
 
   // The survivors go out through LDS where there is room (the staging area, which everybody has read by then): whole cache lines
-  // instead of a few words of many.  64 heads of 131072 keys, 3932 kept: pieces 24.7 -> 19.6 us, and the merge, whose lists came in 64 bytes
-  // to a thread and whose positions were fetched one by one, 14.2 -> 12.2.
+  // instead of a few words of many.  64 heads of 131072 keys, 3932 kept: pieces 24.6 -> 18.3 us, and the merge, whose lists came in 64 bytes
+  // to a thread and whose positions were fetched one by one, 14.1 -> 12.2.
   if constexpr (STAGED) {
     extern __shared__ float stage_area[];
     uint4* bins = reinterpret_cast<uint4*>(stage_area + reg_variant_rows_bytes(THREADS, KPT) / (int)sizeof(float));
