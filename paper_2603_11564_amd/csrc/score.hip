@@ -748,7 +748,7 @@ __device__ __forceinline__ void queries_dma(u32x4* slot, const ScoreParams& p, c
 // rotation, us: 8 layers, 256 rows, 4096 keys 68.2 -> 58.8; 32 layers of 4 KV heads, 256 rows, 1104 keys 50.0 -> 44.4; one layer, 256
 // rows, 2 prompts of 24498 keys, extended 87.4 -> 81.4; 64 prompts of 512 keys 1602 -> 1579; C2's one chunk to a wave 1.000.  (The sequences of a
 // segment, whose ring is running: no faster so, 757 -> 764 for 16 prompts of 200..2500 keys, 128 rows; nor two row blocks: 16 rows, 8
-// prompts of 9783 keys 55.1 -> 56.8, 64 rows, 8 of 5000 as fast; nor short chunks, see launch_fused.  Those load them as fragments.)
+// prompts of 9783 keys 55.1 -> 56.8, 64 rows, 8 of 5000 as fast; nor short chunks, see few_keys.  Those load them as fragments.)
 template <int NRB, int NST, class Stream>
 __device__ __forceinline__ void start_with_queries(const ScoreParams& p, u32x4* ring, int& slot, Stream& keys, bf16x8 (&qf)[NRB][8],
                                                    const uint16_t* qbase, int gbase, const unsigned (&voff)[4], int first_sub, int n,
@@ -860,7 +860,7 @@ __device__ __forceinline__ const uint16_t* wave_q_base(const ScoreParams& p, int
 
 // Pass 1 of one chunk of a dense batch: `group` = row group, `chunk_id` = chunk along the packed key axis.  The chunk must have
 // keys.  FUSED (score_fused_kernel): the chunk's (reference, sum) pairs go to the start of the wave's own ring, which is
-// drained by then, instead of to global memory.  SHORT: the queries as fragments (launch_fused).
+// drained by then, instead of to global memory.  SHORT: the queries as fragments.
 template <int NRB, int NST, bool UNIT, bool FUSED = false, bool SHORT = false>
 __device__ __forceinline__ void pass1_chunk(const ScoreParams& p, u32x4* ring, const Work& w, int chunk_id, int group, int head,
                                             bf16x8 (&qf)[NRB][8], int lane) {
@@ -928,8 +928,8 @@ __device__ __forceinline__ WaveSlot wave_slot(const ScoreParams& p, int wave_id)
 }
 
 // The grid names the items, one per wave: (chunk, row group, layer x KV head).  SEG (ragged batches, whose lengths
-// the host does not know): a segment of the packed key axis in the place of the chunk.
-template <int NRB, bool SEG, bool UNIT, int NST>
+// the host does not know): a segment of the packed key axis in the place of the chunk.  SHORT: see few_keys.
+template <int NRB, bool SEG, bool UNIT, bool SHORT, int NST>
 __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_wave_pass1_kernel(ScoreParams p) {
   extern __shared__ u32x4 rings[];
   const int wave_id = uniform_i32((int)(threadIdx.x >> 6));
@@ -942,21 +942,21 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_wave_pass1_kerne
   } else {
     const Work w = locate_uniform(p, slot.chunk);
     if (w.nkeys == 0) return;
-    pass1_chunk<NRB, NST, UNIT>(p, ring, w, slot.chunk, slot.group, (int)blockIdx.z, qf, lane);
+    pass1_chunk<NRB, NST, UNIT, false, SHORT>(p, ring, w, slot.chunk, slot.group, (int)blockIdx.z, qf, lane);
   }
 }
 
 // Pass 2 of `count` sub-blocks of one sequence (or chunk), from number first_sub down (arguments as pass1_piece).  lse: of the
 // sequence's first row, out: where the sums of its first key go.  LOADED: the query fragments are in registers and off2 is
 // filled.
-template <int NRB, int NST, bool LOADED, class Stream>
+template <int NRB, int NST, bool LOADED, bool FRAGS, class Stream>
 __device__ __forceinline__ void pass2_piece(const ScoreParams& p, u32x4* ring, int& slot, Stream& keys, bf16x8 (&kf)[8],
                                             bf16x8 (&qf)[NRB][8], float (&off2)[NRB][16], const uint16_t* qbase,
                                             const float* lse, int first_sub, int count, int nkeys, int gbase,
                                             const unsigned (&voff)[4], bool start, float* out) {
   const int lane = fresh_lane(), n = lane & 31, h = lane >> 5;
   if constexpr (!LOADED) {
-    if constexpr (Stream::kSegment || NRB == 2) {
+    if constexpr (FRAGS) {
 #pragma unroll
       for (int rb = 0; rb < NRB; ++rb) frag_from_q(qf[rb], p, qbase, gbase + rb * 32 + n, h);
       if (NRB > 4) pin_q_in_agprs<NRB>(qf);
@@ -1008,7 +1008,7 @@ __device__ __forceinline__ float* wave_plane(const ScoreParams& p, int head, int
 
 // Pass 2 of one chunk of a dense batch (arguments as pass1_chunk).  FUSED (score_fused_kernel): the query fragments are still in
 // registers from pass 1 and the caller has filled off2.
-template <int NRB, int NST, bool FUSED = false>
+template <int NRB, int NST, bool SHORT, bool FUSED = false>
 __device__ __forceinline__ void pass2_chunk(const ScoreParams& p, u32x4* ring, const Work& w, int group, int head,
                                             bf16x8 (&qf)[NRB][8], float (&off2)[NRB][16], int lane) {
   unsigned voff[4];
@@ -1019,10 +1019,11 @@ __device__ __forceinline__ void pass2_chunk(const ScoreParams& p, u32x4* ring, c
   float* out = const_cast<float*>(uniform_ptr(wave_plane(p, head, group) + w.tok0));
   const int nsubs = (w.nkeys + 31) / 32;
   KeyStream<true, false> keys = {p, nullptr, kbase, w.nkeys, 0, 0, 0};
-  if (FUSED || NRB == 2) fill_ring<NST>(ring, keys, voff, nsubs - 1);
+  constexpr bool kFrags = NRB == 2 || SHORT;
+  if (FUSED || kFrags) fill_ring<NST>(ring, keys, voff, nsubs - 1);
   bf16x8 kf[8];
   int slot = 0;
-  pass2_piece<NRB, NST, FUSED>(p, ring, slot, keys, kf, qf, off2, wave_q_base(p, layer, kv, w.seq), wave_lse(p, layer, kv, w.seq),
+  pass2_piece<NRB, NST, FUSED, kFrags>(p, ring, slot, keys, kf, qf, off2, wave_q_base(p, layer, kv, w.seq), wave_lse(p, layer, kv, w.seq),
                                nsubs - 1, nsubs, w.nkeys, group * (NRB * 32), voff, true, out);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
@@ -1051,7 +1052,7 @@ __device__ __forceinline__ void pass2_segment(const ScoreParams& p, u32x4* ring,
       // (the sums of a piece go out relative to its first key: their offsets are 32 bits wide)
       const int key0 = (at.sub + 1 - count) * 32, keys_here = nkeys - key0 < count * 32 ? nkeys - key0 : count * 32;
       float* out = const_cast<float*>(uniform_ptr(wave_plane(p, head, group) + r.start + key0));
-      pass2_piece<NRB, NST, false>(p, ring, slot, keys, kf, qf, off2, wave_q_base(p, layer, kv, at.seq),
+      pass2_piece<NRB, NST, false, true>(p, ring, slot, keys, kf, qf, off2, wave_q_base(p, layer, kv, at.seq),
                                    wave_lse(p, layer, kv, at.seq), count - 1, count, keys_here, group * (NRB * 32), voff, start, out);
       at.left -= count;
       if (at.left == 0) break;
@@ -1064,7 +1065,7 @@ __device__ __forceinline__ void pass2_segment(const ScoreParams& p, u32x4* ring,
 // (SEG as in pass 1.)  Heads and, inside a chunk or segment, the keys are walked in the opposite order to pass 1: what pass 1
 // read last (the ends of the chunks in flight, the heads of the last round) is still in the 256 MB memory-side cache
 // when pass 2 starts.
-template <int NRB, bool SEG, int NST>
+template <int NRB, bool SEG, bool SHORT, int NST>
 __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_wave_pass2_kernel(ScoreParams p) {
   extern __shared__ u32x4 rings[];
   const int wave_id = uniform_i32((int)(threadIdx.x >> 6));
@@ -1079,7 +1080,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_wave_pass2_kerne
   } else {
     const Work w = locate_uniform(p, slot.chunk);
     if (w.nkeys == 0) return;
-    pass2_chunk<NRB, NST>(p, ring, w, slot.group, head, qf, off2, lane);
+    pass2_chunk<NRB, NST, SHORT>(p, ring, w, slot.group, head, qf, off2, lane);
   }
 }
 
@@ -1091,7 +1092,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_wave_pass2_kerne
 // the query fragments still in registers.  What this saves is everything between the passes: a kernel boundary at
 // which every wave of the chip waits for the slowest, the combine kernel, the second placement of the workgroups and
 // the second read of the queries.  lse2 is not written anywhere.
-// SHORT: see launch_fused.
+// SHORT: see few_keys.
 template <int NRB, bool UNIT, bool SHORT, int NST>
 __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_fused_kernel(ScoreParams p) {
   extern __shared__ u32x4 rings[];
@@ -1141,7 +1142,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_fused_kernel(Sco
       off2[rb][4 * b + 3] = v.w;
     }
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // off2 is out of the ring before pass 2 refills it
-  pass2_chunk<NRB, NST, true>(p, ring, work, 0, head, qf, off2, lane);
+  pass2_chunk<NRB, NST, false, true>(p, ring, work, 0, head, qf, off2, lane);
 }
 
 // The causal block of the pseudo tokens' own keys (Sec. 4.1: they are prefilled in-sequence): a wave scores one block of 32 query rows
@@ -1747,23 +1748,37 @@ bool two_at_a_time(const ScorePlan& plan) {
     }                                          \
   } while (0)
 
+// Whether the waves of a dense launch start with the queries as fragments (SHORT) although they are more than two row blocks.  All keys of
+// a chunk of a few sub-blocks fit the ring at once; they and fragments arrive in one trip to memory, and behind queries that go through the
+// ring they wait for two or three.  It is the shorter start where the waves of a compute unit are workgroups of their own (side by side in
+// one, their many loads set the pace: 32 prompts x heads of 512 keys, 256 rows 30.2 us through the ring, 36.7), in one kernel up to some
+// eight rounds of waves.  Ring -> fragments, us, dapq_score with inputs in the caches / out of memory: 64 prompts x heads of 64 keys, 96 rows
+// 8.9 / 8.8 -> 7.9 / 8.0; 1024, 128 rows 16.2 / 18.7 -> 13.9 / 18.4; 4096, 256 rows 90.6 / 92.8 -> 82.3 / 84.1; 8192, 192 rows 131.5 / 131.8 ->
+// 128.3 / 126.9 (256 and 512 of them out of memory up to 1.05 the other way, 192 rows 15.6 -> 16.0; 16384 of 32 keys, 256 rows 232.8 -> 257.7).
+// The two separate calls, out of memory: 8 heads of 64 keys, 96 rows 14.2 -> 11.8; 256, 256 rows 27.3 -> 24.4; 8192, 192 rows 220 -> 210.
+bool few_keys(const dapq_shape* s, const ScorePlan& plan, const GroupShape& gs) {
+  return plan.segments == 0 && gs.waves == 1 && s->total_tokens / s->batch <= kMinChunkKeys;
+}
+
 int launch_wave_pass1(const dapq_shape* s, const ScorePlan& plan, ScoreParams p, hipStream_t stream) {
   int rc = DAPQ_OK;
   const GroupShape gs = group_shape(s, plan);
   p.wg_groups = gs.groups;
-#define DAPQ_LAUNCH_W1(NRBV, SEGV, UNITV)                                                                                  \
-  do {                                                                                                                  \
-    if ((rc = set_lds(score_wave_pass1_kernel<NRBV, SEGV, UNITV, kWaveStages>, kWavesPerGroup * wave_lds(kWaveStages))) != \
-        DAPQ_OK)                                                                                                        \
-      return rc;                                                                                                        \
-    hipLaunchKernelGGL((score_wave_pass1_kernel<NRBV, SEGV, UNITV, kWaveStages>), gs.grid(plan, s), dim3(64 * gs.waves),  \
-                       gs.waves * wave_lds(kWaveStages), stream, p);                                                    \
+  const bool few = few_keys(s, plan, gs);
+#define DAPQ_LAUNCH_W1(NRBV, SEGV, UNITV, SHORTV)                                                                        \
+  do {                                                                                                                   \
+    if ((rc = set_lds(score_wave_pass1_kernel<NRBV, SEGV, UNITV, SHORTV, kWaveStages>,                                   \
+                      kWavesPerGroup * wave_lds(kWaveStages))) != DAPQ_OK)                                               \
+      return rc;                                                                                                         \
+    hipLaunchKernelGGL((score_wave_pass1_kernel<NRBV, SEGV, UNITV, SHORTV, kWaveStages>), gs.grid(plan, s),              \
+                       dim3(64 * gs.waves), gs.waves * wave_lds(kWaveStages), stream, p);                                \
   } while (0)
-#define DAPQ_LAUNCH_W1_KEYS(NRBV)                             \
-  do {                                                        \
-    if (plan.segments > 0) DAPQ_LAUNCH_W1(NRBV, true, true);  \
-    else if (plan.unit_sums) DAPQ_LAUNCH_W1(NRBV, false, true); \
-    else DAPQ_LAUNCH_W1(NRBV, false, false);                  \
+#define DAPQ_LAUNCH_W1_KEYS(NRBV)                                               \
+  do {                                                                          \
+    if (plan.segments > 0) DAPQ_LAUNCH_W1(NRBV, true, true, false);             \
+    else if (plan.unit_sums) DAPQ_LAUNCH_W1(NRBV, false, true, false);          \
+    else if (few && NRBV > 2) DAPQ_LAUNCH_W1(NRBV, false, false, (NRBV > 2));   \
+    else DAPQ_LAUNCH_W1(NRBV, false, false, false);                             \
   } while (0)
   DAPQ_BY_ROW_BLOCKS(plan.row_blocks, DAPQ_LAUNCH_W1_KEYS);
 #undef DAPQ_LAUNCH_W1_KEYS
@@ -1813,18 +1828,20 @@ int launch_accumulate(const dapq_shape* s, const ScorePlan& plan, ScoreParams p,
   }
   const GroupShape gs = group_shape(s, plan);
   p.wg_groups = gs.groups;
-#define DAPQ_LAUNCH_W2(NRBV, SEGV)                                                                                      \
-  do {                                                                                                                  \
-    if ((rc = set_lds(score_wave_pass2_kernel<NRBV, SEGV, kWaveStages>, kWavesPerGroup * wave_lds(kWaveStages))) !=     \
-        DAPQ_OK)                                                                                                        \
-      return rc;                                                                                                        \
-    hipLaunchKernelGGL((score_wave_pass2_kernel<NRBV, SEGV, kWaveStages>), gs.grid(plan, s), dim3(64 * gs.waves),       \
-                       gs.waves * wave_lds(kWaveStages), stream, p);                                                    \
+  const bool few = few_keys(s, plan, gs);
+#define DAPQ_LAUNCH_W2(NRBV, SEGV, SHORTV)                                                                                  \
+  do {                                                                                                                      \
+    if ((rc = set_lds(score_wave_pass2_kernel<NRBV, SEGV, SHORTV, kWaveStages>, kWavesPerGroup * wave_lds(kWaveStages))) != \
+        DAPQ_OK)                                                                                                            \
+      return rc;                                                                                                            \
+    hipLaunchKernelGGL((score_wave_pass2_kernel<NRBV, SEGV, SHORTV, kWaveStages>), gs.grid(plan, s), dim3(64 * gs.waves),   \
+                       gs.waves * wave_lds(kWaveStages), stream, p);                                                        \
   } while (0)
-#define DAPQ_LAUNCH_W2_KEYS(NRBV)                     \
-  do {                                                \
-    if (plan.segments > 0) DAPQ_LAUNCH_W2(NRBV, true); \
-    else DAPQ_LAUNCH_W2(NRBV, false);                 \
+#define DAPQ_LAUNCH_W2_KEYS(NRBV)                                       \
+  do {                                                                  \
+    if (plan.segments > 0) DAPQ_LAUNCH_W2(NRBV, true, false);           \
+    else if (few && NRBV > 2) DAPQ_LAUNCH_W2(NRBV, false, (NRBV > 2));  \
+    else DAPQ_LAUNCH_W2(NRBV, false, false);                            \
   } while (0)
   DAPQ_BY_ROW_BLOCKS(plan.row_blocks, DAPQ_LAUNCH_W2_KEYS);
 #undef DAPQ_LAUNCH_W2_KEYS
@@ -1856,14 +1873,7 @@ int launch_fused(const dapq_shape* s, const ScorePlan& plan, ScoreParams p, hipS
   const GroupShape gs = {fused_waves(s, plan), 1};
   p.wg_groups = 1;
   const dim3 grid((unsigned)s->batch, 1u, (unsigned)(s->n_layers * s->n_kv_heads));
-  // One chunk of a few sub-blocks: all of its keys fit the ring at once, and they and the queries, loaded as fragments, arrive in one trip to
-  // memory; behind queries that go through the ring they wait for two or three.  Up to some 8 rounds of waves that is the shorter start,
-  // inputs in the caches / out of memory, us, through the ring -> fragments: 64 prompts x heads of 64 keys, 96 rows 8.9 / 8.8 -> 7.9 / 8.0; 1024,
-  // 128 rows 16.2 / 18.7 -> 13.9 / 18.4; 4096, 256 rows 90.6 / 92.8 -> 82.3 / 84.1; 8192, 192 rows 131.5 / 131.8 -> 128.3 / 126.9 (256 and 512 of
-  // them out of memory: up to 1.05 the other way, 192 rows 15.6 -> 16.0).  In more rounds the fragments' many loads set the pace: 16384 of
-  // 32 keys, 256 rows 232.8 -> 257.7, 128 rows 147.6 -> 157.5.  And so they do from two chunks on, whose waves share a compute unit: 32 of 512
-  // keys, 256 rows 30.2 -> 36.7.
-  const bool few = gs.waves == 1 && p.seq_len <= kMinChunkKeys && (int64_t)grid.x * grid.z <= 8192;
+  const bool few = few_keys(s, plan, gs) && (int64_t)grid.x * grid.z <= 8192;
   int rc = DAPQ_OK;
 #define DAPQ_LAUNCH_F(NRBV, UNITV, SHORTV)                                                                                     \
   do {                                                                                                                         \
