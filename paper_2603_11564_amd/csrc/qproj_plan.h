@@ -57,7 +57,7 @@ inline QprojPlan make_qproj_plan(const dapq_qproj& s) {
   // along the hidden axis as there is room for planes, but not more than eight, or single waves, of which a compute unit holds four or
   // five (their rings) and which take a block the faster the fewer they are.  The constants lose least over 826 calls (1 to 8 layers, 16 to
   // 256 rows, 1024 to 16384 wide, 8 to 64 heads of 128), each timed as single waves and as one to eight workgroups of four, weights out of
-  // memory: against the single waves 0.942 of the time in the geometric mean and 32 calls above 1.025, none above 1.10 (with 40 for a block of
+  // memory: against the single waves 0.942 of the time in the geometric mean and 36 calls above 1.025, none above 1.12 (with 40 for a block of
   // three single waves too, and a tenth on top of them for their planes: 0.949, 86 calls, up to 1.245; the best of all ways 0.923).  Calls,
   // us, single waves -> four: one layer 4096 wide, 256 rows 24.0 -> 20.9; 2 layers of 64 rows 22.8 -> 18.0; 8 layers 83.0 -> 66.8, of 16
   // rows 73.5 -> 55.7; 5120 wide, 64 rows 18.5 -> 16.5.  Single waves stay where three to each unit are a whole round: 3 layers of 8 heads, 5120
@@ -70,11 +70,17 @@ inline QprojPlan make_qproj_plan(const dapq_qproj& s) {
   if (shared <= 3) best += 33 * pl.kb_per_split + 150;
   else if (shared == 4) best += rounds * (45 * pl.kb_per_split + 60);
   else best += rounds * (55 * pl.kb_per_split + 130);
+  // (rows that a last sweep is short of are not fetched, which the workgroups of four gain by: one layer 4096 wide, 192 rows 23.7 us, 148 rows
+  // 21.3 out of memory and 18.3 with the weights in the caches; single waves 22.1, 21.7 and 19.4)
+  auto blocks_of_four = [&](int64_t each) {
+    const int64_t rows = (int64_t)pl.sweeps * 32 * pl.mb;
+    return 40 * each - (pl.sweeps > 1 ? 15 * each * (rows - s.rows) / rows : 0);
+  };
   const int most = pl.k_splits < 8 ? pl.k_splits : 8;
   for (int splits = 1; splits <= most; ++splits) {
     const int each = (n_kb + 4 * splits - 1) / (4 * splits);
     if ((int64_t)(splits - 1) * 4 * each >= n_kb) continue;  // (a workgroup without blocks)
-    const int64_t cost = (tiles * splits + units - 1) / units * (40 * (int64_t)each + (pl.mb == 2 ? 110 : 80)) + kPlane * splits;
+    const int64_t cost = (tiles * splits + units - 1) / units * (blocks_of_four(each) + (pl.mb == 2 ? 110 : 80)) + kPlane * splits;
     if (cost < best) {
       best = cost;
       pl.waves = 4;

@@ -2,8 +2,8 @@
 partial sums.  tests/test_qproj_plan.py holds the list to the planner; the GPU tests run the shapes."""
 SPLIT_SHAPES = {
     (3, 38, 72, 65, 1024): (1, 2),
-    (6, 9, 72, 65, 2112): (1, 4),
-    (4, 9, 72, 65, 5184): (1, 8),
+    (3, 38, 72, 65, 2048): (1, 4),
+    (8, 9, 72, 37, 5184): (1, 8),
     (6, 9, 72, 65, 1024): (4, 1),
     (4, 32, 128, 64, 1024): (4, 1),
     (1, 1, 64, 7, 1024): (4, 2),

@@ -30,10 +30,11 @@ int main(int argc, char**) {
     return 0;
   }
   long split = 0, wrong = 0;
-  for (int rows : {1, 16, 32, 33, 64, 65, 128, 129, 200, 256, 300})
+  for (int rows : {0, 1, 16, 32, 33, 64, 65, 128, 129, 148, 200, 256, 300})
     for (int blocks = 1; blocks <= 300; ++blocks)
       for (int tiles = 1; tiles <= 800; ++tiles) {
         const QprojPlan p = make_qproj_plan(describe(1, tiles, 64, rows, blocks * kBlockK));
+        if (rows == 0) continue;  // (nothing is launched)
         const long covered = (long)p.k_splits * p.waves * p.kb_per_split;
         const size_t plane = (size_t)p.sweeps * 32 * p.mb * p.tiles_f * 32 * p.ft * sizeof(float);
         bool ok = covered >= blocks;
