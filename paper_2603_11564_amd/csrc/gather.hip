@@ -2,9 +2,15 @@
 // discarded.  Copies the retained K and V rows, bit for bit, into the compact cache
 // [layer][sequence][KV head][slot][d].
 //
-// Pure copy: 16 lanes move one 256-byte row with one 16-byte load and store each, so every row is
-// read and written in full cache lines; a workgroup of 256 threads moves 64 rows of K or of V, four
-// per 16-lane group, with the four loads in flight together.
+// Pure copy, bound by memory: 16 lanes move one 256-byte row with one 16-byte load and store each, so every row is
+// read and written in full cache lines; a workgroup of 256 threads moves 32 rows of K or of V, two per 16-lane group.
+// Two rows to a group are enough in flight with eight workgroups to a compute unit, and leave the last workgroups of a launch less to do (four and
+// one: below).  From 8 MB on the stores carry the non-temporal hint: nobody reads the compact cache before the rest of it is
+// written, and lines that are not kept leave room for reads.  From 192 MB on, where the rows read can't still lie in the 256 MB
+// memory-side cache for a second call either, the loads do too; smaller calls find rows there that the score passes or the caller brought in.
+// Us, four rows to a group without hints -> two without, two with hinted stores, two with both (one with both), MB read and written:
+//   2 MB    2.37 -> 1.94, 1.94, 1.94 (1.98)       8   2.90 -> 2.54, 2.42, 2.75 (3.25)      32    6.6 -> 6.4, 5.9, 7.3 (7.7)
+//   129    27.9 -> 26.4, 21.3, 22.7 (23.2)      258  52.5 -> 51.1, 44.8, 42.5 (43.4)      515  104.9 -> 102.9, 92.8, 84.2 (87.3; 6.1 TB/s)
 #include "dapq_internal.h"
 #include "kernel_args.h"
 
@@ -25,13 +31,14 @@ struct GatherParams {
   float inv_kv_heads, inv_batch;
 };
 
-constexpr int kGatherRowsPerGroup = 4;  // rows in flight per 16-lane group
-constexpr int kGatherRowsPerBlock = 16 * kGatherRowsPerGroup;
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
+// ROWS: rows in flight per 16-lane group.  STREAM_IN, STREAM_OUT: loads and stores of rows carry the non-temporal hint.
+template <int ROWS, bool STREAM_IN, bool STREAM_OUT>
 __global__ __launch_bounds__(256) void gather_kernel(GatherParams p) {
   touch_args<sizeof(GatherParams)>();
   const int ch = threadIdx.x & 15;
-  const int slot0 = blockIdx.x * kGatherRowsPerBlock + (threadIdx.x >> 4);  // this group's slots: slot0 + 16*r
+  const int slot0 = blockIdx.x * (16 * ROWS) + (threadIdx.x >> 4);  // this group's slots: slot0 + 16*r
   const int head = (int)blockIdx.y;  // (layer * batch + seq) * Hkv + kv
   const bool is_v = blockIdx.z == 1;
   const int n = p.count[head];
@@ -53,23 +60,30 @@ __global__ __launch_bounds__(256) void gather_kernel(GatherParams p) {
   const int64_t stride_token = is_v ? p.v_stride_token : p.k_stride_token;
   uint16_t* dst = (is_v ? p.v_out : p.k_out) + (int64_t)head * p.budget * kHeadDim;
   const int32_t* idx = p.idx + (int64_t)head * p.budget;
-  // all index loads first, then all row loads, then the stores: four rows in flight per group
-  int j[kGatherRowsPerGroup];
+  // all index loads first, then all row loads, then the stores
+  int j[ROWS];
 #pragma unroll
-  for (int r = 0; r < kGatherRowsPerGroup; ++r) {
+  for (int r = 0; r < ROWS; ++r) {
     const int slot = slot0 + 16 * r;
     j[r] = slot < n ? idx[slot] : -1;
   }
-  uint4 row[kGatherRowsPerGroup];
+  u32x4 row[ROWS];
 #pragma unroll
-  for (int r = 0; r < kGatherRowsPerGroup; ++r) {
-    const bool ok = j[r] >= 0 && j[r] < L;  // never follow an index outside the sequence
-    row[r] = ok ? reinterpret_cast<const uint4*>(base + (start + j[r]) * stride_token)[ch] : make_uint4(0, 0, 0, 0);
+  for (int r = 0; r < ROWS; ++r) {
+    row[r] = u32x4{0, 0, 0, 0};
+    if (j[r] >= 0 && j[r] < L) {  // never follow an index outside the sequence
+      const u32x4* src = reinterpret_cast<const u32x4*>(base + (start + j[r]) * stride_token) + ch;
+      row[r] = STREAM_IN ? __builtin_nontemporal_load(src) : *src;
+    }
   }
 #pragma unroll
-  for (int r = 0; r < kGatherRowsPerGroup; ++r) {
+  for (int r = 0; r < ROWS; ++r) {
     const int slot = slot0 + 16 * r;
-    if (j[r] >= 0 && j[r] < L) reinterpret_cast<uint4*>(dst + (int64_t)slot * kHeadDim)[ch] = row[r];
+    if (j[r] >= 0 && j[r] < L) {
+      u32x4* out = reinterpret_cast<u32x4*>(dst + (int64_t)slot * kHeadDim) + ch;
+      if (STREAM_OUT) __builtin_nontemporal_store(row[r], out);
+      else *out = row[r];
+    }
   }
 }
 
@@ -110,7 +124,16 @@ extern "C" DAPQ_API int dapq_gather(const dapq_shape* shape, const void* k, cons
   p.batch = shape->batch;
   p.n_kv_heads = shape->n_kv_heads;
   p.budget = budget;
-  hipLaunchKernelGGL(gather_kernel, dim3((unsigned)((budget + kGatherRowsPerBlock - 1) / kGatherRowsPerBlock), (unsigned)heads, 2), dim3(256), 0,
+  // bytes read and written where every head keeps its whole budget (figures: above)
+  const int64_t moved = 2 * 2 * heads * budget * kHeadDim * (int64_t)sizeof(uint16_t);
+  auto kernel = moved >= ((int64_t)192 << 20) ? gather_kernel<2, true, true>
+                                              : (moved >= ((int64_t)8 << 20) ? gather_kernel<2, false, true> : gather_kernel<2, false, false>);
+  int rows = 32;  // of a workgroup
+  if (budget > 1 << 28) {  // (a launch holds fewer than 2^32 threads along an axis)
+    rows = 64;
+    kernel = gather_kernel<4, true, true>;
+  }
+  hipLaunchKernelGGL(kernel, dim3((unsigned)(((int64_t)budget + rows - 1) / rows), (unsigned)heads, 2), dim3(256), 0,
                      static_cast<hipStream_t>(stream), p);
   DAPQ_HIP_LAUNCH_CHECK("gather_kernel");
   return DAPQ_OK;

@@ -701,3 +701,36 @@ def test_short_heads_of_ragged_batches(H, lens, layers, pieces):
                 assert np.array_equal(P[l, h, head].astype(np.float64), want_p), (l, h, b)
                 assert counts[l, b, h] == len(want) and np.array_equal(got[l, b, h, :len(want)], want), (l, h, b)
                 assert (got[l, b, h, len(want):] == -7).all()
+
+
+# bytes moved around the lines of the non-temporal hints (8 MB: 128 heads of 64 rows; 192 MB: 3072 of 64), budgets around a workgroup's
+# 32 rows; heads that keep nothing, less than the budget, all of it
+@pytest.mark.parametrize("heads,budget", [(2, 1), (2, 33), (128, 63), (128, 64), (3072, 63), (3072, 64), (2049, 97)], ids=str)
+@pytest.mark.parametrize("ragged", [False, True])
+def test_gather_with_and_without_streaming_hints(heads, budget, ragged):
+    import paper_2603_11564_amd as D
+    announce(f"gather of {heads} heads, budget {budget}, ragged {ragged}")
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(heads + budget)
+    L, H = 130, 4
+    cu = torch.tensor([0, 101, L], dtype=torch.int32, device="cuda") if ragged else None
+    batch = 2 if ragged else 1
+    layers = (heads + H * batch - 1) // (H * batch)
+    # every layer reads the same keys and values (layer stride 0)
+    k = torch.randint(-32768, 32767, (H, L, 128), dtype=torch.int16, device="cuda", generator=gen)
+    v = torch.randint(-32768, 32767, (H, L, 128), dtype=torch.int16, device="cuda", generator=gen)
+    strides = (0, 0, L * 128, 128)
+    shape = D.make_shape(n_layers=layers, batch=batch, n_q_heads=H, n_kv_heads=H, n_pseudo=1, total_tokens=L, cu_seqlens=cu,
+                         k_strides=strides, v_strides=strides, scale=1.0)
+    lens = [101, L - 101] if ragged else [L]
+    idx = torch.stack([torch.randint(0, n, (layers, H, budget), dtype=torch.int32, device="cuda", generator=gen) for n in lens], 1)
+    count = torch.randint(0, budget + 1, (layers, batch, H), dtype=torch.int32, device="cuda", generator=gen)
+    count[0], count[-1] = budget, budget - 1
+    out = [torch.full((layers, batch, H, budget, 128), 77, dtype=torch.int16, device="cuda") for _ in range(2)]
+    D.dapq_gather(shape, k, v, idx, count, budget, out[0], out[1])
+    start = torch.tensor([0, 101], device="cuda")[:batch].view(1, batch, 1, 1)
+    kept = torch.arange(budget, device="cuda") < count[..., None]
+    for got, src in zip(out, (k, v)):
+        want = src[torch.arange(H, device="cuda").view(1, 1, H, 1), idx + start]
+        want[~kept] = 77  # slots past the count stay as they were
+        assert torch.equal(got, want)
