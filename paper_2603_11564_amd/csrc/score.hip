@@ -81,6 +81,7 @@ struct ScoreParams {
   int32_t chunk_shift;              // ragged batches and the tile form: log2(chunk_keys)
   int32_t stage_q;                  // tile form: the queries go through LDS too
   float inv_n_pseudo, inv_kv_heads, inv_rows_pad;
+  float stream_share;               // see KeyStream
 };
 
 
@@ -449,6 +450,9 @@ __device__ __forceinline__ void sub_dma_lane_offsets(unsigned (&voff)[4], int64_
 // the chunk or at or past its end) gets an empty descriptor: the eight transfers still count as vector
 // memory operations (the waits rely on a fixed number per sub-block) but fetch nothing and fill the
 // slot with zeros.
+// AUX: the transfers' cache policy.
+constexpr int kNonTemporal = 2;
+template <int AUX = 0>
 __device__ __forceinline__ void sub_dma(u32x4* slot, const uint16_t* kbase, int64_t stride_token, int key0, int nkeys, bool live,
                                         const unsigned (&voff)[4]) {
   const int64_t stride_b = stride_token * 2;
@@ -460,7 +464,7 @@ __device__ __forceinline__ void sub_dma(u32x4* slot, const uint16_t* kbase, int6
 #pragma unroll
   for (int i = 0; i < 8; ++i)
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)(slot + i * 64), 16,
-                                             (int)voff[i & 3], (int)((unsigned)(4 * i) * (unsigned)stride_b), 0, 0);
+                                             (int)voff[i & 3], (int)((unsigned)(4 * i) * (unsigned)stride_b), 0, AUX);
 }
 
 // Waits until the sub-block after the current one has landed: at most the transfers (8 operations each) of the NST - 1 newer
@@ -679,11 +683,20 @@ __device__ __forceinline__ void wave_load_frags(bf16x8 (&kf)[8], const u32x4* sl
   for (int s = 0; s < 8; ++s) kf[s] = lds_read16((unsigned)(uintptr_t)(lds_vec_ptr)slot + (unsigned)lds_chunk_index(n, 2 * s + h) * 16u, 0);
 }
 
+// Two waves fit a SIMD as soon as their registers are half of it or less, as up to four row blocks' are, and then the waves of workgroups of one,
+// two or three are put two to a SIMD while others have none.  Naming a register keeps a SIMD for every wave.
+template <int NRB>
+__device__ __forceinline__ void one_wave_per_simd() {
+  if (NRB <= 4) asm volatile("" ::: "a127");
+}
+
 // The keys a wave goes through, in the order in which they enter its ring: the sub-blocks of one chunk of a dense batch, or
 // (SEG) of a segment of a ragged one, sequence after sequence.  REV: from the last sub-block down.  The ring is filled ahead
 // across the sequences of a segment: while the wave changes to the queries of the next one, that one's first NST - 1
 // sub-blocks are on their way.
-template <bool REV, bool SEG, bool UNIT = SEG>
+// STREAM (see key_hints): the transfers carry the non-temporal hint, but for the last keys of a dense chunk in pass 1 (from `stream_to` on,
+// 128 MB of all chunks in flight), which the memory-side cache then still has when pass 2 starts there.
+template <bool REV, bool SEG, bool UNIT, bool STREAM>
 struct KeyStream {
   static constexpr bool kReversed = REV, kSegment = SEG, kUnitSums = UNIT;
   const ScoreParams& p;
@@ -691,13 +704,23 @@ struct KeyStream {
   const uint16_t* base;  // first key of the sequence (dense: of the chunk) that is being fetched
   int nkeys;             // its keys
   int sub, seq, left;    // SEG: the sub-block that is fetched next, of which sequence, and how many of the segment are to come
+  int stream_to;         // (STREAM, pass 1 of a chunk)
   __device__ __forceinline__ void enter(SeqRange r) {
     nkeys = uniform_i32(r.len);
     base = uniform_ptr(head + (int64_t)seq * p.k_stride_seq + (int64_t)r.start * p.k_stride_token);
   }
   // key0: the first key of the sub-block in its chunk (a segment counts them itself)
   __device__ __forceinline__ void fetch(u32x4* slot, const unsigned (&voff)[4], int key0) {
-    sub_dma(slot, base, p.k_stride_token, SEG ? sub * 32 : key0, nkeys, SEG ? left > 0 : (REV ? key0 >= 0 : key0 < nkeys), voff);
+    const int first = SEG ? sub * 32 : key0;
+    const bool live = SEG ? left > 0 : (REV ? key0 >= 0 : key0 < nkeys);
+    if constexpr (STREAM && (REV || SEG)) {
+      sub_dma<kNonTemporal>(slot, base, p.k_stride_token, first, nkeys, live, voff);
+    } else if constexpr (STREAM) {
+      if (key0 < stream_to) sub_dma<kNonTemporal>(slot, base, p.k_stride_token, first, nkeys, live, voff);
+      else sub_dma(slot, base, p.k_stride_token, first, nkeys, live, voff);
+    } else {
+      sub_dma(slot, base, p.k_stride_token, first, nkeys, live, voff);
+    }
     if constexpr (SEG) {
       sub += REV ? -1 : 1;
       left -= 1;
@@ -861,7 +884,7 @@ __device__ __forceinline__ const uint16_t* wave_q_base(const ScoreParams& p, int
 // Pass 1 of one chunk of a dense batch: `group` = row group, `chunk_id` = chunk along the packed key axis.  The chunk must have
 // keys.  FUSED (score_fused_kernel): the chunk's (reference, sum) pairs go to the start of the wave's own ring, which is
 // drained by then, instead of to global memory.  SHORT: the queries as fragments.
-template <int NRB, int NST, bool UNIT, bool FUSED = false, bool SHORT = false>
+template <int NRB, int NST, bool UNIT, bool STREAM, bool FUSED = false, bool SHORT = false>
 __device__ __forceinline__ void pass1_chunk(const ScoreParams& p, u32x4* ring, const Work& w, int chunk_id, int group, int head,
                                             bf16x8 (&qf)[NRB][8], int lane) {
   unsigned voff[4];
@@ -870,7 +893,8 @@ __device__ __forceinline__ void pass1_chunk(const ScoreParams& p, u32x4* ring, c
   const uint16_t* kbase = uniform_ptr(p.k + (int64_t)layer * p.k_stride_layer + (int64_t)w.seq * p.k_stride_seq +
                                       (int64_t)kv * p.k_stride_head + w.tok0 * p.k_stride_token);
   const int gbase = group * (NRB * 32);  // first row of this wave's row group
-  KeyStream<false, false, UNIT> keys = {p, nullptr, kbase, w.nkeys, 0, 0, 0};
+  KeyStream<false, false, UNIT, STREAM> keys = {p, nullptr, kbase, w.nkeys, 0, 0, 0,
+                                                STREAM ? uniform_i32((int)(p.stream_share * (float)w.nkeys)) : 0};
   constexpr bool kFrags = NRB == 2 || SHORT;
   if (kFrags) fill_ring<NST>(ring, keys, voff, 0);
   bf16x8 kf[8];
@@ -881,7 +905,7 @@ __device__ __forceinline__ void pass1_chunk(const ScoreParams& p, u32x4* ring, c
 }
 
 // Pass 1 of one segment of a ragged batch.
-template <int NRB, int NST>
+template <int NRB, int NST, bool STREAM>
 __device__ __forceinline__ void pass1_segment(const ScoreParams& p, u32x4* ring, int segment, int group, int head,
                                               bf16x8 (&qf)[NRB][8], int lane) {
   Segment at = segment_of_wave(p, segment, false);
@@ -890,8 +914,8 @@ __device__ __forceinline__ void pass1_segment(const ScoreParams& p, u32x4* ring,
   sub_dma_lane_offsets(voff, p.k_stride_token, lane);
   const int layer = uniform_i32(quotient(head, p.inv_kv_heads)), kv = head - layer * p.n_kv_heads;
   const int gbase = group * (NRB * 32);
-  KeyStream<false, true> keys = {p, uniform_ptr(p.k + (int64_t)layer * p.k_stride_layer + (int64_t)kv * p.k_stride_head),
-                                 nullptr, 0, at.sub, at.seq, at.left};
+  KeyStream<false, true, true, STREAM> keys = {
+      p, uniform_ptr(p.k + (int64_t)layer * p.k_stride_layer + (int64_t)kv * p.k_stride_head), nullptr, 0, at.sub, at.seq, at.left, 0};
   keys.enter(seq_range(p, at.seq));
   fill_ring<NST>(ring, keys, voff, 0);
   bf16x8 kf[8];
@@ -929,20 +953,21 @@ __device__ __forceinline__ WaveSlot wave_slot(const ScoreParams& p, int wave_id)
 
 // The grid names the items, one per wave: (chunk, row group, layer x KV head).  SEG (ragged batches, whose lengths
 // the host does not know): a segment of the packed key axis in the place of the chunk.  SHORT: see few_keys.
-template <int NRB, bool SEG, bool UNIT, bool SHORT, int NST>
+template <int NRB, bool SEG, bool UNIT, bool SHORT, bool STREAM, int NST>
 __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_wave_pass1_kernel(ScoreParams p) {
   extern __shared__ u32x4 rings[];
+  one_wave_per_simd<NRB>();
   const int wave_id = uniform_i32((int)(threadIdx.x >> 6));
   u32x4* ring = rings + wave_id * (wave_lds(NST) / 16);
   const int lane = threadIdx.x & 63;
   bf16x8 qf[NRB][8];
   const WaveSlot slot = wave_slot(p, wave_id);
   if constexpr (SEG) {
-    pass1_segment<NRB, NST>(p, ring, slot.chunk, slot.group, (int)blockIdx.z, qf, lane);
+    pass1_segment<NRB, NST, STREAM>(p, ring, slot.chunk, slot.group, (int)blockIdx.z, qf, lane);
   } else {
     const Work w = locate_uniform(p, slot.chunk);
     if (w.nkeys == 0) return;
-    pass1_chunk<NRB, NST, UNIT, false, SHORT>(p, ring, w, slot.chunk, slot.group, (int)blockIdx.z, qf, lane);
+    pass1_chunk<NRB, NST, UNIT, STREAM, false, SHORT>(p, ring, w, slot.chunk, slot.group, (int)blockIdx.z, qf, lane);
   }
 }
 
@@ -1008,7 +1033,7 @@ __device__ __forceinline__ float* wave_plane(const ScoreParams& p, int head, int
 
 // Pass 2 of one chunk of a dense batch (arguments as pass1_chunk).  FUSED (score_fused_kernel): the query fragments are still in
 // registers from pass 1 and the caller has filled off2.
-template <int NRB, int NST, bool SHORT, bool FUSED = false>
+template <int NRB, int NST, bool SHORT, bool STREAM, bool FUSED = false>
 __device__ __forceinline__ void pass2_chunk(const ScoreParams& p, u32x4* ring, const Work& w, int group, int head,
                                             bf16x8 (&qf)[NRB][8], float (&off2)[NRB][16], int lane) {
   unsigned voff[4];
@@ -1018,7 +1043,7 @@ __device__ __forceinline__ void pass2_chunk(const ScoreParams& p, u32x4* ring, c
                                       (int64_t)kv * p.k_stride_head + w.tok0 * p.k_stride_token);
   float* out = const_cast<float*>(uniform_ptr(wave_plane(p, head, group) + w.tok0));
   const int nsubs = (w.nkeys + 31) / 32;
-  KeyStream<true, false> keys = {p, nullptr, kbase, w.nkeys, 0, 0, 0};
+  KeyStream<true, false, false, STREAM> keys = {p, nullptr, kbase, w.nkeys, 0, 0, 0, 0};
   constexpr bool kFrags = NRB == 2 || SHORT;
   if (FUSED || kFrags) fill_ring<NST>(ring, keys, voff, nsubs - 1);
   bf16x8 kf[8];
@@ -1029,7 +1054,7 @@ __device__ __forceinline__ void pass2_chunk(const ScoreParams& p, u32x4* ring, c
 }
 
 // Pass 2 of one segment of a ragged batch, from its last sub-block to its first.
-template <int NRB, int NST>
+template <int NRB, int NST, bool STREAM>
 __device__ __forceinline__ void pass2_segment(const ScoreParams& p, u32x4* ring, int segment, int group, int head,
                                               bf16x8 (&qf)[NRB][8], float (&off2)[NRB][16], int lane) {
   Segment at = segment_of_wave(p, segment, true);
@@ -1037,8 +1062,8 @@ __device__ __forceinline__ void pass2_segment(const ScoreParams& p, u32x4* ring,
   unsigned voff[4];
   sub_dma_lane_offsets(voff, p.k_stride_token, lane);
   const int layer = uniform_i32(quotient(head, p.inv_kv_heads)), kv = head - layer * p.n_kv_heads;
-  KeyStream<true, true> keys = {p, uniform_ptr(p.k + (int64_t)layer * p.k_stride_layer + (int64_t)kv * p.k_stride_head),
-                                nullptr, 0, at.sub, at.seq, at.left};
+  KeyStream<true, true, true, STREAM> keys = {
+      p, uniform_ptr(p.k + (int64_t)layer * p.k_stride_layer + (int64_t)kv * p.k_stride_head), nullptr, 0, at.sub, at.seq, at.left, 0};
   keys.enter(seq_range(p, at.seq));
   fill_ring<NST>(ring, keys, voff, 0);
   bf16x8 kf[8];
@@ -1065,9 +1090,10 @@ __device__ __forceinline__ void pass2_segment(const ScoreParams& p, u32x4* ring,
 // (SEG as in pass 1.)  Heads and, inside a chunk or segment, the keys are walked in the opposite order to pass 1: what pass 1
 // read last (the ends of the chunks in flight, the heads of the last round) is still in the 256 MB memory-side cache
 // when pass 2 starts.
-template <int NRB, bool SEG, bool SHORT, int NST>
+template <int NRB, bool SEG, bool SHORT, bool STREAM, int NST>
 __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_wave_pass2_kernel(ScoreParams p) {
   extern __shared__ u32x4 rings[];
+  one_wave_per_simd<NRB>();
   const int wave_id = uniform_i32((int)(threadIdx.x >> 6));
   u32x4* ring = rings + wave_id * (wave_lds(NST) / 16);
   const int lane = threadIdx.x & 63;
@@ -1076,11 +1102,11 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_wave_pass2_kerne
   const WaveSlot slot = wave_slot(p, wave_id);
   const int head = (int)(gridDim.z - 1 - blockIdx.z);
   if constexpr (SEG) {
-    pass2_segment<NRB, NST>(p, ring, slot.chunk, slot.group, head, qf, off2, lane);
+    pass2_segment<NRB, NST, STREAM>(p, ring, slot.chunk, slot.group, head, qf, off2, lane);
   } else {
     const Work w = locate_uniform(p, slot.chunk);
     if (w.nkeys == 0) return;
-    pass2_chunk<NRB, NST, SHORT>(p, ring, w, slot.group, head, qf, off2, lane);
+    pass2_chunk<NRB, NST, SHORT, STREAM>(p, ring, w, slot.group, head, qf, off2, lane);
   }
 }
 
@@ -1093,9 +1119,10 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_wave_pass2_kerne
 // which every wave of the chip waits for the slowest, the combine kernel, the second placement of the workgroups and
 // the second read of the queries.  lse2 is not written anywhere.
 // SHORT: see few_keys.
-template <int NRB, bool UNIT, bool SHORT, int NST>
+template <int NRB, bool UNIT, bool SHORT, bool STREAM, int NST>
 __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_fused_kernel(ScoreParams p) {
   extern __shared__ u32x4 rings[];
+  one_wave_per_simd<NRB>();
   const int wave_id = uniform_i32((int)(threadIdx.x >> 6)), waves = (int)(blockDim.x >> 6);
   u32x4* ring = rings + wave_id * (wave_lds(NST) / 16);
   const int lane = threadIdx.x & 63, h = lane >> 5;
@@ -1103,7 +1130,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_fused_kernel(Sco
   const int chunk = uniform_i32((int)blockIdx.x * waves + wave_id);  // blockIdx.x is the sequence
   const int head = (int)blockIdx.z;
   const Work work = locate_uniform(p, chunk);
-  pass1_chunk<NRB, NST, UNIT, true, SHORT>(p, ring, work, chunk, 0, head, qf, lane);
+  pass1_chunk<NRB, NST, UNIT, STREAM, true, SHORT>(p, ring, work, chunk, 0, head, qf, lane);
   __syncthreads();
   // lse2 of rows lane, lane + 64, ...: every wave merges all chunks itself
   constexpr int kRowsPerLane = (NRB * 32 + 63) / 64;  // (an odd number of row blocks: the last rows are no one's)
@@ -1142,7 +1169,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_fused_kernel(Sco
       off2[rb][4 * b + 3] = v.w;
     }
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // off2 is out of the ring before pass 2 refills it
-  pass2_chunk<NRB, NST, false, true>(p, ring, work, 0, head, qf, off2, lane);
+  pass2_chunk<NRB, NST, false, STREAM, true>(p, ring, work, 0, head, qf, off2, lane);
 }
 
 // The causal block of the pseudo tokens' own keys (Sec. 4.1: they are prefilled in-sequence): a wave scores one block of 32 query rows
@@ -1664,6 +1691,32 @@ GroupShape group_shape(const dapq_shape* s, const ScorePlan& plan) {
   return {groups * chunks, groups};
 }
 
+// Whether the keys of a call stream: the transfers of the wave kernels carry the non-temporal hint.  Keys that the caches cannot hold until pass
+// 2 reads them again are kept there to no one's use, and what they push out costs the stream more than the hint does: up to 128 rows, where the
+// stream sets the pace, the passes gain a tenth, and the power that the caches do not take is worth 1 to 2 % to the others.  `reuse`: bytes of
+// keys between a key's two reads (one kernel: those of the workgroups that run at a time; else all).  Without hints -> with, us, dapq_score
+// of 8 KV heads a layer:
+//   64 rows, MB of keys   134 64.4 -> 63.7    268 98.5 -> 98.6    403 144.9 -> 139.2    537 177.9 -> 162.9    786 274 -> 244    2147 730 -> 664
+//   128 rows              134 64.6 -> 65.0    268 108.5 -> 110.8  403 161.2 -> 158.4    537 191.9 -> 183.8    786 282 -> 268    2147 767 -> 735
+//   192 and 256 rows      403 to 1074 0.98 to 1.02 of the time; 2147 931 -> 932 and 1139 -> 1118
+//   ragged, 128 rows      374 158.9 -> 158.0  572 234.7 -> 216.6  791 335.6 -> 303.2    2998 1161 -> 1054 (256 rows 374 1.01, 791 0.96, 2998 1.00)
+//   one kernel, 32 layers, 64 rows: 64 prompts of 512 keys (134 MB at a time) 620 -> 714, 32 of 1024 (268 MB) 637 -> 700, 8 of 2048 (537 MB)
+//   363 -> 342; 128 rows 757 -> 840, 763 -> 806, 378 -> 371
+// Not so several row groups, whose waves find each other's keys in L2: 512 rows, 8 prompts of 4096..16384 keys 5321 -> 5625.
+struct KeyHints {
+  bool on;
+  float share;  // of a chunk that streams in pass 1 (see KeyStream)
+};
+KeyHints key_hints(const dapq_shape* s, const ScorePlan& plan, bool one_kernel) {
+  if (plan.tile || plan.n_groups > 1) return {false, 0.0f};
+  const double all = (double)s->n_layers * s->n_kv_heads * (double)s->total_tokens * (kHeadDim * 2);
+  const int64_t mean = s->total_tokens / s->batch, wave_keys = mean < plan.chunk_keys ? mean : plan.chunk_keys;
+  const double at_once = (double)simd_count() * (double)wave_keys * (kHeadDim * 2), reuse = one_kernel && at_once < all ? at_once : all;
+  const bool on = reuse >= (plan.row_blocks <= 4 ? 384e6 : (plan.segments > 0 ? 768e6 : 1536e6));
+  constexpr double kKept = 128e6;  // half the memory-side cache
+  return {on, reuse > kKept ? (float)(1.0 - kKept / reuse) : 0.0f};
+}
+
 int fill_params(const dapq_shape* s, const ScorePlan& plan, ScoreParams* p) {
   p->cu_seqlens = s->cu_seqlens;
   p->k_stride_layer = s->k_stride_layer; p->k_stride_seq = s->k_stride_seq;
@@ -1686,6 +1739,7 @@ int fill_params(const dapq_shape* s, const ScorePlan& plan, ScoreParams* p) {
   p->inv_n_pseudo = 1.0f / (float)s->n_pseudo;
   p->inv_kv_heads = 1.0f / (float)s->n_kv_heads;
   p->inv_rows_pad = 1.0f / (float)plan.rows_pad;
+  p->stream_share = 0.0f;
   return DAPQ_OK;
 }
 
@@ -1765,20 +1819,26 @@ int launch_wave_pass1(const dapq_shape* s, const ScorePlan& plan, ScoreParams p,
   const GroupShape gs = group_shape(s, plan);
   p.wg_groups = gs.groups;
   const bool few = few_keys(s, plan, gs);
-#define DAPQ_LAUNCH_W1(NRBV, SEGV, UNITV, SHORTV)                                                                        \
+  const KeyHints key = key_hints(s, plan, false);
+  const bool hints = key.on;
+  p.stream_share = key.share;
+#define DAPQ_LAUNCH_W1(NRBV, SEGV, UNITV, SHORTV, STREAMV)                                                               \
   do {                                                                                                                   \
-    if ((rc = set_lds(score_wave_pass1_kernel<NRBV, SEGV, UNITV, SHORTV, kWaveStages>,                                   \
+    if ((rc = set_lds(score_wave_pass1_kernel<NRBV, SEGV, UNITV, SHORTV, STREAMV, kWaveStages>,                          \
                       kWavesPerGroup * wave_lds(kWaveStages))) != DAPQ_OK)                                               \
       return rc;                                                                                                         \
-    hipLaunchKernelGGL((score_wave_pass1_kernel<NRBV, SEGV, UNITV, SHORTV, kWaveStages>), gs.grid(plan, s),              \
+    hipLaunchKernelGGL((score_wave_pass1_kernel<NRBV, SEGV, UNITV, SHORTV, STREAMV, kWaveStages>), gs.grid(plan, s),     \
                        dim3(64 * gs.waves), gs.waves * wave_lds(kWaveStages), stream, p);                                \
   } while (0)
-#define DAPQ_LAUNCH_W1_KEYS(NRBV)                                               \
-  do {                                                                          \
-    if (plan.segments > 0) DAPQ_LAUNCH_W1(NRBV, true, true, false);             \
-    else if (plan.unit_sums) DAPQ_LAUNCH_W1(NRBV, false, true, false);          \
-    else if (few && NRBV > 2) DAPQ_LAUNCH_W1(NRBV, false, false, (NRBV > 2));   \
-    else DAPQ_LAUNCH_W1(NRBV, false, false, false);                             \
+#define DAPQ_LAUNCH_W1_KEYS(NRBV)                                                      \
+  do {                                                                                 \
+    if (plan.segments > 0 && hints) DAPQ_LAUNCH_W1(NRBV, true, true, false, true);     \
+    else if (plan.segments > 0) DAPQ_LAUNCH_W1(NRBV, true, true, false, false);        \
+    else if (plan.unit_sums && hints) DAPQ_LAUNCH_W1(NRBV, false, true, false, true);  \
+    else if (plan.unit_sums) DAPQ_LAUNCH_W1(NRBV, false, true, false, false);          \
+    else if (few && NRBV > 2) DAPQ_LAUNCH_W1(NRBV, false, false, (NRBV > 2), false);   \
+    else if (hints) DAPQ_LAUNCH_W1(NRBV, false, false, false, true);                   \
+    else DAPQ_LAUNCH_W1(NRBV, false, false, false, false);                             \
   } while (0)
   DAPQ_BY_ROW_BLOCKS(plan.row_blocks, DAPQ_LAUNCH_W1_KEYS);
 #undef DAPQ_LAUNCH_W1_KEYS
@@ -1828,20 +1888,22 @@ int launch_accumulate(const dapq_shape* s, const ScorePlan& plan, ScoreParams p,
   }
   const GroupShape gs = group_shape(s, plan);
   p.wg_groups = gs.groups;
-  const bool few = few_keys(s, plan, gs);
-#define DAPQ_LAUNCH_W2(NRBV, SEGV, SHORTV)                                                                                  \
-  do {                                                                                                                      \
-    if ((rc = set_lds(score_wave_pass2_kernel<NRBV, SEGV, SHORTV, kWaveStages>, kWavesPerGroup * wave_lds(kWaveStages))) != \
-        DAPQ_OK)                                                                                                            \
-      return rc;                                                                                                            \
-    hipLaunchKernelGGL((score_wave_pass2_kernel<NRBV, SEGV, SHORTV, kWaveStages>), gs.grid(plan, s), dim3(64 * gs.waves),   \
-                       gs.waves * wave_lds(kWaveStages), stream, p);                                                        \
+  const bool few = few_keys(s, plan, gs), hints = key_hints(s, plan, false).on;
+#define DAPQ_LAUNCH_W2(NRBV, SEGV, SHORTV, STREAMV)                                                                       \
+  do {                                                                                                                    \
+    if ((rc = set_lds(score_wave_pass2_kernel<NRBV, SEGV, SHORTV, STREAMV, kWaveStages>,                                  \
+                      kWavesPerGroup * wave_lds(kWaveStages))) != DAPQ_OK)                                                \
+      return rc;                                                                                                          \
+    hipLaunchKernelGGL((score_wave_pass2_kernel<NRBV, SEGV, SHORTV, STREAMV, kWaveStages>), gs.grid(plan, s),             \
+                       dim3(64 * gs.waves), gs.waves * wave_lds(kWaveStages), stream, p);                                 \
   } while (0)
-#define DAPQ_LAUNCH_W2_KEYS(NRBV)                                       \
-  do {                                                                  \
-    if (plan.segments > 0) DAPQ_LAUNCH_W2(NRBV, true, false);           \
-    else if (few && NRBV > 2) DAPQ_LAUNCH_W2(NRBV, false, (NRBV > 2));  \
-    else DAPQ_LAUNCH_W2(NRBV, false, false);                            \
+#define DAPQ_LAUNCH_W2_KEYS(NRBV)                                               \
+  do {                                                                          \
+    if (plan.segments > 0 && hints) DAPQ_LAUNCH_W2(NRBV, true, false, true);    \
+    else if (plan.segments > 0) DAPQ_LAUNCH_W2(NRBV, true, false, false);       \
+    else if (few && NRBV > 2) DAPQ_LAUNCH_W2(NRBV, false, (NRBV > 2), false);   \
+    else if (hints) DAPQ_LAUNCH_W2(NRBV, false, false, true);                   \
+    else DAPQ_LAUNCH_W2(NRBV, false, false, false);                             \
   } while (0)
   DAPQ_BY_ROW_BLOCKS(plan.row_blocks, DAPQ_LAUNCH_W2_KEYS);
 #undef DAPQ_LAUNCH_W2_KEYS
@@ -1874,19 +1936,25 @@ int launch_fused(const dapq_shape* s, const ScorePlan& plan, ScoreParams p, hipS
   p.wg_groups = 1;
   const dim3 grid((unsigned)s->batch, 1u, (unsigned)(s->n_layers * s->n_kv_heads));
   const bool few = few_keys(s, plan, gs) && (int64_t)grid.x * grid.z <= 8192;
+  const KeyHints key = key_hints(s, plan, true);
+  const bool hints = key.on;
+  p.stream_share = key.share;
   int rc = DAPQ_OK;
-#define DAPQ_LAUNCH_F(NRBV, UNITV, SHORTV)                                                                                     \
-  do {                                                                                                                         \
-    if ((rc = set_lds(score_fused_kernel<NRBV, UNITV, SHORTV, kWaveStages>, kWavesPerGroup * wave_lds(kWaveStages))) != DAPQ_OK) \
-      return rc;                                                                                                               \
-    hipLaunchKernelGGL((score_fused_kernel<NRBV, UNITV, SHORTV, kWaveStages>), grid, dim3(64 * gs.waves),                      \
-                       gs.waves * wave_lds(kWaveStages), stream, p);                                                           \
+#define DAPQ_LAUNCH_F(NRBV, UNITV, SHORTV, STREAMV)                                                                         \
+  do {                                                                                                                      \
+    if ((rc = set_lds(score_fused_kernel<NRBV, UNITV, SHORTV, STREAMV, kWaveStages>,                                        \
+                      kWavesPerGroup * wave_lds(kWaveStages))) != DAPQ_OK)                                                  \
+      return rc;                                                                                                            \
+    hipLaunchKernelGGL((score_fused_kernel<NRBV, UNITV, SHORTV, STREAMV, kWaveStages>), grid, dim3(64 * gs.waves),          \
+                       gs.waves * wave_lds(kWaveStages), stream, p);                                                        \
   } while (0)
-#define DAPQ_LAUNCH_F_FORM(NRBV)                                       \
-  do {                                                                 \
-    if (plan.unit_sums) DAPQ_LAUNCH_F(NRBV, true, false);              \
-    else if (few && NRBV > 2) DAPQ_LAUNCH_F(NRBV, false, (NRBV > 2));  \
-    else DAPQ_LAUNCH_F(NRBV, false, false);                            \
+#define DAPQ_LAUNCH_F_FORM(NRBV)                                              \
+  do {                                                                        \
+    if (plan.unit_sums && hints) DAPQ_LAUNCH_F(NRBV, true, false, true);      \
+    else if (plan.unit_sums) DAPQ_LAUNCH_F(NRBV, true, false, false);         \
+    else if (few && NRBV > 2) DAPQ_LAUNCH_F(NRBV, false, (NRBV > 2), false);  \
+    else if (hints) DAPQ_LAUNCH_F(NRBV, false, false, true);                  \
+    else DAPQ_LAUNCH_F(NRBV, false, false, false);                            \
   } while (0)
   DAPQ_BY_ROW_BLOCKS(plan.row_blocks, DAPQ_LAUNCH_F_FORM);
 #undef DAPQ_LAUNCH_F_FORM

@@ -617,6 +617,32 @@ def test_row_blocks_of_a_wave(H, rows, lens, layers, ragged):
     H.assert_scores_close(X[:1].cpu().numpy(), O.score(q, k, 1, cu, None, kp), f"extended, rows={rows}")
 
 
+# more keys than the caches hold until pass 2 (of up to four row blocks 384 MB, of more 1536 MB of a dense and 768 MB of a ragged batch): what
+# pass 1 leaves in the caches starts inside a chunk, whose last sub-block is partial; two to eight row blocks
+@pytest.mark.parametrize("lens,layers,ragged", [([24101], 256, False), ([61003], 101, False), ([9000, 0, 33, 15000, 70], 256, True)],
+                         ids=["one kernel", "launches", "segments"])
+@pytest.mark.parametrize("rows", [40, 96, 128, 160, 200, 224, 256])
+def test_keys_that_stream(H, rows, lens, layers, ragged):
+    """Every layer is the same problem (layer strides of 0): the oracle's scores within 1e-3, the same bits in every layer and from the
+    two separate entry points."""
+    announce(f"streamed keys: rows={rows} {lens}")
+    assert layers * sum(lens) * 256 >= 1536e6
+    q, k, v, cu = problem_bits(rows, 1, lens, 1, 1, rows)
+    prob = H.Problem(q, k, v, 1, cu if ragged else None, "thd")
+    tokens = int(cu[-1])
+    shape = H.D.make_shape(n_layers=layers, batch=len(lens), n_q_heads=1, n_kv_heads=1, n_pseudo=rows, total_tokens=tokens,
+                           cu_seqlens=prob.cu, k_strides=(0, 0, 128, 128), q_strides=(0, rows * 128, rows * 128, 128), scale=128 ** -0.5)
+    assert H.D.score_single_launch(shape) == (layers == 256 and not ragged)
+    ws = torch.full((H.D.workspace_bytes(shape),), 0xA5, dtype=torch.uint8, device="cuda")
+    S, T = (torch.full((layers, 1, tokens), float("nan"), dtype=torch.float32, device="cuda") for _ in range(2))
+    lse = torch.full((layers, len(lens), 1, rows), float("nan"), dtype=torch.float32, device="cuda")
+    H.D.dapq_score(shape, prob.q, prob.k, S, ws)
+    H.D.dapq_score_stats(shape, prob.q, prob.k, lse, ws)
+    H.D.dapq_score_accumulate(shape, prob.q, prob.k, lse, T, ws)
+    assert torch.equal(S, T) and torch.equal(S, S[:1].expand_as(S))
+    H.assert_scores_close(S[:1].cpu().numpy(), O.score(q, k, 1, cu), f"rows={rows}")
+
+
 def selection_call(H, S, batch, width, budget, pieces):
     """dapq_pool_topk over scores [layers][heads][batch * length]: positions, counts and pooled scores on the host."""
     layers, heads, tokens = S.shape
