@@ -91,7 +91,8 @@ __device__ __forceinline__ void qp_wait_vm() {
 
 // WAVES > 1: that many waves, each with a ring of its own and kb_per_split hidden blocks, add their sums up through LDS and write one
 // plane of partial sums.
-template <int FT, int MB, int WAVES>
+// STREAM: the weights carry the non-temporal hint.
+template <int FT, int MB, int WAVES, bool STREAM>
 __global__ __launch_bounds__(64 * WAVES) void qproj_wave_kernel(QprojParams p) {
   constexpr int NXB = XBuffers<FT>::value;
   constexpr int XT = 4 * MB;       // 1 KB transfers per x block
@@ -170,7 +171,7 @@ __global__ __launch_bounds__(64 * WAVES) void qproj_wave_kernel(QprojParams p) {
     for (int i = 0; i < 4; ++i)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (__attribute__((address_space(3))) void*)(slot + i * 64), 16,
                                                (int)voff_w[i & 1], (int)((unsigned)(8 * i) * w_stride_b + (unsigned)kb * 128u),
-                                               0, 0);
+                                               0, STREAM ? 2 : 0);
     u32x4* const xb = xbuf + ((kb + 1) % NXB) * (MB * kTileVec);
 #pragma unroll
     for (int i = T * XQ; i < (T + 1) * XQ; ++i)
@@ -386,17 +387,26 @@ __global__ __launch_bounds__(256) void qproj_reduce_rope_kernel(QprojParams p, i
   dst[ib] = f64_to_bf16(xb * cs + xa * sn);
 }
 
-template <int FT, int MB, int WAVES>
-int launch_qproj(const QprojParams& p, hipStream_t stream) {
+template <int FT, int MB, int WAVES, bool STREAM>
+int launch_qproj_as(const QprojParams& p, hipStream_t stream) {
   constexpr int kBytes = WAVES > 1 ? WAVES * QprojLds<FT, MB>::bytes : 0;
   if (kBytes > 64 * 1024) {
-    const int rc = set_max_dynamic_lds(reinterpret_cast<const void*>(qproj_wave_kernel<FT, MB, WAVES>), kBytes);
+    const int rc = set_max_dynamic_lds(reinterpret_cast<const void*>(qproj_wave_kernel<FT, MB, WAVES, STREAM>), kBytes);
     if (rc != DAPQ_OK) return rc;
   }
   const int64_t grid = (int64_t)p.tiles_f * p.sweeps * p.k_splits * p.n_layers;
-  hipLaunchKernelGGL((qproj_wave_kernel<FT, MB, WAVES>), dim3((unsigned)grid), dim3(64 * WAVES), kBytes, stream, p);
+  hipLaunchKernelGGL((qproj_wave_kernel<FT, MB, WAVES, STREAM>), dim3((unsigned)grid), dim3(64 * WAVES), kBytes, stream, p);
   DAPQ_HIP_LAUNCH_CHECK("qproj_wave_kernel");
   return DAPQ_OK;
+}
+
+// Weights of 96 MB and more that one sweep of rows reads stream past the caches; less than that a caller whose weights come round finds in the
+// memory-side cache, and further sweeps find them in L2.  Us without -> with hints, 64 rows: one layer 4096 wide (34 MB) 12.1 -> 13.3; 2 (67 MB)
+// 16.5 -> 18.2; 2 of 5120 (105 MB) 30.8 -> 29.6; 4 of 4096 33.0 -> 30.1; 8 62.5 -> 57.1; 32 200 -> 174 (6.2 TB/s); 256 rows, 8 of 5120 239 -> 279.
+template <int FT, int MB, int WAVES>
+int launch_qproj(const QprojParams& p, hipStream_t stream) {
+  const double weights = 2.0 * p.n_layers * p.n_features * p.hidden;
+  return p.sweeps == 1 && weights >= 96e6 ? launch_qproj_as<FT, MB, WAVES, true>(p, stream) : launch_qproj_as<FT, MB, WAVES, false>(p, stream);
 }
 
 int check_qproj(const dapq_qproj* desc) {

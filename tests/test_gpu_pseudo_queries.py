@@ -298,3 +298,13 @@ def test_queries_feed_the_score_path(H):
     S_want = O.score(q_want[None, None], k_bits, Hkv)
     assert np.isfinite(S).all()
     assert (np.abs(S - S_want) <= 5e-3 * np.abs(S_want)).all()
+
+
+# 96 MB of weights, which one sweep of up to 64 rows reads; waves of two and of four feature tiles, of one and of two row blocks
+@pytest.mark.parametrize("layers,hidden,rows", [(11, 4096, 64), (12, 4096, 64), (12, 4096, 20), (12, 4096, 65), (96, 512, 64), (96, 512, 20)])
+def test_weights_that_stream(H, layers, hidden, rows):
+    announce(f"streamed weights: {layers} layers, hidden {hidden}, {rows} rows")
+    rng = np.random.default_rng(layers + rows)
+    tok = rng.integers(0, 70, rows)
+    got, x, w = run_case(H, layers, layers, 70, hidden, 8, 128, tok)
+    assert check_projection(got, x, w, tok, 8, hidden) > 0.98
