@@ -66,33 +66,36 @@ struct DecodeSource {
   __amdgpu_buffer_rsrc_t k, v;
   unsigned k_off[4], v_off;
 };
+// AUX: cache policy of the loads.
+constexpr int kNonTemporal = 2;
 // One wave moves a tile of K_c into an LDS slot, 1 KB (4 rows) per transfer, rows 256 B apart, the 16-byte chunks of a row
 // XOR-swizzled by the row so that the operand reads are free of bank conflicts.
+template <int AUX>
 __device__ __forceinline__ void load_k(char* slot, const DecodeSource& src, int row0) {
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     const unsigned off = src.k_off[i & 3] + (unsigned)(row0 + 16 * (i >> 2)) * kHeadDim * 2;
     __builtin_amdgcn_raw_ptr_buffer_load_lds(src.k, (__attribute__((address_space(3))) void*)(slot + i * 1024), 16, (int)off, 0,
-                                             0, 0);
+                                             0, AUX);
   }
 }
 // A tile of a slice of V_c as it sits in the registers of lane 16 * kg + n: v[e] = channels CPL * n .. + CPL of the slice of
 // row 16 * (e / 4) + 4 * kg + e % 4.
-template <int CPL>
+template <int CPL, int AUX>
 __device__ __forceinline__ void load_v(unsigned (&v)[8][CPL / 2], const DecodeSource& src, int row0) {
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     const unsigned off = src.v_off + (unsigned)(row0 + 16 * (e >> 2)) * kHeadDim * 2 + (e & 3) * kHeadDim * 2;
     if constexpr (CPL == 8) {
-      const u32x4 u = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(src.v, (int)off, 0, 0));
+      const u32x4 u = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(src.v, (int)off, 0, AUX));
 #pragma unroll
       for (int i = 0; i < 4; ++i) v[e][i] = u[i];
     } else if constexpr (CPL == 4) {
-      const u32x2 u = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(src.v, (int)off, 0, 0));
+      const u32x2 u = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(src.v, (int)off, 0, AUX));
       v[e][0] = u[0];
       v[e][1] = u[1];
     } else {
-      v[e][0] = __builtin_bit_cast(unsigned, __builtin_amdgcn_raw_buffer_load_b32(src.v, (int)off, 0, 0));
+      v[e][0] = __builtin_bit_cast(unsigned, __builtin_amdgcn_raw_buffer_load_b32(src.v, (int)off, 0, AUX));
     }
   }
 }
@@ -104,9 +107,11 @@ __device__ __forceinline__ void keep_order() {
 }
 
 // HT tiles of 4 query heads per sweep over the cache, CPL channels per lane (16 * CPL of the 128 per workgroup).
-template <int HT, int CPL, int WAVES>
+// STREAM: the caches of all heads are more than the chip's caches keep until the next step, and their loads carry the non-temporal hint.
+template <int HT, int CPL, int WAVES, bool STREAM>
 __global__ __launch_bounds__(64 * WAVES, 2) void decode_attention_kernel(DecodeParams p) {
   extern __shared__ char lds[];  // [waves]: kDecodeSlots tiles of K_c, the queries; at the end weighted sums, references, sums of weights
+  constexpr int kAux = STREAM ? kNonTemporal : 0;
   constexpr int kHeads = 4 * HT, kChannels = 16 * CPL, kSlices = kHeadDim / kChannels, kThreads = 64 * WAVES;
   static_assert((kDecodeParts * kHeads * kChannels + 2 * kHeads) * 4 <= kDecodeSlots * kDecodeSlotBytes,
                 "what a wave leaves at the end fits where its tiles were");
@@ -150,10 +155,10 @@ __global__ __launch_bounds__(64 * WAVES, 2) void decode_attention_kernel(DecodeP
     // the first tiles are on their way before the row count is known (rows past the count are inside the cache all the same)
     unsigned vt[8][CPL / 2];
     auto first_loads = [&]() {
-      load_k(ring, src, row_of(wave));
-      load_k(ring + kDecodeSlotBytes, src, row_of(wave + WAVES));
+      load_k<kAux>(ring, src, row_of(wave));
+      load_k<kAux>(ring + kDecodeSlotBytes, src, row_of(wave + WAVES));
       keep_order();
-      load_v<CPL>(vt, src, row_of(wave));
+      load_v<CPL, kAux>(vt, src, row_of(wave));
       keep_order();
     };
     first_loads();
@@ -218,7 +223,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void decode_attention_kernel(DecodeP
         }
       }
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the tile is out of its slot before that is refilled
-      load_k(ring + slot * kDecodeSlotBytes, src, i + 2 * WAVES < tiles ? row_of(i + 2 * WAVES) : kDecodeMaxRows);
+      load_k<kAux>(ring + slot * kDecodeSlotBytes, src, i + 2 * WAVES < tiles ? row_of(i + 2 * WAVES) : kDecodeMaxRows);
       slot ^= 1;
       keep_order();
       u32x4 pa[HT];  // the weights as A operand
@@ -279,7 +284,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void decode_attention_kernel(DecodeP
           acc[t][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, pa[t]), __builtin_bit_cast(bf16x8, vb),
                                                              acc[t][j], 0, 0, 0);
       }
-      load_v<CPL>(vt, src, i + WAVES < tiles ? row_of(i + WAVES) : kDecodeMaxRows);  // (past the end: fetches nothing)
+      load_v<CPL, kAux>(vt, src, i + WAVES < tiles ? row_of(i + WAVES) : kDecodeMaxRows);  // (past the end: fetches nothing)
       keep_order();
     }
 
@@ -327,10 +332,10 @@ __global__ __launch_bounds__(64 * WAVES, 2) void decode_attention_kernel(DecodeP
   }
 }
 
-template <int HT, int CPL, int WAVES>
+template <int HT, int CPL, int WAVES, bool STREAM>
 int launch_decode(int64_t heads, const DecodeParams& p, hipStream_t stream) {
   constexpr int kBytes = WAVES * decode_wave_bytes(HT);
-  const int rc = set_max_dynamic_lds(reinterpret_cast<const void*>(decode_attention_kernel<HT, CPL, WAVES>), kBytes);
+  const int rc = set_max_dynamic_lds(reinterpret_cast<const void*>(decode_attention_kernel<HT, CPL, WAVES, STREAM>), kBytes);
   if (rc != DAPQ_OK) return rc;
   // a launch holds fewer than 2^32 threads along an axis: 2^24 heads and more go in several
   constexpr int64_t kMostHeads = (int64_t)1 << 22;
@@ -342,7 +347,7 @@ int launch_decode(int64_t heads, const DecodeParams& p, hipStream_t stream) {
     part.v_cache += first * cache_step;
     part.count += first;
     part.out += first * q_step;
-    hipLaunchKernelGGL((decode_attention_kernel<HT, CPL, WAVES>),
+    hipLaunchKernelGGL((decode_attention_kernel<HT, CPL, WAVES, STREAM>),
                        dim3((unsigned)(heads - first < kMostHeads ? heads - first : kMostHeads), kHeadDim / (16 * CPL)),
                        dim3(64 * WAVES), kBytes, stream, part);
     DAPQ_HIP_LAUNCH_CHECK("decode_attention_kernel");
@@ -365,9 +370,13 @@ int launch_decode(int64_t heads, const DecodeParams& p, hipStream_t stream) {
 template <int HT>
 int launch_decode_slices(int64_t heads, const DecodeParams& p, hipStream_t stream) {
   const int64_t rows = heads * p.budget;
-  if (heads <= 64 && (rows <= 88 * 1024 || heads <= 24)) return launch_decode<HT, 2, 8>(heads, p, stream);
-  if (heads <= 128 && (HT == 1 ? rows <= 112 * 1024 || heads <= 48 : heads * rows <= 11 << 20 || heads <= 64)) return launch_decode<HT, 4, 8>(heads, p, stream);
-  return launch_decode<HT, 8, 4>(heads, p, stream);
+  if (heads <= 64 && (rows <= 88 * 1024 || heads <= 24)) return launch_decode<HT, 2, 8, false>(heads, p, stream);
+  if (heads <= 128 && (HT == 1 ? rows <= 112 * 1024 || heads <= 48 : heads * rows <= 11 << 20 || heads <= 64)) return launch_decode<HT, 4, 8, false>(heads, p, stream);
+  // From 128 MB of caches on their rows stream, if one sweep reads them: us without -> with hints, 8 KV heads, 983 rows, sequences: 16 (64 MB)
+  // 12.2 -> 14.4, 24 (97 MB) 17.6 -> 18.0, 32 24.4 -> 23.0, 64 44.9 -> 41.3 (6.2 TB/s); 4096 rows: 8 (134 MB) 43.8 -> 41.6, 16 50.7 -> 46.5.
+  // (Smaller ones that come round are found in the memory-side cache.)
+  if (p.group <= 4 * HT && rows >= (int64_t)128 * 1000 * 1000 / (2 * kHeadDim * 2)) return launch_decode<HT, 8, 4, true>(heads, p, stream);
+  return launch_decode<HT, 8, 4, false>(heads, p, stream);
 }
 
 }  // namespace

@@ -760,3 +760,15 @@ def test_gather_with_and_without_streaming_hints(heads, budget, ragged):
         want = src[torch.arange(H, device="cuda").view(1, 1, H, 1), idx + start]
         want[~kept] = 77  # slots past the count stay as they were
         assert torch.equal(got, want)
+
+
+# 128 MB of caches, one sweep over them or (more than 8 query heads) several
+@pytest.mark.parametrize("heads,rows,g", [(256, 976, 4), (256, 977, 4), (256, 977, 1), (300, 851, 8), (256, 977, 9)])
+def test_decode_caches_that_stream(H, heads, rows, g):
+    test_decode_lines_between_slices(H, heads, rows, g)
+
+
+# 4 MB of results, runs of heads that are not whole trips of four
+@pytest.mark.parametrize("rows,heads", [(64, 255), (64, 256), (64, 259), (1031, 19)])
+def test_rotation_that_streams(H, rows, heads):
+    test_rotation_of_many_heads(H, rows, heads, 128)
