@@ -22,7 +22,11 @@ namespace {
 // half_shift: log2(head_dim / 2), or -1 if that is no power of two.  HEADS > 0: the length of the runs of a small call, whose loads are
 // all in flight before the angle is evaluated (64 rows, 32 heads, 2 to a thread: 3.0 -> 2.8 us; with runs of sixteen heads that
 // would cost more registers than it gives).
-template <int HEADS>
+// STREAM: the results are stored with the non-temporal hint, so that they leave the caches while the kernel runs and are not written back in the
+// midst of the key stream of the score pass that follows.  Rotation and both passes of 16 prompts of 200..2500 keys, 32 layers, 128 rows (134 MB of
+// queries) 674 -> 661 us; 32 prompts of 700 keys 627 -> 619; 32 layers, 2000 keys (8.4 MB) 64.5 -> 62.2; 16 (4.2 MB) 45.0 -> 45.2; 8 (2.1 MB)
+// 28.3 -> 28.6.  The rotation alone: 8.4 MB 6.2 -> 5.5 us, 67 MB 32.0 -> 27.4, 268 MB 100 -> 98.  (Loads with the hint: 95.5, but 665 for 656.)
+template <int HEADS, bool STREAM>
 __global__ __launch_bounds__(256) void rope_kernel(const uint16_t* x_in, uint16_t* x_out, const int32_t* __restrict__ pos,
                                                    int64_t rows, int heads, int head_dim, int64_t stride_row, int64_t stride_head,
                                                    double neg_log2_theta_2_over_d, int pairing, int heads_per_thread, int half_shift) {
@@ -59,6 +63,10 @@ __global__ __launch_bounds__(256) void rope_kernel(const uint16_t* x_in, uint16_
     return;
   }
   rope_angle(pos[row], c, neg_log2_theta_2_over_d, &sn, &cs);
+  auto put = [&](int64_t at, uint16_t v) {
+    if constexpr (STREAM) __builtin_nontemporal_store(v, dst + at);
+    else dst[at] = v;
+  };
   const int hd0 = blockIdx.y * heads_per_thread;
   const int hd1 = hd0 + heads_per_thread < heads ? hd0 + heads_per_thread : heads;
   int hd = hd0;
@@ -72,15 +80,15 @@ __global__ __launch_bounds__(256) void rope_kernel(const uint16_t* x_in, uint16_
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const double a = bf16_to_f64(ra[u]), b = bf16_to_f64(rb[u]);
-      dst[(int64_t)(hd + u) * stride_head + ia] = f64_to_bf16(a * cs - b * sn);
-      dst[(int64_t)(hd + u) * stride_head + ib] = f64_to_bf16(b * cs + a * sn);
+      put((int64_t)(hd + u) * stride_head + ia, f64_to_bf16(a * cs - b * sn));
+      put((int64_t)(hd + u) * stride_head + ib, f64_to_bf16(b * cs + a * sn));
     }
   }
   for (; hd < hd1; ++hd) {
     const double a = bf16_to_f64(src[(int64_t)hd * stride_head + ia]);
     const double b = bf16_to_f64(src[(int64_t)hd * stride_head + ib]);
-    dst[(int64_t)hd * stride_head + ia] = f64_to_bf16(a * cs - b * sn);
-    dst[(int64_t)hd * stride_head + ib] = f64_to_bf16(b * cs + a * sn);
+    put((int64_t)hd * stride_head + ia, f64_to_bf16(a * cs - b * sn));
+    put((int64_t)hd * stride_head + ib, f64_to_bf16(b * cs + a * sn));
   }
 }
 
@@ -157,7 +165,8 @@ extern "C" DAPQ_API int dapq_rope_apply(const void* x_in, void* x_out, const int
   DAPQ_REQUIRE(head_runs <= 65535, DAPQ_ERR_UNSUPPORTED, "heads (%d) exceeds %d", heads, 65535 * hpt);
   const double e = rope_exponent(theta, head_dim);
   const int half = head_dim / 2, half_shift = (half & (half - 1)) == 0 ? __builtin_ctz((unsigned)half) : -1;
-  auto kernel = hpt == 1 ? rope_kernel<1> : (hpt == 2 ? rope_kernel<2> : (hpt == 4 ? rope_kernel<4> : rope_kernel<0>));
+  auto kernel = hpt == 1 ? rope_kernel<1, false> : (hpt == 2 ? rope_kernel<2, false> : (hpt == 4 ? rope_kernel<4, false> : rope_kernel<0, false>));
+  if (hpt >= 8 && work >= ((int64_t)1 << 20) / heads) kernel = rope_kernel<0, true>;  // from 4 MB of results on (a pair: four bytes)
   hipLaunchKernelGGL(kernel, dim3((unsigned)((work + 255) / 256), (unsigned)head_runs), dim3(256), 0,
                      static_cast<hipStream_t>(stream),
                      static_cast<const uint16_t*>(x_in), static_cast<uint16_t*>(x_out), pos, rows, heads, head_dim,
