@@ -25,11 +25,12 @@
 //            them once the keys of an instruction are counted tile by tile; V_c follows: a lane loads the same
 //            piece (CPL channels) of 8 rows and transposes the 8 x CPL block in its own registers, and instruction
 //            j of a tile gives the channels CPL * n + j.
-// Measured (32 query / 8 KV heads, one layer): 983 rows, 1 sequence 24.9 -> 7.3 us (of which the launch path of the host is
-// the larger part); 64..256 rows, 50 sequences 38.9 -> 10.8 us (3.1 TB/s); 983 rows, 64 sequences 74.9 -> 45.6 us
-// (5.6 TB/s); 8 query heads per KV head, 4096 rows, 1 sequence 140.7 -> 19.9 us.  (Before: vector products, sixteen
+// Measured (32 query / 8 KV heads, one layer): 983 rows, 1 sequence 24.9 -> 6.7 us; 64..256 rows, 50 sequences
+// 38.9 -> 9.8 us (3.4 TB/s); 983 rows, 64 sequences 74.9 -> 40.5 us (6.3 TB/s); 8 query heads per KV head, 4096 rows, 1 sequence 140.7 -> 19.9 us.  (Before: vector products, sixteen
 // waves per head, logits and weights through LDS, the cache read twice for more than 4 query heads.)
 #include <math.h>
+
+#include <type_traits>
 
 #include "dapq_internal.h"
 
@@ -112,6 +113,8 @@ template <int HT, int CPL, int WAVES, bool STREAM>
 __global__ __launch_bounds__(64 * WAVES, 2) void decode_attention_kernel(DecodeParams p) {
   extern __shared__ char lds[];  // [waves]: kDecodeSlots tiles of K_c, the queries; at the end weighted sums, references, sums of weights
   constexpr int kAux = STREAM ? kNonTemporal : 0;
+  constexpr bool kEarly = kHeadDim / (16 * CPL) > 1;  // (see first_loads)
+  constexpr bool kTail = HT == 1 || CPL < 8;         // a wave's last tile has code of its own (two head tiles and all channels: no registers for it)
   constexpr int kHeads = 4 * HT, kChannels = 16 * CPL, kSlices = kHeadDim / kChannels, kThreads = 64 * WAVES;
   static_assert((kDecodeParts * kHeads * kChannels + 2 * kHeads) * 4 <= kDecodeSlots * kDecodeSlotBytes,
                 "what a wave leaves at the end fits where its tiles were");
@@ -139,7 +142,13 @@ __global__ __launch_bounds__(64 * WAVES, 2) void decode_attention_kernel(DecodeP
     t = t < tiles ? t : t - tiles;
     return t * kDecodeTile;
   };
+  auto row_or_none = [&](int i) { return kEarly || i < tiles ? row_of(i) : kDecodeMaxRows; };
   int rows = p.count[head];
+  auto clamp_rows = [&]() {
+    rows = __builtin_amdgcn_readfirstlane(rows);
+    rows = rows < 0 ? 0 : (rows > p.budget ? p.budget : rows);
+    return (rows + kDecodeTile - 1) / kDecodeTile;
+  };
 
   for (int h0 = 0; h0 < g; h0 += kHeads) {
     const int nh = g - h0 < kHeads ? g - h0 : kHeads;  // query heads of this sweep
@@ -152,13 +161,19 @@ __global__ __launch_bounds__(64 * WAVES, 2) void decode_attention_kernel(DecodeP
       __builtin_memcpy(&qrow[t], p.q + (qrow0 + (h < nh ? h : nh - 1)) * kHeadDim + 8 * n, 16);  // (q_decode may be unaligned)
     }
     keep_order();
-    // the first tiles are on their way before the row count is known (rows past the count are inside the cache all the same)
+    // The slices of a few heads have the first tiles on their way before the row count is known (rows past the count are inside the cache all the
+    // same).  Where heads fill the chip, bytes count: only a wave's first rows of K_c, and not of heads so short that a wave may have none.  Us, all
+    // tiles early and four waves' worth of loads past the end -> first tile early -> none early, one slice: 50 sequences of 64..256 rows
+    // 10.9 -> 9.8 -> 9.8; 64 of 32..130, 1 query head 8.6 -> 7.9 -> 7.5; 20 of 256 6.8 -> 6.7 -> 6.9; 16 of 983 12.2 -> 12.2 -> 12.3.
     unsigned vt[8][CPL / 2];
     auto first_loads = [&]() {
-      load_k<kAux>(ring, src, row_of(wave));
-      load_k<kAux>(ring + kDecodeSlotBytes, src, row_of(wave + WAVES));
+      const bool short_head = tiles < 2 * WAVES;
+      if (!kEarly && h0 == 0 && short_head) tiles = clamp_rows();
+      load_k<kAux>(ring, src, row_or_none(wave));
+      if (!kEarly && h0 == 0 && !short_head) tiles = clamp_rows();
+      if (kEarly || !kTail || wave + WAVES < tiles) load_k<kAux>(ring + kDecodeSlotBytes, src, row_or_none(wave + WAVES));
       keep_order();
-      load_v<CPL, kAux>(vt, src, row_of(wave));
+      load_v<CPL, kAux>(vt, src, row_or_none(wave));
       keep_order();
     };
     first_loads();
@@ -171,16 +186,12 @@ __global__ __launch_bounds__(64 * WAVES, 2) void decode_attention_kernel(DecodeP
 #pragma unroll
       for (int s = 0; s < 4; ++s)
         qf[t][s] = __builtin_bit_cast(bf16x8, qs[t * 64 + (n & 3) * 16 + ((4 * s + kg) ^ (n & 3))]);
-    if (h0 == 0) {
-      rows = __builtin_amdgcn_readfirstlane(rows);
-      rows = rows < 0 ? 0 : (rows > p.budget ? p.budget : rows);
-      const int filled = (rows + kDecodeTile - 1) / kDecodeTile;
-      if (filled != tiles) {
+    if (kEarly && h0 == 0) {
+      const int filled = clamp_rows();
+      if (filled != tiles) {  // the slices start elsewhere
         tiles = filled;
-        if (kSlices > 1) {  // the slices start elsewhere
-          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-          first_loads();
-        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        first_loads();
       }
     }
     if (rows == 0) {  // an empty cache attends to nothing
@@ -199,11 +210,16 @@ __global__ __launch_bounds__(64 * WAVES, 2) void decode_attention_kernel(DecodeP
     }
 
     int slot = 0;
-    for (int i = wave; i < tiles; i += WAVES) {
+    // Tile i; MORE: the wave has another one, whose loads go out.  (Loads past the end of the cache fetch nothing, but keep the compute unit's
+    // address unit busy as long as any others: with three tiles' worth of them at a wave's end 983 rows, 1 sequence 7.05 us, now 6.7; 256 rows
+    // 4.9, now 4.2; 32 layers, 4 sequences of 75..300 rows 24.7, now 21.7.)
+    auto step = [&](int i, auto more) {
+      constexpr bool MORE = decltype(more)::value;
       const int row0 = row_of(i);
       const bool partial = row0 + kDecodeTile > rows;
-      // in flight, oldest first: K_c of this tile, K_c of the next one, V_c of this tile (8 loads each)
-      asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+      // in flight, oldest first: K_c of this tile, (MORE) K_c of the next one, V_c of this tile (8 loads each)
+      if constexpr (MORE) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+      else asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
       const u32x4* kt = reinterpret_cast<const u32x4*>(ring + slot * kDecodeSlotBytes);
       bf16x8 kf[2][4];
 #pragma unroll
@@ -222,10 +238,12 @@ __global__ __launch_bounds__(64 * WAVES, 2) void decode_attention_kernel(DecodeP
           for (int v = 0; v < 4; ++v) xs[t][4 * hf + v] = d[v];
         }
       }
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the tile is out of its slot before that is refilled
-      load_k<kAux>(ring + slot * kDecodeSlotBytes, src, i + 2 * WAVES < tiles ? row_of(i + 2 * WAVES) : kDecodeMaxRows);
-      slot ^= 1;
-      keep_order();
+      if constexpr (MORE) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the tile is out of its slot before that is refilled
+        load_k<kAux>(ring + slot * kDecodeSlotBytes, src, i + 2 * WAVES < tiles ? row_of(i + 2 * WAVES) : kDecodeMaxRows);
+        slot ^= 1;
+        keep_order();
+      }
       u32x4 pa[HT];  // the weights as A operand
 #pragma unroll
       for (int t = 0; t < HT; ++t) {
@@ -284,9 +302,14 @@ __global__ __launch_bounds__(64 * WAVES, 2) void decode_attention_kernel(DecodeP
           acc[t][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, pa[t]), __builtin_bit_cast(bf16x8, vb),
                                                              acc[t][j], 0, 0, 0);
       }
-      load_v<CPL, kAux>(vt, src, i + WAVES < tiles ? row_of(i + WAVES) : kDecodeMaxRows);  // (past the end: fetches nothing)
-      keep_order();
-    }
+      if constexpr (MORE) {
+        load_v<CPL, kAux>(vt, src, kTail || i + WAVES < tiles ? row_of(i + WAVES) : kDecodeMaxRows);
+        keep_order();
+      }
+    };
+    int i = wave;
+    for (; i + (kTail ? WAVES : 0) < tiles; i += WAVES) step(i, std::true_type{});
+    if (kTail && i < tiles) step(i, std::false_type{});
 
     // What the wave leaves goes where its tiles were (none is in flight any more).  (A wave without a tile is not read below.)
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
