@@ -1,4 +1,4 @@
-"""DapQ eviction scoring for MI355X: a thin ctypes binding over libdapq.so (hand-written HIP, gfx950).
+"""DapQ eviction scoring for MI355X: a thin binding over libdapq.so (hand-written HIP, gfx950).
 
 Only argument marshalling happens here; every step of the path runs in the library's kernels.
 There is no fallback: if libdapq.so is missing, importing `paper_2603_11564_amd.binding` raises.

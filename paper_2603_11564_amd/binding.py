@@ -1,7 +1,9 @@
-"""ctypes binding for libdapq.so.  Function names and argument order follow include/dapq.h.
+"""Binding for libdapq.so.  Function names and argument order follow include/dapq.h.
 
 torch is used for device memory and streams only: tensors are passed down as raw pointers, the
-current torch stream as the hipStream_t.  Nothing here computes anything.
+current torch stream as the hipStream_t.  Nothing here computes anything.  The library is loaded with ctypes, and the
+functions that only ask it something are called so; those that launch kernels go through the extension module _native,
+which marshals their arguments in a third of the time.
 """
 from __future__ import annotations
 
@@ -14,6 +16,7 @@ _PKG = os.path.dirname(os.path.abspath(__file__))
 # implementation to fall back to
 _LIB_PATH = os.environ.get("DAPQ_LIBRARY") or os.path.join(_PKG, "libdapq.so")
 _lib = None
+_native = None
 
 EXPORTS = (
     "dapq_workspace_bytes", "dapq_last_error", "dapq_rope_apply", "dapq_pseudo_tokens", "dapq_pseudo_queries", "dapq_pseudo_queries_workspace_bytes", "dapq_score", "dapq_score_stats",
@@ -61,7 +64,7 @@ def lib_path() -> str:
 
 def load_library():
     """Load libdapq.so (built in-tree by paper_2603_11564_amd/build.py).  Raises if it is missing."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
@@ -97,6 +100,13 @@ def load_library():
     lib.dapq_pseudo_queries_workspace_bytes.restype = sz
     lib.dapq_score_static_capacity.restype = sz
     lib.dapq_topk_workspace_bytes.restype = sz
+    try:
+        from . import _native as native
+    except ImportError as e:
+        raise ImportError(f"the extension module {_PKG}/_native.so is not built for this Python; run "
+                          "`python -m paper_2603_11564_amd.build` (there is no fallback path)") from e
+    native.bind({name: C.cast(getattr(lib, name), vp).value for name in EXPORTS}, _resolve_current_stream)
+    _native = native
     _lib = lib
     return lib
 
@@ -106,31 +116,27 @@ def _check(rc: int):
         raise DapqError(rc, load_library().dapq_last_error().decode())
 
 
+def _calls():
+    """The extension module, bound to the library."""
+    if _native is None:
+        load_library()
+    return _native
+
+
 def _ptr(t) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
 def _resolve_current_stream():
-    """A function for the current stream's handle.  torch.cuda.current_stream() builds a Stream object each time, 2.9 us
-    next to the 3.1 us that checking and launching a kernel take; the raw handle takes 0.2 us."""
+    """A function for the current stream's handle and one for the device number it takes (None: it takes none).
+    torch.cuda.current_stream() builds a Stream object each time, 2.9 us next to the 3.1 us that checking and launching a
+    kernel take; the raw handle takes 0.2 us."""
     import torch
     raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
     if raw is None or device is None:
-        return lambda: torch.cuda.current_stream().cuda_stream
+        return lambda: torch.cuda.current_stream().cuda_stream, None
     torch.cuda.current_stream()  # initialises the device the way torch wants it, once
-    return lambda: raw(device())
-
-
-_current_stream = None
-
-
-def _stream(stream) -> Optional[int]:
-    global _current_stream
-    if stream is not None:
-        return stream if isinstance(stream, int) else stream.cuda_stream
-    if _current_stream is None:
-        _current_stream = _resolve_current_stream()
-    return _current_stream()
+    return raw, device
 
 
 def make_shape(*, n_layers, batch, n_q_heads, n_kv_heads, n_pseudo, total_tokens, head_dim=128, cu_seqlens=None,
@@ -155,14 +161,13 @@ def workspace_bytes(shape: Shape) -> int:
 
 def dapq_rope_apply(x_in, x_out, pos, rows, heads, head_dim, stride_row, stride_head, theta, pairing=0,
                     stream=None):
-    _check(load_library().dapq_rope_apply(_ptr(x_in), _ptr(x_out), _ptr(pos), rows, heads, head_dim, stride_row,
-                                          stride_head, float(theta), pairing, _stream(stream)))
+    if rc := (_native or _calls()).rope_apply(x_in, x_out, pos, rows, heads, head_dim, stride_row, stride_head, theta, pairing, stream):
+        _check(rc)
 
 
 def dapq_score(shape, q, k, scores, workspace, stream=None):
-    _check(load_library().dapq_score(C.byref(shape), _ptr(q), _ptr(k), _ptr(scores), _ptr(workspace),
-                                     0 if workspace is None else workspace.numel() * workspace.element_size(),
-                                     _stream(stream)))
+    if rc := (_native or _calls()).score(shape, q, k, scores, workspace, stream):
+        _check(rc)
 
 
 def score_single_launch(shape) -> bool:
@@ -174,7 +179,8 @@ def score_single_launch(shape) -> bool:
 
 
 def dapq_score_static(shape, q, k, scores, stream=None):
-    _check(load_library().dapq_score_static(C.byref(shape), _ptr(q), _ptr(k), _ptr(scores), _stream(stream)))
+    if rc := (_native or _calls()).score_static(shape, q, k, scores, stream):
+        _check(rc)
 
 
 def score_static_capacity() -> int:
@@ -182,40 +188,35 @@ def score_static_capacity() -> int:
 
 
 def dapq_score_stats(shape, q, k, lse2, workspace, stream=None):
-    _check(load_library().dapq_score_stats(C.byref(shape), _ptr(q), _ptr(k), _ptr(lse2), _ptr(workspace),
-                                           0 if workspace is None else workspace.numel() * workspace.element_size(),
-                                           _stream(stream)))
+    if rc := (_native or _calls()).score_stats(shape, q, k, lse2, workspace, stream):
+        _check(rc)
 
 
 def dapq_score_accumulate(shape, q, k, lse2, scores, workspace, stream=None):
-    _check(load_library().dapq_score_accumulate(
-        C.byref(shape), _ptr(q), _ptr(k), _ptr(lse2), _ptr(scores), _ptr(workspace),
-        0 if workspace is None else workspace.numel() * workspace.element_size(), _stream(stream)))
+    if rc := (_native or _calls()).score_accumulate(shape, q, k, lse2, scores, workspace, stream):
+        _check(rc)
 
 
 def dapq_score_stats_extend(shape, q, k_pseudo, kp_strides, lse2, stream=None):
     """kp_strides = (layer, seq, head, row) in elements."""
     sl, ss, sh, sr = kp_strides
-    _check(load_library().dapq_score_stats_extend(C.byref(shape), _ptr(q), _ptr(k_pseudo), sl, ss, sh, sr, _ptr(lse2),
-                                                  _stream(stream)))
+    if rc := (_native or _calls()).score_stats_extend(shape, q, k_pseudo, sl, ss, sh, sr, lse2, stream):
+        _check(rc)
 
 
 def dapq_pool(shape, scores, pooled, width=7, stream=None):
-    _check(load_library().dapq_pool(C.byref(shape), _ptr(scores), _ptr(pooled), width, _stream(stream)))
+    if rc := (_native or _calls()).pool(shape, scores, pooled, width, stream):
+        _check(rc)
 
 
 def dapq_topk(shape, pooled, budget, budget_per_seq, idx, count, workspace=None, stream=None):
-    _check(load_library().dapq_topk(C.byref(shape), _ptr(pooled), budget, _ptr(budget_per_seq), _ptr(idx),
-                                    _ptr(count), _ptr(workspace),
-                                    0 if workspace is None else workspace.numel() * workspace.element_size(),
-                                    _stream(stream)))
+    if rc := (_native or _calls()).topk(shape, pooled, budget, budget_per_seq, idx, count, workspace, stream):
+        _check(rc)
 
 
 def dapq_pool_topk(shape, scores, width, budget, budget_per_seq, idx, count, pooled=None, stream=None, workspace=None):
-    _check(load_library().dapq_pool_topk(C.byref(shape), _ptr(scores), width, budget, _ptr(budget_per_seq), _ptr(idx),
-                                         _ptr(count), _ptr(pooled), _ptr(workspace),
-                                         0 if workspace is None else workspace.numel() * workspace.element_size(),
-                                         _stream(stream)))
+    if rc := (_native or _calls()).pool_topk(shape, scores, width, budget, budget_per_seq, idx, count, pooled, workspace, stream):
+        _check(rc)
 
 
 def topk_workspace_bytes(shape, budget) -> int:
@@ -224,24 +225,25 @@ def topk_workspace_bytes(shape, budget) -> int:
 
 
 def dapq_gather(shape, k, v, idx, count, budget, k_out, v_out, stream=None):
-    _check(load_library().dapq_gather(C.byref(shape), _ptr(k), _ptr(v), _ptr(idx), _ptr(count), budget,
-                                      _ptr(k_out), _ptr(v_out), _stream(stream)))
+    if rc := (_native or _calls()).gather(shape, k, v, idx, count, budget, k_out, v_out, stream):
+        _check(rc)
 
 
 def dapq_recall(shape, idx_gold, count_gold, budget_gold, idx_pred, count_pred, budget_pred, common, recall=None,
                 stream=None):
-    _check(load_library().dapq_recall(C.byref(shape), _ptr(idx_gold), _ptr(count_gold), budget_gold, _ptr(idx_pred),
-                                      _ptr(count_pred), budget_pred, _ptr(common), _ptr(recall), _stream(stream)))
+    if rc := (_native or _calls()).recall(shape, idx_gold, count_gold, budget_gold, idx_pred, count_pred, budget_pred, common,
+                                          recall, stream):
+        _check(rc)
 
 
 def dapq_decode_attention(shape, q_decode, k_cache, v_cache, count, budget, out, stream=None):
-    _check(load_library().dapq_decode_attention(C.byref(shape), _ptr(q_decode), _ptr(k_cache), _ptr(v_cache), _ptr(count),
-                                                budget, _ptr(out), _stream(stream)))
+    if rc := (_native or _calls()).decode_attention(shape, q_decode, k_cache, v_cache, count, budget, out, stream):
+        _check(rc)
 
 
 def dapq_pseudo_tokens(shape, first_m, last_n, token_idx, positions, stream=None):
-    _check(load_library().dapq_pseudo_tokens(C.byref(shape), first_m, last_n, _ptr(token_idx), _ptr(positions),
-                                             _stream(stream)))
+    if rc := (_native or _calls()).pseudo_tokens(shape, first_m, last_n, token_idx, positions, stream):
+        _check(rc)
 
 
 def pseudo_queries_workspace_bytes(desc) -> int:
@@ -249,7 +251,5 @@ def pseudo_queries_workspace_bytes(desc) -> int:
 
 
 def dapq_pseudo_queries(desc, x, token_idx, w_q, positions, theta, pairing, q_out, workspace=None, stream=None):
-    _check(load_library().dapq_pseudo_queries(C.byref(desc), _ptr(x), _ptr(token_idx), _ptr(w_q), _ptr(positions),
-                                              float(theta), int(pairing), _ptr(q_out), _ptr(workspace),
-                                              0 if workspace is None else workspace.numel() * workspace.element_size(),
-                                              _stream(stream)))
+    if rc := (_native or _calls()).pseudo_queries(desc, x, token_idx, w_q, positions, theta, pairing, q_out, workspace, stream):
+        _check(rc)

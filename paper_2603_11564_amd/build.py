@@ -1,9 +1,11 @@
-"""Builds libdapq.so (the HIP kernels and their C ABI) for gfx950, in-tree, with hipcc."""
+"""Builds libdapq.so (the HIP kernels and their C ABI) for gfx950, in-tree, with hipcc, and the Python extension module
+that calls it (_native.so) with the host compiler."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -13,6 +15,7 @@ LIB = os.path.join(PKG, "libdapq.so")
 # measurement support for `bench.py --ceilings` (stream and instruction-issue probes); not part of the eviction path
 CEILING_LIB = os.path.join(PKG, "libdapq_ceiling.so")
 CEILING_SOURCES = ["ceiling.hip"]
+NATIVE_LIB = os.path.join(PKG, "_native.so")
 SOURCES = ["common.hip", "rope.hip", "score.hip", "pool.hip", "topk.hip", "gather.hip", "recall.hip", "decode.hip", "qproj.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",
@@ -73,8 +76,19 @@ def build_sanitized(verbose: bool = False) -> str:
     return SANITIZED_LIB
 
 
+def build_native() -> str:
+    """The extension module; returns its path."""
+    cxx = os.environ.get("CXX") or "g++"
+    r = subprocess.run([cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-I", os.path.join(ROOT, "include"),
+                        "-I", sysconfig.get_paths()["include"], "-DDAPQ_API=", os.path.join(CSRC, "native.cpp"), "-o", NATIVE_LIB],
+                       capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"{cxx} failed on native.cpp:\n{r.stderr[-4000:]}")
+    return NATIVE_LIB
+
+
 def build(verbose: bool = False) -> str:
-    """Compile every translation unit and link the shared library; returns its path."""
+    """Compile every translation unit, link the shared library and build the extension module; returns the library's path."""
     hipcc = _hipcc()
     objdir = os.path.join(PKG, "_build")
     os.makedirs(objdir, exist_ok=True)
@@ -96,6 +110,9 @@ def build(verbose: bool = False) -> str:
                            capture_output=True, text=True)
         if r.returncode != 0:
             raise RuntimeError(f"link of {os.path.basename(lib)} failed:\n{r.stderr[-4000:]}")
+    build_native()
+    if verbose:
+        print("compiled native.cpp", flush=True)
     return LIB
 
 
