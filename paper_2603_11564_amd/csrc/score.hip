@@ -1642,6 +1642,145 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(!S
   }
 }
 
+// ---------------------------------------------------------------------------------------------
+// Short prompts of dense batches: one workgroup has all keys (up to 512) and query rows (up to 256) of a (layer, sequence, KV head), which come into
+// LDS once, in whole rows; both passes run out of it in one launch.  A wave works on one row block and its share of the sub-blocks, as in the
+// tile form.  The waves of score_fused_kernel, one to 128 keys, each take in all the queries, and a head of 200 keys has two of them: what bounds
+// calls of up to a few heads to a compute unit is that start and a wave's 32 units in a row (short_call has figures).
+// MODE: both passes, or the first (lse2 out) or the second (lse2 in) alone, with the same bits.  STAGED: the queries through LDS too, which
+// together with more than 256 keys they exceed.
+// ---------------------------------------------------------------------------------------------
+constexpr int kShortKeys = 512, kShortRows = 256;
+enum { kShortBoth = 0, kShortStats = 1, kShortAccumulate = 2 };
+constexpr int short_lds(int subs, int row_blocks, bool stage_q) {
+  return subs * kSubBytes + row_blocks * ((stage_q ? kSubBytes : 0) + subs * 32 * (int)sizeof(float));
+}
+constexpr int kShortStaticLds = kTileWaves * 32 * (int)sizeof(float2) + kShortRows * (int)sizeof(float);
+constexpr int kShortMostLds = 160 * 1024 - kShortStaticLds;
+template <int MODE, bool STAGED>
+__global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(4))) void score_short_kernel(ScoreParams p) {
+  extern __shared__ u32x4 tile_area[];
+  __shared__ float2 sums[kTileWaves][32];
+  __shared__ __align__(16) float neg_lse[kShortRows];
+  touch_args<sizeof(ScoreParams)>();
+  const int seq = (int)blockIdx.x, nkeys = p.seq_len, wave = uniform_i32((int)(threadIdx.x >> 6));
+  const int lane = threadIdx.x & 63, n = lane & 31, h = lane >> 5;
+  Tile t;
+  t.layer = uniform_i32(quotient((int)blockIdx.z, p.inv_kv_heads));
+  t.kv = (int)blockIdx.z - t.layer * p.n_kv_heads;
+  t.chunk = 0;
+  TileShare s;
+  s.subs = (nkeys + 31) / 32;
+  s.rbs = (p.rows + 31) / 32;
+  s.parts = tile_most_parts(s.rbs);
+  s.parts = s.parts < s.subs ? s.parts : s.subs;
+  s.rb = wave;
+  s.part = 0;
+  while (s.rb >= s.rbs) {
+    s.rb -= s.rbs;
+    s.part += 1;
+  }
+  const bool mine = s.part < s.parts;  // (the other waves bring in keys and queries)
+  u32x4 *keys = tile_area, *queries = tile_area + s.subs * kSubVec;
+  float* cols = reinterpret_cast<float*>(queries + (STAGED ? s.rbs * kSubVec : 0));  // [row block][key]
+  const int64_t tok0 = (int64_t)seq * p.seq_len;
+  const uint16_t* qbase = tile_q_base(p, t, seq);
+  const uint16_t* kbase = uniform_ptr(p.k + (int64_t)t.layer * p.k_stride_layer + (int64_t)seq * p.k_stride_seq +
+                                      (int64_t)t.kv * p.k_stride_head + tok0 * p.k_stride_token);
+  float* lse = p.lse2 + (((int64_t)t.layer * p.batch + seq) * p.n_q_heads + (int64_t)t.kv * p.group) * p.n_pseudo;
+  const int row = (int)threadIdx.x;  // of the threads that look after a row
+  float old = 0.0f;
+  if (MODE == kShortAccumulate && row < p.rows) old = lse[row];
+  bf16x8 qf[8];
+  if (!STAGED && mine) frag_from_q(qf, p, qbase, s.rb * 32 + n, h);
+  tile_dma<STAGED>(keys, queries, p, kbase, qbase, nkeys, s, wave, kTileWaves, lane);
+
+  if constexpr (MODE == kShortAccumulate) {
+    if (row < s.rbs * 32) neg_lse[row] = row < p.rows ? -old : -INFINITY;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+  } else {
+    float ref = -INFINITY, z[2] = {0.0f, 0.0f};
+#pragma unroll 1
+    for (int sub0 = 0; sub0 < s.subs; sub0 += s.parts) {
+      tile_wait(s.subs - sub0 - s.parts > 0 ? s.subs - sub0 - s.parts : 0);
+      if (STAGED && sub0 == 0 && mine) wave_load_frags<1>(qf, queries + s.rb * kSubVec, n, h);
+      const int sub = sub0 + s.part;
+      if (!mine || sub >= s.subs) continue;
+      bf16x8 kf[8];
+      wave_load_frags<1>(kf, keys + sub * kSubVec, n, h);
+      f32x16 a = {0};
+#pragma unroll
+      for (int e = 0; e < 8; ++e) a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[e], qf[e], a, 0, 0, 0);
+      if (nkeys < sub * 32 + 32) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+          if (acc_row(v, 0) >= nkeys - sub * 32 - 4 * h) a[v] = -INFINITY;
+      }
+      float m = a[0];
+#pragma unroll
+      for (int v = 1; v < 16; ++v) m = fmaxf(m, a[v]);
+      const float mnew = fmaxf(ref, max_halves(m) * p.c);  // (finite: a sub-block has a key)
+      const float scale = __builtin_amdgcn_exp2f(ref - mnew);
+      z[0] *= scale;
+      z[1] *= scale;
+      ref = mnew;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) z[v & 1] += __builtin_amdgcn_exp2f(fmaf(a[v], p.c, -mnew));
+    }
+    const float both = sum_halves(z[0] + z[1]);
+    if (h == 0) sums[wave][n] = make_float2(ref, both);  // (waves that are no one's: not read)
+    __syncthreads();
+    if (row < s.rbs * 32) {
+      const int block = row >> 5;
+      float m = -INFINITY, sum = 0.0f;
+      for (int i = 0; i < s.parts; ++i) m = fmaxf(m, sums[i * s.rbs + block][n].x);
+      for (int i = 0; i < s.parts; ++i) {
+        const float2 v = sums[i * s.rbs + block][n];
+        sum = fmaf(v.y, __builtin_amdgcn_exp2f(v.x - m), sum);
+      }
+      const float l = sum > 0.0f ? m + log2f(sum) : 0.0f;
+      if (MODE == kShortStats && row < p.rows) lse[row] = l;
+      neg_lse[row] = row < p.rows ? -l : -INFINITY;
+    }
+    if constexpr (MODE == kShortStats) return;
+    __syncthreads();
+  }
+
+  if (mine) {
+    if (STAGED && MODE == kShortAccumulate) wave_load_frags<1>(qf, queries + s.rb * kSubVec, n, h);
+    float off[16];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const float4 v = *reinterpret_cast<const float4*>(&neg_lse[s.rb * 32 + acc_row(4 * b, h)]);
+      off[4 * b] = v.x;
+      off[4 * b + 1] = v.y;
+      off[4 * b + 2] = v.z;
+      off[4 * b + 3] = v.w;
+    }
+#pragma unroll 1
+    for (int sub = s.part; sub < s.subs; sub += s.parts) {
+      bf16x8 kf[8];
+      wave_load_frags<1>(kf, keys + sub * kSubVec, n, h);
+      f32x16 a = {0};
+#pragma unroll
+      for (int e = 0; e < 8; ++e) a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[e], kf[e], a, 0, 0, 0);
+      float z[2] = {0.0f, 0.0f};
+#pragma unroll
+      for (int v = 0; v < 16; ++v) z[v & 1] += __builtin_amdgcn_exp2f(fmaf(a[v], p.c, off[v]));
+      const float both = sum_halves(z[0] + z[1]);
+      if (h == 0) cols[s.rb * s.subs * 32 + sub * 32 + n] = both;
+    }
+  }
+  __syncthreads();
+  float* out = p.scores + ((int64_t)t.layer * p.n_kv_heads + t.kv) * p.total_tokens + tok0;
+  if (row < nkeys) {  // (at most a key to a thread)
+    float sum = cols[row];
+    for (int i = 1; i < s.rbs; ++i) sum += cols[i * s.subs * 32 + row];
+    out[row] = sum;
+  }
+}
+
 // S = sum over row groups of their planes of column sums, in group order; group 0's plane is the
 // result array itself.
 __global__ void score_group_sum_kernel(const float* partial, float* scores, int64_t count, int n_groups) {
@@ -1963,6 +2102,49 @@ int launch_fused(const dapq_shape* s, const ScorePlan& plan, ScoreParams p, hipS
   return DAPQ_OK;
 }
 
+// Whether the calls of a shape run in score_short_kernel (the same line for the call of both passes and for the separate ones, whose bits agree).
+// Its workgroup has a compute unit's LDS nearly to itself from 64 rows and 256 keys on, so it loses where a unit gets several heads in turn
+// that the waves of score_fused_kernel take four at a time.  8 KV heads a layer, us, waves -> this, dapq_score (stats, accumulate):
+//   up to 256 heads    256 rows, 128 keys, 8 heads 19.5 -> 8.3 (14.4 -> 6.2, 11.5 -> 5.5), 256 heads 20.8 -> 10.9; 384 keys, 256 heads 26.0 -> 22.6
+//                      128 rows, 256 keys, 8 heads 13.4 -> 8.5, 256 heads 15.3 -> 10.7; 64 rows, 512 keys, 256 heads 17.1 -> 12.8; 32 rows 16.0 -> 9.7;
+//                      a wave with sixteen sub-blocks: 256 rows, 512 keys, 256 heads 28.4 -> 27.9 (19.9 -> 19.9, 17.4 -> 18.7), 192 rows 24.7 -> 26.6
+//   512 heads          256 rows, 128 keys 25.1 -> 20.3 (19.6 -> 15.6, 16.4 -> 15.0), 200 keys 27.9 -> 28.1; 64 rows, 384 keys 20.8 -> 18.8 (16.9 ->
+//                      15.2, 14.4 -> 14.7); 128 rows, 256 keys 20.3 -> 19.5 (16.7 -> 15.1, 14.1 -> 14.8)
+//   (1070 calls of 1 to 8192 heads, drawn: 0.63 of the time in the geometric mean, stats 0.56, accumulate 0.66; row blocks that leave waves idle lose
+//   with long prompts: 160 rows, 384 keys 16.4 -> 17.9, 96 rows, 448 keys 14.8 -> 12.3 (accumulate 7.2 -> 7.7): at most twice as many in a row)
+//   more, two to a unit     128 rows, 128 keys, 1024 heads 22.4 -> 17.2, 4096 77.3 -> 61.1; 64 rows, 200 keys 22.6 -> 17.8 and 78.7 -> 63.3; 32 rows, 256
+//                      keys 23.6 -> 15.1 and 85.5 -> 56.2; one to a unit: 64 rows, 256 keys, 1024 heads 24.6 -> 26.7, 256 rows, 64 keys 25.4 -> 27.1
+bool short_call(const dapq_shape* s, const ScorePlan& plan) {
+  if (plan.tile || s->cu_seqlens != nullptr || plan.rows > kShortRows || s->total_tokens < s->batch || s->total_tokens / s->batch > kShortKeys) return false;
+  const int subs = (int)((s->total_tokens / s->batch + 31) / 32), row_blocks = (plan.rows + 31) / 32;
+  const int parts = tile_most_parts(row_blocks) < subs ? tile_most_parts(row_blocks) : subs, in_a_row = (subs + parts - 1) / parts;
+  const int staged = short_lds(subs, row_blocks, true);
+  const int64_t heads = (int64_t)s->n_layers * s->n_kv_heads * s->batch;
+  if (heads <= 256) return in_a_row <= 12 && in_a_row <= 2 * row_blocks && (staged <= kShortMostLds || subs <= 12);
+  if (heads <= 512 && staged <= kShortMostLds && (subs <= 4 || in_a_row <= 3)) return true;
+  return staged + kShortStaticLds <= 80 * 1024 && subs * row_blocks > 1;
+}
+int launch_short(const dapq_shape* s, const ScorePlan& plan, const ScoreParams& p, int mode, hipStream_t stream) {
+  const int subs = (int)((s->total_tokens / s->batch + 31) / 32), row_blocks = (plan.rows + 31) / 32;
+  const bool stage_q = short_lds(subs, row_blocks, true) <= kShortMostLds;
+  const dim3 grid((unsigned)s->batch, 1u, (unsigned)(s->n_layers * s->n_kv_heads));
+  int rc = DAPQ_OK;
+#define DAPQ_LAUNCH_SHORT(MODEV, STAGEDV)                                                                                              \
+  do {                                                                                                                                 \
+    if ((rc = set_lds(score_short_kernel<MODEV, STAGEDV>, kShortMostLds)) != DAPQ_OK) return rc;                                       \
+    hipLaunchKernelGGL((score_short_kernel<MODEV, STAGEDV>), grid, dim3(kTileThreads), short_lds(subs, row_blocks, STAGEDV), stream, p); \
+  } while (0)
+  if (mode == kShortBoth && stage_q) DAPQ_LAUNCH_SHORT(kShortBoth, true);
+  else if (mode == kShortBoth) DAPQ_LAUNCH_SHORT(kShortBoth, false);
+  else if (mode == kShortStats && stage_q) DAPQ_LAUNCH_SHORT(kShortStats, true);
+  else if (mode == kShortStats) DAPQ_LAUNCH_SHORT(kShortStats, false);
+  else if (stage_q) DAPQ_LAUNCH_SHORT(kShortAccumulate, true);
+  else DAPQ_LAUNCH_SHORT(kShortAccumulate, false);
+#undef DAPQ_LAUNCH_SHORT
+  DAPQ_HIP_LAUNCH_CHECK("score_short_kernel");
+  return DAPQ_OK;
+}
+
 // Whether pass 2 of the tile form merges the partials itself: the threads of a workgroup can hold every sequence's, and
 // there is a compute unit for every workgroup (tiles of 128 keys, one layer: 4096 keys 18.7 -> 17.6 us; 8191, two workgroups to a
 // compute unit: 25.5 -> 27.2).
@@ -2006,6 +2188,7 @@ extern "C" DAPQ_API int dapq_score_stats(const dapq_shape* shape, const void* q,
   p.lse2 = lse2;
   p.scores = nullptr;
   p.partial = nullptr;
+  if (short_call(shape, plan)) return launch_short(shape, plan, p, kShortStats, static_cast<hipStream_t>(stream));
   return launch_stats(shape, plan, p, static_cast<hipStream_t>(stream));
 }
 
@@ -2030,6 +2213,7 @@ extern "C" DAPQ_API int dapq_score_accumulate(const dapq_shape* shape, const voi
   p.partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + plan.off_partial);
   p.lse2 = const_cast<float*>(lse2);
   p.scores = scores;
+  if (short_call(shape, plan)) return launch_short(shape, plan, p, kShortAccumulate, static_cast<hipStream_t>(stream));
   return launch_accumulate(shape, plan, p, static_cast<hipStream_t>(stream));
 }
 
@@ -2061,6 +2245,7 @@ extern "C" DAPQ_API int dapq_score(const dapq_shape* shape, const void* q, const
     p.partial = nullptr;
     p.lse2 = nullptr;
     p.scores = scores;
+    if (short_call(shape, plan)) return launch_short(shape, plan, p, kShortBoth, static_cast<hipStream_t>(stream));
     return launch_fused(shape, plan, p, static_cast<hipStream_t>(stream));
   }
   if (tile_merges(shape, plan)) {

@@ -479,6 +479,18 @@ def test_chunks_of_few_keys(H, layers, batch, length, rows):
     test_equal_chunks_of_dense_batches(H, layers, batch, length, rows)
 
 
+# short prompts, all of a head in one workgroup: edges of sub-blocks and row blocks (eight waves make eight, four, two parts or one of them), queries
+# through LDS and (more than 320 keys) not; the lines between it and the waves: 256 heads, 512, two workgroups to a compute unit
+@pytest.mark.parametrize("layers,batch,length,rows", [
+    (1, 1, 1, 1), (1, 1, 32, 32), (1, 2, 33, 31), (3, 1, 256, 33), (1, 1, 512, 32), (2, 1, 511, 64), (1, 1, 300, 65), (1, 2, 384, 96),
+    (1, 1, 385, 97), (1, 1, 448, 128), (1, 1, 449, 128), (2, 1, 319, 129), (1, 1, 320, 160), (1, 1, 321, 160), (1, 1, 384, 193),
+    (1, 1, 352, 256), (1, 2, 384, 256), (1, 1, 385, 256), (128, 1, 129, 250), (129, 1, 128, 250), (129, 1, 129, 250), (64, 4, 96, 200),
+    (64, 5, 40, 70), (257, 1, 64, 33), (257, 1, 32, 32), (86, 3, 224, 64), (86, 3, 225, 64)])
+def test_short_prompts(H, layers, batch, length, rows):
+    """As above."""
+    test_equal_chunks_of_dense_batches(H, layers, batch, length, rows)
+
+
 @pytest.mark.parametrize("rows", [33, 96, 128, 160, 192, 224, 250])
 @pytest.mark.parametrize("layers,batch,length", [(160, 2, 700), (100, 3, 1500), (40, 5, 3000)])
 def test_one_or_two_chunks_in_one_kernel(H, layers, batch, length, rows):
