@@ -7,6 +7,7 @@
 // share one KV head.  Nothing of size N x L_p is ever stored.  Where a (layer, sequence, KV head) fits one
 // workgroup -- one row group, at most 4 chunks per sequence of a dense batch -- dapq_score runs both passes in
 // one launch (score_fused_kernel: the same two walks, the merge in between through LDS).
+// Prompts of up to 512 keys, at most 256 rows, are the waves of one workgroup: score_short_kernel, one launch for both passes or for either.
 // Calls too small to fill the chip that way go through score_tile_pass1_kernel and score_tile_pass2_kernel instead: a
 // workgroup per 32 to 256 keys whose waves share out the query rows (make_score_plan draws the line).  Ragged batches go through the
 // wave kernels in segments of the packed key axis (Segments).
@@ -1941,14 +1942,13 @@ bool two_at_a_time(const ScorePlan& plan) {
     }                                          \
   } while (0)
 
-// Whether the waves of a dense launch start with the queries as fragments (SHORT) although they are more than two row blocks.  All keys of
+// Whether the waves of a dense launch start with the queries as fragments (SHORT) although they are five row blocks or more.  All keys of
 // a chunk of a few sub-blocks fit the ring at once; they and fragments arrive in one trip to memory, and behind queries that go through the
 // ring they wait for two or three.  It is the shorter start where the waves of a compute unit are workgroups of their own (side by side in
 // one, their many loads set the pace: 32 prompts x heads of 512 keys, 256 rows 30.2 us through the ring, 36.7), in one kernel up to some
-// eight rounds of waves.  Ring -> fragments, us, dapq_score with inputs in the caches / out of memory: 64 prompts x heads of 64 keys, 96 rows
-// 8.9 / 8.8 -> 7.9 / 8.0; 1024, 128 rows 16.2 / 18.7 -> 13.9 / 18.4; 4096, 256 rows 90.6 / 92.8 -> 82.3 / 84.1; 8192, 192 rows 131.5 / 131.8 ->
-// 128.3 / 126.9 (256 and 512 of them out of memory up to 1.05 the other way, 192 rows 15.6 -> 16.0; 16384 of 32 keys, 256 rows 232.8 -> 257.7).
-// The two separate calls, out of memory: 8 heads of 64 keys, 96 rows 14.2 -> 11.8; 256, 256 rows 27.3 -> 24.4; 8192, 192 rows 220 -> 210.
+// eight rounds of waves.  Ring -> fragments, us, dapq_score with inputs in the caches / out of memory: 4096 prompts x heads of 64 keys, 256
+// rows 90.6 / 92.8 -> 82.3 / 84.1; 8192, 192 rows 131.5 / 131.8 -> 128.3 / 126.9 (16384 of 32 keys, 256 rows 232.8 -> 257.7); the two
+// separate calls, 8192, 192 rows, out of memory 220 -> 210.  (Three and four row blocks with as few keys are all score_short_kernel's.)
 bool few_keys(const dapq_shape* s, const ScorePlan& plan, const GroupShape& gs) {
   return plan.segments == 0 && gs.waves == 1 && s->total_tokens / s->batch <= kMinChunkKeys;
 }
@@ -1975,7 +1975,7 @@ int launch_wave_pass1(const dapq_shape* s, const ScorePlan& plan, ScoreParams p,
     else if (plan.segments > 0) DAPQ_LAUNCH_W1(NRBV, true, true, false, false);        \
     else if (plan.unit_sums && hints) DAPQ_LAUNCH_W1(NRBV, false, true, false, true);  \
     else if (plan.unit_sums) DAPQ_LAUNCH_W1(NRBV, false, true, false, false);          \
-    else if (few && NRBV > 2) DAPQ_LAUNCH_W1(NRBV, false, false, (NRBV > 2), false);   \
+    else if (few && NRBV > 4) DAPQ_LAUNCH_W1(NRBV, false, false, (NRBV > 4), false);   \
     else if (hints) DAPQ_LAUNCH_W1(NRBV, false, false, false, true);                   \
     else DAPQ_LAUNCH_W1(NRBV, false, false, false, false);                             \
   } while (0)
@@ -2040,7 +2040,7 @@ int launch_accumulate(const dapq_shape* s, const ScorePlan& plan, ScoreParams p,
   do {                                                                          \
     if (plan.segments > 0 && hints) DAPQ_LAUNCH_W2(NRBV, true, false, true);    \
     else if (plan.segments > 0) DAPQ_LAUNCH_W2(NRBV, true, false, false);       \
-    else if (few && NRBV > 2) DAPQ_LAUNCH_W2(NRBV, false, (NRBV > 2), false);   \
+    else if (few && NRBV > 4) DAPQ_LAUNCH_W2(NRBV, false, (NRBV > 4), false);   \
     else if (hints) DAPQ_LAUNCH_W2(NRBV, false, false, true);                   \
     else DAPQ_LAUNCH_W2(NRBV, false, false, false);                             \
   } while (0)
@@ -2091,7 +2091,7 @@ int launch_fused(const dapq_shape* s, const ScorePlan& plan, ScoreParams p, hipS
   do {                                                                        \
     if (plan.unit_sums && hints) DAPQ_LAUNCH_F(NRBV, true, false, true);      \
     else if (plan.unit_sums) DAPQ_LAUNCH_F(NRBV, true, false, false);         \
-    else if (few && NRBV > 2) DAPQ_LAUNCH_F(NRBV, false, (NRBV > 2), false);  \
+    else if (few && NRBV > 4) DAPQ_LAUNCH_F(NRBV, false, (NRBV > 4), false);  \
     else if (hints) DAPQ_LAUNCH_F(NRBV, false, false, true);                  \
     else DAPQ_LAUNCH_F(NRBV, false, false, false);                            \
   } while (0)
