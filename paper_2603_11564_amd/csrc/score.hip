@@ -43,6 +43,7 @@
 // one exponential and one add each; the rest (transfer issue, ring wait, fragment reads, loop
 // control) is about one more instruction per slice.
 
+#include <float.h>
 #include <math.h>
 
 #include <mutex>
@@ -1701,7 +1702,7 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(4)
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
   } else {
-    float ref = -INFINITY, z[2] = {0.0f, 0.0f};
+    float ref = -FLT_MAX, z[2] = {0.0f, 0.0f};  // (not -inf: the logits of a whole sub-block may be, and add nothing then)
 #pragma unroll 1
     for (int sub0 = 0; sub0 < s.subs; sub0 += s.parts) {
       tile_wait(s.subs - sub0 - s.parts > 0 ? s.subs - sub0 - s.parts : 0);
@@ -1721,7 +1722,7 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(4)
       float m = a[0];
 #pragma unroll
       for (int v = 1; v < 16; ++v) m = fmaxf(m, a[v]);
-      const float mnew = fmaxf(ref, max_halves(m) * p.c);  // (finite: a sub-block has a key)
+      const float mnew = fmaxf(ref, max_halves(m) * p.c);
       const float scale = __builtin_amdgcn_exp2f(ref - mnew);
       z[0] *= scale;
       z[1] *= scale;
@@ -1735,10 +1736,13 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(4)
     if (row < s.rbs * 32) {
       const int block = row >> 5;
       float m = -INFINITY, sum = 0.0f;
-      for (int i = 0; i < s.parts; ++i) m = fmaxf(m, sums[i * s.rbs + block][n].x);
+      for (int i = 0; i < s.parts; ++i) {  // (parts whose sum is no number are left out, as score_combine_kernel does)
+        const float2 v = sums[i * s.rbs + block][n];
+        if (v.y > 0.0f) m = fmaxf(m, v.x);
+      }
       for (int i = 0; i < s.parts; ++i) {
         const float2 v = sums[i * s.rbs + block][n];
-        sum = fmaf(v.y, __builtin_amdgcn_exp2f(v.x - m), sum);
+        if (v.y > 0.0f) sum = fmaf(v.y, __builtin_amdgcn_exp2f(v.x - m), sum);
       }
       const float l = sum > 0.0f ? m + log2f(sum) : 0.0f;
       if (MODE == kShortStats && row < p.rows) lse[row] = l;

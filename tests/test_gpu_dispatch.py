@@ -491,6 +491,23 @@ def test_short_prompts(H, layers, batch, length, rows):
     test_equal_chunks_of_dense_batches(H, layers, batch, length, rows)
 
 
+# whole sub-blocks of a short prompt whose logits overflow to -inf (bf16's lowest value in a key, as a mask would have it): a wave's only one,
+# its first one, its last one; a prompt of a sub-block and a key
+@pytest.mark.parametrize("length,rows,masked", [(96, 33, (32, 64)), (256, 32, (0, 32)), (300, 250, (0, 64)), (300, 65, (288, 300)), (33, 20, (0, 32))])
+def test_short_prompts_with_masked_keys(H, length, rows, masked):
+    """The oracle's scores within 1e-3 and normalisers within 2e-4 in the log2 domain: the masked keys add nothing to any row."""
+    announce(f"masked keys {masked} of {length}, rows={rows}")
+    q, k, v, cu = problem_bits(rows, 1, [length], 2, 2, rows)
+    q[..., 0] = W.to_bf16_bits(np.full(q.shape[:-1], 2.0, dtype=np.float32))
+    k[0, masked[0]:masked[1]] = 0
+    k[0, masked[0]:masked[1], :, 0] = 0xFF7F
+    prob = H.Problem(q, k, v, 2, None, "thd")
+    S = prob.score()
+    assert torch.isfinite(S).all() and not S[:, :, masked[0]:masked[1]].any()
+    H.assert_scores_close(S.cpu().numpy(), O.score(q, k, 2, cu), f"{length} rows={rows}")
+    assert np.abs(prob.stats().cpu().numpy() - oracle_lse2(q, k, 2, cu)).max() < 2e-4
+
+
 @pytest.mark.parametrize("rows", [33, 96, 128, 160, 192, 224, 250])
 @pytest.mark.parametrize("layers,batch,length", [(160, 2, 700), (100, 3, 1500), (40, 5, 3000)])
 def test_one_or_two_chunks_in_one_kernel(H, layers, batch, length, rows):
