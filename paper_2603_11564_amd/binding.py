@@ -105,7 +105,7 @@ def load_library():
     except ImportError as e:
         raise ImportError(f"the extension module {_PKG}/_native.so is not built for this Python; run "
                           "`python -m paper_2603_11564_amd.build` (there is no fallback path)") from e
-    native.bind({name: C.cast(getattr(lib, name), vp).value for name in EXPORTS}, _resolve_current_stream)
+    native.bind({name: C.cast(getattr(lib, name), vp).value for name in EXPORTS}, _resolve_current_stream, Shape, Qproj)
     _native = native
     _lib = lib
     return lib
@@ -161,7 +161,8 @@ def workspace_bytes(shape: Shape) -> int:
 
 def dapq_rope_apply(x_in, x_out, pos, rows, heads, head_dim, stride_row, stride_head, theta, pairing=0,
                     stream=None):
-    if rc := (_native or _calls()).rope_apply(x_in, x_out, pos, rows, heads, head_dim, stride_row, stride_head, theta, pairing, stream):
+    if rc := (_native or _calls()).rope_apply(x_in, x_out, pos, rows, heads, head_dim, stride_row, stride_head, float(theta), pairing,
+                                               stream):
         _check(rc)
 
 
@@ -251,5 +252,5 @@ def pseudo_queries_workspace_bytes(desc) -> int:
 
 
 def dapq_pseudo_queries(desc, x, token_idx, w_q, positions, theta, pairing, q_out, workspace=None, stream=None):
-    if rc := (_native or _calls()).pseudo_queries(desc, x, token_idx, w_q, positions, theta, pairing, q_out, workspace, stream):
+    if rc := (_native or _calls()).pseudo_queries(desc, x, token_idx, w_q, positions, float(theta), int(pairing), q_out, workspace, stream):
         _check(rc)

@@ -14,6 +14,7 @@
 namespace {
 
 PyObject *g_resolver = nullptr, *g_stream = nullptr, *g_device = nullptr;  // see stream_of
+PyTypeObject *g_shape = nullptr, *g_qproj = nullptr;                       // the descriptors' classes
 PyObject *g_data_ptr, *g_numel, *g_element_size, *g_cuda_stream;           // interned names
 
 // Every converter returns false with a Python error set.
@@ -67,26 +68,35 @@ bool stream_of(PyObject* s, void** out) {
       Py_INCREF(stream);
       Py_INCREF(device);
       Py_DECREF(pair);
-      g_device = device;
-      g_stream = stream;
+      Py_XSETREF(g_device, device);
+      Py_XSETREF(g_stream, stream);
     }
-    if (g_device == Py_None) {
-      v = PyObject_CallNoArgs(g_stream);
-    } else {
-      PyObject* d = PyObject_CallNoArgs(g_device);
-      if (d == nullptr) return false;
-      v = PyObject_CallOneArg(g_stream, d);
+    PyObject *stream = g_stream, *device = g_device;  // (kept for the calls, during which another thread may bind anew)
+    Py_INCREF(stream);
+    Py_INCREF(device);
+    if (device == Py_None) {
+      v = PyObject_CallNoArgs(stream);
+    } else if (PyObject* d = PyObject_CallNoArgs(device)) {
+      v = PyObject_CallOneArg(stream, d);
       Py_DECREF(d);
     }
+    Py_DECREF(device);
+    Py_DECREF(stream);
   }
   if (v == nullptr) return false;
   *out = reinterpret_cast<void*>((uintptr_t)PyLong_AsUnsignedLongLongMask(v));
   Py_DECREF(v);
   return PyErr_Occurred() == nullptr;
 }
-// A copy of a descriptor (a ctypes structure).
+// A copy of a descriptor (a ctypes structure of its own class: what else has as many bytes is refused).
+PyTypeObject* class_of(const dapq_shape*) { return g_shape; }
+PyTypeObject* class_of(const dapq_qproj*) { return g_qproj; }
 template <typename T>
 bool struct_of(PyObject* v, T* out) {
+  if (class_of(out) == nullptr || !PyObject_TypeCheck(v, class_of(out))) {
+    PyErr_Format(PyExc_TypeError, "descriptor expected instead of %s", Py_TYPE(v)->tp_name);
+    return false;
+  }
   Py_buffer b;
   if (PyObject_GetBuffer(v, &b, PyBUF_SIMPLE) != 0) return false;
   const bool ok = b.len == (Py_ssize_t)sizeof(T);
@@ -125,8 +135,9 @@ constexpr int kCalls = (int)(sizeof(kNames) / sizeof(kNames[0]));
 static_assert(sizeof(Calls) == kCalls * sizeof(void*), "a name for every function");
 Calls g_calls = {};
 
-PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {  // (addresses by name, resolver of the current stream)
-  if (!count_is(n, 2)) return nullptr;
+PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {  // (addresses by name, resolver of the current stream, Shape, Qproj)
+  if (!count_is(n, 4)) return nullptr;
+  if (!PyType_Check(a[2]) || !PyType_Check(a[3])) return PyErr_Format(PyExc_TypeError, "classes expected");
   void* at[kCalls];
   for (int i = 0; i < kCalls; ++i) {
     PyObject* v = PyDict_Check(a[0]) ? PyDict_GetItemString(a[0], kNames[i]) : nullptr;
@@ -137,6 +148,10 @@ PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {  // (addresses by 
   __builtin_memcpy(&g_calls, at, sizeof(at));
   Py_INCREF(a[1]);
   Py_XSETREF(g_resolver, a[1]);
+  Py_INCREF(a[2]);
+  Py_XSETREF(g_shape, reinterpret_cast<PyTypeObject*>(a[2]));
+  Py_INCREF(a[3]);
+  Py_XSETREF(g_qproj, reinterpret_cast<PyTypeObject*>(a[3]));
   Py_CLEAR(g_stream);
   Py_CLEAR(g_device);
   Py_RETURN_NONE;

@@ -62,8 +62,15 @@ def test_arguments_of_the_wrong_kind_are_refused():
     for bad, error in ((lambda: D.dapq_gather(shape(), 4096, T, T, T, 8, T, T, 0), AttributeError),
                        (lambda: D.dapq_gather(shape(), T, T, T, T, 8.0, T, T, 0), TypeError),
                        (lambda: D.dapq_gather(desc(), T, T, T, T, 8, T, T, 0), TypeError),
+                       (lambda: D.dapq_gather(bytearray(C.sizeof(D.Shape)), T, T, T, T, 8, T, T, 0), TypeError),
                        (lambda: D.dapq_gather(shape(), T, T, T, T, 8, T, T, "stream"), AttributeError),
                        (lambda: D.dapq_pseudo_queries(shape(), T, T, T, T, 5e5, 0, T, N, 0), TypeError)):
         with pytest.raises(error):
             bad()
     assert C.sizeof(D.Shape) != C.sizeof(D.Qproj)
+
+
+def test_numbers_of_other_kinds_are_converted():
+    for theta, pairing in (("-1", 0.0), (torch.tensor(-1.0), "0"), (-1, True)):
+        with pytest.raises(D.DapqError, match="finite theta"):
+            D.dapq_pseudo_queries(desc(), T, T, T, T, theta, pairing, T, N, 0)
