@@ -1731,18 +1731,17 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(4)
       for (int v = 0; v < 16; ++v) z[v & 1] += __builtin_amdgcn_exp2f(fmaf(a[v], p.c, -mnew));
     }
     const float both = sum_halves(z[0] + z[1]);
-    if (h == 0) sums[wave][n] = make_float2(ref, both);  // (waves that are no one's: not read)
+    // (parts whose sum is no number are left out, as score_combine_kernel does; here, since a branch in the merge costs 1 us of 6; waves that are no
+    // one's are not read)
+    if (h == 0) sums[wave][n] = both > 0.0f ? make_float2(ref, both) : make_float2(-INFINITY, 0.0f);
     __syncthreads();
     if (row < s.rbs * 32) {
       const int block = row >> 5;
       float m = -INFINITY, sum = 0.0f;
-      for (int i = 0; i < s.parts; ++i) {  // (parts whose sum is no number are left out, as score_combine_kernel does)
-        const float2 v = sums[i * s.rbs + block][n];
-        if (v.y > 0.0f) m = fmaxf(m, v.x);
-      }
+      for (int i = 0; i < s.parts; ++i) m = fmaxf(m, sums[i * s.rbs + block][n].x);
       for (int i = 0; i < s.parts; ++i) {
         const float2 v = sums[i * s.rbs + block][n];
-        if (v.y > 0.0f) sum = fmaf(v.y, __builtin_amdgcn_exp2f(v.x - m), sum);
+        sum = fmaf(v.y, __builtin_amdgcn_exp2f(v.x - m), sum);
       }
       const float l = sum > 0.0f ? m + log2f(sum) : 0.0f;
       if (MODE == kShortStats && row < p.rows) lse[row] = l;
