@@ -1817,15 +1817,38 @@ int simd_count() {
 // The waves of a launch per head and row group: chunks of a dense batch, segments of a ragged one.
 int64_t wave_chunks(const ScorePlan& plan) { return plan.segments > 0 ? plan.segments : plan.max_chunks; }
 
+// A launch holds fewer than 2^32 threads along an axis; with more its grid comes out short, without an error.  The sequences of a dense batch go
+// through in as many launches as that takes, `threads` along the axis to each: launch(parameters of those from one on, how many).  All but the
+// last launch have a multiple of four sequences, so that workgroups stay full (see group_shape).
+template <typename F>
+int for_sequences(const dapq_shape* s, const ScoreParams& p, int64_t threads, F launch) {
+  const int64_t most = (((int64_t)1 << 32) - 1) / threads / 4 * 4;
+  if (s->cu_seqlens != nullptr || s->batch <= most || p.seq_len == 0) return launch(p, (int64_t)s->batch);
+  for (int64_t first = 0; first < s->batch; first += most) {
+    ScoreParams part = p;
+    part.q += first * p.q_stride_seq;
+    part.k += first * (p.k_stride_seq + p.seq_len * p.k_stride_token);
+    if (p.parts != nullptr) part.parts += first * p.chunks_per_seq * p.rows_pad;
+    if (p.lse2 != nullptr) part.lse2 += first * p.n_q_heads * p.n_pseudo;
+    if (p.scores != nullptr) part.scores += first * p.seq_len;
+    if (p.partial != nullptr) part.partial += first * p.seq_len;
+    const int rc = launch(part, s->batch - first < most ? s->batch - first : most);
+    if (rc != DAPQ_OK) return rc;
+  }
+  return DAPQ_OK;
+}
+
 // How a launch packs its waves into workgroups: `waves` to a workgroup (kWavesPerGroup or 1), of which `groups`
 // are the row groups of one chunk side by side (see wave_slot) and waves / groups consecutive chunks.
 struct GroupShape {
   int waves, groups;
-  dim3 grid(const ScorePlan& plan, const dapq_shape* s) const {
+  dim3 grid(const ScorePlan& plan, const dapq_shape* s, int64_t seqs) const {  // `seqs` of the batch's sequences
     const int cpw = waves / groups;
-    return dim3((unsigned)((wave_chunks(plan) + cpw - 1) / cpw), (unsigned)(plan.n_groups / groups),
-                (unsigned)(s->n_layers * s->n_kv_heads));
+    const int64_t chunks = seqs < s->batch ? wave_chunks(plan) / s->batch * seqs : wave_chunks(plan);
+    return dim3((unsigned)((chunks + cpw - 1) / cpw), (unsigned)(plan.n_groups / groups), (unsigned)(s->n_layers * s->n_kv_heads));
   }
+  // threads of a launch along the axis of the sequences, to each (see for_sequences)
+  int64_t threads(const ScorePlan& plan, const dapq_shape* s) const { return 64 * groups * ((wave_chunks(plan) + s->batch - 1) / s->batch); }
 };
 GroupShape group_shape(const dapq_shape* s, const ScorePlan& plan) {
   const int groups = plan.n_groups % 4 == 0 ? 4 : (plan.n_groups % 2 == 0 ? 2 : 1);
@@ -1956,21 +1979,22 @@ bool few_keys(const dapq_shape* s, const ScorePlan& plan, const GroupShape& gs) 
   return plan.segments == 0 && gs.waves == 1 && s->total_tokens / s->batch <= kMinChunkKeys;
 }
 
-int launch_wave_pass1(const dapq_shape* s, const ScorePlan& plan, ScoreParams p, hipStream_t stream) {
-  int rc = DAPQ_OK;
+int launch_wave_pass1(const dapq_shape* s, const ScorePlan& plan, ScoreParams all, hipStream_t stream) {
   const GroupShape gs = group_shape(s, plan);
-  p.wg_groups = gs.groups;
+  all.wg_groups = gs.groups;
   const bool few = few_keys(s, plan, gs);
   const KeyHints key = key_hints(s, plan, false);
   const bool hints = key.on;
-  p.stream_share = key.share;
-#define DAPQ_LAUNCH_W1(NRBV, SEGV, UNITV, SHORTV, STREAMV)                                                               \
-  do {                                                                                                                   \
-    if ((rc = set_lds(score_wave_pass1_kernel<NRBV, SEGV, UNITV, SHORTV, STREAMV, kWaveStages>,                          \
-                      kWavesPerGroup * wave_lds(kWaveStages))) != DAPQ_OK)                                               \
-      return rc;                                                                                                         \
-    hipLaunchKernelGGL((score_wave_pass1_kernel<NRBV, SEGV, UNITV, SHORTV, STREAMV, kWaveStages>), gs.grid(plan, s),     \
-                       dim3(64 * gs.waves), gs.waves * wave_lds(kWaveStages), stream, p);                                \
+  all.stream_share = key.share;
+  return for_sequences(s, all, gs.threads(plan, s), [&](const ScoreParams& p, int64_t seqs) -> int {
+    int rc = DAPQ_OK;
+#define DAPQ_LAUNCH_W1(NRBV, SEGV, UNITV, SHORTV, STREAMV)                                                                 \
+  do {                                                                                                                     \
+    if ((rc = set_lds(score_wave_pass1_kernel<NRBV, SEGV, UNITV, SHORTV, STREAMV, kWaveStages>,                            \
+                      kWavesPerGroup * wave_lds(kWaveStages))) != DAPQ_OK)                                                 \
+      return rc;                                                                                                           \
+    hipLaunchKernelGGL((score_wave_pass1_kernel<NRBV, SEGV, UNITV, SHORTV, STREAMV, kWaveStages>), gs.grid(plan, s, seqs), \
+                       dim3(64 * gs.waves), gs.waves * wave_lds(kWaveStages), stream, p);                                  \
   } while (0)
 #define DAPQ_LAUNCH_W1_KEYS(NRBV)                                                      \
   do {                                                                                 \
@@ -1982,11 +2006,12 @@ int launch_wave_pass1(const dapq_shape* s, const ScorePlan& plan, ScoreParams p,
     else if (hints) DAPQ_LAUNCH_W1(NRBV, false, false, false, true);                   \
     else DAPQ_LAUNCH_W1(NRBV, false, false, false, false);                             \
   } while (0)
-  DAPQ_BY_ROW_BLOCKS(plan.row_blocks, DAPQ_LAUNCH_W1_KEYS);
+    DAPQ_BY_ROW_BLOCKS(plan.row_blocks, DAPQ_LAUNCH_W1_KEYS);
 #undef DAPQ_LAUNCH_W1_KEYS
 #undef DAPQ_LAUNCH_W1
-  DAPQ_HIP_LAUNCH_CHECK("score_wave_pass1_kernel");
-  return DAPQ_OK;
+    DAPQ_HIP_LAUNCH_CHECK("score_wave_pass1_kernel");
+    return DAPQ_OK;
+  });
 }
 
 int launch_stats(const dapq_shape* s, const ScorePlan& plan, ScoreParams p, hipStream_t stream) {
@@ -2016,6 +2041,36 @@ int launch_stats(const dapq_shape* s, const ScorePlan& plan, ScoreParams p, hipS
   return DAPQ_OK;
 }
 
+int launch_wave_pass2(const dapq_shape* s, const ScorePlan& plan, ScoreParams all, hipStream_t stream) {
+  const GroupShape gs = group_shape(s, plan);
+  all.wg_groups = gs.groups;
+  const bool few = few_keys(s, plan, gs), hints = key_hints(s, plan, false).on;
+  return for_sequences(s, all, gs.threads(plan, s), [&](const ScoreParams& p, int64_t seqs) -> int {
+    int rc = DAPQ_OK;
+#define DAPQ_LAUNCH_W2(NRBV, SEGV, SHORTV, STREAMV)                                                                       \
+  do {                                                                                                                    \
+    if ((rc = set_lds(score_wave_pass2_kernel<NRBV, SEGV, SHORTV, STREAMV, kWaveStages>,                                  \
+                      kWavesPerGroup * wave_lds(kWaveStages))) != DAPQ_OK)                                                \
+      return rc;                                                                                                          \
+    hipLaunchKernelGGL((score_wave_pass2_kernel<NRBV, SEGV, SHORTV, STREAMV, kWaveStages>), gs.grid(plan, s, seqs),       \
+                       dim3(64 * gs.waves), gs.waves * wave_lds(kWaveStages), stream, p);                                 \
+  } while (0)
+#define DAPQ_LAUNCH_W2_KEYS(NRBV)                                               \
+  do {                                                                          \
+    if (plan.segments > 0 && hints) DAPQ_LAUNCH_W2(NRBV, true, false, true);    \
+    else if (plan.segments > 0) DAPQ_LAUNCH_W2(NRBV, true, false, false);       \
+    else if (few && NRBV > 4) DAPQ_LAUNCH_W2(NRBV, false, (NRBV > 4), false);   \
+    else if (hints) DAPQ_LAUNCH_W2(NRBV, false, false, true);                   \
+    else DAPQ_LAUNCH_W2(NRBV, false, false, false);                             \
+  } while (0)
+    DAPQ_BY_ROW_BLOCKS(plan.row_blocks, DAPQ_LAUNCH_W2_KEYS);
+#undef DAPQ_LAUNCH_W2_KEYS
+#undef DAPQ_LAUNCH_W2
+    DAPQ_HIP_LAUNCH_CHECK("score_wave_pass2_kernel");
+    return DAPQ_OK;
+  });
+}
+
 int launch_accumulate(const dapq_shape* s, const ScorePlan& plan, ScoreParams p, hipStream_t stream) {
   int rc = launch_chunk_prefix(s, plan, p, stream);  // (pass 2 can be called on its own: it rebuilds the prefix it walks)
   if (rc != DAPQ_OK) return rc;
@@ -2028,29 +2083,7 @@ int launch_accumulate(const dapq_shape* s, const ScorePlan& plan, ScoreParams p,
     else DAPQ_LAUNCH_TILE((score_tile_pass2_kernel<false, false, 1>), true);
     return DAPQ_OK;
   }
-  const GroupShape gs = group_shape(s, plan);
-  p.wg_groups = gs.groups;
-  const bool few = few_keys(s, plan, gs), hints = key_hints(s, plan, false).on;
-#define DAPQ_LAUNCH_W2(NRBV, SEGV, SHORTV, STREAMV)                                                                       \
-  do {                                                                                                                    \
-    if ((rc = set_lds(score_wave_pass2_kernel<NRBV, SEGV, SHORTV, STREAMV, kWaveStages>,                                  \
-                      kWavesPerGroup * wave_lds(kWaveStages))) != DAPQ_OK)                                                \
-      return rc;                                                                                                          \
-    hipLaunchKernelGGL((score_wave_pass2_kernel<NRBV, SEGV, SHORTV, STREAMV, kWaveStages>), gs.grid(plan, s),             \
-                       dim3(64 * gs.waves), gs.waves * wave_lds(kWaveStages), stream, p);                                 \
-  } while (0)
-#define DAPQ_LAUNCH_W2_KEYS(NRBV)                                               \
-  do {                                                                          \
-    if (plan.segments > 0 && hints) DAPQ_LAUNCH_W2(NRBV, true, false, true);    \
-    else if (plan.segments > 0) DAPQ_LAUNCH_W2(NRBV, true, false, false);       \
-    else if (few && NRBV > 4) DAPQ_LAUNCH_W2(NRBV, false, (NRBV > 4), false);   \
-    else if (hints) DAPQ_LAUNCH_W2(NRBV, false, false, true);                   \
-    else DAPQ_LAUNCH_W2(NRBV, false, false, false);                             \
-  } while (0)
-  DAPQ_BY_ROW_BLOCKS(plan.row_blocks, DAPQ_LAUNCH_W2_KEYS);
-#undef DAPQ_LAUNCH_W2_KEYS
-#undef DAPQ_LAUNCH_W2
-  DAPQ_HIP_LAUNCH_CHECK("score_wave_pass2_kernel");
+  if ((rc = launch_wave_pass2(s, plan, p, stream)) != DAPQ_OK) return rc;
   if (plan.n_groups > 1) {
     const int64_t count = (int64_t)s->n_layers * s->n_kv_heads * s->total_tokens;
     const int64_t want = (count + 255) / 256;
@@ -2073,15 +2106,17 @@ int fused_waves(const dapq_shape* s, const ScorePlan& plan) {
 }
 bool fused_applies(const dapq_shape* s, const ScorePlan& plan) { return fused_waves(s, plan) != 0; }
 
-int launch_fused(const dapq_shape* s, const ScorePlan& plan, ScoreParams p, hipStream_t stream) {
+int launch_fused(const dapq_shape* s, const ScorePlan& plan, ScoreParams all, hipStream_t stream) {
   const GroupShape gs = {fused_waves(s, plan), 1};
-  p.wg_groups = 1;
-  const dim3 grid((unsigned)s->batch, 1u, (unsigned)(s->n_layers * s->n_kv_heads));
-  const bool few = few_keys(s, plan, gs) && (int64_t)grid.x * grid.z <= 8192;
+  all.wg_groups = 1;
+  const int64_t heads = (int64_t)s->n_layers * s->n_kv_heads;
+  const bool few = few_keys(s, plan, gs) && s->batch * heads <= 8192;
   const KeyHints key = key_hints(s, plan, true);
   const bool hints = key.on;
-  p.stream_share = key.share;
-  int rc = DAPQ_OK;
+  all.stream_share = key.share;
+  return for_sequences(s, all, 64 * gs.waves, [&](const ScoreParams& p, int64_t seqs) -> int {
+    const dim3 grid((unsigned)seqs, 1u, (unsigned)heads);
+    int rc = DAPQ_OK;
 #define DAPQ_LAUNCH_F(NRBV, UNITV, SHORTV, STREAMV)                                                                         \
   do {                                                                                                                      \
     if ((rc = set_lds(score_fused_kernel<NRBV, UNITV, SHORTV, STREAMV, kWaveStages>,                                        \
@@ -2098,11 +2133,12 @@ int launch_fused(const dapq_shape* s, const ScorePlan& plan, ScoreParams p, hipS
     else if (hints) DAPQ_LAUNCH_F(NRBV, false, false, true);                  \
     else DAPQ_LAUNCH_F(NRBV, false, false, false);                            \
   } while (0)
-  DAPQ_BY_ROW_BLOCKS(plan.row_blocks, DAPQ_LAUNCH_F_FORM);
+    DAPQ_BY_ROW_BLOCKS(plan.row_blocks, DAPQ_LAUNCH_F_FORM);
 #undef DAPQ_LAUNCH_F_FORM
 #undef DAPQ_LAUNCH_F
-  DAPQ_HIP_LAUNCH_CHECK("score_fused_kernel");
-  return DAPQ_OK;
+    DAPQ_HIP_LAUNCH_CHECK("score_fused_kernel");
+    return DAPQ_OK;
+  });
 }
 
 // Whether the calls of a shape run in score_short_kernel (the same line for the call of both passes and for the separate ones, whose bits agree).
@@ -2127,25 +2163,27 @@ bool short_call(const dapq_shape* s, const ScorePlan& plan) {
   if (heads <= 512 && staged <= kShortMostLds && (subs <= 4 || in_a_row <= 3)) return true;
   return staged + kShortStaticLds <= 80 * 1024 && subs * row_blocks > 1;
 }
-int launch_short(const dapq_shape* s, const ScorePlan& plan, const ScoreParams& p, int mode, hipStream_t stream) {
+int launch_short(const dapq_shape* s, const ScorePlan& plan, const ScoreParams& all, int mode, hipStream_t stream) {
   const int subs = (int)((s->total_tokens / s->batch + 31) / 32), row_blocks = (plan.rows + 31) / 32;
   const bool stage_q = short_lds(subs, row_blocks, true) <= kShortMostLds;
-  const dim3 grid((unsigned)s->batch, 1u, (unsigned)(s->n_layers * s->n_kv_heads));
-  int rc = DAPQ_OK;
+  return for_sequences(s, all, kTileThreads, [&](const ScoreParams& p, int64_t seqs) -> int {
+    const dim3 grid((unsigned)seqs, 1u, (unsigned)(s->n_layers * s->n_kv_heads));
+    int rc = DAPQ_OK;
 #define DAPQ_LAUNCH_SHORT(MODEV, STAGEDV)                                                                                              \
   do {                                                                                                                                 \
     if ((rc = set_lds(score_short_kernel<MODEV, STAGEDV>, kShortMostLds)) != DAPQ_OK) return rc;                                       \
     hipLaunchKernelGGL((score_short_kernel<MODEV, STAGEDV>), grid, dim3(kTileThreads), short_lds(subs, row_blocks, STAGEDV), stream, p); \
   } while (0)
-  if (mode == kShortBoth && stage_q) DAPQ_LAUNCH_SHORT(kShortBoth, true);
-  else if (mode == kShortBoth) DAPQ_LAUNCH_SHORT(kShortBoth, false);
-  else if (mode == kShortStats && stage_q) DAPQ_LAUNCH_SHORT(kShortStats, true);
-  else if (mode == kShortStats) DAPQ_LAUNCH_SHORT(kShortStats, false);
-  else if (stage_q) DAPQ_LAUNCH_SHORT(kShortAccumulate, true);
-  else DAPQ_LAUNCH_SHORT(kShortAccumulate, false);
+    if (mode == kShortBoth && stage_q) DAPQ_LAUNCH_SHORT(kShortBoth, true);
+    else if (mode == kShortBoth) DAPQ_LAUNCH_SHORT(kShortBoth, false);
+    else if (mode == kShortStats && stage_q) DAPQ_LAUNCH_SHORT(kShortStats, true);
+    else if (mode == kShortStats) DAPQ_LAUNCH_SHORT(kShortStats, false);
+    else if (stage_q) DAPQ_LAUNCH_SHORT(kShortAccumulate, true);
+    else DAPQ_LAUNCH_SHORT(kShortAccumulate, false);
 #undef DAPQ_LAUNCH_SHORT
-  DAPQ_HIP_LAUNCH_CHECK("score_short_kernel");
-  return DAPQ_OK;
+    DAPQ_HIP_LAUNCH_CHECK("score_short_kernel");
+    return DAPQ_OK;
+  });
 }
 
 // Whether pass 2 of the tile form merges the partials itself: the threads of a workgroup can hold every sequence's, and

@@ -344,6 +344,34 @@ def test_small_ragged_scores_in_a_workspace_sized_for_longer_ones(H, rows):
     H.assert_scores_close(S[:1].cpu().numpy(), O.score(q[:1], k[:1], 2, cu), f"rows={rows}")
 
 
+# 2^23 workgroups of 512 threads are the 2^32 threads that an axis of a launch does not hold; as many single waves are 2^26
+@pytest.mark.parametrize("batch,rows", [((1 << 23) + 37, 33), ((1 << 26) + 101, 2)], ids=["one workgroup a sequence", "one wave a sequence"])
+def test_scores_of_very_many_dense_sequences(H, batch, rows):
+    """A key to a sequence, with a channel of its own value, and queries that overlap from sequence to sequence: every score is the number
+    of rows, and every normaliser the logit, of 8 bits times 8 bits.  The second: keys of 17 GB, a workspace of 35 GB."""
+    announce(f"scores of {batch} dense sequences, rows={rows}")
+    seq = torch.arange(batch, device="cuda")
+    value = ((seq * 37) % 251 + 1).to(torch.bfloat16)
+    k = torch.zeros((batch, 128), dtype=torch.bfloat16, device="cuda")
+    k[:, 0] = value
+    q = (torch.arange(batch * 8 + rows * 128, device="cuda") % 253 - 126).to(torch.bfloat16)
+    shape = H.D.make_shape(n_layers=1, batch=batch, n_q_heads=1, n_kv_heads=1, n_pseudo=rows, total_tokens=batch,
+                           k_strides=(0, 0, 0, 128), q_strides=(0, 8, 0, 128), scale=1.0 / 128)
+    ws = torch.empty(H.D.workspace_bytes(shape), dtype=torch.uint8, device="cuda")
+    ws.fill_(0xFF)
+    lse = torch.full((batch, rows), float("nan"), dtype=torch.float32, device="cuda")
+    S, T = (torch.full((batch,), float("nan"), dtype=torch.float32, device="cuda") for _ in range(2))
+    H.D.dapq_score(shape, q, k, S, ws)
+    H.D.dapq_score_stats(shape, q, k, lse, ws)
+    H.D.dapq_score_accumulate(shape, q, k, lse, T, ws)
+    assert torch.equal(S, T) and (S - rows).abs().max() < 1e-3 * rows
+    worst = 0.0
+    for row in range(rows):
+        want = q[row * 128: row * 128 + batch * 8: 8].float() * value.float() * (1.4426950408889634 / 128)
+        worst = max(worst, float((lse[:, row] - want).abs().max()))
+    assert worst < 2e-4
+
+
 def score_values(kind, rng, n):
     x = rng.random(n, dtype=np.float32)
     if kind == "octaves":
