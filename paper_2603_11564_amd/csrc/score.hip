@@ -88,6 +88,8 @@ struct ScoreParams {
 
 
 constexpr int kSubBytes = 32 * kHeadDim * 2;          // one 32-key sub-block
+// Where a running maximum starts.  Not at -inf: the logits of a whole sub-block may be that (masked keys, say), and then add nothing.
+constexpr float kLowest = -FLT_MAX;
 
 // Which (sequence, chunk) a workgroup works on.
 struct Work {
@@ -849,7 +851,7 @@ __device__ __forceinline__ void pass1_piece(const ScoreParams& p, u32x4* ring, i
     advance(last_sub);
   }
 
-  // a sum that is not finite means a logit sat more than ~127 binades above the reference: redo
+  // a sum that is not finite means a logit sat more than ~127 binades above the reference, or that those of the first sub-block are all -inf: redo
   // the piece with a running maximum, one sub-block at a time, straight from memory
   bool bad = false;
 #pragma unroll
@@ -857,7 +859,7 @@ __device__ __forceinline__ void pass1_piece(const ScoreParams& p, u32x4* ring, i
   if (__any(bad ? 1 : 0)) {
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) {
-      ref[rb] = -INFINITY;
+      ref[rb] = kLowest;
       z[rb] = 0.0f;
     }
     for (int sub = first_sub; sub <= last_sub; ++sub) {
@@ -1175,8 +1177,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, 1) void score_fused_kernel(Sco
 }
 
 // The causal block of the pseudo tokens' own keys (Sec. 4.1: they are prefilled in-sequence): a wave scores one block of 32 query rows
-// against the n_pseudo pseudo keys, row i = row % n_pseudo seeing keys 0..i, and folds the result into lse2 in place.  Every row sees
-// key 0, so its running maximum is finite from the first sub-block on.  The four waves of a workgroup have row blocks of the same (sequence,
+// against the n_pseudo pseudo keys, row i = row % n_pseudo seeing keys 0..i, and folds the result into lse2 in place.  The four waves of a workgroup have row blocks of the same (sequence,
 // layer, KV head) and share its keys, which come into LDS in whole rows, a sub-block to a wave; the queries too, or, FRAGS, straight
 // from memory: up to two row blocks, whose loads keep no one waiting and whose LDS would keep other workgroups out.  Up to sixteen waves of
 // a compute unit hide each other's trips to memory.  One launch, us, one wave for up to eight row blocks -> this: 4096 sequences x heads of 128
@@ -1210,7 +1211,7 @@ __global__ __launch_bounds__(64 * kPseudoWaves, 4) void score_pseudo_kernel(Scor
   }
   const int last_key[1] = {rc - quotient(rc, p.inv_n_pseudo) * p.n_pseudo};
   const float old = lse[rc];
-  float ref[1] = {-INFINITY}, z[1] = {0.0f};
+  float ref[1] = {kLowest}, z[1] = {0.0f};
   unsigned voff[4];
   sub_dma_lane_offsets(voff, pp.stride_row, lane);
   const int nsubs = (p.n_pseudo + 31) / 32;
@@ -1233,7 +1234,7 @@ __global__ __launch_bounds__(64 * kPseudoWaves, 4) void score_pseudo_kernel(Scor
   }
   const float zz = z[0] + xhalf(z[0]);
   if (mine && h == 0 && row < p.rows) {
-    const float block = ref[0] + log2f(zz);  // log2 of the block's sum; zz >= 1
+    const float block = ref[0] + log2f(zz);  // log2 of the block's sum; zz >= 1, or 0: the logits that the row sees are all -inf
     const float m = fmaxf(old, block);
     lse[row] = m + log2f(__builtin_amdgcn_exp2f(old - m) + __builtin_amdgcn_exp2f(block - m));
   }
@@ -1375,7 +1376,7 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(!S
     frag_from_q(qf, p, qbase, wave * 32 + n, h);
     tile_wait(0);
     for (int rb = wave; rb < row_blocks; rb += waves) {
-      float ref = -INFINITY, z[2] = {0.0f, 0.0f};
+      float ref = kLowest, z[2] = {0.0f, 0.0f};
 #pragma unroll 1
       for (int half = 0; half < kTileKeys / 64; ++half) {
         f32x16 a[2];
@@ -1401,7 +1402,7 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(!S
         for (int u = 0; u < 2; ++u)
 #pragma unroll
           for (int v = 0; v < 16; ++v) m = fmaxf(m, a[u][v]);
-        const float mnew = fmaxf(ref, max_halves(m) * p.c);  // (finite: the first half has a key)
+        const float mnew = fmaxf(ref, max_halves(m) * p.c);
         const float scale = __builtin_amdgcn_exp2f(ref - mnew);
         z[0] *= scale;
         z[1] *= scale;
@@ -1421,7 +1422,7 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(!S
     const int rb = rb0 + s.rb;
     const bool mine = s.part < s.parts && rb < row_blocks;
     if (rb0 != 0 && mine) frag_from_q(qf, p, qbase, rb * 32 + n, h);
-    float ref = -INFINITY, z[2] = {0.0f, 0.0f};
+    float ref = kLowest, z[2] = {0.0f, 0.0f};
     const int step = U * s.parts;
 #pragma unroll 1
     for (int sub0 = 0; sub0 < s.subs; sub0 += step) {
@@ -1452,7 +1453,7 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(!S
       for (int u = 0; u < U; ++u)
 #pragma unroll
         for (int v = 0; v < 16; ++v) m = fmaxf(m, a[u][v]);
-      const float mnew = fmaxf(ref, max_halves(m) * p.c);  // (finite: the first sub-block has a key)
+      const float mnew = fmaxf(ref, max_halves(m) * p.c);
       const float scale = __builtin_amdgcn_exp2f(ref - mnew);
       z[0] *= scale;
       z[1] *= scale;
@@ -1702,7 +1703,7 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(4)
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
   } else {
-    float ref = -FLT_MAX, z[2] = {0.0f, 0.0f};  // (not -inf: the logits of a whole sub-block may be, and add nothing then)
+    float ref = kLowest, z[2] = {0.0f, 0.0f};
 #pragma unroll 1
     for (int sub0 = 0; sub0 < s.subs; sub0 += s.parts) {
       tile_wait(s.subs - sub0 - s.parts > 0 ? s.subs - sub0 - s.parts : 0);

@@ -536,6 +536,59 @@ def test_short_prompts_with_masked_keys(H, length, rows, masked):
     assert np.abs(prob.stats().cpu().numpy() - oracle_lse2(q, k, 2, cu)).max() < 2e-4
 
 
+# the same in the other forms: tiles of one sub-block, of several with a part to each, two at a time and several times two, with the queries straight
+# from memory; the waves of a dense batch in separate launches and in one, with 64 keys too, and of a ragged batch; a whole tile, chunk or prompt
+@pytest.mark.parametrize("rows,lens,layers,ragged,masked", [
+    (250, [1024], 1, False, [(0, 32), (100, 170)]), (16, [5000], 1, False, [(0, 32), (128, 320), (4990, 5000)]),
+    (128, [5000], 1, False, [(64, 96), (200, 500)]), (250, [16384], 1, False, [(0, 64), (256, 352), (1024, 1300)]),
+    (250, [5000], 8, False, [(0, 64), (1000, 1500)]), (40, [513], 1, False, [(0, 40)]), (60, [1000, 70, 33], 2, True, [(0, 64), (1000, 1070)]),
+    (250, [3001], 64, False, [(0, 32), (400, 1000), (2990, 3001)]), (128, [1500] * 3, 100, False, [(0, 40), (700, 1600), (3000, 4500)]),
+    (256, [64], 300, False, [(0, 32)]), (33, [700, 0, 33, 1500], 1000, True, [(0, 32), (700, 1100)]),
+    (250, [211] * 20 + [1500], 100, True, [(0, 33), (211, 422), (4220, 4900)])])
+def test_masked_keys(H, rows, lens, layers, ragged, masked):
+    """As above, in every layer and from the two separate entry points (layer strides of 0); a prompt of masked keys alone has scores of 0."""
+    announce(f"masked keys {masked} of {layers} x {lens}, rows={rows}")
+    q, k, v, cu = problem_bits(rows, 1, lens, 2, 2, rows)
+    q[..., 0] = W.to_bf16_bits(np.full(q.shape[:-1], 2.0, dtype=np.float32))
+    hidden = np.zeros(int(cu[-1]), dtype=bool)
+    for first, end in masked:
+        hidden[first:end] = True
+    k[0, hidden] = 0
+    k[0, hidden, :, 0] = 0xFF7F
+    prob = H.Problem(q, k, v, 2, cu if ragged else None, "thd")
+    tokens, batch = int(cu[-1]), len(lens)
+    shape = H.D.make_shape(n_layers=layers, batch=batch, n_q_heads=2, n_kv_heads=2, n_pseudo=rows, total_tokens=tokens, cu_seqlens=prob.cu,
+                           k_strides=(0, 0, 128, 256), q_strides=(0, 2 * rows * 128, rows * 128, 128), scale=128 ** -0.5)
+    ws = torch.full((H.D.workspace_bytes(shape),), 0xA5, dtype=torch.uint8, device="cuda")
+    S, T = (torch.full((layers, 2, tokens), float("nan"), dtype=torch.float32, device="cuda") for _ in range(2))
+    lse = torch.full((layers, batch, 2, rows), float("nan"), dtype=torch.float32, device="cuda")
+    H.D.dapq_score(shape, prob.q, prob.k, S, ws)
+    H.D.dapq_score_stats(shape, prob.q, prob.k, lse, ws)
+    H.D.dapq_score_accumulate(shape, prob.q, prob.k, lse, T, ws)
+    assert torch.equal(S, T) and torch.equal(S, S[:1].expand_as(S)) and torch.equal(lse, lse[:1].expand_as(lse))
+    S, lse, logs = S[0].cpu().numpy(), lse[0].cpu().numpy(), oracle_lse2(q, k, 2, cu)[0]
+    assert not S[:, hidden].any()
+    for b in range(batch):
+        here = slice(int(cu[b]), int(cu[b + 1]))
+        if not hidden[here].all():
+            H.assert_scores_close(S[None, :, here], O.score(q[:, b:b + 1], k[:, here], 2), f"sequence {b} of {lens}, rows={rows}")
+            assert np.abs(lse[b] - logs[b]).max() < 2e-4
+
+
+# the pseudo tokens' own block: the only key that the first row sees, a sub-block, the last keys
+@pytest.mark.parametrize("rows,masked", [(20, (0, 1)), (40, (0, 33)), (130, (0, 40)), (64, (50, 64))])
+def test_masked_pseudo_keys(H, rows, masked):
+    """The oracle's scores over the extended sequence within 1e-3."""
+    announce(f"masked pseudo keys {masked}, rows={rows}")
+    q, k, v, cu = problem_bits(rows, 1, [300], 2, 2, rows)
+    q[..., 0] = W.to_bf16_bits(np.full(q.shape[:-1], 2.0, dtype=np.float32))
+    kp = problem_bits(rows + 1, 1, [1], 2, 2, rows)[0]
+    kp[:, :, :, masked[0]:masked[1]] = 0
+    kp[:, :, :, masked[0]:masked[1], 0] = 0xFF7F
+    S = H.Problem(q, k, v, 2, None, "thd").score_extended(kp)
+    H.assert_scores_close(S.cpu().numpy(), O.score(q, k, 2, cu, None, kp), f"masked pseudo keys, rows={rows}")
+
+
 @pytest.mark.parametrize("rows", [33, 96, 128, 160, 192, 224, 250])
 @pytest.mark.parametrize("layers,batch,length", [(160, 2, 700), (100, 3, 1500), (40, 5, 3000)])
 def test_one_or_two_chunks_in_one_kernel(H, layers, batch, length, rows):
