@@ -103,7 +103,7 @@ def load_library():
     try:
         from . import _native as native
     except ImportError as e:
-        raise ImportError(f"the extension module {_PKG}/_native.so is not built for this Python; run "
+        raise ImportError(f"the extension module {_PKG}/_native is not built for this Python; run "
                           "`python -m paper_2603_11564_amd.build` (there is no fallback path)") from e
     native.bind({name: C.cast(getattr(lib, name), vp).value for name in EXPORTS}, _resolve_current_stream, Shape, Qproj)
     _native = native

@@ -1,5 +1,5 @@
 """Builds libdapq.so (the HIP kernels and their C ABI) for gfx950, in-tree, with hipcc, and the Python extension module
-that calls it (_native.so) with the host compiler."""
+that calls it (_native) with the host compiler."""
 from __future__ import annotations
 
 import os
@@ -15,7 +15,8 @@ LIB = os.path.join(PKG, "libdapq.so")
 # measurement support for `bench.py --ceilings` (stream and instruction-issue probes); not part of the eviction path
 CEILING_LIB = os.path.join(PKG, "libdapq_ceiling.so")
 CEILING_SOURCES = ["ceiling.hip"]
-NATIVE_LIB = os.path.join(PKG, "_native.so")
+# (with the name of this Python's binary interface: another Python does not load it, and says so)
+NATIVE_LIB = os.path.join(PKG, "_native" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 SOURCES = ["common.hip", "rope.hip", "score.hip", "pool.hip", "topk.hip", "gather.hip", "recall.hip", "decode.hip", "qproj.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",
@@ -84,6 +85,9 @@ def build_native() -> str:
                        capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"{cxx} failed on native.cpp:\n{r.stderr[-4000:]}")
+    untagged = os.path.join(PKG, "_native.so")  # (of an earlier build: any Python would load it)
+    if NATIVE_LIB != untagged and os.path.exists(untagged):
+        os.remove(untagged)
     return NATIVE_LIB
 
 

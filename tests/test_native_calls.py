@@ -1,6 +1,10 @@
 """The calls that go through the extension module: each reaches its own function of the library with its arguments in order.  On the host: every
 call is refused by the library's argument checks, whose message names the argument, before anything touches a GPU."""
 import ctypes as C
+import os
+import subprocess
+import sys
+import sysconfig
 
 import pytest
 import torch
@@ -74,3 +78,17 @@ def test_numbers_of_other_kinds_are_converted():
     for theta, pairing in (("-1", 0.0), (torch.tensor(-1.0), "0"), (-1, True)):
         with pytest.raises(D.DapqError, match="finite theta"):
             D.dapq_pseudo_queries(desc(), T, T, T, T, theta, pairing, T, N, 0)
+
+
+def test_extension_module_belongs_to_this_python():
+    """Its file name carries the interpreter's binary interface, and nothing lies beside it that another interpreter would load instead;
+    where there is none the library does not load."""
+    D.load_library()
+    path = sys.modules["paper_2603_11564_amd._native"].__file__
+    suffix = sysconfig.get_config_var("EXT_SUFFIX")
+    assert suffix != ".so" and os.path.basename(path) == "_native" + suffix
+    assert not os.path.exists(os.path.join(os.path.dirname(path), "_native.so"))
+    r = subprocess.run([sys.executable, "-c", "import sys; sys.modules['paper_2603_11564_amd._native'] = None\n"
+                                              "import paper_2603_11564_amd as D; D.load_library()"],
+                       capture_output=True, text=True, cwd=os.path.dirname(os.path.dirname(path)))
+    assert r.returncode == 1 and "is not built for this Python" in r.stderr
