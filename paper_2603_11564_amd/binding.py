@@ -105,7 +105,8 @@ def load_library():
     except ImportError as e:
         raise ImportError(f"the extension module {_PKG}/_native is not built for this Python; run "
                           "`python -m paper_2603_11564_amd.build` (there is no fallback path)") from e
-    native.bind({name: C.cast(getattr(lib, name), vp).value for name in EXPORTS}, _resolve_current_stream, Shape, Qproj)
+    native.bind({name: C.cast(getattr(lib, name), vp).value for name in EXPORTS}, _resolve_current_stream, Shape, Qproj,
+                _through_ctypes)
     _native = native
     _lib = lib
     return lib
@@ -137,6 +138,35 @@ def _resolve_current_stream():
         return lambda: torch.cuda.current_stream().cuda_stream, None
     torch.cuda.current_stream()  # initialises the device the way torch wants it, once
     return raw, device
+
+
+class _RefusedArgument(C.ArgumentError, TypeError):
+    """What ctypes says of an argument that it does not take."""
+
+
+def _through_ctypes(name, *args):
+    """A call with arguments of kinds that the extension module does not convert (it hands them over): ctypes takes or refuses them."""
+    call, given, values, tensor = getattr(load_library(), name), iter(args), [], None
+    for kind in call.argtypes[:-1]:
+        if kind is C.c_size_t:  # (of the workspace before it)
+            values.append(0 if tensor is None else tensor.numel() * tensor.element_size())
+            continue
+        arg = next(given)
+        if kind is C.c_void_p:
+            tensor, arg = arg, _ptr(arg)
+        elif issubclass(kind, C._Pointer):
+            arg = C.byref(arg)
+        values.append(arg)
+    stream = next(given)
+    if stream is None:
+        current, device = _resolve_current_stream()
+        stream = current() if device is None else current(device())
+    elif not isinstance(stream, int):
+        stream = stream.cuda_stream
+    try:
+        return call(*values, stream)
+    except C.ArgumentError as e:
+        raise _RefusedArgument(*e.args) from None
 
 
 def make_shape(*, n_layers, batch, n_q_heads, n_kv_heads, n_pseudo, total_tokens, head_dim=128, cu_seqlens=None,

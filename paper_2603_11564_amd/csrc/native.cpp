@@ -15,6 +15,7 @@ namespace {
 
 PyObject *g_resolver = nullptr, *g_stream = nullptr, *g_device = nullptr;  // see stream_of
 PyTypeObject *g_shape = nullptr, *g_qproj = nullptr;                       // the descriptors' classes
+PyObject* g_other_way = nullptr;                                           // see other_way
 PyObject *g_data_ptr, *g_numel, *g_element_size, *g_cuda_stream;           // interned names
 
 // Every converter returns false with a Python error set.
@@ -88,7 +89,7 @@ bool stream_of(PyObject* s, void** out) {
   Py_DECREF(v);
   return PyErr_Occurred() == nullptr;
 }
-// A copy of a descriptor (a ctypes structure of its own class: what else has as many bytes is refused).
+// A copy of a descriptor (a ctypes structure of its own class).
 PyTypeObject* class_of(const dapq_shape*) { return g_shape; }
 PyTypeObject* class_of(const dapq_qproj*) { return g_qproj; }
 template <typename T>
@@ -135,8 +136,9 @@ constexpr int kCalls = (int)(sizeof(kNames) / sizeof(kNames[0]));
 static_assert(sizeof(Calls) == kCalls * sizeof(void*), "a name for every function");
 Calls g_calls = {};
 
-PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {  // (addresses by name, resolver of the current stream, Shape, Qproj)
-  if (!count_is(n, 4)) return nullptr;
+// (addresses by name, resolver of the current stream, Shape, Qproj, the way through ctypes)
+PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  if (!count_is(n, 5)) return nullptr;
   if (!PyType_Check(a[2]) || !PyType_Check(a[3])) return PyErr_Format(PyExc_TypeError, "classes expected");
   void* at[kCalls];
   for (int i = 0; i < kCalls; ++i) {
@@ -152,9 +154,32 @@ PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {  // (addresses by 
   Py_XSETREF(g_shape, reinterpret_cast<PyTypeObject*>(a[2]));
   Py_INCREF(a[3]);
   Py_XSETREF(g_qproj, reinterpret_cast<PyTypeObject*>(a[3]));
+  Py_INCREF(a[4]);
+  Py_XSETREF(g_other_way, a[4]);
   Py_CLEAR(g_stream);
   Py_CLEAR(g_device);
   Py_RETURN_NONE;
+}
+
+// A call with an argument of a kind that is not converted here (a number or an address as a ctypes object, a descriptor with more fields, a handle
+// of None): ctypes takes it, or refuses it.  With another error than a TypeError set, that one stays.
+PyObject* other_way(const char* name, PyObject* const* a, Py_ssize_t n) {
+  if (!PyErr_ExceptionMatches(PyExc_TypeError)) return nullptr;
+  PyErr_Clear();
+  PyObject* all = PyTuple_New(n + 1);
+  PyObject* first = all ? PyUnicode_FromString(name) : nullptr;
+  if (first == nullptr) {
+    Py_XDECREF(all);
+    return nullptr;
+  }
+  PyTuple_SET_ITEM(all, 0, first);
+  for (Py_ssize_t i = 0; i < n; ++i) {
+    Py_INCREF(a[i]);
+    PyTuple_SET_ITEM(all, i + 1, a[i]);
+  }
+  PyObject* rc = g_other_way ? PyObject_CallObject(g_other_way, all) : PyErr_Format(PyExc_RuntimeError, "not bound to the library");
+  Py_DECREF(all);
+  return rc;
 }
 
 // The call itself, without the interpreter's lock (a full queue makes a launch wait); its return code as a Python number.
@@ -180,7 +205,7 @@ PyObject* without_lock(F call) {
 
 PyObject* rope_apply(PyObject*, PyObject* const* a, Py_ssize_t n) {
   ARGS(11);
-  if (!(P(0) && P(1) && P(2) && I(3) && I(4) && I(5) && I(6) && I(7) && I(9) && stream_of(a[10], &p[10]))) return nullptr;
+  if (!(P(0) && P(1) && P(2) && I(3) && I(4) && I(5) && I(6) && I(7) && I(9) && stream_of(a[10], &p[10]))) return other_way("dapq_rope_apply", a, n);
   const double theta = PyFloat_AsDouble(a[8]);
   if (PyErr_Occurred()) return nullptr;
   return without_lock([&] { return g_calls.rope_apply(p[0], p[1], IP(2), x[3], I32(4), I32(5), x[6], x[7], theta, I32(9), p[10]); });
@@ -189,46 +214,46 @@ PyObject* score(PyObject*, PyObject* const* a, Py_ssize_t n) {
   ARGS(6);
   dapq_shape s;
   size_t bytes;
-  if (!(struct_of(a[0], &s) && P(1) && P(2) && P(3) && P(4) && bytes_of(a[4], &bytes) && stream_of(a[5], &p[5]))) return nullptr;
+  if (!(struct_of(a[0], &s) && P(1) && P(2) && P(3) && P(4) && bytes_of(a[4], &bytes) && stream_of(a[5], &p[5]))) return other_way("dapq_score", a, n);
   return without_lock([&] { return g_calls.score(&s, p[1], p[2], FP(3), p[4], bytes, p[5]); });
 }
 PyObject* score_static(PyObject*, PyObject* const* a, Py_ssize_t n) {
   ARGS(5);
   dapq_shape s;
-  if (!(struct_of(a[0], &s) && P(1) && P(2) && P(3) && stream_of(a[4], &p[4]))) return nullptr;
+  if (!(struct_of(a[0], &s) && P(1) && P(2) && P(3) && stream_of(a[4], &p[4]))) return other_way("dapq_score_static", a, n);
   return without_lock([&] { return g_calls.score_static(&s, p[1], p[2], FP(3), p[4]); });
 }
 PyObject* score_stats(PyObject*, PyObject* const* a, Py_ssize_t n) {
   ARGS(6);
   dapq_shape s;
   size_t bytes;
-  if (!(struct_of(a[0], &s) && P(1) && P(2) && P(3) && P(4) && bytes_of(a[4], &bytes) && stream_of(a[5], &p[5]))) return nullptr;
+  if (!(struct_of(a[0], &s) && P(1) && P(2) && P(3) && P(4) && bytes_of(a[4], &bytes) && stream_of(a[5], &p[5]))) return other_way("dapq_score_stats", a, n);
   return without_lock([&] { return g_calls.score_stats(&s, p[1], p[2], FP(3), p[4], bytes, p[5]); });
 }
 PyObject* score_accumulate(PyObject*, PyObject* const* a, Py_ssize_t n) {
   ARGS(7);
   dapq_shape s;
   size_t bytes;
-  if (!(struct_of(a[0], &s) && P(1) && P(2) && P(3) && P(4) && P(5) && bytes_of(a[5], &bytes) && stream_of(a[6], &p[6]))) return nullptr;
+  if (!(struct_of(a[0], &s) && P(1) && P(2) && P(3) && P(4) && P(5) && bytes_of(a[5], &bytes) && stream_of(a[6], &p[6]))) return other_way("dapq_score_accumulate", a, n);
   return without_lock([&] { return g_calls.score_accumulate(&s, p[1], p[2], FP(3), FP(4), p[5], bytes, p[6]); });
 }
 PyObject* score_stats_extend(PyObject*, PyObject* const* a, Py_ssize_t n) {
   ARGS(9);
   dapq_shape s;
-  if (!(struct_of(a[0], &s) && P(1) && P(2) && I(3) && I(4) && I(5) && I(6) && P(7) && stream_of(a[8], &p[8]))) return nullptr;
+  if (!(struct_of(a[0], &s) && P(1) && P(2) && I(3) && I(4) && I(5) && I(6) && P(7) && stream_of(a[8], &p[8]))) return other_way("dapq_score_stats_extend", a, n);
   return without_lock([&] { return g_calls.score_stats_extend(&s, p[1], p[2], x[3], x[4], x[5], x[6], FP(7), p[8]); });
 }
 PyObject* pool(PyObject*, PyObject* const* a, Py_ssize_t n) {
   ARGS(5);
   dapq_shape s;
-  if (!(struct_of(a[0], &s) && P(1) && P(2) && I(3) && stream_of(a[4], &p[4]))) return nullptr;
+  if (!(struct_of(a[0], &s) && P(1) && P(2) && I(3) && stream_of(a[4], &p[4]))) return other_way("dapq_pool", a, n);
   return without_lock([&] { return g_calls.pool(&s, FP(1), FP(2), I32(3), p[4]); });
 }
 PyObject* topk(PyObject*, PyObject* const* a, Py_ssize_t n) {
   ARGS(8);
   dapq_shape s;
   size_t bytes;
-  if (!(struct_of(a[0], &s) && P(1) && I(2) && P(3) && P(4) && P(5) && P(6) && bytes_of(a[6], &bytes) && stream_of(a[7], &p[7]))) return nullptr;
+  if (!(struct_of(a[0], &s) && P(1) && I(2) && P(3) && P(4) && P(5) && P(6) && bytes_of(a[6], &bytes) && stream_of(a[7], &p[7]))) return other_way("dapq_topk", a, n);
   return without_lock([&] { return g_calls.topk(&s, FP(1), I32(2), IP(3), IP(4), IP(5), p[6], bytes, p[7]); });
 }
 PyObject* pool_topk(PyObject*, PyObject* const* a, Py_ssize_t n) {
@@ -236,31 +261,31 @@ PyObject* pool_topk(PyObject*, PyObject* const* a, Py_ssize_t n) {
   dapq_shape s;
   size_t bytes;
   if (!(struct_of(a[0], &s) && P(1) && I(2) && I(3) && P(4) && P(5) && P(6) && P(7) && P(8) && bytes_of(a[8], &bytes) && stream_of(a[9], &p[9])))
-    return nullptr;
+    return other_way("dapq_pool_topk", a, n);
   return without_lock([&] { return g_calls.pool_topk(&s, FP(1), I32(2), I32(3), IP(4), IP(5), IP(6), FP(7), p[8], bytes, p[9]); });
 }
 PyObject* gather(PyObject*, PyObject* const* a, Py_ssize_t n) {
   ARGS(9);
   dapq_shape s;
-  if (!(struct_of(a[0], &s) && P(1) && P(2) && P(3) && P(4) && I(5) && P(6) && P(7) && stream_of(a[8], &p[8]))) return nullptr;
+  if (!(struct_of(a[0], &s) && P(1) && P(2) && P(3) && P(4) && I(5) && P(6) && P(7) && stream_of(a[8], &p[8]))) return other_way("dapq_gather", a, n);
   return without_lock([&] { return g_calls.gather(&s, p[1], p[2], IP(3), IP(4), I32(5), p[6], p[7], p[8]); });
 }
 PyObject* recall(PyObject*, PyObject* const* a, Py_ssize_t n) {
   ARGS(10);
   dapq_shape s;
-  if (!(struct_of(a[0], &s) && P(1) && P(2) && I(3) && P(4) && P(5) && I(6) && P(7) && P(8) && stream_of(a[9], &p[9]))) return nullptr;
+  if (!(struct_of(a[0], &s) && P(1) && P(2) && I(3) && P(4) && P(5) && I(6) && P(7) && P(8) && stream_of(a[9], &p[9]))) return other_way("dapq_recall", a, n);
   return without_lock([&] { return g_calls.recall(&s, IP(1), IP(2), I32(3), IP(4), IP(5), I32(6), IP(7), FP(8), p[9]); });
 }
 PyObject* decode_attention(PyObject*, PyObject* const* a, Py_ssize_t n) {
   ARGS(8);
   dapq_shape s;
-  if (!(struct_of(a[0], &s) && P(1) && P(2) && P(3) && P(4) && I(5) && P(6) && stream_of(a[7], &p[7]))) return nullptr;
+  if (!(struct_of(a[0], &s) && P(1) && P(2) && P(3) && P(4) && I(5) && P(6) && stream_of(a[7], &p[7]))) return other_way("dapq_decode_attention", a, n);
   return without_lock([&] { return g_calls.decode_attention(&s, p[1], p[2], p[3], IP(4), I32(5), FP(6), p[7]); });
 }
 PyObject* pseudo_tokens(PyObject*, PyObject* const* a, Py_ssize_t n) {
   ARGS(6);
   dapq_shape s;
-  if (!(struct_of(a[0], &s) && I(1) && I(2) && P(3) && P(4) && stream_of(a[5], &p[5]))) return nullptr;
+  if (!(struct_of(a[0], &s) && I(1) && I(2) && P(3) && P(4) && stream_of(a[5], &p[5]))) return other_way("dapq_pseudo_tokens", a, n);
   return without_lock([&] { return g_calls.pseudo_tokens(&s, I32(1), I32(2), IP(3), IP(4), p[5]); });
 }
 PyObject* pseudo_queries(PyObject*, PyObject* const* a, Py_ssize_t n) {
@@ -268,7 +293,7 @@ PyObject* pseudo_queries(PyObject*, PyObject* const* a, Py_ssize_t n) {
   dapq_qproj d;
   size_t bytes;
   if (!(struct_of(a[0], &d) && P(1) && P(2) && P(3) && P(4) && I(6) && P(7) && P(8) && bytes_of(a[8], &bytes) && stream_of(a[9], &p[9])))
-    return nullptr;
+    return other_way("dapq_pseudo_queries", a, n);
   const double theta = PyFloat_AsDouble(a[5]);
   if (PyErr_Occurred()) return nullptr;
   return without_lock([&] { return g_calls.pseudo_queries(&d, p[1], IP(2), p[3], IP(4), theta, I32(6), p[7], p[8], bytes, p[9]); });

@@ -80,6 +80,49 @@ def test_numbers_of_other_kinds_are_converted():
             D.dapq_pseudo_queries(desc(), T, T, T, T, theta, pairing, T, N, 0)
 
 
+class Larger(D.Shape):
+    _fields_ = [("tag", C.c_int64)]
+
+
+class Thing:
+    def __init__(self, **kw):
+        self.__dict__.update(kw)
+
+
+def larger():
+    s = Larger()
+    C.memmove(C.byref(s), C.byref(shape()), C.sizeof(D.Shape))
+    return s
+
+
+@pytest.mark.parametrize("call,message", [
+    (lambda: D.dapq_gather(shape(), T, T, T, T, C.c_int32(-8), T, T, 0), r"budget \(-8\)"),
+    (lambda: D.dapq_gather(shape(), T, T, T, T, Thing(_as_parameter_=-8), T, T, 0), r"budget \(-8\)"),
+    (lambda: D.dapq_gather(larger(), T, T, T, T, -8, T, T, 0), r"budget \(-8\)"),
+    (lambda: D.dapq_gather(shape(), T, T, T, T, -8, T, T, Thing(cuda_stream=None)), r"budget \(-8\)"),
+    (lambda: D.dapq_gather(shape(), T, T, T, T, -8, T, T, Thing(cuda_stream=C.c_void_p(0))), r"budget \(-8\)"),
+    (lambda: D.dapq_gather(shape(), T, T, T, T, 8, T, Thing(data_ptr=lambda: None), 0), "v_out must not be NULL"),
+    (lambda: D.dapq_score(larger(), Thing(data_ptr=lambda: C.c_void_p(4096)), T, N, T, 0), "scores is NULL"),
+    (lambda: D.dapq_score_accumulate(larger(), T, T, T, T, N, 0), "workspace is NULL"),
+    (lambda: D.dapq_score_stats_extend(shape(), T, T, (0, 0, 0, C.c_int64(64)), T, 0), r"kp_stride_row \(64\)"),
+    (lambda: D.dapq_pool_topk(larger(), T, 4, 8, N, T, T, N, 0, N), r"width \(4\)"),
+    (lambda: D.dapq_rope_apply(T, T, T, 4, 1, 128, C.c_int64(-5), 512, 5e5, 0, 0), r"stride_row \(-5\)"),
+    (lambda: D.dapq_pseudo_queries(desc(), T, T, T, T, -1.0, 0, T, Thing(data_ptr=lambda: C.c_void_p(0), numel=lambda: 4, element_size=lambda: 1), 0),
+     "finite theta"),
+])
+def test_arguments_that_ctypes_converts(call, message):
+    """Numbers and addresses as ctypes objects, descriptors with fields of the caller's, handles of None: each reaches the library."""
+    with pytest.raises(D.DapqError, match=message):
+        call()
+
+
+def test_arguments_that_ctypes_refuses():
+    for bad in (lambda: D.dapq_gather(shape(), T, T, T, T, 8.0, T, T, 0), lambda: D.dapq_gather(shape(), T, T, T, T, C.c_int64(8), T, T, 0),
+                lambda: D.dapq_gather(desc(), T, T, T, T, 8, T, T, 0), lambda: D.dapq_score(C.pointer(shape()), T, T, T, T, 0)):
+        with pytest.raises(C.ArgumentError):
+            bad()
+
+
 def test_extension_module_belongs_to_this_python():
     """Its file name carries the interpreter's binary interface, and nothing lies beside it that another interpreter would load instead;
     where there is none the library does not load."""
