@@ -88,7 +88,7 @@ struct ScoreParams {
 
 
 constexpr int kSubBytes = 32 * kHeadDim * 2;          // one 32-key sub-block
-// Where a running maximum starts.  Not at -inf: the logits of a whole sub-block may be that (masked keys, say), and then add nothing.
+// The least that a running maximum is.  Not -inf: the logits of a whole sub-block may be that (masked keys, say), and then add nothing.
 constexpr float kLowest = -FLT_MAX;
 
 // Which (sequence, chunk) a workgroup works on.
@@ -655,7 +655,7 @@ __device__ __forceinline__ void wave_sub_simple(const bf16x8 (&kf)[8], const bf1
       for (int v = 1; v < 16; ++v) m = fmaxf(m, a[v]);
       m = fmaxf(m, xhalf(m)) * c;
       if (SAFE) {
-        const float mnew = fmaxf(ref[rb], m);
+        const float mnew = fmaxf(fmaxf(ref[rb], m), kLowest);
         z[rb] *= __builtin_amdgcn_exp2f(ref[rb] - mnew);
         ref[rb] = mnew;
       } else {
@@ -859,7 +859,7 @@ __device__ __forceinline__ void pass1_piece(const ScoreParams& p, u32x4* ring, i
   if (__any(bad ? 1 : 0)) {
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) {
-      ref[rb] = kLowest;
+      ref[rb] = -INFINITY;
       z[rb] = 0.0f;
     }
     for (int sub = first_sub; sub <= last_sub; ++sub) {
@@ -1211,7 +1211,7 @@ __global__ __launch_bounds__(64 * kPseudoWaves, 4) void score_pseudo_kernel(Scor
   }
   const int last_key[1] = {rc - quotient(rc, p.inv_n_pseudo) * p.n_pseudo};
   const float old = lse[rc];
-  float ref[1] = {kLowest}, z[1] = {0.0f};
+  float ref[1] = {-INFINITY}, z[1] = {0.0f};
   unsigned voff[4];
   sub_dma_lane_offsets(voff, pp.stride_row, lane);
   const int nsubs = (p.n_pseudo + 31) / 32;
