@@ -11,6 +11,7 @@ from paper_2603_11564_amd import build
 
 
 LDS_BYTES = {}  # of a kernel, without what its launch adds
+REGISTERS = {}  # vector and accumulation registers of a kernel
 
 
 def compile_device(src, out):
@@ -21,10 +22,12 @@ def compile_device(src, out):
     assert r.returncode == 0, r.stderr[-4000:]
     functions, current, spills, kernel = {}, None, {}, None
     for line in open(out):
-        entry = re.match(r"\s+\.(symbol|vgpr_spill_count):\s+(\S+)", line)    # of the kernel descriptors at the end
+        entry = re.match(r"\s+\.(symbol|vgpr_count|vgpr_spill_count):\s+(\S+)", line)    # of the kernel descriptors at the end
         if entry and entry.group(1) == "symbol":
             kernel = entry.group(2)
             LDS_BYTES[kernel] = lds
+        elif entry and entry.group(1) == "vgpr_count":
+            REGISTERS[kernel] = int(entry.group(2))
         elif entry:
             spills[kernel] = int(entry.group(2))
         size = re.match(r"\s+\.group_segment_fixed_size:\s+(\d+)", line)     # (stands before the symbol)
@@ -107,6 +110,13 @@ def test_no_kernel_spills_vector_registers(units):
     spills = {f"{src}: {name}": n for src, (_, kernels) in units.items() for name, n in kernels.items()}
     assert len(spills) > 40 and any("score_wave_pass1_kernel" in name for name in spills)
     assert not {name: n for name, n in spills.items() if n}
+
+
+def test_waves_of_a_score_walk_have_a_simd_to_themselves(units):
+    """A SIMD has 512 registers: two waves fit one from 256 down, and would sit there while other SIMDs have none."""
+    walks = {name: n for name, n in REGISTERS.items() if re.search(r"score_(wave_pass[12]|fused)_kernel", name)}
+    assert len(walks) > 60 and any("score_fused_kernelILi2E" in name for name in walks)
+    assert not {name: n for name, n in walks.items() if n <= 256}
 
 
 def test_four_workgroups_of_a_large_tile_call_fit_a_compute_unit(units):
