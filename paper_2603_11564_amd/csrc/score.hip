@@ -1650,8 +1650,8 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(!S
 // LDS once, in whole rows; both passes run out of it in one launch.  A wave works on one row block and its share of the sub-blocks, as in the
 // tile form.  The waves of score_fused_kernel, one to 128 keys, each take in all the queries, and a head of 200 keys has two of them: what bounds
 // calls of up to a few heads to a compute unit is that start and a wave's 32 units in a row (short_call has figures).
-// MODE: both passes, or the first (lse2 out) or the second (lse2 in) alone, with the same bits.  STAGED: the queries through LDS too, which
-// together with more than 256 keys they exceed.
+// MODE: both passes, or the first (lse2 out) or the second (lse2 in) alone, with the same bits.  STAGED: the queries through LDS too, which holds
+// them beside all 512 keys up to two row blocks, 480 with three, 448 with four, 416, 384 and 352 with five to seven and 320 with eight.
 // ---------------------------------------------------------------------------------------------
 constexpr int kShortKeys = 512, kShortRows = 256;
 enum { kShortBoth = 0, kShortStats = 1, kShortAccumulate = 2 };
@@ -1969,13 +1969,18 @@ bool two_at_a_time(const ScorePlan& plan) {
     }                                          \
   } while (0)
 
-// Whether the waves of a dense launch start with the queries as fragments (SHORT) although they are five row blocks or more.  All keys of
+// Whether the waves of a dense launch start with the queries as fragments (SHORT) although they are six row blocks or more.  All keys of
 // a chunk of a few sub-blocks fit the ring at once; they and fragments arrive in one trip to memory, and behind queries that go through the
 // ring they wait for two or three.  It is the shorter start where the waves of a compute unit are workgroups of their own (side by side in
 // one, their many loads set the pace: 32 prompts x heads of 512 keys, 256 rows 30.2 us through the ring, 36.7), in one kernel up to some
-// eight rounds of waves.  Ring -> fragments, us, dapq_score with inputs in the caches / out of memory: 4096 prompts x heads of 64 keys, 256
-// rows 90.6 / 92.8 -> 82.3 / 84.1; 8192, 192 rows 131.5 / 131.8 -> 128.3 / 126.9 (16384 of 32 keys, 256 rows 232.8 -> 257.7); the two
-// separate calls, 8192, 192 rows, out of memory 220 -> 210.  (Three and four row blocks with as few keys are all score_short_kernel's.)
+// eight rounds of waves.  (Three to five row blocks with as few keys are all score_short_kernel's, as are up to 512 heads.)  Ring -> fragments, us,
+// dapq_score with inputs in the caches / out of memory, by workgroups:
+//                       600                    1024                   4096                    8192                    12288                   32768
+//   192 rows, 128 keys  22.6/22.5 -> 21.7/23.5  27.9/28.9 -> 24.6/28.9  100.7/101.1 -> 95.7/99.3  190.5/184.6 -> 189.1/183.3  277.7/265.9 -> 285.1/269.8  677/670 -> 712/704
+//   256 rows, 64 keys   19.5/21.1 -> 18.8/21.7  26.7/30.7 -> 24.0/27.5  92.6/93.5 -> 85.7/87.3    169.0/162.1 -> 167.2/156.8  238.3/230.1 -> 247.9/239.7  570/553 -> 639/622
+// (224 rows, 70 and 128 keys, and 256 rows, 96 and 128 keys, alike.)  Stats and accumulate alone, an odd number of chunks: from a wave per SIMD on 0.87
+// to 1.01 of the time (2056 of 256 rows, 64 keys 46.9 -> 40.9, 42.8 -> 41.0; 2056 of 768 rows, 128 keys 138.9 -> 129.4, 145.7 -> 136.4; 16392 of 192 rows,
+// 128 keys 295 -> 286, 290 -> 281), with fewer (513 to 1023 of up to 256 rows) 1.02 to 1.11 (600 of 256 rows, 128 keys 21.3 -> 22.9, 17.4 -> 19.1).
 bool few_keys(const dapq_shape* s, const ScorePlan& plan, const GroupShape& gs) {
   return plan.segments == 0 && gs.waves == 1 && s->total_tokens / s->batch <= kMinChunkKeys;
 }
@@ -2003,7 +2008,7 @@ int launch_wave_pass1(const dapq_shape* s, const ScorePlan& plan, ScoreParams al
     else if (plan.segments > 0) DAPQ_LAUNCH_W1(NRBV, true, true, false, false);        \
     else if (plan.unit_sums && hints) DAPQ_LAUNCH_W1(NRBV, false, true, false, true);  \
     else if (plan.unit_sums) DAPQ_LAUNCH_W1(NRBV, false, true, false, false);          \
-    else if (few && NRBV > 4) DAPQ_LAUNCH_W1(NRBV, false, false, (NRBV > 4), false);   \
+    else if (few && NRBV > 5) DAPQ_LAUNCH_W1(NRBV, false, false, (NRBV > 5), false);   \
     else if (hints) DAPQ_LAUNCH_W1(NRBV, false, false, false, true);                   \
     else DAPQ_LAUNCH_W1(NRBV, false, false, false, false);                             \
   } while (0)
@@ -2060,7 +2065,7 @@ int launch_wave_pass2(const dapq_shape* s, const ScorePlan& plan, ScoreParams al
   do {                                                                          \
     if (plan.segments > 0 && hints) DAPQ_LAUNCH_W2(NRBV, true, false, true);    \
     else if (plan.segments > 0) DAPQ_LAUNCH_W2(NRBV, true, false, false);       \
-    else if (few && NRBV > 4) DAPQ_LAUNCH_W2(NRBV, false, (NRBV > 4), false);   \
+    else if (few && NRBV > 5) DAPQ_LAUNCH_W2(NRBV, false, (NRBV > 5), false);   \
     else if (hints) DAPQ_LAUNCH_W2(NRBV, false, false, true);                   \
     else DAPQ_LAUNCH_W2(NRBV, false, false, false);                             \
   } while (0)
@@ -2130,7 +2135,7 @@ int launch_fused(const dapq_shape* s, const ScorePlan& plan, ScoreParams all, hi
   do {                                                                        \
     if (plan.unit_sums && hints) DAPQ_LAUNCH_F(NRBV, true, false, true);      \
     else if (plan.unit_sums) DAPQ_LAUNCH_F(NRBV, true, false, false);         \
-    else if (few && NRBV > 4) DAPQ_LAUNCH_F(NRBV, false, (NRBV > 4), false);  \
+    else if (few && NRBV > 5) DAPQ_LAUNCH_F(NRBV, false, (NRBV > 5), false);  \
     else if (hints) DAPQ_LAUNCH_F(NRBV, false, false, true);                  \
     else DAPQ_LAUNCH_F(NRBV, false, false, false);                            \
   } while (0)
@@ -2147,13 +2152,16 @@ int launch_fused(const dapq_shape* s, const ScorePlan& plan, ScoreParams all, hi
 // that the waves of score_fused_kernel take four at a time.  8 KV heads a layer, us, waves -> this, dapq_score (stats, accumulate):
 //   up to 256 heads    256 rows, 128 keys, 8 heads 19.5 -> 8.3 (14.4 -> 6.2, 11.5 -> 5.5), 256 heads 20.8 -> 10.9; 384 keys, 256 heads 26.0 -> 22.6
 //                      128 rows, 256 keys, 8 heads 13.4 -> 8.5, 256 heads 15.3 -> 10.7; 64 rows, 512 keys, 256 heads 17.1 -> 12.8; 32 rows 16.0 -> 9.7;
-//                      a wave with sixteen sub-blocks: 256 rows, 512 keys, 256 heads 28.4 -> 27.9 (19.9 -> 19.9, 17.4 -> 18.7), 192 rows 24.7 -> 26.6
-//   512 heads          256 rows, 128 keys 25.1 -> 20.3 (19.6 -> 15.6, 16.4 -> 15.0), 200 keys 27.9 -> 28.1; 64 rows, 384 keys 20.8 -> 18.8 (16.9 ->
-//                      15.2, 14.4 -> 14.7); 128 rows, 256 keys 20.3 -> 19.5 (16.7 -> 15.1, 14.1 -> 14.8)
-//   (1070 calls of 1 to 8192 heads, drawn: 0.63 of the time in the geometric mean, stats 0.56, accumulate 0.66; row blocks that leave waves idle lose
-//   with long prompts: 160 rows, 384 keys 16.4 -> 17.9, 96 rows, 448 keys 14.8 -> 12.3 (accumulate 7.2 -> 7.7): at most twice as many in a row)
+//                      left to the waves, a wave with sixteen sub-blocks: 256 rows, 512 keys, 256 heads 28.4 -> 27.9 (19.9 -> 19.9, 17.4 -> 18.7),
+//                      192 rows 24.7 -> 26.6; and row blocks that leave waves idle over long prompts (at most twice as many sub-blocks in a row):
+//                      160 rows, 384 keys 16.4 -> 17.9, 96 rows, 448 keys 14.8 -> 12.3 (accumulate 7.2 -> 7.7)
+//   512 heads          256 rows, 128 keys 25.1 -> 20.3 (19.6 -> 15.6, 16.4 -> 15.0); 64 rows, 384 keys 19.8 -> 18.7 (16.7 -> 15.0, 14.1 -> 14.4: the one
+//                      call of the three that loses at all); left to the waves: 256 rows, 200 keys 27.9 -> 28.1, 128 rows, 256 keys 20.3 -> 19.5 (16.7 -> 15.1,
+//                      14.1 -> 14.8)
 //   more, two to a unit     128 rows, 128 keys, 1024 heads 22.4 -> 17.2, 4096 77.3 -> 61.1; 64 rows, 200 keys 22.6 -> 17.8 and 78.7 -> 63.3; 32 rows, 256
-//                      keys 23.6 -> 15.1 and 85.5 -> 56.2; one to a unit: 64 rows, 256 keys, 1024 heads 24.6 -> 26.7, 256 rows, 64 keys 25.4 -> 27.1
+//                      keys 23.6 -> 15.1 and 85.5 -> 56.2; left to the waves, one to a unit: 64 rows, 256 keys, 1024 heads 24.6 -> 26.7, 256 rows, 64 keys
+//                      25.4 -> 27.1
+// 300 drawn calls of 8 to 8192 heads that it takes: 0.65 of the time in the geometric mean, 1.01 at most (stats 0.55, 1.00; accumulate 0.66, 1.02).
 bool short_call(const dapq_shape* s, const ScorePlan& plan) {
   if (plan.tile || s->cu_seqlens != nullptr || plan.rows > kShortRows || s->total_tokens < s->batch || s->total_tokens / s->batch > kShortKeys) return false;
   const int subs = (int)((s->total_tokens / s->batch + 31) / 32), row_blocks = (plan.rows + 31) / 32;
