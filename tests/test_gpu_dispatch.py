@@ -499,10 +499,20 @@ def test_equal_chunks_of_dense_batches(H, layers, batch, length, rows):
     assert np.abs(lse[:1].cpu().numpy() - oracle_lse2(q, k, 2, cu)).max() < 2e-4
 
 
-# one chunk of at most 128 keys: up to 8192 of them the queries come as fragments, with more through the ring; from 129 keys on it does not hold
+# one chunk of at most 128 keys, or of 129: on both sides of the kernel for short prompts, which has nearly all of these, and of the waves
 @pytest.mark.parametrize("rows", [64, 65, 128, 129, 192, 193, 256])
 @pytest.mark.parametrize("layers,batch,length", [(2, 3, 1), (3, 1, 33), (1, 2, 127), (2, 2, 128), (2, 2, 129), (1365, 3, 40), (1366, 3, 40)])
 def test_chunks_of_few_keys(H, layers, batch, length, rows):
+    """As above."""
+    test_equal_chunks_of_dense_batches(H, layers, batch, length, rows)
+
+
+# what it leaves to waves that start with fragments: six to eight row blocks, more than 512 heads, an odd number of chunks (a wave to a workgroup);
+# both passes in one kernel up to 8192 of them, with more through the ring; three row groups, in separate launches
+@pytest.mark.parametrize("layers,batch,length,rows", [
+    (87, 3, 128, 192), (87, 3, 97, 161), (1366, 3, 128, 192), (87, 3, 128, 224), (87, 3, 65, 193), (1366, 3, 65, 224), (87, 3, 128, 256),
+    (87, 3, 33, 256), (87, 3, 64, 225), (1366, 3, 64, 256), (172, 3, 128, 576), (172, 3, 64, 672), (172, 3, 33, 768), (172, 3, 1, 600)])
+def test_few_keys_in_waves(H, layers, batch, length, rows):
     """As above."""
     test_equal_chunks_of_dense_batches(H, layers, batch, length, rows)
 
