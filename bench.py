@@ -35,8 +35,8 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0
 # by what the same counter reads for kernels of known size in the same run (the 2 GiB read-stream probe; the
 # fp32 -> bf16 conversion of the input generator: 128 MiB read, 64 MiB written); profiles/score_c2_hbm_traffic.md.
 MEASURED_TRAFFIC_BYTES = {    # (workload, N, kernel)
-    ("C2", 64, "score"): 4.330e9,         # both passes in one kernel: 4.296 GB fetched (K twice, Q once) + 32 MiB written
-    ("C2", 32, "score"): 4.319e9,         # 4.286 GB fetched + 32 MiB written
+    ("C2", 64, "score"): 4.329e9,         # both passes in one kernel: 4.296 GB fetched (K twice, Q once) + 32 MiB written
+    ("C2", 32, "score"): 4.319e9,         # 4.285 GB fetched + 32 MiB written
     ("C2", 64, "score_pass2"): 2.199e9,   # 2.165 GB fetched (keys + the pseudo queries once per head) + 32 MiB written
     ("C2", 64, "score_pass1"): 2.167e9,   # 2.165 GB fetched + 2 MiB of partial row statistics written
     ("C2", 32, "score_pass2"): 2.190e9,   # 2.156 GB fetched + 32 MiB written
@@ -44,7 +44,7 @@ MEASURED_TRAFFIC_BYTES = {    # (workload, N, kernel)
 }
 # Where those figures come from: the profile file and the commit whose score kernels were profiled.  A CPU test
 # (tests/test_bench_host.py) fails when the sources of the score kernels have changed since that commit, i.e. when they are stale.
-TRAFFIC_SOURCE = {"file": "profiles/score_c2_hbm_traffic.md", "commit": "e5f0fe2"}
+TRAFFIC_SOURCE = {"file": "profiles/score_c2_hbm_traffic.md", "commit": "f338f72"}
 
 
 def parse():
