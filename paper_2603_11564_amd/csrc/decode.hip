@@ -395,9 +395,9 @@ int launch_decode_slices(int64_t heads, const DecodeParams& p, hipStream_t strea
   const int64_t rows = heads * p.budget;
   if (heads <= 64 && (rows <= 88 * 1024 || heads <= 24)) return launch_decode<HT, 2, 8, false>(heads, p, stream);
   if (heads <= 128 && (HT == 1 ? rows <= 112 * 1024 || heads <= 48 : heads * rows <= 11 << 20 || heads <= 64)) return launch_decode<HT, 4, 8, false>(heads, p, stream);
-  // From 128 MB of caches on their rows stream, if one sweep reads them: us without -> with hints, 8 KV heads, 983 rows, sequences: 16 (64 MB)
-  // 12.2 -> 14.4, 24 (97 MB) 17.6 -> 18.0, 32 24.4 -> 23.0, 64 44.9 -> 41.3 (6.2 TB/s); 4096 rows: 8 (134 MB) 43.8 -> 41.6, 16 50.7 -> 46.5.
-  // (Smaller ones that come round are found in the memory-side cache.)
+  // From 128 MB of caches on their rows stream, if one sweep reads them: us without -> with hints, 8 KV heads, 983 rows, the same caches again / those
+  // of several layers in turn, as in a model, sequences: 16 (64 MB) 12.4 -> 14.6 / 16.7 -> 15.5, 24 (97 MB) 16.7 -> 16.6 / 20.2 -> 18.5, 32
+  // 21.5 -> 21.3 / 25.4 -> 23.0, 64 40.6 -> 40.9 / 47.4 -> 42.2 (6.1 TB/s).  (Smaller ones that come round at once are found in the memory-side cache.)
   if (p.group <= 4 * HT && rows >= (int64_t)128 * 1000 * 1000 / (2 * kHeadDim * 2)) return launch_decode<HT, 8, 4, true>(heads, p, stream);
   return launch_decode<HT, 8, 4, false>(heads, p, stream);
 }

@@ -6,11 +6,17 @@
 // read and written in full cache lines; a workgroup of 256 threads moves 32 rows of K or of V, two per 16-lane group.
 // Two rows to a group are enough in flight with eight workgroups to a compute unit, and leave the last workgroups of a launch less to do (four and
 // one: below).  From 8 MB on the stores carry the non-temporal hint: nobody reads the compact cache before the rest of it is
-// written, and lines that are not kept leave room for reads.  From 192 MB on, where the rows read can't still lie in the 256 MB
+// written (a model's weights pass through the caches in between), and lines that are not kept leave room for reads.  From 192 MB on, where the rows read can't still lie in the 256 MB
 // memory-side cache for a second call either, the loads do too; smaller calls find rows there that the score passes or the caller brought in.
 // Us, four rows to a group without hints -> two without, two with hinted stores, two with both (one with both), MB read and written:
 //   2 MB    2.37 -> 1.94, 1.94, 1.94 (1.98)       8   2.90 -> 2.54, 2.42, 2.75 (3.25)      32    6.6 -> 6.4, 5.9, 7.3 (7.7)
 //   129    27.9 -> 26.4, 21.3, 22.7 (23.2)      258  52.5 -> 51.1, 44.8, 42.5 (43.4)      515  104.9 -> 102.9, 92.8, 84.2 (87.3; 6.1 TB/s)
+// Those are calls again and again.  Four rows without hints -> these, with a selection and over three sets of buffers in turn: 16 MB 10.8 -> 9.9, 64 23.5 ->
+// 21.9, 134 43.0 -> 37.2, 258 67.4 -> 57.4, 515 115.4 -> 99.2.  Behind score passes a call gains nothing: what it writes goes out during the next
+// kernels without the hint (258 MB 48.0 -> 49.2, 64 16.7 -> 17.2; with the decode steps of all layers after it, each behind 200 MB of weights, 2275 -> 2271
+// and 578 -> 577).  Decode steps with nothing between read the compact cache from memory and take 10 to 24 % longer (8 layers of 64 MB 62 -> 77, 32 of
+// 134 190 -> 211, 32 of 258 253 -> 303): with stores that only write through L2 they do not (62, 190, 242; the call behind score passes 43.3 at 258 MB),
+// but the calls in turn lose half their gain and more (64 MB 23.3, 134 41.8; 258 64.1 for 60.5).
 #include "dapq_internal.h"
 #include "kernel_args.h"
 

@@ -425,8 +425,10 @@ int launch_qproj_as(const QprojParams& p, hipStream_t stream) {
 }
 
 // Weights of 96 MB and more that one sweep of rows reads stream past the caches; less than that a caller whose weights come round finds in the
-// memory-side cache, and further sweeps find them in L2.  Us without -> with hints, 64 rows: one layer 4096 wide (34 MB) 12.1 -> 13.3; 2 (67 MB)
-// 16.5 -> 18.2; 2 of 5120 (105 MB) 30.8 -> 29.6; 4 of 4096 33.0 -> 30.1; 8 62.5 -> 57.1; 32 200 -> 174 (6.2 TB/s); 256 rows, 8 of 5120 239 -> 279.
+// memory-side cache, and further sweeps find them in L2.  Us without -> with hints, 64 rows, calls that go through 1 GB of a model's weights in turn:
+// one layer 4096 wide (34 MB) 13.8 -> 13.8; 2 (67 MB) 20.8 -> 20.0; 2 of 5120 (105 MB) 32.0 -> 31.8; 4 of 4096 34.1 -> 32.5; 8 66.7 -> 64.5; 32 200 ->
+// 174 (6.2 TB/s); 256 rows, 8 of 5120 239 -> 279.  The same weights again and again, as no model has it: 10.8 -> 12.6, 16.2 -> 19.6, 25.1 -> 31.6,
+// 26.2 -> 32.2.
 template <int FT, int MB, int WAVES>
 int launch_qproj(const QprojParams& p, hipStream_t stream) {
   const double weights = 2.0 * p.n_layers * p.n_features * p.hidden;
