@@ -3,6 +3,8 @@ that calls it (_native) with the host compiler."""
 from __future__ import annotations
 
 import os
+import shlex
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -78,13 +80,14 @@ def build_sanitized(verbose: bool = False) -> str:
 
 
 def build_native() -> str:
-    """The extension module; returns its path."""
-    cxx = os.environ.get("CXX") or "g++"
-    r = subprocess.run([cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-I", os.path.join(ROOT, "include"),
+    """The extension module, by $CXX (a command, with arguments or without), g++ or the clang++ that hipcc runs; returns its path."""
+    clang = os.path.join(os.path.dirname(os.path.dirname(os.path.realpath(shutil.which(_hipcc()) or _hipcc()))), "lib", "llvm", "bin", "clang++")
+    cxx = shlex.split(os.environ.get("CXX", "")) or ["g++" if shutil.which("g++") else clang]
+    r = subprocess.run([*cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-I", os.path.join(ROOT, "include"),
                         "-I", sysconfig.get_paths()["include"], "-DDAPQ_API=", os.path.join(CSRC, "native.cpp"), "-o", NATIVE_LIB],
                        capture_output=True, text=True)
     if r.returncode != 0:
-        raise RuntimeError(f"{cxx} failed on native.cpp:\n{r.stderr[-4000:]}")
+        raise RuntimeError(f"{cxx[0]} failed on native.cpp:\n{r.stderr[-4000:]}")
     untagged = os.path.join(PKG, "_native.so")  # (of an earlier build: any Python would load it)
     if NATIVE_LIB != untagged and os.path.exists(untagged):
         os.remove(untagged)

@@ -135,3 +135,16 @@ def test_extension_module_belongs_to_this_python():
                                               "import paper_2603_11564_amd as D; D.load_library()"],
                        capture_output=True, text=True, cwd=os.path.dirname(os.path.dirname(path)))
     assert r.returncode == 1 and "is not built for this Python" in r.stderr
+
+
+@pytest.mark.parametrize("cxx", ["env g++", "", None])
+def test_extension_module_builds_with_any_compiler_command(cxx, tmp_path, monkeypatch):
+    """With arguments in CXX, without CXX, and (None) where there is no g++."""
+    from paper_2603_11564_amd import build
+    target = str(tmp_path / "module.so")
+    monkeypatch.setattr(build, "NATIVE_LIB", target)
+    monkeypatch.setenv("CXX", cxx or "")
+    if cxx is None:
+        which = build.shutil.which
+        monkeypatch.setattr(build.shutil, "which", lambda name, **kw: None if name == "g++" else which(name, **kw))
+    assert build.build_native() == target and os.path.getsize(target) > 0
